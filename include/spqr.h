@@ -233,9 +233,9 @@ int spqr_gemv(const spqr_matrix_t* A, const uint16_t* x_f16, void* y, int y_dtyp
  * slice), or, for tiles of 16x16, 8x32 (group_axis 1) and 32x8 (group_axis 0)
  * and a batch / layer large enough to pay for it, slices of up to 16: the
  * weights are read once per slice, dequantised to binary16 and multiplied on
- * the matrix cores, then a second kernel adds the outliers.  That path needs
- * device scratch, about (n+1)*32 + (nnz/256 + 2)*64 + splits*16*m*4 (+ 32*n
- * with a permutation) bytes per slice.
+ * the matrix cores, the outliers added in binary32.  That path needs device
+ * scratch, splits*b*m*4 bytes (+ 2*b*n with a permutation) per slice, 16 MB at
+ * most where the columns are split.
  * THIS entry point takes it from the library: one scratch buffer per stream
  * (up to 8 streams per device), kept until the process ends and grown on
  * demand -- growing synchronises the stream and calls hipFree and hipMalloc
@@ -316,8 +316,8 @@ int spqr_gemv_fused(const spqr_matrix_t* const* A, int count, const uint16_t* x_
  * (the q/k/v or gate/up projections of a decoder block at batch b): what
  * spqr_gemv_fused is for one vector.  Same agreement rules (SPQR_ERR_PARAM
  * otherwise), A and Y are HOST arrays.  Where the batch takes the matrix-core
- * path of spqr_gemm_smallbatch, all matrices share one transposition of the
- * batch, one dense launch and one finishing launch per slice of 16 vectors;
+ * path of spqr_gemm_smallbatch, all matrices share one launch for the products
+ * and one for the sums per slice of 16 vectors;
  * otherwise, and whenever `stream` is being captured into a graph, the call is
  * `count` calls of spqr_gemm_smallbatch (b == 1: one spqr_gemv_fused).  Scratch
  * as for spqr_gemm_smallbatch (library-owned; spqr_gemm_fused_ws takes the
@@ -363,8 +363,8 @@ int spqr_gemv_grouped(const spqr_matrix_t* const* A, int count, const uint16_t* 
  *                          batches for any batch it exists for
  *   SPQR_OPT_FORCE_GENERIC 1: every product takes the element-wise fallback
  *                          kernel
- *   SPQR_OPT_BATCH_STEPS   k > 0: the matrix-core path's dense launch gives every
- *                          workgroup min(k, steps) steps of 64 tiles
+ *   SPQR_OPT_BATCH_STEPS   k > 0: the matrix-core path's launch gives every
+ *                          workgroup min(k, units) units of 16 tile columns
  *   SPQR_OPT_DENSE_ROWS    64 or 128: rows per workgroup of the large-batch
  *                          multiply (0: the library's rule)
  *   SPQR_OPT_GEMV_PLAN     16 * P + R > 0: the batch-1 kernel runs with P

@@ -1,5 +1,5 @@
-// Batches above 4 vectors: dense part on the matrix cores, outliers in a finishing kernel; launchers,
-// launch plan and scratch of that path.
+// Batches of 4 to 16 vectors on the matrix cores: one kernel for the dense part and the outliers, one that adds the
+// partial results; launchers, launch plan and scratch of that path.
 #include <hip/hip_runtime.h>
 #include <cstdint>
 #include <cstdlib>
@@ -14,613 +14,586 @@
 namespace spqr {
 
 // ---------------------------------------------------------------------------
-// Batches above 4 on 16x16 tiles: the dense part on the matrix cores (weights
-// stream once for the whole batch), then a finishing kernel that adds the outliers.
+// P[split][b][rows] = X[b][columns of the split] . W_hat[rows][columns of the split]^T in binary32, outliers included.
 //
-// Dense part: P[split][b][rows] = X[b][cols of the split] . dequant(strip)^T in
-// binary32, no outliers.  A workgroup is 4 wavefronts = 4 consecutive strips that
-// walk the same steps of 64 tiles in lock-step, because they share the 16 x 1024
-// piece of X that belongs to the step: it is staged in LDS once per workgroup
-// (prefetched into registers one step ahead).  A lane still fetches one whole
-// tile (same loads, same layout as the GEMV).  An MFMA operand, though, wants
-// 16 rows x 4 columns across the 64 lanes, while here the lanes hold 64 different
-// tiles: so every lane dequantises its tile to binary16 (s_hat*(q - z_hat) evaluated
-// in binary32, one rounding -- the kernel of Sec. 4.2 multiplies 16-bit weights
-// as well) into its wavefront's LDS buffer, a quarter (4 columns) at a time to
-// keep the buffer small enough for two workgroups per CU.  One
-// v_mfma_f32_16x16x32_f16 then sums 8 tiles at once: its K index is (tile, column),
-// A: lane l = row l%16 of tiles 8j + 2(l/16) and the next, B: lane l = batch l%16, the
-// same two tiles' 4 columns of X; D[row][batch] accumulates over the whole column
-// range in 8 registers.
-// Batch rows beyond `batch` repeat the last one and are dropped at the end.
-// The steps of a matrix can be split over gridDim.y workgroups (few strips, many
-// columns); every split writes its own partial result.  Workgroups behind the
-// dense ones (blockIdx.x >= groups) take the long outlier rows, see long_rows_block.
+// Dense part.  A lane owns one whole tile (256 codes in registers, the layout's own unit) and an MFMA's A operand wants
+// 16 different rows of the same columns across 16 lanes.  Lanes 16g .. 16g+15 therefore hold the SAME tile column of 16
+// consecutive strips: row r of the 16 strips is one A operand of v_mfma_f32_16x16x32_f16 straight from the registers
+// the lane dequantised it into (K index = tile column g of 4 and 8 columns inside the tile), and D[r] holds row r of
+// the 16 strips for the 16 vectors of the batch.  No weight passes through LDS, the wavefronts of a workgroup meet
+// only for the outliers and at the end.  Weights are dequantised as in Sec. 4.2's kernel, s_hat * (q - z_hat) in one
+// binary32 FMA, rounded once to binary16; a B operand is 8 consecutive columns of one batch row, 16 bytes from X.
+//
+// A workgroup of 4 wavefronts owns a group of 16 strips and a range of columns, in units of 16 tile columns (4 per
+// wavefront).  Few rows x many columns would leave CUs idle, so gridDim.y splits the columns; every split writes its
+// own partial result (see sum_groups_kernel).
+//
+// Outliers.  The workgroup's piece of the batch passes through LDS transposed, XT[column][16 vectors], at most
+// kChunkCols columns at a time, so an outlier meets its 16 activations in two 16-byte LDS reads.  (From L2 the same
+// 32-byte line costs an L1 look-up per entry, about 10 clocks per entry and CU.)  A row's entries inside the columns
+// of the piece are found by bisection (columns increase inside a row), 16 lanes take a row's entries in turn, rows
+// of more than kLongRow entries in the piece are shared out among the wavefronts, 64 lanes each.  One writer per sum, fixed
+// orders everywhere: results are deterministic.
+//
+// What bounds it (17920 x 6656, 4-bit, 16 vectors, 42 us with the sums): about half of it is vector issue (2.4
+// instructions per weight for the dequantisation, the outliers on top) beside the stream of the weights (14 us at the
+// rate of a copy); the rest is the start (row bounds, XT) and the memory latency that two workgroups per CU leave.
+// Without outliers 28 us.  Before (weights transposed through LDS quarter tile by quarter tile, outliers in a kernel of
+// their own that gathered from L2): 52 us; 8192 x 22016, 3-bit, 73 -> 64 us; three of 6656^2 at 4 vectors 52 -> 48 us.
 // ---------------------------------------------------------------------------
 typedef _Float16 half8_t __attribute__((ext_vector_type(8)));
 typedef float float4_t __attribute__((ext_vector_type(4)));
-constexpr int kMfmaTileStride = 36;          // dwords per tile quarter (16 rows x 8 bytes + 16: spreads the banks)
 
-// Outlier rows longer than `long_row` entries (far longer than the average row), for the batch path.  Such a row
-// would keep the one CU that owns its strip busy long after the others are done (every outlier is an L1 line
-// look-up), so these rows are taken out of the finishing kernel: extra workgroups of the dense kernel's grid (they
-// run beside the dense workgroups and need nothing from them) compute, slice by slice of kLongSlice entries,
-// sum_k val_k * XT[col_k][b] for the 16 vectors
-// into slots[lo / kSlotGrain + k][16] for slice k of the row that starts at entry lo -- a long row has no more
-// slices than multiples of kSlotGrain among its entry indices (ceil(len/512) <= floor(len/256) from len = 256 on),
-// so the slots of different rows never meet and the finishing kernel finds them without a search.
-// Work is shared out by entries, not by rows: workgroup wg of nwg owns the slices that start in its equal share
-// [a, z) of the entry indices, so heavy rows next to each other (or one row of many slices) spread over as many
-// workgroups as their entries fill.  It narrows the rows down to NT around the one that holds entry a by a search
-// all threads take part in (NT probes of the row pointers per round; none for up to NT rows, one for up to NT*NT),
-// then walks the rows from there, NT - 1 at a time, up to the first that starts at or behind z.  A slice is one wavefront's: a lane takes every 64th entry (consecutive lanes read
-// consecutive entries) with its whole 32-byte line of XT, all loads in flight at once; the 16 sums are reduced over
-// the lanes in a fixed order and written by the wavefront itself.  The wavefronts of a workgroup take its slices
-// in turn and meet only where the next rows are fetched.
-constexpr int kLongRowMin = 256, kLongSlice = 512, kSlotGrain = 256;
+constexpr int kUnitTiles = 16;               // tile columns of a unit of the split: one step of 4 for each of 4 wavefronts
+constexpr int kLongRow = 64;                 // entries of a row inside a piece beyond which a whole wavefront takes it
 
-template <int NT>
-__device__ __forceinline__ void long_rows_block(const DevMatrix& A, const uint16_t* __restrict__ XT,
-                                                float* __restrict__ slots, int long_row, int wg, int nwg, uint8_t* smem) {
-  constexpr int EPT = kLongSlice / 64, NW = NT / 64;
-  int* rpl = reinterpret_cast<int*>(smem);                                   // NT row pointers
-  uint32_t* masks = reinterpret_cast<uint32_t*>(smem + 4 * NT);              // 2 per wavefront
-  int* below = reinterpret_cast<int*>(smem + 4 * NT + 8 * NW);               // 1 per wavefront
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int m = A.g.m;
-  const int64_t nnz = A.nnz;
-  const uint32_t zoff = (uint32_t)A.g.n * 32u;                               // the zero line of XT
-  int64_t per = (nnz + nwg - 1) / nwg;
-  if (per < kLongSlice) per = kLongSlice;
-  const int64_t a64 = (int64_t)wg * per;
-  if (a64 >= nnz) return;                                                    // workgroup-uniform
-  const int a = (int)a64, z = (int)(a64 + per < nnz ? a64 + per : nnz);
-  // the last row r with row_ptr[r] <= a lies in [L, H): row_ptr[L] <= a < row_ptr[H] throughout
-  int L = 0, H = m;
-  while (H - L > NT) {                                                       // workgroup-uniform
-    // probe t looks at the end of the t-th of NT parts of the bracket: distinct rows in (L, H], the last is H
-    const int span = H - L;
-    const bool is_below = A.row_ptr[L + (int)(((int64_t)(tid + 1) * span) / NT)] <= a;
-    const uint64_t bal = __builtin_amdgcn_ballot_w64(is_below);
-    if (lane == 0) below[wave] = __builtin_popcountll(bal);
-    __syncthreads();
-    int c = 0;                                                               // probes at or below a: a prefix of them,
+// Rows a lane multiplies: its tile's 8 or 16; a tile of 32 rows is taken as two of 16 (128 accumulators a lane spill), so
+// that the strips of the kernel are 8 or 16 rows in every format.
+constexpr int lane_rows(int tile_rows) { return tile_rows == 32 ? 16 : tile_rows; }
+
+template <int TR, int TC> struct BatchShape {
+  static constexpr int ROWS = 16 * lane_rows(TR);                    // rows of a group of 16 strips
+  static constexpr int CHUNK = 1536 / (kUnitTiles * TC);             // units per piece of XT
+  static constexpr int COLS = CHUNK * kUnitTiles * TC;
+  static constexpr int SUM = ROWS + 4;                               // floats per vector of a buffer of sums (the 4: banks)
+  static constexpr int XT = (COLS + COLS / 8) * 32;                  // a column's line of 32 bytes, one line free in nine (banks)
+  static constexpr int SLICE = 16 * 20;                              // floats of one row of 16 strips, 16 vectors (20: banks)
+  static constexpr int SUMS = 3 * lane_rows(TR) * SLICE * 4;         // each wavefront sums a quarter of the rows, from three others
+  static constexpr int SHARED = XT > SUMS ? XT : SUMS;               // XT, then the wavefronts' sums
+  static constexpr int LDS = SHARED + SUM * 64 + ROWS * 8;           // + sums of the outliers + row bounds
+  static_assert(2 * LDS <= 160 * 1024, "two workgroups share a CU");
+};
+
+// What a lane holds of its tile: the codes of its rows (a tile of 32 rows: of one half) and the tile's statistics.
+template <int W, int TR, int TC, int AXIS> struct BatchTile {
+  using T = TileRegs<W, TR, TC, AXIS>;
+  static constexpr int KW = T::KW * lane_rows(TR) / TR;
+  uint32_t c[4 * KW];
+  uint32_t s[T::SD];
+};
+
+// `blk` and L (the block and its tiles) are uniform, `l` is the lane's tile in it, `off` the lane's strip's byte offset,
+// `half` (tiles of 32 rows) which rows.
+template <int W, int TR, int TC, int AXIS>
+__device__ __forceinline__ void load_batch_tile(BatchTile<W, TR, TC, AXIS>& t, const uint8_t* blk, int L, uint32_t off,
+                                                uint32_t l, int half) {
+  using B = BatchTile<W, TR, TC, AXIS>;
+  using T = typename B::T;
+  const uint32_t off16 = off + 16u * l, off4 = off + 4u * l;
+  const uint8_t* sb = blk + 16 * T::KW * L;
 #pragma unroll
-    for (int k = 0; k < NW; ++k) c += below[k];                              // never all (row H is above a)
-    __syncthreads();
-    c = min(c, NT - 1);                      // (all only if row_ptr[m] < nnz, a broken descriptor: stay inside the bracket)
-    const int newL = c == 0 ? L : L + (int)(((int64_t)c * span) / NT);
-    H = L + (int)(((int64_t)(c + 1) * span) / NT);
-    L = newL;
+  for (int k = 0; k < T::SWF; ++k) {
+    const u32x4 v = *reinterpret_cast<const u32x4*>(sb + 16 * k * L + off16);
+    t.s[4 * k] = v.x; t.s[4 * k + 1] = v.y; t.s[4 * k + 2] = v.z; t.s[4 * k + 3] = v.w;
   }
-  // The rows from L on, NT - 1 at a time.  The row that holds entry a is among the first H - L <= NT of them; the
-  // rows before it end at or before a and own nothing here.
-  int taken = 0;                                                             // slices of this workgroup so far
-  for (int r0 = L; r0 < m;) {                                                // workgroup-uniform
-    const int nrows = min(NT - 1, m - r0);
-    if (tid <= nrows) rpl[tid] = A.row_ptr[r0 + tid];
-    __syncthreads();
-    const int t1 = min(tid, NT - 2);
-    const bool is_long = tid < nrows && rpl[t1 + 1] - rpl[t1] > long_row && rpl[t1] < z && rpl[t1 + 1] > a;
-    const uint64_t bal = __builtin_amdgcn_ballot_w64(is_long);
-    if (lane == 0) { masks[2 * wave] = (uint32_t)bal; masks[2 * wave + 1] = (uint32_t)(bal >> 32); }
-    __syncthreads();
-    for (int w = 0; w < NW; ++w) {
-      uint64_t mask = (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)masks[2 * w]) |      // no sign extension
-                      ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)masks[2 * w + 1]) << 32);
-      while (mask) {                                                         // workgroup-uniform
-        const int r = 64 * w + __builtin_ctzll(mask);
-        mask &= mask - 1;
-        const int lo = rpl[r], hi = rpl[r + 1];
-        // the row's slices that start in [a, z)
-        const int k0 = lo >= a ? 0 : (a - lo + kLongSlice - 1) / kLongSlice;
-        for (int k = k0; lo + k * kLongSlice < min(hi, z); ++k) {
-          if (taken++ % NW != wave) continue;                                // wavefront-uniform
-          const int e0 = lo + k * kLongSlice;
-          // all of the lane's entries first, then their lines of XT, then the arithmetic: one round trip each
-          uint32_t off[EPT];
-          float val[EPT];
+  const uint8_t* rb = sb + 16 * T::SWF * L;
 #pragma unroll
-          for (int i = 0; i < EPT; ++i) {
-            const int e = e0 + lane + 64 * i;
-            const bool ok = e < hi;
-            off[i] = ok ? (uint32_t)A.col[e] * 32u : zoff;
-            val[i] = ok ? h2f(A.val[e]) : 0.f;
-          }
-          u32x4 x0[EPT], x1[EPT];
+  for (int k = 0; k < T::SR; ++k) t.s[4 * T::SWF + k] = *reinterpret_cast<const uint32_t*>(rb + 4 * k * L + off4);
+  const uint32_t offc = B::KW == T::KW ? off16 : off16 + (half ? 16u * B::KW * (uint32_t)L : 0u);
 #pragma unroll
-          for (int i = 0; i < EPT; ++i) {
-            const u32x4* line = reinterpret_cast<const u32x4*>(reinterpret_cast<const uint8_t*>(XT) + off[i]);
-            x0[i] = line[0];
-            x1[i] = line[1];
-          }
-          float acc[16];
-#pragma unroll
-          for (int b = 0; b < 16; ++b) acc[b] = 0.f;
-#pragma unroll
-          for (int i = 0; i < EPT; ++i) {
-            const uint32_t xw[8] = {x0[i].x, x0[i].y, x0[i].z, x0[i].w, x1[i].x, x1[i].y, x1[i].z, x1[i].w};
-#pragma unroll
-            for (int q = 0; q < 8; ++q) {
-              acc[2 * q] = fmaf(val[i], h2f((uint16_t)(xw[q] & 0xFFFFu)), acc[2 * q]);
-              acc[2 * q + 1] = fmaf(val[i], h2f((uint16_t)(xw[q] >> 16)), acc[2 * q + 1]);
-            }
-          }
-          int row;
-          const float red = wave_reduce_rows<16>(acc, lane, &row);           // every lane: the sum of vector `row`
-          if ((lane & 3) == 0) slots[(int64_t)(lo / kSlotGrain + k) * 16 + row] = red;   // 4 lanes hold each sum
-        }
-      }
-    }
-    if (rpl[nrows] >= z) break;                                              // the next row starts behind the share
-    r0 += nrows;
-    __syncthreads();                                                         // everyone is done with these row pointers
+  for (int k = 0; k < B::KW; ++k) {
+    const u32x4 v = *reinterpret_cast<const u32x4*>(blk + 16 * k * L + offc);
+    t.c[4 * k] = v.x; t.c[4 * k + 1] = v.y; t.c[4 * k + 2] = v.z; t.c[4 * k + 3] = v.w;
   }
 }
 
-// Shape of the dense kernel for a tile of TR x TC = 256 codes.  A phase covers PC = 64/TR columns of every tile
-// (a lane always writes 64 binary16 values = 128 bytes per phase: rows x PC columns), four phases per step.
-// The 8 K-values a lane supplies to one MFMA are PC columns of 8/PC tiles.  Strips per workgroup: what the LDS
-// allows next to the piece of X (16 batch rows x 64*TC columns): 8 x 32 tiles share a 64 KB piece among 8 strips.
-template <int TR, int TC> struct MfmaShape {
-  static constexpr int PC = 64 / TR;                       // columns per phase: 8, 4, 2
-  static constexpr int TPK = 8 / PC;                       // tiles per K-group of a lane: 1, 2, 4
-  static constexpr int MB = TR >= 16 ? TR / 16 : 1;        // blocks of 16 rows (an 8-row tile fills half a block)
-  static constexpr int NS = TC == 32 ? 8 : 4;              // strips = wavefronts per workgroup
-  static constexpr int WGS = TC == 32 ? 1 : 2;             // workgroups per CU
-  static constexpr int XROW = 128 * TC + 8;                // bytes per batch row of the staged piece of X
-  static constexpr size_t LDS = (size_t)NS * 64 * kMfmaTileStride * 4 + 16 * (size_t)XROW;
-  static_assert(WGS * (LDS + 1024) <= 160 * 1024, "the workgroups of a CU must fit its LDS");
-};
-
-// `group` is the group of NS strips this workgroup multiplies, or negative for a workgroup that takes long outlier
-// rows instead: then it is number `extra` of `nextra` such workgroups of its matrix.  `split` of the splits of the
-// steps, `smem` the workgroup's dynamic LDS.
-template <int W, int TR, int TC, int AXIS, bool ONE>
-__device__ __forceinline__ void gemm_mfma_body(const DevMatrix& A, const uint16_t* __restrict__ X, float* __restrict__ P,
-                                               int64_t split_stride, int steps_per_split, int batch,
-                                               const uint16_t* __restrict__ XT, float* __restrict__ slots, int long_row,
-                                               int group, int split, int extra, int nextra, uint8_t* smem) {
-  using SH = MfmaShape<TR, TC>;
-  constexpr int PPR = TC / 2, S = kMfmaTileStride, NS = SH::NS, NT = 64 * NS, PC = SH::PC, TPK = SH::TPK, MB = SH::MB;
-  constexpr int UROW = 8 * TC;               // 16-byte units of the X piece per batch row
-  constexpr int UPT = 16 * UROW / NT;        // ... per thread
-  constexpr int B2 = AXIS == 1 ? TC : TR;    // first-level groups per tile
-  constexpr int NM = 2 * PC;                 // MFMAs per phase and block of rows
-  static_assert(NT % UROW == 0 && TR * TC == 256, "shape");
-  using T = TileRegs<W, TR, TC, AXIS>;
-  constexpr int TILE_BYTES = 16 * T::KW + 4 * T::SD;
-  constexpr float SCALE = (float)(1 << W);
-  uint8_t* xbuf = smem + NS * 64 * S * 4;
-  if (group < 0) {                           // long outlier rows
-    if (split == 0)
-      long_rows_block<NT>(A, XT, slots, long_row, extra, nextra, smem);
-    return;
+// Reduces 16 values per lane over the aligned group of 4 lanes: lane l of the group ends with values 4l .. 4l+3 in v[0..3].
+__device__ __forceinline__ void quad_scatter(float (&v)[16], int lane) {
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    const float send = lane & 2 ? v[i] : v[i + 8], keep = lane & 2 ? v[i + 8] : v[i];
+    v[i] = keep + stage_partner<4>(send, lane);
   }
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const float send = lane & 1 ? v[i] : v[i + 4], keep = lane & 1 ? v[i + 4] : v[i];
+    v[i] = keep + stage_partner<5>(send, lane);
+  }
+}
 
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int n = A.g.n, ntc = A.g.ntc, m = A.g.m, ntr = A.g.ntr;
-  const int nsteps = (ntc + 63) >> 6;
-  const int s_lo = split * steps_per_split, s_hi = min(nsteps, s_lo + steps_per_split);   // never empty (host)
-  const int strip = group * NS + wave;
-  const bool active = strip < ntr;           // wave-uniform; an idle wavefront still stages X and meets the barriers
-  const uint8_t* strip_base = A.packed + (int64_t)min(strip, ntr - 1) * ntc * TILE_BYTES;
-  uint32_t* buf = reinterpret_cast<uint32_t*>(smem) + wave * 64 * S;
-  const int i16 = lane & 15, g4 = lane >> 4;
-  const PairConsts kc = make_pair_consts<W>();
-  const PairConsts k3 = make_pair_consts<3>();
-  // Groups along the tile's columns, and the class of a code pair (the offset K its in-place extraction leaves,
-  // see CodeClass) a function of its column alone: then K folds into the column's additive constant and most
-  // shifts of the extraction go away.  True for 4-bit codes and for 3-bit codes in rows of 16 pairs.
-  constexpr bool FOLD = AXIS == 1 && (W == 4 || PPR == 16);
-  const ClassConsts kk = make_class_consts<W>();
-  float4_t D[MB][2];
+// p[s]: the first index in [a, z) whose column is >= c[s], or z (columns increase; on a broken row some index in
+// [a, z]); a < z.  Both at once.  A look-up is a lane's own cache line and a round a trip to memory (a microsecond while
+// the weights stream), so both are kept few: the columns of a row are spread over [0, n) as a rule, so a granule of 8
+// entries is read where the column is expected, and again as far off as its columns say; from the fourth round on the
+// bracket is halved.  (Binary search: 14 look-ups in 7 rounds for a row of 67; seven probes a round: 42 in 3, and
+// slower than that.)
+__device__ __forceinline__ void lower_columns(const uint16_t* __restrict__ col, int n, int a, int z, const int (&c)[2],
+                                              int (&p)[2]) {
+  const u32x4* col8 = reinterpret_cast<const u32x4*>(col);
+  const float density = (float)(z - a) / (float)n;
+  int hi[2], at[2];
 #pragma unroll
-  for (int mb = 0; mb < MB; ++mb) { D[mb][0] = float4_t{0.f, 0.f, 0.f, 0.f}; D[mb][1] = float4_t{0.f, 0.f, 0.f, 0.f}; }
-
-  // the piece of X of step st: unit u = 16 bytes = 8 columns of batch row u/UROW; loads unconditional (clamped)
-  u32x4 xr[UPT];
-  uint32_t xrow[UPT];                        // byte offset of the unit's (clamped) batch row in X
+  for (int s = 0; s < 2; ++s) { p[s] = a; hi[s] = z; at[s] = a + (int)((float)c[s] * density); }
+  for (int round = 0; p[0] < hi[0] || p[1] < hi[1]; ++round) {
+    int q[2];
+    u32x4 g[2];
 #pragma unroll
-  for (int k = 0; k < UPT; ++k) xrow[k] = (uint32_t)min((tid + k * NT) / UROW, batch - 1) * (uint32_t)n * 2u;
-  const int xj = tid % UROW;                 // NT is a multiple of UROW: the unit's place in its row is the same for all k
-  auto fetch_x = [&](int st) {
-    const int sc = min(st, s_hi - 1);
-    const int L = min(64, ntc - 64 * sc);
-    const uint8_t* xs = reinterpret_cast<const uint8_t*>(X + (int64_t)(64 * TC) * sc);
-    const uint32_t jb = 16u * (uint32_t)min(xj, L * (TC / 8) - 1);
+    for (int s = 0; s < 2; ++s) {
+      if (round >= 3) at[s] = p[s] + ((hi[s] - p[s]) >> 1);
+      q[s] = max(min(at[s], hi[s] - 1), min(p[s], z - 1)) >> 3;   // (a bracket that is closed: some granule of the row)
+      g[s] = col8[(uint32_t)q[s]];
+    }
 #pragma unroll
-    for (int k = 0; k < UPT; ++k) xr[k] = *reinterpret_cast<const u32x4*>(xs + (xrow[k] + jb));
-    asm volatile("" ::: "memory");
-  };
-  auto store_x = [&](int st) {
-    const int L = min(64, ntc - 64 * st);
-    typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
-    // columns behind the last tile: zeros (finite), they meet zero weights
-    const bool keep = xj < L * (TC / 8);
+    for (int s = 0; s < 2; ++s) {
+      const int first = max(p[s], 8 * q[s]), last = min(hi[s], 8 * q[s] + 8);
+      if (first >= last) continue;             // closed
+      const uint32_t w[4] = {g[s].x, g[s].y, g[s].z, g[s].w};
+      int below = 0;
 #pragma unroll
-    for (int k = 0; k < UPT; ++k) {
-      const int b = (tid + k * NT) / UROW;
-      const u32x2 lo = {keep ? xr[k].x : 0u, keep ? xr[k].y : 0u}, hi = {keep ? xr[k].z : 0u, keep ? xr[k].w : 0u};
-      if (b < batch) {
-        u32x2* d = reinterpret_cast<u32x2*>(xbuf + b * SH::XROW + xj * 16);
-        d[0] = lo;
-        d[1] = hi;
+      for (int k = 0; k < 8; ++k) {
+        const int v = (int)(k & 1 ? w[k / 2] >> 16 : w[k / 2] & 0xFFFFu), e = 8 * q[s] + k;
+        below += e >= first && e < last && v < c[s];
+      }
+      if (below == last - first) {             // all left of c: on to the right
+        p[s] = last;
+        at[s] = last + (int)((float)max(c[s] - (int)(w[3] >> 16), 0) * density);
+      } else if (below == 0) {                 // none: to the left
+        hi[s] = first;
+        at[s] = first - 1 - (int)((float)max((int)(w[0] & 0xFFFFu) - c[s], 0) * density);
+      } else {
+        p[s] = hi[s] = first + below;
       }
     }
+  }
+}
+
+// The sums of one workgroup: group `group` of matrix A, units [u_lo, u_hi) of its columns.  X: the batch in the
+// matrix's column order.  P: this split's partial results of the matrix (b * m floats).
+template <int W, int TR, int TC, int AXIS>
+__device__ __forceinline__ void batch_group_body(const DevMatrix& A, const uint16_t* __restrict__ X, int batch,
+                                                 float* __restrict__ P, int group, int u_lo, int u_hi, uint8_t* smem) {
+  using SH = BatchShape<TR, TC>;
+  using B = BatchTile<W, TR, TC, AXIS>;
+  using T = typename B::T;
+  constexpr int TILE_BYTES = 16 * T::KW + 4 * T::SD, ROWS = SH::ROWS, PPR = TC / 2, KG = TC / 8, SUM = SH::SUM;
+  constexpr int LR = lane_rows(TR), NSUB = TR / LR;           // rows of a lane; strips of the kernel per strip of tiles
+  constexpr int NG = AXIS == 1 ? TC : LR;                     // first-level groups of a lane
+  constexpr float SCALE = (float)(1 << W);
+  // Groups along the tile's columns: the offset K that the in-place extraction of a code leaves (its class, see CodeClass)
+  // folds into the column's additive constant, and most shifts go away.  The class is a function of the pair's column,
+  // for 3-bit codes in rows of 8 pairs of the column and the parity of the row.
+  constexpr bool FOLD = AXIS == 1;
+  constexpr int NK = FOLD && W == 3 && PPR == 8 ? 2 : 1;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int i16 = lane & 15, g4 = lane >> 4;
+  const int n = A.g.n, ntc = A.g.ntc, ntr = A.g.ntr * NSUB, m = A.g.m;
+  const bool sparse = A.nnz > 0;
+  const int outliers_first = sparse ? (int)((blockIdx.x + gridDim.x * blockIdx.y) / kCUs) & 1 : 0;
+  uint16_t* xt = reinterpret_cast<uint16_t*>(smem);                       // XT[COLS][16]
+  float* red = reinterpret_cast<float*>(smem);                            // afterwards: slices of [16][20]
+  float* osum = reinterpret_cast<float*>(smem + SH::SHARED);              // [16][SUM]: outlier sums
+  int* row_lo = reinterpret_cast<int*>(smem + SH::SHARED + SUM * 64);     // [ROWS] entries of the piece, by row
+  int* row_hi = row_lo + ROWS;
+
+  constexpr int STRIPS = 16 / NSUB;          // strips of tiles of a group
+  const uint8_t* base = A.packed + (int64_t)group * STRIPS * ntc * TILE_BYTES;
+  const int my_strip = min(group * 16 + i16, ntr - 1) - group * 16, half = NSUB == 2 ? my_strip & 1 : 0;
+  const uint32_t strip_off = (uint32_t)(my_strip / NSUB) * (uint32_t)ntc * TILE_BYTES;
+  const uint32_t xrow = (uint32_t)min(i16, batch - 1) * (uint32_t)n * 2u;
+  const PairConsts kc = make_pair_consts<W>();
+  const PairConsts k3 = make_pair_consts<3>();
+  const ClassConsts kk = make_class_consts<W>();
+
+  float4_t D[LR];
+#pragma unroll
+  for (int r = 0; r < LR; ++r) D[r] = float4_t{0.f, 0.f, 0.f, 0.f};
+
+  const int nst = (ntc + 3) >> 2;              // steps of 4 tile columns
+  // the wavefront's step of unit u (a step behind the last one loads the last one and counts nothing)
+  auto issue = [&](B& t, u32x4 (&x)[KG], int u) {
+    const int st = min(4 * u + wave, nst - 1);
+    const int blk = st >> 4, L = min(64, ntc - 64 * blk), tl = min(4 * st + g4, ntc - 1);
+    const bool real = u < u_hi;                // uniform; behind the range every lane reads the group's first tile
+    const uint32_t l = real ? (uint32_t)(tl - 64 * blk) : 0u;
+    load_batch_tile(t, base + (real ? (int64_t)64 * blk * TILE_BYTES : 0), real ? L : 1, real ? strip_off : 0u, l, half);
+    const uint8_t* xs = reinterpret_cast<const uint8_t*>(X);
+#pragma unroll
+    for (int j = 0; j < KG; ++j) x[j] = *reinterpret_cast<const u32x4*>(xs + (real ? xrow + (uint32_t)tl * (TC * 2) + 16 * j : 0u));
+    __builtin_amdgcn_sched_barrier(0);         // the requests go out here, not between the multiplies of the tile before
   };
-  auto issue = [&](T& t, int st) {
-    const bool real = st < s_hi;
-    const int L = real ? min(64, ntc - 64 * st) : 1;
-    load_tile<false>(t, strip_base + (int64_t)64 * (real ? st : s_lo) * TILE_BYTES, L, min(lane, L - 1));
-    asm volatile("" ::: "memory");
-  };
-  // operand fragments of MFMA j of a phase: tiles (4j + g4)*TPK .. +TPK-1, PC columns each.
-  // A: row i16 (+16 per block of rows; an 8-row tile repeats its rows, the copies are dropped at the end)
-  const uint32_t* afrag = buf + g4 * TPK * S + ((TR >= 16 ? i16 : (i16 & 7)) * PC) / 2;
-  const uint32_t* xfrag = reinterpret_cast<const uint32_t*>(xbuf + min(i16, batch - 1) * SH::XROW) + g4 * TPK * (TC / 2);
-  // one step: publish its piece of X, then per phase: dequantise PC columns of this lane's tile, multiply
-  auto run_step = [&](const T& t, int st) {
-    const int L = min(64, ntc - 64 * st);
-    __syncthreads();                         // every wavefront is done with the previous piece of X
-    store_x(st);
-    if constexpr (!ONE) fetch_x(st + 1);
-    __syncthreads();
+  auto multiply = [&](const B& t, const u32x4 (&x)[KG], int u) {
+    const bool live = 16 * u + 4 * wave + g4 < ntc;
     const uint32_t a2 = t.s[T::SD - 2], b2 = t.s[T::SD - 1];
     const float s_s = h2f((uint16_t)(a2 & 0xFFFF)), z_s = h2f((uint16_t)(a2 >> 16));
     const float s_z = h2f((uint16_t)(b2 & 0xFFFF)), z_z = h2f((uint16_t)(b2 >> 16));
     // w = s_hat*(q - z_hat) = fa*(1 + q/2^W) + fb with fa = 2^W*s_hat, fb = -s_hat*(2^W + z_hat), per group,
     // where s_hat = s_s*(s_q - z_s) and z_hat = s_z*(z_q - z_z) and the extracted codes are 1 + code/8:
     //   fa = c1*(1 + s_q/8) + c2,   -(2^W + z_hat)/2^W = e1*(1 + z_q/8) + e2,   fb = fa * that.
-    // A lane behind the step's last tile (its loads were clamped) writes a tile of zeros.
-    const bool live = lane < L;
+    // A lane without a tile of its own multiplies zero weights with zero activations.
     const float c1 = live ? SCALE * 8.f * s_s : 0.f, c2 = live ? SCALE * (-s_s * z_s - 8.f * s_s) : 0.f;
     const float e1 = -8.f * s_z / SCALE, e2 = -(SCALE - s_z * z_z - 8.f * s_z) / SCALE;
-    float fa[B2], fb[B2];
-#pragma unroll
-    for (int p = 0; p < B2 / 2; ++p) {
-      const half2_t sq = as_half2(pair_f16<3>(t.s, p, k3));
-      const half2_t zq = as_half2(pair_f16<3>(t.s, B2 / 2 + p, k3));
-      fa[2 * p] = fmaf((float)sq.x, c1, c2);
-      fa[2 * p + 1] = fmaf((float)sq.y, c1, c2);
-      fb[2 * p] = fa[2 * p] * fmaf((float)zq.x, e1, e2);
-      fb[2 * p + 1] = fa[2 * p + 1] * fmaf((float)zq.y, e1, e2);
-      if constexpr (FOLD) {                  // the extracted value is K + code/2^W instead of 1 + code/2^W
-        const float K = CodeClass<W, true>::K(CodeClass<W, true>::of_pair(p));   // a constant once the loop is unrolled
-        fb[2 * p] = fmaf(1.f - K, fa[2 * p], fb[2 * p]);
-        fb[2 * p + 1] = fmaf(1.f - K, fa[2 * p + 1], fb[2 * p + 1]);
+    auto group_pair = [&](int p, float* fa, float* fb0, float* fb1) {   // groups 2p and 2p + 1 of the lane
+      uint32_t sp = pair_f16<3>(t.s, p, k3), zp = pair_f16<3>(t.s, T::B2 / 2 + p, k3);
+      if constexpr (NSUB == 2) {               // the groups of the lane's half of the rows
+        sp = half ? pair_f16<3>(t.s, NG / 2 + p, k3) : sp;
+        zp = half ? pair_f16<3>(t.s, T::B2 / 2 + NG / 2 + p, k3) : zp;
       }
+      const half2_t sq = as_half2(sp), zq = as_half2(zp);
+      fa[0] = fmaf((float)sq.x, c1, c2);
+      fa[1] = fmaf((float)sq.y, c1, c2);
+      const float b0 = fa[0] * fmaf((float)zq.x, e1, e2), b1 = fa[1] * fmaf((float)zq.y, e1, e2);
+      fb0[0] = b0;
+      fb0[1] = b1;
+      if constexpr (FOLD) {                    // the extracted value is K + code/2^W instead of 1 + code/2^W
+        const float K0 = CodeClass<W, true>::K(CodeClass<W, true>::of_pair(p));   // constants once the loop is unrolled
+        fb0[0] = fmaf(1.f - K0, fa[0], b0);
+        fb0[1] = fmaf(1.f - K0, fa[1], b1);
+        if constexpr (NK == 2) {               // odd rows
+          const float K1 = CodeClass<W, true>::K(CodeClass<W, true>::of_pair(PPR + p));
+          fb1[0] = fmaf(1.f - K1, fa[0], b0);
+          fb1[1] = fmaf(1.f - K1, fa[1], b1);
+        }
+      }
+    };
+    // 8 columns at a time, so that few groups' constants are alive (the two tiles and the sums leave room for no more)
+    constexpr int NF = AXIS == 1 ? 8 : NG;
+    float fa[NF], fb[NK][NF];
+    if constexpr (AXIS == 0) {
+#pragma unroll
+      for (int p = 0; p < NG / 2; ++p) group_pair(p, fa + 2 * p, fb[0] + 2 * p, fb[NK - 1] + 2 * p);
     }
-    uint32_t* mine = buf + lane * S;
 #pragma unroll
-    for (int ph = 0; ph < 4; ++ph) {         // columns PC*ph .. PC*ph+PC-1 of every tile
-      // the lane's 64 values of the phase, row by row (PC/2 dwords per row), 16 bytes per store
+    for (int j = 0; j < KG; ++j) {
+      if constexpr (AXIS == 1) {
 #pragma unroll
-      for (int k4 = 0; k4 < 8; ++k4) {
+        for (int d = 0; d < 4; ++d) group_pair(4 * j + d, fa + 2 * d, fb[0] + 2 * d, fb[NK - 1] + 2 * d);
+      }
+      const uint32_t xv[4] = {live ? x[j].x : 0u, live ? x[j].y : 0u, live ? x[j].z : 0u, live ? x[j].w : 0u};
+#pragma unroll
+      for (int r = 0; r < LR; ++r) {
         uint32_t o[4];
 #pragma unroll
         for (int d = 0; d < 4; ++d) {
-          const int dw = 4 * k4 + d, r = dw / (PC / 2), p = (PC / 2) * ph + dw % (PC / 2);
-          const half2_t q2 = as_half2(FOLD ? pair_class_inline<W>(t.c, r * PPR + p, kk) : pair_f16<W>(t.c, r * PPR + p, kc));
-          const int g0 = AXIS == 1 ? 2 * p : r, g1 = AXIS == 1 ? 2 * p + 1 : r;
+          const int q = r * PPR + 4 * j + d;
+          const half2_t q2 = as_half2(FOLD ? pair_class_inline<W>(t.c, q, kk) : pair_f16<W>(t.c, q, kc));
+          const int g0 = AXIS == 1 ? 2 * d : r, g1 = AXIS == 1 ? 2 * d + 1 : r;
           half2_t w;
-          w.x = (_Float16)fmaf((float)q2.x, fa[g0], fb[g0]);
-          w.y = (_Float16)fmaf((float)q2.y, fa[g1], fb[g1]);
+          w.x = (_Float16)fmaf((float)q2.x, fa[g0], fb[r % NK][g0]);
+          w.y = (_Float16)fmaf((float)q2.y, fa[g1], fb[r % NK][g1]);
           o[d] = __builtin_bit_cast(uint32_t, w);
         }
-        const u32x4 v = {o[0], o[1], o[2], o[3]};
-        *reinterpret_cast<u32x4*>(mine + 4 * k4) = v;
+        D[r] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8_t, o), __builtin_bit_cast(half8_t, xv), D[r],
+                                                      0, 0, 0);
+        if (r % 4 == 3) __builtin_amdgcn_sched_barrier(0);
       }
-      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-      __builtin_amdgcn_wave_barrier();       // the buffer is this wavefront's own: its LDS operations stay in order
-      constexpr int JG = NM < 8 ? NM : 8;    // MFMAs whose operands are in flight at a time
-#pragma unroll
-      for (int j0 = 0; j0 < NM; j0 += JG) {
-        uint32_t av[MB][JG][4], bv[JG][4];
-#pragma unroll
-        for (int j = 0; j < JG; ++j) {
-#pragma unroll
-          for (int tt = 0; tt < TPK; ++tt) {
-            const int tile0 = (4 * (j0 + j)) * TPK + tt;         // + g4*TPK: in afrag / xfrag
-            const uint32_t* pb = xfrag + tile0 * (TC / 2) + (PC / 2) * ph;
-#pragma unroll
-            for (int d = 0; d < PC / 2; ++d) bv[j][tt * (PC / 2) + d] = pb[d];
-#pragma unroll
-            for (int mb = 0; mb < MB; ++mb) {
-              const uint32_t* pa = afrag + tile0 * S + mb * (16 * PC / 2);
-#pragma unroll
-              for (int d = 0; d < PC / 2; ++d) av[mb][j][tt * (PC / 2) + d] = pa[d];
-            }
-          }
-        }
-#pragma unroll
-        for (int j = 0; j < JG; ++j) {
-          const uint32_t b4v[4] = {bv[j][0], bv[j][1], bv[j][2], bv[j][3]};
-#pragma unroll
-          for (int mb = 0; mb < MB; ++mb) {
-            const uint32_t a4v[4] = {av[mb][j][0], av[mb][j][1], av[mb][j][2], av[mb][j][3]};
-            D[mb][j & 1] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8_t, a4v),
-                                                                   __builtin_bit_cast(half8_t, b4v), D[mb][j & 1], 0, 0, 0);
-          }
-        }
-      }
-      __builtin_amdgcn_wave_barrier();       // the reads are issued before the next phase overwrites the buffer
     }
   };
 
-  if constexpr (ONE) {                       // one step per workgroup: no second tile, no loop (fewer registers)
-    T t0;
-    fetch_x(s_lo);
-    issue(t0, s_lo);
-    run_step(t0, s_lo);
-  } else {
-    T t0, t1;
-    fetch_x(s_lo);
-    issue(t0, s_lo);
-    int st = s_lo;
-    while (st + 1 < s_hi) {                  // workgroup-uniform; two steps per trip, one exit at the bottom
-      issue(t1, st + 1);
-      run_step(t0, st);
-      issue(t0, st + 2);                     // a dummy behind the last step
-      run_step(t1, st + 1);
-      st += 2;
-    }
-    if (st < s_hi) run_step(t0, st);
-  }
-
-  // D[mb][row 16*mb + 4*g4 + v][batch i16]
-  if (active && i16 < batch) {
+  for (int c_lo = u_lo; c_lo < u_hi; c_lo += SH::CHUNK) {   // pieces of the column range, workgroup-uniform
+    const int c_hi = min(u_hi, c_lo + SH::CHUNK);
+    const int k0 = c_lo * kUnitTiles * TC, k1 = min(n, c_hi * kUnitTiles * TC);
+    B t0, t1;
+    u32x4 x0[KG], x1[KG];
+    issue(t0, x0, c_lo);
+    if (sparse) {
+      if (c_lo > u_lo) __syncthreads();        // everyone is done with the previous piece
+      int bounds[2] = {0, 0};                  // of the row's entries, then of those in the piece; requested ahead of X
+      const int row = group * ROWS + tid;
+      if (tid < ROWS && row < m) {
+        bounds[0] = A.row_ptr[row];
+        bounds[1] = A.row_ptr[row + 1];
+      }
+      // the piece of X, transposed: thread = 8 columns of 2 vectors; the 8 pairs of vectors of 8 neighbouring blocks of
+      // columns are a wavefront's, which write all 64 banks (the free line after every 8)
+      const int units8 = (k1 - k0) >> 3;       // n and the units are multiples of 8
+      for (int q = tid; q < 8 * units8; q += 256) {
+        const int c8 = q >> 3, v = 2 * (q & 7);
+        const u32x4 z = {0u, 0u, 0u, 0u};
+        const u32x4 lo = v < batch ? *reinterpret_cast<const u32x4*>(X + (int64_t)v * n + k0 + 8 * c8) : z;
+        const u32x4 hi = v + 1 < batch ? *reinterpret_cast<const u32x4*>(X + (int64_t)(v + 1) * n + k0 + 8 * c8) : z;
+        uint32_t* d = reinterpret_cast<uint32_t*>(xt + (9 * c8) * 16 + v);
+        const uint32_t a4[4] = {lo.x, lo.y, lo.z, lo.w}, b4[4] = {hi.x, hi.y, hi.z, hi.w};
 #pragma unroll
-    for (int mb = 0; mb < MB; ++mb) {
-      const float4_t d = D[mb][0] + D[mb][1];
-      if (16 * mb + 4 * g4 < TR)
-        *reinterpret_cast<float4_t*>(P + (int64_t)split * split_stride + (int64_t)i16 * m + (int64_t)strip * TR +
-                                     16 * mb + 4 * g4) = d;
+        for (int k = 0; k < 4; ++k) {
+          d[(2 * k) * 8] = (a4[k] & 0xFFFFu) | (b4[k] << 16);
+          d[(2 * k + 1) * 8] = (a4[k] >> 16) | (b4[k] & 0xFFFF0000u);
+        }
+      }
+      if (tid < ROWS) {
+        const int a = bounds[0], z = bounds[1], c[2] = {k0, k1};
+        if (a < z && (k0 > 0 || k1 < n)) lower_columns(A.col, n, a, z, c, bounds);
+        row_lo[tid] = bounds[0];
+        row_hi[tid] = bounds[1];
+      }
     }
-  }
-}
-
-template <int W, int TR, int TC, int AXIS>
-__global__ void __launch_bounds__((64 * MfmaShape<TR, TC>::NS), 2)
-gemm_mfma_kernel(DevMatrix A, const uint16_t* __restrict__ X, float* __restrict__ P, int64_t split_stride,
-                 int steps_per_split, int batch, const uint16_t* __restrict__ XT, float* __restrict__ slots, int long_row,
-                 int groups) {
-  extern __shared__ __align__(16) uint8_t smem[];
-  const int bx = blockIdx.x;
-  gemm_mfma_body<W, TR, TC, AXIS, false>(A, X, P, split_stride, steps_per_split, batch, XT, slots, long_row,
-                                         bx < groups ? bx : -1, (int)blockIdx.y, bx - groups, (int)gridDim.x - groups, smem);
-}
-
-template <int W, int TR, int TC, int AXIS>
-__global__ void __launch_bounds__((64 * MfmaShape<TR, TC>::NS), (TC == 32 ? 2 : 3))
-gemm_mfma_one_kernel(DevMatrix A, const uint16_t* __restrict__ X, float* __restrict__ P, int64_t split_stride,
-                     int batch, const uint16_t* __restrict__ XT, float* __restrict__ slots, int long_row, int groups) {
-  extern __shared__ __align__(16) uint8_t smem[];
-  const int bx = blockIdx.x;
-  gemm_mfma_body<W, TR, TC, AXIS, true>(A, X, P, split_stride, 1, batch, XT, slots, long_row,
-                                        bx < groups ? bx : -1, (int)blockIdx.y, bx - groups, (int)gridDim.x - groups, smem);
-}
-
-// Several matrices that share the batch X and the format (q/k/v, gate/up of a decoder block) in one grid:
-// blockIdx.x counts the dense workgroups of all matrices first, then their long-row workgroups.  Every
-// workgroup does exactly what it would do in a launch of its own matrix.
-struct MfmaFusedItem {
-  DevMatrix A;
-  float* P;                                  // partial results (or the output itself, see the finishing kernel)
-  float* slots;
-  void* Y;
-  int long_row;
-  int groups, extra;                         // dense / long-row workgroups of this matrix
-  int blocks16;                              // workgroups of the finishing kernel
-};
-struct MfmaFused {
-  int count;
-  MfmaFusedItem it[SPQR_MAX_FUSED];
-};
-
-template <int W, int TR, int TC, int AXIS, bool ONE>
-__global__ void __launch_bounds__((64 * MfmaShape<TR, TC>::NS), (ONE && TC != 32 ? 3 : 2))
-gemm_mfma_fused_kernel(MfmaFused F, const uint16_t* __restrict__ X, int steps_per_split, int batch,
-                       const uint16_t* __restrict__ XT) {
-  extern __shared__ __align__(16) uint8_t smem[];
-  int bx = blockIdx.x, i = 0;
-  bool dense = false;                        // workgroup-uniform search, count <= SPQR_MAX_FUSED
-  for (; i < F.count; ++i) {
-    if (bx < F.it[i].groups) { dense = true; break; }
-    bx -= F.it[i].groups;
-  }
-  if (!dense) {
-    for (i = 0; i < F.count - 1; ++i) {
-      if (bx < F.it[i].extra) break;
-      bx -= F.it[i].extra;
-    }
-  }
-  const MfmaFusedItem& it = F.it[i];
-  gemm_mfma_body<W, TR, TC, AXIS, ONE>(it.A, X, it.P, (int64_t)batch * it.A.g.m, ONE ? 1 : steps_per_split, batch, XT, it.slots,
-                                  it.long_row, dense ? bx : -1, (int)blockIdx.y, bx, it.extra, smem);
-}
-
-// Prepares the batch for the batch path.  With an input permutation, column j of the
-// matrix meets x[perm[j]] (act-order, Sec. 4 / Alg. 1: the quantiser reorders the input
-// dimension): XP[b][j] = X[b][perm[j]] is the batch in the matrix's column order, read by
-// the dense kernel in place of X.  For the outlier kernels, XT[j][16] binary16 is the same
-// transposed, batch rows beyond `batch` zero, so that one outlier (one column j) meets its
-// 16 activations in one 32-byte line; line n is all zeros: the place entry slots behind
-// the end of a row read.  Either output may be absent.
-__global__ void __launch_bounds__(256)
-transpose_x16_kernel(const uint16_t* __restrict__ X, const int32_t* __restrict__ perm, uint16_t* __restrict__ XT,
-                     uint16_t* __restrict__ XP, int n, int batch) {
-  const int j = blockIdx.x * 256 + threadIdx.x;
-  if (j > n) return;
-  const int src = j < n ? (perm ? perm[j] : j) : 0;
-  uint32_t o[8];
+    // the dense part of the piece: two units per trip, the next one's loads ahead of the arithmetic
+    auto dense_part = [&]() {
+      int u = c_lo;
+      while (u + 1 < c_hi) {
+        issue(t1, x1, u + 1);
+        multiply(t0, x0, u);
+        issue(t0, x0, u + 2);                  // behind the last unit: a dummy
+        multiply(t1, x1, u + 1);
+        u += 2;
+      }
+      if (u < c_hi) multiply(t0, x0, u);
+    };
+    auto outlier_part = [&]() {
+      __syncthreads();                           // XT and the row bounds are complete
+      const bool first = c_lo == u_lo;
+      const int width = k1 - k0;
+      auto line_of = [&](uint32_t col) {         // a column outside the piece (a broken row) stays inside XT
+        const int c = min(max((int)col - k0, 0), width - 1);
+        return reinterpret_cast<const u32x4*>(xt + (c + (c >> 3)) * 16);
+      };
+      // acc += two entries' values (binary16 pair) times their 16 activations: one v_perm pairs the two activations of
+      // a vector, one v_dot2 takes them (products exact, binary32 sums); half the issue of two v_fma_mix
+      auto add_pair = [&](uint32_t cols, uint32_t vals, float (&acc)[16]) {
+        const u32x4 *l0 = line_of(cols & 0xFFFFu), *l1 = line_of(cols >> 16);
+        const u32x4 a0 = l0[0], a1 = l0[1], b0 = l1[0], b1 = l1[1];
+        const uint32_t a[8] = {a0.x, a0.y, a0.z, a0.w, a1.x, a1.y, a1.z, a1.w}, b[8] = {b0.x, b0.y, b0.z, b0.w, b1.x, b1.y, b1.z, b1.w};
+        const half2_t w = as_half2(vals);
 #pragma unroll
-  for (int k = 0; k < 8; ++k) {
-    const uint32_t lo = (j < n && 2 * k < batch) ? X[(int64_t)(2 * k) * n + src] : 0u;
-    const uint32_t hi = (j < n && 2 * k + 1 < batch) ? X[(int64_t)(2 * k + 1) * n + src] : 0u;
-    o[k] = lo | (hi << 16);
-    if (XP != nullptr && j < n) {
-      if (2 * k < batch) XP[(int64_t)(2 * k) * n + j] = (uint16_t)lo;
-      if (2 * k + 1 < batch) XP[(int64_t)(2 * k + 1) * n + j] = (uint16_t)hi;
+        for (int q = 0; q < 8; ++q) {
+          const half2_t lo = as_half2(__builtin_amdgcn_perm(b[q], a[q], 0x05040100u));   // a.lo, b.lo
+          const half2_t hi = as_half2(__builtin_amdgcn_perm(b[q], a[q], 0x07060302u));   // a.hi, b.hi
+          acc[2 * q] = __builtin_amdgcn_fdot2(w, lo, acc[2 * q], false);
+          acc[2 * q + 1] = __builtin_amdgcn_fdot2(w, hi, acc[2 * q + 1], false);
+        }
+      };
+      // the values of entries x and x + 1 as far as they lie in [lo, hi)
+      auto inside = [](uint32_t vals, int x, int lo, int hi) {
+        return (x >= lo && x < hi ? vals & 0xFFFFu : 0u) | (x + 1 >= lo && x + 1 < hi ? vals & 0xFFFF0000u : 0u);
+      };
+      auto put = [&](int lr, int v, float s) {   // row lr = LR * strip + r lives at r * 16 + strip
+        float* d = osum + v * SUM + (lr % LR) * 16 + lr / LR;
+        *d = first ? s : *d + s;
+      };
+      const uint32_t* col2 = reinterpret_cast<const uint32_t*>(A.col);    // aligned pairs of entries; the last entry's
+      const uint32_t* val2 = reinterpret_cast<const uint32_t*>(A.val);    // pair is inside its granule of 16 bytes
+      const int last2 = (int)((A.nnz - 1) >> 1);
+      // Rows of up to kLongRow entries: 4 lanes each, 16 rows per wavefront at a time, a lane takes every 4th pair.  The
+      // first pairs of all of the wavefront's rows are requested together.
+      constexpr int SETS = ROWS / 64, PRE = 8 / SETS;
+      uint32_t cw[SETS][PRE], vw[SETS][PRE];
+      int lo[SETS], hi[SETS];
+      bool mine[SETS];                           // not a long row: its sums are written below
+#pragma unroll
+      for (int k = 0; k < SETS; ++k) {
+        const int lr = 16 * (wave + 4 * k) + (lane >> 2);
+        lo[k] = row_lo[lr];
+        hi[k] = row_hi[lr];
+        mine[k] = hi[k] - lo[k] <= kLongRow;
+        hi[k] = mine[k] ? hi[k] : lo[k];
+#pragma unroll
+        for (int h = 0; h < PRE; ++h) {
+          const uint32_t at = (uint32_t)min((lo[k] >> 1) + (lane & 3) + 4 * h, last2);
+          cw[k][h] = col2[at];
+          vw[k][h] = val2[at];
+        }
+      }
+#pragma unroll
+      for (int k = 0; k < SETS; ++k) {
+        float acc[16];
+#pragma unroll
+        for (int v = 0; v < 16; ++v) acc[v] = 0.f;
+        const int x0 = (lo[k] & ~1) + 2 * (lane & 3);
+#pragma unroll
+        for (int h = 0; h < PRE; ++h)
+          if (__builtin_amdgcn_ballot_w64(x0 + 8 * h < hi[k]) != 0)
+            add_pair(cw[k][h], inside(vw[k][h], x0 + 8 * h, lo[k], hi[k]), acc);
+        for (int x = x0 + 8 * PRE; __builtin_amdgcn_ballot_w64(x < hi[k]) != 0; x += 32) {   // 32 more entries at a time
+          uint32_t cm[4], vm[4];
+#pragma unroll
+          for (int h = 0; h < 4; ++h) {
+            const uint32_t at = (uint32_t)min((x >> 1) + 4 * h, last2);
+            cm[h] = col2[at];
+            vm[h] = val2[at];
+          }
+#pragma unroll
+          for (int h = 0; h < 4; ++h)
+            if (__builtin_amdgcn_ballot_w64(x + 8 * h < hi[k]) != 0)
+              add_pair(cm[h], inside(vm[h], x + 8 * h, lo[k], hi[k]), acc);
+        }
+        quad_scatter(acc, lane);
+        if (mine[k]) {
+#pragma unroll
+          for (int i = 0; i < 4; ++i) put(16 * (wave + 4 * k) + (lane >> 2), 4 * (lane & 3) + i, acc[i]);
+        }
+      }
+      // Long rows, dealt to the wavefronts in turn: aligned granules of 8 entries (16 bytes of columns, 16 of values), two
+      // per lane at a time; a row's first ones are requested while the row before is added up.
+      const u32x4* col8 = reinterpret_cast<const u32x4*>(A.col);
+      const u32x4* val8 = reinterpret_cast<const u32x4*>(A.val);
+      int taken = 0, r0 = -64;
+      uint64_t mask = 0;
+      auto next_long = [&]() {                   // this wavefront's next long row, -1 behind the last (wave-uniform)
+        for (;;) {
+          while (mask == 0) {
+            r0 += 64;
+            if (r0 >= ROWS) return -1;
+            mask = __builtin_amdgcn_ballot_w64(row_hi[r0 + lane] - row_lo[r0 + lane] > kLongRow);
+          }
+          const int lr = r0 + __builtin_ctzll(mask);
+          mask &= mask - 1;
+          if ((taken++ & 3) == wave) return lr;
+        }
+      };
+      auto fetch = [&](int g0, int g_hi, u32x4 (&c8)[2], u32x4 (&v8)[2]) {
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          const uint32_t at = (uint32_t)min(g0 + lane + 64 * h, g_hi);
+          c8[h] = col8[at];
+          v8[h] = val8[at];
+        }
+      };
+      u32x4 c8[2], v8[2], nc8[2], nv8[2];
+      int lr = next_long();
+      if (lr >= 0) fetch(row_lo[lr] >> 3, (row_hi[lr] - 1) >> 3, c8, v8);
+      while (lr >= 0) {                          // wave-uniform
+        const int next = next_long();
+        if (next >= 0) fetch(row_lo[next] >> 3, (row_hi[next] - 1) >> 3, nc8, nv8);
+        const int rlo = row_lo[lr], rhi = row_hi[lr], g_hi = (rhi - 1) >> 3;
+        float acc[16];
+#pragma unroll
+        for (int v = 0; v < 16; ++v) acc[v] = 0.f;
+        for (int g0 = rlo >> 3;;) {
+#pragma unroll
+          for (int h = 0; h < 2; ++h) {
+            const int e = 8 * (g0 + lane + 64 * h);
+            if (h > 0 && __builtin_amdgcn_ballot_w64(e < rhi) == 0) break;
+            const uint32_t c4[4] = {c8[h].x, c8[h].y, c8[h].z, c8[h].w}, v4[4] = {v8[h].x, v8[h].y, v8[h].z, v8[h].w};
+#pragma unroll
+            for (int k = 0; k < 4; ++k) add_pair(c4[k], inside(v4[k], e + 2 * k, rlo, rhi), acc);
+          }
+          if ((g0 += 128) > g_hi) break;
+          fetch(g0, g_hi, c8, v8);
+        }
+        int v;
+        const float s = wave_reduce_rows<16>(acc, lane, &v);
+        if ((lane & 3) == 0) put(lr, v, s);      // 4 lanes hold each sum
+        lr = next;
+#pragma unroll
+        for (int h = 0; h < 2; ++h) { c8[h] = nc8[h]; v8[h] = nv8[h]; }
+      }
+    };
+    // Every second workgroup of a CU takes the outliers first: one of a pair is at its look-ups while the other's
+    // weights stream.
+#pragma unroll 1
+    for (int part = 0; part < 2; ++part) {
+      if (part == outliers_first) dense_part();
+      else if (sparse) outlier_part();
     }
   }
-  if (XT != nullptr) {
-    u32x4* d = reinterpret_cast<u32x4*>(XT + (int64_t)j * 16);
-    const u32x4 v0 = {o[0], o[1], o[2], o[3]}, v1 = {o[4], o[5], o[6], o[7]};
-    d[0] = v0;
-    d[1] = v1;
-  }
-}
 
-// value of lane J (0 or 1) of the caller's pair of lanes, for both lanes of the pair
-template <int J>
-__device__ __forceinline__ uint32_t pair_broadcast(uint32_t v) {
-  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, J == 0 ? 0xA0 : 0xF5, 0xF, 0xF, false);   // quad_perm [J,J,2+J,2+J]
-}
-
-// Finishing kernel for up to 16 activation vectors:
-// Y[b][i] = sum_split P[split][b][i] + sum_k val_k * X[b][col_k]  (Sec. 4.2: the sparse
-// part is a separate product), rounded to y_dtype.  With one split and binary32
-// output P may be Y itself.
-// One workgroup of 512 threads per strip of 16 rows.  The strip's CSR entries pass
-// through LDS in chunks of 4096 (every thread brings one aligned granule of 8
-// entries; chunks that lie inside one long row are skipped).  A pair of lanes works
-// on one part of one row, each lane on 8 of the 16 activation vectors (16 bytes of
-// the entry's line of XT), so no reduction across lanes exists: the pair walks its
-// entries in order, 4 per trip (each lane reads 2 of them from LDS and hands them to
-// its partner).  A row is cut into 16 contiguous parts (256 pairs = 16 rows x 16);
-// parts are added in order by the row's owner.  A row longer than long_row comes
-// ready-made from long_rows_block: its owner adds the row's slots in order.  Fixed
-// order everywhere, one writer per output.
-constexpr int kFinishThreads = 512;
-
-__device__ __forceinline__ void finish_xt16_body(const DevMatrix& A, const uint16_t* __restrict__ XT,
-                                                 const float* __restrict__ slots, const float* P, int nsplit,
-                                                 int64_t split_stride, int long_row, void* Y, int y_dtype, int batch,
-                                                 const int s) {
-  constexpr int TR = 16, NP = kFinishThreads / 2, PER_ROW = NP / TR, CHUNK = 8 * kFinishThreads;
-  __shared__ int rp[TR + 1];
-  __shared__ float part[NP][16];
-  __shared__ __align__(16) uint16_t scol[CHUNK], sval[CHUNK];
-  const int tid = threadIdx.x, pr = tid >> 1, bq = tid & 1;
-  const int g = tid >> 4, b = tid & 15;      // the owner of Y[b][row g] for tid < 256
-  const int m = A.g.m;
-  if (tid <= TR) rp[tid] = A.row_ptr[min(s * TR + tid, m)];      // rows behind the last one (m % 16 == 8) are empty
-  // the dense part of this thread's output: requested now, needed at the very end
-  const int64_t at = (int64_t)min(b, batch - 1) * m + min(s * TR + min(g, TR - 1), m - 1);
-  float dense = 0.f;
-  for (int k = 0; k < nsplit; ++k) dense += P[k * split_stride + at];
+  // The wavefronts' sums meet in LDS (over XT): every wavefront adds up a quarter of the rows, in the order of the
+  // wavefronts, and writes them.  Slice (3 q + k) holds row q of the wavefront that is number k of the other three.
   __syncthreads();
-  const int e_lo = rp[0], e_hi = rp[TR];
-  const bool inplace = static_cast<const void*>(P) == static_cast<const void*>(Y);   // one split, written to Y by the dense kernel
-  if (inplace && e_hi == e_lo) return;       // nothing to add (workgroup-uniform)
-  const uint8_t* xt16 = reinterpret_cast<const uint8_t*>(XT) + 16 * bq;
-  const uint32_t zoff = (uint32_t)A.g.n * 32u;
-  // Both lanes of the pair add the 4 entries at chunk positions i0 + bq and i0 + 2 + bq (global index e0 + i),
-  // those inside [lo, hi) (hi never beyond the chunk); the others read the zero line of XT with value 0.
-  auto consume = [&](int e0, int i0, int lo, int hi, float (&acc)[8]) {
-    uint32_t off[2], val[2];
+  constexpr int QR = LR / 4;
+  const int at = i16 * 20 + 4 * g4;
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      const int i = i0 + 2 * h + bq, e = e0 + i;
-      const bool ok = e >= lo && e < hi;
-      const int ic = min(i, CHUNK - 1);
-      off[h] = ok ? (uint32_t)scol[ic] * 32u : zoff;
-      val[h] = ok ? __builtin_bit_cast(uint32_t, h2f(sval[ic])) : 0u;
-    }
-    u32x4 xx[4];
-    float vv[4];
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      const uint32_t o[2] = {pair_broadcast<0>(off[h]), pair_broadcast<1>(off[h])};
-      const uint32_t v[2] = {pair_broadcast<0>(val[h]), pair_broadcast<1>(val[h])};
-#pragma unroll
-      for (int j = 0; j < 2; ++j) {
-        xx[2 * h + j] = *reinterpret_cast<const u32x4*>(xt16 + o[j]);
-        vv[2 * h + j] = __builtin_bit_cast(float, v[j]);
-      }
-    }
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const uint32_t w[4] = {xx[i].x, xx[i].y, xx[i].z, xx[i].w};
-#pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        acc[2 * k] = fmaf(vv[i], h2f((uint16_t)(w[k] & 0xFFFFu)), acc[2 * k]);
-        acc[2 * k + 1] = fmaf(vv[i], h2f((uint16_t)(w[k] >> 16)), acc[2 * k + 1]);
-      }
-    }
-  };
-  float sum = 0.f;
-  if (e_hi > e_lo) {
-    const u32x4* col8 = reinterpret_cast<const u32x4*>(A.col);
-    const u32x4* val8 = reinterpret_cast<const u32x4*>(A.val);
-    const int g_lo = e_lo >> 3, ngran = ((e_hi - 1) >> 3) - g_lo + 1;
-    // this pair's part of an ordinary row (empty for a long row)
-    int a, z;
-    {
-      const int r = pr / PER_ROW;
-      const int lo = rp[r], hi = rp[r + 1], len = hi - lo;
-      const int per = (len + PER_ROW - 1) / PER_ROW;
-      a = min(lo + (pr % PER_ROW) * per, hi);
-      z = len <= long_row ? min(a + per, hi) : a;
-    }
-    float acc[8];
-#pragma unroll
-    for (int k = 0; k < 8; ++k) acc[k] = 0.f;
-    for (int ch = 0; ch * kFinishThreads < ngran; ++ch) {         // workgroup-uniform
-      const int e0 = 8 * (g_lo + ch * kFinishThreads), e1 = e0 + CHUNK;   // the chunk's entries
-      bool skip = false;                     // nothing but one long row in it
-#pragma unroll
-      for (int r = 0; r < TR; ++r) skip = skip || (rp[r + 1] - rp[r] > long_row && rp[r] <= max(e0, e_lo) && rp[r + 1] >= min(e1, e_hi));
-      if (skip) continue;
-      const int gi = ch * kFinishThreads + tid;
-      const u32x4 none = {0u, 0u, 0u, 0u};
-      const u32x4 nc = gi < ngran ? col8[g_lo + gi] : none, nv = gi < ngran ? val8[g_lo + gi] : none;
-      __syncthreads();                       // the previous chunk is consumed
-      reinterpret_cast<u32x4*>(scol)[tid] = nc;
-      reinterpret_cast<u32x4*>(sval)[tid] = nv;
-      __syncthreads();
-      for (int e = max(a, e0); e < min(z, e1); e += 4) consume(e0, e - e0, a, min(z, e1), acc);
-    }
-#pragma unroll
-    for (int k2 = 0; k2 < 8; ++k2) part[pr][8 * bq + k2] = acc[k2];
-    __syncthreads();
-    if (g < TR) {
-      const int lo = rp[g], hi = rp[g + 1];
-      if (hi - lo <= long_row) {
-#pragma unroll
-        for (int k = 0; k < PER_ROW; ++k) sum += part[g * PER_ROW + k][b];
-      } else {
-        for (int e0 = lo; e0 < hi; e0 += kLongSlice) sum += slots[(int64_t)(lo / kSlotGrain + (e0 - lo) / kLongSlice) * 16 + b];
-      }
-    }
+  for (int r = 0; r < LR; ++r) {
+    const int q = r / QR;                      // the wavefront that adds up row r
+    if (q != wave) *reinterpret_cast<float4_t*>(red + (3 * r + (wave < q ? wave : wave - 1)) * SH::SLICE + at) = D[r];
   }
-  if (g < TR && s * TR + g < m && b < batch && (rp[g + 1] > rp[g] || !inplace)) {
-    if (y_dtype == SPQR_F32) static_cast<float*>(Y)[at] = dense + sum;
-    else static_cast<uint16_t*>(Y)[at] = f2h_rne(dense + sum);
+  __syncthreads();
+  if (i16 >= batch) return;
+  // partial results of a group: [vector][row of the strip][strip], `strips` of them (16, fewer in the last group)
+  const int strips = min(16, ntr - group * 16);
+  float* out = P + (int64_t)batch * group * ROWS + i16 * (strips * LR);
+#pragma unroll
+  for (int r = 0; r < LR; ++r) {
+    if (r / QR != wave) continue;              // wave-uniform
+    float4_t sum = float4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int w = 0; w < 4; ++w)
+      sum += w == r / QR ? D[r] : *reinterpret_cast<const float4_t*>(red + (3 * r + (w < r / QR ? w : w - 1)) * SH::SLICE + at);
+    if (sparse) sum += *reinterpret_cast<const float4_t*>(osum + i16 * SUM + 16 * r + 4 * g4);
+    if (strips == 16) {
+      *reinterpret_cast<float4_t*>(out + 16 * r + 4 * g4) = sum;       // 16-byte stores: m is a multiple of 8
+    } else {
+#pragma unroll
+      for (int k = 0; k < 4; ++k)
+        if (4 * g4 + k < strips) out[strips * r + 4 * g4 + k] = sum[k];
+    }
   }
 }
 
-__global__ void __launch_bounds__(kFinishThreads, 8)
-finish_xt16_kernel(DevMatrix A, const uint16_t* __restrict__ XT, const float* __restrict__ slots, const float* P,
-                   int nsplit, int64_t split_stride, int long_row, void* Y, int y_dtype, int batch) {
-  finish_xt16_body(A, XT, slots, P, nsplit, split_stride, long_row, Y, y_dtype, batch, (int)blockIdx.x);
+template <int W, int TR, int TC, int AXIS>
+__global__ void __launch_bounds__(256, 2)
+batch_group_kernel(DevMatrix A, const uint16_t* __restrict__ X, int batch, float* __restrict__ P, int units_per_split) {
+  extern __shared__ __align__(16) uint8_t smem[];
+  const int units = (A.g.ntc + kUnitTiles - 1) / kUnitTiles, u_lo = blockIdx.y * units_per_split;   // never empty (host)
+  batch_group_body<W, TR, TC, AXIS>(A, X, batch, P + (int64_t)blockIdx.y * batch * A.g.m, blockIdx.x, u_lo,
+                                    min(units, u_lo + units_per_split), smem);
 }
 
-__global__ void __launch_bounds__(kFinishThreads, 8)
-finish_xt16_fused_kernel(MfmaFused F, const uint16_t* __restrict__ XT, int nsplit, int y_dtype, int batch) {
+// Several matrices that share the batch X and the format (q/k/v, gate/up of a decoder block) in one grid: blockIdx.x
+// counts the groups of all matrices.  Every workgroup does exactly what it would do in a launch of its own matrix.
+struct BatchFusedItem {
+  DevMatrix A;
+  float* P;                                  // partial results
+  void* Y;
+  int groups;
+};
+struct BatchFused {
+  int count;
+  BatchFusedItem it[SPQR_MAX_FUSED];
+};
+
+template <int W, int TR, int TC, int AXIS>
+__global__ void __launch_bounds__(256, 2)
+batch_group_fused_kernel(BatchFused F, const uint16_t* __restrict__ X, int batch, int units_per_split) {
+  extern __shared__ __align__(16) uint8_t smem[];
   int bx = blockIdx.x, i = 0;
   for (; i < F.count - 1; ++i) {             // workgroup-uniform
-    if (bx < F.it[i].blocks16) break;
-    bx -= F.it[i].blocks16;
+    if (bx < F.it[i].groups) break;
+    bx -= F.it[i].groups;
   }
-  const MfmaFusedItem& it = F.it[i];
-  finish_xt16_body(it.A, XT, it.slots, it.P, nsplit, (int64_t)batch * it.A.g.m, it.long_row, it.Y, y_dtype, batch, bx);
+  const BatchFusedItem& it = F.it[i];
+  const int units = (it.A.g.ntc + kUnitTiles - 1) / kUnitTiles, u_lo = blockIdx.y * units_per_split;
+  batch_group_body<W, TR, TC, AXIS>(it.A, X, batch, it.P + (int64_t)blockIdx.y * batch * it.A.g.m, bx, u_lo,
+                                    min(units, u_lo + units_per_split), smem);
 }
 
-// ---- batches above 4 on 16x16 tiles: matrix-core dense pass + outlier pass ----
-// Steps per workgroup of the dense pass, chosen by simulating the launch: the workgroups start in grid order
+// Y[v][row] = sum over the splits of P, in their order, rounded once to the output type.  One workgroup per group of
+// 16 strips and vector, a thread per row of the group: the splits are read in the order they were
+// written, the rows leave in their own.
+__device__ __forceinline__ void sum_groups_body(const Geometry& g, const float* __restrict__ P, int splits, int batch,
+                                                void* __restrict__ Y, int y_dtype, int group) {
+  __shared__ float rows[256];
+  const int TR = lane_rows(g.tile_rows), strips = min(16, g.m / TR - group * 16), live = strips * TR;
+  const int t = threadIdx.x, v = blockIdx.y;
+  if (t < live) {
+    const float* p = P + (int64_t)batch * group * 16 * TR + v * live + t;
+    const int64_t stride = (int64_t)batch * g.m;
+    float s = p[0];
+#pragma unroll 4
+    for (int k = 1; k < splits; ++k) s += p[k * stride];
+    rows[(t % strips) * TR + t / strips] = s;
+  }
+  __syncthreads();
+  if (t < live) {
+    const int64_t at = (int64_t)v * g.m + group * 16 * TR + t;
+    if (y_dtype == SPQR_F32) static_cast<float*>(Y)[at] = rows[t];
+    else static_cast<uint16_t*>(Y)[at] = f2h_rne(rows[t]);
+  }
+}
+__global__ void __launch_bounds__(256)
+sum_groups_kernel(Geometry g, const float* __restrict__ P, int splits, int batch, void* __restrict__ Y, int y_dtype) {
+  sum_groups_body(g, P, splits, batch, Y, y_dtype, blockIdx.x);
+}
+__global__ void __launch_bounds__(256) sum_groups_fused_kernel(BatchFused F, int splits, int batch, int y_dtype) {
+  int bx = blockIdx.x, i = 0;
+  for (; i < F.count - 1; ++i) {             // workgroup-uniform
+    if (bx < F.it[i].groups) break;
+    bx -= F.it[i].groups;
+  }
+  sum_groups_body(F.it[i].A.g, F.it[i].P, splits, batch, F.it[i].Y, y_dtype, bx);
+}
+
+// XP[v][j] = X[v][perm[j]]: the batch in the matrix's column order (act-order checkpoints, Sec. 5).
+__global__ void __launch_bounds__(256)
+permute_batch_kernel(const uint16_t* __restrict__ X, const int32_t* __restrict__ perm, uint16_t* __restrict__ XP, int n,
+                     int batch) {
+  const int j = blockIdx.x * 256 + threadIdx.x;
+  if (j >= n) return;
+  const int src = min(max(perm[j], 0), n - 1);
+  for (int v = 0; v < batch; ++v) XP[(int64_t)v * n + j] = X[(int64_t)v * n + src];
+}
+
+// Steps per workgroup of a split launch with workgroups of unequal cost beside it, chosen by simulating the launch
+// (plan_batch_steps, a test hook; launches of equal workgroups: batch_units_per_split): the workgroups start in grid order
 // (split by split: the strip groups, behind those of the first split the long-row workgroups) on the first free of
 // the chip's workgroup slots; a dense workgroup costs its steps plus a start-up of 0.3 step, a long-row workgroup
 // 0.45 step, and every split 0.3 step for its partial result (written, and read again by the finishing kernel).
@@ -764,14 +737,6 @@ static hipError_t scratch_put(Scratch* sc, hipStream_t stream) {
   return e;
 }
 
-// Workgroups for the long outlier rows of a matrix: each owns an equal share of the entries (see long_rows_block)
-// and pays a look at the row pointers whether its share holds long rows or not: one per strip of 16 rows, 128 at most.
-static int long_row_workgroups(const DevMatrix& A) {
-  if (A.nnz <= 0) return 0;
-  const int strips = (A.g.m + 15) / 16;
-  return strips < kCUs / 2 ? strips : kCUs / 2;
-}
-
 static int mfma_steps_per_split(int groups, int nsteps, int slots1, int slots, int nlong) {
   if (const int v = option(SPQR_OPT_BATCH_STEPS); v >= 1) return v < nsteps ? v : nsteps;   // pinned (tuning, tests)
   struct Known { int groups, nsteps, slots1, slots, nlong, best; };
@@ -801,86 +766,89 @@ int plan_batch_steps(int groups, int nsteps, int slots_one_step, int slots, int 
   return mfma_steps_per_split(groups, nsteps, slots_one_step, slots, long_workgroups);
 }
 
-// Transposition, dense pass (with the long outlier rows beside it) and finishing pass.  Scratch (the batch
-// transposed, (n+1) x 32 bytes, the sums of the long outlier rows, 64 bytes per 256 outliers, the batch in the
-// matrix's column order if there is a permutation, and the partial results when the steps are split or the
-// output is binary16): see scratch_get.
+// Groups of 16 strips of a matrix, and the units of its columns the splits are made of.
+static int batch_groups(const Geometry& g) { return (g.m / lane_rows(g.tile_rows) + 15) / 16; }
+static int batch_units(const Geometry& g) { return (g.ntc + kUnitTiles - 1) / kUnitTiles; }
+
+// Units per split for `groups` groups of this format, by a model of the launch in microseconds fitted to sweeps of the
+// units (4096^2 to 20480 x 5120 with 3-bit codes, 17920 x 6656, three of 6656^2 and 8192 x 22016, 4 to 16 vectors): a CU's
+// one workgroup takes 2.3 per unit, two take 4.4 together, another piece of XT (outliers only) costs 4.5, a workgroup
+// 1, a further round of the chip's 512 places 3.  Measured, chosen against next best: 11008 x 4096 at 16 vectors, 3 units
+// 22.2 us (258 workgroups) against 4 units 23.9 and 2 units 26.1; 17920 x 6656, 4 units 47 against 5 units 51; 13824 x
+// 5120, 5 units 27.3 against 3 units 30.2; 5120^2, 2 units 18.5 against 1 unit 21.1.  The partial results stay below
+// 16 MB: beyond that the columns are not split (so many rows fill the chip by themselves).
+static int batch_units_per_split(const Geometry& g, int groups, bool sparse, int64_t values) {
+  const int units = batch_units(g), chunk = 1536 / (kUnitTiles * g.tile_cols);
+  if (const int v = option(SPQR_OPT_BATCH_STEPS); v >= 1) return v < units ? v : units;   // pinned (tuning, tests)
+  const int64_t most = values > 0 ? ((int64_t)4 << 20) / values : 1;       // splits of `values` floats each
+  int best = units;
+  double best_cost = 1e30;
+  for (int s = 1; s <= units && (s == 1 || s <= most); ++s) {
+    const int per = (units + s - 1) / s, splits = (units + per - 1) / per;
+    const int64_t wgs = (int64_t)groups * splits, k = wgs <= 8 ? 1 : (wgs - 8 + kCUs - 1) / kCUs;   // on the fullest CU
+    const double pieces = sparse ? 4.5 * ((per + chunk - 1) / chunk - 1) : 0.0;
+    const double one = 1.0 + 2.3 * per + pieces, two = 2.0 + 4.4 * per + pieces;
+    const double cost = (double)(k / 2) * two + (double)(k % 2) * one + 3.0 * (double)((k + 1) / 2 - 1);
+    if (cost < best_cost - 1e-9) { best_cost = cost; best = per; }
+  }
+  return best;
+}
+
+static size_t up256(size_t v) { return (v + 255) & ~(size_t)255; }
+
+template <typename Kernel>
+static hipError_t allow_lds(Kernel k, int bytes, PerDevice& ready) {
+  const int dev = current_device();
+  if (ready.get(dev)) return hipSuccess;
+  const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k), hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+  if (e == hipSuccess) ready.set(dev, 1);
+  return e;
+}
+
+// Takes `bytes` of scratch from the caller's workspace or the library.
+static hipError_t batch_scratch(const Workspace& ws, size_t bytes, hipStream_t stream, bool allow_stream_ordered, Scratch* sc,
+                                uint8_t** p) {
+  if (ws.from_caller) {                      // nothing is allocated, freed or waited for
+    if (ws.p == nullptr || ws.bytes < bytes) return hipErrorOutOfMemory;
+    *p = ws.p;
+    return hipSuccess;
+  }
+  if (scratch_get(sc, bytes, current_device(), stream, allow_stream_ordered) != hipSuccess) return hipErrorNotSupported;
+  *p = sc->p;
+  return hipSuccess;
+}
+
+// Scratch: the partial results and, with a permutation, the batch in the matrix's column order: see scratch_get.
 // hipErrorNotSupported = no scratch to be had; the caller takes the vector path.
 template <int W, int TR, int TC, int AXIS>
 static hipError_t launch_mfma_t(const DevMatrix& A, const uint16_t* X, int b, void* Y, int y_dtype, hipStream_t stream,
                                 const Workspace& ws) {
-  using SH = MfmaShape<TR, TC>;
+  using SH = BatchShape<TR, TC>;
   const Geometry& g = A.g;
   static PerDevice ready;
-  const int dev = current_device();
-  if (!ready.get(dev)) {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_mfma_kernel<W, TR, TC, AXIS>),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)SH::LDS);
-    if (e != hipSuccess) return e;
-    ready.set(dev, 1);
-  }
-  const int groups = (g.ntr + SH::NS - 1) / SH::NS;
-  const int nsteps = (g.ntc + 63) / 64;
-  const bool sparse = A.nnz > 0, permuted = A.perm != nullptr;
-  constexpr int kNT = 64 * SH::NS;
-  const int extra = long_row_workgroups(A);
-  // the one-step variant fits three workgroups on a CU while the staged batch rows leave the LDS for them
-  const int wgs1 = (TC != 32 && 3 * ((size_t)SH::NS * 64 * kMfmaTileStride * 4 + (size_t)b * SH::XROW + 1024) <= 160 * 1024) ? 3 : SH::WGS;
-  const int steps_per_split = mfma_steps_per_split(groups, nsteps, wgs1 * kCUs, SH::WGS * kCUs, extra);
-  const int nsplit = (nsteps + steps_per_split - 1) / steps_per_split;
-  // the dense kernel writes Y itself (16 bytes per store) if nothing has to be added or converted afterwards
-  const bool direct = nsplit == 1 && y_dtype == SPQR_F32 && reinterpret_cast<uintptr_t>(Y) % 16 == 0;
-  auto up = [](size_t v) { return (v + 255) & ~(size_t)255; };
-  const size_t xt_bytes = sparse ? up(((size_t)g.n + 1) * 32) : 0;   // one more row: zeros
-  const size_t slot_bytes = sparse ? up(((size_t)(A.nnz / kSlotGrain) + 2) * 64) : 0;
-  const size_t xp_bytes = permuted ? up((size_t)b * g.n * 2) : 0;
-  const size_t part_bytes = direct ? 0 : (size_t)nsplit * b * g.m * sizeof(float);
+  hipError_t e = allow_lds(&batch_group_kernel<W, TR, TC, AXIS>, SH::LDS, ready);
+  if (e != hipSuccess) return e;
+  const int groups = batch_groups(g), units = batch_units(g);
+  const int per = batch_units_per_split(g, groups, A.nnz > 0, (int64_t)b * g.m), splits = (units + per - 1) / per;
+  const size_t xp_bytes = A.perm != nullptr ? up256((size_t)b * g.n * 2) : 0;
   Scratch sc;
   uint8_t* scratch = nullptr;
-  if (const size_t need = xt_bytes + slot_bytes + xp_bytes + part_bytes; need > 0) {
-    if (ws.from_caller) {                    // nothing is allocated, freed or waited for
-      if (ws.p == nullptr || ws.bytes < need) return hipErrorOutOfMemory;
-      scratch = ws.p;
-    } else {
-      if (scratch_get(&sc, need, dev, stream) != hipSuccess) return hipErrorNotSupported;
-      scratch = sc.p;
-    }
+  e = batch_scratch(ws, xp_bytes + (size_t)splits * b * g.m * sizeof(float), stream, true, &sc, &scratch);
+  if (e != hipSuccess) return e;
+  float* P = reinterpret_cast<float*>(scratch + xp_bytes);
+  const uint16_t* Xin = X;
+  if (A.perm != nullptr) {
+    uint16_t* xp = reinterpret_cast<uint16_t*>(scratch);
+    hipLaunchKernelGGL(permute_batch_kernel, dim3((g.n + 255) / 256), dim3(256), 0, stream, X, A.perm, xp, g.n, b);
+    e = hipGetLastError();
+    Xin = xp;
   }
-  uint16_t* xt = sparse ? reinterpret_cast<uint16_t*>(scratch) : nullptr;
-  float* slots = reinterpret_cast<float*>(scratch + xt_bytes);
-  uint16_t* xp = permuted ? reinterpret_cast<uint16_t*>(scratch + xt_bytes + slot_bytes) : nullptr;
-  float* part = direct ? static_cast<float*>(Y) : reinterpret_cast<float*>(scratch + xt_bytes + slot_bytes + xp_bytes);
-  const int64_t split_stride = (int64_t)b * g.m;
-  // a row is long if it holds far more outliers than the average row (and at least kLongRowMin): rows like the
-  // average one stay with their strip's workgroup in the finishing kernel, whatever the outlier rate
-  const int64_t avg_row = A.nnz / (g.m > 0 ? g.m : 1);
-  const int long_row = (int)(4 * avg_row > kLongRowMin ? (4 * avg_row < (1 << 30) ? 4 * avg_row : (1 << 30)) : kLongRowMin);
-  hipError_t e = hipSuccess;
-  if (sparse || permuted) {
-    hipLaunchKernelGGL(transpose_x16_kernel, dim3((g.n + 256) / 256), dim3(256), 0, stream, X, A.perm, xt, xp, g.n, b);
+  if (e == hipSuccess) {
+    hipLaunchKernelGGL((batch_group_kernel<W, TR, TC, AXIS>), dim3(groups, splits), dim3(256), SH::LDS, stream, A, Xin, b, P, per);
     e = hipGetLastError();
   }
   if (e == hipSuccess) {
-    if (steps_per_split == 1) {
-      static PerDevice ready1;
-      if (!ready1.get(dev)) {
-        e = hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_mfma_one_kernel<W, TR, TC, AXIS>),
-                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)SH::LDS);
-        if (e == hipSuccess) ready1.set(dev, 1);
-      }
-      const size_t lds_now = (size_t)SH::NS * 64 * kMfmaTileStride * 4 + (size_t)b * SH::XROW;   // only b rows of X are staged
-      if (e == hipSuccess)
-        hipLaunchKernelGGL((gemm_mfma_one_kernel<W, TR, TC, AXIS>), dim3(groups + extra, nsplit), dim3(kNT), lds_now,
-                           stream, A, permuted ? xp : X, part, split_stride, b, xt, slots, long_row, groups);
-    } else {
-      hipLaunchKernelGGL((gemm_mfma_kernel<W, TR, TC, AXIS>), dim3(groups + extra, nsplit), dim3(kNT), SH::LDS,
-                         stream, A, permuted ? xp : X, part, split_stride, steps_per_split, b, xt, slots, long_row, groups);
-    }
-    if (e == hipSuccess) e = hipGetLastError();
-  }
-  if (e == hipSuccess && (sparse || !direct)) {
-    hipLaunchKernelGGL(finish_xt16_kernel, dim3((g.m + 15) / 16), dim3(kFinishThreads), 0, stream, A, xt, slots, part, nsplit,
-                       split_stride, long_row, Y, y_dtype, b);
+    hipLaunchKernelGGL(sum_groups_kernel, dim3(groups, b), dim3(SH::ROWS), 0, stream, g, P, splits, b, Y, y_dtype);
     e = hipGetLastError();
   }
   const hipError_t ef = scratch_put(&sc, stream);
@@ -915,94 +883,49 @@ bool stream_is_capturing(hipStream_t stream) {
 template <int W, int TR, int TC, int AXIS>
 static hipError_t launch_mfma_fused_t(const DevMatrix* As, int count, const uint16_t* X, int b, void* const* Ys, int y_dtype,
                                       hipStream_t stream, const Workspace& ws) {
-  using SH = MfmaShape<TR, TC>;
+  using SH = BatchShape<TR, TC>;
   const Geometry& g0 = As[0].g;
   static PerDevice ready;
-  const int dev = current_device();
-  if (!ready.get(dev)) {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_mfma_fused_kernel<W, TR, TC, AXIS, false>),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)SH::LDS);
-    if (e == hipSuccess)
-      e = hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_mfma_fused_kernel<W, TR, TC, AXIS, true>),
-                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)SH::LDS);
-    if (e != hipSuccess) return e;
-    ready.set(dev, 1);
-  }
-  constexpr int kNT = 64 * SH::NS;
-  const int nsteps = (g0.ntc + 63) / 64;
-  int total_groups = 0, total_extra = 0, extras[SPQR_MAX_FUSED];
+  hipError_t e = allow_lds(&batch_group_fused_kernel<W, TR, TC, AXIS>, SH::LDS, ready);
+  if (e != hipSuccess) return e;
+  BatchFused F;
+  F.count = count;
+  int groups = 0;
+  int64_t rows = 0;
   bool sparse = false;
   for (int i = 0; i < count; ++i) {
-    const Geometry& g = As[i].g;
-    total_groups += (g.ntr + SH::NS - 1) / SH::NS;
+    F.it[i].A = As[i];
+    F.it[i].Y = Ys[i];
+    F.it[i].groups = batch_groups(As[i].g);
+    groups += F.it[i].groups;
+    rows += As[i].g.m;
     sparse = sparse || As[i].nnz > 0;
-    extras[i] = long_row_workgroups(As[i]);
-    total_extra += extras[i];
   }
-  const int wgs1 = (TC != 32 && 3 * ((size_t)SH::NS * 64 * kMfmaTileStride * 4 + (size_t)b * SH::XROW + 1024) <= 160 * 1024) ? 3 : SH::WGS;
-  const int steps_per_split = mfma_steps_per_split(total_groups, nsteps, wgs1 * kCUs, SH::WGS * kCUs, total_extra);
-  const int nsplit = (nsteps + steps_per_split - 1) / steps_per_split;
-  const bool permuted = As[0].perm != nullptr;
-  bool direct = nsplit == 1 && y_dtype == SPQR_F32;              // the dense kernel writes the outputs itself (16-byte stores)
-  for (int i = 0; i < count; ++i) direct = direct && reinterpret_cast<uintptr_t>(Ys[i]) % 16 == 0;
-  auto up = [](size_t v) { return (v + 255) & ~(size_t)255; };
-  const size_t xt_bytes = sparse ? up(((size_t)g0.n + 1) * 32) : 0;
-  const size_t xp_bytes = permuted ? up((size_t)b * g0.n * 2) : 0;
-  size_t total = xt_bytes + xp_bytes, slot_off[SPQR_MAX_FUSED], part_off[SPQR_MAX_FUSED];
+  const int units = batch_units(g0), per = batch_units_per_split(g0, groups, sparse, (int64_t)b * rows);
+  const int splits = (units + per - 1) / per;
+  size_t total = As[0].perm != nullptr ? up256((size_t)b * g0.n * 2) : 0, at[SPQR_MAX_FUSED];
   for (int i = 0; i < count; ++i) {
-    slot_off[i] = total;
-    total += As[i].nnz > 0 ? up(((size_t)(As[i].nnz / kSlotGrain) + 2) * 64) : 0;
-    part_off[i] = total;
-    total += direct ? 0 : up((size_t)nsplit * b * As[i].g.m * sizeof(float));
+    at[i] = total;
+    total += up256((size_t)splits * b * As[i].g.m * sizeof(float));
   }
   Scratch sc;
   uint8_t* scratch = nullptr;
-  if (total > 0) {
-    if (ws.from_caller) {
-      if (ws.p == nullptr || ws.bytes < total) return hipErrorOutOfMemory;
-      scratch = ws.p;
-    } else {
-      if (scratch_get(&sc, total, dev, stream, false) != hipSuccess) return hipErrorNotSupported;
-      scratch = sc.p;
-    }
+  e = batch_scratch(ws, total, stream, false, &sc, &scratch);
+  if (e != hipSuccess) return e;
+  for (int i = 0; i < count; ++i) F.it[i].P = reinterpret_cast<float*>(scratch + at[i]);
+  const uint16_t* Xin = X;
+  if (As[0].perm != nullptr) {
+    uint16_t* xp = reinterpret_cast<uint16_t*>(scratch);
+    hipLaunchKernelGGL(permute_batch_kernel, dim3((g0.n + 255) / 256), dim3(256), 0, stream, X, As[0].perm, xp, g0.n, b);
+    e = hipGetLastError();
+    Xin = xp;
   }
-  uint16_t* xt = sparse ? reinterpret_cast<uint16_t*>(scratch) : nullptr;
-  uint16_t* xp = permuted ? reinterpret_cast<uint16_t*>(scratch + xt_bytes) : nullptr;
-  MfmaFused F;
-  F.count = count;
-  int dense_blocks = 0, extra_blocks = 0, finish_blocks = 0;
-  for (int i = 0; i < count; ++i) {
-    MfmaFusedItem& it = F.it[i];
-    const Geometry& g = As[i].g;
-    it.A = As[i];
-    it.Y = Ys[i];
-    it.P = direct ? static_cast<float*>(Ys[i]) : reinterpret_cast<float*>(scratch + part_off[i]);
-    it.slots = reinterpret_cast<float*>(scratch + slot_off[i]);
-    const int64_t avg_row = As[i].nnz / (g.m > 0 ? g.m : 1);
-    it.long_row = (int)(4 * avg_row > kLongRowMin ? (4 * avg_row < (1 << 30) ? 4 * avg_row : (1 << 30)) : kLongRowMin);
-    it.groups = (g.ntr + SH::NS - 1) / SH::NS;
-    it.extra = extras[i];
-    it.blocks16 = (g.m + 15) / 16;
-    dense_blocks += it.groups;
-    extra_blocks += it.extra;
-    finish_blocks += it.blocks16;
-  }
-  hipError_t e = hipSuccess;
-  if (sparse || permuted) {
-    hipLaunchKernelGGL(transpose_x16_kernel, dim3((g0.n + 256) / 256), dim3(256), 0, stream, X, As[0].perm, xt, xp, g0.n, b);
+  if (e == hipSuccess) {
+    hipLaunchKernelGGL((batch_group_fused_kernel<W, TR, TC, AXIS>), dim3(groups, splits), dim3(256), SH::LDS, stream, F, Xin, b, per);
     e = hipGetLastError();
   }
   if (e == hipSuccess) {
-    if (steps_per_split == 1)                // the variant without the second tile; only b rows of X are staged
-      hipLaunchKernelGGL((gemm_mfma_fused_kernel<W, TR, TC, AXIS, true>), dim3(dense_blocks + extra_blocks, nsplit), dim3(kNT),
-                         (size_t)SH::NS * 64 * kMfmaTileStride * 4 + (size_t)b * SH::XROW, stream, F, permuted ? xp : X, 1, b, xt);
-    else
-      hipLaunchKernelGGL((gemm_mfma_fused_kernel<W, TR, TC, AXIS, false>), dim3(dense_blocks + extra_blocks, nsplit), dim3(kNT),
-                         SH::LDS, stream, F, permuted ? xp : X, steps_per_split, b, xt);
-    e = hipGetLastError();
-  }
-  if (e == hipSuccess && (sparse || !direct)) {
-    hipLaunchKernelGGL(finish_xt16_fused_kernel, dim3(finish_blocks), dim3(kFinishThreads), 0, stream, F, xt, nsplit, y_dtype, b);
+    hipLaunchKernelGGL(sum_groups_fused_kernel, dim3(groups, b), dim3(SH::ROWS), 0, stream, F, splits, b, y_dtype);
     e = hipGetLastError();
   }
   const hipError_t ef = scratch_put(&sc, stream);
@@ -1014,52 +937,30 @@ static hipError_t launch_mfma_fused_t(const DevMatrix* As, int count, const uint
   CASE(3, 16, 16, 1) CASE(3, 16, 16, 0) CASE(4, 16, 16, 1) CASE(4, 16, 16, 0) \
   CASE(3, 8, 32, 1) CASE(4, 8, 32, 1) CASE(3, 32, 8, 0) CASE(4, 32, 8, 0)
 
-// Upper bound of the scratch a batch of b <= 16 vectors needs on this path (the launchers need less when the dense
-// kernel can write the output itself): for one matrix alone, and for `count` matrices in one fused launch set.
-template <int TR, int TC>
-static size_t mfma_scratch_bound(const DevMatrix* As, int count, int b, bool fused) {
-  using SH = MfmaShape<TR, TC>;
-  auto up = [](size_t v) { return (v + 255) & ~(size_t)255; };
-  const Geometry& g0 = As[0].g;
-  const int nsteps = (g0.ntc + 63) / 64;
-  const int wgs1 = (TC != 32 && 3 * ((size_t)SH::NS * 64 * kMfmaTileStride * 4 + (size_t)b * SH::XROW + 1024) <= 160 * 1024) ? 3 : SH::WGS;
-  int total_groups = 0, total_extra = 0;
-  bool sparse = false;
-  for (int i = 0; i < count; ++i) {
-    total_groups += (As[i].g.ntr + SH::NS - 1) / SH::NS;
-    total_extra += long_row_workgroups(As[i]);
-    sparse = sparse || As[i].nnz > 0;
-  }
+// Scratch a batch of b <= 16 vectors needs on this path: for the matrices one at a time and, if `fused`, all of them in
+// one launch set.
+size_t mfma_workspace_bound(const DevMatrix* As, int count, int b, bool fused) {
+  const int units = batch_units(As[0].g);
+  const size_t xp = As[0].perm != nullptr ? up256((size_t)b * As[0].g.n * 2) : 0;
   size_t worst = 0;
-  if (fused) {
-    const int s = mfma_steps_per_split(total_groups, nsteps, wgs1 * kCUs, SH::WGS * kCUs, total_extra);
-    const int nsplit = (nsteps + s - 1) / s;
-    size_t total = (sparse ? up(((size_t)g0.n + 1) * 32) : 0) + (As[0].perm ? up((size_t)b * g0.n * 2) : 0);
-    for (int i = 0; i < count; ++i)
-      total += (As[i].nnz > 0 ? up(((size_t)(As[i].nnz / kSlotGrain) + 2) * 64) : 0) +
-               up((size_t)nsplit * b * As[i].g.m * sizeof(float));
-    worst = total;
-  }
   for (int i = 0; i < count; ++i) {
-    const DevMatrix& A = As[i];
-    const int groups = (A.g.ntr + SH::NS - 1) / SH::NS;
-    const int s = mfma_steps_per_split(groups, nsteps, wgs1 * kCUs, SH::WGS * kCUs, long_row_workgroups(A));
-    const int nsplit = (nsteps + s - 1) / s;
-    const size_t need = (A.nnz > 0 ? up(((size_t)A.g.n + 1) * 32) + up(((size_t)(A.nnz / kSlotGrain) + 2) * 64) : 0) +
-                        (A.perm ? up((size_t)b * A.g.n * 2) : 0) + up((size_t)nsplit * b * A.g.m * sizeof(float));
+    const int per = batch_units_per_split(As[i].g, batch_groups(As[i].g), As[i].nnz > 0, (int64_t)b * As[i].g.m);
+    const size_t need = xp + up256((size_t)((units + per - 1) / per) * b * As[i].g.m * sizeof(float));
     if (need > worst) worst = need;
   }
-  return worst;
-}
-
-size_t mfma_workspace_bound(const DevMatrix* As, int count, int b, bool fused) {
-  const Geometry& g = As[0].g;
-#define SPQR_MFMA_CASE(W_, TR_, TC_, AX_) \
-  if (g.w_bits == W_ && g.tile_rows == TR_ && g.tile_cols == TC_ && g.axis == AX_) \
-    return mfma_scratch_bound<TR_, TC_>(As, count, b, fused);
-  SPQR_MFMA_INSTANCES(SPQR_MFMA_CASE)
-#undef SPQR_MFMA_CASE
-  return 0;
+  if (!fused) return worst;
+  int groups = 0;
+  int64_t rows = 0;
+  bool sparse = false;
+  for (int i = 0; i < count; ++i) {
+    groups += batch_groups(As[i].g);
+    rows += As[i].g.m;
+    sparse = sparse || As[i].nnz > 0;
+  }
+  const int per = batch_units_per_split(As[0].g, groups, sparse, (int64_t)b * rows), splits = (units + per - 1) / per;
+  size_t total = xp;
+  for (int i = 0; i < count; ++i) total += up256((size_t)splits * b * As[i].g.m * sizeof(float));
+  return total > worst ? total : worst;
 }
 
 hipError_t launch_prefill_scratch(const DevMatrix& A, const uint16_t* X, int b, void* Y, int y_dtype, hipStream_t stream,
