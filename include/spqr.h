@@ -247,15 +247,18 @@ int spqr_gemv(const spqr_matrix_t* A, const uint16_t* x_f16, void* y, int y_dtyp
  * 10 us more per call), on further streams one from a pool of the library's
  * own.  If no scratch can be had, the slices of 4 run instead.  Callers that
  * must not allocate or synchronise use spqr_gemm_smallbatch_ws.
- * Large batches (48 vectors and more, 12 where no slices of 16 exist; the
- * prompt phase of Sec. 5 "Inference Time"; tiles of 256 codes in any layout
- * and 3-bit tiles of 8 x 64, Y 16-byte aligned): the matrix is
- * dequantised once into a dense binary16 copy in scratch (2 bytes per weight,
- * rows padded to a multiple of 64 columns; with a permutation b*n*2 bytes more),
- * the outliers are added into the copy, and one matrix-core kernel multiplies
- * the whole batch with it.  Where that much scratch cannot be had (a captured
- * call without a workspace, a workspace smaller than spqr_workspace_bytes says)
- * the slices of 16 run instead.
+ * Prompt-sized batches (33 vectors and more; Sec. 5 "Inference Time") of the same
+ * tile shapes take one pass over the weights: a workgroup dequantises them into
+ * LDS, adds the outliers there and multiplies all vectors with them (scratch: 4
+ * bytes per outlier, the partial sums, with a permutation b*n*2 bytes).
+ * Other formats (12 vectors and more; tiles of 256 codes in any layout and 3-bit
+ * tiles of 8 x 64, Y 16-byte aligned) and matrices with more outliers than one
+ * weight in four: the matrix is dequantised once into a dense binary16 copy in
+ * scratch (2 bytes per weight, rows padded to a multiple of 64 columns; with a
+ * permutation b*n*2 bytes more), the outliers are added into the copy, and one
+ * matrix-core kernel multiplies the whole batch with it.  Where that much
+ * scratch cannot be had (a captured call without a workspace, a workspace smaller
+ * than spqr_workspace_bytes says) the slices of 16 run instead.
  * Results are deterministic (fixed summation order) on every path; the paths
  * differ by rounding only (all within the product tolerance).
  * X: [b][n] binary16 row-major.  Y: [b][m] of y_dtype, overwritten. */

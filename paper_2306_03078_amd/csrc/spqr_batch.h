@@ -1,0 +1,143 @@
+// What the matrix-core products of all batch sizes share: the part of a tile a lane holds when 16 lanes hold the same
+// tile column of 16 strips, and its dequantisation into operands of v_mfma_f32_16x16x32_f16.
+#pragma once
+#include <hip/hip_runtime.h>
+#include <stdint.h>
+
+#include "spqr_tile.h"
+
+namespace spqr {
+
+typedef _Float16 half8_t __attribute__((ext_vector_type(8)));
+typedef float float4_t __attribute__((ext_vector_type(4)));
+
+constexpr int kUnitTiles = 16;               // tile columns of a unit of the split: one step of 4 for each of 4 wavefronts
+// Rows a lane multiplies: its tile's 8 or 16; a tile of 32 rows is taken as two of 16 (128 accumulators a lane spill), so
+// that the strips of the kernel are 8 or 16 rows in every format.
+constexpr int lane_rows(int tile_rows) { return tile_rows == 32 ? 16 : tile_rows; }
+
+// What a lane holds of its tile: the codes of its rows (a tile of 32 rows: of one half) and the tile's statistics.
+template <int W, int TR, int TC, int AXIS> struct BatchTile {
+  using T = TileRegs<W, TR, TC, AXIS>;
+  static constexpr int KW = T::KW * lane_rows(TR) / TR;
+  uint32_t c[4 * KW];
+  uint32_t s[T::SD];
+};
+
+// `blk` and L (the block and its tiles) are uniform, `l` is the lane's tile in it, `off` the lane's strip's byte offset,
+// `half` (tiles of 32 rows) which rows.
+template <int W, int TR, int TC, int AXIS>
+__device__ __forceinline__ void load_batch_tile(BatchTile<W, TR, TC, AXIS>& t, const uint8_t* blk, int L, uint32_t off,
+                                                uint32_t l, int half) {
+  using B = BatchTile<W, TR, TC, AXIS>;
+  using T = typename B::T;
+  const uint32_t off16 = off + 16u * l, off4 = off + 4u * l;
+  const uint8_t* sb = blk + 16 * T::KW * L;
+#pragma unroll
+  for (int k = 0; k < T::SWF; ++k) {
+    const u32x4 v = *reinterpret_cast<const u32x4*>(sb + 16 * k * L + off16);
+    t.s[4 * k] = v.x; t.s[4 * k + 1] = v.y; t.s[4 * k + 2] = v.z; t.s[4 * k + 3] = v.w;
+  }
+  const uint8_t* rb = sb + 16 * T::SWF * L;
+#pragma unroll
+  for (int k = 0; k < T::SR; ++k) t.s[4 * T::SWF + k] = *reinterpret_cast<const uint32_t*>(rb + 4 * k * L + off4);
+  const uint32_t offc = B::KW == T::KW ? off16 : off16 + (half ? 16u * B::KW * (uint32_t)L : 0u);
+#pragma unroll
+  for (int k = 0; k < B::KW; ++k) {
+    const u32x4 v = *reinterpret_cast<const u32x4*>(blk + 16 * k * L + offc);
+    t.c[4 * k] = v.x; t.c[4 * k + 1] = v.y; t.c[4 * k + 2] = v.z; t.c[4 * k + 3] = v.w;
+  }
+}
+
+// Dequantisation of a lane's rows, 8 columns at a time: w = s_hat * (q - z_hat) in one binary32 FMA, rounded once to
+// binary16.  With the extracted codes 1 + q/2^W and 1 + code/8 of the statistics:
+//   w = fa*(1 + q/2^W) + fb with fa = 2^W*s_hat, fb = -s_hat*(2^W + z_hat), per group, where s_hat = s_s*(s_q - z_s) and
+//   z_hat = s_z*(z_q - z_z):  fa = c1*(1 + s_q/8) + c2,   -(2^W + z_hat)/2^W = e1*(1 + z_q/8) + e2,   fb = fa * that.
+template <int W, int TR, int TC, int AXIS> struct Dequant {
+  using B = BatchTile<W, TR, TC, AXIS>;
+  using T = typename B::T;
+  static constexpr int LR = lane_rows(TR), NSUB = TR / LR;    // rows of a lane; strips of the kernel per strip of tiles
+  static constexpr int PPR = TC / 2, KG = TC / 8;             // code pairs per row; blocks of 8 columns
+  static constexpr int NG = AXIS == 1 ? TC : LR;              // first-level groups of a lane
+  // Groups along the tile's columns: the offset K that the in-place extraction of a code leaves (its class, see CodeClass)
+  // folds into the column's additive constant, and most shifts go away.  The class is a function of the pair's column,
+  // for 3-bit codes in rows of 8 pairs of the column and the parity of the row.
+  static constexpr bool FOLD = AXIS == 1;
+  static constexpr int NK = FOLD && W == 3 && PPR == 8 ? 2 : 1;
+  static constexpr int NF = AXIS == 1 ? 8 : NG;               // groups whose constants are alive at a time
+  static constexpr float SCALE = (float)(1 << W);
+  PairConsts kc, k3;
+  ClassConsts kk;
+  int half;                                                   // which rows of a tile of 32
+  float c1, c2, e1, e2;                                       // of the current tile
+  float fa[NF], fb[NK][NF];
+
+  __device__ __forceinline__ Dequant(int half_) : half(half_) {
+    kc = make_pair_consts<W>();
+    k3 = make_pair_consts<3>();
+    kk = make_class_consts<W>();
+  }
+  // A lane without a tile of its own (live = false) gets zero weights.
+  __device__ __forceinline__ void begin(const B& t, bool live) {
+    const uint32_t a2 = t.s[T::SD - 2], b2 = t.s[T::SD - 1];
+    const float s_s = h2f((uint16_t)(a2 & 0xFFFF)), z_s = h2f((uint16_t)(a2 >> 16));
+    const float s_z = h2f((uint16_t)(b2 & 0xFFFF)), z_z = h2f((uint16_t)(b2 >> 16));
+    c1 = live ? SCALE * 8.f * s_s : 0.f;
+    c2 = live ? SCALE * (-s_s * z_s - 8.f * s_s) : 0.f;
+    e1 = -8.f * s_z / SCALE;
+    e2 = -(SCALE - s_z * z_z - 8.f * s_z) / SCALE;
+    if constexpr (AXIS == 0) {
+#pragma unroll
+      for (int p = 0; p < NG / 2; ++p) group_pair(t, p, 2 * p);
+    }
+  }
+  // The constants of columns 8j .. 8j+7 (groups along the columns; groups along the rows have theirs from begin()).
+  __device__ __forceinline__ void columns(const B& t, int j) {
+    if constexpr (AXIS == 1) {
+#pragma unroll
+      for (int d = 0; d < 4; ++d) group_pair(t, 4 * j + d, 2 * d);
+    }
+  }
+  // Row r, columns 8j + 2d and 8j + 2d + 1: a quarter of an operand.
+  __device__ __forceinline__ uint32_t pair(const B& t, int r, int j, int d) const {
+    const int q = r * PPR + 4 * j + d;
+    const half2_t q2 = as_half2(FOLD ? pair_class_inline<W>(t.c, q, kk) : pair_f16<W>(t.c, q, kc));
+    const int g0 = AXIS == 1 ? 2 * d : r, g1 = AXIS == 1 ? 2 * d + 1 : r;
+    half2_t w;
+    w.x = (_Float16)fmaf((float)q2.x, fa[g0], fb[r % NK][g0]);
+    w.y = (_Float16)fmaf((float)q2.y, fa[g1], fb[r % NK][g1]);
+    return __builtin_bit_cast(uint32_t, w);
+  }
+  // Row r, columns 8j .. 8j+7 as an operand.
+  __device__ __forceinline__ half8_t operand(const B& t, int r, int j) const {
+    const uint32_t o[4] = {pair(t, r, j, 0), pair(t, r, j, 1), pair(t, r, j, 2), pair(t, r, j, 3)};
+    return __builtin_bit_cast(half8_t, o);
+  }
+
+ private:
+  __device__ __forceinline__ void group_pair(const B& t, int p, int at) {    // groups 2p and 2p + 1 of the lane
+    uint32_t sp = pair_f16<3>(t.s, p, k3), zp = pair_f16<3>(t.s, T::B2 / 2 + p, k3);
+    if constexpr (NSUB == 2) {                 // the groups of the lane's half of the rows
+      sp = half ? pair_f16<3>(t.s, NG / 2 + p, k3) : sp;
+      zp = half ? pair_f16<3>(t.s, T::B2 / 2 + NG / 2 + p, k3) : zp;
+    }
+    const half2_t sq = as_half2(sp), zq = as_half2(zp);
+    fa[at] = fmaf((float)sq.x, c1, c2);
+    fa[at + 1] = fmaf((float)sq.y, c1, c2);
+    const float b0 = fa[at] * fmaf((float)zq.x, e1, e2), b1 = fa[at + 1] * fmaf((float)zq.y, e1, e2);
+    fb[0][at] = b0;
+    fb[0][at + 1] = b1;
+    if constexpr (FOLD) {                      // the extracted value is K + code/2^W instead of 1 + code/2^W
+      const float K0 = CodeClass<W, true>::K(CodeClass<W, true>::of_pair(p));   // constants once the loop is unrolled
+      fb[0][at] = fmaf(1.f - K0, fa[at], b0);
+      fb[0][at + 1] = fmaf(1.f - K0, fa[at + 1], b1);
+      if constexpr (NK == 2) {                 // odd rows
+        const float K1 = CodeClass<W, true>::K(CodeClass<W, true>::of_pair(PPR + p));
+        fb[NK - 1][at] = fmaf(1.f - K1, fa[at], b0);
+        fb[NK - 1][at + 1] = fmaf(1.f - K1, fa[at + 1], b1);
+      }
+    }
+  }
+};
+
+}  // namespace spqr

@@ -80,9 +80,15 @@ hipError_t static_workspace(Workspace* ws);
 // Steps of 64 tiles per workgroup of the batch path's dense launch (host arithmetic only, see the definition).
 int plan_batch_steps(int groups, int nsteps, int slots_one_step, int slots, int long_workgroups);
 
-// Large batches through a dense binary16 copy of the matrix (spqr_prefill.hip) on the library's scratch or the
+// The sums over the splits of partial results in the order the batch and prompt kernels write them.
+hipError_t launch_sum_groups(const Geometry& g, const float* P, int splits, int b, void* Y, int y_dtype, hipStream_t stream);
+
+// Prompt-sized batches (spqr_prompt.hip) and large batches through a dense binary16 copy of the matrix
+// (spqr_prefill.hip) on the library's scratch or the
 // caller's workspace.  hipErrorNotSupported: no scratch of that size to be had (or the stream is being captured
 // and the library would have to allocate it): the caller takes the slices of 16.
+hipError_t launch_prompt_scratch(const DevMatrix& A, const uint16_t* X, int b, void* Y, int y_dtype, hipStream_t stream,
+                                 const Workspace& ws);
 hipError_t launch_prefill_scratch(const DevMatrix& A, const uint16_t* X, int b, void* Y, int y_dtype, hipStream_t stream,
                                   const Workspace& ws);
 
@@ -93,6 +99,16 @@ size_t prefill_workspace_bytes(const DevMatrix& A, int b);
 // `scratch`: prefill_workspace_bytes(A, b) bytes, 256-byte aligned; Y 16-byte aligned.
 hipError_t launch_prefill(const DevMatrix& A, const uint16_t* X, int b, void* Y, int y_dtype, hipStream_t stream,
                           uint8_t* scratch);
+
+hipError_t launch_gather_x(const uint16_t* X, const int32_t* perm, uint16_t* XP, int n, int b, hipStream_t stream);
+
+// ---- spqr_prompt.hip: prompt-sized batches in one pass over the compressed weights ----
+bool prompt_has_instance(const DevMatrix& A);
+bool prompt_wanted(const DevMatrix& A, int b);
+size_t prompt_workspace_bytes(const DevMatrix& A, int b);
+// `scratch`: prompt_workspace_bytes(A, b) bytes, 256-byte aligned.
+hipError_t launch_prompt(const DevMatrix& A, const uint16_t* X, int b, void* Y, int y_dtype, hipStream_t stream,
+                         uint8_t* scratch);
 
 // ---- spqr_misc.hip: fallback product, debug decode, validation ----
 hipError_t launch_generic(const DevMatrix& A, const uint16_t* x, void* y, int y_dtype, hipStream_t stream);

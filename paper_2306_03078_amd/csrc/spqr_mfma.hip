@@ -8,7 +8,7 @@
 #include <vector>
 
 #include "../../include/spqr.h"
-#include "spqr_tile.h"
+#include "spqr_batch.h"
 #include "spqr_kernels.h"
 
 namespace spqr {
@@ -41,15 +41,7 @@ namespace spqr {
 // Without outliers 28 us.  Before (weights transposed through LDS quarter tile by quarter tile, outliers in a kernel of
 // their own that gathered from L2): 52 us; 8192 x 22016, 3-bit, 73 -> 64 us; three of 6656^2 at 4 vectors 52 -> 48 us.
 // ---------------------------------------------------------------------------
-typedef _Float16 half8_t __attribute__((ext_vector_type(8)));
-typedef float float4_t __attribute__((ext_vector_type(4)));
-
-constexpr int kUnitTiles = 16;               // tile columns of a unit of the split: one step of 4 for each of 4 wavefronts
 constexpr int kLongRow = 64;                 // entries of a row inside a piece beyond which a whole wavefront takes it
-
-// Rows a lane multiplies: its tile's 8 or 16; a tile of 32 rows is taken as two of 16 (128 accumulators a lane spill), so
-// that the strips of the kernel are 8 or 16 rows in every format.
-constexpr int lane_rows(int tile_rows) { return tile_rows == 32 ? 16 : tile_rows; }
 
 template <int TR, int TC> struct BatchShape {
   static constexpr int ROWS = 16 * lane_rows(TR);                    // rows of a group of 16 strips
@@ -63,39 +55,6 @@ template <int TR, int TC> struct BatchShape {
   static constexpr int LDS = SHARED + SUM * 64 + ROWS * 8;           // + sums of the outliers + row bounds
   static_assert(2 * LDS <= 160 * 1024, "two workgroups share a CU");
 };
-
-// What a lane holds of its tile: the codes of its rows (a tile of 32 rows: of one half) and the tile's statistics.
-template <int W, int TR, int TC, int AXIS> struct BatchTile {
-  using T = TileRegs<W, TR, TC, AXIS>;
-  static constexpr int KW = T::KW * lane_rows(TR) / TR;
-  uint32_t c[4 * KW];
-  uint32_t s[T::SD];
-};
-
-// `blk` and L (the block and its tiles) are uniform, `l` is the lane's tile in it, `off` the lane's strip's byte offset,
-// `half` (tiles of 32 rows) which rows.
-template <int W, int TR, int TC, int AXIS>
-__device__ __forceinline__ void load_batch_tile(BatchTile<W, TR, TC, AXIS>& t, const uint8_t* blk, int L, uint32_t off,
-                                                uint32_t l, int half) {
-  using B = BatchTile<W, TR, TC, AXIS>;
-  using T = typename B::T;
-  const uint32_t off16 = off + 16u * l, off4 = off + 4u * l;
-  const uint8_t* sb = blk + 16 * T::KW * L;
-#pragma unroll
-  for (int k = 0; k < T::SWF; ++k) {
-    const u32x4 v = *reinterpret_cast<const u32x4*>(sb + 16 * k * L + off16);
-    t.s[4 * k] = v.x; t.s[4 * k + 1] = v.y; t.s[4 * k + 2] = v.z; t.s[4 * k + 3] = v.w;
-  }
-  const uint8_t* rb = sb + 16 * T::SWF * L;
-#pragma unroll
-  for (int k = 0; k < T::SR; ++k) t.s[4 * T::SWF + k] = *reinterpret_cast<const uint32_t*>(rb + 4 * k * L + off4);
-  const uint32_t offc = B::KW == T::KW ? off16 : off16 + (half ? 16u * B::KW * (uint32_t)L : 0u);
-#pragma unroll
-  for (int k = 0; k < B::KW; ++k) {
-    const u32x4 v = *reinterpret_cast<const u32x4*>(blk + 16 * k * L + offc);
-    t.c[4 * k] = v.x; t.c[4 * k + 1] = v.y; t.c[4 * k + 2] = v.z; t.c[4 * k + 3] = v.w;
-  }
-}
 
 // Reduces 16 values per lane over the aligned group of 4 lanes: lane l of the group ends with values 4l .. 4l+3 in v[0..3].
 __device__ __forceinline__ void quad_scatter(float (&v)[16], int lane) {
@@ -163,17 +122,10 @@ template <int W, int TR, int TC, int AXIS>
 __device__ __forceinline__ void batch_group_body(const DevMatrix& A, const uint16_t* __restrict__ X, int batch,
                                                  float* __restrict__ P, int group, int u_lo, int u_hi, uint8_t* smem) {
   using SH = BatchShape<TR, TC>;
+  using DQ = Dequant<W, TR, TC, AXIS>;
   using B = BatchTile<W, TR, TC, AXIS>;
   using T = typename B::T;
-  constexpr int TILE_BYTES = 16 * T::KW + 4 * T::SD, ROWS = SH::ROWS, PPR = TC / 2, KG = TC / 8, SUM = SH::SUM;
-  constexpr int LR = lane_rows(TR), NSUB = TR / LR;           // rows of a lane; strips of the kernel per strip of tiles
-  constexpr int NG = AXIS == 1 ? TC : LR;                     // first-level groups of a lane
-  constexpr float SCALE = (float)(1 << W);
-  // Groups along the tile's columns: the offset K that the in-place extraction of a code leaves (its class, see CodeClass)
-  // folds into the column's additive constant, and most shifts go away.  The class is a function of the pair's column,
-  // for 3-bit codes in rows of 8 pairs of the column and the parity of the row.
-  constexpr bool FOLD = AXIS == 1;
-  constexpr int NK = FOLD && W == 3 && PPR == 8 ? 2 : 1;
+  constexpr int TILE_BYTES = 16 * T::KW + 4 * T::SD, ROWS = SH::ROWS, LR = DQ::LR, NSUB = DQ::NSUB, KG = DQ::KG, SUM = SH::SUM;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int i16 = lane & 15, g4 = lane >> 4;
   const int n = A.g.n, ntc = A.g.ntc, ntr = A.g.ntr * NSUB, m = A.g.m;
@@ -190,9 +142,7 @@ __device__ __forceinline__ void batch_group_body(const DevMatrix& A, const uint1
   const int my_strip = min(group * 16 + i16, ntr - 1) - group * 16, half = NSUB == 2 ? my_strip & 1 : 0;
   const uint32_t strip_off = (uint32_t)(my_strip / NSUB) * (uint32_t)ntc * TILE_BYTES;
   const uint32_t xrow = (uint32_t)min(i16, batch - 1) * (uint32_t)n * 2u;
-  const PairConsts kc = make_pair_consts<W>();
-  const PairConsts k3 = make_pair_consts<3>();
-  const ClassConsts kk = make_class_consts<W>();
+  DQ dq(half);
 
   float4_t D[LR];
 #pragma unroll
@@ -213,67 +163,15 @@ __device__ __forceinline__ void batch_group_body(const DevMatrix& A, const uint1
   };
   auto multiply = [&](const B& t, const u32x4 (&x)[KG], int u) {
     const bool live = 16 * u + 4 * wave + g4 < ntc;
-    const uint32_t a2 = t.s[T::SD - 2], b2 = t.s[T::SD - 1];
-    const float s_s = h2f((uint16_t)(a2 & 0xFFFF)), z_s = h2f((uint16_t)(a2 >> 16));
-    const float s_z = h2f((uint16_t)(b2 & 0xFFFF)), z_z = h2f((uint16_t)(b2 >> 16));
-    // w = s_hat*(q - z_hat) = fa*(1 + q/2^W) + fb with fa = 2^W*s_hat, fb = -s_hat*(2^W + z_hat), per group,
-    // where s_hat = s_s*(s_q - z_s) and z_hat = s_z*(z_q - z_z) and the extracted codes are 1 + code/8:
-    //   fa = c1*(1 + s_q/8) + c2,   -(2^W + z_hat)/2^W = e1*(1 + z_q/8) + e2,   fb = fa * that.
-    // A lane without a tile of its own multiplies zero weights with zero activations.
-    const float c1 = live ? SCALE * 8.f * s_s : 0.f, c2 = live ? SCALE * (-s_s * z_s - 8.f * s_s) : 0.f;
-    const float e1 = -8.f * s_z / SCALE, e2 = -(SCALE - s_z * z_z - 8.f * s_z) / SCALE;
-    auto group_pair = [&](int p, float* fa, float* fb0, float* fb1) {   // groups 2p and 2p + 1 of the lane
-      uint32_t sp = pair_f16<3>(t.s, p, k3), zp = pair_f16<3>(t.s, T::B2 / 2 + p, k3);
-      if constexpr (NSUB == 2) {               // the groups of the lane's half of the rows
-        sp = half ? pair_f16<3>(t.s, NG / 2 + p, k3) : sp;
-        zp = half ? pair_f16<3>(t.s, T::B2 / 2 + NG / 2 + p, k3) : zp;
-      }
-      const half2_t sq = as_half2(sp), zq = as_half2(zp);
-      fa[0] = fmaf((float)sq.x, c1, c2);
-      fa[1] = fmaf((float)sq.y, c1, c2);
-      const float b0 = fa[0] * fmaf((float)zq.x, e1, e2), b1 = fa[1] * fmaf((float)zq.y, e1, e2);
-      fb0[0] = b0;
-      fb0[1] = b1;
-      if constexpr (FOLD) {                    // the extracted value is K + code/2^W instead of 1 + code/2^W
-        const float K0 = CodeClass<W, true>::K(CodeClass<W, true>::of_pair(p));   // constants once the loop is unrolled
-        fb0[0] = fmaf(1.f - K0, fa[0], b0);
-        fb0[1] = fmaf(1.f - K0, fa[1], b1);
-        if constexpr (NK == 2) {               // odd rows
-          const float K1 = CodeClass<W, true>::K(CodeClass<W, true>::of_pair(PPR + p));
-          fb1[0] = fmaf(1.f - K1, fa[0], b0);
-          fb1[1] = fmaf(1.f - K1, fa[1], b1);
-        }
-      }
-    };
+    dq.begin(t, live);
     // 8 columns at a time, so that few groups' constants are alive (the two tiles and the sums leave room for no more)
-    constexpr int NF = AXIS == 1 ? 8 : NG;
-    float fa[NF], fb[NK][NF];
-    if constexpr (AXIS == 0) {
-#pragma unroll
-      for (int p = 0; p < NG / 2; ++p) group_pair(p, fa + 2 * p, fb[0] + 2 * p, fb[NK - 1] + 2 * p);
-    }
 #pragma unroll
     for (int j = 0; j < KG; ++j) {
-      if constexpr (AXIS == 1) {
-#pragma unroll
-        for (int d = 0; d < 4; ++d) group_pair(4 * j + d, fa + 2 * d, fb[0] + 2 * d, fb[NK - 1] + 2 * d);
-      }
+      dq.columns(t, j);
       const uint32_t xv[4] = {live ? x[j].x : 0u, live ? x[j].y : 0u, live ? x[j].z : 0u, live ? x[j].w : 0u};
 #pragma unroll
       for (int r = 0; r < LR; ++r) {
-        uint32_t o[4];
-#pragma unroll
-        for (int d = 0; d < 4; ++d) {
-          const int q = r * PPR + 4 * j + d;
-          const half2_t q2 = as_half2(FOLD ? pair_class_inline<W>(t.c, q, kk) : pair_f16<W>(t.c, q, kc));
-          const int g0 = AXIS == 1 ? 2 * d : r, g1 = AXIS == 1 ? 2 * d + 1 : r;
-          half2_t w;
-          w.x = (_Float16)fmaf((float)q2.x, fa[g0], fb[r % NK][g0]);
-          w.y = (_Float16)fmaf((float)q2.y, fa[g1], fb[r % NK][g1]);
-          o[d] = __builtin_bit_cast(uint32_t, w);
-        }
-        D[r] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8_t, o), __builtin_bit_cast(half8_t, xv), D[r],
-                                                      0, 0, 0);
+        D[r] = __builtin_amdgcn_mfma_f32_16x16x32_f16(dq.operand(t, r, j), __builtin_bit_cast(half8_t, xv), D[r], 0, 0, 0);
         if (r % 4 == 3) __builtin_amdgcn_sched_barrier(0);
       }
     }
@@ -582,14 +480,10 @@ __global__ void __launch_bounds__(256) sum_groups_fused_kernel(BatchFused F, int
   sum_groups_body(F.it[i].A.g, F.it[i].P, splits, batch, F.it[i].Y, y_dtype, bx);
 }
 
-// XP[v][j] = X[v][perm[j]]: the batch in the matrix's column order (act-order checkpoints, Sec. 5).
-__global__ void __launch_bounds__(256)
-permute_batch_kernel(const uint16_t* __restrict__ X, const int32_t* __restrict__ perm, uint16_t* __restrict__ XP, int n,
-                     int batch) {
-  const int j = blockIdx.x * 256 + threadIdx.x;
-  if (j >= n) return;
-  const int src = min(max(perm[j], 0), n - 1);
-  for (int v = 0; v < batch; ++v) XP[(int64_t)v * n + j] = X[(int64_t)v * n + src];
+hipError_t launch_sum_groups(const Geometry& g, const float* P, int splits, int b, void* Y, int y_dtype, hipStream_t stream) {
+  const int rows = 16 * lane_rows(g.tile_rows);
+  hipLaunchKernelGGL(sum_groups_kernel, dim3((g.m + rows - 1) / rows, b), dim3(rows), 0, stream, g, P, splits, b, Y, y_dtype);
+  return hipGetLastError();
 }
 
 // Steps per workgroup of a split launch with workgroups of unequal cost beside it, chosen by simulating the launch
@@ -839,18 +733,14 @@ static hipError_t launch_mfma_t(const DevMatrix& A, const uint16_t* X, int b, vo
   const uint16_t* Xin = X;
   if (A.perm != nullptr) {
     uint16_t* xp = reinterpret_cast<uint16_t*>(scratch);
-    hipLaunchKernelGGL(permute_batch_kernel, dim3((g.n + 255) / 256), dim3(256), 0, stream, X, A.perm, xp, g.n, b);
-    e = hipGetLastError();
+    e = launch_gather_x(X, A.perm, xp, g.n, b, stream);
     Xin = xp;
   }
   if (e == hipSuccess) {
     hipLaunchKernelGGL((batch_group_kernel<W, TR, TC, AXIS>), dim3(groups, splits), dim3(256), SH::LDS, stream, A, Xin, b, P, per);
     e = hipGetLastError();
   }
-  if (e == hipSuccess) {
-    hipLaunchKernelGGL(sum_groups_kernel, dim3(groups, b), dim3(SH::ROWS), 0, stream, g, P, splits, b, Y, y_dtype);
-    e = hipGetLastError();
-  }
+  if (e == hipSuccess) e = launch_sum_groups(g, P, splits, b, Y, y_dtype, stream);
   const hipError_t ef = scratch_put(&sc, stream);
   return e == hipSuccess ? ef : e;
 }
@@ -916,8 +806,7 @@ static hipError_t launch_mfma_fused_t(const DevMatrix* As, int count, const uint
   const uint16_t* Xin = X;
   if (As[0].perm != nullptr) {
     uint16_t* xp = reinterpret_cast<uint16_t*>(scratch);
-    hipLaunchKernelGGL(permute_batch_kernel, dim3((g0.n + 255) / 256), dim3(256), 0, stream, X, As[0].perm, xp, g0.n, b);
-    e = hipGetLastError();
+    e = launch_gather_x(X, As[0].perm, xp, g0.n, b, stream);
     Xin = xp;
   }
   if (e == hipSuccess) {
@@ -963,19 +852,31 @@ size_t mfma_workspace_bound(const DevMatrix* As, int count, int b, bool fused) {
   return total > worst ? total : worst;
 }
 
-hipError_t launch_prefill_scratch(const DevMatrix& A, const uint16_t* X, int b, void* Y, int y_dtype, hipStream_t stream,
-                                  const Workspace& ws) {
-  const size_t need = prefill_workspace_bytes(A, b);
+// Runs `launch` on `need` bytes of the caller's workspace or of the library's buffer for the stream.
+template <typename Launch>
+static hipError_t on_scratch(const Workspace& ws, size_t need, hipStream_t stream, Launch launch) {
   if (ws.from_caller) {
     if (ws.p == nullptr || ws.bytes < need) return hipErrorNotSupported;
-    return launch_prefill(A, X, b, Y, y_dtype, stream, ws.p);
+    return launch(ws.p);
   }
-  // the dense copy is far too large for allocation nodes of a graph, and stream-ordered allocations wait on the host
+  // far too large for allocation nodes of a graph, and stream-ordered allocations wait on the host
   Scratch sc;
   if (scratch_get(&sc, need, current_device(), stream, false) != hipSuccess) return hipErrorNotSupported;
-  const hipError_t e = launch_prefill(A, X, b, Y, y_dtype, stream, sc.p);
+  const hipError_t e = launch(sc.p);
   const hipError_t ef = scratch_put(&sc, stream);
   return e == hipSuccess ? ef : e;
+}
+
+hipError_t launch_prompt_scratch(const DevMatrix& A, const uint16_t* X, int b, void* Y, int y_dtype, hipStream_t stream,
+                                 const Workspace& ws) {
+  return on_scratch(ws, prompt_workspace_bytes(A, b), stream,
+                    [&](uint8_t* p) { return launch_prompt(A, X, b, Y, y_dtype, stream, p); });
+}
+
+hipError_t launch_prefill_scratch(const DevMatrix& A, const uint16_t* X, int b, void* Y, int y_dtype, hipStream_t stream,
+                                  const Workspace& ws) {
+  return on_scratch(ws, prefill_workspace_bytes(A, b), stream,
+                    [&](uint8_t* p) { return launch_prefill(A, X, b, Y, y_dtype, stream, p); });
 }
 
 // ---- scratch for callers that cannot allocate ------------------------------------------------------------

@@ -118,10 +118,16 @@ __global__ void __launch_bounds__(256) add_outliers_f16_kernel(DevMatrix A, uint
 // XP[v][j] = X[v][perm[j]]: the batch in the matrix's column order (act-order checkpoints).
 __global__ void __launch_bounds__(256)
 gather_x_kernel(const uint16_t* __restrict__ X, const int32_t* __restrict__ perm, uint16_t* __restrict__ XP, int n, int b) {
-  const int j = blockIdx.x * 256 + threadIdx.x;
+  const int j = blockIdx.x * 256 + threadIdx.x, v0 = 8 * blockIdx.y;       // 8 vectors per thread
   if (j >= n) return;
   const int src = min(max(perm[j], 0), n - 1);
-  for (int v = 0; v < b; ++v) XP[(int64_t)v * n + j] = X[(int64_t)v * n + src];
+#pragma unroll
+  for (int k = 0; k < 8; ++k)
+    if (v0 + k < b) XP[(int64_t)(v0 + k) * n + j] = X[(int64_t)(v0 + k) * n + src];
+}
+hipError_t launch_gather_x(const uint16_t* X, const int32_t* perm, uint16_t* XP, int n, int b, hipStream_t stream) {
+  hipLaunchKernelGGL(gather_x_kernel, dim3((n + 255) / 256, (b + 7) / 8), dim3(256), 0, stream, X, perm, XP, n, b);
+  return hipGetLastError();
 }
 
 // ---------------------------------------------------------------------------
@@ -406,8 +412,7 @@ hipError_t launch_prefill(const DevMatrix& A, const uint16_t* X, int b, void* Y,
   }
   const uint16_t* Xin = X;
   if (XP != nullptr) {
-    hipLaunchKernelGGL(gather_x_kernel, dim3((g.n + 255) / 256), dim3(256), 0, stream, X, A.perm, XP, g.n, b);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
+    if ((e = launch_gather_x(X, A.perm, XP, g.n, b, stream)) != hipSuccess) return e;
     Xin = XP;
   }
   return launch_dense_gemm(Xin, b, g.n, Wd, ldw, g.m, Y, y_dtype, partial, stream);

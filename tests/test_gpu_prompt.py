@@ -1,0 +1,74 @@
+"""GPU tests of the one-pass product of prompt-sized batches and of the batch kernel's edges: ragged groups of strips,
+units and blocks of vectors, outliers beyond what a thread has in flight, every split pinned.  Against the oracle."""
+import numpy as np
+import pytest
+
+import spqr_synth as synth
+from oracle import spqr_oracle as orc
+
+pytestmark = [pytest.mark.gpu, pytest.mark.timeout(600)]
+
+REL_L2 = 1e-3            # weights rounded once to binary16, 2^-11 each; measured 2.1e-4
+
+
+@pytest.fixture(scope="module")
+def P():
+    import torch
+    import paper_2306_03078_amd as P
+    P.load_library()
+    assert torch.cuda.is_available()
+    return P
+
+
+def run(P, f, b, steps=0):
+    import torch
+    A = P.SpQRMatrix.from_logical(f)
+    X = synth.make_x(f.n, b, seed=(71, b))
+    P.spqr_set_option(P.SPQR_OPT_BATCH_STEPS, steps)
+    try:
+        need = P.spqr_workspace_bytes(A, b)
+        buf = torch.full((need + 512,), 0xA5, dtype=torch.uint8, device="cuda:0")
+        Y = P.spqr_gemm_smallbatch_ws(A, torch.from_numpy(X).to("cuda:0"), buf[256:256 + need])
+        again = P.spqr_gemm_smallbatch_ws(A, torch.from_numpy(X).to("cuda:0"), buf[256:256 + need])
+        assert torch.equal(Y, again)
+        assert bool((buf[:256] == 0xA5).all()) and bool((buf[256 + need:] == 0xA5).all())
+    finally:
+        P.spqr_set_option(P.SPQR_OPT_BATCH_STEPS, 0)
+    ref = orc.matvec(f, X)
+    got = Y.cpu().numpy().astype(np.float64)
+    err = np.linalg.norm(got - ref, axis=1) / np.linalg.norm(ref, axis=1)
+    assert err.max() <= REL_L2, (int(err.argmax()), float(err.max()))
+
+
+# strips: one, 16 k + 1, a full group; tile columns: one, a unit and one, many units
+@pytest.mark.parametrize("w,b1,b2,axis,ntr,ntc,structure,rate", [
+    (3, 16, 16, 1, 1, 1, "uniform", 0.1), (4, 16, 16, 1, 17, 17, "zipf", 0.1), (3, 16, 16, 0, 16, 67, "rows8cols4", 0.2),
+    (4, 8, 32, 1, 33, 65, "cols64", 0.2), (3, 8, 32, 0, 9, 131, "uniform", 0.24), (3, 8, 32, 1, 2, 160, "uniform", 0.2)])
+@pytest.mark.parametrize("b", [4, 16, 33, 65, 129, 256])
+@pytest.mark.parametrize("steps", [0, 1, 1000])
+def test_edges(P, w, b1, b2, axis, ntr, ntc, structure, rate, b, steps):
+    tr, tc = synth.tile_shape(b1, b2, axis)
+    P.spqr_set_option(P.SPQR_OPT_BATCH_PATH, P.SPQR_BATCH_PATH_MATRIX if b <= 16 else P.SPQR_BATCH_PATH_AUTO)
+    try:
+        f = synth.make_matrix(ntr * tr, ntc * tc, w_bits=w, beta1=b1, beta2=b2, group_axis=axis, outlier_rate=rate,
+                              outlier_structure=structure, seed=(72, w, axis, ntr, ntc))
+        if (ntr + b) % 2:
+            f.perm = np.random.default_rng(5).permutation(f.n).astype(np.int32)
+        run(P, f, b, steps)
+    finally:
+        P.spqr_set_option(P.SPQR_OPT_BATCH_PATH, P.SPQR_BATCH_PATH_AUTO)
+
+
+def test_permutation_wider_than_the_room_of_the_products(P):
+    """Batch 1 and 2 with a permutation: x through LDS where the products leave it room, gathered from memory where not."""
+    import torch
+    for w, b1, b2, axis, ntr, ntc in ((3, 8, 32, 0, 3, 300), (3, 16, 16, 1, 5, 3000), (4, 16, 16, 0, 4, 67)):
+        tr, tc = synth.tile_shape(b1, b2, axis)
+        f = synth.make_matrix(ntr * tr, ntc * tc, w_bits=w, beta1=b1, beta2=b2, group_axis=axis, outlier_rate=0.01, seed=(73, ntc))
+        f.perm = np.random.default_rng(6).permutation(f.n).astype(np.int32)
+        A = P.SpQRMatrix.from_logical(f)
+        for b in (1, 2):
+            X = synth.make_x(f.n, b, seed=(74, b))
+            got = P.spqr_gemm_smallbatch(A, torch.from_numpy(X).to("cuda:0")).cpu().numpy().astype(np.float64)
+            ref = orc.matvec(f, X)
+            assert (np.linalg.norm(got - ref, axis=1) / np.linalg.norm(ref, axis=1)).max() <= REL_L2
