@@ -1,5 +1,6 @@
-"""GPU tests of the one-pass product of prompt-sized batches and of the batch kernel's edges: ragged groups of strips,
-units and blocks of vectors, outliers beyond what a thread has in flight, every split pinned.  Against the oracle."""
+"""GPU tests of the one-pass product of prompt-sized batches and of the batch kernel's edges (ragged groups of strips, units
+and blocks of vectors, outliers beyond what a thread has in flight, every split pinned; against the oracle), of the
+permutation at batch 1, and of the quantiser's two ways of sharing out rows (against each other, bit for bit)."""
 import numpy as np
 import pytest
 
@@ -72,3 +73,29 @@ def test_permutation_wider_than_the_room_of_the_products(P):
             got = P.spqr_gemm_smallbatch(A, torch.from_numpy(X).to("cuda:0")).cpu().numpy().astype(np.float64)
             ref = orc.matvec(f, X)
             assert (np.linalg.norm(got - ref, axis=1) / np.linalg.norm(ref, axis=1)).max() <= REL_L2
+
+
+def test_sweep_is_the_same_on_both_row_splits(P):
+    """Rows are independent outside their tile: the first rows of a layer too tall for 16 rows per workgroup come out bit
+    for bit as when they are a layer of their own, which takes 16 rows per workgroup."""
+    import torch
+    import paper_2306_03078_amd.encode_binding as E
+    for b1, b2, n in ((16, 16, 160), (8, 2, 72), (32, 8, 128), (4, 16, 68)):
+        m = 4096 + 16
+        W, _ = synth.make_quantizer_problem(7, m, n, 8)
+        rng = np.random.default_rng(8)
+        U = np.triu(rng.normal(size=(n, n)) * 0.02, 1) + np.diag(0.01 + 0.01 * rng.random(n))
+        Wd, Ud = torch.from_numpy(W).to("cuda:0"), torch.from_numpy(U).to("cuda:0")
+        tall = E.spqr_quantize_device(Wd, Ud, 3, b1, b2, 5.0)
+        for rows in (4096, 48):
+            own = E.spqr_quantize_device(Wd[:rows].contiguous(), Ud, 3, b1, b2, 5.0)
+            for k in ("Q", "s_q", "z_q", "outlier_mask"):
+                assert torch.equal(own[k], tall[k][:rows]), k
+            for k in ("s_s", "z_s", "s_z", "z_z"):
+                assert torch.equal(own[k].view(torch.int16), tall[k][:rows // b2].view(torch.int16)), k
+            assert torch.equal(own["outlier_val"].view(torch.int16), tall["outlier_val"][:rows].view(torch.int16))
+            assert torch.equal(own["W_final"].view(torch.int64), tall["W_final"][:rows].view(torch.int64))
+            assert torch.equal(own["row_ptr"], tall["row_ptr"][:rows + 1])
+        # without W_final the workspace is the working copy
+        none = E.spqr_quantize_device(Wd[:48].contiguous(), Ud, 3, b1, b2, 5.0, want_final=False)
+        assert torch.equal(none["Q"], tall["Q"][:48])
