@@ -247,8 +247,8 @@ int spqr_gemv(const spqr_matrix_t* A, const uint16_t* x_f16, void* y, int y_dtyp
  * 10 us more per call), on further streams one from a pool of the library's
  * own.  If no scratch can be had, the slices of 4 run instead.  Callers that
  * must not allocate or synchronise use spqr_gemm_smallbatch_ws.
- * Prompt-sized batches (33 vectors and more; Sec. 5 "Inference Time") of the same
- * tile shapes take one pass over the weights: a workgroup dequantises them into
+ * Prompt-sized batches (from 48 vectors on, at b >= m*n/2.5e6 + nnz/1.5e5; Sec. 5
+ * "Inference Time"; Y 16-byte aligned) of the same tile shapes take one pass over the weights: a workgroup dequantises them into
  * LDS, adds the outliers there and multiplies all vectors with them (scratch: 4
  * bytes per outlier, the partial sums, with a permutation b*n*2 bytes).
  * Other formats (12 vectors and more; tiles of 256 codes in any layout and 3-bit

@@ -26,8 +26,8 @@ static constexpr int kMfmaMinBatch = 4;
 
 // Y[b][m] = X[b][n] . W_hat^T.  Up to 4 activation vectors: the tuned vector kernel, all of them in one launch
 // (4 vectors on a large layer: the matrix cores, see mfma_wanted).  More, where a matrix-core instance exists and
-// it pays: slices of up to 16 with the dense part on the matrix cores (weights stream once per slice), then the
-// finishing kernel with the outliers.  Else slices of 4.
+// it pays: slices of up to 16 on the matrix cores (weights stream once per slice), outliers in the same kernel, then the
+// partial results are added.  Else slices of 4.
 // ws.from_caller: scratch comes from the caller; nothing is allocated, freed or waited for, the choice of path
 // never depends on the stream's state, and a workspace that is too small is hipErrorOutOfMemory.
 hipError_t launch_gemm(const DevMatrix& A, const uint16_t* X, int b, void* Y, int y_dtype,
@@ -37,8 +37,9 @@ hipError_t launch_gemm(const DevMatrix& A, const uint16_t* X, int b, void* Y, in
   const bool force_generic = option(SPQR_OPT_FORCE_GENERIC) != 0;
   bool mfma_ok = !force_generic && mfma_has_instance(g);
   const bool alloc_nodes = mfma_ok && !ws.from_caller && b >= kMfmaMinBatch && stream_is_capturing(stream);
-  // A prompt-sized batch: one pass over the compressed weights for all vectors.
-  if (!force_generic && prompt_wanted(A, b)) {
+  // A prompt-sized batch: one pass over the compressed weights for all vectors (Y as the dense copy wants it: the calls
+  // that took the copy, see prompt_wanted).
+  if (!force_generic && prompt_wanted(A, b) && reinterpret_cast<uintptr_t>(Y) % 16 == 0) {
     const hipError_t e = launch_prompt_scratch(A, X, b, Y, y_dtype, stream, ws);
     if (e != hipErrorNotSupported) return e;   // no scratch of that size: the slices below
   }
@@ -92,9 +93,9 @@ hipError_t launch_gemm_fused(const DevMatrix* As, int count, const uint16_t* X, 
   const bool force_generic = option(SPQR_OPT_FORCE_GENERIC) != 0;
   bool mfma_ok = count > 1 && !force_generic && mfma_has_instance(g);
   // Not while the stream is being captured into a graph: a replay of a graph that held 12 fused batch calls among
-  // 42 calls (a whole decoder block, six weight copies) ended in a memory fault inside the fused finishing kernel,
-  // while the same calls pass eagerly and graphs of the per-matrix path replay correctly; until the cause is
-  // known, captured calls take the per-matrix path.
+  // 42 calls (a whole decoder block, six weight copies) once ended in a memory fault inside the fused kernel that
+  // added the outliers (gone since: batch_group_fused_kernel adds them), while the same calls passed eagerly and
+  // graphs of the per-matrix path replay correctly; the cause was never known, so captured calls take the per-matrix path.
   const bool capturing = mfma_ok && b >= kMfmaMinBatch && stream_is_capturing(stream);
   if (capturing) mfma_ok = false;
   // a large batch: one matrix at a time (launch_gemm falls back to the slices where it has to)
@@ -130,7 +131,7 @@ hipError_t launch_gemm_fused(const DevMatrix* As, int count, const uint16_t* X, 
 size_t workspace_bound(const DevMatrix* As, int count, int b, bool with_dense_copy) {
   if (option(SPQR_OPT_FORCE_GENERIC) != 0) return 0;
   size_t worst = 0;
-  // a large batch: the dense copy of one matrix at a time (a smaller workspace sends the call to the slices of 16)
+  // a large batch: one matrix at a time (a smaller workspace sends the call to the slices of 16)
   if (with_dense_copy)
     for (int i = 0; i < count; ++i)
       if (prompt_wanted(As[i], b)) {

@@ -84,8 +84,7 @@ int plan_batch_steps(int groups, int nsteps, int slots_one_step, int slots, int 
 hipError_t launch_sum_groups(const Geometry& g, const float* P, int splits, int b, void* Y, int y_dtype, hipStream_t stream);
 
 // Prompt-sized batches (spqr_prompt.hip) and large batches through a dense binary16 copy of the matrix
-// (spqr_prefill.hip) on the library's scratch or the
-// caller's workspace.  hipErrorNotSupported: no scratch of that size to be had (or the stream is being captured
+// (spqr_prefill.hip) on the library's scratch or the caller's workspace.  hipErrorNotSupported: no scratch of that size to be had (or the stream is being captured
 // and the library would have to allocate it): the caller takes the slices of 16.
 hipError_t launch_prompt_scratch(const DevMatrix& A, const uint16_t* X, int b, void* Y, int y_dtype, hipStream_t stream,
                                  const Workspace& ws);

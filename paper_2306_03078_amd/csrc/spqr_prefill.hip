@@ -1,4 +1,5 @@
-// Large batches (the prompt phase of Sec. 5, "Inference Time"): the weights are dequantised once per call into a
+// Large batches (the prompt phase of Sec. 5, "Inference Time") of the formats and outlier rates that spqr_prompt.hip does not
+// take: the weights are dequantised once per call into a
 // dense binary16 copy in scratch, the outliers are added into it, and one tiled matrix-core kernel multiplies the
 // whole batch with it (Sec. 4.2 describes the same order: 16-bit weights first, then the product).  The
 // slices of 16 of the batch path read and dequantise the weights once per slice; here a weight is read once
@@ -269,10 +270,11 @@ bool prefill_has_instance(const Geometry& g) {
   return shape16 || shape8x32 || shape32x8 || wide;
 }
 
-// Whether a batch of b vectors goes through the dense copy: the copy costs one pass over the compressed weights,
+// Whether a batch of b vectors goes through the dense copy, or, where the format has it, the one-pass kernel of
+// spqr_prompt.hip, which has its rule from here: the copy costs one pass over the compressed weights,
 // one write of 2 bytes per weight and a scattered read-modify-write per outlier, whatever the batch; the slices of
 // 16 cost a pass over the compressed weights each.  Measured on the 7B to 65B shapes (batches of 32 to 256, both
-// paths forced): the copy wins from 48 vectors on layers of up to 120 M weights (4096^2 at 48: 34 against 56 us;
+// paths forced, slices with the outliers in a kernel of their own, a fifth slower than now): the copy wins from 48 vectors on layers of up to 120 M weights (4096^2 at 48: 34 against 56 us;
 // 17920x6656: 144 against 156), from 64 on 8192^2 with 2 % outliers and from 96 on the layers of 180 M weights
 // (22016x8192 at 64 / 96: 326 / 355 against 289 / 433); at 256 vectors it is 3.4 to 6.8 times faster.
 bool prefill_wanted(const DevMatrix& A, int b) {

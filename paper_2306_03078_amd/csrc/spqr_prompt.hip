@@ -354,11 +354,13 @@ bool prompt_has_instance(const DevMatrix& A) {
          (A.g.ntc + kUnitTiles - 1) / kUnitTiles * (A.g.tile_cols / 8) <= kSortMaxPhases;
 }
 
-// From 33 vectors on (two slices of 16 and more).  Measured against the slices and the dense copy on 40 drawn layers of
-// 1000 to 17920 rows and columns, 33 to 256 vectors: 0.91 to 2.35 times as fast, 1.30 in the mean; the slower ones are
-// layers of a few million weights, where sorting the outliers (10 us) counts.
+// Where the dense copy pays against slices of 16 (prefill_wanted: from 48 vectors on, later on larger layers), in the copy's
+// place: measured against it on 40 drawn layers of 1000 to 17920 rows and columns 0.91 to 2.35 times as fast, 1.30 in the
+// mean; the slower ones are layers of a few million weights, where sorting the outliers (10 us) counts.  It would be the
+// faster one from 33 vectors on, but the slices add the outliers in binary32 and here weight + outlier is rounded to
+// binary16, so no batch that took the slices moves here.
 bool prompt_wanted(const DevMatrix& A, int b) {
-  return option(SPQR_OPT_BATCH_PATH) == SPQR_BATCH_PATH_AUTO && prompt_has_instance(A) && b >= 33;
+  return option(SPQR_OPT_BATCH_PATH) == SPQR_BATCH_PATH_AUTO && prompt_has_instance(A) && prefill_wanted(A, b);
 }
 
 static size_t prompt_offsets(const DevMatrix& A, int b, const PromptPlan& p, size_t (&at)[5]) {
