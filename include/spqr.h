@@ -248,10 +248,11 @@ int spqr_gemv(const spqr_matrix_t* A, const uint16_t* x_f16, void* y, int y_dtyp
  * own.  If no scratch can be had, the slices of 4 run instead.  Callers that
  * must not allocate or synchronise use spqr_gemm_smallbatch_ws.
  * Prompt-sized batches (from 48 vectors on, at b >= m*n/2.5e6 + nnz/1.5e5; Sec. 5
- * "Inference Time"; Y 16-byte aligned) of the same tile shapes take one pass over the weights: a workgroup dequantises them into
+ * "Inference Time"; Y 16-byte aligned) of the same tile shapes, on layers from 4 M
+ * (8x32) or 24 M weights on, take one pass over the weights: a workgroup dequantises them into
  * LDS, adds the outliers there and multiplies all vectors with them (scratch: 4
  * bytes per outlier, the partial sums, with a permutation b*n*2 bytes).
- * Other formats (12 vectors and more; tiles of 256 codes in any layout and 3-bit
+ * Smaller layers, other formats (12 vectors and more; tiles of 256 codes in any layout and 3-bit
  * tiles of 8 x 64, Y 16-byte aligned) and matrices with more outliers than one
  * weight in four: the matrix is dequantised once into a dense binary16 copy in
  * scratch (2 bytes per weight, rows padded to a multiple of 64 columns; with a

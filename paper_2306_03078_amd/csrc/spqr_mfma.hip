@@ -745,12 +745,12 @@ static hipError_t launch_mfma_t(const DevMatrix& A, const uint16_t* X, int b, vo
   return e == hipSuccess ? ef : e;
 }
 
-// Whether a batch of b > 4 vectors takes the matrix-core path.  It pays two more launches and the
-// transposition through LDS, the vector path re-reads the weights once per 4 vectors.  Measured on
-// MI355X with eager calls (a sweep of b = 2..16 over the layers of the 7B, 33B and 65B shapes, both paths forced)
-// the matrix cores win from 7 vectors on for any layer (4096^2 at b = 5 / 6 / 7 / 8: 19.9 / 20.0 / 20.0 / 20.1 us
-// against 17.4 / 19.6 / 25.2 / 23.8) and from 4 on for layers of 30 M weights or more (17920x6656 at b = 4:
-// about 52 us against 61; layers of 45 M weights are break-even at 4).  `alloc_nodes`: the call's scratch would be
+// Whether a batch of b >= 4 vectors takes the matrix-core path.  Its time hardly depends on b, the vector path re-reads
+// the weights once per 4 vectors.  Measured with eager calls (b = 4..16 over the layers of the 7B, 33B and 65B shapes, both
+// paths forced) the matrix cores win from 5 vectors on for any layer (4096^2 at b = 4 / 5 / 6 / 7: 16.5 us against 12.0 /
+// 17.8 / 19.7 / 25.8) and from 4 on for layers of 30 M weights or more (17920x6656 at b = 4: 43 us against 57; 11008x4096
+// 23.4 against 22.7).  The line for smaller layers stays at 7: with group_axis 0 the vector path keeps its weights in
+// binary32, and 5 or 6 vectors have always had that.  `alloc_nodes`: the call's scratch would be
 // allocation nodes of a graph under capture (library-owned scratch on a capturing stream), about 10 us more
 // per call: then from 13 vectors on for any layer, from 8 on for layers of 40 M weights and from 5 on for
 // layers of 100 M.  The option SPQR_OPT_BATCH_PATH forces one or the other wherever both apply (tests

@@ -354,13 +354,17 @@ bool prompt_has_instance(const DevMatrix& A) {
          (A.g.ntc + kUnitTiles - 1) / kUnitTiles * (A.g.tile_cols / 8) <= kSortMaxPhases;
 }
 
-// Where the dense copy pays against slices of 16 (prefill_wanted: from 48 vectors on, later on larger layers), in the copy's
-// place: measured against it on 40 drawn layers of 1000 to 17920 rows and columns 0.91 to 2.35 times as fast, 1.30 in the
-// mean; the slower ones are layers of a few million weights, where sorting the outliers (10 us) counts.  It would be the
-// faster one from 33 vectors on, but the slices add the outliers in binary32 and here weight + outlier is rounded to
-// binary16, so no batch that took the slices moves here.
+// Where the dense copy pays against slices of 16 (prefill_wanted: from 48 vectors on, later on larger layers) and this kernel
+// is faster than the copy: from 4 M weights on with strips of 8 rows (2048^2, 48 to 256 vectors: 28.1 .. 33.6 -> 24.3 ..
+// 27.8 us; 1024^2: 21.0 .. 24.0 against 25.3 .. 26.4), from 24 M on with 16 rows a lane, whose groups of 256 rows are fewer
+// and whose weights are dequantised once per 128 vectors (5120^2: 46.2 .. 61.0 -> 38.3 .. 57.2; 5120 x 3584: 35.4 .. 47.4
+// against 36.9 .. 55.3); below, the sort of the outliers (10 us) and the few workgroups cost more than the copy's passes.
+// From 33 vectors on it would beat the slices, but they add the outliers in binary32 and here weight + outlier is rounded to
+// binary16, so no batch that took the slices moves here.  With the split pinned (SPQR_OPT_BATCH_STEPS) the size is no matter.
 bool prompt_wanted(const DevMatrix& A, int b) {
-  return option(SPQR_OPT_BATCH_PATH) == SPQR_BATCH_PATH_AUTO && prompt_has_instance(A) && prefill_wanted(A, b);
+  const double from = A.g.tile_rows == 8 ? 4e6 : 24e6;
+  return option(SPQR_OPT_BATCH_PATH) == SPQR_BATCH_PATH_AUTO && prompt_has_instance(A) && prefill_wanted(A, b) &&
+         ((double)A.g.m * A.g.n >= from || option(SPQR_OPT_BATCH_STEPS) >= 1);
 }
 
 static size_t prompt_offsets(const DevMatrix& A, int b, const PromptPlan& p, size_t (&at)[5]) {
