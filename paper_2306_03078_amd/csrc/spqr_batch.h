@@ -50,27 +50,32 @@ __device__ __forceinline__ void load_batch_tile(BatchTile<W, TR, TC, AXIS>& t, c
 }
 
 // Dequantisation of a lane's rows, 8 columns at a time: w = s_hat * (q - z_hat) in one binary32 FMA, rounded once to
-// binary16.  With the extracted codes 1 + q/2^W and 1 + code/8 of the statistics:
-//   w = fa*(1 + q/2^W) + fb with fa = 2^W*s_hat, fb = -s_hat*(2^W + z_hat), per group, where s_hat = s_s*(s_q - z_s) and
-//   z_hat = s_z*(z_q - z_z):  fa = c1*(1 + s_q/8) + c2,   -(2^W + z_hat)/2^W = e1*(1 + z_q/8) + e2,   fb = fa * that.
+// binary16, where s_hat = s_s*(s_q - z_s) and z_hat = s_z*(z_q - z_z).  The codes of the statistics come as 1 + code/8.
+// Groups along the tile's rows: the weight's code comes as 1 + q/2^W, and
+//   w = fa*(1 + q/2^W) + fb with fa = 2^W*s_hat, fb = -s_hat*(2^W + z_hat), per group:
+//   fa = c1*(1 + s_q/8) + c2,   -(2^W + z_hat)/2^W = e1*(1 + z_q/8) + e2,   fb = fa * that.
+// Groups along the tile's columns: the code is used where it lies, as the subnormal q * 2^(bit - 24), and the power of two
+// goes into the column's factor (exactly): w = fa*(q * 2^(bit - 24)) + fb with fa = s_hat * 2^(24 - bit), fb = -s_hat*z_hat.
+// No shift for most codes, and no offset that would have to cancel inside the FMA: the offset 2^(7 - bit) that the batch-1
+// kernel's extraction leaves is up to 128 times a weight of s_hat, and with it 8 to 11 % of the weights were not the
+// nearest binary16.  So measured over 16384 weights per format none is not, with 1 + q/2^W 0.2 to 0.4 %; same time.
 template <int W, int TR, int TC, int AXIS> struct Dequant {
   using B = BatchTile<W, TR, TC, AXIS>;
   using T = typename B::T;
   static constexpr int LR = lane_rows(TR), NSUB = TR / LR;    // rows of a lane; strips of the kernel per strip of tiles
   static constexpr int PPR = TC / 2, KG = TC / 8;             // code pairs per row; blocks of 8 columns
   static constexpr int NG = AXIS == 1 ? TC : LR;              // first-level groups of a lane
-  // Groups along the tile's columns: the offset K that the in-place extraction of a code leaves (its class, see CodeClass)
-  // folds into the column's additive constant, and most shifts go away.  The class is a function of the pair's column,
-  // for 3-bit codes in rows of 8 pairs of the column and the parity of the row.
-  static constexpr bool FOLD = AXIS == 1;
-  static constexpr int NK = FOLD && W == 3 && PPR == 8 ? 2 : 1;
+  // The bit a code lies at (its class, see CodeClass) is a function of the pair's column, for 3-bit codes in rows of 8
+  // pairs of the column and the parity of the row.
+  static constexpr bool INPLACE = AXIS == 1;
+  static constexpr int NK = INPLACE && W == 3 && PPR == 8 ? 2 : 1;
   static constexpr int NF = AXIS == 1 ? 8 : NG;               // groups whose constants are alive at a time
   static constexpr float SCALE = (float)(1 << W);
   PairConsts kc, k3;
   ClassConsts kk;
   int half;                                                   // which rows of a tile of 32
   float c1, c2, e1, e2;                                       // of the current tile
-  float fa[NF], fb[NK][NF];
+  float fa[NK][NF], fb[NF];
 
   __device__ __forceinline__ Dequant(int half_) : half(half_) {
     kc = make_pair_consts<W>();
@@ -82,10 +87,11 @@ template <int W, int TR, int TC, int AXIS> struct Dequant {
     const uint32_t a2 = t.s[T::SD - 2], b2 = t.s[T::SD - 1];
     const float s_s = h2f((uint16_t)(a2 & 0xFFFF)), z_s = h2f((uint16_t)(a2 >> 16));
     const float s_z = h2f((uint16_t)(b2 & 0xFFFF)), z_z = h2f((uint16_t)(b2 >> 16));
-    c1 = live ? SCALE * 8.f * s_s : 0.f;
-    c2 = live ? SCALE * (-s_s * z_s - 8.f * s_s) : 0.f;
-    e1 = -8.f * s_z / SCALE;
-    e2 = -(SCALE - s_z * z_z - 8.f * s_z) / SCALE;
+    constexpr float UP = INPLACE ? 0x1p24f : SCALE, OFFSET = INPLACE ? 0.f : SCALE;
+    c1 = live ? UP * 8.f * s_s : 0.f;
+    c2 = live ? UP * (-s_s * z_s - 8.f * s_s) : 0.f;
+    e1 = -8.f * s_z / UP;
+    e2 = -(OFFSET - s_z * z_z - 8.f * s_z) / UP;
     if constexpr (AXIS == 0) {
 #pragma unroll
       for (int p = 0; p < NG / 2; ++p) group_pair(t, p, 2 * p);
@@ -101,11 +107,11 @@ template <int W, int TR, int TC, int AXIS> struct Dequant {
   // Row r, columns 8j + 2d and 8j + 2d + 1: a quarter of an operand.
   __device__ __forceinline__ uint32_t pair(const B& t, int r, int j, int d) const {
     const int q = r * PPR + 4 * j + d;
-    const half2_t q2 = as_half2(FOLD ? pair_class_inline<W>(t.c, q, kk) : pair_f16<W>(t.c, q, kc));
+    const half2_t q2 = as_half2(INPLACE ? pair_code_bits<W>(t.c, q, kk) : pair_f16<W>(t.c, q, kc));
     const int g0 = AXIS == 1 ? 2 * d : r, g1 = AXIS == 1 ? 2 * d + 1 : r;
     half2_t w;
-    w.x = (_Float16)fmaf((float)q2.x, fa[g0], fb[r % NK][g0]);
-    w.y = (_Float16)fmaf((float)q2.y, fa[g1], fb[r % NK][g1]);
+    w.x = (_Float16)fmaf((float)q2.x, fa[r % NK][g0], fb[g0]);
+    w.y = (_Float16)fmaf((float)q2.y, fa[r % NK][g1], fb[g1]);
     return __builtin_bit_cast(uint32_t, w);
   }
   // Row r, columns 8j .. 8j+7 as an operand.
@@ -122,20 +128,14 @@ template <int W, int TR, int TC, int AXIS> struct Dequant {
       zp = half ? pair_f16<3>(t.s, T::B2 / 2 + NG / 2 + p, k3) : zp;
     }
     const half2_t sq = as_half2(sp), zq = as_half2(zp);
-    fa[at] = fmaf((float)sq.x, c1, c2);
-    fa[at + 1] = fmaf((float)sq.y, c1, c2);
-    const float b0 = fa[at] * fmaf((float)zq.x, e1, e2), b1 = fa[at + 1] * fmaf((float)zq.y, e1, e2);
-    fb[0][at] = b0;
-    fb[0][at + 1] = b1;
-    if constexpr (FOLD) {                      // the extracted value is K + code/2^W instead of 1 + code/2^W
-      const float K0 = CodeClass<W, true>::K(CodeClass<W, true>::of_pair(p));   // constants once the loop is unrolled
-      fb[0][at] = fmaf(1.f - K0, fa[at], b0);
-      fb[0][at + 1] = fmaf(1.f - K0, fa[at + 1], b1);
-      if constexpr (NK == 2) {                 // odd rows
-        const float K1 = CodeClass<W, true>::K(CodeClass<W, true>::of_pair(PPR + p));
-        fb[NK - 1][at] = fmaf(1.f - K1, fa[at], b0);
-        fb[NK - 1][at + 1] = fmaf(1.f - K1, fa[at + 1], b1);
-      }
+    const float f0 = fmaf((float)sq.x, c1, c2), f1 = fmaf((float)sq.y, c1, c2);
+    fb[at] = f0 * fmaf((float)zq.x, e1, e2);
+    fb[at + 1] = f1 * fmaf((float)zq.y, e1, e2);
+#pragma unroll
+    for (int h = 0; h < NK; ++h) {             // NK == 2: even and odd rows; exact
+      const float down = INPLACE ? 1.f / (float)(1 << class_bit<W>(CodeClass<W, true>::of_pair(h * PPR + p))) : 1.f;
+      fa[h][at] = f0 * down;
+      fa[h][at + 1] = f1 * down;
     }
   }
 };

@@ -149,22 +149,24 @@ __device__ __forceinline__ uint32_t pair_class_f16(const uint32_t* c, const Shif
   }
 }
 
-// The same with the shifts written out (no state carried between pairs; the compiler shares a shifted
-// dword between the pairs that are extracted next to each other).
+// The codes of pair q where they lie, as two binary16 subnormals: code * 2^(class_bit - 24), exact and without an offset.
+// One v_and per pair and the shifts above, written out (the compiler shares a shifted dword between the pairs that are
+// extracted next to each other).
+template <int W> constexpr int class_bit(int c) { return W * c; }      // 3-bit: 0, 3, 6; 4-bit: 0, 4
 template <int W>
-__device__ __forceinline__ uint32_t pair_class_inline(const uint32_t* c, int q, const ClassConsts& k) {
+__device__ __forceinline__ uint32_t pair_code_bits(const uint32_t* c, int q, const ClassConsts& k) {
   if constexpr (W == 4) {
     const int e = q & 3;
     const uint32_t d = c[q >> 2], src = e < 2 ? d : (d >> 8);
-    return (src & k.mask[e & 1]) | k.magic[e & 1];
+    return src & k.mask[e & 1];
   } else {
     const int t3 = q >> 4, e = q & 15;
     if (e < 15) {
       const int j = e / 5, i = e % 5;
       const uint32_t d = c[3 * t3 + j], src = i < 3 ? d : (d >> 9);
-      return (src & k.mask[i % 3]) | k.magic[i % 3];
+      return src & k.mask[i % 3];
     } else {                                         // bits 15 / 31 of the three dwords -> bits 6, 7, 8
-      uint32_t t = ((c[3 * t3] >> 9) & k.m0) | k.magic[2];
+      uint32_t t = (c[3 * t3] >> 9) & k.m0;
       t = ((c[3 * t3 + 1] >> 8) & k.m1) | t;
       t = ((c[3 * t3 + 2] >> 7) & k.m2) | t;
       return t;
