@@ -147,6 +147,8 @@ __device__ __forceinline__ void batch_group_body(const DevMatrix& A, const uint1
   float4_t D[LR];
 #pragma unroll
   for (int r = 0; r < LR; ++r) D[r] = float4_t{0.f, 0.f, 0.f, 0.f};
+  // the first free line of XT stays zero: it is what an entry of another row meets (its own column may hold an infinity)
+  if (sparse && tid < 8) reinterpret_cast<uint32_t*>(xt + 8 * 16)[tid] = 0;
 
   const int nst = (ntc + 3) >> 2;              // steps of 4 tile columns
   // the wavefront's step of unit u (a step behind the last one loads the last one and counts nothing)
@@ -211,7 +213,7 @@ __device__ __forceinline__ void batch_group_body(const DevMatrix& A, const uint1
         const int a = bounds[0], z = bounds[1], c[2] = {k0, k1};
         if (a < z && (k0 > 0 || k1 < n)) lower_columns(A.col, n, a, z, c, bounds);
         row_lo[tid] = bounds[0];
-        row_hi[tid] = bounds[1];
+        row_hi[tid] = max(bounds[0], bounds[1]);
       }
     }
     // the dense part of the piece: two units per trip, the next one's loads ahead of the arithmetic
@@ -230,28 +232,25 @@ __device__ __forceinline__ void batch_group_body(const DevMatrix& A, const uint1
       __syncthreads();                           // XT and the row bounds are complete
       const bool first = c_lo == u_lo;
       const int width = k1 - k0;
-      auto line_of = [&](uint32_t col) {         // a column outside the piece (a broken row) stays inside XT
-        const int c = min(max((int)col - k0, 0), width - 1);
-        return reinterpret_cast<const u32x4*>(xt + (c + (c >> 3)) * 16);
-      };
-      // acc += two entries' values (binary16 pair) times their 16 activations: one v_perm pairs the two activations of
-      // a vector, one v_dot2 takes them (products exact, binary32 sums); half the issue of two v_fma_mix
-      auto add_pair = [&](uint32_t cols, uint32_t vals, float (&acc)[16]) {
-        const u32x4 *l0 = line_of(cols & 0xFFFFu), *l1 = line_of(cols >> 16);
+      // acc += two entries' values (binary16 pair) times their 16 activations, x the index of the first, those of them that
+      // lie in [lo, lo + len): one v_perm pairs the two activations of a vector, one v_dot2 takes them (products exact,
+      // binary32 sums, the same bits as two v_fma_mix; half the issue)
+      auto add_pair = [&](uint32_t cols, uint32_t vals, int x, int lo, uint32_t len, float (&acc)[16]) {
+        const bool in0 = (uint32_t)(x - lo) < len, in1 = (uint32_t)(x + 1 - lo) < len;
+        // a column outside the piece (a broken row) stays inside XT
+        const int c0 = min(max((int)(cols & 0xFFFFu) - k0, 0), width - 1), c1 = min(max((int)(cols >> 16) - k0, 0), width - 1);
+        const u32x4* l0 = reinterpret_cast<const u32x4*>(xt + (in0 ? c0 + (c0 >> 3) : 8) * 16);
+        const u32x4* l1 = reinterpret_cast<const u32x4*>(xt + (in1 ? c1 + (c1 >> 3) : 8) * 16);
         const u32x4 a0 = l0[0], a1 = l0[1], b0 = l1[0], b1 = l1[1];
         const uint32_t a[8] = {a0.x, a0.y, a0.z, a0.w, a1.x, a1.y, a1.z, a1.w}, b[8] = {b0.x, b0.y, b0.z, b0.w, b1.x, b1.y, b1.z, b1.w};
-        const half2_t w = as_half2(vals);
+        const half2_t w = as_half2((in0 ? vals & 0xFFFFu : 0u) | (in1 ? vals & 0xFFFF0000u : 0u));
 #pragma unroll
         for (int q = 0; q < 8; ++q) {
-          const half2_t lo = as_half2(__builtin_amdgcn_perm(b[q], a[q], 0x05040100u));   // a.lo, b.lo
-          const half2_t hi = as_half2(__builtin_amdgcn_perm(b[q], a[q], 0x07060302u));   // a.hi, b.hi
-          acc[2 * q] = __builtin_amdgcn_fdot2(w, lo, acc[2 * q], false);
-          acc[2 * q + 1] = __builtin_amdgcn_fdot2(w, hi, acc[2 * q + 1], false);
+          const half2_t lo16 = as_half2(__builtin_amdgcn_perm(b[q], a[q], 0x05040100u));   // a.lo, b.lo
+          const half2_t hi16 = as_half2(__builtin_amdgcn_perm(b[q], a[q], 0x07060302u));   // a.hi, b.hi
+          acc[2 * q] = __builtin_amdgcn_fdot2(w, lo16, acc[2 * q], false);
+          acc[2 * q + 1] = __builtin_amdgcn_fdot2(w, hi16, acc[2 * q + 1], false);
         }
-      };
-      // the values of entries x and x + 1 as far as they lie in [lo, hi)
-      auto inside = [](uint32_t vals, int x, int lo, int hi) {
-        return (x >= lo && x < hi ? vals & 0xFFFFu : 0u) | (x + 1 >= lo && x + 1 < hi ? vals & 0xFFFF0000u : 0u);
       };
       auto put = [&](int lr, int v, float s) {   // row lr = LR * strip + r lives at r * 16 + strip
         float* d = osum + v * SUM + (lr % LR) * 16 + lr / LR;
@@ -289,7 +288,7 @@ __device__ __forceinline__ void batch_group_body(const DevMatrix& A, const uint1
 #pragma unroll
         for (int h = 0; h < PRE; ++h)
           if (__builtin_amdgcn_ballot_w64(x0 + 8 * h < hi[k]) != 0)
-            add_pair(cw[k][h], inside(vw[k][h], x0 + 8 * h, lo[k], hi[k]), acc);
+            add_pair(cw[k][h], vw[k][h], x0 + 8 * h, lo[k], (uint32_t)(hi[k] - lo[k]), acc);
         for (int x = x0 + 8 * PRE; __builtin_amdgcn_ballot_w64(x < hi[k]) != 0; x += 32) {   // 32 more entries at a time
           uint32_t cm[4], vm[4];
 #pragma unroll
@@ -301,7 +300,7 @@ __device__ __forceinline__ void batch_group_body(const DevMatrix& A, const uint1
 #pragma unroll
           for (int h = 0; h < 4; ++h)
             if (__builtin_amdgcn_ballot_w64(x + 8 * h < hi[k]) != 0)
-              add_pair(cm[h], inside(vm[h], x + 8 * h, lo[k], hi[k]), acc);
+              add_pair(cm[h], vm[h], x + 8 * h, lo[k], (uint32_t)(hi[k] - lo[k]), acc);
         }
         quad_scatter(acc, lane);
         if (mine[k]) {
@@ -352,7 +351,7 @@ __device__ __forceinline__ void batch_group_body(const DevMatrix& A, const uint1
             if (h > 0 && __builtin_amdgcn_ballot_w64(e < rhi) == 0) break;
             const uint32_t c4[4] = {c8[h].x, c8[h].y, c8[h].z, c8[h].w}, v4[4] = {v8[h].x, v8[h].y, v8[h].z, v8[h].w};
 #pragma unroll
-            for (int k = 0; k < 4; ++k) add_pair(c4[k], inside(v4[k], e + 2 * k, rlo, rhi), acc);
+            for (int k = 0; k < 4; ++k) add_pair(c4[k], v4[k], e + 2 * k, rlo, (uint32_t)(rhi - rlo), acc);
           }
           if ((g0 += 128) > g_hi) break;
           fetch(g0, g_hi, c8, v8);

@@ -127,3 +127,31 @@ def test_weights_are_rounded_from_an_exact_code(P, w, b1, b2, axis, b):
     want = orc.decode_dense(f)[:, cols].T.astype(np.float16)
     assert np.array_equal(got, got.astype(np.float16).astype(np.float32))
     assert (got != want.astype(np.float32)).mean() <= 0.01
+
+
+@pytest.mark.parametrize("w,b1,b2,axis,structure", [(3, 16, 16, 1, "uniform"), (4, 16, 16, 0, "rows8cols4"), (3, 8, 32, 1, "zipf"), (4, 8, 32, 0, "cols64")])
+@pytest.mark.parametrize("b", [4, 16, 64])
+def test_an_infinite_activation_meets_only_its_own_columns_weights(P, w, b1, b2, axis, structure, b):
+    """One infinite activation per vector (NaN in the last vector): every row whose weight there is not zero gives the
+    infinity of the product's sign, whatever the outliers of the rows next to it.  (Not compared: a row with an outlier
+    there.  Slices add w * inf and value * inf, which may be of opposite signs.)"""
+    import torch
+    tr, tc = synth.tile_shape(b1, b2, axis)
+    m, n = 33 * 32, 1664
+    f = synth.make_matrix(m, n, w_bits=w, beta1=b1, beta2=b2, group_axis=axis, outlier_rate=0.1, outlier_structure=structure, seed=(76, w, axis))
+    rng = np.random.default_rng(10)
+    X = synth.make_x(n, b, seed=(77, b))
+    at = rng.permutation(n)[:b]
+    X[np.arange(b), at] = np.where(np.arange(b) % 2 == 0, np.float16(np.inf), np.float16(-np.inf))
+    X[b - 1, at[b - 1]] = np.nan
+    P.spqr_set_option(P.SPQR_OPT_BATCH_PATH, P.SPQR_BATCH_PATH_MATRIX if b <= 16 else P.SPQR_BATCH_PATH_AUTO)
+    P.spqr_set_option(P.SPQR_OPT_BATCH_STEPS, 1000 if b > 16 else 0)
+    got = P.spqr_gemm_smallbatch(P.SpQRMatrix.from_logical(f), torch.from_numpy(X).to("cuda:0")).cpu().numpy()
+    weight = orc.reconstruct(f)[:, at].T                      # the weight each infinity meets, [b, m]
+    sure = (np.abs(weight) > 1e-6) & (weight == orc.decode_dense(f)[:, at].T)   # not a zero in binary16, no outlier
+    assert sure.mean() > 0.7
+    assert np.isnan(got[b - 1]).all()
+    want = np.copysign(np.inf, weight * np.where(np.arange(b) % 2 == 0, 1.0, -1.0)[:, None])
+    ok = (got == want) | ~sure
+    ok[b - 1] = True
+    assert ok.all(), np.argwhere(~ok)[:5]
