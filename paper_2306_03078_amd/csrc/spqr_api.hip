@@ -6,6 +6,7 @@
 #include "../../include/spqr.h"
 #include "spqr_kernels.h"
 #include "spqr_gemv_inst.h"
+#include "spqr_sort.h"
 #include "spqr_test_hooks.h"
 
 namespace {
@@ -277,4 +278,17 @@ extern "C" int spqr_plan_grouped(int count, const int32_t* m, const int32_t* n, 
   *wavefronts = gp.nw;
   *lds_bytes = (int64_t)gp.lds;
   return gp.count;
+}
+
+extern "C" int64_t spqr_sort_ranges(const int32_t* row_ptr, int m, int64_t nnz, int rows, int32_t* ranges) {
+  if (!row_ptr || !ranges) return SPQR_ERR_NULL;
+  if (m < 1 || nnz < 0 || nnz > 0x7FFFFFFFll || rows < 1) return SPQR_ERR_PARAM;
+  const int groups = (m + rows - 1) / rows;
+  for (int g = 0; g < groups; ++g) {
+    const spqr::GroupRange r = spqr::group_range(row_ptr, g, rows, m, (int)nnz);
+    ranges[3 * g] = r.s;
+    ranges[3 * g + 1] = r.z;
+    ranges[3 * g + 2] = (int32_t)spqr::count_slot(r, g, 0);
+  }
+  return spqr::count_slots(nnz, groups);
 }

@@ -7,17 +7,17 @@
 #include "../../include/spqr.h"
 #include "spqr_batch.h"
 #include "spqr_kernels.h"
+#include "spqr_sort.h"
 
 namespace spqr {
 
 // ---------------------------------------------------------------------------
 // The outliers of a group of 16 strips, sorted by phase (8 columns of each of 16 tile columns, the block the multiplying
 // kernel has in LDS at a time): the group's range of `entries` becomes offs[group][phase] .. offs[group][phase + 1], each
-// entry its place in the block (16 bits) and its value.  A counting sort in two kernels over chunks of kSortChunk entries;
-// a chunk never spans two groups, chunk k of the group that starts at entry s is slot (s / kSortChunk) + group + k of
-// `counts`.
+// entry its place in the block (16 bits) and its value.  A counting sort in two kernels over chunks of kSortChunk entries,
+// each with a slot of `counts` (spqr_sort.h).
 // ---------------------------------------------------------------------------
-constexpr int kSortChunk = 4096, kSortPer = kSortChunk / 256, kSortMaxPhases = 512;
+constexpr int kSortPer = kSortChunk / 256, kSortMaxPhases = 512;
 constexpr int kSortWgs = 8;                  // workgroups per group; each takes every 8th chunk
 
 // Phase of a column: a unit of 16 tile columns (1 << unit_shift columns) has kg of them.
@@ -27,7 +27,8 @@ __global__ void __launch_bounds__(256)
 count_phases_kernel(DevMatrix A, int rows, int unit_shift, int kg, int phases, uint32_t* __restrict__ counts) {
   __shared__ uint32_t hist[kSortMaxPhases];
   const int tid = threadIdx.x, group = blockIdx.x;
-  const int s = A.row_ptr[group * rows], z = A.row_ptr[min(group * rows + rows, A.g.m)];
+  const GroupRange range = group_range(A.row_ptr, group, rows, A.g.m, (int)A.nnz);
+  const int s = range.s, z = range.z;
   for (int k = blockIdx.y; s + kSortChunk * k < z; k += kSortWgs) {          // workgroup-uniform
     for (int u = tid; u < phases; u += 256) hist[u] = 0;
     __syncthreads();
@@ -38,7 +39,7 @@ count_phases_kernel(DevMatrix A, int rows, int unit_shift, int kg, int phases, u
     for (int i = 0; i < kSortPer; ++i)
       if (s + kSortChunk * k + tid + 256 * i < z) atomicAdd(&hist[phase_of(min((int)c[i], A.g.n - 1), unit_shift, kg)], 1u);
     __syncthreads();
-    uint32_t* out = counts + (int64_t)(s / kSortChunk + group + k) * phases;
+    uint32_t* out = counts + count_slot(range, group, k) * phases;
     for (int u = tid; u < phases; u += 256) out[u] = hist[u];
     __syncthreads();
   }
@@ -54,9 +55,9 @@ sort_phases_kernel(DevMatrix A, int unit_shift, int kg, int phases, const uint32
   __shared__ int start[kSortMaxPhases];      // this chunk's next free place, by phase
   __shared__ int wave_sum[4];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, group = blockIdx.x, m = A.g.m;
-  const int s = A.row_ptr[group * ROWS], z = A.row_ptr[min(group * ROWS + ROWS, m)];
-  const int chunks = (z - s + kSortChunk - 1) / kSortChunk;
-  const uint32_t* in = counts + (int64_t)(s / kSortChunk + group) * phases;
+  const GroupRange range = group_range(A.row_ptr, group, ROWS, m, (int)A.nnz);
+  const int s = range.s, z = range.z, chunks = sort_chunks(range);
+  const uint32_t* in = counts + count_slot(range, group, 0) * phases;
   for (int k = blockIdx.y; k < max(chunks, 1); k += kSortWgs) {              // workgroup-uniform
     // the chunk's entries and the row pointers are on their way while the places are worked out
     uint16_t c[kSortPer], v[kSortPer];
@@ -94,7 +95,8 @@ sort_phases_kernel(DevMatrix A, int unit_shift, int kg, int phases, const uint32
     __syncthreads();
 #pragma unroll
     for (int w = 0; w < 3; ++w) sum += w < wave ? wave_sum[w] : 0;
-    const int first[2] = {s + sum - total[0] - total[1], s + sum - total[1]};
+    // (no further than z, also where broken row pointers let groups share slots)
+    const int first[2] = {min(s + sum - total[0] - total[1], z), min(s + sum - total[1], z)};
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
       const int u = 2 * tid + h;
@@ -219,7 +221,7 @@ prompt_group_kernel(DevMatrix A, const uint16_t* __restrict__ X, int batch, floa
       uint16_t w[AHEAD];
 #pragma unroll
       for (int k = 0; k < AHEAD; ++k) {
-        at[k] = from + tid + 256 * k < o1 ? at0 + (ent[k] & 0xFFFFu) : spare;
+        at[k] = from + tid + 256 * k < o1 ? at0 + (ent[k] & (PHASE / 2 - 1)) : spare;   // (a place is below PHASE / 2)
         w[k] = all[at[k]];
       }
 #pragma unroll
@@ -373,7 +375,7 @@ static size_t prompt_offsets(const DevMatrix& A, int b, const PromptPlan& p, siz
   at[0] = take(A.perm != nullptr ? (size_t)b * A.g.n * 2 : 0);
   at[1] = take(A.nnz > 0 ? (size_t)A.nnz * 4 : 0);                                                  // sorted entries
   at[2] = take(A.nnz > 0 ? (size_t)p.groups * (p.phases + 1) * 4 : 0);                               // their ranges
-  at[3] = take(A.nnz > 0 ? ((size_t)(A.nnz / kSortChunk) + p.groups + 1) * p.phases * 4 : 0);        // counts
+  at[3] = take(A.nnz > 0 ? (size_t)count_slots(A.nnz, p.groups) * p.phases * 4 : 0);        // counts
   at[4] = take((size_t)p.splits * b * A.g.m * sizeof(float));
   return total;
 }

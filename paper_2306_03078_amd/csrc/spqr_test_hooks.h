@@ -41,6 +41,11 @@ int spqr_plan_grouped(int count, const int32_t* m, const int32_t* n, const int32
                       int w_bits, int beta1, int beta2, int group_axis, int layout_version, int max_waves, int slots,
                       int row_dots_on_matrix_cores, int32_t* entries, int32_t* wavefronts, int64_t* lds_bytes);
 
+/* What the outlier sort of the one-pass product makes of the row pointers (a HOST array of m + 1 entries) of a matrix with
+ * nnz outliers in groups of `rows` rows: ranges[3 * g + 0..2] = first entry, end, slot of the group's first chunk of
+ * 4096 entries (the others follow).  Returns the number of slots the scratch holds, or an SPQR_ERR_* code. */
+int64_t spqr_sort_ranges(const int32_t* row_ptr, int m, int64_t nnz, int rows, int32_t* ranges);
+
 #ifdef __cplusplus
 }
 #endif

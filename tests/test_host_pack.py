@@ -33,7 +33,7 @@ def test_library_exports_every_declared_symbol():
             "spqr_permute_columns", "spqr_permute_symmetric"} == enc
     names = names | enc
     hooks = _declared(os.path.join(ROOT, "paper_2306_03078_amd", "csrc", "spqr_test_hooks.h"))
-    assert hooks == {"spqr_plan_batch_steps", "spqr_plan_grouped"}
+    assert hooks == {"spqr_plan_batch_steps", "spqr_plan_grouped", "spqr_sort_ranges"}
     lib = C.CDLL(P.library_path())
     for nm in sorted(names | hooks):
         assert hasattr(lib, nm), nm
@@ -324,3 +324,40 @@ def test_grouped_plan_arguments():
     assert fn(1, None, one32, one32, one64, 3, 16, 16, 1, 1, 16, 16, 0, ent, C.byref(nw), C.byref(lds)) == -1
     assert fn(1, one32, one32, one32, one64, 5, 16, 16, 1, 1, 16, 16, 0, ent, C.byref(nw), C.byref(lds)) == -3   # w_bits
 
+
+# ---- the outlier sort of the one-pass product: where its groups read and write ----
+
+def _sort_ranges(row_ptr, nnz, rows):
+    lib = C.CDLL(P.library_path())
+    fn = lib.spqr_sort_ranges
+    fn.restype, fn.argtypes = C.c_int64, [C.c_void_p, C.c_int, C.c_int64, C.c_int, C.c_void_p]
+    m = len(row_ptr) - 1
+    out = np.zeros((-(-m // rows), 3), np.int32)
+    row_ptr = np.ascontiguousarray(row_ptr, np.int32)
+    return fn(row_ptr.ctypes.data, m, nnz, rows, out.ctypes.data), out.astype(np.int64)
+
+
+@pytest.mark.parametrize("rows", [128, 256])
+def test_sort_ranges_of_valid_prefixes_are_the_groups_and_their_slots_never_meet(rows):
+    rng = np.random.default_rng(11)
+    for m in (1, 8, 127, 128, 129, 256, 4000):
+        for scale in (0, 3, 200, 9000):
+            ptr = np.concatenate([[0], np.cumsum(rng.integers(0, scale + 1, m) * (rng.random(m) < 0.7))])
+            nnz = int(ptr[-1])
+            slots, got = _sort_ranges(ptr, nnz, rows)
+            bounds = ptr[np.minimum(np.arange(len(got) + 1) * rows, m)]
+            assert (got[:, 0] == bounds[:-1]).all() and (got[:, 1] == bounds[1:]).all()
+            used = [s + k for a, z, s in got for k in range(-(-(z - a) // 4096))]
+            assert len(used) == len(set(used)) and all(0 <= u < slots for u in used)
+
+
+@pytest.mark.parametrize("rows", [128, 256])
+def test_sort_ranges_stay_inside_the_arrays_whatever_the_row_pointers_hold(rows):
+    rng = np.random.default_rng(12)
+    for _ in range(300):
+        m, nnz = int(rng.integers(1, 3000)), int(rng.integers(0, 200000))
+        ptr = rng.integers(-2 ** 31, 2 ** 31, m + 1) if rng.random() < 0.5 else rng.integers(-1000, nnz + 100000, m + 1)
+        slots, got = _sort_ranges(ptr, nnz, rows)
+        a, z, s = got.T
+        assert (0 <= a).all() and (a <= z).all() and (z <= nnz).all()
+        assert (s >= 0).all() and (s + -(-(z - a) // 4096) <= slots).all()
