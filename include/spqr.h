@@ -234,7 +234,7 @@ int spqr_gemv(const spqr_matrix_t* A, const uint16_t* x_f16, void* y, int y_dtyp
  * and a batch / layer large enough to pay for it, slices of up to 16: the
  * weights are read once per slice, dequantised to binary16 and multiplied on
  * the matrix cores, the outliers added in binary32.  That path needs device
- * scratch, splits*b*m*4 bytes (+ 2*b*n with a permutation) per slice, 16 MB at
+ * scratch, a few times b*m*4 bytes (+ 2*b*n with a permutation) per slice, 24 MB at
  * most where the columns are split.
  * THIS entry point takes it from the library: one scratch buffer per stream
  * (up to 8 streams per device), kept until the process ends and grown on
@@ -271,8 +271,8 @@ int spqr_gemm_smallbatch(const spqr_matrix_t* A, const uint16_t* X_f16, int b, v
  * call takes kernels that need none.  A is a HOST array of `count` descriptor
  * pointers (1 <= count <= SPQR_MAX_FUSED; they must agree as for
  * spqr_gemm_fused).  Host arithmetic only; a negative return is an SPQR_ERR_*
- * code.  The value depends on the descriptors' shapes, nnz and perm, on b and
- * on the options of spqr_set_option, not on pointers or the stream. */
+ * code.  The value depends on the descriptors' shapes, nnz, max_row_nnz and perm,
+ * on b and on the options of spqr_set_option, not on pointers or the stream. */
 int64_t spqr_workspace_bytes(const spqr_matrix_t* const* A, int count, int b);
 
 /* spqr_gemm_smallbatch with scratch the CALLER owns (Sec. 4.2's product, as
@@ -373,13 +373,18 @@ int spqr_gemv_grouped(const spqr_matrix_t* const* A, int count, const uint16_t* 
  *                          multiply (0: the library's rule)
  *   SPQR_OPT_GEMV_PLAN     16 * P + R > 0: the batch-1 kernel runs with P
  *                          wavefronts per strip and R strips per workgroup
- *                          (clamped to what the matrix and the kernel allow) */
+ *                          (clamped to what the matrix and the kernel allow)
+ *   SPQR_OPT_BATCH_SHARES  k > 0: in the matrix-core path's launch k - 1
+ *                          workgroups (0, 1, 2 or 4; 2 at most with 8 x 32
+ *                          tiles) share the outliers beside each dense one, 0
+ *                          of them: the dense one takes them too */
 #define SPQR_OPT_BATCH_PATH     0
 #define SPQR_OPT_FORCE_GENERIC  1
 #define SPQR_OPT_BATCH_STEPS    2
 #define SPQR_OPT_DENSE_ROWS     3
 #define SPQR_OPT_GEMV_PLAN      4
-#define SPQR_OPT_COUNT_         5
+#define SPQR_OPT_BATCH_SHARES   5
+#define SPQR_OPT_COUNT_         6
 #define SPQR_BATCH_PATH_AUTO    0
 #define SPQR_BATCH_PATH_VECTOR  1
 #define SPQR_BATCH_PATH_MATRIX  2

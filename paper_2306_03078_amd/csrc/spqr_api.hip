@@ -104,6 +104,7 @@ extern "C" int spqr_set_option(int option, int value) {
     case SPQR_OPT_FORCE_GENERIC: ok = value == 0 || value == 1; break;
     case SPQR_OPT_BATCH_STEPS: ok = value >= 0; break;
     case SPQR_OPT_DENSE_ROWS: ok = value == 0 || value == 64 || value == 128; break;
+    case SPQR_OPT_BATCH_SHARES: ok = value == 0 || value == 1 || value == 2 || value == 3 || value == 5; break;
     case SPQR_OPT_GEMV_PLAN: ok = value >= 0 && value < 16 * 17; break;
     default: ok = false;
   }
@@ -250,6 +251,22 @@ extern "C" int spqr_dequant_dense(const spqr_matrix_t* A, int what, void* out, v
 extern "C" int spqr_plan_batch_steps(int groups, int nsteps, int slots_one_step, int slots, int long_workgroups) {
   if (groups < 1 || nsteps < 1 || slots_one_step < 1 || slots < 1 || long_workgroups < 0) return SPQR_ERR_PARAM;
   return spqr::plan_batch_steps(groups, nsteps, slots_one_step, slots, long_workgroups);
+}
+
+extern "C" int spqr_plan_batch(int count, const int32_t* m, const int32_t* n, const int32_t* max_row_nnz, const int64_t* nnz,
+                               int w_bits, int beta1, int beta2, int group_axis, int b, int32_t* plan) {
+  if (!m || !n || !max_row_nnz || !nnz || !plan) return SPQR_ERR_NULL;
+  if (count < 1 || count > SPQR_MAX_FUSED || b < 1 || b > 16) return SPQR_ERR_PARAM;
+  spqr::DevMatrix D[SPQR_MAX_FUSED] = {};
+  for (int i = 0; i < count; ++i) {
+    if (max_row_nnz[i] < 0 || nnz[i] < 0 || n[i] != n[0]) return SPQR_ERR_PARAM;
+    const int rc = spqr::make_geometry(spqr::kBilevel, m[i], n[i], w_bits, 3, 3, beta1, beta2, group_axis, &D[i].g);
+    if (rc) return rc;
+    D[i].nnz = nnz[i];
+    D[i].max_row_nnz = max_row_nnz[i];
+  }
+  if (!spqr::mfma_has_instance(D[0].g)) return SPQR_ERR_PARAM;
+  return spqr::plan_batch_hook(D, count, b, &plan[0], &plan[1], &plan[2]);
 }
 
 extern "C" int spqr_plan_grouped(int count, const int32_t* m, const int32_t* n, const int32_t* max_row_nnz,

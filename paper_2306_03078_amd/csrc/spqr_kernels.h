@@ -77,6 +77,9 @@ size_t mfma_workspace_bound(const DevMatrix* As, int count, int b, bool fused);
 // The library's static device array as a workspace (callers that cannot allocate); its size is
 // SPQR_STATIC_SCRATCH_BYTES.
 hipError_t static_workspace(Workspace* ws);
+// The launch plan of a slice of b vectors (host arithmetic only): units of 16 tile columns per split, splits, workgroups
+// that share a split's outliers.  Returns the units of the matrix.
+int plan_batch_hook(const DevMatrix* As, int count, int b, int* per, int* splits, int* shares);
 // Steps of 64 tiles per workgroup of the batch path's dense launch (host arithmetic only, see the definition).
 int plan_batch_steps(int groups, int nsteps, int slots_one_step, int slots, int long_workgroups);
 

@@ -117,10 +117,12 @@ __device__ __forceinline__ void lower_columns(const uint16_t* __restrict__ col, 
 }
 
 // The sums of one workgroup: group `group` of matrix A, units [u_lo, u_hi) of its columns.  X: the batch in the
-// matrix's column order.  P: this split's partial results of the matrix (b * m floats).
-template <int W, int TR, int TC, int AXIS>
+// matrix's column order.  P: this split's partial results of the matrix (b * m floats).  APART: the workgroup takes only
+// the dense part or only the outliers of the sets [set_lo, set_hi) of 64 rows (and writes those rows), else both.
+template <int W, int TR, int TC, int AXIS, bool APART>
 __device__ __forceinline__ void batch_group_body(const DevMatrix& A, const uint16_t* __restrict__ X, int batch,
-                                                 float* __restrict__ P, int group, int u_lo, int u_hi, uint8_t* smem) {
+                                                 float* __restrict__ P, int group, int u_lo, int u_hi, int set_lo, int set_hi,
+                                                 uint8_t* smem) {
   using SH = BatchShape<TR, TC>;
   using DQ = Dequant<W, TR, TC, AXIS>;
   using B = BatchTile<W, TR, TC, AXIS>;
@@ -129,7 +131,7 @@ __device__ __forceinline__ void batch_group_body(const DevMatrix& A, const uint1
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int i16 = lane & 15, g4 = lane >> 4;
   const int n = A.g.n, ntc = A.g.ntc, ntr = A.g.ntr * NSUB, m = A.g.m;
-  const bool sparse = A.nnz > 0;
+  const bool dense = !APART || set_lo >= set_hi, sparse = A.nnz > 0 && (!APART || !dense);
   const int outliers_first = sparse ? (int)((blockIdx.x + gridDim.x * blockIdx.y) / kCUs) & 1 : 0;
   uint16_t* xt = reinterpret_cast<uint16_t*>(smem);                       // XT[COLS][16]
   float* red = reinterpret_cast<float*>(smem);                            // afterwards: slices of [16][20]
@@ -184,12 +186,12 @@ __device__ __forceinline__ void batch_group_body(const DevMatrix& A, const uint1
     const int k0 = c_lo * kUnitTiles * TC, k1 = min(n, c_hi * kUnitTiles * TC);
     B t0, t1;
     u32x4 x0[KG], x1[KG];
-    issue(t0, x0, c_lo);
+    if (dense) issue(t0, x0, c_lo);
     if (sparse) {
       if (c_lo > u_lo) __syncthreads();        // everyone is done with the previous piece
       int bounds[2] = {0, 0};                  // of the row's entries, then of those in the piece; requested ahead of X
       const int row = group * ROWS + tid;
-      if (tid < ROWS && row < m) {
+      if ((APART ? tid >= 64 * set_lo && tid < 64 * set_hi : tid < ROWS) && row < m) {
         bounds[0] = A.row_ptr[row];
         bounds[1] = A.row_ptr[row + 1];
       }
@@ -267,6 +269,7 @@ __device__ __forceinline__ void batch_group_body(const DevMatrix& A, const uint1
       bool mine[SETS];                           // not a long row: its sums are written below
 #pragma unroll
       for (int k = 0; k < SETS; ++k) {
+        if (APART && (k < set_lo || k >= set_hi)) continue;   // workgroup-uniform
         const int lr = 16 * (wave + 4 * k) + (lane >> 2);
         lo[k] = row_lo[lr];
         hi[k] = row_hi[lr];
@@ -281,6 +284,7 @@ __device__ __forceinline__ void batch_group_body(const DevMatrix& A, const uint1
       }
 #pragma unroll
       for (int k = 0; k < SETS; ++k) {
+        if (APART && (k < set_lo || k >= set_hi)) continue;
         float acc[16];
 #pragma unroll
         for (int v = 0; v < 16; ++v) acc[v] = 0.f;
@@ -368,8 +372,11 @@ __device__ __forceinline__ void batch_group_body(const DevMatrix& A, const uint1
     // weights stream.
 #pragma unroll 1
     for (int part = 0; part < 2; ++part) {
-      if (part == outliers_first) dense_part();
-      else if (sparse) outlier_part();
+      if (part == outliers_first) {
+        if (dense) dense_part();
+      } else if (sparse) {
+        outlier_part();
+      }
     }
   }
 
@@ -378,12 +385,16 @@ __device__ __forceinline__ void batch_group_body(const DevMatrix& A, const uint1
   __syncthreads();
   constexpr int QR = LR / 4;
   const int at = i16 * 20 + 4 * g4;
+  if (dense) {                                 // workgroup-uniform
 #pragma unroll
-  for (int r = 0; r < LR; ++r) {
-    const int q = r / QR;                      // the wavefront that adds up row r
-    if (q != wave) *reinterpret_cast<float4_t*>(red + (3 * r + (wave < q ? wave : wave - 1)) * SH::SLICE + at) = D[r];
+    for (int r = 0; r < LR; ++r) {
+      const int q = r / QR;                    // the wavefront that adds up row r
+      if (q != wave) *reinterpret_cast<float4_t*>(red + (3 * r + (wave < q ? wave : wave - 1)) * SH::SLICE + at) = D[r];
+    }
+    __syncthreads();
+  } else if (4 * g4 * LR < 64 * set_lo || 4 * g4 * LR >= 64 * set_hi) {
+    return;                                    // another workgroup's rows
   }
-  __syncthreads();
   if (i16 >= batch) return;
   // partial results of a group: [vector][row of the strip][strip], `strips` of them (16, fewer in the last group)
   const int strips = min(16, ntr - group * 16);
@@ -392,9 +403,11 @@ __device__ __forceinline__ void batch_group_body(const DevMatrix& A, const uint1
   for (int r = 0; r < LR; ++r) {
     if (r / QR != wave) continue;              // wave-uniform
     float4_t sum = float4_t{0.f, 0.f, 0.f, 0.f};
+    if (dense) {
 #pragma unroll
-    for (int w = 0; w < 4; ++w)
-      sum += w == r / QR ? D[r] : *reinterpret_cast<const float4_t*>(red + (3 * r + (w < r / QR ? w : w - 1)) * SH::SLICE + at);
+      for (int w = 0; w < 4; ++w)
+        sum += w == r / QR ? D[r] : *reinterpret_cast<const float4_t*>(red + (3 * r + (w < r / QR ? w : w - 1)) * SH::SLICE + at);
+    }
     if (sparse) sum += *reinterpret_cast<const float4_t*>(osum + i16 * SUM + 16 * r + 4 * g4);
     if (strips == 16) {
       *reinterpret_cast<float4_t*>(out + 16 * r + 4 * g4) = sum;       // 16-byte stores: m is a multiple of 8
@@ -406,13 +419,23 @@ __device__ __forceinline__ void batch_group_body(const DevMatrix& A, const uint1
   }
 }
 
-template <int W, int TR, int TC, int AXIS>
+// APART: z == 0 is the dense part, the other z share the sets of 64 rows of the outliers, whose sums are partial results of
+// their own (gridDim.y of them, behind the dense ones).
+template <int W, int TR, int TC, int AXIS, bool APART>
+__device__ __forceinline__ void batch_group_share(const DevMatrix& A, const uint16_t* __restrict__ X, int batch,
+                                                  float* __restrict__ P, int group, int units_per_split, uint8_t* smem) {
+  const int units = (A.g.ntc + kUnitTiles - 1) / kUnitTiles, u_lo = blockIdx.y * units_per_split;   // never empty (host)
+  const int z = APART ? blockIdx.z : 0, sets = APART ? BatchShape<TR, TC>::ROWS / 64 / (gridDim.z - 1) : 0;
+  const int split = blockIdx.y + (z > 0 ? gridDim.y : 0);
+  batch_group_body<W, TR, TC, AXIS, APART>(A, X, batch, P + (int64_t)split * batch * A.g.m, group, u_lo,
+                                           min(units, u_lo + units_per_split), z > 0 ? (z - 1) * sets : 0, z * sets, smem);
+}
+
+template <int W, int TR, int TC, int AXIS, bool APART>
 __global__ void __launch_bounds__(256, 2)
 batch_group_kernel(DevMatrix A, const uint16_t* __restrict__ X, int batch, float* __restrict__ P, int units_per_split) {
   extern __shared__ __align__(16) uint8_t smem[];
-  const int units = (A.g.ntc + kUnitTiles - 1) / kUnitTiles, u_lo = blockIdx.y * units_per_split;   // never empty (host)
-  batch_group_body<W, TR, TC, AXIS>(A, X, batch, P + (int64_t)blockIdx.y * batch * A.g.m, blockIdx.x, u_lo,
-                                    min(units, u_lo + units_per_split), smem);
+  batch_group_share<W, TR, TC, AXIS, APART>(A, X, batch, P, blockIdx.x, units_per_split, smem);
 }
 
 // Several matrices that share the batch X and the format (q/k/v, gate/up of a decoder block) in one grid: blockIdx.x
@@ -428,7 +451,7 @@ struct BatchFused {
   BatchFusedItem it[SPQR_MAX_FUSED];
 };
 
-template <int W, int TR, int TC, int AXIS>
+template <int W, int TR, int TC, int AXIS, bool APART>
 __global__ void __launch_bounds__(256, 2)
 batch_group_fused_kernel(BatchFused F, const uint16_t* __restrict__ X, int batch, int units_per_split) {
   extern __shared__ __align__(16) uint8_t smem[];
@@ -437,10 +460,7 @@ batch_group_fused_kernel(BatchFused F, const uint16_t* __restrict__ X, int batch
     if (bx < F.it[i].groups) break;
     bx -= F.it[i].groups;
   }
-  const BatchFusedItem& it = F.it[i];
-  const int units = (it.A.g.ntc + kUnitTiles - 1) / kUnitTiles, u_lo = blockIdx.y * units_per_split;
-  batch_group_body<W, TR, TC, AXIS>(it.A, X, batch, it.P + (int64_t)blockIdx.y * batch * it.A.g.m, bx, u_lo,
-                                    min(units, u_lo + units_per_split), smem);
+  batch_group_share<W, TR, TC, AXIS, APART>(F.it[i].A, X, batch, F.it[i].P, bx, units_per_split, smem);
 }
 
 // Y[v][row] = sum over the splits of P, in their order, rounded once to the output type.  One workgroup per group of
@@ -661,30 +681,139 @@ int plan_batch_steps(int groups, int nsteps, int slots_one_step, int slots, int 
 
 // Groups of 16 strips of a matrix, and the units of its columns the splits are made of.
 static int batch_groups(const Geometry& g) { return (g.m / lane_rows(g.tile_rows) + 15) / 16; }
+static int batch_sets(const Geometry& g) { return lane_rows(g.tile_rows) / 4; }      // of 64 rows
 static int batch_units(const Geometry& g) { return (g.ntc + kUnitTiles - 1) / kUnitTiles; }
 
-// Units per split for `groups` groups of this format, by a model of the launch in microseconds fitted to sweeps of the
-// units (4096^2 to 20480 x 5120 with 3-bit codes, 17920 x 6656, three of 6656^2 and 8192 x 22016, 4 to 16 vectors): a CU's
-// one workgroup takes 2.3 per unit, two take 4.4 together, another piece of XT (outliers only) costs 4.5, a workgroup
-// 1, a further round of the chip's 512 places 3.  Measured, chosen against next best: 11008 x 4096 at 16 vectors, 3 units
-// 22.2 us (258 workgroups) against 4 units 23.9 and 2 units 26.1; 17920 x 6656, 4 units 47 against 5 units 51; 13824 x
-// 5120, 5 units 27.3 against 3 units 30.2; 5120^2, 2 units 18.5 against 1 unit 21.1.  The partial results stay below
-// 16 MB: beyond that the columns are not split (so many rows fill the chip by themselves).
-static int batch_units_per_split(const Geometry& g, int groups, bool sparse, int64_t values) {
-  const int units = batch_units(g), chunk = 1536 / (kUnitTiles * g.tile_cols);
-  if (const int v = option(SPQR_OPT_BATCH_STEPS); v >= 1) return v < units ? v : units;   // pinned (tuning, tests)
-  const int64_t most = values > 0 ? ((int64_t)4 << 20) / values : 1;       // splits of `values` floats each
-  int best = units;
-  double best_cost = 1e30;
-  for (int s = 1; s <= units && (s == 1 || s <= most); ++s) {
-    const int per = (units + s - 1) / s, splits = (units + per - 1) / per;
-    const int64_t wgs = (int64_t)groups * splits, k = wgs <= 8 ? 1 : (wgs - 8 + kCUs - 1) / kCUs;   // on the fullest CU
-    const double pieces = sparse ? 4.5 * ((per + chunk - 1) / chunk - 1) : 0.0;
-    const double one = 1.0 + 2.3 * per + pieces, two = 2.0 + 4.4 * per + pieces;
-    const double cost = (double)(k / 2) * two + (double)(k % 2) * one + 3.0 * (double)((k + 1) / 2 - 1);
-    if (cost < best_cost - 1e-9) { best_cost = cost; best = per; }
+// Plan of a launch for the groups of one matrix or of several: units per split and how many workgroups share the outliers
+// of a split of a group beside its dense one (0: the dense workgroup takes them too), by a model of the launch in
+// microseconds.  The chip's 256 CUs take the workgroups in grid order, each the CU with the least work; the launch lasts
+// `start` and the longest CU.  A workgroup that does both costs both + both_unit per unit of 16 tile columns, for every further
+// piece of XT (with outliers) `piece`, and for its outliers (thousands of entries, rows far longer than the mean); a
+// dense one and one of outliers less each, but all of them together more.  So outliers go apart where the chip has CUs left
+// over (small layers: the outliers' trips to memory run beside the weights' instead of behind them, and heavy rows are
+// shared out further), and wide pieces of XT pay on large ones.
+// Fitted to every split and share of 173 layers and sets of layers (1024^2 to two of 22016 x 8192, 16 vectors; uniform, full
+// columns, full rows, Zipf rows): the choice is 1.5 % off the best on average, 14 % at most, and 11 % faster than the
+// model before, which knew no shares and priced a piece at 4.5 (5 % slower at most): 22016 x 8192 with 8 x 32 tiles 80 -> 63
+// us (3 units), 5120^2 4-bit with Zipf rows 24.9 -> 18.3, 1024^2 with them 16.9 -> 11.1, two of 22016 x 8192 with 16 x 16
+// tiles 118 -> 98; 17920 x 6656 as before.
+struct BatchCosts {
+  float start_both, both, both_unit, both_entry, both_heavy, both_heavy_unit;              // workgroups that do both
+  float start_apart, dense, dense_unit, outliers, outlier_unit, entry, heavy, heavy_unit;  // (entry, heavy: shared)
+};
+constexpr float kPieceBoth = 7.f, kPieceApart = 6.f;
+static const BatchCosts kCosts16x16 = {13.72f, 3.05f, 1.93f, 0.05f, 4.81f, 1.22f, 7.54f, 1.51f, 1.75f, 2.47f, 0.03f, 1.49f, 9.33f, 0.54f};
+static const BatchCosts kCosts8x32 = {8.55f, 4.1f, 2.86f, 0.63f, 1.8f, 0.f, 6.83f, 0.93f, 2.34f, 3.21f, 0.26f, 1.15f, 3.12f, 0.f};
+static const BatchCosts kCosts32x8 = {7.98f, 6.48f, 1.29f, 0.32f, 3.f, 0.f, 5.08f, 1.55f, 1.15f, 5.37f, 0.f, 1.04f, 3.f, 0.f};
+
+// The chip's CUs by the work they have been given.
+class CuLoads {
+  struct Level { float load; int64_t cus; };
+  Level l_[16];                              // rising loads
+  int n_ = 1;
+  void put(float load, int64_t cus) {
+    int k = n_;
+    while (k > 0 && l_[k - 1].load > load) --k;
+    if (k > 0 && load - l_[k - 1].load < 1e-3f) { l_[k - 1].cus += cus; return; }
+    if (n_ == 16) { l_[n_ - 1].cus += cus; return; }   // (never seen; the longest CU stays right to a level)
+    for (int i = n_++; i > k; --i) l_[i] = l_[i - 1];
+    l_[k] = {load, cus};
   }
+
+ public:
+  CuLoads() { l_[0] = {0.f, kCUs}; }
+  void add(int64_t workgroups, float cost) {
+    if (workgroups <= 0 || cost <= 0.f) return;
+    while (workgroups > 0) {
+      if (n_ == 1 && workgroups >= kCUs) {
+        l_[0].load += cost * (float)(workgroups / kCUs);
+        workgroups %= kCUs;
+        continue;
+      }
+      const int64_t k = workgroups < l_[0].cus ? workgroups : l_[0].cus;
+      const float load = l_[0].load + cost;
+      if ((l_[0].cus -= k) == 0) {
+        --n_;
+        for (int i = 0; i < n_; ++i) l_[i] = l_[i + 1];
+      }
+      put(load, k);
+      workgroups -= k;
+    }
+  }
+  float longest() const { return l_[n_ - 1].load; }
+};
+
+struct BatchPlan { int groups, per, splits, shares, parts; };  // parts: partial results, dense and of the outliers
+
+// Partial results stay below 24 MB where there is more than one: beyond that the columns are not split (so many rows fill
+// the chip by themselves).
+static BatchPlan plan_batch(const DevMatrix* As, int count, int b) {
+  const Geometry& g = As[0].g;
+  const int units = batch_units(g), chunk = 1536 / (kUnitTiles * g.tile_cols), sets = batch_sets(g);
+  int groups = 0;
+  int64_t rows = 0, nnz = 0;
+  bool heavy = false;                        // rows far longer than the mean, by the descriptor's hint
+  for (int i = 0; i < count; ++i) {
+    groups += batch_groups(As[i].g);
+    rows += As[i].g.m;
+    nnz += As[i].nnz;
+    heavy = heavy || (double)As[i].max_row_nnz > kLongRow + 8.0 * (double)As[i].nnz / As[i].g.m;
+  }
+  const bool sparse = nnz > 0;
+  const BatchCosts& c = g.tile_cols == 16 ? kCosts16x16 : (g.tile_cols == 32 ? kCosts8x32 : kCosts32x8);
+  const float entries = (float)((double)nnz / (double)rows * 16 * lane_rows(g.tile_rows) / units / 1000.0);   // per unit
+  const int64_t values = (int64_t)b * rows, most = values > 0 ? ((int64_t)6 << 20) / values : 1;
+  const int pin_per = option(SPQR_OPT_BATCH_STEPS), pin_shares = option(SPQR_OPT_BATCH_SHARES);
+  auto cost = [&](int per, int splits, int shares) {
+    const int last = units - (splits - 1) * per;
+    auto pieces = [&](int p, float price) { return sparse ? price * (float)((p + chunk - 1) / chunk - 1) : 0.f; };
+    auto both = [&](int p) {
+      return c.both + c.both_unit * (float)p + pieces(p, kPieceBoth) + c.both_entry * entries * (float)p +
+             (heavy ? c.both_heavy + c.both_heavy_unit * (float)p : 0.f);
+    };
+    auto dense = [&](int p) { return c.dense + c.dense_unit * (float)p; };
+    auto outliers = [&](int p) {
+      return c.outliers + pieces(p, kPieceApart) + c.outlier_unit * (float)p +
+             (c.entry * entries * (float)p + (heavy ? c.heavy + c.heavy_unit * (float)p : 0.f)) / (float)shares;
+    };
+    CuLoads cu;
+    const bool apart = shares > 0 || !sparse;
+    cu.add((int64_t)groups * (splits - 1), apart ? dense(per) : both(per));
+    cu.add(groups, apart ? dense(last) : both(last));
+    if (shares > 0) {
+      cu.add((int64_t)groups * (splits - 1) * shares, outliers(per));
+      cu.add((int64_t)groups * shares, outliers(last));
+    }
+    return (apart ? c.start_apart : c.start_both) + cu.longest();
+  };
+  BatchPlan best = {groups, units, 1, 0, 1};
+  float best_cost = 1e30f;
+  auto consider = [&](int per) {
+    const int splits = (units + per - 1) / per;
+    if (pin_per < 1 && per != (units + splits - 1) / splits) return;       // the same splits in more even pieces exist
+    for (int shares = 0; shares <= (sparse ? sets : 0); shares = shares == 0 ? 1 : 2 * shares) {
+      const int parts = splits * (shares > 0 ? 2 : 1);
+      if (pin_shares >= 1 && shares != (pin_shares - 1 < sets ? pin_shares - 1 : sets) && sparse) continue;
+      if (parts > 1 && parts > most && !(pin_per >= 1 && shares == 0)) continue;
+      const float t = cost(per, splits, shares);
+      if (t < best_cost - 1e-3f) { best_cost = t; best = {groups, per, splits, shares, parts}; }
+    }
+  };
+  if (pin_per >= 1) {                        // pinned (tuning, tests)
+    best.per = pin_per < units ? pin_per : units;
+    best.parts = best.splits = (units + best.per - 1) / best.per;
+    consider(best.per);
+    return best;
+  }
+  for (int per = chunk < units ? chunk : units; per >= 1; --per) consider(per);
+  for (int per = chunk + 1; per <= units && best_cost > 1e29f; ++per) consider(per);   // few parts allowed: more pieces each
   return best;
+}
+
+int plan_batch_hook(const DevMatrix* As, int count, int b, int* per, int* splits, int* shares) {
+  const BatchPlan p = plan_batch(As, count, b);
+  *per = p.per; *splits = p.splits; *shares = p.shares;
+  return batch_units(As[0].g);
 }
 
 static size_t up256(size_t v) { return (v + 255) & ~(size_t)255; }
@@ -718,15 +847,15 @@ static hipError_t launch_mfma_t(const DevMatrix& A, const uint16_t* X, int b, vo
                                 const Workspace& ws) {
   using SH = BatchShape<TR, TC>;
   const Geometry& g = A.g;
-  static PerDevice ready;
-  hipError_t e = allow_lds(&batch_group_kernel<W, TR, TC, AXIS>, SH::LDS, ready);
-  if (e != hipSuccess) return e;
-  const int groups = batch_groups(g), units = batch_units(g);
-  const int per = batch_units_per_split(g, groups, A.nnz > 0, (int64_t)b * g.m), splits = (units + per - 1) / per;
+  const BatchPlan p = plan_batch(&A, 1, b);
   const size_t xp_bytes = A.perm != nullptr ? up256((size_t)b * g.n * 2) : 0;
+  static PerDevice ready[2];
+  const auto kernel = p.shares > 0 ? &batch_group_kernel<W, TR, TC, AXIS, true> : &batch_group_kernel<W, TR, TC, AXIS, false>;
+  hipError_t e = allow_lds(kernel, SH::LDS, ready[p.shares > 0]);
+  if (e != hipSuccess) return e;
   Scratch sc;
   uint8_t* scratch = nullptr;
-  e = batch_scratch(ws, xp_bytes + (size_t)splits * b * g.m * sizeof(float), stream, true, &sc, &scratch);
+  e = batch_scratch(ws, xp_bytes + (size_t)p.parts * b * g.m * sizeof(float), stream, true, &sc, &scratch);
   if (e != hipSuccess) return e;
   float* P = reinterpret_cast<float*>(scratch + xp_bytes);
   const uint16_t* Xin = X;
@@ -736,10 +865,10 @@ static hipError_t launch_mfma_t(const DevMatrix& A, const uint16_t* X, int b, vo
     Xin = xp;
   }
   if (e == hipSuccess) {
-    hipLaunchKernelGGL((batch_group_kernel<W, TR, TC, AXIS>), dim3(groups, splits), dim3(256), SH::LDS, stream, A, Xin, b, P, per);
+    hipLaunchKernelGGL(kernel, dim3(p.groups, p.splits, 1 + p.shares), dim3(256), SH::LDS, stream, A, Xin, b, P, p.per);
     e = hipGetLastError();
   }
-  if (e == hipSuccess) e = launch_sum_groups(g, P, splits, b, Y, y_dtype, stream);
+  if (e == hipSuccess) e = launch_sum_groups(g, P, p.parts, b, Y, y_dtype, stream);
   const hipError_t ef = scratch_put(&sc, stream);
   return e == hipSuccess ? ef : e;
 }
@@ -774,29 +903,23 @@ static hipError_t launch_mfma_fused_t(const DevMatrix* As, int count, const uint
                                       hipStream_t stream, const Workspace& ws) {
   using SH = BatchShape<TR, TC>;
   const Geometry& g0 = As[0].g;
-  static PerDevice ready;
-  hipError_t e = allow_lds(&batch_group_fused_kernel<W, TR, TC, AXIS>, SH::LDS, ready);
-  if (e != hipSuccess) return e;
   BatchFused F;
   F.count = count;
-  int groups = 0;
-  int64_t rows = 0;
-  bool sparse = false;
   for (int i = 0; i < count; ++i) {
     F.it[i].A = As[i];
     F.it[i].Y = Ys[i];
     F.it[i].groups = batch_groups(As[i].g);
-    groups += F.it[i].groups;
-    rows += As[i].g.m;
-    sparse = sparse || As[i].nnz > 0;
   }
-  const int units = batch_units(g0), per = batch_units_per_split(g0, groups, sparse, (int64_t)b * rows);
-  const int splits = (units + per - 1) / per;
+  const BatchPlan p = plan_batch(As, count, b);
   size_t total = As[0].perm != nullptr ? up256((size_t)b * g0.n * 2) : 0, at[SPQR_MAX_FUSED];
   for (int i = 0; i < count; ++i) {
     at[i] = total;
-    total += up256((size_t)splits * b * As[i].g.m * sizeof(float));
+    total += up256((size_t)p.parts * b * As[i].g.m * sizeof(float));
   }
+  static PerDevice ready[2];
+  const auto kernel = p.shares > 0 ? &batch_group_fused_kernel<W, TR, TC, AXIS, true> : &batch_group_fused_kernel<W, TR, TC, AXIS, false>;
+  hipError_t e = allow_lds(kernel, SH::LDS, ready[p.shares > 0]);
+  if (e != hipSuccess) return e;
   Scratch sc;
   uint8_t* scratch = nullptr;
   e = batch_scratch(ws, total, stream, false, &sc, &scratch);
@@ -809,11 +932,11 @@ static hipError_t launch_mfma_fused_t(const DevMatrix* As, int count, const uint
     Xin = xp;
   }
   if (e == hipSuccess) {
-    hipLaunchKernelGGL((batch_group_fused_kernel<W, TR, TC, AXIS>), dim3(groups, splits), dim3(256), SH::LDS, stream, F, Xin, b, per);
+    hipLaunchKernelGGL(kernel, dim3(p.groups, p.splits, 1 + p.shares), dim3(256), SH::LDS, stream, F, Xin, b, p.per);
     e = hipGetLastError();
   }
   if (e == hipSuccess) {
-    hipLaunchKernelGGL(sum_groups_fused_kernel, dim3(groups, b), dim3(SH::ROWS), 0, stream, F, splits, b, y_dtype);
+    hipLaunchKernelGGL(sum_groups_fused_kernel, dim3(p.groups, b), dim3(SH::ROWS), 0, stream, F, p.parts, b, y_dtype);
     e = hipGetLastError();
   }
   const hipError_t ef = scratch_put(&sc, stream);
@@ -828,26 +951,16 @@ static hipError_t launch_mfma_fused_t(const DevMatrix* As, int count, const uint
 // Scratch a batch of b <= 16 vectors needs on this path: for the matrices one at a time and, if `fused`, all of them in
 // one launch set.
 size_t mfma_workspace_bound(const DevMatrix* As, int count, int b, bool fused) {
-  const int units = batch_units(As[0].g);
   const size_t xp = As[0].perm != nullptr ? up256((size_t)b * As[0].g.n * 2) : 0;
   size_t worst = 0;
   for (int i = 0; i < count; ++i) {
-    const int per = batch_units_per_split(As[i].g, batch_groups(As[i].g), As[i].nnz > 0, (int64_t)b * As[i].g.m);
-    const size_t need = xp + up256((size_t)((units + per - 1) / per) * b * As[i].g.m * sizeof(float));
+    const size_t need = xp + up256((size_t)plan_batch(&As[i], 1, b).parts * b * As[i].g.m * sizeof(float));
     if (need > worst) worst = need;
   }
   if (!fused) return worst;
-  int groups = 0;
-  int64_t rows = 0;
-  bool sparse = false;
-  for (int i = 0; i < count; ++i) {
-    groups += batch_groups(As[i].g);
-    rows += As[i].g.m;
-    sparse = sparse || As[i].nnz > 0;
-  }
-  const int per = batch_units_per_split(As[0].g, groups, sparse, (int64_t)b * rows), splits = (units + per - 1) / per;
+  const BatchPlan p = plan_batch(As, count, b);
   size_t total = xp;
-  for (int i = 0; i < count; ++i) total += up256((size_t)splits * b * As[i].g.m * sizeof(float));
+  for (int i = 0; i < count; ++i) total += up256((size_t)p.parts * b * As[i].g.m * sizeof(float));
   return total > worst ? total : worst;
 }
 

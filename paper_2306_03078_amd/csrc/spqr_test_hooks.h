@@ -25,6 +25,14 @@ extern "C" {
  * A negative return is an SPQR_ERR_* code (an argument below 1, or long_workgroups below 0). */
 int spqr_plan_batch_steps(int groups, int nsteps, int slots_one_step, int slots, int long_workgroups);
 
+/* Launch plan of a slice of b <= 16 vectors on the matrix-core path of spqr_gemm_smallbatch (count = 1) or of
+ * spqr_gemm_fused for matrices m[i] x n[0] of one format (layout 1, 3-bit statistic codes) with nnz[i] outliers and the
+ * hint max_row_nnz[i]; host arithmetic only, no device is touched.  plan[0..2] = units of 16 tile columns per split,
+ * splits, workgroups that share a split's outliers beside its dense one (0: none).  Returns the units of the matrix, or
+ * an SPQR_ERR_* code (SPQR_ERR_PARAM also for a format without that path). */
+int spqr_plan_batch(int count, const int32_t* m, const int32_t* n, const int32_t* max_row_nnz, const int64_t* nnz, int w_bits,
+                    int beta1, int beta2, int group_axis, int b, int32_t* plan);
+
 /* Plan of ONE launch of spqr_gemv_grouped for `count` (1..8) matrices of one format (w_bits, beta1, beta2,
  * group_axis, layout_version; 3-bit statistic codes, or 16-bit statistics for layout 3), matrix i being m[i] x n[i]
  * with nnz[i] outliers and the hint max_row_nnz[i]; host arithmetic only, no device is touched.  The matrices of

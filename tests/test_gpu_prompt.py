@@ -24,11 +24,12 @@ def P():
     return P
 
 
-def run(P, f, b, steps=0):
+def run(P, f, b, steps=0, shares=0):
     import torch
     A = P.SpQRMatrix.from_logical(f)
     X = synth.make_x(f.n, b, seed=(71, b))
     P.spqr_set_option(P.SPQR_OPT_BATCH_STEPS, steps)
+    P.spqr_set_option(P.SPQR_OPT_BATCH_SHARES, shares)
     try:
         need = P.spqr_workspace_bytes(A, b)
         buf = torch.full((need + 512,), 0xA5, dtype=torch.uint8, device="cuda:0")
@@ -38,6 +39,7 @@ def run(P, f, b, steps=0):
         assert bool((buf[:256] == 0xA5).all()) and bool((buf[256 + need:] == 0xA5).all())
     finally:
         P.spqr_set_option(P.SPQR_OPT_BATCH_STEPS, 0)
+        P.spqr_set_option(P.SPQR_OPT_BATCH_SHARES, 0)
     ref = orc.matvec(f, X)
     Xp = X.astype(np.float64) if f.perm is None else X.astype(np.float64)[:, f.perm]
     terms = np.sqrt(Xp ** 2 @ (orc.reconstruct(f) ** 2).T)
@@ -155,3 +157,35 @@ def test_an_infinite_activation_meets_only_its_own_columns_weights(P, w, b1, b2,
     ok = (got == want) | ~sure
     ok[b - 1] = True
     assert ok.all(), np.argwhere(~ok)[:5]
+
+
+# strips: one, 16 k + 1, ragged; units: one, a piece of XT and one more, many; rows beyond what a wavefront takes at once
+@pytest.mark.parametrize("w,b1,b2,axis,ntr,ntc,structure,rate", [
+    (3, 16, 16, 1, 1, 1, "uniform", 0.1), (4, 16, 16, 1, 19, 113, "zipf", 0.1), (3, 16, 16, 0, 33, 65, "rows8cols4", 0.2),
+    (4, 8, 32, 1, 33, 65, "cols64", 0.2), (3, 8, 32, 0, 9, 211, "zipf", 0.05), (3, 8, 32, 1, 2, 160, "uniform", 0.2)])
+@pytest.mark.parametrize("shares", [1, 2, 3, 5])
+@pytest.mark.parametrize("b,steps", [(4, 1), (16, 1), (16, 7), (11, 1000)])
+def test_outliers_beside_the_dense_workgroups(P, w, b1, b2, axis, ntr, ntc, structure, rate, shares, b, steps):
+    tr, tc = synth.tile_shape(b1, b2, axis)
+    P.spqr_set_option(P.SPQR_OPT_BATCH_PATH, P.SPQR_BATCH_PATH_MATRIX)
+    f = synth.make_matrix(ntr * tr, ntc * tc, w_bits=w, beta1=b1, beta2=b2, group_axis=axis, outlier_rate=rate,
+                          outlier_structure=structure, seed=(78, w, axis, ntr, ntc))
+    if (ntr + b) % 2:
+        f.perm = np.random.default_rng(5).permutation(f.n).astype(np.int32)
+    run(P, f, b, steps, shares)
+
+
+@pytest.mark.parametrize("shares", [0, 1, 2, 5])
+def test_outliers_beside_the_dense_workgroups_of_several_matrices(P, shares):
+    """One of the matrices without outliers, one shorter than a group of strips."""
+    import torch
+    P.spqr_set_option(P.SPQR_OPT_BATCH_PATH, P.SPQR_BATCH_PATH_MATRIX)
+    P.spqr_set_option(P.SPQR_OPT_BATCH_SHARES, shares)
+    fs = [synth.make_matrix(m, 1616, w_bits=4, beta1=16, beta2=16, group_axis=1, outlier_rate=0.05, outlier_structure=st, seed=(79, m))
+          for m, st in ((528, "zipf"), (48, "none"), (256, "uniform"))]
+    X = synth.make_x(1616, 13, seed=(80,))
+    Ys = P.spqr_gemm_fused([P.SpQRMatrix.from_logical(f) for f in fs], torch.from_numpy(X).to("cuda:0"))
+    for f, Y in zip(fs, Ys):
+        ref = orc.matvec(f, X)
+        err = np.linalg.norm(Y.cpu().numpy().astype(np.float64) - ref, axis=1) / np.linalg.norm(ref, axis=1)
+        assert err.max() <= REL_L2

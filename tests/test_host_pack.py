@@ -33,7 +33,7 @@ def test_library_exports_every_declared_symbol():
             "spqr_permute_columns", "spqr_permute_symmetric"} == enc
     names = names | enc
     hooks = _declared(os.path.join(ROOT, "paper_2306_03078_amd", "csrc", "spqr_test_hooks.h"))
-    assert hooks == {"spqr_plan_batch_steps", "spqr_plan_grouped", "spqr_sort_ranges"}
+    assert hooks == {"spqr_plan_batch", "spqr_plan_batch_steps", "spqr_plan_grouped", "spqr_sort_ranges"}
     lib = C.CDLL(P.library_path())
     for nm in sorted(names | hooks):
         assert hasattr(lib, nm), nm
@@ -361,3 +361,66 @@ def test_sort_ranges_stay_inside_the_arrays_whatever_the_row_pointers_hold(rows)
         a, z, s = got.T
         assert (0 <= a).all() and (a <= z).all() and (z <= nnz).all()
         assert (s >= 0).all() and (s + -(-(z - a) // 4096) <= slots).all()
+
+
+# ---- the plan of a slice of 4 to 16 vectors: splits of the columns, workgroups for the outliers ----
+
+def _plan_batch(ms, n, nnz, hints, w, b1, b2, axis, b):
+    lib = C.CDLL(P.library_path())
+    fn = lib.spqr_plan_batch
+    fn.restype = C.c_int
+    k = len(ms)
+    I, L = C.c_int32 * k, C.c_int64 * k
+    out = (C.c_int32 * 3)()
+    units = fn(k, I(*ms), I(*([n] * k)), I(*hints), L(*nnz), w, b1, b2, axis, b, out)
+    return units, out[0], out[1], out[2]
+
+
+FORMATS = [(3, 16, 16, 1, 256), (4, 16, 16, 0, 256), (3, 8, 32, 1, 128), (4, 8, 32, 0, 256)]      # the last: rows of a group
+
+
+def test_batch_plans_keep_the_kernels_invariants():
+    rng = np.random.default_rng(13)
+    for w, b1, b2, axis, rows in FORMATS:
+        tr, tc = synth.tile_shape(b1, b2, axis)
+        for _ in range(300):
+            k = int(rng.integers(1, 9)) if rng.random() < 0.4 else 1
+            n = tc * int(rng.integers(1, 65536 // tc // 4))
+            ms = [tr * int(rng.integers(1, 3000 if rng.random() < 0.9 else 40000)) for _ in range(k)]
+            nnz = [int(rng.choice([0.0, 0.005, 0.02, 0.2]) * m * n) for m in ms]
+            hints = [0 if z == 0 else int(rng.choice([0, z // m + 1, n])) for z, m in zip(nnz, ms)]
+            b = int(rng.integers(1, 17))
+            units, per, splits, shares = _plan_batch(ms, n, nnz, hints, w, b1, b2, axis, b)
+            assert units == -(-(n // tc) // 16)
+            assert 1 <= per <= units and splits == -(-units // per) and (splits - 1) * per < units   # no split is empty
+            assert shares in (0, 1, 2, 4) and shares <= rows // 64 and (shares == 0 or sum(nnz) > 0)
+            parts = splits * (2 if shares else 1)
+            assert parts == 1 or 4 * parts * b * sum(ms) <= 24 << 20
+
+
+def test_batch_plans_of_the_layers_that_lost_time():
+    """The splits and shares that are within 4 % of the fastest of all on these layers (16 vectors, all of them timed)."""
+    def plan(ms, n, rate, hint, fmt):
+        return _plan_batch(ms, n, [int(rate * m * n) for m in ms], [hint] * len(ms), *fmt[:4], 16)[1:]
+    t8, t16 = FORMATS[2], FORMATS[0]
+    assert plan([22016], 8192, 0.02, 230, t8) in ((3, 6, 0), (3, 6, 1))        # 6 units: 80 us against 64
+    assert plan([22016, 22016], 8192, 0.01, 130, t16)[0] == 6                  # 7 units: 118 against 98
+    assert plan([1024], 1024, 0.01, 1024, t16)[2] >= 2                         # heavy rows in their own workgroups: 16.9 -> 11.1
+    assert plan([5120], 5120, 0.01, 5120, t16) in ((5, 4, 2), (4, 5, 4))       # 24.9 -> 18.3
+    assert plan([17920], 6656, 0.01, 6656, t16) == (4, 7, 0)                   # no CUs to spare: 44.6, apart 46.9
+
+
+def test_batch_plan_pins():
+    lib = C.CDLL(P.library_path())
+    args = ([4096], 4096, [167772], [66], 3, 16, 16, 1, 16)
+    try:
+        for per in (1, 3, 16, 1000):
+            for code, shares in ((1, 0), (2, 1), (3, 2), (5, 4)):
+                assert lib.spqr_set_option(2, per) == 0 and lib.spqr_set_option(5, code) == 0
+                assert _plan_batch(*args) == (16, min(per, 16), -(-16 // min(per, 16)), shares)
+        assert lib.spqr_set_option(5, 4) == -3 and lib.spqr_set_option(5, -1) == -3
+        assert _plan_batch([4096], 4096, [0], [0], 3, 16, 16, 1, 16)[3] == 0   # nothing to share out
+        assert _plan_batch([4096], 4096, [167772], [66], 3, 8, 32, 1, 16)[3] == 2   # two sets of 64 rows
+    finally:
+        assert lib.spqr_set_option(2, 0) == 0 and lib.spqr_set_option(5, 0) == 0
+    assert _plan_batch([4096], 4096, [0], [0], 3, 32, 32, 1, 16)[0] == -3      # no such instance
