@@ -339,8 +339,8 @@ __global__ void __launch_bounds__(64 * kWaves) sweep_kernel(SweepArgs a) {
 // ---------------------------------------------------------------------------
 // The sweep for layers of up to 4096 rows (and beta2 <= 16): a workgroup of 8 wavefronts owns 16 rows, so 4096 rows have
 // a workgroup per CU where 64 rows each would leave three of four idle.  The working copy is row-major.
-//   chain     the first wavefront alone, a lane per row (its four groups of 16 lanes do the same), the block's columns in
-//             registers: the steps of a column depend on one another, nothing is read from LDS but H^ic
+//   chain     the first wavefront alone, a lane per row (its four groups of 16 lanes do the same), 16 of the block's columns
+//             in registers: the steps of a column depend on one another, nothing is read from LDS but H^ic
 //   feedback  lanes = columns, a wavefront takes 64 columns of all 16 rows (16 sums a lane), its piece of H^ic comes
 //             straight from memory, one number per lane and step, and the errors E as LDS broadcasts
 // Same operations in the same order on every weight as sweep_kernel, hence the same bits.
@@ -410,59 +410,74 @@ __global__ void __launch_bounds__(64 * kWaves16, 2) sweep16_kernel(SweepArgs a) 
       if (wave == 0) {
         const int r = lane & 15, row = row0 + r;
         const uint32_t om = S.omask[r];
-        double w[B1];
-#pragma unroll
-        for (int c = 0; c < B1; ++c) w[c] = S.wbs[c][r];
         double s_hat, z_hat;
         uint8_t sq, zq;
         uint16_t ssb, zsb, szb, zzb;
         {
           double lo = INFINITY, hi = -INFINITY;
 #pragma unroll
-          for (int c = 0; c < B1; ++c)
-            if (!((om >> c) & 1u)) { lo = fmin(lo, w[c]); hi = fmax(hi, w[c]); }
+          for (int c = 0; c < B1; ++c) {
+            const double v = S.wbs[c][r];
+            if (!((om >> c) & 1u)) { lo = fmin(lo, v); hi = fmax(hi, v); }
+          }
           if (lo > hi) { lo = 0.0; hi = 0.0; }           // nothing left
           double s1, z1;
           fit_from_range(lo, hi, a.w_top, &s1, &z1);
           second_level(s1, a.beta2, a.s_top, &s_hat, &sq, &ssb, &zsb);
           second_level(z1, a.beta2, a.z_top, &z_hat, &zq, &szb, &zzb);
         }
-        uint32_t qs[B1 / 4], ms[B1 / 4], vs[B1 / 2];
-#pragma unroll
-        for (int k = 0; k < B1 / 4; ++k) qs[k] = ms[k] = 0;
-#pragma unroll
-        for (int k = 0; k < B1 / 2; ++k) vs[k] = 0;
-#pragma unroll
-        for (int c = 0; c < B1; ++c) {
-          const bool is_out = (om >> c) & 1u;
-          const double v = w[c];
-          const double q = quantize(v, s_hat, z_hat, a.w_top);
-          const double wq = s_hat * (q - z_hat);
-          const double ec = (v - wq) / S.ublk[c][c] * (is_out ? 0.0 : 1.0);
-          if (lane < kRows16) S.esb[i - sb + c][r] = ec;
-#pragma unroll
-          for (int k = c; k < B1; ++k) w[k] = w[k] - ec * S.ublk[c][k];    // line 14, inside the block
-          qs[c / 4] |= (uint32_t)(uint8_t)q << (8 * (c % 4));
-          ms[c / 4] |= (is_out ? 1u : 0u) << (8 * (c % 4));
-          vs[c / 2] |= (uint32_t)(is_out ? f64_to_f16_bits(w[c] - wq) : (uint16_t)0) << (16 * (c % 2));
-        }
         if (lane < rows) {
-          const size_t at = (size_t)row * n + i;
-#pragma unroll
-          for (int k = 0; k < B1 / 4; ++k) {
-            reinterpret_cast<uint32_t*>(a.out.Q + at)[k] = qs[k];
-            reinterpret_cast<uint32_t*>(a.out.outlier_mask + at)[k] = ms[k];
-          }
-#pragma unroll
-          for (int k = 0; k < B1 / 2; ++k) reinterpret_cast<uint32_t*>(a.out.outlier_val + at)[k] = vs[k];
           a.out.s_q[(size_t)row * ng + g] = sq;
           a.out.z_q[(size_t)row * ng + g] = zq;
           if ((row % a.beta2) == 0) {
             const size_t t = (size_t)(row / a.beta2) * ng + g;
             a.out.s_s[t] = ssb; a.out.z_s[t] = zsb; a.out.s_z[t] = szb; a.out.z_z[t] = zzb;
           }
+        }
+        // HB columns in registers at a time: 32 of them spill (540 registers).  The second half first takes the errors of the
+        // first, in the order of the columns, which is the order line 14 gives it.
+        constexpr int HB = B1 < 16 ? B1 : 16;
+#pragma unroll 1
+        for (int h0 = 0; h0 < B1; h0 += HB) {
+          double w[HB];
 #pragma unroll
-          for (int c = 0; c < B1; ++c) W[at + c] = w[c];
+          for (int c = 0; c < HB; ++c) w[c] = S.wbs[h0 + c][r];
+          for (int j = 0; j < h0; ++j) {
+            const double ej = S.esb[i - sb + j][r];
+#pragma unroll
+            for (int k = 0; k < HB; ++k) w[k] = w[k] - ej * S.ublk[j][h0 + k];
+          }
+          uint32_t qs[HB / 4], ms[HB / 4], vs[HB / 2];
+#pragma unroll
+          for (int k = 0; k < HB / 4; ++k) qs[k] = ms[k] = 0;
+#pragma unroll
+          for (int k = 0; k < HB / 2; ++k) vs[k] = 0;
+#pragma unroll
+          for (int c = 0; c < HB; ++c) {
+            const bool is_out = (om >> (h0 + c)) & 1u;
+            const double v = w[c];
+            const double q = quantize(v, s_hat, z_hat, a.w_top);
+            const double wq = s_hat * (q - z_hat);
+            const double ec = (v - wq) / S.ublk[h0 + c][h0 + c] * (is_out ? 0.0 : 1.0);
+            if (lane < kRows16) S.esb[i - sb + h0 + c][r] = ec;
+#pragma unroll
+            for (int k = c; k < HB; ++k) w[k] = w[k] - ec * S.ublk[h0 + c][h0 + k];    // line 14, inside the block
+            qs[c / 4] |= (uint32_t)(uint8_t)q << (8 * (c % 4));
+            ms[c / 4] |= (is_out ? 1u : 0u) << (8 * (c % 4));
+            vs[c / 2] |= (uint32_t)(is_out ? f64_to_f16_bits(w[c] - wq) : (uint16_t)0) << (16 * (c % 2));
+          }
+          if (lane < rows) {
+            const size_t at = (size_t)row * n + i + h0;
+#pragma unroll
+            for (int k = 0; k < HB / 4; ++k) {
+              reinterpret_cast<uint32_t*>(a.out.Q + at)[k] = qs[k];
+              reinterpret_cast<uint32_t*>(a.out.outlier_mask + at)[k] = ms[k];
+            }
+#pragma unroll
+            for (int k = 0; k < HB / 2; ++k) reinterpret_cast<uint32_t*>(a.out.outlier_val + at)[k] = vs[k];
+#pragma unroll
+            for (int c = 0; c < HB; ++c) W[at + c] = w[c];
+          }
         }
       }
       __syncthreads();
@@ -647,8 +662,10 @@ int spqr_quantize(const double* W, const double* Hic, int32_t m, int32_t n, int3
   a.tau = tau;
   a.out = *out;
   // 16 rows per workgroup where a tile has no more and every workgroup gets a CU (beta1 = beta2 = 16, 1 % outliers, 4096
-  // columns: 4096 rows 17.8 -> 10.9 ms, 1024 columns and rows 2.38 -> 1.33 ms), in place on W_final where the caller wants it;
-  // 64 rows per workgroup where there are more rows (11008: 18.3 ms, with 16 a workgroup 32.4) or taller tiles.
+  // columns: 4096 rows 17.7 -> 11.1 ms, 1024 columns and rows 2.38 -> 1.33 ms; beta1 = 32, no outlier test, 4000 x 512 0.76 -> 0.43),
+  // in place on W_final where the caller wants it; 64 rows per workgroup where there are more rows (5120^2 25.7 ms, with 16 a
+  // workgroup 30.9; 8192 x 1024 2.44 against 2.68, 11008 x 4096 18.3 against 32.4; with beta1 = 8 the line would lie higher: 8192 x
+  // 2048 5.8 against 4.3) or taller tiles.
   if (beta2 <= kRows16 && m <= kRows16 * 256) {
     if (out->W_final) a.Wt = out->W_final;
     if (a.Wt != W) hipLaunchKernelGGL(copy_kernel, dim3(2048), dim3(256), 0, st, W, a.Wt, (size_t)m * n);
