@@ -377,14 +377,21 @@ int spqr_gemv_grouped(const spqr_matrix_t* const* A, int count, const uint16_t* 
  *   SPQR_OPT_BATCH_SHARES  k > 0: in the matrix-core path's launch k - 1
  *                          workgroups (0, 1, 2 or 4; 2 at most with 8 x 32
  *                          tiles) share the outliers beside each dense one, 0
- *                          of them: the dense one takes them too */
+ *                          of them: the dense one takes them too
+ *   SPQR_OPT_PROMPT_PLAN   1024 * V + U > 0: prompt-sized batches take the
+ *                          one-pass kernel on layers of any size (formats and
+ *                          outlier rates it has), with 64 * V vectors (V = 1, 2
+ *                          or 4; 2 at most with 16-row strips; 0: the library's
+ *                          rule) per workgroup and U units of 16 tile columns
+ *                          per split (0: the library's rule) */
 #define SPQR_OPT_BATCH_PATH     0
 #define SPQR_OPT_FORCE_GENERIC  1
 #define SPQR_OPT_BATCH_STEPS    2
 #define SPQR_OPT_DENSE_ROWS     3
 #define SPQR_OPT_GEMV_PLAN      4
 #define SPQR_OPT_BATCH_SHARES   5
-#define SPQR_OPT_COUNT_         6
+#define SPQR_OPT_PROMPT_PLAN    6
+#define SPQR_OPT_COUNT_         7
 #define SPQR_BATCH_PATH_AUTO    0
 #define SPQR_BATCH_PATH_VECTOR  1
 #define SPQR_BATCH_PATH_MATRIX  2

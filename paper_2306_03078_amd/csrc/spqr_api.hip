@@ -104,6 +104,7 @@ extern "C" int spqr_set_option(int option, int value) {
     case SPQR_OPT_FORCE_GENERIC: ok = value == 0 || value == 1; break;
     case SPQR_OPT_BATCH_STEPS: ok = value >= 0; break;
     case SPQR_OPT_DENSE_ROWS: ok = value == 0 || value == 64 || value == 128; break;
+    case SPQR_OPT_PROMPT_PLAN: ok = value >= 0 && (value < 3 * 1024 || value / 1024 == 4); break;
     case SPQR_OPT_BATCH_SHARES: ok = value == 0 || value == 1 || value == 2 || value == 3 || value == 5; break;
     case SPQR_OPT_GEMV_PLAN: ok = value >= 0 && value < 16 * 17; break;
     default: ok = false;

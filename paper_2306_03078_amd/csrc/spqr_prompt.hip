@@ -334,8 +334,11 @@ static PromptPlan plan_prompt(const Geometry& g, int b) {
   // compiler no register to turn in (it moves half of them back and forth, 8.9 us a phase).
   const double split_us = (double)b * g.m * 8 / 4e6;
   const int64_t most = ((int64_t)16 << 20) / ((int64_t)b * g.m);
+  const int pin = option(SPQR_OPT_PROMPT_PLAN), pin_units = pin % 1024, most_nvb = p.rows == 256 ? 2 : 4;   // (tuning, tests)
+  const int pin_nvb = pin / 1024 < most_nvb ? pin / 1024 : most_nvb;
   double best = 1e30;
-  for (int nvb = 1; nvb <= (p.rows == 256 ? 2 : 4); nvb *= 2) {
+  for (int nvb = 1; nvb <= most_nvb; nvb *= 2) {
+    if (pin_nvb >= 1 && nvb != pin_nvb) continue;
     const double phase_us = p.rows == 256 ? (nvb == 1 ? 1.8 : 2.3) : (nvb == 1 ? 1.0 : nvb == 2 ? 1.2 : 1.8);
     const int vblocks = (b + 64 * nvb - 1) / (64 * nvb);
     for (int s = 1; s <= p.units && (s == 1 || s <= most); ++s) {
@@ -345,7 +348,7 @@ static PromptPlan plan_prompt(const Geometry& g, int b) {
       if (cost < best - 1e-9) { best = cost; p.nvb = nvb; p.vblocks = vblocks; p.per = per; }
     }
   }
-  if (const int v = option(SPQR_OPT_BATCH_STEPS); v >= 1) p.per = v < p.units ? v : p.units;   // pinned (tuning, tests)
+  if (pin_units >= 1) p.per = pin_units < p.units ? pin_units : p.units;
   p.splits = (p.units + p.per - 1) / p.per;
   return p;
 }
@@ -362,11 +365,11 @@ bool prompt_has_instance(const DevMatrix& A) {
 // and whose weights are dequantised once per 128 vectors (5120^2: 46.2 .. 61.0 -> 38.3 .. 57.2; 5120 x 3584: 35.4 .. 47.4
 // against 36.9 .. 55.3); below, the sort of the outliers (10 us) and the few workgroups cost more than the copy's passes.
 // From 33 vectors on it would beat the slices, but they add the outliers in binary32 and here weight + outlier is rounded to
-// binary16, so no batch that took the slices moves here.  With the split pinned (SPQR_OPT_BATCH_STEPS) the size is no matter.
+// binary16, so no batch that took the slices moves here.  With a pinned plan (SPQR_OPT_PROMPT_PLAN) the size is no matter.
 bool prompt_wanted(const DevMatrix& A, int b) {
   const double from = A.g.tile_rows == 8 ? 4e6 : 24e6;
   return option(SPQR_OPT_BATCH_PATH) == SPQR_BATCH_PATH_AUTO && prompt_has_instance(A) && prefill_wanted(A, b) &&
-         ((double)A.g.m * A.g.n >= from || option(SPQR_OPT_BATCH_STEPS) >= 1);
+         ((double)A.g.m * A.g.n >= from || option(SPQR_OPT_PROMPT_PLAN) >= 1);
 }
 
 static size_t prompt_offsets(const DevMatrix& A, int b, const PromptPlan& p, size_t (&at)[5]) {

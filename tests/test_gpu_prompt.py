@@ -24,12 +24,13 @@ def P():
     return P
 
 
-def run(P, f, b, steps=0, shares=0):
+def run(P, f, b, steps=0, shares=0, prompt=0):
     import torch
     A = P.SpQRMatrix.from_logical(f)
     X = synth.make_x(f.n, b, seed=(71, b))
     P.spqr_set_option(P.SPQR_OPT_BATCH_STEPS, steps)
     P.spqr_set_option(P.SPQR_OPT_BATCH_SHARES, shares)
+    P.spqr_set_option(P.SPQR_OPT_PROMPT_PLAN, prompt)
     try:
         need = P.spqr_workspace_bytes(A, b)
         buf = torch.full((need + 512,), 0xA5, dtype=torch.uint8, device="cuda:0")
@@ -40,6 +41,7 @@ def run(P, f, b, steps=0, shares=0):
     finally:
         P.spqr_set_option(P.SPQR_OPT_BATCH_STEPS, 0)
         P.spqr_set_option(P.SPQR_OPT_BATCH_SHARES, 0)
+        P.spqr_set_option(P.SPQR_OPT_PROMPT_PLAN, 0)
     ref = orc.matvec(f, X)
     Xp = X.astype(np.float64) if f.perm is None else X.astype(np.float64)[:, f.perm]
     terms = np.sqrt(Xp ** 2 @ (orc.reconstruct(f) ** 2).T)
@@ -52,7 +54,7 @@ def run(P, f, b, steps=0, shares=0):
 @pytest.mark.parametrize("w,b1,b2,axis,ntr,ntc,structure,rate", [
     (3, 16, 16, 1, 1, 1, "uniform", 0.1), (4, 16, 16, 1, 17, 17, "zipf", 0.1), (3, 16, 16, 0, 16, 67, "rows8cols4", 0.2),
     (4, 8, 32, 1, 33, 65, "cols64", 0.2), (3, 8, 32, 0, 9, 131, "uniform", 0.24), (3, 8, 32, 1, 2, 160, "uniform", 0.2)])
-# prompts with the split pinned: at this size the library's own choice is the dense copy, which has tests of its own
+# prompts with the plan pinned: at this size the library's own choice is the dense copy, which has tests of its own
 @pytest.mark.parametrize("b,steps", [(4, 0), (4, 1), (4, 1000), (16, 0), (16, 1), (16, 1000)] +
                          [(b, s) for b in (49, 65, 129, 256) for s in (1, 3, 1000)])
 def test_edges(P, w, b1, b2, axis, ntr, ntc, structure, rate, b, steps):
@@ -63,9 +65,32 @@ def test_edges(P, w, b1, b2, axis, ntr, ntc, structure, rate, b, steps):
                               outlier_structure=structure, seed=(72, w, axis, ntr, ntc))
         if (ntr + b) % 2:
             f.perm = np.random.default_rng(5).permutation(f.n).astype(np.int32)
-        run(P, f, b, steps)
+        run(P, f, b, steps if b <= 16 else 0, prompt=steps if b > 16 else 0)
     finally:
         P.spqr_set_option(P.SPQR_OPT_BATCH_PATH, P.SPQR_BATCH_PATH_AUTO)
+
+
+# ragged groups of strips, last units and blocks of vectors at every number of vectors a workgroup takes
+@pytest.mark.parametrize("w,b1,b2,axis,ntr,ntc,structure,rate", [
+    (3, 16, 16, 1, 17, 67, "rows8cols4", 0.2), (4, 16, 16, 0, 3, 18, "none", 0.0), (4, 8, 32, 1, 33, 35, "cols64", 0.24),
+    (3, 8, 32, 1, 18, 17, "none", 0.0), (3, 8, 32, 0, 9, 67, "zipf", 0.1)])
+@pytest.mark.parametrize("vectors", [1, 2, 4])
+@pytest.mark.parametrize("b,units", [(48, 0), (65, 1), (77, 3), (129, 1000), (255, 2)])
+def test_every_width_of_the_one_pass_kernel(P, w, b1, b2, axis, ntr, ntc, structure, rate, vectors, b, units):
+    tr, tc = synth.tile_shape(b1, b2, axis)
+    f = synth.make_matrix(ntr * tr, ntc * tc, w_bits=w, beta1=b1, beta2=b2, group_axis=axis, outlier_rate=rate,
+                          outlier_structure=structure, seed=(81, w, axis, ntr, ntc))
+    if (ntr + b) % 2:
+        f.perm = np.random.default_rng(5).permutation(f.n).astype(np.int32)
+    run(P, f, b, prompt=1024 * vectors + units)
+
+
+def test_a_large_layer_takes_four_blocks_of_64_vectors_by_itself(P):
+    """8-row strips and 200 vectors, nothing pinned: 172 groups of strips are one workgroup per CU with 256 vectors each (19
+    us by the plan's model), two rounds of them with 128 (29) and three with 64 (39)."""
+    f = synth.make_matrix(8 * 2751, 32 * 19, w_bits=3, beta1=8, beta2=32, group_axis=1, outlier_rate=0.02,
+                          outlier_structure="cols64", seed=(82,))
+    run(P, f, 200)
 
 
 def test_permutation_wider_than_the_room_of_the_products(P):
@@ -124,7 +149,7 @@ def test_weights_are_rounded_from_an_exact_code(P, w, b1, b2, axis, b):
     X = np.zeros((b, f.n), np.float16)
     X[np.arange(b), cols] = 1
     P.spqr_set_option(P.SPQR_OPT_BATCH_PATH, P.SPQR_BATCH_PATH_MATRIX if b <= 16 else P.SPQR_BATCH_PATH_AUTO)
-    P.spqr_set_option(P.SPQR_OPT_BATCH_STEPS, 1000)
+    P.spqr_set_option(P.SPQR_OPT_PROMPT_PLAN, 1000)
     got = P.spqr_gemm_smallbatch(P.SpQRMatrix.from_logical(f), torch.from_numpy(X.view(np.float16)).to("cuda:0")).cpu().numpy()
     want = orc.decode_dense(f)[:, cols].T.astype(np.float16)
     assert np.array_equal(got, got.astype(np.float16).astype(np.float32))
@@ -147,7 +172,7 @@ def test_an_infinite_activation_meets_only_its_own_columns_weights(P, w, b1, b2,
     X[np.arange(b), at] = np.where(np.arange(b) % 2 == 0, np.float16(np.inf), np.float16(-np.inf))
     X[b - 1, at[b - 1]] = np.nan
     P.spqr_set_option(P.SPQR_OPT_BATCH_PATH, P.SPQR_BATCH_PATH_MATRIX if b <= 16 else P.SPQR_BATCH_PATH_AUTO)
-    P.spqr_set_option(P.SPQR_OPT_BATCH_STEPS, 1000 if b > 16 else 0)
+    P.spqr_set_option(P.SPQR_OPT_PROMPT_PLAN, 1000)
     got = P.spqr_gemm_smallbatch(P.SpQRMatrix.from_logical(f), torch.from_numpy(X).to("cuda:0")).cpu().numpy()
     weight = orc.reconstruct(f)[:, at].T                      # the weight each infinity meets, [b, m]
     sure = (np.abs(weight) > 1e-6) & (weight == orc.decode_dense(f)[:, at].T)   # not a zero in binary16, no outlier

@@ -211,6 +211,8 @@ def test_batch_launch_plan_arguments_and_the_pinned_choice():
     finally:
         assert lib.spqr_set_option(2, 0) == 0
     assert lib.spqr_set_option(2, -1) == -3 and lib.spqr_set_option(9, 0) == -3 and lib.spqr_set_option(0, 4) == -3
+    assert all(lib.spqr_set_option(6, v) == -3 for v in (-1, 3 * 1024, 5 * 1024)) and lib.spqr_set_option(6, 4 * 1024 + 7) == 0
+    assert lib.spqr_set_option(6, 0) == 0                                                                            # SPQR_OPT_PROMPT_PLAN
     assert lib.spqr_set_option(3, 96) == -3 and lib.spqr_set_option(3, 64) == 0 and lib.spqr_set_option(3, 0) == 0   # SPQR_OPT_DENSE_ROWS
 
 
