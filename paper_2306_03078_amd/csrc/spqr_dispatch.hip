@@ -100,7 +100,7 @@ hipError_t launch_gemm_fused(const DevMatrix* As, int count, const uint16_t* X, 
   if (capturing) mfma_ok = false;
   // a large batch: one matrix at a time (launch_gemm falls back to the slices where it has to)
   bool dense = !force_generic && prefill_has_instance(g);
-  for (int i = 0; i < count && dense; ++i) dense = prompt_wanted(As[i], b) || prefill_wanted(As[i], b);
+  for (int i = 0; i < count && dense; ++i) dense = prefill_wanted(As[i], b);   // (prompt_wanted is a part of that)
   if (dense) mfma_ok = false;
   int k = 0;
   while (k < b) {
@@ -131,17 +131,12 @@ hipError_t launch_gemm_fused(const DevMatrix* As, int count, const uint16_t* X, 
 size_t workspace_bound(const DevMatrix* As, int count, int b, bool with_dense_copy) {
   if (option(SPQR_OPT_FORCE_GENERIC) != 0) return 0;
   size_t worst = 0;
-  // a large batch: one matrix at a time (a smaller workspace sends the call to the slices of 16)
-  if (with_dense_copy)
-    for (int i = 0; i < count; ++i)
-      if (prompt_wanted(As[i], b)) {
-        const size_t need = prompt_workspace_bytes(As[i], b);
-        if (need > worst) worst = need;
-      }
+  // a large batch: one matrix at a time, in one pass or through the dense copy (a smaller workspace sends the call to the
+  // slices of 16; one that holds the dense copy and not what the one pass needs, to the copy)
   if (with_dense_copy && prefill_has_instance(As[0].g))
     for (int i = 0; i < count; ++i) {
       if (!prefill_wanted(As[i], b)) continue;
-      const size_t need = prefill_workspace_bytes(As[i], b);
+      const size_t need = prompt_wanted(As[i], b) ? prompt_workspace_bytes(As[i], b) : prefill_workspace_bytes(As[i], b);
       if (need > worst) worst = need;
     }
   if (!mfma_has_instance(As[0].g) || b < kMfmaMinBatch) return worst;

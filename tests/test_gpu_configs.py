@@ -146,16 +146,21 @@ def test_fused_projections_at_full_size(P):
 
 
 def test_large_batches_at_full_size(P):
-    """256 and 64 vectors on the LLaMA-33B- and 65B-shaped layers (the dense-copy path, with and without split k):
-    every output element against the oracle."""
+    """256 and 64 vectors on the LLaMA-33B- and 65B-shaped layers (the one-pass kernel, with and without split columns; its
+    workspace holds no dense copy of the matrix): every output element against the oracle."""
+    import torch
     for cfg, name, b in ((3, "gate", 256), (3, "down", 256), (4, "q", 64), (4, "down", 128)):
         i = [k for k, sp in enumerate(synth.config_layers(cfg)) if sp.name == name][0]
         f = synth.make_config_layer(cfg, i, group_axis=1)
         A = P.SpQRMatrix.from_logical(f)
-        assert P.spqr_workspace_bytes([A], b) >= 2 * f.m * f.n        # the path with the dense copy is the one taken
+        need = P.spqr_workspace_bytes([A], b)
+        assert 0 < need < 2 * f.m * f.n                               # no room for a dense copy: not the path taken
         X = synth.make_x(f.n, b, seed=(80, b))
-        Y = P.spqr_gemm_smallbatch(A, dev(X)).cpu().numpy()
-        check_outputs(Y, orc.matvec(f, X), ("dense copy", cfg, name, b))
+        Xd = dev(X)
+        Y = P.spqr_gemm_smallbatch_ws(A, Xd, torch.empty(need, dtype=torch.uint8, device="cuda:0"))
+        assert torch.equal(Y, P.spqr_gemm_smallbatch(A, Xd))
+        Y = Y.cpu().numpy()
+        check_outputs(Y, orc.matvec(f, X), ("one pass", cfg, name, b))
         del f, A
 
 

@@ -426,3 +426,25 @@ def test_batch_plan_pins():
     finally:
         assert lib.spqr_set_option(2, 0) == 0 and lib.spqr_set_option(5, 0) == 0
     assert _plan_batch([4096], 4096, [0], [0], 3, 32, 32, 1, 16)[0] == -3      # no such instance
+
+
+# ---- scratch of large batches (host arithmetic on descriptors whose pointers are never followed) ----
+
+def _workspace_bytes(m, n, w, b1, b2, axis, rate, b):
+    from paper_2306_03078_amd import binding as B
+    lib = B.load_library()
+    d = B.spqr_matrix_t(m=m, n=n, w_bits=w, s_bits=3, z_bits=3, beta1=b1, beta2=b2, group_axis=axis, layout_version=1,
+                        packed=4096, packed_bytes=P.packed_bytes(m, n, w, 3, 3, b1, b2, axis), row_ptr=4096, col_idx=4096,
+                        out_val=4096, nnz=int(rate * m * n))
+    return lib.spqr_workspace_bytes((C.POINTER(B.spqr_matrix_t) * 1)(C.pointer(d)), 1, b)
+
+
+def test_workspace_of_the_one_pass_kernel_holds_no_dense_copy():
+    for m, n, w, b1, b2, rate, b in ((17920, 6656, 4, 16, 16, 0.01, 256), (8192, 22016, 3, 8, 32, 0.02, 128), (8192, 8192, 3, 8, 32, 0.02, 64)):
+        need = _workspace_bytes(m, n, w, b1, b2, 1, rate, b)
+        # 4 bytes per outlier, partial results of 64 MB at most where there are several, the sort's ranges and counts
+        assert 4 * int(rate * m * n) < need < 4 * int(rate * m * n) + max(64 << 20, 4 * b * m) + (8 << 20)
+        assert need < 2 * m * n                                            # the copy alone
+    # more outliers than one weight in four, or a layer too small: the copy
+    assert _workspace_bytes(8192, 4096, 4, 16, 16, 1, 0.3, 128) > 2 * 8192 * 4096
+    assert _workspace_bytes(1024, 1024, 4, 16, 16, 1, 0.01, 64) > 2 * 1024 * 1024
