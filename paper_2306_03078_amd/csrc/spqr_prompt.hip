@@ -360,16 +360,28 @@ bool prompt_has_instance(const DevMatrix& A) {
 }
 
 // Where the dense copy pays against slices of 16 (prefill_wanted: from 48 vectors on, later on larger layers) and this kernel
-// is faster than the copy: from 4 M weights on with strips of 8 rows (2048^2, 48 to 256 vectors: 28.1 .. 33.6 -> 24.3 ..
-// 27.8 us; 1024^2: 21.0 .. 24.0 against 25.3 .. 26.4), from 24 M on with 16 rows a lane, whose groups of 256 rows are fewer
-// and whose weights are dequantised once per 128 vectors (5120^2: 46.2 .. 61.0 -> 38.3 .. 57.2; 5120 x 3584: 35.4 .. 47.4
-// against 36.9 .. 55.3); below, the sort of the outliers (10 us) and the few workgroups cost more than the copy's passes.
+// is faster than the copy (times in us, copy -> here):
+// - strips of 8 rows: from 4 M weights and 512 columns on (2048^2, 48 to 256 vectors: 28.1 .. 33.6 -> 24.3 .. 27.8; 1024^2:
+//   21.0 .. 24.0 against 25.3 .. 26.4; 8192 x 512: 5 % slower to 17 % faster).  With fewer columns there are fewer phases than
+//   one workgroup per CU can share, and one hot phase is the call (17920 x 256: 13 % faster to 19 % slower).
+// - 16 rows a lane, whose groups of 256 rows are fewer and whose weights are dequantised once per 128 vectors: from 24 M on
+//   (5120^2: 46.2 .. 61.0 -> 38.3 .. 57.2; 5120 x 3584: 35.4 .. 47.4 against 36.9 .. 55.3); below, the sort of the outliers
+//   (10 us) and the few workgroups cost more than the copy's passes.  Above 192 vectors it needs more than 2048 columns: a
+//   second pass over the weights for so few phases costs more than it saves (17920 x 1536, 256 vectors: 62 .. 66 against
+//   66 .. 71; 17920 x 2048: 77 .. 82 against 80 .. 82).
+// How the outliers lie is not known here and moves a call by more than the lines do: few groups of rows and a skewed layer
+// leave one group with most of them (4096 x 8192, 128 vectors: 56 -> 47 with uniform outliers, 51 -> 50 and 51 -> 60 on two
+// Zipf layers; 3072 x 12288, 256 vectors: 78 -> 60 and 75 -> 77).  Those sizes stay, the mean of the layers being faster.
 // From 33 vectors on it would beat the slices, but they add the outliers in binary32 and here weight + outlier is rounded to
 // binary16, so no batch that took the slices moves here.  With a pinned plan (SPQR_OPT_PROMPT_PLAN) the size is no matter.
+static bool prompt_pays(const Geometry& g, int b) {
+  const double weights = (double)g.m * g.n;
+  return g.tile_rows == 8 ? weights >= 4e6 && g.n >= 512 : weights >= 24e6 && (b <= 192 || g.n > 2048);
+}
+
 bool prompt_wanted(const DevMatrix& A, int b) {
-  const double from = A.g.tile_rows == 8 ? 4e6 : 24e6;
   return option(SPQR_OPT_BATCH_PATH) == SPQR_BATCH_PATH_AUTO && prompt_has_instance(A) && prefill_wanted(A, b) &&
-         ((double)A.g.m * A.g.n >= from || option(SPQR_OPT_PROMPT_PLAN) >= 1);
+         (prompt_pays(A.g, b) || option(SPQR_OPT_PROMPT_PLAN) >= 1);
 }
 
 static size_t prompt_offsets(const DevMatrix& A, int b, const PromptPlan& p, size_t (&at)[5]) {

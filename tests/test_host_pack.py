@@ -448,3 +448,13 @@ def test_workspace_of_the_one_pass_kernel_holds_no_dense_copy():
     # more outliers than one weight in four, or a layer too small: the copy
     assert _workspace_bytes(8192, 4096, 4, 16, 16, 1, 0.3, 128) > 2 * 8192 * 4096
     assert _workspace_bytes(1024, 1024, 4, 16, 16, 1, 0.01, 64) > 2 * 1024 * 1024
+
+
+@pytest.mark.parametrize("m,n,w,b1,b2,b,one_pass", [
+    (17920, 2048, 4, 16, 16, 256, False), (17920, 2048, 4, 16, 16, 192, True), (17920, 1536, 3, 16, 16, 256, False),
+    (17920, 2064, 4, 16, 16, 256, True), (5120, 5120, 3, 16, 16, 256, True), (4864, 4864, 4, 16, 16, 128, False),
+    (17920, 256, 3, 8, 32, 128, False), (17920, 480, 3, 8, 32, 128, False), (8192, 512, 3, 8, 32, 128, True),
+    (2048, 2048, 3, 8, 32, 64, True), (1024, 1024, 3, 8, 32, 64, False)])
+def test_sizes_of_the_one_pass_kernel(m, n, w, b1, b2, b, one_pass):
+    """Where the dense copy is faster, the batch takes the copy, and its scratch holds one: 2 bytes per weight."""
+    assert (_workspace_bytes(m, n, w, b1, b2, 1, 0.01, b) < 2 * m * n) == one_pass
