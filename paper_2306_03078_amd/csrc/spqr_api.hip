@@ -249,11 +249,6 @@ extern "C" int spqr_dequant_dense(const spqr_matrix_t* A, int what, void* out, v
   return e == hipSuccess ? SPQR_OK : SPQR_ERR_HIP;
 }
 
-extern "C" int spqr_plan_batch_steps(int groups, int nsteps, int slots_one_step, int slots, int long_workgroups) {
-  if (groups < 1 || nsteps < 1 || slots_one_step < 1 || slots < 1 || long_workgroups < 0) return SPQR_ERR_PARAM;
-  return spqr::plan_batch_steps(groups, nsteps, slots_one_step, slots, long_workgroups);
-}
-
 extern "C" int spqr_plan_batch(int count, const int32_t* m, const int32_t* n, const int32_t* max_row_nnz, const int64_t* nnz,
                                int w_bits, int beta1, int beta2, int group_axis, int b, int32_t* plan) {
   if (!m || !n || !max_row_nnz || !nnz || !plan) return SPQR_ERR_NULL;

@@ -80,8 +80,6 @@ hipError_t static_workspace(Workspace* ws);
 // The launch plan of a slice of b vectors (host arithmetic only): units of 16 tile columns per split, splits, workgroups
 // that share a split's outliers.  Returns the units of the matrix.
 int plan_batch_hook(const DevMatrix* As, int count, int b, int* per, int* splits, int* shares);
-// Steps of 64 tiles per workgroup of the batch path's dense launch (host arithmetic only, see the definition).
-int plan_batch_steps(int groups, int nsteps, int slots_one_step, int slots, int long_workgroups);
 
 // The sums over the splits of partial results in the order the batch and prompt kernels write them.
 hipError_t launch_sum_groups(const Geometry& g, const float* P, int splits, int b, void* Y, int y_dtype, hipStream_t stream);

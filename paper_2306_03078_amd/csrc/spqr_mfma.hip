@@ -4,8 +4,6 @@
 #include <cstdint>
 #include <cstdlib>
 #include <mutex>
-#include <queue>
-#include <vector>
 
 #include "../../include/spqr.h"
 #include "spqr_batch.h"
@@ -505,36 +503,6 @@ hipError_t launch_sum_groups(const Geometry& g, const float* P, int splits, int 
   return hipGetLastError();
 }
 
-// Steps per workgroup of a split launch with workgroups of unequal cost beside it, chosen by simulating the launch
-// (plan_batch_steps, a test hook; launches of equal workgroups: batch_units_per_split): the workgroups start in grid order
-// (split by split: the strip groups, behind those of the first split the long-row workgroups) on the first free of
-// the chip's workgroup slots; a dense workgroup costs its steps plus a start-up of 0.3 step, a long-row workgroup
-// 0.45 step, and every split 0.3 step for its partial result (written, and read again by the finishing kernel).
-// The shortest schedule wins, ties go to fewer splits.  The constants are fitted to sweeps over the steps on
-// MI355X (eight projection shapes of the 7B to 65B configurations at batch 8 and 16, every count of steps: the choice is
-// within 2.2 % of the best measured one).  slots1 = slots when a workgroup takes one step (the variant with fewer registers),
-// slots = otherwise.  Results are remembered per argument tuple (the simulation costs up to a few milliseconds).
-static double mfma_schedule_length(int groups, int nsteps, int s, int slots, int nlong) {
-  const int nsplit = (nsteps + s - 1) / s;
-  std::priority_queue<double, std::vector<double>, std::greater<double>> free_at;
-  for (int i = 0; i < slots; ++i) free_at.push(0.0);
-  double end = 0.0;
-  auto run = [&](int count, double cost) {
-    for (int i = 0; i < count; ++i) {
-      const double t = free_at.top() + cost;
-      free_at.pop();
-      free_at.push(t);
-      if (t > end) end = t;
-    }
-  };
-  for (int y = 0; y < nsplit; ++y) {
-    const int steps = s < nsteps - y * s ? s : nsteps - y * s;
-    run(groups, 0.3 + steps);
-    run(nlong, y == 0 ? 0.45 : 0.02);         // behind the first split they leave at once
-  }
-  return end + 0.3 * nsplit;
-}
-
 // Scratch of the batch path.  A call on a stream that is not being captured takes the buffer the library keeps for
 // that stream: work on one stream runs in order, so its calls can share one buffer, and nothing is allocated or
 // freed per call (on this runtime a stream-ordered allocation waits on the host until the stream's earlier work is
@@ -648,35 +616,6 @@ static hipError_t scratch_put(Scratch* sc, hipStream_t stream) {
   if (sc->hold.owns_lock()) sc->hold.unlock();
   sc->p = nullptr;
   return e;
-}
-
-static int mfma_steps_per_split(int groups, int nsteps, int slots1, int slots, int nlong) {
-  if (const int v = option(SPQR_OPT_BATCH_STEPS); v >= 1) return v < nsteps ? v : nsteps;   // pinned (tuning, tests)
-  struct Known { int groups, nsteps, slots1, slots, nlong, best; };
-  static std::mutex lock;
-  static std::vector<Known> known;
-  {
-    std::lock_guard<std::mutex> hold(lock);
-    for (const Known& k : known)
-      if (k.groups == groups && k.nsteps == nsteps && k.slots1 == slots1 && k.slots == slots && k.nlong == nlong) return k.best;
-  }
-  int best = nsteps;
-  double best_cost = 1e30;
-  // candidates: every count of steps up to 32, and all of them in one workgroup; launches of more than
-  // 200 000 workgroups are not simulated (only very large matrices: any choice fills the chip)
-  for (int s = nsteps; s >= 1; s = (s > 32 ? 32 : s - 1)) {
-    const long wgs = (long)(groups + nlong) * ((nsteps + s - 1) / s);
-    if (wgs > 200000) continue;
-    const double cost = mfma_schedule_length(groups, nsteps, s, s == 1 ? slots1 : slots, nlong);
-    if (cost < best_cost - 1e-9) { best_cost = cost; best = s; }
-  }
-  std::lock_guard<std::mutex> hold(lock);
-  if (known.size() < 4096) known.push_back(Known{groups, nsteps, slots1, slots, nlong, best});
-  return best;
-}
-
-int plan_batch_steps(int groups, int nsteps, int slots_one_step, int slots, int long_workgroups) {
-  return mfma_steps_per_split(groups, nsteps, slots_one_step, slots, long_workgroups);
 }
 
 // Groups of 16 strips of a matrix, and the units of its columns the splits are made of.

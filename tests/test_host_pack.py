@@ -26,14 +26,14 @@ def test_library_exports_every_declared_symbol():
             "spqr_gemm_smallbatch_ws", "spqr_gemm_fused_ws", "spqr_workspace_bytes", "spqr_dequant_dense", "spqr_set_option",
             "spqr_pack_host", "spqr_packed_bytes", "spqr_pack_host_layout", "spqr_packed_bytes_layout", "spqr_strerror",
             "spqr_version"} <= names
-    assert "spqr_plan_batch_steps" not in names      # a test hook, not part of the public interface
+    assert "spqr_plan_batch" not in names      # a test hook, not part of the public interface
     enc = _declared(os.path.join(ROOT, "include", "spqr_encode.h"))
     assert {"spqr_hessian", "spqr_inverse_cholesky", "spqr_inverse_cholesky_workspace_bytes", "spqr_quantize",
             "spqr_quantize_workspace_bytes", "spqr_gather_outliers", "spqr_act_order", "spqr_act_order_workspace_bytes",
             "spqr_permute_columns", "spqr_permute_symmetric"} == enc
     names = names | enc
     hooks = _declared(os.path.join(ROOT, "paper_2306_03078_amd", "csrc", "spqr_test_hooks.h"))
-    assert hooks == {"spqr_plan_batch", "spqr_plan_batch_steps", "spqr_plan_grouped", "spqr_sort_ranges"}
+    assert hooks == {"spqr_plan_batch", "spqr_plan_grouped", "spqr_sort_ranges"}
     lib = C.CDLL(P.library_path())
     for nm in sorted(names | hooks):
         assert hasattr(lib, nm), nm
@@ -155,61 +155,8 @@ def test_host_side_descriptor_checks_need_no_gpu():
     assert lib.spqr_dequant_dense(C.byref(d), 0, None, None) == -3
 
 
-def _schedule_length(groups, nsteps, s, slots, nlong):
-    """The launch plan's schedule, written out: workgroups in grid order, each on the place that is free first."""
-    import heapq
-    nsplit = -(-nsteps // s)
-    free = [0.0] * slots
-    end = 0.0
-    for y in range(nsplit):
-        steps = min(s, nsteps - y * s)
-        for count, cost in ((groups, 0.3 + steps), (nlong, 0.45 if y == 0 else 0.02)):
-            for _ in range(count):
-                t = heapq.heappop(free) + cost
-                heapq.heappush(free, t)
-                end = max(end, t)
-    return end + 0.3 * nsplit
-
-
-@pytest.mark.parametrize("groups,nsteps,slots1,slots,nlong", [
-    (64, 4, 512, 512, 128), (172, 4, 768, 512, 128), (64, 11, 512, 512, 128), (104, 7, 512, 512, 128),
-    (280, 7, 512, 512, 128), (104, 18, 512, 512, 128), (344, 4, 256, 256, 128), (128, 11, 256, 256, 128),
-    (1, 1, 512, 512, 0), (3, 40, 512, 512, 1), (2000, 2, 512, 512, 0), (312, 7, 768, 512, 384)])
-def test_batch_launch_plan_is_the_shortest_simulated_schedule(groups, nsteps, slots1, slots, nlong):
+def test_option_values():
     lib = C.CDLL(P.library_path())
-    assert lib.spqr_set_option(2, 0) == 0                                # SPQR_OPT_BATCH_STEPS: not pinned
-    fn = lib.spqr_plan_batch_steps
-    fn.restype = C.c_int
-    fn.argtypes = [C.c_int] * 5
-    got = fn(groups, nsteps, slots1, slots, nlong)
-    assert 1 <= got <= nsteps
-    cands = [s for s in range(1, nsteps + 1) if s <= 32 or s == nsteps]
-    cost = {s: _schedule_length(groups, nsteps, s, slots1 if s == 1 else slots, nlong) for s in cands}
-    best = min(cost.values())
-    assert cost[got] <= best + 1e-6
-    assert got == max(s for s in cands if cost[s] <= best + 1e-9)       # ties: fewer splits
-    assert fn(groups, nsteps, slots1, slots, nlong) == got               # remembered, same answer
-
-
-def test_batch_launch_plan_arguments_and_the_pinned_choice():
-    lib = C.CDLL(P.library_path())
-    fn = lib.spqr_plan_batch_steps
-    fn.restype = C.c_int
-    fn.argtypes = [C.c_int] * 5
-    for bad in ((0, 4, 512, 512, 0), (4, 0, 512, 512, 0), (4, 4, 0, 512, 0), (4, 4, 512, 0, 0), (4, 4, 512, 512, -1)):
-        assert fn(*bad) == -3                                            # SPQR_ERR_PARAM
-    assert fn(100, 1, 512, 512, 0) == 1
-    # one group: splitting buys parallelism, 9 steps never stay in one workgroup
-    assert fn(1, 9, 512, 512, 0) < 9
-    # far more groups than places and nothing to balance: whole strips per workgroup cost the fewest partial results
-    assert fn(512 * 40, 3, 512, 512, 0) == 3
-    try:
-        assert lib.spqr_set_option(2, 2) == 0                            # SPQR_OPT_BATCH_STEPS
-        assert fn(280, 7, 512, 512, 128) == 2
-        assert lib.spqr_set_option(2, 50) == 0
-        assert fn(280, 7, 512, 512, 128) == 7
-    finally:
-        assert lib.spqr_set_option(2, 0) == 0
     assert lib.spqr_set_option(2, -1) == -3 and lib.spqr_set_option(9, 0) == -3 and lib.spqr_set_option(0, 4) == -3
     assert all(lib.spqr_set_option(6, v) == -3 for v in (-1, 3 * 1024, 5 * 1024)) and lib.spqr_set_option(6, 4 * 1024 + 7) == 0
     assert lib.spqr_set_option(6, 0) == 0                                                                            # SPQR_OPT_PROMPT_PLAN
