@@ -505,8 +505,7 @@ def test_matrix_core_batch_path_8x32_tiles(P, monkeypatch, w, axis, ntr, ntc, b)
 @pytest.mark.parametrize("structure,rate", [("zipf", 0.05), ("cols64", 0.08), ("rows8cols4", 0.3), ("uniform", 0.95),
                                             ("uniform", 0.2), ("zipf", 0.3)])
 def test_matrix_core_batch_path_outlier_mixes(P, monkeypatch, structure, rate):
-    """The finishing kernel of the batch path: rows dealt to all lanes, rows cut into parts that
-    cross a chunk of staged entries (rate 0.2: 16 rows of about 416), nearly dense CSR."""
+    """Outliers of the batch path: short rows, rows of about 416 entries (rate 0.2), nearly dense CSR."""
     P.spqr_set_option(P.SPQR_OPT_BATCH_PATH, P.SPQR_BATCH_PATH_MATRIX)
     f = make(4, 16, 16, 1, 5, 130, rate=rate, structure=structure, seed=(81, int(rate * 100)))
     A = P.SpQRMatrix.from_logical(f)
@@ -518,8 +517,8 @@ def test_matrix_core_batch_path_outlier_mixes(P, monkeypatch, structure, rate):
 
 @pytest.mark.parametrize("ntc,rate", [(138, 0.95), (300, 0.45), (600, 0.45), (40, 0.9)])
 def test_matrix_core_long_rows_back_to_back(P, monkeypatch, ntc, rate):
-    """Every row about as long as the next (2098, 2160, 4320, 576 entries): none of them is far above the average,
-    so all stay in the finishing kernel, in 16 parts of up to 270 entries that cross the chunks of staged entries."""
+    """Every row about as long as the next (2098, 2160, 4320, 576 entries): every row is one that a whole wavefront takes in
+    every piece of columns."""
     P.spqr_set_option(P.SPQR_OPT_BATCH_PATH, P.SPQR_BATCH_PATH_MATRIX)
     f = make(3, 16, 16, 0, 3, ntc, rate=rate, structure="uniform", seed=(83, ntc))
     assert np.diff(f.row_ptr).min() > 512
@@ -532,10 +531,9 @@ def test_matrix_core_long_rows_back_to_back(P, monkeypatch, ntc, rate):
 
 
 def test_matrix_core_long_rows_many_rows_per_workgroup(P, monkeypatch):
-    """A tall matrix whose rows 31, 32, 63, 64 and 79 of every 80 hold 700 outliers, the others none: a workgroup
-    that takes long rows looks at 255 rows at a time and keeps which of them are long in one 64-bit mask per
-    wavefront (row 31 of a wavefront's 64 is bit 31 of the mask's low word, rows 63 / 64 the seam between two
-    wavefronts' masks)."""
+    """A tall matrix whose rows 31, 32, 63, 64 and 79 of every 80 hold 700 outliers, the others none: a workgroup keeps
+    which of its rows are long in one 64-bit mask per 64 rows (row 31 is bit 31 of the mask's low word, rows 63 / 64 the
+    seam between two masks)."""
     P.spqr_set_option(P.SPQR_OPT_BATCH_PATH, P.SPQR_BATCH_PATH_MATRIX)
     f = make(3, 16, 16, 1, 640, 48, rate=0.0, structure="none", seed=(85,))
     assert f.m == 10240 and f.n == 768
@@ -564,10 +562,9 @@ def _with_row_counts(f, counts, seed):
 
 @pytest.mark.parametrize("w,b1,b2,axis,ntr,ntc", [(3, 16, 16, 1, 40, 140), (4, 8, 32, 1, 80, 70)])
 def test_matrix_core_long_rows_shared_out_by_entries(P, monkeypatch, w, b1, b2, axis, ntr, ntc):
-    """The long-row workgroups own equal shares of the entry indices, whatever the rows: a block of heavy rows next
-    to each other (full rows, rows of 513, 1024 and 1025 entries: one entry into a new slice, exact slices), rows
-    just at and just above what counts as long (256 / 257 entries), empty rows between them, and shares whose
-    bounds fall inside a row, on a slice bound and on a row bound."""
+    """Rows of very different lengths next to each other: a block of full rows and rows of 513, 1024 and 1025 entries, two
+    of 256 and 257, rows of 3, empty rows between them, a long last row.  (Rows around what counts as long inside a piece
+    of columns: test_rows_around_what_counts_as_long_in_a_piece.)"""
     P.spqr_set_option(P.SPQR_OPT_BATCH_PATH, P.SPQR_BATCH_PATH_MATRIX)
     f = make(w, b1, b2, axis, ntr, ntc, rate=0.0, structure="none", seed=(120, w))
     assert f.n == 2240
@@ -576,8 +573,8 @@ def test_matrix_core_long_rows_shared_out_by_entries(P, monkeypatch, w, b1, b2, 
     counts[108] = 513
     counts[110] = 1024
     counts[111] = 1025
-    counts[300] = 256                          # not long: stays with the finishing kernel
-    counts[301] = 257                          # long
+    counts[300] = 256
+    counts[301] = 257
     counts[f.m - 1] = 2000                     # the last row
     counts[::7] += 3                           # a few entries in every 7th row
     counts = np.minimum(counts, f.n)
@@ -592,8 +589,8 @@ def test_matrix_core_long_rows_shared_out_by_entries(P, monkeypatch, w, b1, b2, 
 
 
 def test_matrix_core_long_rows_of_a_very_tall_matrix(P, monkeypatch):
-    """More than 65536 rows: the search for a share's first row takes two rounds of probes.  Long rows at the very
-    top, around the probes' first bracket and at the bottom; the oracle is sampled on those rows and 64 others."""
+    """More than 65536 rows: many groups of strips, the last one ragged.  Long rows at the very top, around a group's end
+    and at the bottom; the oracle is sampled on those rows and 64 others."""
     P.spqr_set_option(P.SPQR_OPT_BATCH_PATH, P.SPQR_BATCH_PATH_MATRIX)
     f = make(3, 16, 16, 1, 4200, 20, rate=0.0, structure="none", seed=(122,))
     assert f.m == 67200 and f.n == 320
@@ -704,8 +701,7 @@ def test_batch_path_in_a_captured_graph_replays_like_the_eager_call(P, monkeypat
 
 
 def test_matrix_core_long_rows_next_to_rows_like_the_average(P, monkeypatch):
-    """What counts as a long row depends on the average: with 30 % outliers everywhere (about 600 per row) plus two
-    full rows of 2080, only the full rows leave the finishing kernel; the others are cut into 16 parts of about 39."""
+    """30 % outliers everywhere (about 600 per row, all of them long) plus two full rows of 2080 next to them."""
     P.spqr_set_option(P.SPQR_OPT_BATCH_PATH, P.SPQR_BATCH_PATH_MATRIX)
     f = make(4, 16, 16, 1, 5, 130, rate=0.3, structure="uniform", seed=(94,))
     rng = np.random.default_rng(94)

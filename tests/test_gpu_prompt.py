@@ -214,3 +214,103 @@ def test_outliers_beside_the_dense_workgroups_of_several_matrices(P, shares):
         ref = orc.matvec(f, X)
         err = np.linalg.norm(Y.cpu().numpy().astype(np.float64) - ref, axis=1) / np.linalg.norm(ref, axis=1)
         assert err.max() <= REL_L2
+
+
+def _one_pass_layer(P, b, perm):
+    """A layer and batch the library gives to the one-pass kernel by itself: its scratch holds no dense copy."""
+    f = synth.make_matrix(2056, 2080, w_bits=3, beta1=8, beta2=32, group_axis=1, outlier_rate=0.02, outlier_structure="zipf", seed=(83,))
+    if perm:
+        f.perm = np.random.default_rng(6).permutation(f.n).astype(np.int32)
+    A = P.SpQRMatrix.from_logical(f)
+    need = P.spqr_workspace_bytes(A, b)
+    assert 0 < need < 2 * f.m * f.n
+    return f, A, synth.make_x(f.n, b, seed=(84, b)), need
+
+
+@pytest.mark.parametrize("perm", [False, True])
+def test_one_pass_with_a_workspace_under_capture(P, perm):
+    """Kernel nodes only, and every replay gives the eager result bit for bit, with eager work in the same workspace and
+    another batch in the input between the replays."""
+    import ctypes as C
+    import torch
+    from test_gpu_workspace import _graph_node_types
+    f, A, X, need = _one_pass_layer(P, 77, perm)
+    Xd = torch.from_numpy(X).to("cuda:0")
+    ws = torch.empty(need, dtype=torch.uint8, device="cuda:0")
+    eager = P.spqr_gemm_smallbatch_ws(A, Xd, ws).clone()
+    turned = P.spqr_gemm_smallbatch_ws(A, Xd.flip(0).contiguous(), ws).clone()
+    run(P, f, 77)                                            # the same path against the oracle
+    Xg, Y = Xd.clone(), torch.zeros_like(eager)
+    torch.cuda.synchronize()
+    types, ex, graph, st, hip = _graph_node_types(lambda s: P.spqr_gemm_smallbatch_ws(A, Xg, ws, out=Y, stream=s))
+    assert len(types) == (5 if perm else 4) and all(t == 0 for t in types), types       # (gather,) count, sort, product, sums
+    for rep in range(4):
+        Xg.copy_(Xd if rep % 2 == 0 else Xd.flip(0))
+        Y.zero_()
+        torch.cuda.synchronize()
+        assert hip.hipGraphLaunch(ex, C.c_void_p(st.cuda_stream)) == 0
+        torch.cuda.synchronize()
+        assert torch.equal(Y, eager if rep % 2 == 0 else turned), rep
+        ws.fill_(0xA5)
+        P.spqr_gemm_smallbatch_ws(A, Xd, ws)
+        torch.cuda.synchronize()
+    assert hip.hipGraphExecDestroy(ex) == 0 and hip.hipGraphDestroy(graph) == 0
+
+
+def test_one_pass_scratch_limits_and_the_static_array(P):
+    """One byte too little: the slices of 16, bit for bit what they give when asked for; the entry that allocates nothing
+    and the one with the library's scratch: the one-pass result."""
+    import torch
+    b = 64
+    f, A, X, need = _one_pass_layer(P, b, True)
+    Xd = torch.from_numpy(X).to("cuda:0")
+    ws = torch.empty(need, dtype=torch.uint8, device="cuda:0")
+    one = P.spqr_gemm_smallbatch_ws(A, Xd, ws).clone()
+    run(P, f, b)
+    few = P.spqr_gemm_smallbatch_ws(A, Xd, ws[:need - 1]).clone()
+    P.spqr_set_option(P.SPQR_OPT_BATCH_PATH, P.SPQR_BATCH_PATH_MATRIX)
+    try:
+        small = P.spqr_workspace_bytes(A, b)
+        assert 0 < small < need
+        slices = P.spqr_gemm_smallbatch_ws(A, Xd, ws[:small]).clone()
+    finally:
+        P.spqr_set_option(P.SPQR_OPT_BATCH_PATH, P.SPQR_BATCH_PATH_AUTO)
+    assert torch.equal(few, slices) and not torch.equal(few, one)
+    assert torch.equal(P.spqr_gemm_smallbatch_ws(A, Xd, ws[:small]), slices)
+    assert need <= P.SPQR_STATIC_SCRATCH_BYTES
+    out = torch.zeros_like(one)
+    P.spqr_gemm_smallbatch_noalloc(A, Xd, out)
+    assert torch.equal(out, one)
+    assert torch.equal(P.spqr_gemm_smallbatch(A, Xd), one)
+    half = torch.zeros((b, f.m), dtype=torch.float16, device="cuda:0")
+    P.spqr_gemm_smallbatch_noalloc(A, Xd, half, y_dtype=P.SPQR_F16)
+    assert torch.equal(half, one.to(torch.float16))
+
+
+# rows of up to 64 entries inside a piece of 1536 columns are taken by 4 lanes each, longer ones by a whole wavefront
+@pytest.mark.parametrize("w,b1,b2,axis,ntr", [(3, 16, 16, 1, 20), (4, 8, 32, 1, 40), (3, 8, 32, 0, 10)])
+@pytest.mark.parametrize("b", [5, 16])
+@pytest.mark.parametrize("steps,shares", [(1, 0), (1000, 0), (1, 3), (1000, 1)])
+def test_rows_around_what_counts_as_long_in_a_piece(P, w, b1, b2, axis, ntr, b, steps, shares):
+    tr, tc = synth.tile_shape(b1, b2, axis)
+    f = synth.make_matrix(ntr * tr, 4096, w_bits=w, beta1=b1, beta2=b2, group_axis=axis, outlier_structure="none", seed=(85, w, axis))
+    rng = np.random.default_rng(86)
+    cols = {}
+    for r, (first, second) in {0: (63, 0), 1: (64, 0), 2: (65, 0), 3: (64, 64), 4: (65, 64), 5: (0, 65), 17: (1, 129), 40: (128, 63),
+                               41: (127, 0), 42: (1536, 0), 43: (1535, 1), 100: (66, 66), 255: (64, 65), 256: (65, 0), 319: (2, 64)}.items():
+        # so many entries in the columns 0 .. 1535 and 1536 .. 3071, a few behind them
+        cols[r] = np.concatenate([np.sort(rng.choice(1536, first, replace=False)), 1536 + np.sort(rng.choice(1536, second, replace=False)),
+                                  3072 + np.sort(rng.choice(1024, r % 3, replace=False))])
+    for r in range(6, 320, 5):
+        cols.setdefault(r, np.sort(rng.choice(4096, 3, replace=False)))
+    counts = np.zeros(f.m, np.int64)
+    for r, c in cols.items():
+        counts[r] = len(c)
+    f.row_ptr = np.concatenate([[0], np.cumsum(counts)]).astype(np.int32)
+    f.col_idx = np.concatenate([cols[r] for r in sorted(cols)]).astype(np.uint16)
+    f.val = rng.standard_normal(len(f.col_idx)).astype(np.float16)
+    P.spqr_set_option(P.SPQR_OPT_BATCH_PATH, P.SPQR_BATCH_PATH_MATRIX)
+    try:
+        run(P, f, b, steps, shares)
+    finally:
+        P.spqr_set_option(P.SPQR_OPT_BATCH_PATH, P.SPQR_BATCH_PATH_AUTO)
