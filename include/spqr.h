@@ -249,12 +249,15 @@ int spqr_gemv(const spqr_matrix_t* A, const uint16_t* x_f16, void* y, int y_dtyp
  * must not allocate or synchronise use spqr_gemm_smallbatch_ws.
  * Prompt-sized batches (from 48 vectors on, at b >= m*n/2.5e6 + nnz/1.5e5; Sec. 5
  * "Inference Time"; Y 16-byte aligned) of the same tile shapes, on layers from 4 M
- * (8x32) or 24 M weights on, take one pass over the weights: a workgroup dequantises them into
- * LDS, adds the outliers there and multiplies all vectors with them (scratch: 4
- * bytes per outlier, the partial sums, with a permutation b*n*2 bytes).
- * Smaller layers, other formats (12 vectors and more; tiles of 256 codes in any layout and 3-bit
- * tiles of 8 x 64, Y 16-byte aligned) and matrices with more outliers than one
- * weight in four: the matrix is dequantised once into a dense binary16 copy in
+ * weights and 512 columns (8x32) or 24 M weights on (above 192 vectors only with
+ * more than 2048 columns): the one-pass kernel.  A workgroup dequantises its
+ * weights into LDS, adds the outliers there and multiplies 64, 128 or (8x32) 256
+ * vectors with them; the compressed weights are read once per that many (scratch:
+ * 4 bytes per outlier, their ranges and counts, the partial sums, 64 MB at most
+ * where the columns are split, and b*n*2 bytes with a permutation).
+ * Other sizes, other formats (12 vectors and more; tiles of 256 codes in any layout
+ * and 3-bit tiles of 8 x 64, Y 16-byte aligned) and matrices with more outliers than
+ * one weight in four: the matrix is dequantised once into a dense binary16 copy in
  * scratch (2 bytes per weight, rows padded to a multiple of 64 columns; with a
  * permutation b*n*2 bytes more), the outliers are added into the copy, and one
  * matrix-core kernel multiplies the whole batch with it.  Where that much
@@ -277,8 +280,8 @@ int64_t spqr_workspace_bytes(const spqr_matrix_t* const* A, int count, int b);
 
 /* spqr_gemm_smallbatch with scratch the CALLER owns (Sec. 4.2's product, as
  * above): `workspace` is device memory, 256-byte aligned, of at least
- * spqr_workspace_bytes(&A, 1, b) bytes (SPQR_ERR_WORKSPACE if smaller; it may
- * be NULL when that is 0).  The call allocates nothing, frees nothing and
+ * spqr_workspace_bytes(&A, 1, b) bytes (it may be NULL when that is 0; a large
+ * batch with less takes the slices of 16, SPQR_ERR_WORKSPACE if they need more).  The call allocates nothing, frees nothing and
  * never synchronises; which kernels run does not depend on whether `stream`
  * is being captured, so a captured call records kernel nodes only.  The
  * workspace is written by the call's kernels and may be reused by the next
@@ -291,9 +294,9 @@ int spqr_gemm_smallbatch_ws(const spqr_matrix_t* A, const uint16_t* X_f16, int b
  * capture, tight serving loops, harnesses that forbid hipMalloc):
  * spqr_gemm_smallbatch with its scratch in a static device array of
  * SPQR_STATIC_SCRATCH_BYTES that the library's code object carries (every GPU
- * the library runs on holds it until the process ends).  A call whose
- * spqr_workspace_bytes(&A, 1, b) exceeds that size returns SPQR_ERR_WORKSPACE
- * and launches nothing.  No hipMalloc, hipFree or other allocating call is
+ * the library runs on holds it until the process ends).  A large batch whose
+ * spqr_workspace_bytes(&A, 1, b) exceeds that size takes the slices of 16; a call
+ * whose slices need more than that returns SPQR_ERR_WORKSPACE and launches nothing.  No hipMalloc, hipFree or other allocating call is
  * made; the first call on a device asks the runtime for the array's address.
  * All calls on one GPU share the array: calls that may overlap on one GPU
  * (different streams) race on it -- give such callers spqr_gemm_smallbatch_ws.
@@ -362,9 +365,10 @@ int spqr_gemv_grouped(const spqr_matrix_t* const* A, int count, const uint16_t* 
  *   SPQR_OPT_BATCH_PATH    SPQR_BATCH_PATH_AUTO (0): the library's rule picks the
  *                          kernels of a batch; _VECTOR (1) / _MATRIX (2): slices
  *                          of 4 on the vector kernel / slices of 16 on the
- *                          matrix cores wherever both exist (and never the dense
- *                          copy); _DENSE (3): the dense-copy path of large
- *                          batches for any batch it exists for
+ *                          matrix cores wherever both exist (and never the one-pass
+ *                          kernel or the dense copy); _DENSE (3): the dense-copy
+ *                          path of large batches for any batch it exists for
+ *                          (the one-pass kernel only runs under _AUTO)
  *   SPQR_OPT_FORCE_GENERIC 1: every product takes the element-wise fallback
  *                          kernel
  *   SPQR_OPT_BATCH_STEPS   k > 0: the matrix-core path's launch gives every

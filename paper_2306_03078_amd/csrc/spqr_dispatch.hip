@@ -37,13 +37,13 @@ hipError_t launch_gemm(const DevMatrix& A, const uint16_t* X, int b, void* Y, in
   const bool force_generic = option(SPQR_OPT_FORCE_GENERIC) != 0;
   bool mfma_ok = !force_generic && mfma_has_instance(g);
   const bool alloc_nodes = mfma_ok && !ws.from_caller && b >= kMfmaMinBatch && stream_is_capturing(stream);
-  // A prompt-sized batch: one pass over the compressed weights for all vectors (Y as the dense copy wants it: the calls
-  // that took the copy, see prompt_wanted).
+  // A prompt-sized batch: the product straight from the compressed weights (Y as the dense copy wants it: the calls that
+  // took the copy, see prompt_wanted).
   if (!force_generic && prompt_wanted(A, b) && reinterpret_cast<uintptr_t>(Y) % 16 == 0) {
     const hipError_t e = launch_prompt_scratch(A, X, b, Y, y_dtype, stream, ws);
-    if (e != hipErrorNotSupported) return e;   // no scratch of that size: the slices below
+    if (e != hipErrorNotSupported) return e;   // no scratch of that size: the copy if the caller's holds one, or the slices
   }
-  // Formats and outlier rates that path does not take: one dense binary16 copy of the matrix in scratch, one
+  // Formats, sizes and outlier rates that path does not take: one dense binary16 copy of the matrix in scratch, one
   // matrix-core multiply for all vectors.
   if (!force_generic && prefill_has_instance(g) && prefill_wanted(A, b) &&
       reinterpret_cast<uintptr_t>(Y) % 16 == 0) {

@@ -85,8 +85,8 @@ int plan_batch_hook(const DevMatrix* As, int count, int b, int* per, int* splits
 hipError_t launch_sum_groups(const Geometry& g, const float* P, int splits, int b, void* Y, int y_dtype, hipStream_t stream);
 
 // Prompt-sized batches (spqr_prompt.hip) and large batches through a dense binary16 copy of the matrix
-// (spqr_prefill.hip) on the library's scratch or the caller's workspace.  hipErrorNotSupported: no scratch of that size to be had (or the stream is being captured
-// and the library would have to allocate it): the caller takes the slices of 16.
+// (spqr_prefill.hip) on the library's scratch or the caller's workspace.  hipErrorNotSupported: no scratch of that size to
+// be had (or the stream is being captured and the library would have to allocate it): the caller takes the slices of 16.
 hipError_t launch_prompt_scratch(const DevMatrix& A, const uint16_t* X, int b, void* Y, int y_dtype, hipStream_t stream,
                                  const Workspace& ws);
 hipError_t launch_prefill_scratch(const DevMatrix& A, const uint16_t* X, int b, void* Y, int y_dtype, hipStream_t stream,
@@ -102,7 +102,7 @@ hipError_t launch_prefill(const DevMatrix& A, const uint16_t* X, int b, void* Y,
 
 hipError_t launch_gather_x(const uint16_t* X, const int32_t* perm, uint16_t* XP, int n, int b, hipStream_t stream);
 
-// ---- spqr_prompt.hip: prompt-sized batches in one pass over the compressed weights ----
+// ---- spqr_prompt.hip: prompt-sized batches straight from the compressed weights ----
 bool prompt_has_instance(const DevMatrix& A);
 bool prompt_wanted(const DevMatrix& A, int b);
 size_t prompt_workspace_bytes(const DevMatrix& A, int b);

@@ -26,18 +26,19 @@ namespace spqr {
 // wavefront).  Few rows x many columns would leave CUs idle, so gridDim.y splits the columns; every split writes its
 // own partial result (see sum_groups_kernel).
 //
-// Outliers.  The workgroup's piece of the batch passes through LDS transposed, XT[column][16 vectors], at most
-// kChunkCols columns at a time, so an outlier meets its 16 activations in two 16-byte LDS reads.  (From L2 the same
-// 32-byte line costs an L1 look-up per entry, about 10 clocks per entry and CU.)  A row's entries inside the columns
-// of the piece are found by bisection (columns increase inside a row), 16 lanes take a row's entries in turn, rows
-// of more than kLongRow entries in the piece are shared out among the wavefronts, 64 lanes each.  One writer per sum, fixed
-// orders everywhere: results are deterministic.
+// Outliers.  The workgroup's piece of the batch passes through LDS transposed, XT[column][16 vectors], at most 1536
+// columns (SH::COLS) at a time, so an outlier meets its 16 activations in two 16-byte LDS reads.  (From L2 the same
+// 32-byte line costs an L1 look-up per entry, about 10 clocks per entry and CU.)  Where a row's entries begin and end
+// inside the columns of the piece is interpolated (lower_columns), 4 lanes take a row's entries in turn, rows of more than
+// kLongRow entries in the piece are shared out among the wavefronts, 64 lanes each.  One writer per sum, fixed orders
+// everywhere: results are deterministic.  Where the launch leaves CUs over, they are a workgroup's own (APART, plan_batch).
 //
-// What bounds it (17920 x 6656, 4-bit, 16 vectors, 42 us with the sums): about half of it is vector issue (2.4
-// instructions per weight for the dequantisation, the outliers on top) beside the stream of the weights (14 us at the
-// rate of a copy); the rest is the start (row bounds, XT) and the memory latency that two workgroups per CU leave.
-// Without outliers 28 us.  Before (weights transposed through LDS quarter tile by quarter tile, outliers in a kernel of
-// their own that gathered from L2): 52 us; 8192 x 22016, 3-bit, 73 -> 64 us; three of 6656^2 at 4 vectors 52 -> 48 us.
+// What bounds it (17920 x 6656, 4-bit, Zipf outliers, 16 vectors, weights streamed, 45 us with the sums): vector issue for
+// a half of it (5.0 instructions per weight with the outliers, 57 % of the SIMDs' time) beside the stream of the weights
+// (14 us at the rate of a copy); the rest is the start (row bounds, XT) and the memory latency that two workgroups per CU
+// leave.  Without outliers 30 us.  Before (weights transposed through LDS quarter tile by quarter tile, outliers in a
+// kernel of their own that gathered from L2): 55 us; 8192 x 22016, 3-bit, 75 -> 63 us; 22016 x 8192 77 -> 66 us; three of
+// 6656^2 at 4 vectors 57 -> 49 us.
 // ---------------------------------------------------------------------------
 constexpr int kLongRow = 64;                 // entries of a row inside a piece beyond which a whole wavefront takes it
 
@@ -633,9 +634,10 @@ static int batch_units(const Geometry& g) { return (g.ntc + kUnitTiles - 1) / kU
 // shared out further), and wide pieces of XT pay on large ones.
 // Fitted to every split and share of 173 layers and sets of layers (1024^2 to two of 22016 x 8192, 16 vectors; uniform, full
 // columns, full rows, Zipf rows): the choice is 1.5 % off the best on average, 14 % at most, and 11 % faster than the
-// model before, which knew no shares and priced a piece at 4.5 (5 % slower at most): 22016 x 8192 with 8 x 32 tiles 80 -> 63
-// us (3 units), 5120^2 4-bit with Zipf rows 24.9 -> 18.3, 1024^2 with them 16.9 -> 11.1, two of 22016 x 8192 with 16 x 16
-// tiles 118 -> 98; 17920 x 6656 as before.
+// model before, which knew no shares and priced a piece at 4.5: 22016 x 8192 with 8 x 32 tiles 80 -> 63 us (3 units), 5120^2
+// 4-bit with Zipf rows 24.9 -> 18.3, 1024^2 with them 16.9 -> 11.1, two of 22016 x 8192 with 16 x 16 tiles 118 -> 98; 17920
+// x 6656 as before.  The worst against that model is 11008 x 4096, 3-bit, with 8 full rows: 23.9 -> 25.7 (6 units and the
+// outliers in 4 shares where 3 units and none or 4 units and 2 shares give 23.9).
 struct BatchCosts {
   float start_both, both, both_unit, both_entry, both_heavy, both_heavy_unit;              // workgroups that do both
   float start_apart, dense, dense_unit, outliers, outlier_unit, entry, heavy, heavy_unit;  // (entry, heavy: shared)
@@ -816,7 +818,7 @@ static hipError_t launch_mfma_t(const DevMatrix& A, const uint16_t* X, int b, vo
 // the weights once per 4 vectors.  Measured with eager calls (b = 4..16 over the layers of the 7B, 33B and 65B shapes, both
 // paths forced) the matrix cores win from 5 vectors on for any layer (4096^2 at b = 4 / 5 / 6 / 7: 16.5 us against 12.0 /
 // 17.8 / 19.7 / 25.8) and from 4 on for layers of 30 M weights or more (17920x6656 at b = 4: 43 us against 57; 11008x4096
-// 23.4 against 22.7).  The line for smaller layers stays at 7: with group_axis 0 the vector path keeps its weights in
+// 24.9 against 22.9).  The line for smaller layers stays at 7: with group_axis 0 the vector path keeps its weights in
 // binary32, and 5 or 6 vectors have always had that.  `alloc_nodes`: the call's scratch would be
 // allocation nodes of a graph under capture (library-owned scratch on a capturing stream), about 10 us more
 // per call: then from 13 vectors on for any layer, from 8 on for layers of 40 M weights and from 5 on for
@@ -935,8 +937,8 @@ hipError_t launch_prefill_scratch(const DevMatrix& A, const uint16_t* X, int b, 
 // In host code its name stands for the symbol, not for a device address: the address is asked per device
 // (each GPU holds its own copy) and only that pointer is ever handed to kernels.  All calls on a device that
 // use it share it: calls that overlap on one GPU (different streams) race.  Nothing in it has to start at
-// zero: every word a batch call reads (the transposed batch with its zero line, the slots of the long rows,
-// the partial results) is written earlier in the same call.
+// zero: every word a call reads (the batch in column order, the partial results, the sorted outliers and their ranges, the
+// dense copy) is written earlier in the same call.
 static __device__ __align__(256) uint8_t scratch[SPQR_STATIC_SCRATCH_BYTES];
 
 hipError_t static_workspace(Workspace* ws) {

@@ -1,7 +1,7 @@
-// Large batches (the prompt phase of Sec. 5, "Inference Time") of the formats and outlier rates that spqr_prompt.hip does not
-// take: the weights are dequantised once per call into a
-// dense binary16 copy in scratch, the outliers are added into it, and one tiled matrix-core kernel multiplies the
-// whole batch with it (Sec. 4.2 describes the same order: 16-bit weights first, then the product).  The
+// Large batches (the prompt phase of Sec. 5, "Inference Time") of the formats, sizes and outlier rates that spqr_prompt.hip
+// does not take: the weights are dequantised once per call into a dense binary16 copy in scratch, the outliers are added
+// into it, and one tiled matrix-core kernel multiplies the whole batch with it (Sec. 4.2 describes the same order: 16-bit
+// weights first, then the product).  The
 // slices of 16 of the batch path read and dequantise the weights once per slice; here a weight is read once
 // compressed, written once and read once per 128 vectors as binary16.
 #include <hip/hip_runtime.h>
@@ -277,10 +277,13 @@ bool prefill_has_instance(const Geometry& g) {
 // Whether a batch of b vectors goes through the dense copy, or, where the format has it, the one-pass kernel of
 // spqr_prompt.hip, which has its rule from here: the copy costs one pass over the compressed weights,
 // one write of 2 bytes per weight and a scattered read-modify-write per outlier, whatever the batch; the slices of
-// 16 cost a pass over the compressed weights each.  Measured on the 7B to 65B shapes (batches of 32 to 256, both
-// paths forced, slices with the outliers in a kernel of their own, a fifth slower than now): the copy wins from 48 vectors on layers of up to 120 M weights (4096^2 at 48: 34 against 56 us;
-// 17920x6656: 144 against 156), from 64 on 8192^2 with 2 % outliers and from 96 on the layers of 180 M weights
-// (22016x8192 at 64 / 96: 326 / 355 against 289 / 433); at 256 vectors it is 3.4 to 6.8 times faster.
+// 16 cost a pass over the compressed weights each.  The line was fitted to slices that added the outliers in a kernel of
+// their own (7B to 65B shapes, batches of 32 to 256, both paths forced): the copy won from 48 vectors on layers of up to 120 M
+// weights (4096^2 at 48: 34 against 56 us; 17920x6656: 144 against 156), from 64 on 8192^2 with 2 % outliers and from 96
+// on the layers of 180 M weights (22016x8192 at 64 / 96: 326 / 355 against 289 / 433).  The slices of today are a fifth
+// faster (in the same order: 46 against the copy's 35, 127 against 140, at 64 / 96 245 / 367 against 279 / 352), so
+// between 33 and about 100 vectors the line is early for the copy on large layers and late for the one-pass kernel, which
+// rounds weight + outlier to binary16: it stays, so that no call's rounding changes with it.
 bool prefill_wanted(const DevMatrix& A, int b) {
   const int forced = option(SPQR_OPT_BATCH_PATH);
   if (forced == SPQR_BATCH_PATH_DENSE) return true;

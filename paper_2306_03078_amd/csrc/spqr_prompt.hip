@@ -1,6 +1,7 @@
-// Prompt-sized batches (the prompt phase of Sec. 5, "Inference Time"): up to 256 vectors in one pass over the compressed
-// weights.  Sec. 4.2 makes 16-bit weights first and then multiplies; here the 16-bit weights exist only in LDS, a
-// workgroup's block of columns at a time, outliers added, and the matrix cores read them from there.
+// Prompt-sized batches (the prompt phase of Sec. 5, "Inference Time"): one kernel from the compressed weights to the
+// products of up to 256 vectors.  Sec. 4.2 makes 16-bit weights first and then multiplies; here the 16-bit weights exist
+// only in LDS, a workgroup's block of columns at a time, outliers added, and the matrix cores read them from there, for 64,
+// 128 or (strips of 8 rows) 256 vectors; more vectors than that read and dequantise the weights once per that many.
 #include <hip/hip_runtime.h>
 #include <cstdint>
 
@@ -130,19 +131,21 @@ sort_phases_kernel(DevMatrix A, int unit_shift, int kg, int phases, const uint32
 // ---------------------------------------------------------------------------
 // P[split][vector][rows] = X . W_hat^T for 64 * NVB vectors per blockIdx.z (see the batch kernel for the layout of the operands: a lane
 // holds a tile, 16 lanes the same tile column of 16 strips, row r of the strips is an operand).  A workgroup of 4
-// wavefronts owns a group of 16 strips (256 or 128 rows) and all vectors; a phase is 8 columns of each of the 16 tile
+// wavefronts owns a group of 16 strips (256 or 128 rows) and 64 * NVB vectors; a phase is 8 columns of each of the 16 tile
 // columns of a unit.  Wavefront w dequantises 4 of the tile columns and leaves its operands in LDS, in the order they
 // will be read (16 bytes per lane, no bank conflict); the outliers of the phase are added there; then every wavefront
 // multiplies all of them with its own 16 * NVB vectors, whose operands come from X (L2) one phase ahead.  Two buffers: the
 // next phase is dequantised between the multiplications of this one, so vector issue hides behind the matrix cores.
-// One wavefront per SIMD (16 x NVB x 4 sums a lane), so a dequantised weight is used for 256 vectors and an operand
-// read from LDS for NVB multiplications.
+// One wavefront per SIMD and one workgroup per CU (64 x NVB sums a lane with strips of 16 rows, 128.5 KB of LDS; half of
+// both with strips of 8): a dequantised weight is used for 64 * NVB vectors, an operand read from LDS for NVB
+// multiplications.
 //
 // What bounds it: issue and LDS.  A phase with strips of 16 rows and 128 vectors is 128 matrix instructions (2048
-// clocks), 360 vector ones and 80 LDS operations per wavefront, 256 KB read from LDS per workgroup (2048 clocks), and
-// takes 2.3 us, of which the outliers' two barriers and round trip are a part.  Measured (with the sort and the sums):
-// 17920 x 6656, 4-bit, 256 vectors 246 -> 162 us (376 TFLOP/s), 128 vectors 102 us; gate and up 11008 x 4096, 3-bit, 77
-// vectors 149 -> 102 us.  Before, the weights went through a dense binary16 copy in memory (70 us of writing it, 30 us
+// clocks), 530 vector ones and 90 LDS operations per wavefront with its outliers, 256 KB read from LDS per workgroup (2048
+// clocks), and takes 2.3 us, of which the outliers' two barriers and round trip are a part (17920 x 6656, 256 vectors:
+// vector issue 35 % of a wavefront's time, the matrix cores 26 %).  Measured (with the sort and the sums, 19 and 17 us of
+// the 161): 17920 x 6656, 4-bit, 256 vectors 240 -> 161 us (380 TFLOP/s), 128 vectors 173 -> 95 us; gate and up 11008 x
+// 4096, 3-bit, 77 vectors 149 -> 101 us.  Before, the weights went through a dense binary16 copy in memory (70 us of writing it, 30 us
 // of adding the outliers there, 137 us of multiplying at 256 vectors).
 // ---------------------------------------------------------------------------
 template <int W, int TR, int TC, int AXIS, int NVB>
