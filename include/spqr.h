@@ -281,7 +281,8 @@ int64_t spqr_workspace_bytes(const spqr_matrix_t* const* A, int count, int b);
 /* spqr_gemm_smallbatch with scratch the CALLER owns (Sec. 4.2's product, as
  * above): `workspace` is device memory, 256-byte aligned, of at least
  * spqr_workspace_bytes(&A, 1, b) bytes (it may be NULL when that is 0; a large
- * batch with less takes the slices of 16, SPQR_ERR_WORKSPACE if they need more).  The call allocates nothing, frees nothing and
+ * batch with less takes the slices of 16, SPQR_ERR_WORKSPACE if they need more).
+ * The call allocates nothing, frees nothing and
  * never synchronises; which kernels run does not depend on whether `stream`
  * is being captured, so a captured call records kernel nodes only.  The
  * workspace is written by the call's kernels and may be reused by the next
@@ -296,8 +297,8 @@ int spqr_gemm_smallbatch_ws(const spqr_matrix_t* A, const uint16_t* X_f16, int b
  * SPQR_STATIC_SCRATCH_BYTES that the library's code object carries (every GPU
  * the library runs on holds it until the process ends).  A large batch whose
  * spqr_workspace_bytes(&A, 1, b) exceeds that size takes the slices of 16; a call
- * whose slices need more than that returns SPQR_ERR_WORKSPACE and launches nothing.  No hipMalloc, hipFree or other allocating call is
- * made; the first call on a device asks the runtime for the array's address.
+ * whose slices need more than that returns SPQR_ERR_WORKSPACE and launches
+ * nothing.  No hipMalloc, hipFree or other allocating call is made; the first call on a device asks the runtime for the array's address.
  * All calls on one GPU share the array: calls that may overlap on one GPU
  * (different streams) race on it -- give such callers spqr_gemm_smallbatch_ws.
  * Same results as spqr_gemm_smallbatch_ws. */
