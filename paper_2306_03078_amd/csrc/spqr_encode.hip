@@ -341,13 +341,69 @@ __global__ void __launch_bounds__(64 * kWaves) sweep_kernel(SweepArgs a) {
 // a workgroup per CU where 64 rows each would leave three of four idle.  The working copy is row-major.
 //   chain     the first wavefront alone, a lane per row (its four groups of 16 lanes do the same), 16 of the block's columns
 //             in registers: the steps of a column depend on one another, nothing is read from LDS but H^ic
-//   feedback  lanes = columns, a wavefront takes 64 columns of all 16 rows (16 sums a lane), its piece of H^ic comes
-//             straight from memory, one number per lane and step, and the errors E as LDS broadcasts
+//   feedback  lanes = columns, a wavefront takes up to 256 columns of all 16 rows (64 sums a lane, far_feedback)
 // Same operations in the same order on every weight as sweep_kernel, hence the same bits.
 // Bound: binary64 issue of the feedback (m n^2 products and differences) next to the chain (n columns, two true
 // divisions each, one after the other).
 // ---------------------------------------------------------------------------
 constexpr int kRows16 = 16, kWaves16 = 8;
+
+// Line 16 for the columns k0 + 64 c + lane, c < C, of the workgroup's rows: W[:, k] -= E[:, j] * H^ic[sb + j, k] for all sbw columns
+// j of the super-block, in order.  A lane holds 16 rows of C columns: the errors are LDS broadcasts (eight reads of 16 bytes
+// per column j whatever C is: with one column a lane they are what the pass waits for, two are even with the arithmetic),
+// H^ic comes straight from memory, four j ahead.  4096^2: 7.8 of the sweep's 11.0 ms with one column a lane, 4.3 of 7.5 with four.
+template <int C>
+__device__ __forceinline__ void far_feedback(double* __restrict__ W, const double* __restrict__ U, int n, int row0, int rows, int lane,
+                                             int sb, int sbw, int k0, const double (*esb)[kRows16]) {
+  typedef double f64x2 __attribute__((ext_vector_type(2)));
+  constexpr int PF = 4;                                  // a super-block has a multiple of 4 columns
+  uint32_t off[C];
+#pragma unroll
+  for (int c = 0; c < C; ++c) off[c] = (uint32_t)min(k0 + 64 * c + lane, n - 1) * 8u;
+  auto at = [&](const double* row, int c) { return *reinterpret_cast<const double*>(reinterpret_cast<const char*>(row) + off[c]); };
+  double cur[C][kRows16], u[PF][C], un[PF][C];
+  const double* uj = U + (size_t)sb * n;
+#pragma unroll
+  for (int q = 0; q < PF; ++q)
+#pragma unroll
+    for (int c = 0; c < C; ++c) u[q][c] = at(uj + (size_t)q * n, c);
+#pragma unroll
+  for (int r = 0; r < kRows16; ++r)
+#pragma unroll
+    for (int c = 0; c < C; ++c) cur[c][r] = at(W + (size_t)(row0 + min(r, rows - 1)) * n, c);
+#pragma unroll 1
+  for (int j = 0; j < sbw; j += PF) {
+    if (j + PF < sbw) uj += (size_t)PF * n;              // behind the last four: the same ones again, unused
+#pragma unroll
+    for (int q = 0; q < PF; ++q)
+#pragma unroll
+      for (int c = 0; c < C; ++c) un[q][c] = at(uj + (size_t)q * n, c);
+#pragma unroll
+    for (int q = 0; q < PF; ++q) {
+#pragma unroll
+      for (int r = 0; r < kRows16; r += 2) {
+        const f64x2 e = *reinterpret_cast<const f64x2*>(&esb[j + q][r]);
+#pragma unroll
+        for (int c = 0; c < C; ++c) {
+          cur[c][r] = cur[c][r] - e.x * u[q][c];
+          cur[c][r + 1] = cur[c][r + 1] - e.y * u[q][c];
+        }
+      }
+    }
+#pragma unroll
+    for (int q = 0; q < PF; ++q)
+#pragma unroll
+      for (int c = 0; c < C; ++c) u[q][c] = un[q][c];
+  }
+#pragma unroll
+  for (int c = 0; c < C; ++c) {
+    if (k0 + 64 * c + lane < n) {
+#pragma unroll
+      for (int r = 0; r < kRows16; ++r)
+        if (r < rows) *reinterpret_cast<double*>(reinterpret_cast<char*>(W + (size_t)(row0 + r) * n) + off[c]) = cur[c][r];
+    }
+  }
+}
 
 template <int B1> struct Sweep16Lds {
   double esb[kSuper][kRows16];                           // errors E of the current super-block's columns
@@ -503,39 +559,20 @@ __global__ void __launch_bounds__(64 * kWaves16, 2) sweep16_kernel(SweepArgs a) 
       }
       __syncthreads();       // the next block's columns are complete; wbs, ublk, omask are free again
     }
-    // ---- line 16 for everything right of the super-block: all of its errors in one pass, 64 columns at a time ----
-    for (int k0 = sb + sbw + 64 * wave; k0 < n; k0 += 64 * kWaves16) {    // wave-uniform
-      const int k = min(k0 + lane, n - 1);
-      const bool live = k0 + lane < n;
-      double cur[kRows16];
-#pragma unroll
-      for (int r = 0; r < kRows16; ++r) cur[r] = W[(size_t)(row0 + min(r, rows - 1)) * n + k];
-      const double* uk = U + (size_t)sb * n + k;
-      constexpr int PF = 4;
-      double u[PF], un[PF];
-#pragma unroll
-      for (int q = 0; q < PF; ++q) u[q] = uk[(size_t)q * n];             // a super-block has at least 4 columns
-      for (int j = 0; j < sbw; j += PF) {                // sbw is a multiple of B1, B1 of 4
-        const int jn = j + PF < sbw ? j + PF : j;
-#pragma unroll
-        for (int q = 0; q < PF; ++q) un[q] = uk[(size_t)(jn + q) * n];
-#pragma unroll
-        for (int q = 0; q < PF; ++q) {
-#pragma unroll
-          for (int r = 0; r < kRows16; r += 2) {
-            const f64x2 e = *reinterpret_cast<const f64x2*>(&S.esb[j + q][r]);
-            cur[r] = cur[r] - e.x * u[q];
-            cur[r + 1] = cur[r + 1] - e.y * u[q];
-          }
+    // ---- line 16 for everything right of the super-block: all of its errors in one pass, shared out in rounds of up to four
+    // columns a lane, rounds of equal width where the columns allow it ----
+    for (int k0 = sb + sbw; k0 < n;) {                   // workgroup-uniform
+      const int pieces = (n - k0 + 64 * kWaves16 - 1) / (64 * kWaves16), rounds = (pieces + 3) / 4;
+      const int cols = (pieces + rounds - 1) / rounds, at = k0 + 64 * cols * wave;
+      if (at < n) {                                      // wave-uniform
+        switch (cols) {
+          case 1: far_feedback<1>(W, U, n, row0, rows, lane, sb, sbw, at, S.esb); break;
+          case 2: far_feedback<2>(W, U, n, row0, rows, lane, sb, sbw, at, S.esb); break;
+          case 3: far_feedback<3>(W, U, n, row0, rows, lane, sb, sbw, at, S.esb); break;
+          default: far_feedback<4>(W, U, n, row0, rows, lane, sb, sbw, at, S.esb); break;
         }
-#pragma unroll
-        for (int q = 0; q < PF; ++q) u[q] = un[q];
       }
-      if (live) {
-#pragma unroll
-        for (int r = 0; r < kRows16; ++r)
-          if (r < rows) W[(size_t)(row0 + r) * n + k] = cur[r];
-      }
+      k0 += 64 * kWaves16 * cols;
     }
     __syncthreads();
   }

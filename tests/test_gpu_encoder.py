@@ -187,3 +187,17 @@ def test_argument_checks(E):
         E.spqr_quantize(W, U, 3, 16, 16, 0.1, workspace=small)
     with pytest.raises(Exception):
         E.spqr_inverse_cholesky(U, 0.1, workspace=small)
+
+
+@pytest.mark.parametrize("b1,m,n", [(16, 16, 1152), (8, 48, 1616), (16, 32, 2192), (32, 16, 2720), (4, 8, 580)])
+def test_sweep_far_columns_bit_exact(E, b1, m, n):
+    # the columns right of a super-block in every width of the rounds (1 to 4 columns a lane, the last ones clamped), equal and
+    # unequal rounds; an upper factor made directly, diagonal of a narrow range
+    rng = np.random.default_rng(m + n)
+    W = rng.normal(0, 0.05, (m, n))
+    W[rng.random((m, n)) < 0.02] *= 6.0
+    U = np.triu(rng.normal(0, 0.3 / np.sqrt(n), (n, n)), 1) + np.eye(n)
+    U *= 0.01 * (0.5 + rng.random((n, 1)))
+    ref = enc.spqr_quantize(W, U, 3, b1, 8, 20.0)
+    got = E.spqr_quantize(dev(W), dev(U), 3, b1, 8, 20.0)
+    _compare_exact(got, ref)
