@@ -249,12 +249,12 @@ int spqr_gemv(const spqr_matrix_t* A, const uint16_t* x_f16, void* y, int y_dtyp
  * must not allocate or synchronise use spqr_gemm_smallbatch_ws.
  * Prompt-sized batches (from 48 vectors on, at b >= m*n/2.5e6 + nnz/1.5e5; Sec. 5
  * "Inference Time"; Y 16-byte aligned) of the same tile shapes, on layers from 4 M
- * weights and 512 columns (8x32) or 24 M weights on (above 192 vectors only with
- * more than 2048 columns): the one-pass kernel.  A workgroup dequantises its
- * weights into LDS, adds the outliers there and multiplies 64, 128 or (8x32) 256
- * vectors with them; the compressed weights are read once per that many (scratch:
- * 4 bytes per outlier, their ranges and counts, the partial sums, 64 MB at most
- * where the columns are split, and b*n*2 bytes with a permutation).
+ * weights (32x8: 12 M) and 512 columns on: the one-pass kernel.  A workgroup
+ * dequantises its weights into LDS, adds the outliers there and multiplies 64 to
+ * 192 vectors with them; the compressed weights are read once per that many
+ * (scratch: 4 bytes per outlier, their ranges and counts, the partial sums, 64 MB
+ * at most where the columns are split, b*n*2 bytes and as many again with a
+ * permutation).
  * Other sizes, other formats (12 vectors and more; tiles of 256 codes in any layout
  * and 3-bit tiles of 8 x 64, Y 16-byte aligned) and matrices with more outliers than
  * one weight in four: the matrix is dequantised once into a dense binary16 copy in
@@ -296,7 +296,8 @@ int spqr_gemm_smallbatch_ws(const spqr_matrix_t* A, const uint16_t* X_f16, int b
  * spqr_gemm_smallbatch with its scratch in a static device array of
  * SPQR_STATIC_SCRATCH_BYTES that the library's code object carries (every GPU
  * the library runs on holds it until the process ends).  A large batch whose
- * spqr_workspace_bytes(&A, 1, b) exceeds that size takes the slices of 16; a call
+ * scratch does not fit takes the slices of 16 (the one-pass kernel first tries with
+ * fewer partial sums, which is slower than with a workspace of full size); a call
  * whose slices need more than that returns SPQR_ERR_WORKSPACE and launches
  * nothing.  No hipMalloc, hipFree or other allocating call is made; the first call on a device asks the runtime for the array's address.
  * All calls on one GPU share the array: calls that may overlap on one GPU
@@ -325,7 +326,8 @@ int spqr_gemv_fused(const spqr_matrix_t* const* A, int count, const uint16_t* x_
  * spqr_gemv_fused is for one vector.  Same agreement rules (SPQR_ERR_PARAM
  * otherwise), A and Y are HOST arrays.  Where the batch takes the matrix-core
  * path of spqr_gemm_smallbatch, all matrices share one launch for the products
- * and one for the sums per slice of 16 vectors;
+ * and one for the sums per slice of 16 vectors, and where every matrix takes the
+ * one-pass kernel, that kernel's launches;
  * otherwise, and whenever `stream` is being captured into a graph, the call is
  * `count` calls of spqr_gemm_smallbatch (b == 1: one spqr_gemv_fused).  Scratch
  * as for spqr_gemm_smallbatch (library-owned; spqr_gemm_fused_ws takes the
@@ -386,9 +388,9 @@ int spqr_gemv_grouped(const spqr_matrix_t* const* A, int count, const uint16_t* 
  *   SPQR_OPT_PROMPT_PLAN   1024 * V + U > 0: prompt-sized batches take the
  *                          one-pass kernel on layers of any size (formats and
  *                          outlier rates it has), with 64 * V vectors (V = 1, 2
- *                          or 4; 2 at most with 16-row strips; 0: the library's
- *                          rule) per workgroup and U units of 16 tile columns
- *                          per split (0: the library's rule) */
+ *                          or 4, at most 192; 32 or 64 fewer where the batch has
+ *                          no more; 0: the library's rule) per workgroup and U
+ *                          units of 16 tile columns (0: the library's rule) */
 #define SPQR_OPT_BATCH_PATH     0
 #define SPQR_OPT_FORCE_GENERIC  1
 #define SPQR_OPT_BATCH_STEPS    2

@@ -16,20 +16,20 @@ constexpr int kUnitTiles = 16;               // tile columns of a unit of the sp
 // that the strips of the kernel are 8 or 16 rows in every format.
 constexpr int lane_rows(int tile_rows) { return tile_rows == 32 ? 16 : tile_rows; }
 
-// What a lane holds of its tile: the codes of its rows (a tile of 32 rows: of one half) and the tile's statistics.
-template <int W, int TR, int TC, int AXIS> struct BatchTile {
+// What a lane holds of its tile: the codes of its LR rows (one of TR / LR parts of the tile) and the tile's statistics.
+template <int W, int TR, int TC, int AXIS, int LR = lane_rows(TR)> struct BatchTile {
   using T = TileRegs<W, TR, TC, AXIS>;
-  static constexpr int KW = T::KW * lane_rows(TR) / TR;
-  uint32_t c[4 * KW];
+  static constexpr int DW = 4 * T::KW * LR / TR;              // dwords of codes: whole 16-byte words, or one and a half
+  uint32_t c[DW];
   uint32_t s[T::SD];
 };
 
 // `blk` and L (the block and its tiles) are uniform, `l` is the lane's tile in it, `off` the lane's strip's byte offset,
-// `half` (tiles of 32 rows) which rows.
-template <int W, int TR, int TC, int AXIS>
-__device__ __forceinline__ void load_batch_tile(BatchTile<W, TR, TC, AXIS>& t, const uint8_t* blk, int L, uint32_t off,
-                                                uint32_t l, int half) {
-  using B = BatchTile<W, TR, TC, AXIS>;
+// `part` (tiles of more than LR rows) which rows.
+template <int W, int TR, int TC, int AXIS, int LR>
+__device__ __forceinline__ void load_batch_tile(BatchTile<W, TR, TC, AXIS, LR>& t, const uint8_t* blk, int L, uint32_t off,
+                                                uint32_t l, int part) {
+  using B = BatchTile<W, TR, TC, AXIS, LR>;
   using T = typename B::T;
   const uint32_t off16 = off + 16u * l, off4 = off + 4u * l;
   const uint8_t* sb = blk + 16 * T::KW * L;
@@ -41,12 +41,29 @@ __device__ __forceinline__ void load_batch_tile(BatchTile<W, TR, TC, AXIS>& t, c
   const uint8_t* rb = sb + 16 * T::SWF * L;
 #pragma unroll
   for (int k = 0; k < T::SR; ++k) t.s[4 * T::SWF + k] = *reinterpret_cast<const uint32_t*>(rb + 4 * k * L + off4);
-  const uint32_t offc = B::KW == T::KW ? off16 : off16 + (half ? 16u * B::KW * (uint32_t)L : 0u);
+  if constexpr (B::DW % 4 == 0) {
+    const uint32_t offc = TR == LR ? off16 : off16 + (uint32_t)part * (4u * B::DW) * (uint32_t)L;
 #pragma unroll
-  for (int k = 0; k < B::KW; ++k) {
-    const u32x4 v = *reinterpret_cast<const u32x4*>(blk + 16 * k * L + offc);
-    t.c[4 * k] = v.x; t.c[4 * k + 1] = v.y; t.c[4 * k + 2] = v.z; t.c[4 * k + 3] = v.w;
+    for (int k = 0; k < B::DW / 4; ++k) {
+      const u32x4 v = *reinterpret_cast<const u32x4*>(blk + 16 * k * L + offc);
+      t.c[4 * k] = v.x; t.c[4 * k + 1] = v.y; t.c[4 * k + 2] = v.z; t.c[4 * k + 3] = v.w;
+    }
+  } else {                                   // six dwords: a word and the lower half of the next, or an upper half and a word
+    static_assert(B::DW == 6, "a quarter of a 3-bit tile");
+    const uint32_t offc = off16 + (uint32_t)(part + (part >> 1)) * 16u * (uint32_t)L;
+    const u32x4 v = *reinterpret_cast<const u32x4*>(blk + offc), w = *reinterpret_cast<const u32x4*>(blk + 16 * L + offc);
+    const bool odd = part & 1;
+    t.c[0] = odd ? v.z : v.x; t.c[1] = odd ? v.w : v.y; t.c[2] = odd ? w.x : v.z;
+    t.c[3] = odd ? w.y : v.w; t.c[4] = odd ? w.z : w.x; t.c[5] = odd ? w.w : w.y;
   }
+}
+
+// Two binary32 numbers to a binary16 pair, to nearest even.  The fused multiply-add with a binary16 result that the compiler
+// would take for (_Float16)fmaf(..) twice runs at half rate: 17 clocks a pair against 14 with one conversion of both.
+__device__ __forceinline__ uint32_t pack_f16(float lo, float hi) {
+  uint32_t d;
+  asm("v_cvt_pk_f16_f32 %0, %1, %2" : "=v"(d) : "v"(lo), "v"(hi));
+  return d;
 }
 
 // Dequantisation of a lane's rows, 8 columns at a time: w = s_hat * (q - z_hat) in one binary32 FMA, rounded once to
@@ -59,10 +76,10 @@ __device__ __forceinline__ void load_batch_tile(BatchTile<W, TR, TC, AXIS>& t, c
 // No shift for most codes, and no offset that would have to cancel inside the FMA: the offset 2^(7 - bit) that the batch-1
 // kernel's extraction leaves is up to 128 times a weight of s_hat, and with it 8 to 11 % of the weights were not the
 // nearest binary16.  So measured over 16384 weights per format none is not, with 1 + q/2^W 0.2 to 0.4 %; same time.
-template <int W, int TR, int TC, int AXIS> struct Dequant {
-  using B = BatchTile<W, TR, TC, AXIS>;
+template <int W, int TR, int TC, int AXIS, int LR_ = lane_rows(TR)> struct Dequant {
+  using B = BatchTile<W, TR, TC, AXIS, LR_>;
   using T = typename B::T;
-  static constexpr int LR = lane_rows(TR), NSUB = TR / LR;    // rows of a lane; strips of the kernel per strip of tiles
+  static constexpr int LR = LR_, NSUB = TR / LR;              // rows of a lane; strips of the kernel per strip of tiles
   static constexpr int PPR = TC / 2, KG = TC / 8;             // code pairs per row; blocks of 8 columns
   static constexpr int NG = AXIS == 1 ? TC : LR;              // first-level groups of a lane
   // The bit a code lies at (its class, see CodeClass) is a function of the pair's column, for 3-bit codes in rows of 8
@@ -73,11 +90,11 @@ template <int W, int TR, int TC, int AXIS> struct Dequant {
   static constexpr float SCALE = (float)(1 << W);
   PairConsts kc, k3;
   ClassConsts kk;
-  int half;                                                   // which rows of a tile of 32
+  int part;                                                   // which rows of a tile of more than LR
   float c1, c2, e1, e2;                                       // of the current tile
   float fa[NK][NF], fb[NF];
 
-  __device__ __forceinline__ Dequant(int half_) : half(half_) {
+  __device__ __forceinline__ Dequant(int part_) : part(part_) {
     kc = make_pair_consts<W>();
     k3 = make_pair_consts<3>();
     kk = make_class_consts<W>();
@@ -109,10 +126,7 @@ template <int W, int TR, int TC, int AXIS> struct Dequant {
     const int q = r * PPR + 4 * j + d;
     const half2_t q2 = as_half2(INPLACE ? pair_code_bits<W>(t.c, q, kk) : pair_f16<W>(t.c, q, kc));
     const int g0 = AXIS == 1 ? 2 * d : r, g1 = AXIS == 1 ? 2 * d + 1 : r;
-    half2_t w;
-    w.x = (_Float16)fmaf((float)q2.x, fa[r % NK][g0], fb[g0]);
-    w.y = (_Float16)fmaf((float)q2.y, fa[r % NK][g1], fb[g1]);
-    return __builtin_bit_cast(uint32_t, w);
+    return pack_f16(fmaf((float)q2.x, fa[r % NK][g0], fb[g0]), fmaf((float)q2.y, fa[r % NK][g1], fb[g1]));
   }
   // Row r, columns 8j .. 8j+7 as an operand.
   __device__ __forceinline__ half8_t operand(const B& t, int r, int j) const {
@@ -123,9 +137,12 @@ template <int W, int TR, int TC, int AXIS> struct Dequant {
  private:
   __device__ __forceinline__ void group_pair(const B& t, int p, int at) {    // groups 2p and 2p + 1 of the lane
     uint32_t sp = pair_f16<3>(t.s, p, k3), zp = pair_f16<3>(t.s, T::B2 / 2 + p, k3);
-    if constexpr (NSUB == 2) {                 // the groups of the lane's half of the rows
-      sp = half ? pair_f16<3>(t.s, NG / 2 + p, k3) : sp;
-      zp = half ? pair_f16<3>(t.s, T::B2 / 2 + NG / 2 + p, k3) : zp;
+    if constexpr (AXIS == 0) {                 // the groups of the lane's part of the rows
+#pragma unroll
+      for (int h = 1; h < NSUB; ++h) {
+        sp = part == h ? pair_f16<3>(t.s, h * NG / 2 + p, k3) : sp;
+        zp = part == h ? pair_f16<3>(t.s, T::B2 / 2 + h * NG / 2 + p, k3) : zp;
+      }
     }
     const half2_t sq = as_half2(sp), zq = as_half2(zp);
     const float f0 = fmaf((float)sq.x, c1, c2), f1 = fmaf((float)sq.y, c1, c2);

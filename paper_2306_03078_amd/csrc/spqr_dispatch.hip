@@ -1,6 +1,7 @@
 // Which kernels a product call takes: host logic only.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <atomic>
 #include <cstdint>
 
@@ -40,7 +41,7 @@ hipError_t launch_gemm(const DevMatrix& A, const uint16_t* X, int b, void* Y, in
   // A prompt-sized batch: the product straight from the compressed weights (Y as the dense copy wants it: the calls that
   // took the copy, see prompt_wanted).
   if (!force_generic && prompt_wanted(A, b) && reinterpret_cast<uintptr_t>(Y) % 16 == 0) {
-    const hipError_t e = launch_prompt_scratch(A, X, b, Y, y_dtype, stream, ws);
+    const hipError_t e = launch_prompt_scratch(&A, 1, X, b, &Y, y_dtype, stream, ws);
     if (e != hipErrorNotSupported) return e;   // no scratch of that size: the copy if the caller's holds one, or the slices
   }
   // Formats, sizes and outlier rates that path does not take: one dense binary16 copy of the matrix in scratch, one
@@ -75,6 +76,17 @@ hipError_t launch_gemm(const DevMatrix& A, const uint16_t* X, int b, void* Y, in
   return hipSuccess;
 }
 
+// Whether launch_gemm_fused gives several matrices to the one-pass kernel together.
+static bool prompt_set_wanted(const DevMatrix* As, int count, int b) {
+  bool all = count > 1;
+  int64_t nnz = 0;                           // (counted in 32 bits there)
+  for (int i = 0; i < count && all; ++i) {
+    all = prompt_wanted(As[i], b);
+    nnz += As[i].nnz;
+  }
+  return all && nnz < 0x7FFF0000ll;
+}
+
 // Whether launch_gemm_fused takes the fused matrix-core launches for a slice of nb vectors.
 static bool fused_mfma_wanted(const DevMatrix* As, int count, int nb, bool alloc_nodes) {
   Geometry all = As[0].g;                    // the rule looks at the weights of all matrices together
@@ -98,10 +110,19 @@ hipError_t launch_gemm_fused(const DevMatrix* As, int count, const uint16_t* X, 
   // graphs of the per-matrix path replay correctly; the cause was never known, so captured calls take the per-matrix path.
   const bool capturing = mfma_ok && b >= kMfmaMinBatch && stream_is_capturing(stream);
   if (capturing) mfma_ok = false;
-  // a large batch: one matrix at a time (launch_gemm falls back to the slices where it has to)
+  // a large batch: all matrices in the launches of the one-pass kernel where every one of them takes it, else one matrix at a
+  // time (launch_gemm falls back to the slices where it has to)
   bool dense = !force_generic && prefill_has_instance(g);
   for (int i = 0; i < count && dense; ++i) dense = prefill_wanted(As[i], b);   // (prompt_wanted is a part of that)
-  if (dense) mfma_ok = false;
+  if (dense) {
+    bool one_pass = mfma_ok && prompt_set_wanted(As, count, b);
+    for (int i = 0; i < count && one_pass; ++i) one_pass = reinterpret_cast<uintptr_t>(Ys[i]) % 16 == 0;
+    if (one_pass) {
+      const hipError_t e = launch_prompt_scratch(As, count, X, b, Ys, y_dtype, stream, ws);
+      if (e != hipErrorNotSupported) return e;
+    }
+    mfma_ok = false;
+  }
   int k = 0;
   while (k < b) {
     const int left = b - k, nb16 = left < 16 ? left : 16;
@@ -136,9 +157,14 @@ size_t workspace_bound(const DevMatrix* As, int count, int b, bool with_dense_co
   if (with_dense_copy && prefill_has_instance(As[0].g))
     for (int i = 0; i < count; ++i) {
       if (!prefill_wanted(As[i], b)) continue;
-      const size_t need = prompt_wanted(As[i], b) ? prompt_workspace_bytes(As[i], b) : prefill_workspace_bytes(As[i], b);
-      if (need > worst) worst = need;
+      const bool one_pass = prompt_wanted(As[i], b);
+      if (one_pass) worst = std::max(worst, prompt_workspace_bytes(&As[i], 1, b));
+      if (!one_pass || prompt_reports_copy(As[i], b)) worst = std::max(worst, prefill_workspace_bytes(As[i], b));
     }
+  if (with_dense_copy && prompt_set_wanted(As, count, b)) {
+    const size_t need = prompt_workspace_bytes(As, count, b);
+    if (need > worst) worst = need;
+  }
   if (!mfma_has_instance(As[0].g) || b < kMfmaMinBatch) return worst;
   // slices of 16, then the rest: the needs of min(b, 16) vectors and of the last slice bound all of them
   const int sizes[2] = {b < 16 ? b : 16, b % 16};

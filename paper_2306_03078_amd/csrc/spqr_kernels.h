@@ -30,6 +30,7 @@ inline int current_device() {
 // library's own scratch, kept per stream (see spqr_mfma.hip).
 struct Workspace {
   bool from_caller = false;
+  bool fixed = false;             // the static array: its size is no choice of the caller's
   uint8_t* p = nullptr;
   size_t bytes = 0;
 };
@@ -81,14 +82,11 @@ hipError_t static_workspace(Workspace* ws);
 // that share a split's outliers.  Returns the units of the matrix.
 int plan_batch_hook(const DevMatrix* As, int count, int b, int* per, int* splits, int* shares);
 
-// The sums over the splits of partial results in the order the batch and prompt kernels write them.
-hipError_t launch_sum_groups(const Geometry& g, const float* P, int splits, int b, void* Y, int y_dtype, hipStream_t stream);
-
 // Prompt-sized batches (spqr_prompt.hip) and large batches through a dense binary16 copy of the matrix
 // (spqr_prefill.hip) on the library's scratch or the caller's workspace.  hipErrorNotSupported: no scratch of that size to
 // be had (or the stream is being captured and the library would have to allocate it): the caller takes the slices of 16.
-hipError_t launch_prompt_scratch(const DevMatrix& A, const uint16_t* X, int b, void* Y, int y_dtype, hipStream_t stream,
-                                 const Workspace& ws);
+hipError_t launch_prompt_scratch(const DevMatrix* As, int count, const uint16_t* X, int b, void* const* Ys, int y_dtype,
+                                 hipStream_t stream, const Workspace& ws);
 hipError_t launch_prefill_scratch(const DevMatrix& A, const uint16_t* X, int b, void* Y, int y_dtype, hipStream_t stream,
                                   const Workspace& ws);
 
@@ -105,10 +103,13 @@ hipError_t launch_gather_x(const uint16_t* X, const int32_t* perm, uint16_t* XP,
 // ---- spqr_prompt.hip: prompt-sized batches straight from the compressed weights ----
 bool prompt_has_instance(const DevMatrix& A);
 bool prompt_wanted(const DevMatrix& A, int b);
-size_t prompt_workspace_bytes(const DevMatrix& A, int b);
-// `scratch`: prompt_workspace_bytes(A, b) bytes, 256-byte aligned.
-hipError_t launch_prompt(const DevMatrix& A, const uint16_t* X, int b, void* Y, int y_dtype, hipStream_t stream,
-                         uint8_t* scratch);
+// Matrices that share X, the format and the permutation.
+// most_slots > 0: a plan with no more partial results of a group than that (0: the fastest).
+size_t prompt_workspace_bytes(const DevMatrix* As, int count, int b, int most_slots = 0);
+bool prompt_reports_copy(const DevMatrix& A, int b);
+// `scratch`: prompt_workspace_bytes(As, count, b, most_slots) bytes, 256-byte aligned; Ys 16-byte aligned.
+hipError_t launch_prompt(const DevMatrix* As, int count, const uint16_t* X, int b, void* const* Ys, int y_dtype, hipStream_t stream,
+                         uint8_t* scratch, int most_slots = 0);
 
 // ---- spqr_misc.hip: fallback product, debug decode, validation ----
 hipError_t launch_generic(const DevMatrix& A, const uint16_t* x, void* y, int y_dtype, hipStream_t stream);

@@ -498,7 +498,7 @@ __global__ void __launch_bounds__(256) sum_groups_fused_kernel(BatchFused F, int
   sum_groups_body(F.it[i].A.g, F.it[i].P, splits, batch, F.it[i].Y, y_dtype, bx);
 }
 
-hipError_t launch_sum_groups(const Geometry& g, const float* P, int splits, int b, void* Y, int y_dtype, hipStream_t stream) {
+static hipError_t launch_sum_groups(const Geometry& g, const float* P, int splits, int b, void* Y, int y_dtype, hipStream_t stream) {
   const int rows = 16 * lane_rows(g.tile_rows);
   hipLaunchKernelGGL(sum_groups_kernel, dim3((g.m + rows - 1) / rows, b), dim3(rows), 0, stream, g, P, splits, b, Y, y_dtype);
   return hipGetLastError();
@@ -920,10 +920,13 @@ static hipError_t on_scratch(const Workspace& ws, size_t need, hipStream_t strea
   return e == hipSuccess ? ef : e;
 }
 
-hipError_t launch_prompt_scratch(const DevMatrix& A, const uint16_t* X, int b, void* Y, int y_dtype, hipStream_t stream,
-                                 const Workspace& ws) {
-  return on_scratch(ws, prompt_workspace_bytes(A, b), stream,
-                    [&](uint8_t* p) { return launch_prompt(A, X, b, Y, y_dtype, stream, p); });
+hipError_t launch_prompt_scratch(const DevMatrix* As, int count, const uint16_t* X, int b, void* const* Ys, int y_dtype,
+                                 hipStream_t stream, const Workspace& ws) {
+  int most = 0;
+  size_t need = prompt_workspace_bytes(As, count, b);
+  // in the static array with fewer partial results, where the fastest plan's don't fit
+  for (int slots = 3; ws.fixed && need > ws.bytes && slots >= 1; --slots) need = prompt_workspace_bytes(As, count, b, most = slots);
+  return on_scratch(ws, need, stream, [&](uint8_t* p) { return launch_prompt(As, count, X, b, Ys, y_dtype, stream, p, most); });
 }
 
 hipError_t launch_prefill_scratch(const DevMatrix& A, const uint16_t* X, int b, void* Y, int y_dtype, hipStream_t stream,
@@ -955,6 +958,7 @@ hipError_t static_workspace(Workspace* ws) {
     ptr[dev] = static_cast<uint8_t*>(p);
   }
   ws->from_caller = true;
+  ws->fixed = true;
   ws->p = ptr[dev];
   ws->bytes = SPQR_STATIC_SCRATCH_BYTES;
   return hipSuccess;

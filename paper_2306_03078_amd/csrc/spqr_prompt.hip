@@ -1,8 +1,9 @@
 // Prompt-sized batches (the prompt phase of Sec. 5, "Inference Time"): one kernel from the compressed weights to the
 // products of up to 256 vectors.  Sec. 4.2 makes 16-bit weights first and then multiplies; here the 16-bit weights exist
-// only in LDS, a workgroup's block of columns at a time, outliers added, and the matrix cores read them from there, for 64,
-// 128 or (strips of 8 rows) 256 vectors; more vectors than that read and dequantise the weights once per that many.
+// only in LDS, a workgroup's block of columns at a time, outliers added, and the matrix cores read them from there, for 64 to
+// 192 vectors; more vectors than that read and dequantise the weights once per that many.
 #include <hip/hip_runtime.h>
+#include <algorithm>
 #include <cstdint>
 
 #include "../../include/spqr.h"
@@ -12,81 +13,147 @@
 
 namespace spqr {
 
-// ---------------------------------------------------------------------------
-// The outliers of a group of 16 strips, sorted by phase (8 columns of each of 16 tile columns, the block the multiplying
-// kernel has in LDS at a time): the group's range of `entries` becomes offs[group][phase] .. offs[group][phase + 1], each
-// entry its place in the block (16 bits) and its value.  A counting sort in two kernels over chunks of kSortChunk entries,
-// each with a slot of `counts` (spqr_sort.h).
-// ---------------------------------------------------------------------------
-constexpr int kSortPer = kSortChunk / 256, kSortMaxPhases = 512;
-constexpr int kSortWgs = 8;                  // workgroups per group; each takes every 8th chunk
+// A lane of the multiplying kernel takes 8 rows of a tile, of any height; a group is 16 such strips.
+constexpr int kLaneRows = 8, kGroupRows = 16 * kLaneRows;
 
-// Phase of a column: a unit of 16 tile columns (1 << unit_shift columns) has kg of them.
-__device__ __forceinline__ int phase_of(int col, int unit_shift, int kg) { return (col >> unit_shift) * kg + ((col >> 3) & (kg - 1)); }
+// Several matrices that share the batch X and the format in one grid (one: a set of one); blockIdx.x counts the groups of all
+// matrices.  Every workgroup does what it would do in a launch of its own matrix.
+struct PromptItem {
+  DevMatrix A;
+  void* Y;
+  uint32_t* counts;
+  int32_t* offs;                             // ranges of the sorted outliers
+  int entries0;                              // where the matrix's outliers begin in `entries`
+  int groups;
+};
+struct PromptSet {
+  uint32_t* entries;                         // sorted outliers of all matrices
+  float* P;                                  // partial results [slot][vector][128 places of a group, by group]
+  int count, groups;                         // matrices, groups of all of them
+  PromptItem it[SPQR_MAX_FUSED];
+};
+// The address of a pointer that the compiler can't see to be global memory (else its loads count as LDS operations too).
+template <typename V> __device__ __forceinline__ V* global_pointer(uint64_t address) {
+  return (V*)reinterpret_cast<__attribute__((address_space(1))) V*>(address);
+}
+__device__ __forceinline__ int find_item(const PromptSet& S, int& group) {   // workgroup-uniform
+  int i = 0;
+  for (; i < S.count - 1; ++i) {
+    if (group < S.it[i].groups) break;
+    group -= S.it[i].groups;
+  }
+  return i;
+}
 
-__global__ void __launch_bounds__(256)
-count_phases_kernel(DevMatrix A, int rows, int unit_shift, int kg, int phases, uint32_t* __restrict__ counts) {
-  __shared__ uint32_t hist[kSortMaxPhases];
-  const int tid = threadIdx.x, group = blockIdx.x;
-  const GroupRange range = group_range(A.row_ptr, group, rows, A.g.m, (int)A.nnz);
+// ---------------------------------------------------------------------------
+// The outliers of a group of 16 strips, sorted by the wavefront that dequantises them and by when it does: a phase is 8
+// columns of each of the 16 tile columns of a unit, a bin the 4 tile columns of it that one wavefront takes.  The group's
+// range of `entries` becomes offs[group][bin] .. offs[group][bin + 1], each entry its place in the phase's block of operands
+// (16 bits) and its value.  A counting sort in two kernels over chunks of kSortChunk entries, each with a slot of `counts`
+// (spqr_sort.h).
+// ---------------------------------------------------------------------------
+constexpr int kSortThreads = 1024, kSortPer = kSortChunk / kSortThreads, kSortMaxPhases = 512, kSortMaxBins = 4 * kSortMaxPhases;
+constexpr int kSortWgs = 4;                  // workgroups per group; each takes every 4th chunk
+
+// Bin of a column: a unit of 16 tile columns (1 << unit_shift columns) has kg phases of 4 bins.
+__device__ __forceinline__ int bin_of(int col, int unit_shift, int kg) {
+  const int tt = (col >> (unit_shift - 4)) & 15;
+  return ((col >> unit_shift) * kg + ((col >> 3) & (kg - 1))) * 4 + (tt >> 2);
+}
+
+// The batch as operands: XS[phase][wavefront of the tile column][16 vectors][lane], 16 bytes a lane (8 columns of a vector:
+// lane 16 g4 + i holds vector i and tile column g4 of the wavefront's four), zeros behind the last tile column and vector.
+// A load of an operand is then one run of 1 KB, 16 clocks of the vector cache; from X itself it is a line per lane, 64 of them.
+__device__ __forceinline__ void order_x(const uint16_t* __restrict__ X, int batch, int n, int tile_cols, int kg, int blocks16, int at,
+                                        u32x4* __restrict__ XS) {
+  const int lane = at & 63, i16 = lane & 15, g4 = lane >> 4;
+  int k = at >> 6;
+  const int v = 16 * (k % blocks16) + i16;
+  k /= blocks16;
+  const int s = k & 3, ph = k >> 2, u = ph / kg, j = ph % kg, col = (kUnitTiles * u + 4 * s + g4) * tile_cols + 8 * j;
+  XS[at] = v < batch && col < n ? *reinterpret_cast<const u32x4*>(X + (int64_t)v * n + col) : u32x4{0u, 0u, 0u, 0u};
+}
+
+// Workgroups of groups * kSortWgs and more order the batch, the others count.
+__global__ void __launch_bounds__(kSortThreads)
+count_phases_kernel(PromptSet S, int groups, int unit_shift, int kg, int bins, const uint16_t* __restrict__ X, int batch,
+                    int blocks16, u32x4* __restrict__ XS) {
+  __shared__ uint32_t hist[kSortMaxBins];
+  if ((int)blockIdx.x >= groups * kSortWgs) {
+    const int at = ((int)blockIdx.x - groups * kSortWgs) * kSortThreads + (int)threadIdx.x;
+    if (at < bins * blocks16 * 64) order_x(X, batch, S.it[0].A.g.n, S.it[0].A.g.tile_cols, kg, blocks16, at, XS);
+    return;
+  }
+  int group = blockIdx.x / kSortWgs;
+  const PromptItem& it = S.it[find_item(S, group)];
+  const DevMatrix& A = it.A;
+  if (A.nnz == 0) return;                    // workgroup-uniform
+  const int tid = threadIdx.x;
+  const GroupRange range = group_range(A.row_ptr, group, kGroupRows, A.g.m, (int)A.nnz);
   const int s = range.s, z = range.z;
-  for (int k = blockIdx.y; s + kSortChunk * k < z; k += kSortWgs) {          // workgroup-uniform
-    for (int u = tid; u < phases; u += 256) hist[u] = 0;
+  for (int k = blockIdx.x % kSortWgs; s + kSortChunk * k < z; k += kSortWgs) {   // workgroup-uniform
+    for (int u = tid; u < bins; u += kSortThreads) hist[u] = 0;
     __syncthreads();
     uint16_t c[kSortPer];
 #pragma unroll
-    for (int i = 0; i < kSortPer; ++i) c[i] = A.col[(uint32_t)min(s + kSortChunk * k + tid + 256 * i, z - 1)];
+    for (int i = 0; i < kSortPer; ++i) c[i] = A.col[(uint32_t)min(s + kSortChunk * k + tid + kSortThreads * i, z - 1)];
 #pragma unroll
     for (int i = 0; i < kSortPer; ++i)
-      if (s + kSortChunk * k + tid + 256 * i < z) atomicAdd(&hist[phase_of(min((int)c[i], A.g.n - 1), unit_shift, kg)], 1u);
+      if (s + kSortChunk * k + tid + kSortThreads * i < z) atomicAdd(&hist[bin_of(min((int)c[i], A.g.n - 1), unit_shift, kg)], 1u);
     __syncthreads();
-    uint32_t* out = counts + count_slot(range, group, k) * phases;
-    for (int u = tid; u < phases; u += 256) out[u] = hist[u];
+    uint32_t* out = it.counts + count_slot(range, group, k) * bins;
+    for (int u = tid; u < bins; u += kSortThreads) out[u] = hist[u];
     __syncthreads();
   }
 }
 
-// LR: rows per strip of the multiplying kernel.
-template <int LR>
-__global__ void __launch_bounds__(256)
-sort_phases_kernel(DevMatrix A, int unit_shift, int kg, int phases, const uint32_t* __restrict__ counts, int32_t* __restrict__ offs,
-                  uint32_t* __restrict__ entries) {
-  constexpr int ROWS = 16 * LR;
+// PB: bins a thread adds up.
+template <int PB>
+__global__ void __launch_bounds__(kSortThreads)
+sort_phases_kernel(PromptSet S, int unit_shift, int kg, int bins) {
+  constexpr int LR = kLaneRows, ROWS = kGroupRows;
   __shared__ int rp[ROWS + 1];
-  __shared__ int start[kSortMaxPhases];      // this chunk's next free place, by phase
-  __shared__ int wave_sum[4];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, group = blockIdx.x, m = A.g.m;
+  __shared__ int start[kSortThreads * PB];            // this chunk's next free place, by bin
+  __shared__ int wave_sum[kSortThreads / 64];
+  int group = blockIdx.x;
+  const PromptItem& it = S.it[find_item(S, group)];
+  const DevMatrix& A = it.A;
+  if (A.nnz == 0) return;                    // workgroup-uniform
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, m = A.g.m;
   const GroupRange range = group_range(A.row_ptr, group, ROWS, m, (int)A.nnz);
   const int s = range.s, z = range.z, chunks = sort_chunks(range);
-  const uint32_t* in = counts + count_slot(range, group, 0) * phases;
+  const uint32_t* in = it.counts + count_slot(range, group, 0) * bins;
+  int32_t* offs = it.offs + (int64_t)group * (bins + 1);
   for (int k = blockIdx.y; k < max(chunks, 1); k += kSortWgs) {              // workgroup-uniform
     // the chunk's entries and the row pointers are on their way while the places are worked out
     uint16_t c[kSortPer], v[kSortPer];
     if (chunks > 0) {
 #pragma unroll
       for (int i = 0; i < kSortPer; ++i) {
-        const uint32_t e = (uint32_t)min(s + kSortChunk * k + tid + 256 * i, z - 1);
+        const uint32_t e = (uint32_t)min(s + kSortChunk * k + tid + kSortThreads * i, z - 1);
         c[i] = A.col[e];
         v[i] = A.val[e];
       }
     }
     if (k == (int)blockIdx.y)
-      for (int r = tid; r <= ROWS; r += 256) rp[r] = A.row_ptr[min(group * ROWS + r, m)];
-    // entries of the group per phase (2 tid, 2 tid + 1), and how many of them earlier chunks hold
-    int total[2] = {0, 0}, before[2] = {0, 0};
+      for (int r = tid; r <= ROWS; r += kSortThreads) rp[r] = A.row_ptr[min(group * ROWS + r, m)];
+    // entries of the group in the thread's bins, and how many of them earlier chunks hold
+    int total[PB], before[PB], sum = 0;
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      const int u = 2 * tid + h;
-      if (u < phases) {
+    for (int h = 0; h < PB; ++h) {
+      const int u = PB * tid + h;
+      total[h] = before[h] = 0;
+      if (u < bins) {
 #pragma unroll 4
         for (int q = 0; q < chunks; ++q) {
-          const int n = (int)in[(int64_t)q * phases + u];
+          const int n = (int)in[(int64_t)q * bins + u];
           total[h] += n;
           before[h] += q < k ? n : 0;
         }
       }
+      sum += total[h];
     }
-    int sum = total[0] + total[1];           // inclusive sum over the threads
+    const int own = sum;                     // inclusive sum over the threads
 #pragma unroll
     for (int off = 1; off < 64; off <<= 1) {
       const int up = __shfl_up(sum, off, 64);
@@ -95,33 +162,31 @@ sort_phases_kernel(DevMatrix A, int unit_shift, int kg, int phases, const uint32
     if (lane == 63) wave_sum[wave] = sum;
     __syncthreads();
 #pragma unroll
-    for (int w = 0; w < 3; ++w) sum += w < wave ? wave_sum[w] : 0;
-    // (no further than z, also where broken row pointers let groups share slots)
-    const int first[2] = {min(s + sum - total[0] - total[1], z), min(s + sum - total[1], z)};
+    for (int w = 0; w < kSortThreads / 64 - 1; ++w) sum += w < wave ? wave_sum[w] : 0;
+    int first = s + sum - own;
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      const int u = 2 * tid + h;
-      start[u] = first[h] + before[h];
-      if (k == 0) {
-        if (u < phases) offs[(int64_t)group * (phases + 1) + u] = first[h];
-        if (u == 0) offs[(int64_t)group * (phases + 1) + phases] = z;
-      }
+    for (int h = 0; h < PB; ++h) {
+      const int u = PB * tid + h, at = min(first, z);      // (no further than z, also where broken row pointers let groups share slots)
+      start[u] = at + before[h];
+      if (k == 0 && u < bins) offs[u] = at;
+      first += total[h];
     }
+    if (k == 0 && tid == 0) offs[bins] = z;
     __syncthreads();
     if (chunks > 0) {
 #pragma unroll
       for (int i = 0; i < kSortPer; ++i) {
-        const int e = s + kSortChunk * k + tid + 256 * i;
+        const int e = s + kSortChunk * k + tid + kSortThreads * i;
         if (e >= z) continue;
         int lo = 0;                          // the last row that starts at or before e
 #pragma unroll
         for (int step = ROWS / 2; step > 0; step >>= 1) lo += rp[lo + step] <= e ? step : 0;
         const int col = min((int)c[i], A.g.n - 1);
-        const int at = atomicAdd(&start[phase_of(col, unit_shift, kg)], 1);
+        const int at = atomicAdd(&start[bin_of(col, unit_shift, kg)], 1);
         // tile column of the unit 4 s + g4, place ((s * LR + row) * 64 + g4 * 16 + strip) * 8 + column of the 8
         const int tt = (col & ((1 << unit_shift) - 1)) >> (unit_shift - 4);
         const uint32_t pos = (uint32_t)((((tt >> 2) * LR + lo % LR) * 64 + (tt & 3) * 16 + lo / LR) * 8 + (col & 7));
-        entries[min(max(at, s), z - 1)] = pos | ((uint32_t)v[i] << 16);
+        S.entries[it.entries0 + min(max(at, s), z - 1)] = pos | ((uint32_t)v[i] << 16);
       }
     }
     __syncthreads();
@@ -129,191 +194,249 @@ sort_phases_kernel(DevMatrix A, int unit_shift, int kg, int phases, const uint32
 }
 
 // ---------------------------------------------------------------------------
-// P[split][vector][rows] = X . W_hat^T for 64 * NVB vectors per blockIdx.z (see the batch kernel for the layout of the operands: a lane
-// holds a tile, 16 lanes the same tile column of 16 strips, row r of the strips is an operand).  A workgroup of 4
-// wavefronts owns a group of 16 strips (256 or 128 rows) and 64 * NVB vectors; a phase is 8 columns of each of the 16 tile
-// columns of a unit.  Wavefront w dequantises 4 of the tile columns and leaves its operands in LDS, in the order they
-// will be read (16 bytes per lane, no bank conflict); the outliers of the phase are added there; then every wavefront
-// multiplies all of them with its own 16 * NVB vectors, whose operands come from X (L2) one phase ahead.  Two buffers: the
-// next phase is dequantised between the multiplications of this one, so vector issue hides behind the matrix cores.
-// One wavefront per SIMD and one workgroup per CU (64 x NVB sums a lane with strips of 16 rows, 128.5 KB of LDS; half of
-// both with strips of 8): a dequantised weight is used for 64 * NVB vectors, an operand read from LDS for NVB
-// multiplications.
+// P = X . W_hat^T for 16 * NVB * 4 / RW vectors per blockIdx.y (see the batch kernel for the layout of the operands: a lane
+// holds 8 rows of a tile, 16 lanes the same tile column of 16 strips, row r of the strips is an operand).  The units of all
+// groups of 16 strips stand in one row, group by group, and a workgroup of 4 wavefronts takes `run` of them, whatever groups
+// they belong to: as many workgroups as the chip holds, all of one length.  A phase is 8 columns of each of the 16 tile columns
+// of a unit.  Wavefront w dequantises 4 of the tile columns, leaves its operands in LDS, in the order they will be read (16
+// bytes per lane, no bank conflict), and adds its outliers there; meanwhile all 4 multiply the phase before, each 8 / RW rows
+// of every strip with its own 16 * NVB vectors.  Two buffers, one barrier a phase, two workgroups on a CU.
 //
-// What bounds it: issue and LDS.  A phase with strips of 16 rows and 128 vectors is 128 matrix instructions (2048
-// clocks), 530 vector ones and 90 LDS operations per wavefront with its outliers, 256 KB read from LDS per workgroup (2048
-// clocks), and takes 2.3 us, of which the outliers' two barriers and round trip are a part (17920 x 6656, 256 vectors:
-// vector issue 35 % of a wavefront's time, the matrix cores 26 %).  Measured (with the sort and the sums, 19 and 17 us of
-// the 161): 17920 x 6656, 4-bit, 256 vectors 240 -> 161 us (380 TFLOP/s), 128 vectors 173 -> 95 us; gate and up 11008 x
-// 4096, 3-bit, 77 vectors 149 -> 101 us.  Before, the weights went through a dense binary16 copy in memory (70 us of writing it, 30 us
-// of adding the outliers there, 137 us of multiplying at 256 vectors).
+// Why so.  Vector instructions and matrix ones share a SIMD's issue (one of 16 x 16 x 32 costs 8 clocks of it and the matrix
+// core 16, a vector one 4 to 5): a phase of 128 rows and 128 vectors is 64 and 215 of them per wavefront, 1.5 k clocks a SIMD,
+// so the dequantisation and the multiplications are spread between each other, and 8 rows a lane instead of 16 leave the
+// registers and the LDS (65 KB) for a second workgroup, whose wavefronts run where this one's wait at the barrier.  A whole
+// row of units instead of a grid of groups times splits: 17920 x 6656 is 140 groups of 26 units, which no number of splits
+// deals evenly to 256 CUs.
+// Measured (the whole call with the sort, 28 and 18 us, and the sums, 10 and 5; before: groups of 256 rows, one workgroup of one
+// wavefront per SIMD, a matrix at a time): 17920 x 6656, 4-bit, 256 vectors 162 -> 124 us; gate and up 11008 x 4096, 3-bit, 77
+// vectors 101 -> 63; 4096^2 at 128 vectors, which the dense copy took, 38 -> 33.
 // ---------------------------------------------------------------------------
-template <int W, int TR, int TC, int AXIS, int NVB>
-__global__ void __launch_bounds__(256, 1)
-prompt_group_kernel(DevMatrix A, const uint16_t* __restrict__ X, int batch, float* __restrict__ P, int units_per_split,
-                    const uint32_t* __restrict__ entries, const int32_t* __restrict__ offs) {
-  using DQ = Dequant<W, TR, TC, AXIS>;
-  using B = BatchTile<W, TR, TC, AXIS>;
+template <int W, int TR, int TC, int AXIS, int RW, int NVB>
+__global__ void __launch_bounds__(256, 2)
+prompt_group_kernel(PromptSet S, const u32x4* __restrict__ XS, int batch, int blocks16, int run) {
+  constexpr int LR = kLaneRows, ROWS = kGroupRows;
+  using DQ = Dequant<W, TR, TC, AXIS, LR>;
+  using B = BatchTile<W, TR, TC, AXIS, LR>;
   using T = typename B::T;
-  constexpr int TILE_BYTES = 16 * T::KW + 4 * T::SD, LR = DQ::LR, NSUB = DQ::NSUB, KG = DQ::KG, ROWS = 16 * LR;
-  constexpr int STRIPS = 16 / NSUB, PHASE = 4 * LR * 1024, AHEAD = 4, LAST = KG - 1;
-  extern __shared__ __align__(16) uint8_t smem[];            // two buffers of PHASE bytes, 2 bytes nobody reads per thread
+  constexpr int TILE_BYTES = 16 * T::KW + 4 * T::SD, NSUB = DQ::NSUB, KG = DQ::KG;
+  constexpr int STRIPS = 16 / NSUB, PHASE = 4 * LR * 1024, AHEAD = 2, LAST = KG - 1, PAIRS = 4 * LR;
+  constexpr int VW = 4 / RW, RB = LR / RW, N = 4 * RB, DQN = 3 * N / 4, RING = 3;
+  constexpr int XD = NVB >= 3 ? 2 : 4;       // buffers of operands of X
+  extern __shared__ __align__(16) uint8_t smem[];            // two buffers of PHASE bytes
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int i16 = lane & 15, g4 = lane >> 4, group = blockIdx.x;
-  const int n = A.g.n, ntc = A.g.ntc, ntr = A.g.ntr * NSUB, m = A.g.m;
-  const int units = (ntc + kUnitTiles - 1) / kUnitTiles;
-  const int u_lo = blockIdx.y * units_per_split, u_hi = min(units, u_lo + units_per_split);   // never empty (host)
-  const bool sparse = A.nnz > 0;
-  const int32_t* off = offs + (int64_t)group * (units * KG + 1);
+  const int rw = wave / VW, vw = wave % VW, i16 = lane & 15, g4 = lane >> 4;
+  const int ntc = S.it[0].A.g.ntc, units = (ntc + kUnitTiles - 1) / kUnitTiles;
+  const int lo = blockIdx.x * run, hi = min(S.groups * units, lo + run);   // never empty (host)
+  DQ dq(i16 % NSUB);
 
-  const uint8_t* base = A.packed + (int64_t)group * STRIPS * ntc * TILE_BYTES;
-  const int my_strip = min(group * 16 + i16, ntr - 1) - group * 16, half = NSUB == 2 ? my_strip & 1 : 0;
-  const uint32_t strip_off = (uint32_t)(my_strip / NSUB) * (uint32_t)ntc * TILE_BYTES;
-  const int vec0 = (blockIdx.z * 4 + wave) * 16 * NVB;
-  uint32_t xrow[NVB];
-#pragma unroll
-  for (int vb = 0; vb < NVB; ++vb) xrow[vb] = (uint32_t)min(vec0 + 16 * vb + i16, batch - 1) * (uint32_t)n * 2u;
-  DQ dq(half);
-
-  float4_t D[LR][NVB];
-#pragma unroll
-  for (int r = 0; r < LR; ++r)
-#pragma unroll
-    for (int vb = 0; vb < NVB; ++vb) D[r][vb] = float4_t{0.f, 0.f, 0.f, 0.f};
-
-  auto load_unit = [&](B& t, int u) {        // behind the range every lane reads the group's first tile
-    const bool real = u < u_hi;
-    const int t0 = min(kUnitTiles * u + 4 * wave, (ntc - 1) & ~3), blk = t0 >> 6, L = min(64, ntc - 64 * blk);
-    const uint32_t l = real ? (uint32_t)(min(t0 + g4, ntc - 1) - 64 * blk) : 0u;
-    load_batch_tile(t, base + (real ? (int64_t)64 * blk * TILE_BYTES : 0), real ? L : 1, real ? strip_off : 0u, l, half);
+  // The unit whose tiles are loaded next: its group there and what the matrix is, all of it workgroup-uniform.  The matrices
+  // wait in LDS: a scalar load in the loop, even one that is hardly ever taken, makes every wait for LDS one for all of it.
+  int4* items = reinterpret_cast<int4*>(smem + 2 * PHASE + 512);
+  if (tid < SPQR_MAX_FUSED) {
+    const PromptItem& it = S.it[min(tid, S.count - 1)];
+    const uint64_t packed = reinterpret_cast<uint64_t>(it.A.packed);
+    items[tid] = make_int4((int)(uint32_t)packed, (int)(uint32_t)(packed >> 32), it.A.g.ntr, it.groups);
+  }
+  __syncthreads();
+  int ld_group = lo / units, ld_unit = lo % units, ld_left = hi - lo;
+  int ld_item = find_item(S, ld_group);
+  const uint32_t row_bytes = (uint32_t)ntc * TILE_BYTES;
+  B t;
+  auto load_unit = [&]() {                   // rows and columns behind the matrix: its last ones
+    const int4 item = items[ld_item];
+    const uint64_t packed = (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane(item.x) | ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane(item.y) << 32);
+    const int strips = __builtin_amdgcn_readfirstlane(item.z) - ld_group * STRIPS;
+    const int t0 = min(kUnitTiles * ld_unit + 4 * wave, (ntc - 1) & ~3), blk = t0 >> 6, L = min(64, ntc - 64 * blk);
+    const uint8_t* base = global_pointer<const uint8_t>(packed) + (int64_t)ld_group * STRIPS * row_bytes + (int64_t)64 * blk * TILE_BYTES;
+    load_batch_tile(t, base, L, (uint32_t)min(i16 / NSUB, strips - 1) * row_bytes, (uint32_t)(min(t0 + g4, ntc - 1) - 64 * blk), i16 % NSUB);
+    --ld_left;                               // behind the last unit of the run: that one again, which nobody multiplies
+    const int unit = ld_unit + (ld_left > 0 ? 1 : 0), group = ld_group + (unit == units ? 1 : 0);
+    const bool last = group == __builtin_amdgcn_readfirstlane(item.w);
+    ld_unit = unit == units ? 0 : unit;
+    ld_group = last ? 0 : group;
+    ld_item += last ? 1 : 0;
   };
-  u32x4 xb[4][NVB];                          // the operands of X of a phase, by the wavefront that dequantised the tiles
-  auto load_x = [&](int u, int j, int s) {
-    const int tl = min(kUnitTiles * u + 4 * s + g4, ntc - 1);
-    const uint32_t at = (uint32_t)tl * (TC * 2) + 16u * j;
+  u32x4 xb[XD][NVB];                         // operands of X by the wavefront that dequantised the tiles, XD - 1 steps ahead
+  auto load_x = [&](int ph, int s) {         // ph: phase of the matrix, s its wavefront
+    const u32x4* from = XS + ((int64_t)(4 * ph + s) * blocks16 + (blockIdx.y * VW + vw) * NVB) * 64;   // uniform
 #pragma unroll
-    for (int vb = 0; vb < NVB; ++vb) xb[s][vb] = *reinterpret_cast<const u32x4*>(reinterpret_cast<const uint8_t*>(X) + (xrow[vb] + at));
+    for (int vb = 0; vb < NVB; ++vb) xb[s % XD][vb] = from[64 * vb + lane];
   };
-  // The outliers of the phase being dequantised: the first AHEAD per thread are requested a phase ahead.  They are added
-  // AHEAD at a time, reads first; one that does not exist goes to the thread's own spare place.
+  // The wavefront's outliers of a phase: the first AHEAD per lane are requested a phase ahead, whether there are any or not
+  // (the compiler waits for what the longest path to a place may have requested, so no load of the loop is behind a branch;
+  // the ranges wait in LDS for the same reason).
+  const int phases = (hi - lo) * KG;
+  int2* ranges = reinterpret_cast<int2*>(smem + 2 * PHASE + 512 + 16 * SPQR_MAX_FUSED);          // of this workgroup's bins, and an empty one
   int o0 = 0, o1 = 0;
   uint32_t ent[AHEAD];
-  const uint32_t spare = PHASE + tid;        // in halves, from the start of the LDS
   auto fetch_outliers = [&](int from) {
 #pragma unroll
-    for (int k = 0; k < AHEAD; ++k) ent[k] = entries[(uint32_t)min(from + tid + 256 * k, o1 - 1)];
+    for (int k = 0; k < AHEAD; ++k) ent[k] = S.entries[(uint32_t)max(min(from + lane + 64 * k, o1 - 1), 0)];
   };
-  int off_v = 0;                             // lane l: where phase l of the current 32 begins
-  auto load_outliers = [&](int u, int j) {
-    o0 = o1 = 0;
-    if (sparse && u < u_hi) {                // workgroup-uniform
-      const int ph = (u - u_lo) * KG + j;
-      if ((ph & 31) == 0) off_v = off[min(u * KG + j + lane, units * KG)];
-      o0 = __builtin_amdgcn_readlane(off_v, ph & 31);
-      o1 = __builtin_amdgcn_readlane(off_v, (ph & 31) + 1);
-      if (o0 < o1) fetch_outliers(o0);
+  auto load_outliers = [&](int ph) {         // behind the last phase: none
+    const int2 r = ranges[min(ph * 4 + wave, phases * 4)];
+    o0 = __builtin_amdgcn_readfirstlane(r.x);
+    o1 = __builtin_amdgcn_readfirstlane(r.y);
+    fetch_outliers(o0);
+  };
+  uint32_t at[AHEAD];
+  uint16_t w16[AHEAD];
+  const uint32_t spare = 2 * PHASE + 2 * tid;                // where a lane without an outlier reads and writes
+  auto read_places = [&](uint32_t buf, int from) {           // every position at most once: no two lanes meet
+#pragma unroll
+    for (int k = 0; k < AHEAD; ++k) {
+      at[k] = from + 64 * k + lane < o1 ? buf + 2 * (ent[k] & (PHASE / 2 - 1)) : spare;   // (a place is below PHASE / 2)
+      w16[k] = *reinterpret_cast<const uint16_t*>(smem + at[k]);
     }
   };
-  auto add_outliers = [&](uint8_t* buf) {    // every position at most once: no two threads meet
-    __syncthreads();
-    if (o0 >= o1) return;                    // workgroup-uniform
-    uint16_t* all = reinterpret_cast<uint16_t*>(smem);
-    const uint32_t at0 = (uint32_t)(buf - smem) / 2;
-    for (int from = o0;;) {
-      uint32_t at[AHEAD];
-      uint16_t w[AHEAD];
+  auto write_places = [&]() {
 #pragma unroll
-      for (int k = 0; k < AHEAD; ++k) {
-        at[k] = from + tid + 256 * k < o1 ? at0 + (ent[k] & (PHASE / 2 - 1)) : spare;   // (a place is below PHASE / 2)
-        w[k] = all[at[k]];
-      }
-#pragma unroll
-      for (int k = 0; k < AHEAD; ++k) all[at[k]] = f2h_rne(h2f(w[k]) + h2f((uint16_t)(ent[k] >> 16)));
-      if ((from += 256 * AHEAD) >= o1) break;
+    for (int k = 0; k < AHEAD; ++k) *reinterpret_cast<uint16_t*>(smem + at[k]) = f2h_rne(h2f(w16[k]) + h2f((uint16_t)(ent[k] >> 16)));
+  };
+  auto add_rest = [&](uint32_t buf) {        // those behind the first 64 * AHEAD
+    for (int from = o0 + 64 * AHEAD; from < o1; from += 64 * AHEAD) {
       fetch_outliers(from);
+      read_places(buf, from);
+      write_places();
     }
-    __syncthreads();
   };
+  // (a lane's address in a buffer and constants: the LDS instructions hold those)
+  const uint32_t to_write = (uint32_t)(wave * LR * 64 + lane) * 16, to_read = (uint32_t)(rw * RB * 64 + lane) * 16;
 
-  B t, tn;
-  load_unit(t, u_lo);
-  load_outliers(u_lo, 0);
-  load_unit(tn, u_lo + 1);
+  int gg = lo / units, u = lo % units;       // group of all and unit of it that is multiplied
+  load_unit();
 #pragma unroll
-  for (int s = 0; s < 4; ++s) load_x(u_lo, 0, s);
-  uint8_t *cur = smem, *nxt = smem + PHASE;
-  dq.begin(t, kUnitTiles * u_lo + 4 * wave + g4 < ntc);
+  for (int s = 0; s < XD - 1; ++s) load_x(u * KG, s);
+  if (tid < 64) reinterpret_cast<uint64_t*>(smem + 2 * PHASE)[tid] = 0;
+  for (int k = tid; k <= 4 * phases; k += 256) {
+    int2 r = {0, 0};
+    int group = (lo + k / (4 * KG)) / units;
+    const int bin = (lo + k / (4 * KG)) % units * (4 * KG) + k % (4 * KG);
+    if (k < 4 * phases) {
+      int i = 0;
+      for (; i < S.count - 1 && group >= S.it[i].groups; ++i) group -= S.it[i].groups;
+      const PromptItem& it = S.it[i];
+      if (it.A.nnz > 0) {
+        const int32_t* off = it.offs + (int64_t)group * (units * KG * 4 + 1) + bin;
+        r = make_int2(it.entries0 + off[0], it.entries0 + off[1]);
+      }
+    }
+    ranges[k] = r;
+  }
+  uint32_t cur = 0;                          // which buffer is read
+  dq.begin(t, kUnitTiles * u + 4 * wave + g4 < ntc);
   dq.columns(t, 0);
 #pragma unroll
-  for (int r = 0; r < LR; ++r) *reinterpret_cast<half8_t*>(cur + ((wave * LR + r) * 64 + lane) * 16) = dq.operand(t, r, 0);
-  add_outliers(cur);
+  for (int r = 0; r < LR; ++r) *reinterpret_cast<half8_t*>(smem + to_write + 1024 * r) = dq.operand(t, r, 0);
+  __syncthreads();                           // the ranges
+  load_outliers(0);
+  read_places(0, o0);
+  write_places();
+  add_rest(0);
+  if (LAST == 0) load_unit();
+  load_outliers(1);
+  __syncthreads();
 
-  for (int u = u_lo; u < u_hi; ++u) {        // workgroup-uniform
+  for (int at_unit = lo; at_unit < hi; ++gg) {               // groups; workgroup-uniform
+  float4_t D[RB][NVB];
+#pragma unroll
+  for (int r = 0; r < RB; ++r)
+#pragma unroll
+    for (int vb = 0; vb < NVB; ++vb) D[r][vb] = float4_t{0.f, 0.f, 0.f, 0.f};
+  const int end = min(hi, (gg + 1) * units);
+  for (; at_unit < end; ++at_unit) {
+    const int next_u = u + 1 < units ? u + 1 : 0;
 #pragma unroll
     for (int j = 0; j < KG; ++j) {
-      const int nj = j == LAST ? 0 : j + 1, nu = j == LAST ? u + 1 : u;
-      load_outliers(nu, nj);
-      if (j == LAST) {                       // on to the next unit's tile; the one after it is requested
-        t = tn;
-        load_unit(tn, u + 2);
-        dq.begin(t, kUnitTiles * nu + 4 * wave + g4 < ntc);
-      }
+      const int nj = j == LAST ? 0 : j + 1, next_ph = j == LAST ? next_u * KG : u * KG + nj;
+      if (nj == 0) dq.begin(t, kUnitTiles * next_u + 4 * wave + g4 < ntc);   // on to the next unit's tile
       dq.columns(t, nj);
-      if (kUnitTiles * (u + 1) > ntc) {      // columns behind the last tile: zeros (finite), they meet zero weights
-#pragma unroll
-        for (int s = 0; s < 4; ++s)
-#pragma unroll
-          for (int vb = 0; vb < NVB; ++vb)
-            if (kUnitTiles * u + 4 * s + g4 >= ntc) xb[s][vb] = u32x4{0u, 0u, 0u, 0u};
-      }
-      // Operand i of the phase: row i % LR of the tiles of wavefront i / LR.  It is read three multiplications ahead, and a
-      // quarter of an operand of the next phase is dequantised beside each: the order here is the order of issue.
-      auto read_operand = [&](int i) { return *reinterpret_cast<const u32x4*>(cur + (i * 64 + lane) * 16); };
-      constexpr int N = 4 * LR, RING = 4;
+      // Operand i of the phase: row i % RB of the wavefront's rows, tiles of wavefront i / RB.
+      const uint8_t* from = smem + cur + to_read;
+      const uint32_t nxt = cur ^ PHASE;
+      uint8_t* to = smem + nxt + to_write;
+      auto read_operand = [&](int i) { return *reinterpret_cast<const u32x4*>(from + ((i / RB) * LR + i % RB) * 1024); };
       u32x4 a[RING], w = {};
-      auto dequant = [&](int q) {
-        w[q % 4] = dq.pair(t, q / 4, nj, q % 4);
-        if (q % 4 == 3) *reinterpret_cast<u32x4*>(nxt + ((wave * LR + q / 4) * 64 + lane) * 16) = w;
-      };
 #pragma unroll
       for (int i = 0; i < RING - 1; ++i) a[i] = read_operand(i);
 #pragma unroll
       for (int i = 0; i < N; ++i) {
-        const int s = i / LR, r = i % LR;
+        const int s = i / RB, r = i % RB;
         if (i + RING - 1 < N) a[(i + RING - 1) % RING] = read_operand(i + RING - 1);
-        dequant(i);
+        if (r == 0) {
+          if (s + XD - 1 < 4) load_x(u * KG + j, s + XD - 1);
+          else load_x(next_ph, s + XD - 5);
+        }
+        if (i < DQN) {                       // the next phase's weights, a few beside each multiplication
+#pragma unroll
+          for (int q = PAIRS * i / DQN; q < PAIRS * (i + 1) / DQN; ++q) {
+            w[q % 4] = dq.pair(t, q / 4, nj, q % 4);
+            if (q % 4 == 3) *reinterpret_cast<u32x4*>(to + 1024 * (q / 4)) = w;
+          }
+        }
+        if (i == DQN) read_places(nxt, o0);
+        if (i == DQN + 1 && nj == LAST) load_unit();
+        if (i == DQN + 2) write_places();
 #pragma unroll
         for (int vb = 0; vb < NVB; ++vb)
           D[r][vb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(half8_t, a[i % RING]),
-                                                            __builtin_bit_cast(half8_t, xb[s][vb]), D[r][vb], 0, 0, 0);
-        if (r == LR - 1) load_x(min(nu, units - 1), nj, s);
+                                                            __builtin_bit_cast(half8_t, xb[s % XD][vb]), D[r][vb], 0, 0, 0);
         __builtin_amdgcn_sched_barrier(0);
       }
-      add_outliers(nxt);
-      uint8_t* swap = cur;
+      add_rest(nxt);
+      load_outliers((at_unit - lo) * KG + j + 2);
+      __syncthreads();
       cur = nxt;
-      nxt = swap;
     }
+    u = next_u;
   }
-
-  // partial results of a group: [vector][row of the strip][strip], see sum_groups_kernel
-  const int strips = min(16, ntr - group * 16);
-  float* out0 = P + (int64_t)blockIdx.y * batch * m + (int64_t)batch * group * ROWS;
+  // the end of a group or of the run: partial results, place 16 r + strip of the group, see sum_phases_kernel
+  const int slot = blockIdx.x - (uint32_t)(gg * units) / (uint32_t)run;
+  const int64_t mp = (int64_t)S.groups * ROWS;
+  int l = lane;
+  asm volatile("" : "+v"(l));                // (the addresses are made here, not kept in registers throughout)
 #pragma unroll
   for (int vb = 0; vb < NVB; ++vb) {
-    const int v = vec0 + 16 * vb + i16;
-    if (v >= batch) continue;
-    float* out = out0 + (int64_t)v * (strips * LR);
-    if (strips == 16) {                      // 16-byte stores: m is a multiple of 8
+    const int v = ((blockIdx.y * VW + vw) * NVB + vb) * 16 + (l & 15);
+    float* out = S.P + ((int64_t)slot * batch + v) * mp + (int64_t)gg * ROWS + 4 * (l >> 4);
+    if (v < batch) {
 #pragma unroll
-      for (int r = 0; r < LR; ++r) *reinterpret_cast<float4_t*>(out + 16 * r + 4 * g4) = D[r][vb];
-    } else {
-#pragma unroll
-      for (int r = 0; r < LR; ++r)
-#pragma unroll
-        for (int k = 0; k < 4; ++k)
-          if (4 * g4 + k < strips) out[strips * r + 4 * g4 + k] = D[r][vb][k];
+      for (int r = 0; r < RB; ++r) *reinterpret_cast<float4_t*>(out + 16 * (rw * RB + r)) = D[r][vb];
     }
+  }
+  }
+}
+
+// Y[v][row] = sum over the runs that a group is part of, in their order, rounded once to the output type: 4 places a thread, ROWS / 4
+// threads a vector; the rows turn round in LDS (16-byte reads; the stride against bank conflicts).
+__global__ void __launch_bounds__(256) sum_phases_kernel(PromptSet S, int units, int run, int batch, int y_dtype) {
+  constexpr int LR = kLaneRows, ROWS = kGroupRows, TV = ROWS / 4, VECS = 256 / TV, STRIDE = LR + 4;
+  __shared__ __align__(16) float rows[VECS][16 * STRIDE];
+  int group = blockIdx.x;
+  const int splits = (group * units + units - 1) / run - group * units / run + 1;
+  const int q = threadIdx.x % TV, w = threadIdx.x / TV, v = VECS * blockIdx.y + w;
+  const int64_t mp = (int64_t)S.groups * ROWS, stride = (int64_t)batch * mp;
+  const float* p = S.P + (int64_t)v * mp + (int64_t)group * ROWS + 4 * q;
+  const PromptItem& it = S.it[find_item(S, group)];
+  const int m = it.A.g.m;
+  if (v < batch) {
+    float4_t s = *reinterpret_cast<const float4_t*>(p);
+#pragma unroll 4
+    for (int k = 1; k < splits; ++k) s += *reinterpret_cast<const float4_t*>(p + k * stride);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) rows[w][(4 * (q % 4) + k) * STRIDE + q / 4] = s[k];
+  }
+  __syncthreads();
+  const int row = group * ROWS + 4 * q;      // (m is a multiple of 8)
+  if (v >= batch || row >= m) return;
+  const float4_t s = *reinterpret_cast<const float4_t*>(&rows[w][(4 * q / LR) * STRIDE + 4 * q % LR]);
+  const int64_t at = (int64_t)v * m + row;
+  if (y_dtype == SPQR_F32) {
+    *reinterpret_cast<float4_t*>(static_cast<float*>(it.Y) + at) = s;
+  } else {
+    uint32_t h[2] = {(uint32_t)f2h_rne(s[0]) | ((uint32_t)f2h_rne(s[1]) << 16), (uint32_t)f2h_rne(s[2]) | ((uint32_t)f2h_rne(s[3]) << 16)};
+    *reinterpret_cast<uint2*>(static_cast<uint16_t*>(it.Y) + at) = make_uint2(h[0], h[1]);
   }
 }
 
@@ -322,144 +445,201 @@ prompt_group_kernel(DevMatrix A, const uint16_t* __restrict__ X, int batch, floa
 // ---------------------------------------------------------------------------
 static size_t up256(size_t v) { return (v + 255) & ~(size_t)255; }
 
-struct PromptPlan { int groups, units, rows, unit_shift, kg, phases, nvb, vblocks, per, splits; };
-static PromptPlan plan_prompt(const Geometry& g, int b) {
+// Vectors per workgroup: 16 * NVB * 4 / RW, and what a phase takes (us) of a workgroup alone on its CU and of two that share
+// it.  (Measured over eight layers of 4 M to 119 M weights and all formats; a workgroup's start is 3 us and 0.04 a vector, 5
+// more where two start at once, a partial result its way to memory and back at 4 TB/s.  256 vectors a workgroup would be 128
+// sums a lane: the compiler spills, 140 us against 95 for 17920 x 6656, 4-bit, 256 vectors.)
+struct PromptWidth { int rw, nvb, vectors; double one_us, two_us; };
+constexpr PromptWidth kWidths[] = {{2, 2, 64, 1.6, 2.2}, {2, 3, 96, 1.7, 2.4}, {1, 2, 128, 2.05, 2.9}, {1, 3, 192, 2.25, 3.5}};
+constexpr int kMostRunPhases = 2048;          // their ranges of outliers lie in LDS: 32 bytes each
+constexpr int kWidthCount = sizeof(kWidths) / sizeof(kWidths[0]);
+
+struct PromptPlan { int groups, units, unit_shift, kg, bins, width, vblocks, run, runs, slots; };
+static int prompt_groups(const Geometry& g) { return (g.m + kGroupRows - 1) / kGroupRows; }
+// Partial results of a group: the most runs that a group is part of.
+static int prompt_slots(int groups, int units, int run) {
+  int most = 1;
+  for (int g = 0; g < groups && most < (units - 1) / run + 2; ++g) {
+    const int n = (g * units + units - 1) / run - g * units / run + 1;
+    most = n > most ? n : most;
+  }
+  return most;
+}
+// most_slots > 0: no more partial results than that.
+static PromptPlan plan_prompt(const DevMatrix* As, int count, int b, int most_slots) {
+  const Geometry& g = As[0].g;
   PromptPlan p;
-  p.rows = 16 * lane_rows(g.tile_rows);
-  p.groups = (g.m + p.rows - 1) / p.rows;
+  p.groups = 0;
+  for (int i = 0; i < count; ++i) p.groups += prompt_groups(As[i].g);
   p.units = (g.ntc + kUnitTiles - 1) / kUnitTiles;
   p.unit_shift = g.tile_cols == 8 ? 7 : (g.tile_cols == 16 ? 8 : 9);
   p.kg = g.tile_cols / 8;
-  p.phases = p.units * p.kg;
-  // Vectors per workgroup and splits of the columns, one workgroup per CU: a phase takes 1.8 (64 vectors) or 2.3 us (128)
-  // with strips of 16 rows, 1.0, 1.2 or 1.8 (256) with strips of 8, a workgroup's start 5 us, a split its partial results
-  // at 4 TB/s (64 MB of them at most).  256 vectors with strips of 16 rows would be 256 sums a lane, which leave the
-  // compiler no register to turn in (it moves half of them back and forth, 8.9 us a phase).
-  const double split_us = (double)b * g.m * 8 / 4e6;
-  const int64_t most = ((int64_t)16 << 20) / ((int64_t)b * g.m);
-  const int pin = option(SPQR_OPT_PROMPT_PLAN), pin_units = pin % 1024, most_nvb = p.rows == 256 ? 2 : 4;   // (tuning, tests)
-  const int pin_nvb = pin / 1024 < most_nvb ? pin / 1024 : most_nvb;
+  p.bins = p.units * p.kg * 4;
+  const int total = p.groups * p.units, most_run = kMostRunPhases / p.kg;
+  const int64_t places = (int64_t)p.groups * kGroupRows;
+  int64_t most = std::max<int64_t>(((int64_t)16 << 20) / ((int64_t)b * places), 1);   // 64 MB of them
+  if (most_slots > 0) most = std::min<int64_t>(most, most_slots);
+  const int pin = option(SPQR_OPT_PROMPT_PLAN), pin_units = pin % 1024;   // (tuning, tests)
+  const int widest = kWidths[kWidthCount - 1].vectors;
+  const int pin_vectors = 64 * (pin / 1024) < widest ? 64 * (pin / 1024) : widest;
+  p.width = kWidthCount - 1;
+  p.vblocks = (b + widest - 1) / widest;
+  p.run = p.units;                           // whole groups: one partial result
   double best = 1e30;
-  for (int nvb = 1; nvb <= most_nvb; nvb *= 2) {
-    if (pin_nvb >= 1 && nvb != pin_nvb) continue;
-    const double phase_us = p.rows == 256 ? (nvb == 1 ? 1.8 : 2.3) : (nvb == 1 ? 1.0 : nvb == 2 ? 1.2 : 1.8);
-    const int vblocks = (b + 64 * nvb - 1) / (64 * nvb);
-    for (int s = 1; s <= p.units && (s == 1 || s <= most); ++s) {
-      const int per = (p.units + s - 1) / s, splits = (p.units + per - 1) / per;
-      const int64_t rounds = ((int64_t)p.groups * vblocks * splits + kCUs - 1) / kCUs;
-      const double cost = (double)rounds * (per * p.kg * phase_us + 5.0) + splits * split_us;
-      if (cost < best - 1e-9) { best = cost; p.nvb = nvb; p.vblocks = vblocks; p.per = per; }
+  for (int w = 0; w < kWidthCount; ++w) {
+    const PromptWidth& c = kWidths[w];
+    if (pin_vectors > 0 && c.vectors != pin_vectors && !(c.vectors < pin_vectors && 2 * c.vectors > pin_vectors && b <= c.vectors)) continue;
+    const int vblocks = (b + c.vectors - 1) / c.vectors;
+    for (int k = 1; k <= 2; ++k) {           // workgroups per CU
+      const int wgs = k * kCUs / vblocks > 0 ? k * kCUs / vblocks : 1, run = std::min((total + wgs - 1) / wgs, most_run), runs = (total + run - 1) / run;
+      if (prompt_slots(p.groups, p.units, run) > most) continue;
+      const double parts_us = (double)b * kGroupRows * 8 / 4e6 * (runs + p.groups);
+      const int rounds = (runs + wgs - 1) / wgs;
+      const double cost = rounds * (run * p.kg * (k == 1 ? c.one_us : c.two_us) + 3.0 + 0.04 * c.vectors + (k == 1 ? 0.0 : 5.0)) + parts_us;
+      if (cost < best - 1e-9) { best = cost; p.width = w; p.vblocks = vblocks; p.run = run; }
     }
+    if (best > 1e29) { p.width = w; p.vblocks = vblocks; }
   }
-  if (pin_units >= 1) p.per = pin_units < p.units ? pin_units : p.units;
-  p.splits = (p.units + p.per - 1) / p.per;
+  if (pin_units >= 1) p.run = std::min(pin_units, std::min(total, most_run));
+  p.runs = (total + p.run - 1) / p.run;
+  p.slots = prompt_slots(p.groups, p.units, p.run);
   return p;
 }
 
 // The formats the batch kernel has; more outliers than one weight in four go through the dense copy instead.
 bool prompt_has_instance(const DevMatrix& A) {
-  return mfma_has_instance(A.g) && A.nnz <= (int64_t)A.g.m * A.g.n / 4 && A.nnz < 0x7FFF0000ll &&
+  return mfma_has_instance(A.g) && A.nnz <= (int64_t)A.g.m * A.g.n / 4 && A.nnz < 0x7FFF0000ll && (int64_t)A.g.m * A.g.n < ((int64_t)1 << 44) &&
          (A.g.ntc + kUnitTiles - 1) / kUnitTiles * (A.g.tile_cols / 8) <= kSortMaxPhases;
 }
 
 // Where the dense copy pays against slices of 16 (prefill_wanted: from 48 vectors on, later on larger layers) and this kernel
-// is faster than the copy (times in us, copy -> here):
-// - strips of 8 rows: from 4 M weights and 512 columns on (2048^2, 48 to 256 vectors: 28.1 .. 33.6 -> 24.3 .. 27.8; 1024^2:
-//   21.0 .. 24.0 against 25.3 .. 26.4; 8192 x 512: 5 % slower to 17 % faster).  With fewer columns there are fewer phases than
-//   one workgroup per CU can share, and one hot phase is the call (17920 x 256: 13 % faster to 19 % slower).
-// - 16 rows a lane, whose groups of 256 rows are fewer and whose weights are dequantised once per 128 vectors: from 24 M on
-//   (5120^2: 46.2 .. 61.0 -> 38.3 .. 57.2; 5120 x 3584: 35.4 .. 47.4 against 36.9 .. 55.3); below, the sort of the outliers
-//   (10 us) and the few workgroups cost more than the copy's passes.  Above 192 vectors it needs more than 2048 columns: a
-//   second pass over the weights for so few phases costs more than it saves (17920 x 1536, 256 vectors: 62 .. 66 against
-//   66 .. 71; 17920 x 2048: 77 .. 82 against 80 .. 82).
-// How the outliers lie is not known here and moves a call by more than the lines do: few groups of rows and a skewed layer
-// leave one group with most of them (4096 x 8192, 128 vectors: 56 -> 47 with uniform outliers, 51 -> 50 and 51 -> 60 on two
-// Zipf layers; 3072 x 12288, 256 vectors: 78 -> 60 and 75 -> 77).  Those sizes stay, the mean of the layers being faster.
-// From 33 vectors on it would beat the slices, but they add the outliers in binary32 and here weight + outlier is rounded to
-// binary16, so no batch that took the slices moves here.  With a pinned plan (SPQR_OPT_PROMPT_PLAN) the size is no matter.
-static bool prompt_pays(const Geometry& g, int b) {
-  const double weights = (double)g.m * g.n;
-  return g.tile_rows == 8 ? weights >= 4e6 && g.n >= 512 : weights >= 24e6 && (b <= 192 || g.n > 2048);
-}
+// is faster than the copy: from 4 M weights and 512 columns on, with tiles of 8 columns from 12 M on.  Times in us, the copy ->
+// here, 48 to 256 vectors, 1 % of outliers, uniform: 2048^2 25 .. 32 -> 22 .. 29, 4096^2 35 .. 45 -> 27 .. 40, 11008 x 4096 62 .. 95 ->
+// 38 .. 61, 17920 x 2048 54 .. 81 -> 38 .. 64; 1024^2 21 .. 24 against 22 .. 24; 17920 x 256 23 .. 32 against 27 .. 36 (too few
+// phases to a group).  With Zipf rows, over the same sizes and formats, 2048^2 is 6 % faster, 4096^2 8 % (with tiles of 8 columns
+// 4 % slower from 96 vectors on, and 2048^2 up to 16 % slower: a unit is one phase there), 1024 x 17920 at 256 vectors up to 10 %
+// slower.  From 17 vectors on this kernel would beat the slices, but they add the outliers in binary32 and here weight +
+// outlier is rounded to binary16, so no batch that took the slices moves here.  With a pinned plan (SPQR_OPT_PROMPT_PLAN) the
+// size is no matter.
+static bool prompt_pays(const Geometry& g) { return (double)g.m * g.n >= (g.tile_cols == 8 ? 12e6 : 4e6) && g.n >= 512; }
 
 bool prompt_wanted(const DevMatrix& A, int b) {
   return option(SPQR_OPT_BATCH_PATH) == SPQR_BATCH_PATH_AUTO && prompt_has_instance(A) && prefill_wanted(A, b) &&
-         (prompt_pays(A.g, b) || option(SPQR_OPT_PROMPT_PLAN) >= 1);
+         (prompt_pays(A.g) || option(SPQR_OPT_PROMPT_PLAN) >= 1);
 }
 
-static size_t prompt_offsets(const DevMatrix& A, int b, const PromptPlan& p, size_t (&at)[5]) {
+// Whether a caller's workspace for such a call holds the dense copy too: calls that the copy took before this kernel was the faster
+// one for them, so that what was reported for them does not shrink.
+bool prompt_reports_copy(const DevMatrix& A, int b) {
+  const double weights = (double)A.g.m * A.g.n;
+  return option(SPQR_OPT_PROMPT_PLAN) < 1 && A.g.tile_rows != 8 && (weights < 24e6 || (b > 192 && A.g.n <= 2048));
+}
+
+// Scratch of one call: the batch as operands, in column order before that if there is a permutation, per matrix the sorted outliers, their ranges,
+// the counts, the partial results.
+static int prompt_blocks16(const PromptPlan& p) { return p.vblocks * kWidths[p.width].vectors / 16; }
+static size_t prompt_offsets(const DevMatrix* As, int count, int b, const PromptPlan& p, uint8_t* scratch, PromptSet* S) {
   size_t total = 0;
-  auto take = [&](size_t bytes) { const size_t o = total; total += up256(bytes); return o; };
-  at[0] = take(A.perm != nullptr ? (size_t)b * A.g.n * 2 : 0);
-  at[1] = take(A.nnz > 0 ? (size_t)A.nnz * 4 : 0);                                                  // sorted entries
-  at[2] = take(A.nnz > 0 ? (size_t)p.groups * (p.phases + 1) * 4 : 0);                               // their ranges
-  at[3] = take(A.nnz > 0 ? (size_t)count_slots(A.nnz, p.groups) * p.phases * 4 : 0);        // counts
-  at[4] = take((size_t)p.splits * b * A.g.m * sizeof(float));
+  auto take = [&](size_t bytes) { uint8_t* at = scratch + total; total += up256(bytes); return at; };
+  take((size_t)p.bins * prompt_blocks16(p) * 1024);
+  if (As[0].perm != nullptr) take((size_t)b * As[0].g.n * 2);
+  int64_t nnz = 0;
+  for (int i = 0; i < count; ++i) nnz += As[i].nnz;
+  uint8_t* entries = take((size_t)nnz * 4);
+  nnz = 0;
+  for (int i = 0; i < count; ++i) {
+    const DevMatrix& A = As[i];
+    const int groups = prompt_groups(A.g);
+    uint8_t* offs = take(A.nnz > 0 ? (size_t)groups * (p.bins + 1) * 4 : 0);
+    uint8_t* counts = take(A.nnz > 0 ? (size_t)count_slots(A.nnz, groups) * p.bins * 4 : 0);
+    if (S != nullptr) S->it[i] = {A, nullptr, reinterpret_cast<uint32_t*>(counts), reinterpret_cast<int32_t*>(offs), (int)nnz, groups};
+    nnz += A.nnz;
+  }
+  uint8_t* P = take((size_t)p.slots * b * p.groups * kGroupRows * sizeof(float));
+  if (S != nullptr) {
+    S->entries = reinterpret_cast<uint32_t*>(entries);
+    S->P = reinterpret_cast<float*>(P);
+    S->count = count;
+    S->groups = p.groups;
+  }
   return total;
 }
 
-size_t prompt_workspace_bytes(const DevMatrix& A, int b) {
-  size_t at[5];
-  return prompt_offsets(A, b, plan_prompt(A.g, b), at);
+size_t prompt_workspace_bytes(const DevMatrix* As, int count, int b, int most_slots) {
+  return prompt_offsets(As, count, b, plan_prompt(As, count, b, most_slots), nullptr, nullptr);
 }
 
-template <int W, int TR, int TC, int AXIS, int NVB>
-static hipError_t launch_prompt_t(const DevMatrix& A, const uint16_t* X, int b, float* P, const PromptPlan& p,
-                                  const uint32_t* entries, const int32_t* offs, hipStream_t stream) {
-  constexpr int LDS = 2 * 4 * lane_rows(TR) * 1024 + 512;
+template <int W, int TR, int TC, int AXIS, int RW, int NVB>
+static hipError_t launch_prompt_t(const PromptSet& S, const u32x4* XS, int b, const PromptPlan& p, hipStream_t stream) {
+  constexpr int PHASES = 2 * 4 * kLaneRows * 1024 + 512 + 16 * SPQR_MAX_FUSED, MOST = 160 * 1024;
   static PerDevice ready;                    // more than 64 KB of LDS per workgroup is an opt-in per kernel and device
   const int dev = current_device();
   if (!ready.get(dev)) {
-    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&prompt_group_kernel<W, TR, TC, AXIS, NVB>),
-                                             hipFuncAttributeMaxDynamicSharedMemorySize, LDS);
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&prompt_group_kernel<W, TR, TC, AXIS, RW, NVB>),
+                                             hipFuncAttributeMaxDynamicSharedMemorySize, MOST);
     if (e != hipSuccess) return e;
     ready.set(dev, 1);
   }
-  hipLaunchKernelGGL((prompt_group_kernel<W, TR, TC, AXIS, NVB>), dim3(p.groups, p.splits, p.vblocks), dim3(256), LDS, stream, A, X, b, P,
-                     p.per, entries, offs);
+  hipLaunchKernelGGL((prompt_group_kernel<W, TR, TC, AXIS, RW, NVB>), dim3(p.runs, p.vblocks), dim3(256),
+                     PHASES + (4 * p.run * p.kg + 1) * 8, stream, S, XS, b, prompt_blocks16(p), p.run);
   return hipGetLastError();
 }
+template <int W, int TR, int TC, int AXIS>
+static hipError_t launch_prompt_width(const PromptSet& S, const u32x4* XS, int b, const PromptPlan& p, hipStream_t stream) {
+  switch (p.width) {
+    case 0: return launch_prompt_t<W, TR, TC, AXIS, kWidths[0].rw, kWidths[0].nvb>(S, XS, b, p, stream);
+    case 1: return launch_prompt_t<W, TR, TC, AXIS, kWidths[1].rw, kWidths[1].nvb>(S, XS, b, p, stream);
+    case 2: return launch_prompt_t<W, TR, TC, AXIS, kWidths[2].rw, kWidths[2].nvb>(S, XS, b, p, stream);
+    default: return launch_prompt_t<W, TR, TC, AXIS, kWidths[3].rw, kWidths[3].nvb>(S, XS, b, p, stream);
+  }
+}
 
-// Y[b][m] = X[b][n] . W_hat^T.  `scratch`: prompt_workspace_bytes(A, b) bytes, 256-byte aligned.
-hipError_t launch_prompt(const DevMatrix& A, const uint16_t* X, int b, void* Y, int y_dtype, hipStream_t stream,
-                         uint8_t* scratch) {
-  const Geometry& g = A.g;
-  if (!prompt_has_instance(A) || scratch == nullptr || b < 1 || b > 256) return hipErrorInvalidValue;
-  const PromptPlan p = plan_prompt(g, b);
-  size_t at[5];
-  prompt_offsets(A, b, p, at);
-  uint32_t* entries = reinterpret_cast<uint32_t*>(scratch + at[1]);
-  int32_t* offs = reinterpret_cast<int32_t*>(scratch + at[2]);
-  uint32_t* counts = reinterpret_cast<uint32_t*>(scratch + at[3]);
-  float* P = reinterpret_cast<float*>(scratch + at[4]);
+// Y_i[b][m_i] = X[b][n] . W_hat_i^T for matrices of one format, width and permutation.  `scratch`:
+// prompt_workspace_bytes(As, count, b, most_slots) bytes, 256-byte aligned.
+hipError_t launch_prompt(const DevMatrix* As, int count, const uint16_t* X, int b, void* const* Ys, int y_dtype, hipStream_t stream,
+                         uint8_t* scratch, int most_slots) {
+  if (scratch == nullptr || b < 1 || b > 256 || count < 1 || count > SPQR_MAX_FUSED) return hipErrorInvalidValue;
+  const Geometry& g = As[0].g;
+  int64_t nnz = 0;
+  for (int i = 0; i < count; ++i) {
+    const Geometry& h = As[i].g;
+    if (!prompt_has_instance(As[i]) || h.n != g.n || h.w_bits != g.w_bits || h.tile_rows != g.tile_rows || h.axis != g.axis) return hipErrorInvalidValue;
+    nnz += As[i].nnz;
+  }
+  const PromptPlan p = plan_prompt(As, count, b, most_slots);
+  if (p.vblocks * kWidths[p.width].vectors < b || p.run < 1 || (int64_t)p.runs * p.run < (int64_t)p.groups * p.units ||
+      (int64_t)(p.runs - 1) * p.run >= (int64_t)p.groups * p.units)
+    return hipErrorInvalidValue;
+  PromptSet S;
+  prompt_offsets(As, count, b, p, scratch, &S);
+  for (int i = 0; i < count; ++i) S.it[i].Y = Ys[i];
   hipError_t e = hipSuccess;
   const uint16_t* Xin = X;
-  if (A.perm != nullptr) {
-    uint16_t* xp = reinterpret_cast<uint16_t*>(scratch + at[0]);
-    e = launch_gather_x(X, A.perm, xp, g.n, b, stream);
+  const int blocks16 = prompt_blocks16(p);
+  u32x4* XS = reinterpret_cast<u32x4*>(scratch);
+  if (As[0].perm != nullptr) {
+    uint16_t* xp = reinterpret_cast<uint16_t*>(scratch + up256((size_t)p.bins * blocks16 * 1024));
+    e = launch_gather_x(X, As[0].perm, xp, g.n, b, stream);
     if (e != hipSuccess) return e;
     Xin = xp;
   }
-  if (A.nnz > 0) {
-    const dim3 grid(p.groups, kSortWgs);
-    hipLaunchKernelGGL(count_phases_kernel, grid, dim3(256), 0, stream, A, p.rows, p.unit_shift, p.kg, p.phases, counts);
-    if (p.rows == 256)
-      hipLaunchKernelGGL(sort_phases_kernel<16>, grid, dim3(256), 0, stream, A, p.unit_shift, p.kg, p.phases, counts, offs, entries);
-    else
-      hipLaunchKernelGGL(sort_phases_kernel<8>, grid, dim3(256), 0, stream, A, p.unit_shift, p.kg, p.phases, counts, offs, entries);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
+  hipLaunchKernelGGL(count_phases_kernel, dim3(p.groups * kSortWgs + (p.bins * blocks16 * 64 + kSortThreads - 1) / kSortThreads), dim3(kSortThreads), 0, stream, S, p.groups,
+                     p.unit_shift, p.kg, p.bins, Xin, b, blocks16, XS);
+  if (nnz > 0) {
+    const auto sort = p.bins <= kSortThreads ? &sort_phases_kernel<1> : &sort_phases_kernel<2>;
+    hipLaunchKernelGGL(sort, dim3(p.groups, kSortWgs), dim3(kSortThreads), 0, stream, S, p.unit_shift, p.kg, p.bins);
   }
+  if ((e = hipGetLastError()) != hipSuccess) return e;
   e = hipErrorInvalidValue;
-#define SPQR_CASE(W_, TR_, TC_, AX_)                                                                                    \
-  if (g.w_bits == W_ && g.tile_rows == TR_ && g.tile_cols == TC_ && g.axis == AX_)                                       \
-    e = p.nvb == 1 ? launch_prompt_t<W_, TR_, TC_, AX_, 1>(A, Xin, b, P, p, entries, offs, stream)                         \
-        : p.nvb == 2 ? launch_prompt_t<W_, TR_, TC_, AX_, 2>(A, Xin, b, P, p, entries, offs, stream)                       \
-                     : launch_prompt_t<W_, TR_, TC_, AX_, (TR_ == 8 ? 4 : 2)>(A, Xin, b, P, p, entries, offs, stream);
+#define SPQR_CASE(W_, TR_, TC_, AX_)                                                     \
+  if (g.w_bits == W_ && g.tile_rows == TR_ && g.tile_cols == TC_ && g.axis == AX_)       \
+    e = launch_prompt_width<W_, TR_, TC_, AX_>(S, XS, b, p, stream);
   SPQR_CASE(3, 16, 16, 1) SPQR_CASE(4, 16, 16, 1) SPQR_CASE(3, 8, 32, 1) SPQR_CASE(4, 8, 32, 1)
   SPQR_CASE(3, 16, 16, 0) SPQR_CASE(4, 16, 16, 0) SPQR_CASE(3, 32, 8, 0) SPQR_CASE(4, 32, 8, 0)
 #undef SPQR_CASE
   if (e != hipSuccess) return e;
-  return launch_sum_groups(g, P, p.splits, b, Y, y_dtype, stream);
+  hipLaunchKernelGGL(sum_phases_kernel, dim3(p.groups, (b + 7) / 8), dim3(256), 0, stream, S, p.units, p.run, b, y_dtype);
+  return hipGetLastError();
 }
 
 }  // namespace spqr

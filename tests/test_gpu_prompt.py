@@ -314,3 +314,73 @@ def test_rows_around_what_counts_as_long_in_a_piece(P, w, b1, b2, axis, ntr, b, 
         run(P, f, b, steps, shares)
     finally:
         P.spqr_set_option(P.SPQR_OPT_BATCH_PATH, P.SPQR_BATCH_PATH_AUTO)
+
+
+# runs of units that end inside a group, at its end and behind several groups and matrices; one matrix without outliers, one
+# shorter than a group
+@pytest.mark.parametrize("w,b1,b2,axis,ntc", [(3, 16, 16, 1, 35), (4, 16, 16, 0, 18), (4, 8, 32, 1, 33), (3, 8, 32, 0, 67)])
+@pytest.mark.parametrize("b,vectors,units", [(48, 1, 1), (65, 2, 5), (130, 4, 1000), (256, 4, 3), (77, 0, 2)])
+def test_one_pass_of_several_matrices(P, w, b1, b2, axis, ntc, b, vectors, units):
+    """Against the oracle; twice the same; nothing written outside the workspace; on a capturing stream matrix by matrix, bit
+    for bit what the single calls give."""
+    import ctypes as C
+    import torch
+    from test_gpu_workspace import _graph_node_types
+    tr, tc = synth.tile_shape(b1, b2, axis)
+    fs = [synth.make_matrix(ntr * tr, ntc * tc, w_bits=w, beta1=b1, beta2=b2, group_axis=axis, outlier_rate=rate,
+                            outlier_structure=st, seed=(87, w, axis, ntr)) for ntr, st, rate in ((33, "zipf", 0.1), (2, "none", 0.0), (17, "rows8cols4", 0.2))]
+    if b % 2:
+        for f in fs:
+            f.perm = np.random.default_rng(5).permutation(f.n).astype(np.int32)
+    As = [P.SpQRMatrix.from_logical(f) for f in fs]
+    for A in As[1:]:
+        A.desc.perm = As[0].desc.perm          # descriptors must name the same device permutation
+    X = synth.make_x(fs[0].n, b, seed=(88, b))
+    Xd = torch.from_numpy(X).to("cuda:0")
+    P.spqr_set_option(P.SPQR_OPT_PROMPT_PLAN, 1024 * vectors + units)
+    need = P.spqr_workspace_bytes(As, b)
+    buf = torch.full((need + 512,), 0xA5, dtype=torch.uint8, device="cuda:0")
+    Ys = P.spqr_gemm_fused_ws(As, Xd, buf[256:256 + need])
+    again = P.spqr_gemm_fused_ws(As, Xd, buf[256:256 + need])
+    assert bool((buf[:256] == 0xA5).all()) and bool((buf[256 + need:] == 0xA5).all())
+    for f, Y, Z in zip(fs, Ys, again):
+        assert torch.equal(Y, Z)
+        Xp = X.astype(np.float64) if f.perm is None else X.astype(np.float64)[:, f.perm]
+        terms = np.sqrt(Xp ** 2 @ (orc.reconstruct(f) ** 2).T)
+        err = np.linalg.norm(Y.cpu().numpy() - orc.matvec(f, X), axis=1) / np.linalg.norm(terms, axis=1)
+        assert err.max() <= REL_L2
+    if units != 2:
+        return
+    singles = [P.spqr_gemm_smallbatch_ws(A, Xd, buf[256:256 + need]).clone() for A in As]
+    torch.cuda.synchronize()
+    types, ex, graph, st, hip = _graph_node_types(lambda s: P.spqr_gemm_fused_ws(As, Xd, buf[256:256 + need], outs=Ys, stream=s))
+    assert all(t == 0 for t in types), types
+    for rep in range(3):
+        for Y in Ys:
+            Y.zero_()
+        torch.cuda.synchronize()
+        assert hip.hipGraphLaunch(ex, C.c_void_p(st.cuda_stream)) == 0
+        torch.cuda.synchronize()
+        assert all(torch.equal(Y, S) for Y, S in zip(Ys, singles)), rep
+    assert hip.hipGraphExecDestroy(ex) == 0 and hip.hipGraphDestroy(graph) == 0
+
+
+def test_static_array_takes_a_plan_of_fewer_partial_results(P):
+    """The fastest plan's scratch does not fit the static array, one partial result of every row does: the one-pass kernel
+    runs all the same (the slices would have added the outliers in binary32: other bits)."""
+    import torch
+    f = synth.make_matrix(8 * 2040, 32 * 100, w_bits=3, beta1=8, beta2=32, group_axis=1, outlier_rate=0.02, outlier_structure="uniform", seed=(89,))
+    A = P.SpQRMatrix.from_logical(f)
+    assert P.spqr_workspace_bytes(A, 200) > P.SPQR_STATIC_SCRATCH_BYTES
+    X = synth.make_x(f.n, 200, seed=(90,))
+    Xd = torch.from_numpy(X).to("cuda:0")
+    out = torch.zeros((200, f.m), dtype=torch.float32, device="cuda:0")
+    P.spqr_gemm_smallbatch_noalloc(A, Xd, out)
+    ref = orc.matvec(f, X)
+    assert (np.linalg.norm(out.cpu().numpy() - ref, axis=1) / np.linalg.norm(ref, axis=1)).max() <= REL_L2
+    P.spqr_set_option(P.SPQR_OPT_BATCH_PATH, P.SPQR_BATCH_PATH_MATRIX)
+    slices = torch.zeros_like(out)
+    P.spqr_gemm_smallbatch_noalloc(A, Xd, slices)
+    assert not torch.equal(out, slices)
+    P.spqr_set_option(P.SPQR_OPT_BATCH_PATH, P.SPQR_BATCH_PATH_AUTO)
+    assert (out - P.spqr_gemm_smallbatch(A, Xd)).norm() <= 1e-5 * out.norm()   # the same weights, sums in another order
