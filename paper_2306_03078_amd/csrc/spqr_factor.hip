@@ -14,11 +14,11 @@
 //             (strictly lower blocks) plus the diagonal blocks' inverses from the potrf step.
 //   final     U[i][j] = X[n-1-i][n-1-j] for j >= i
 //
-// Every tile product runs on the matrix cores (v_mfma_f64_16x16x4_f64).  Their binary64 rate is the vector ALU's, but an
-// operand of one 8-byte LDS read per lane feeds two instructions of 64 clocks, where register tiles of 4 x 4 FMAs need
-// eight LDS reads for sixteen instructions of 4, bound by LDS.  n = d = 4096: Hessian 3.4 -> 2.5 ms (28 of 68 TFLOP/s),
-// trailing updates 23 -> 20 us and panels 11.8 -> 7.0 us each, diagonal blocks 51 -> 20 us, Hessian and factor together 10.9 -> 6.8
-// ms; what is left is the Hessian's operands one step ahead in registers, and the chain of diagonal blocks.
+// Every tile product runs on the matrix cores (v_mfma_f64_16x16x4_f64), at the vector ALU's rate, but an operand of one
+// 8-byte half of an LDS read per lane feeds two instructions of 64 clocks.  n = d = 4096: Hessian 2.4 -> 1.65 ms (42 of 68 TFLOP/s;
+// staged by rows, squares of tiles per XCD), a block column of the factorisation 47 -> 32 us (the next diagonal block beside the trailing
+// update), the triangular inverse 1.13 -> 0.92 ms, Hessian and factor together 6.75 -> 4.9 ms.  What is left: the chain of 64
+// diagonal blocks of 20 us and panels of 5, bank conflicts and the barrier of every step of k in the products.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -28,35 +28,42 @@ namespace spqr_fac {
 
 constexpr int NB = 64;                       // block size of the factorisation
 constexpr int KC = 16;                       // depth of one LDS stage of a tile product
-constexpr int LP = NB + 8;                   // padded row of a staged operand: an operand's four rows meet no bank twice more than they must
+constexpr int LP = KC + 2;                   // padded row of a staged operand: 16 rows of 16 bytes each meet every bank once
 
+typedef double f64x2 __attribute__((ext_vector_type(2)));
+typedef double f64x2_8 __attribute__((ext_vector_type(2), aligned(8)));
 typedef double f64x4 __attribute__((ext_vector_type(4)));
 
 // D += A B for one 16 x 16 block: lane l gives A[l % 16][l / 16] and B[l / 16][l % 16], D[r] is row l / 16 + 4 r, column l % 16.
 __device__ __forceinline__ f64x4 mfma4(double a, double b, f64x4 d) { return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, d, 0, 0, 0); }
 
-// A 64 x 64 tile of four wavefronts, 32 x 32 each; two LDS buffers of KC steps, the next one's values in registers
-// while this one is multiplied.
-struct Tile { f64x4 d[2][2]; };
-struct Stage { double a[2][KC][LP], b[2][KC][LP]; };
+// A tile of 32 WM x 32 WN of four wavefronts, 16 WM x 16 WN each; two LDS buffers of KC steps, the next one's values in
+// registers while this one is multiplied.  Both operands are staged by rows, k innermost: a lane's 16-byte read is two steps
+// of k for one row, so a product of 8 steps takes WM + WN reads for 2 WM WN instructions of 64 clocks.  (One step a read, the
+// rows innermost: as many clocks of LDS as of the matrix cores, with bank conflicts on top.)
+template <int WM, int WN> struct Tile { f64x4 d[WM][WN]; };
+template <int WM, int WN> struct Stage { double a[2][32 * WM][LP], b[2][32 * WN][LP]; };
 
-// get_a / get_b (idx, k0): staged value idx (0 .. 1023) of the step at k0; place_b: where one of B goes.
-template <class GetA, class GetB, class PlaceB>
-__device__ __forceinline__ void tile_product(Tile& acc, int kb, int ke, GetA get_a, GetB get_b, PlaceB place_b, Stage& S) {
+// get_a / get_b (row, k): the values at k and k + 1; b_by_k: consecutive threads fetch consecutive rows of B, else consecutive k.
+template <bool B_BY_K, int WM, int WN, class GetA, class GetB>
+__device__ __forceinline__ void tile_product(Tile<WM, WN>& acc, int kb, int ke, GetA get_a, GetB get_b, Stage<WM, WN>& S) {
+  constexpr int NA = WM, NW = WN;            // pairs a thread stages: 32 W rows of KC / 2 pairs over 256 threads
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6, i16 = lane & 15, g4 = lane >> 4;
-  const int r0 = 32 * (wave & 1) + i16, c0 = 32 * (wave >> 1) + i16;
-  double pa[4], pb[4];
+  const int r0 = 16 * WM * (wave & 1) + i16, c0 = 16 * WN * (wave >> 1) + i16;
+  f64x2 pa[NA], pb[NW];
+  auto b_row = [&](int idx) { return B_BY_K ? idx % (32 * WN) : idx / (KC / 2); };
+  auto b_k = [&](int idx) { return 2 * (B_BY_K ? idx / (32 * WN) : idx % (KC / 2)); };
   auto fetch = [&](int k0) {
 #pragma unroll
-    for (int q = 0; q < 4; ++q) { pa[q] = get_a(t + 256 * q, k0); pb[q] = get_b(t + 256 * q, k0); }
+    for (int q = 0; q < NA; ++q) pa[q] = get_a((t + 256 * q) / (KC / 2), k0 + 2 * (t % (KC / 2)));
+#pragma unroll
+    for (int q = 0; q < NW; ++q) pb[q] = get_b(b_row(t + 256 * q), k0 + b_k(t + 256 * q));
   };
   auto stash = [&](int buf) {
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int idx = t + 256 * q;
-      S.a[buf][idx & 15][idx >> 4] = pa[q];
-      place_b(S.b[buf], idx, pb[q]);
-    }
+    for (int q = 0; q < NA; ++q) *reinterpret_cast<f64x2*>(&S.a[buf][(t + 256 * q) / (KC / 2)][2 * (t % (KC / 2))]) = pa[q];
+#pragma unroll
+    for (int q = 0; q < NW; ++q) *reinterpret_cast<f64x2*>(&S.b[buf][b_row(t + 256 * q)][b_k(t + 256 * q)]) = pb[q];
   };
   if (kb >= ke) return;                      // workgroup-uniform
   __syncthreads();                           // a product before this one may still be read
@@ -67,63 +74,69 @@ __device__ __forceinline__ void tile_product(Tile& acc, int kb, int ke, GetA get
   for (int k0 = kb; k0 < ke; k0 += KC, buf ^= 1) {
     if (k0 + KC < ke) fetch(k0 + KC);
 #pragma unroll
-    for (int kk = 0; kk < KC; kk += 4) {
-      const double *ra = S.a[buf][kk + g4], *rb = S.b[buf][kk + g4];
-      const double a0 = ra[r0], a1 = ra[r0 + 16], b0 = rb[c0], b1 = rb[c0 + 16];
-      acc.d[0][0] = mfma4(a0, b0, acc.d[0][0]);
-      acc.d[0][1] = mfma4(a0, b1, acc.d[0][1]);
-      acc.d[1][0] = mfma4(a1, b0, acc.d[1][0]);
-      acc.d[1][1] = mfma4(a1, b1, acc.d[1][1]);
+    for (int kk = 0; kk < KC; kk += 8) {
+      f64x2 a[WM], b[WN];
+#pragma unroll
+      for (int m = 0; m < WM; ++m) a[m] = *reinterpret_cast<const f64x2*>(&S.a[buf][r0 + 16 * m][kk + 2 * g4]);
+#pragma unroll
+      for (int n = 0; n < WN; ++n) b[n] = *reinterpret_cast<const f64x2*>(&S.b[buf][c0 + 16 * n][kk + 2 * g4]);
+#pragma unroll
+      for (int e = 0; e < 2; ++e)
+#pragma unroll
+        for (int m = 0; m < WM; ++m)
+#pragma unroll
+          for (int n = 0; n < WN; ++n) acc.d[m][n] = mfma4(a[m][e], b[n][e], acc.d[m][n]);
     }
     if (k0 + KC < ke) stash(buf ^ 1);
     __syncthreads();
   }
 }
 
-// sum_{k < K} fa(i, k) * fb(j, k): both operands given by rows; consecutive threads fetch consecutive k of one row.
-template <class FA, class FB>
-__device__ __forceinline__ void tile_nt(Tile& acc, int K, FA fa, FB fb, Stage& S) {
-  tile_product(acc, 0, K, [&](int idx, int k0) { return fa(idx >> 4, k0 + (idx & 15)); },
-               [&](int idx, int k0) { return fb(idx >> 4, k0 + (idx & 15)); },
-               [](double (*b)[LP], int idx, double v) { b[idx & 15][idx >> 4] = v; }, S);
-}
-
-// sum_{kb <= k < ke} fa(i, k) * fb(k, j): the second operand by rows (k, j), consecutive threads fetch consecutive j.
-template <class FA, class FB>
-__device__ __forceinline__ void tile_nn(Tile& acc, int kb, int ke, FA fa, FB fb, Stage& S) {
-  tile_product(acc, kb, ke, [&](int idx, int k0) { return fa(idx >> 4, k0 + (idx & 15)); },
-               [&](int idx, int k0) { return fb(k0 + (idx >> 6), idx & 63); },
-               [](double (*b)[LP], int idx, double v) { b[idx >> 6][idx & 63] = v; }, S);
-}
-
 // f(row, column, value) for the tile's elements of this thread.
-template <class F>
-__device__ __forceinline__ void each_element(const Tile& acc, F f) {
+template <int WM, int WN, class F>
+__device__ __forceinline__ void each_element(const Tile<WM, WN>& acc, F f) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int r0 = 32 * (wave & 1) + (lane >> 4), c0 = 32 * (wave >> 1) + (lane & 15);
+  const int r0 = 16 * WM * (wave & 1) + (lane >> 4), c0 = 16 * WN * (wave >> 1) + (lane & 15);
 #pragma unroll
-  for (int a = 0; a < 2; ++a)
+  for (int a = 0; a < WM; ++a)
 #pragma unroll
-    for (int b = 0; b < 2; ++b)
+    for (int b = 0; b < WN; ++b)
 #pragma unroll
       for (int r = 0; r < 4; ++r) f(r0 + 16 * a + 4 * r, c0 + 16 * b, acc.d[a][b][r]);
 }
+__device__ __forceinline__ f64x2 pair_at(const double* p) { return *reinterpret_cast<const f64x2_8*>(p); }   // two in a row, 8-byte aligned
 
-// H = 2 X X^T, tiles on and above the diagonal, mirrored.
-__global__ void __launch_bounds__(256) hessian_kernel(const double* __restrict__ X, int n, int d, double* __restrict__ H) {
-  __shared__ Stage S;
-  const int bi = blockIdx.y, bj = blockIdx.x;
-  if (bj < bi) return;
-  const int i0 = bi * NB, j0 = bj * NB;
-  Tile acc = {};
-  auto fa = [&](int i, int k) { return (i0 + i < n && k < d) ? X[(size_t)(i0 + i) * d + k] : 0.0; };
-  auto fb = [&](int j, int k) { return (j0 + j < n && k < d) ? X[(size_t)(j0 + j) * d + k] : 0.0; };
-  tile_nt(acc, d, fa, fb, S);
+// Number of a cell of an upper triangle (row by row, `side` cells in the first) -> row and column.
+__device__ __forceinline__ void upper_cell(int at, int side, int* row, int* col) {
+  int r = 0;
+  for (int left = side; at >= left; --left, ++r) at -= left;
+  *row = r;
+  *col = r + at;
+}
+
+// H = 2 X X^T, tiles on and above the diagonal, mirrored.  Squares of SQ x SQ tiles, a run of them for each of the 8 XCDs
+// (workgroups go to the XCDs in turn): the tiles that run side by side on an XCD share rows of X in its L2.
+constexpr int SQ = 2;
+__global__ void __launch_bounds__(256) hessian_kernel(const double* __restrict__ X, int n, int d, double* __restrict__ H, int squares, int run) {
+  __shared__ Stage<2, 2> S;
+  const int xcd = blockIdx.x % 8, at = blockIdx.x / 8, square = xcd * run + at / (SQ * SQ), side = (n + SQ * NB - 1) / (SQ * NB);
+  if (square >= squares) return;             // workgroup-uniform
+  int sr, sc;
+  upper_cell(square, side, &sr, &sc);
+  const int i0 = (sr * SQ + at % (SQ * SQ) / SQ) * NB, j0 = (sc * SQ + at % SQ) * NB;
+  if (j0 < i0 || j0 >= n) return;            // below the diagonal or behind the matrix
+  Tile<2, 2> acc = {};
+  auto get = [&](int row, int k) {           // (rows behind the last: the last, their sums are not written)
+    const double* x = X + (size_t)min(row, n - 1) * d + k;
+    if (k + 1 < d) return pair_at(x);
+    return f64x2{k < d ? *x : 0.0, 0.0};
+  };
+  tile_product<false>(acc, 0, d, [&](int i, int k) { return get(i0 + i, k); }, [&](int j, int k) { return get(j0 + j, k); }, S);
   each_element(acc, [&](int r, int c, double v) {
     const int i = i0 + r, j = j0 + c;
-    if (i < n && j < n) {
+    if (i <= j && j < n) {
       H[(size_t)i * n + j] = 2.0 * v;
-      if (bi != bj) H[(size_t)j * n + i] = 2.0 * v;
+      H[(size_t)j * n + i] = 2.0 * v;
     }
   });
 }
@@ -168,15 +181,16 @@ __device__ __forceinline__ double rsqrt_f64(double x, double* root) {
 // doubling: the four diagonal blocks of 16 at once, a wavefront each, then 16 -> 32 -> 64 as products of blocks.  (One
 // wavefront for all 64 columns and the inverse took 51 us: 2016 updates and as many LDS reads in one chain, and a
 // division and a square root per step.)
-__global__ void __launch_bounds__(256) potrf_diag_kernel(double* __restrict__ L, int np, int kb, double* __restrict__ Dinv) {
-  constexpr int DP = NB + 2;
-  __shared__ double D[NB][DP], X[NB][DP], T[32][34], rd[NB];     // block, inverse, a product between, 1 / diagonal
+struct Diagonal {                            // block, inverse, a product between, 1 / diagonal
+  static constexpr int DP = NB + 2;
+  double D[NB][DP], X[NB][DP], T[32][34], rd[NB];
+};
+// `S.D` holds the block; every thread of the workgroup.
+__device__ __forceinline__ void potrf_diag(Diagonal& S, double* __restrict__ L, int np, int kb, double* __restrict__ Dinv) {
+  double (&D)[NB][Diagonal::DP] = S.D, (&X)[NB][Diagonal::DP] = S.X, (&T)[32][34] = S.T, (&rd)[NB] = S.rd;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, i16 = lane & 15, g4 = lane >> 4;
   double* blk = L + (size_t)kb * NB * np + (size_t)kb * NB;
-  for (int idx = tid; idx < NB * NB; idx += 256) {
-    D[idx >> 6][idx & 63] = blk[(size_t)(idx >> 6) * np + (idx & 63)];
-    X[idx >> 6][idx & 63] = 0.0;
-  }
+  for (int idx = tid; idx < NB * NB; idx += 256) X[idx >> 6][idx & 63] = 0.0;
   __syncthreads();
   for (int p = 0; p < 4; ++p) {              // panel of columns c0 .. c0 + 15
     const int c0 = 16 * p;
@@ -258,32 +272,52 @@ __global__ void __launch_bounds__(256) potrf_diag_kernel(double* __restrict__ L,
   for (int idx = tid; idx < NB * NB; idx += 256) inv[idx] = X[idx >> 6][idx & 63];
 }
 
+// The first diagonal block.
+__global__ void __launch_bounds__(256) potrf_first_kernel(double* __restrict__ L, int np, double* __restrict__ Dinv) {
+  __shared__ Diagonal S;
+  for (int idx = threadIdx.x; idx < NB * NB; idx += 256) S.D[idx >> 6][idx & 63] = L[(size_t)(idx >> 6) * np + (idx & 63)];
+  __syncthreads();
+  potrf_diag(S, L, np, 0, Dinv);
+}
+
 // Panel below diagonal block kb: A[ib, kb] <- A[ib, kb] . inv(L_kk)^T
 __global__ void __launch_bounds__(256) trsm_panel_kernel(double* __restrict__ L, int np, int kb, const double* __restrict__ Dinv) {
-  __shared__ Stage S;
+  __shared__ Stage<2, 2> S;
   const int ib = kb + 1 + blockIdx.x;
   double* blk = L + (size_t)ib * NB * np + (size_t)kb * NB;
   const double* inv = Dinv + (size_t)kb * NB * NB;
-  Tile acc = {};
-  auto fa = [&](int r, int k) { return blk[(size_t)r * np + k]; };
-  auto fb = [&](int c, int k) { return inv[c * NB + k]; };
-  tile_nt(acc, NB, fa, fb, S);          // every read of the block is done when tile_nt returns
+  Tile<2, 2> acc = {};
+  auto fa = [&](int r, int k) { return pair_at(blk + (size_t)r * np + k); };
+  auto fb = [&](int c, int k) { return pair_at(inv + c * NB + k); };
+  tile_product<false>(acc, 0, NB, fa, fb, S);           // every read of the block is done when it returns
   each_element(acc, [&](int r, int c, double v) { blk[(size_t)r * np + c] = v; });
 }
 
-// Trailing update: A[ib, jb] -= P_ib . P_jb^T for kb < jb <= ib.
-__global__ void __launch_bounds__(256) syrk_kernel(double* __restrict__ L, int np, int kb) {
-  __shared__ Stage S;
-  const int ib = kb + 1 + blockIdx.y, jb = kb + 1 + blockIdx.x;
-  if (jb > ib) return;
+// Trailing update: A[ib, jb] -= P_ib . P_jb^T for kb < jb <= ib, tile by tile of the lower triangle.  The first workgroup's is the
+// next diagonal block, which it then factorises: a launch lasts as long as the longer of the two, and the chain of block
+// columns is this launch and the panel's (n = 4096: 64 of 47 us, diagonal block, panel and update one after the other).
+__global__ void __launch_bounds__(256) update_kernel(double* __restrict__ L, int np, int kb, double* __restrict__ Dinv) {
+  union Shared { Stage<2, 2> stage; Diagonal diagonal; };
+  __shared__ Shared S;
+  // tile number -> (row, column) of the lower triangle: row (row + 1) / 2 tiles stand before a row's first
+  int row = (int)((sqrtf(8.0f * (float)blockIdx.x + 1.0f) - 1.0f) * 0.5f);
+  while (row * (row + 1) / 2 > (int)blockIdx.x) --row;
+  while ((row + 1) * (row + 2) / 2 <= (int)blockIdx.x) ++row;
+  const int ib = kb + 1 + row, jb = kb + 1 + (int)blockIdx.x - row * (row + 1) / 2;
   const double* pi = L + (size_t)ib * NB * np + (size_t)kb * NB;
   const double* pj = L + (size_t)jb * NB * np + (size_t)kb * NB;
-  Tile acc = {};
-  auto fa = [&](int r, int k) { return pi[(size_t)r * np + k]; };
-  auto fb = [&](int c, int k) { return pj[(size_t)c * np + k]; };
-  tile_nt(acc, NB, fa, fb, S);
+  Tile<2, 2> acc = {};
+  auto fa = [&](int r, int k) { return pair_at(pi + (size_t)r * np + k); };
+  auto fb = [&](int c, int k) { return pair_at(pj + (size_t)c * np + k); };
+  tile_product<false>(acc, 0, NB, fa, fb, S.stage);
   double* blk = L + (size_t)ib * NB * np + (size_t)jb * NB;
-  each_element(acc, [&](int r, int c, double v) { blk[(size_t)r * np + c] -= v; });
+  if (blockIdx.x > 0) {                      // workgroup-uniform
+    each_element(acc, [&](int r, int c, double v) { blk[(size_t)r * np + c] -= v; });
+    return;
+  }
+  each_element(acc, [&](int r, int c, double v) { S.diagonal.D[r][c] = blk[(size_t)r * np + c] - v; });   // (the product is over: a barrier ends it)
+  __syncthreads();
+  potrf_diag(S.diagonal, L, np, kb + 1, Dinv);
 }
 
 // Element (r, c), r >= c, of the inverse as far as it is built: the diagonal 64-blocks live in Dinv, the blocks
@@ -295,34 +329,41 @@ __device__ __forceinline__ double inverse_at(const double* __restrict__ L, const
   return rb > cb ? L[(size_t)r * np + c] : 0.0;
 }
 
+// Elements (r, c) and (r, c + 1), c even.
+__device__ __forceinline__ f64x2 inverse_pair(const double* __restrict__ L, const double* __restrict__ Dinv, int np, int r, int c) {
+  const int rb = r >> 6, cb = c >> 6;
+  if (rb == cb) return pair_at(Dinv + (size_t)rb * NB * NB + (r & 63) * NB + (c & 63));
+  return rb > cb ? pair_at(L + (size_t)r * np + c) : f64x2{0.0, 0.0};
+}
+
 // Level with diagonal blocks of `b` rows: pair p joins A = [2pb, 2pb + b) and B = [2pb + b, min(2pb + 2b, np)).
 // Step 1: T = C . A^-1 into `T` (at C's place);  C = L[B rows, A columns].
 __global__ void __launch_bounds__(256) trtri_step1_kernel(const double* __restrict__ L, const double* __restrict__ Dinv,
                                                          int np, int b, double* __restrict__ T) {
-  __shared__ Stage S;
+  __shared__ Stage<2, 2> S;
   const int a0 = 2 * b * blockIdx.z, b0 = a0 + b;
   const int i0 = b0 + blockIdx.y * NB, j0 = blockIdx.x * NB;        // tile: rows i0.. (in B), columns a0 + j0.. (in A)
   if (i0 >= np) return;                                              // B is shorter than b, or missing
-  Tile acc = {};
-  auto fa = [&](int i, int k) { return L[(size_t)(i0 + i) * np + a0 + k]; };
-  auto fb = [&](int k, int j) { return inverse_at(L, Dinv, np, a0 + k, a0 + j0 + j); };
-  tile_nn(acc, j0, b, fa, fb, S);                               // A^-1 is lower triangular: rows k >= j0 only
+  Tile<2, 2> acc = {};
+  auto fa = [&](int i, int k) { return pair_at(L + (size_t)(i0 + i) * np + a0 + k); };
+  auto fb = [&](int j, int k) { return f64x2{inverse_at(L, Dinv, np, a0 + k, a0 + j0 + j), inverse_at(L, Dinv, np, a0 + k + 1, a0 + j0 + j)}; };
+  tile_product<true>(acc, j0, b, fa, fb, S);                    // A^-1 is lower triangular: rows k >= j0 only
   each_element(acc, [&](int r, int c, double v) { T[(size_t)(i0 + r) * np + a0 + j0 + c] = v; });
 }
 
 // Step 2: -B^-1 . T over C.
 __global__ void __launch_bounds__(256) trtri_step2_kernel(double* __restrict__ L, const double* __restrict__ Dinv, int np,
                                                          int b, const double* __restrict__ T) {
-  __shared__ Stage S;
+  __shared__ Stage<2, 2> S;
   const int a0 = 2 * b * blockIdx.z, b0 = a0 + b;
   const int i0 = blockIdx.y * NB, j0 = blockIdx.x * NB;              // tile: rows b0 + i0.., columns a0 + j0..
   if (b0 + i0 >= np) return;
-  Tile acc = {};
+  Tile<2, 2> acc = {};
   // B^-1 (lower triangular, rows / columns relative to b0): its blocks left of the diagonal were written by the
   // lower levels, which are complete; this level writes blocks of C only
-  auto fa = [&](int i, int k) { return inverse_at(L, Dinv, np, b0 + i0 + i, b0 + k); };
-  auto fb = [&](int k, int j) { return T[(size_t)(b0 + k) * np + a0 + j0 + j]; };
-  tile_nn(acc, 0, i0 + NB, fa, fb, S);
+  auto fa = [&](int i, int k) { return inverse_pair(L, Dinv, np, b0 + i0 + i, b0 + k); };
+  auto fb = [&](int j, int k) { return f64x2{T[(size_t)(b0 + k) * np + a0 + j0 + j], T[(size_t)(b0 + k + 1) * np + a0 + j0 + j]}; };
+  tile_product<true>(acc, 0, i0 + NB, fa, fb, S);
   each_element(acc, [&](int r, int c, double v) { L[(size_t)(b0 + i0 + r) * np + a0 + j0 + c] = -v; });
 }
 
@@ -343,8 +384,9 @@ int spqr_hessian(const double* X, int32_t n, int32_t d, double* H, void* stream)
   if (!X || !H) return SPQR_ERR_NULL;
   if (n < 1 || d < 1) return SPQR_ERR_SHAPE;
   if (reinterpret_cast<uintptr_t>(X) % 8 != 0 || reinterpret_cast<uintptr_t>(H) % 8 != 0) return SPQR_ERR_ALIGN;
-  const int nb = (n + NB - 1) / NB;
-  hipLaunchKernelGGL(hessian_kernel, dim3(nb, nb), dim3(256), 0, static_cast<hipStream_t>(stream), X, n, d, H);
+  hipStream_t st = static_cast<hipStream_t>(stream);
+  const int side = (n + SQ * NB - 1) / (SQ * NB), squares = side * (side + 1) / 2, run = (squares + 7) / 8;
+  hipLaunchKernelGGL(hessian_kernel, dim3(8 * run * SQ * SQ), dim3(256), 0, st, X, n, d, H, squares, run);
   return hipGetLastError() == hipSuccess ? SPQR_OK : SPQR_ERR_HIP;
 }
 
@@ -371,13 +413,11 @@ int spqr_inverse_cholesky(const double* H, int32_t n, double lambda, double* Hic
   double* Dinv = X + (size_t)np * np;
   const unsigned cells = (unsigned)(((size_t)np * np + 255) / 256);
   hipLaunchKernelGGL(init_reversed_kernel, dim3(cells), dim3(256), 0, st, H, n, np, lambda, L);
-  for (int kb = 0; kb < nb; ++kb) {
-    hipLaunchKernelGGL(potrf_diag_kernel, dim3(1), dim3(256), 0, st, L, np, kb, Dinv);
+  hipLaunchKernelGGL(potrf_first_kernel, dim3(1), dim3(256), 0, st, L, np, Dinv);
+  for (int kb = 0; kb + 1 < nb; ++kb) {
     const int rest = nb - kb - 1;
-    if (rest > 0) {
-      hipLaunchKernelGGL(trsm_panel_kernel, dim3(rest), dim3(256), 0, st, L, np, kb, Dinv);
-      hipLaunchKernelGGL(syrk_kernel, dim3(rest, rest), dim3(256), 0, st, L, np, kb);
-    }
+    hipLaunchKernelGGL(trsm_panel_kernel, dim3(rest), dim3(256), 0, st, L, np, kb, Dinv);
+    hipLaunchKernelGGL(update_kernel, dim3(rest * (rest + 1) / 2), dim3(256), 0, st, L, np, kb, Dinv);
   }
   for (int b = NB; b < np; b *= 2) {
     const int tiles = b / NB, pairs = (np + 2 * b - 1) / (2 * b);

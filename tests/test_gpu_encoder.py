@@ -201,3 +201,25 @@ def test_sweep_far_columns_bit_exact(E, b1, m, n):
     ref = enc.spqr_quantize(W, U, 3, b1, 8, 20.0)
     got = E.spqr_quantize(dev(W), dev(U), 3, b1, 8, 20.0)
     _compare_exact(got, ref)
+
+
+# one tile, ragged ones, a square of tiles and one more, several squares per XCD; odd depths (pairs that end behind a row)
+@pytest.mark.parametrize("n,d", [(1, 1), (63, 5), (65, 129), (128, 64), (130, 33), (449, 1000), (1157, 17)])
+def test_hessian_and_factor_at_the_edges_of_tiles_and_squares(n, d):
+    """Sums of d products against torch's: d roundings of 2^-53 of the sum of the magnitudes each way.  H is symmetric to the
+    bit.  U: the residual of U^T U (H + lambda I) is n roundings of the condition number at most."""
+    import torch
+    import paper_2306_03078_amd.encode_binding as E
+    g = torch.Generator(device="cuda")
+    g.manual_seed(n + d)
+    X = torch.randn((n, d), generator=g, dtype=torch.float64, device="cuda")
+    H = E.spqr_hessian(X)
+    assert torch.equal(H, H.T)
+    bound = 2 * d * 2.0 ** -53 * (2 * X.abs() @ X.abs().T)
+    assert bool(((H - 2 * X @ X.T).abs() <= bound).all())
+    lam = float(H.diagonal().mean()) * 0.5
+    U = E.spqr_inverse_cholesky(H, lam)
+    assert bool((U.tril(-1) == 0).all())
+    A = H + lam * torch.eye(n, dtype=torch.float64, device="cuda")
+    cond = float(torch.linalg.norm(A, 2) / lam)
+    assert float((U.T @ U @ A - torch.eye(n, dtype=torch.float64, device="cuda")).abs().max()) <= 4 * n * cond * 2.0 ** -53
