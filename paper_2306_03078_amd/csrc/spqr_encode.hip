@@ -340,18 +340,20 @@ __global__ void __launch_bounds__(64 * kWaves) sweep_kernel(SweepArgs a) {
 // The sweep for layers of up to 4096 rows (and beta2 <= 16): a workgroup of 8 wavefronts owns 16 rows, so 4096 rows have
 // a workgroup per CU where 64 rows each would leave three of four idle.  The working copy is row-major.
 //   chain     the first wavefront alone, a lane per row (its four groups of 16 lanes do the same), 16 of the block's columns
-//             in registers: the steps of a column depend on one another, nothing is read from LDS but H^ic
+//             in registers: the steps of a column depend on one another
 //   feedback  lanes = columns, a wavefront takes up to 256 columns of all 16 rows (64 sums a lane, far_feedback)
 // Same operations in the same order on every weight as sweep_kernel, hence the same bits.
 // Bound: binary64 issue of the feedback (m n^2 products and differences) next to the chain (n columns, two true
-// divisions each, one after the other).
+// divisions each, one after the other).  4096^2 with blocks of 16, measured part by part: far feedback 3.3 ms (2.1 at the
+// issue rate of its products and differences, 9.5 clocks a pair), chain 1.9 (7.5 us a block), tests 0.9, the rest 0.6.
 // ---------------------------------------------------------------------------
-constexpr int kRows16 = 16, kWaves16 = 8;
+constexpr int kRows16 = 16, kWaves16 = 8, kSuper16 = 128;
 
 // Line 16 for the columns k0 + 64 c + lane, c < C, of the workgroup's rows: W[:, k] -= E[:, j] * H^ic[sb + j, k] for all sbw columns
 // j of the super-block, in order.  A lane holds 16 rows of C columns: the errors are LDS broadcasts (eight reads of 16 bytes
 // per column j whatever C is: with one column a lane they are what the pass waits for, two are even with the arithmetic),
-// H^ic comes straight from memory, four j ahead.  4096^2: 7.8 of the sweep's 11.0 ms with one column a lane, 4.3 of 7.5 with four.
+// H^ic comes straight from memory, four j ahead.  4096^2: 7.8 of the sweep's 11.0 ms with one column a lane, 4.3 of 7.5 with four,
+// 3.3 of 6.9 with super-blocks of 128 columns (half the trips of W to memory and back) and even shares.
 template <int C>
 __device__ __forceinline__ void far_feedback(double* __restrict__ W, const double* __restrict__ U, int n, int row0, int rows, int lane,
                                              int sb, int sbw, int k0, const double (*esb)[kRows16]) {
@@ -371,6 +373,12 @@ __device__ __forceinline__ void far_feedback(double* __restrict__ W, const doubl
   for (int r = 0; r < kRows16; ++r)
 #pragma unroll
     for (int c = 0; c < C; ++c) cur[c][r] = at(W + (size_t)(row0 + min(r, rows - 1)) * n, c);
+  // pairs of errors, AHEAD of them on their way (the last ones read behind the errors, into what follows them in LDS)
+  constexpr int AHEAD = 1, PAIRS = kRows16 / 2;
+  const f64x2* pe = reinterpret_cast<const f64x2*>(&esb[0][0]);
+  f64x2 e[AHEAD + 1];
+#pragma unroll
+  for (int t = 0; t < AHEAD; ++t) e[t] = pe[t];
 #pragma unroll 1
   for (int j = 0; j < sbw; j += PF) {
     if (j + PF < sbw) uj += (size_t)PF * n;              // behind the last four: the same ones again, unused
@@ -381,15 +389,18 @@ __device__ __forceinline__ void far_feedback(double* __restrict__ W, const doubl
 #pragma unroll
     for (int q = 0; q < PF; ++q) {
 #pragma unroll
-      for (int r = 0; r < kRows16; r += 2) {
-        const f64x2 e = *reinterpret_cast<const f64x2*>(&esb[j + q][r]);
+      for (int h = 0; h < PAIRS; ++h) {
+        const int t = q * PAIRS + h;
+        e[(t + AHEAD) % (AHEAD + 1)] = pe[t + AHEAD];
 #pragma unroll
         for (int c = 0; c < C; ++c) {
-          cur[c][r] = cur[c][r] - e.x * u[q][c];
-          cur[c][r + 1] = cur[c][r + 1] - e.y * u[q][c];
+          cur[c][2 * h] = cur[c][2 * h] - e[t % (AHEAD + 1)].x * u[q][c];
+          cur[c][2 * h + 1] = cur[c][2 * h + 1] - e[t % (AHEAD + 1)].y * u[q][c];
         }
+        __builtin_amdgcn_sched_barrier(0);
       }
     }
+    pe += PF * PAIRS;
 #pragma unroll
     for (int q = 0; q < PF; ++q)
 #pragma unroll
@@ -405,59 +416,66 @@ __device__ __forceinline__ void far_feedback(double* __restrict__ W, const doubl
   }
 }
 
+// A super-block's columns of the workgroup's rows and its corner of H^ic stay in LDS from its first block to its last, so that a
+// block waits for no memory (three trips of it a block before: 4096^2 7.45 -> 6.65 ms with all that is said above, 256 x 4064
+// 10.0 -> 6.2 against one column a lane).  The corner: for each block of B1 rows the columns from its own diagonal on, block after block.
 template <int B1> struct Sweep16Lds {
-  double esb[kSuper][kRows16];                           // errors E of the current super-block's columns
-  double wbs[B1][kRows16];                               // the block's columns, for the tests
-  double ublk[B1][B1];                                   // the block's corner of H^ic
-  uint32_t omask[kRows16];
+  double esb[kSuper16][kRows16];                         // errors E of the current super-block's columns
+  double wsb[kSuper16][kRows16 + 1];                     // its weights (the 1: banks)
+  double corner[(kSuper16 / B1 + 1) * kSuper16 * B1 / 2];
+  double err[B1 + 1][kRows16];                           // summed error of the group, whole and without each column
 };
+template <int B1> constexpr int corner_at(int g) { return B1 * (g * kSuper16 - B1 * (g * (g - 1) / 2)); }   // block g's rows of kSuper16 - g B1
+static_assert(corner_at<16>(kSuper16 / 16) == (kSuper16 / 16 + 1) * kSuper16 * 16 / 2, "all of the blocks");
 
 template <int B1>
 __global__ void __launch_bounds__(64 * kWaves16, 2) sweep16_kernel(SweepArgs a) {
-  __shared__ Sweep16Lds<B1> S;
-  typedef double f64x2 __attribute__((ext_vector_type(2)));
+  extern __shared__ __align__(16) uint8_t lds[];
+  Sweep16Lds<B1>& S = *reinterpret_cast<Sweep16Lds<B1>*>(lds);
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int m = a.m, n = a.n, row0 = blockIdx.x * kRows16, rows = min(kRows16, m - row0);   // a tile is inside or outside
   const int ng = n / B1;
   const double* __restrict__ U = a.U;
   double* __restrict__ W = a.Wt;                         // row-major here
 
-  for (int sb = 0; sb < n; sb += kSuper) {
-    const int sbw = min(kSuper, n - sb);
-    for (int i = sb; i < sb + sbw; i += B1) {
-      const int g = i / B1;
-      for (int idx = tid; idx < B1 * B1; idx += 64 * kWaves16) S.ublk[idx / B1][idx % B1] = U[(size_t)(i + idx / B1) * n + i + idx % B1];
-      for (int idx = tid; idx < B1 * kRows16; idx += 64 * kWaves16)        // rows behind the last one shadow it
-        S.wbs[idx % B1][idx / B1] = W[(size_t)(row0 + min(idx / B1, rows - 1)) * n + i + idx % B1];
-      if (tid < kRows16) S.omask[tid] = 0;
-      __syncthreads();
-
-      // ---- outliers(): a thread per leave-one-out test (line 8) ----
-      if (a.tau < INFINITY) {
-        for (int idx = tid; idx < B1 * kRows16; idx += 64 * kWaves16) {
-          const int r = idx & 15, cand = idx >> 4;
-          auto group_error = [&](int x) -> double {      // summed error of the group without column x (-1: all columns)
-            double lo = INFINITY, hi = -INFINITY;
+  for (int sb = 0; sb < n; sb += kSuper16) {
+    const int sbw = min(kSuper16, n - sb);
 #pragma unroll 4
-            for (int c = 0; c < B1; ++c) {
-              const double v = S.wbs[c][r];
-              if (c != x) { lo = fmin(lo, v); hi = fmax(hi, v); }
-            }
-            double s, z;
-            fit_from_range(lo, hi, a.w_top, &s, &z);
-            double t = 0.0;
-#pragma unroll 2
-            for (int c = 0; c < B1; ++c) {
-              if (c != x) {
-                const double v = S.wbs[c][r];
-                const double e = (v - s * (quantize(v, s, z, a.w_top) - z)) / S.ublk[c][c];
-                t = t + e * e;
-              }
-            }
-            return t;
-          };
-          const double base = group_error(-1);
-          if ((base - group_error(cand)) > a.tau) atomicOr(&S.omask[r], 1u << cand);
+    for (int j = wave; j < sbw; j += kWaves16) {
+      const int g = j / B1;
+      double* to = S.corner + corner_at<B1>(g) + (j % B1) * (kSuper16 - g * B1) - g * B1;
+#pragma unroll
+      for (int k = 0; k < kSuper16; k += 64)
+        if (k + lane >= g * B1 && k + lane < sbw) to[k + lane] = U[(size_t)(sb + j) * n + sb + k + lane];
+    }
+#pragma unroll
+    for (int r = tid / kSuper16; r < kRows16; r += 64 * kWaves16 / kSuper16)           // rows behind the last one shadow it
+      if (tid % kSuper16 < sbw) S.wsb[tid % kSuper16][r] = W[(size_t)(row0 + min(r, rows - 1)) * n + sb + tid % kSuper16];
+    __syncthreads();
+    for (int i = sb; i < sb + sbw; i += B1) {
+      const int g = i / B1, ib = i - sb, width = kSuper16 - ib;
+      const double* ublk = S.corner + corner_at<B1>(ib / B1);              // rows i .., columns i ..
+
+      // ---- outliers(): a thread per leave-one-out test (line 8), and one for the whole group ----
+      if (a.tau < INFINITY) {
+        for (int idx = tid; idx < (B1 + 1) * kRows16; idx += 64 * kWaves16) {
+          const int r = idx & 15, x = (idx >> 4) - 1;    // without column x (-1: all columns)
+          double lo = INFINITY, hi = -INFINITY;
+#pragma unroll 4
+          for (int c = 0; c < B1; ++c) {
+            const double v = S.wsb[ib + c][r];
+            if (c != x) { lo = fmin(lo, v); hi = fmax(hi, v); }
+          }
+          double s, z;
+          fit_from_range(lo, hi, a.w_top, &s, &z);
+          double t = 0.0;
+#pragma unroll 4
+          for (int c = 0; c < B1; ++c) {
+            const double v = S.wsb[ib + c][r];
+            const double e = (v - s * (quantize(v, s, z, a.w_top) - z)) / ublk[c * width + c];
+            t = c != x ? t + e * e : t;
+          }
+          S.err[x + 1][r] = t;
         }
         __syncthreads();
       }
@@ -465,7 +483,12 @@ __global__ void __launch_bounds__(64 * kWaves16, 2) sweep16_kernel(SweepArgs a) 
       // ---- fit_statistics() (line 9) and lines 10-15 ----
       if (wave == 0) {
         const int r = lane & 15, row = row0 + r;
-        const uint32_t om = S.omask[r];
+        uint32_t om = 0;
+        if (a.tau < INFINITY) {                          // (the four groups of lanes share the columns)
+          for (int c = lane >> 4; c < B1; c += 4) om |= (S.err[0][r] - S.err[c + 1][r]) > a.tau ? 1u << c : 0u;
+          om |= __shfl_xor(om, 16, 64);
+          om |= __shfl_xor(om, 32, 64);
+        }
         double s_hat, z_hat;
         uint8_t sq, zq;
         uint16_t ssb, zsb, szb, zzb;
@@ -473,7 +496,7 @@ __global__ void __launch_bounds__(64 * kWaves16, 2) sweep16_kernel(SweepArgs a) 
           double lo = INFINITY, hi = -INFINITY;
 #pragma unroll
           for (int c = 0; c < B1; ++c) {
-            const double v = S.wbs[c][r];
+            const double v = S.wsb[ib + c][r];
             if (!((om >> c) & 1u)) { lo = fmin(lo, v); hi = fmax(hi, v); }
           }
           if (lo > hi) { lo = 0.0; hi = 0.0; }           // nothing left
@@ -497,11 +520,11 @@ __global__ void __launch_bounds__(64 * kWaves16, 2) sweep16_kernel(SweepArgs a) 
         for (int h0 = 0; h0 < B1; h0 += HB) {
           double w[HB];
 #pragma unroll
-          for (int c = 0; c < HB; ++c) w[c] = S.wbs[h0 + c][r];
+          for (int c = 0; c < HB; ++c) w[c] = S.wsb[ib + h0 + c][r];
           for (int j = 0; j < h0; ++j) {
-            const double ej = S.esb[i - sb + j][r];
+            const double ej = S.esb[ib + j][r];
 #pragma unroll
-            for (int k = 0; k < HB; ++k) w[k] = w[k] - ej * S.ublk[j][h0 + k];
+            for (int k = 0; k < HB; ++k) w[k] = w[k] - ej * ublk[j * width + h0 + k];
           }
           uint32_t qs[HB / 4], ms[HB / 4], vs[HB / 2];
 #pragma unroll
@@ -514,10 +537,10 @@ __global__ void __launch_bounds__(64 * kWaves16, 2) sweep16_kernel(SweepArgs a) 
             const double v = w[c];
             const double q = quantize(v, s_hat, z_hat, a.w_top);
             const double wq = s_hat * (q - z_hat);
-            const double ec = (v - wq) / S.ublk[h0 + c][h0 + c] * (is_out ? 0.0 : 1.0);
-            if (lane < kRows16) S.esb[i - sb + h0 + c][r] = ec;
+            const double ec = (v - wq) / ublk[(h0 + c) * width + h0 + c] * (is_out ? 0.0 : 1.0);
+            if (lane < kRows16) S.esb[ib + h0 + c][r] = ec;
 #pragma unroll
-            for (int k = c; k < HB; ++k) w[k] = w[k] - ec * S.ublk[h0 + c][h0 + k];    // line 14, inside the block
+            for (int k = c; k < HB; ++k) w[k] = w[k] - ec * ublk[(h0 + c) * width + h0 + k];    // line 14, inside the block
             qs[c / 4] |= (uint32_t)(uint8_t)q << (8 * (c % 4));
             ms[c / 4] |= (is_out ? 1u : 0u) << (8 * (c % 4));
             vs[c / 2] |= (uint32_t)(is_out ? f64_to_f16_bits(w[c] - wq) : (uint16_t)0) << (16 * (c % 2));
@@ -537,42 +560,31 @@ __global__ void __launch_bounds__(64 * kWaves16, 2) sweep16_kernel(SweepArgs a) 
         }
       }
       __syncthreads();
-      // ---- line 16 for the rest of the super-block (fewer than 64 columns): two rows per wavefront ----
-      {
-        const int k = i + B1 + lane;
-        if (k < sb + sbw) {
-          const int r = 2 * wave;
-          double* w0 = W + (size_t)(row0 + min(r, rows - 1)) * n + k;
-          double* w1 = W + (size_t)(row0 + min(r + 1, rows - 1)) * n + k;
-          double c0 = *w0, c1 = *w1, u[B1];
+      // ---- line 16 for the rest of the super-block: a thread per weight ----
+      for (int k = ib + B1 + (tid >> 4); k < sbw; k += 64 * kWaves16 / 16) {
+        const int r = tid & 15;
+        double c = S.wsb[k][r];
 #pragma unroll
-          for (int j = 0; j < B1; ++j) u[j] = U[(size_t)(i + j) * n + k];
-#pragma unroll
-          for (int j = 0; j < B1; ++j) {
-            const f64x2 e = *reinterpret_cast<const f64x2*>(&S.esb[i - sb + j][r]);
-            c0 = c0 - e.x * u[j];
-            c1 = c1 - e.y * u[j];
-          }
-          if (r < rows) *w0 = c0;
-          if (r + 1 < rows) *w1 = c1;
-        }
+        for (int j = 0; j < B1; ++j) c = c - S.esb[ib + j][r] * ublk[j * width + k - ib];
+        S.wsb[k][r] = c;
       }
-      __syncthreads();       // the next block's columns are complete; wbs, ublk, omask are free again
+      __syncthreads();       // the next block's columns are complete
     }
-    // ---- line 16 for everything right of the super-block: all of its errors in one pass, shared out in rounds of up to four
-    // columns a lane, rounds of equal width where the columns allow it ----
-    for (int k0 = sb + sbw; k0 < n;) {                   // workgroup-uniform
-      const int pieces = (n - k0 + 64 * kWaves16 - 1) / (64 * kWaves16), rounds = (pieces + 3) / 4;
-      const int cols = (pieces + rounds - 1) / rounds, at = k0 + 64 * cols * wave;
-      if (at < n) {                                      // wave-uniform
-        switch (cols) {
-          case 1: far_feedback<1>(W, U, n, row0, rows, lane, sb, sbw, at, S.esb); break;
-          case 2: far_feedback<2>(W, U, n, row0, rows, lane, sb, sbw, at, S.esb); break;
-          case 3: far_feedback<3>(W, U, n, row0, rows, lane, sb, sbw, at, S.esb); break;
-          default: far_feedback<4>(W, U, n, row0, rows, lane, sb, sbw, at, S.esb); break;
-        }
+    // ---- line 16 for everything right of the super-block: all of its errors in one pass.  Its columns in runs of 64, as many
+    // for each wavefront as for the others or one more (the first four, one on each SIMD, before the others), up to four of them at
+    // a time ----
+    const int chunks = (n - (sb + sbw) + 63) / 64, each = chunks / kWaves16, more = chunks % kWaves16;
+    int at = sb + sbw + 64 * (wave * each + min(wave, more));
+    for (int left = each + (wave < more ? 1 : 0); left > 0;) {             // wave-uniform
+      const int cols = left == 5 ? 3 : min(left, 4);
+      switch (cols) {
+        case 1: far_feedback<1>(W, U, n, row0, rows, lane, sb, sbw, at, S.esb); break;
+        case 2: far_feedback<2>(W, U, n, row0, rows, lane, sb, sbw, at, S.esb); break;
+        case 3: far_feedback<3>(W, U, n, row0, rows, lane, sb, sbw, at, S.esb); break;
+        default: far_feedback<4>(W, U, n, row0, rows, lane, sb, sbw, at, S.esb); break;
       }
-      k0 += 64 * kWaves16 * cols;
+      at += 64 * cols;
+      left -= cols;
     }
     __syncthreads();
   }
@@ -663,6 +675,15 @@ hipError_t launch_sweep(dim3 grid, dim3 block, hipStream_t st, const SweepArgs& 
   return hipGetLastError();
 }
 
+template <int B1>
+hipError_t launch_sweep16(int m, hipStream_t st, const SweepArgs& a) {
+  const int lds = (int)sizeof(Sweep16Lds<B1>);
+  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&sweep16_kernel<B1>), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(sweep16_kernel<B1>, dim3((m + kRows16 - 1) / kRows16), dim3(64 * kWaves16), lds, st, a);
+  return hipGetLastError();
+}
+
 }  // namespace spqr_enc
 
 extern "C" {
@@ -706,13 +727,14 @@ int spqr_quantize(const double* W, const double* Hic, int32_t m, int32_t n, int3
   if (beta2 <= kRows16 && m <= kRows16 * 256) {
     if (out->W_final) a.Wt = out->W_final;
     if (a.Wt != W) hipLaunchKernelGGL(copy_kernel, dim3(2048), dim3(256), 0, st, W, a.Wt, (size_t)m * n);
-    const dim3 grid((m + kRows16 - 1) / kRows16), block(64 * kWaves16);
+    hipError_t e = hipSuccess;
     switch (beta1) {
-      case 4: hipLaunchKernelGGL(sweep16_kernel<4>, grid, block, 0, st, a); break;
-      case 8: hipLaunchKernelGGL(sweep16_kernel<8>, grid, block, 0, st, a); break;
-      case 16: hipLaunchKernelGGL(sweep16_kernel<16>, grid, block, 0, st, a); break;
-      default: hipLaunchKernelGGL(sweep16_kernel<32>, grid, block, 0, st, a); break;
+      case 4: e = launch_sweep16<4>(m, st, a); break;
+      case 8: e = launch_sweep16<8>(m, st, a); break;
+      case 16: e = launch_sweep16<16>(m, st, a); break;
+      default: e = launch_sweep16<32>(m, st, a); break;
     }
+    if (e != hipSuccess) return SPQR_ERR_HIP;
   } else {
     const dim3 tgrid((n + 31) / 32, (m + 31) / 32);
     hipLaunchKernelGGL(transpose_kernel, tgrid, dim3(256), 0, st, W, a.Wt, m, n);
