@@ -14,6 +14,9 @@ import numpy as np
 HERE = os.path.dirname(os.path.abspath(__file__))
 _LIB_PATH = os.path.join(HERE, "libspqr.so")
 _lib = None
+_call = None                    # the extension module's call, the entries' addresses for it, torch.float16
+_entry = {}
+_half = None
 
 SPQR_F32, SPQR_F16 = 0, 1
 SPQR_CHECK_CSR, SPQR_CHECK_NONFINITE, SPQR_CHECK_PERM = 1, 2, 4
@@ -52,7 +55,7 @@ def library_path() -> str:
 
 def load_library():
     """Load libspqr.so (built in-tree by paper_2306_03078_amd.build)."""
-    global _lib
+    global _lib, _call, _half
     if _lib is not None:
         return _lib
     # PyTorch ships its own HIP runtime; importing it first makes the dynamic
@@ -101,6 +104,11 @@ def load_library():
     lib.spqr_gemv_grouped.argtypes = [C.POINTER(P), C.c_int, C.POINTER(vp), C.POINTER(vp), C.c_int, vp]
     lib.spqr_gemm_smallbatch_noalloc.restype = C.c_int
     lib.spqr_gemm_smallbatch_noalloc.argtypes = [P, vp, C.c_int, vp, C.c_int, vp]
+    from . import _calls
+    for name in ("spqr_gemv", "spqr_gemm_smallbatch", "spqr_gemm_smallbatch_ws"):
+        _entry[name] = C.cast(getattr(lib, name), C.c_void_p).value
+    _call = _calls.call
+    _half = torch.float16
     _lib = lib
     return lib
 
@@ -156,9 +164,15 @@ def pack_host(fmt) -> np.ndarray:
 
 
 def _stream_ptr(stream) -> Optional[int]:
+    """The HIP stream as an address; None: torch's current stream of the current device (by the raw calls where this torch has
+    them: a stream object for every launch costs as much as the launch)."""
+    if stream is not None:
+        return stream.cuda_stream
     import torch
-    s = torch.cuda.current_stream() if stream is None else stream
-    return C.c_void_p(s.cuda_stream)
+    c = torch._C
+    if hasattr(c, "_cuda_getCurrentRawStream") and hasattr(c, "_cuda_getDevice") and torch.cuda.is_initialized():
+        return c._cuda_getCurrentRawStream(c._cuda_getDevice())
+    return torch.cuda.current_stream().cuda_stream
 
 
 class SpQRMatrix:
@@ -235,12 +249,15 @@ def _out_dtype(y_dtype):
 
 def spqr_gemv(A: SpQRMatrix, x, out=None, y_dtype: int = SPQR_F32, stream=None):
     """y[m] = W_hat . x, x: float16 device tensor [n]."""
-    import torch
-    assert x.dtype == torch.float16 and x.is_contiguous() and x.numel() == A.n
+    if _lib is None:
+        load_library()
+    assert x.dtype == _half and x.is_contiguous() and x.numel() == A.n
     if out is None:
+        import torch
         out = torch.empty(A.m, dtype=_out_dtype(y_dtype), device=x.device)
-    _check(load_library().spqr_gemv(C.byref(A.desc), x.data_ptr(), out.data_ptr(), y_dtype,
-                                    _stream_ptr(stream)), "spqr_gemv")
+    rc = _call(_entry["spqr_gemv"], A.desc, x, out, y_dtype, _stream_ptr(stream))
+    if rc != 0:
+        _check(rc, "spqr_gemv")
     return out
 
 
@@ -251,8 +268,9 @@ def spqr_gemm_smallbatch(A: SpQRMatrix, X, out=None, y_dtype: int = SPQR_F32, st
     b = int(X.shape[0])
     if out is None:
         out = torch.empty((b, A.m), dtype=_out_dtype(y_dtype), device=X.device)
-    _check(load_library().spqr_gemm_smallbatch(C.byref(A.desc), X.data_ptr(), b, out.data_ptr(),
-                                               y_dtype, _stream_ptr(stream)), "spqr_gemm_smallbatch")
+    if _lib is None:
+        load_library()
+    _check(_call(_entry["spqr_gemm_smallbatch"], A.desc, X, b, out, y_dtype, _stream_ptr(stream)), "spqr_gemm_smallbatch")
     return out
 
 
@@ -317,8 +335,9 @@ def spqr_gemm_smallbatch_ws(A: SpQRMatrix, X, workspace, out=None, y_dtype: int 
     if out is None:
         out = torch.empty((b, A.m), dtype=_out_dtype(y_dtype), device=X.device)
     wp, wb = _ws_args(workspace)
-    _check(load_library().spqr_gemm_smallbatch_ws(C.byref(A.desc), X.data_ptr(), b, out.data_ptr(), y_dtype, wp, wb,
-                                                  _stream_ptr(stream)), "spqr_gemm_smallbatch_ws")
+    if _lib is None:
+        load_library()
+    _check(_call(_entry["spqr_gemm_smallbatch_ws"], A.desc, X, b, out, y_dtype, wp, wb, _stream_ptr(stream)), "spqr_gemm_smallbatch_ws")
     return out
 
 

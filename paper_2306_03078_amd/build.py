@@ -1,14 +1,17 @@
-"""Builds libspqr.so (HIP, gfx950) in-tree with hipcc: one object per source, compiled side by side, then linked."""
+"""Builds libspqr.so (HIP, gfx950) in-tree with hipcc: one object per source, compiled side by side, then linked; and the
+extension module through which Python calls it (host code only)."""
 from __future__ import annotations
 
 import os
 import subprocess
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libspqr.so")
+CALLS = os.path.join(HERE, "_calls" + sysconfig.get_config_var("EXT_SUFFIX"))
 SOURCES = ["spqr_pack.cpp", "spqr_api.hip", "spqr_dispatch.hip", "spqr_gemv.hip", "spqr_gemv_l1.hip", "spqr_gemv_l1w.hip", "spqr_gemv_l2.hip", "spqr_gemv_l3.hip", "spqr_mfma.hip", "spqr_prompt.hip", "spqr_prefill.hip", "spqr_misc.hip", "spqr_encode.hip", "spqr_factor.hip", "spqr_order.hip"]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
          # packed-FP32 VALU forms are kept out of the generated code on purpose
@@ -22,7 +25,7 @@ def _run(cmd, verbose):
         print(res.stdout)
         print("\n".join(l for l in res.stderr.splitlines() if "packed-fp32-ops" not in l))
     if res.returncode != 0:
-        raise RuntimeError("hipcc failed: " + " ".join(cmd[-3:]))
+        raise RuntimeError("the compiler failed: " + " ".join(cmd[-3:]))
 
 
 def build_library(verbose: bool = False) -> str:
@@ -33,6 +36,8 @@ def build_library(verbose: bool = False) -> str:
     with ThreadPoolExecutor(max_workers=min(len(jobs), os.cpu_count() or 1, 8)) as pool:
         list(pool.map(lambda c: _run(c, verbose), jobs))
     _run([hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB, *objs], verbose)
+    _run(["gcc", "-O2", "-Wall", "-shared", "-fPIC", "-I" + sysconfig.get_paths()["include"], "-o", CALLS,
+          os.path.join(CSRC, "spqr_calls.c")], verbose)
     return LIB
 
 

@@ -405,3 +405,25 @@ def test_workspace_of_the_one_pass_kernel_holds_no_dense_copy():
 def test_sizes_of_the_one_pass_kernel(m, n, w, b1, b2, b, one_pass):
     """Where the dense copy is faster, the batch takes the copy, and its scratch holds one: 2 bytes per weight."""
     assert (_workspace_bytes(m, n, w, b1, b2, 1, 0.01, b) < 2 * m * n) == one_pass
+
+
+def test_direct_calls_take_tensors_by_address_and_refuse_what_they_cannot_pass():
+    """The extension module's call: a one-element integer tensor is an address like any other, not the number it holds;
+    statuses come back as they are; nothing else than integers, tensors and None is passed."""
+    import torch
+    from paper_2306_03078_amd import binding as B
+    B.load_library()
+    d, one = B.spqr_matrix_t(), torch.tensor([7])
+    seen = []
+
+    @C.CFUNCTYPE(C.c_int, *[C.c_int64] * 8)
+    def entry(*args):
+        seen.append(args)
+        return -5
+    address = C.cast(entry, C.c_void_p).value
+    assert B._call(address, d, one, None, np.int32(3), -2, 2 ** 63 + 5) == -5
+    assert seen == [(C.addressof(d), one.data_ptr(), 0, 3, -2, 2 ** 63 + 5 - 2 ** 64, 0, 0)]
+    for bad in ((address,), (address, 5), (address, d, "x"), (address, d, 1.5), (address, d) + (0,) * 8):
+        with pytest.raises(TypeError):
+            B._call(*bad)
+    assert B._call(B._entry["spqr_gemv"], d, one, one, 0, None) == -3      # refused before any HIP call
