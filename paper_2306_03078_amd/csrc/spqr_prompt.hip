@@ -52,8 +52,11 @@ __device__ __forceinline__ int find_item(const PromptSet& S, int& group) {   // 
 // (16 bits) and its value.  A counting sort in two kernels over chunks of kSortChunk entries, each with a slot of `counts`
 // (spqr_sort.h).
 // ---------------------------------------------------------------------------
-constexpr int kSortThreads = 1024, kSortPer = kSortChunk / kSortThreads, kSortMaxPhases = 512, kSortMaxBins = 4 * kSortMaxPhases;
-constexpr int kSortWgs = 4;                  // workgroups per group; each takes every 4th chunk
+constexpr int kSortThreads = 512, kSortPer = kSortChunk / kSortThreads, kSortMaxPhases = 512, kSortMaxBins = 4 * kSortMaxPhases;
+// Workgroups per group, each takes every 4th chunk.  The kernels are trips to memory one after the other, so the entries of a
+// thread are few (512 threads: 11008 x 4096 twice, 5.8 and 10.2 us; 256: 5.2 and 12; 1024: 6.4 and 13) and the chunks side by side
+// (17920 x 6656 with Zipf rows: 2 workgroups 11.6 and 22.6, 4 8.9 and 14.8; 8 start too many that find no chunk: 10.3 and 14.4).
+constexpr int kSortWgs = 4;
 
 // Bin of a column: a unit of 16 tile columns (1 << unit_shift columns) has kg phases of 4 bins.
 __device__ __forceinline__ int bin_of(int col, int unit_shift, int kg) {
@@ -208,7 +211,7 @@ sort_phases_kernel(PromptSet S, int unit_shift, int kg, int bins) {
 // registers and the LDS (65 KB) for a second workgroup, whose wavefronts run where this one's wait at the barrier.  A whole
 // row of units instead of a grid of groups times splits: 17920 x 6656 is 140 groups of 26 units, which no number of splits
 // deals evenly to 256 CUs.
-// Measured (the whole call with the sort, 28 and 18 us, and the sums, 10 and 5; before: groups of 256 rows, one workgroup of one
+// Measured (the whole call with the sort, 24 and 16 us, and the sums, 11 and 5; before: groups of 256 rows, one workgroup of one
 // wavefront per SIMD, a matrix at a time): 17920 x 6656, 4-bit, 256 vectors 162 -> 124 us; gate and up 11008 x 4096, 3-bit, 77
 // vectors 101 -> 63; 4096^2 at 128 vectors, which the dense copy took, 38 -> 33.
 // ---------------------------------------------------------------------------
@@ -626,7 +629,7 @@ hipError_t launch_prompt(const DevMatrix* As, int count, const uint16_t* X, int 
   hipLaunchKernelGGL(count_phases_kernel, dim3(p.groups * kSortWgs + (p.bins * blocks16 * 64 + kSortThreads - 1) / kSortThreads), dim3(kSortThreads), 0, stream, S, p.groups,
                      p.unit_shift, p.kg, p.bins, Xin, b, blocks16, XS);
   if (nnz > 0) {
-    const auto sort = p.bins <= kSortThreads ? &sort_phases_kernel<1> : &sort_phases_kernel<2>;
+    const auto sort = p.bins <= kSortThreads ? &sort_phases_kernel<1> : p.bins <= 2 * kSortThreads ? &sort_phases_kernel<2> : &sort_phases_kernel<4>;
     hipLaunchKernelGGL(sort, dim3(p.groups, kSortWgs), dim3(kSortThreads), 0, stream, S, p.unit_shift, p.kg, p.bins);
   }
   if ((e = hipGetLastError()) != hipSuccess) return e;
