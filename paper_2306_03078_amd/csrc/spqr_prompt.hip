@@ -5,6 +5,7 @@
 #include <hip/hip_runtime.h>
 #include <algorithm>
 #include <cstdint>
+#include <numeric>
 
 #include "../../include/spqr.h"
 #include "spqr_batch.h"
@@ -459,15 +460,9 @@ constexpr int kWidthCount = sizeof(kWidths) / sizeof(kWidths[0]);
 
 struct PromptPlan { int groups, units, unit_shift, kg, bins, width, vblocks, run, runs, slots; };
 static int prompt_groups(const Geometry& g) { return (g.m + kGroupRows - 1) / kGroupRows; }
-// Partial results of a group: the most runs that a group is part of.
-static int prompt_slots(int groups, int units, int run) {
-  int most = 1;
-  for (int g = 0; g < groups && most < (units - 1) / run + 2; ++g) {
-    const int n = (g * units + units - 1) / run - g * units / run + 1;
-    most = n > most ? n : most;
-  }
-  return most;
-}
+// Partial results of a group: the most runs that a group can be part of.  Groups begin at multiples of gcd(units, run) behind a
+// run's beginning, at run - gcd at the latest.
+static int prompt_slots(int units, int run) { return (run - std::gcd(units, run) + units - 1) / run + 1; }
 // most_slots > 0: no more partial results than that.
 static PromptPlan plan_prompt(const DevMatrix* As, int count, int b, int most_slots) {
   const Geometry& g = As[0].g;
@@ -495,7 +490,7 @@ static PromptPlan plan_prompt(const DevMatrix* As, int count, int b, int most_sl
     const int vblocks = (b + c.vectors - 1) / c.vectors;
     for (int k = 1; k <= 2; ++k) {           // workgroups per CU
       const int wgs = k * kCUs / vblocks > 0 ? k * kCUs / vblocks : 1, run = std::min((total + wgs - 1) / wgs, most_run), runs = (total + run - 1) / run;
-      if (prompt_slots(p.groups, p.units, run) > most) continue;
+      if (prompt_slots(p.units, run) > most) continue;
       const double parts_us = (double)b * kGroupRows * 8 / 4e6 * (runs + p.groups);
       const int rounds = (runs + wgs - 1) / wgs;
       const double cost = rounds * (run * p.kg * (k == 1 ? c.one_us : c.two_us) + 3.0 + 0.04 * c.vectors + (k == 1 ? 0.0 : 5.0)) + parts_us;
@@ -505,7 +500,7 @@ static PromptPlan plan_prompt(const DevMatrix* As, int count, int b, int most_sl
   }
   if (pin_units >= 1) p.run = std::min(pin_units, std::min(total, most_run));
   p.runs = (total + p.run - 1) / p.run;
-  p.slots = prompt_slots(p.groups, p.units, p.run);
+  p.slots = prompt_slots(p.units, p.run);
   return p;
 }
 
