@@ -254,7 +254,11 @@ int spqr_gemv(const spqr_matrix_t* A, const uint16_t* x_f16, void* y, int y_dtyp
  * 192 vectors with them; the compressed weights are read once per that many
  * (scratch: 4 bytes per outlier, their ranges and counts, the partial sums, 64 MB
  * at most where the columns are split, b*n*2 bytes and as many again with a
- * permutation).
+ * permutation).  It rounds weight + outlier to binary16 like the dense copy below,
+ * so a call whose scratch is limited (a workspace, the static array) takes it only
+ * where it could have taken the copy, on layers that are the copy's but for their
+ * speed, and above a fixed size on the others; else the slices of 16 run, which add
+ * the outliers in binary32.  spqr_workspace_bytes reports no less than that size.
  * Other sizes, other formats (12 vectors and more; tiles of 256 codes in any layout
  * and 3-bit tiles of 8 x 64, Y 16-byte aligned) and matrices with more outliers than
  * one weight in four: the matrix is dequantised once into a dense binary16 copy in

@@ -293,6 +293,23 @@ extern "C" int spqr_plan_grouped(int count, const int32_t* m, const int32_t* n, 
   return gp.count;
 }
 
+extern "C" int spqr_batch_route(int m, int n, int64_t nnz, int has_perm, int w_bits, int beta1, int beta2, int group_axis, int b,
+                                int64_t scratch) {
+  static const int32_t some = 0;             // an address that is not null, never read
+  spqr::DevMatrix D = {};
+  if (nnz < 0 || scratch < SPQR_SCRATCH_STATIC) return SPQR_ERR_PARAM;
+  if (b < 1 || b > SPQR_MAX_BATCH) return SPQR_ERR_BATCH;
+  const int rc = spqr::make_geometry(spqr::kBilevel, m, n, w_bits, 3, 3, beta1, beta2, group_axis, &D.g);
+  if (rc) return rc;
+  D.nnz = nnz;
+  D.perm = has_perm ? &some : nullptr;
+  spqr::Workspace ws;
+  ws.from_caller = scratch != SPQR_SCRATCH_LIBRARY;
+  ws.fixed = scratch == SPQR_SCRATCH_STATIC;
+  ws.bytes = ws.fixed ? (size_t)SPQR_STATIC_SCRATCH_BYTES : scratch >= 0 ? (size_t)scratch : 0;
+  return spqr::batch_route(D, b, ws);
+}
+
 extern "C" int64_t spqr_sort_ranges(const int32_t* row_ptr, int m, int64_t nnz, int rows, int32_t* ranges) {
   if (!row_ptr || !ranges) return SPQR_ERR_NULL;
   if (m < 1 || nnz < 0 || nnz > 0x7FFFFFFFll || rows < 1) return SPQR_ERR_PARAM;

@@ -38,18 +38,14 @@ hipError_t launch_gemm(const DevMatrix& A, const uint16_t* X, int b, void* Y, in
   const bool force_generic = option(SPQR_OPT_FORCE_GENERIC) != 0;
   bool mfma_ok = !force_generic && mfma_has_instance(g);
   const bool alloc_nodes = mfma_ok && !ws.from_caller && b >= kMfmaMinBatch && stream_is_capturing(stream);
-  // A prompt-sized batch: the product straight from the compressed weights (Y as the dense copy wants it: the calls that
-  // took the copy, see prompt_wanted).
-  if (!force_generic && prompt_wanted(A, b) && reinterpret_cast<uintptr_t>(Y) % 16 == 0) {
-    const hipError_t e = launch_prompt_scratch(&A, 1, X, b, &Y, y_dtype, stream, ws);
-    if (e != hipErrorNotSupported) return e;   // no scratch of that size: the copy if the caller's holds one, or the slices
-  }
-  // Formats, sizes and outlier rates that path does not take: one dense binary16 copy of the matrix in scratch, one
-  // matrix-core multiply for all vectors.
-  if (!force_generic && prefill_has_instance(g) && prefill_wanted(A, b) &&
-      reinterpret_cast<uintptr_t>(Y) % 16 == 0) {
-    const hipError_t e = launch_prefill_scratch(A, X, b, Y, y_dtype, stream, ws);
-    if (e != hipErrorNotSupported) return e;   // no scratch of that size: the slices below
+  // A prompt-sized batch: the product straight from the compressed weights, or (formats, sizes and outlier rates that path does
+  // not take) one dense binary16 copy of the matrix in scratch and one matrix-core multiply for all vectors.  Both write Y 16
+  // bytes at a time.
+  const BatchRoute route = force_generic || reinterpret_cast<uintptr_t>(Y) % 16 != 0 ? kRouteSlices : batch_route(A, b, ws);
+  if (route != kRouteSlices) {
+    const hipError_t e = route == kRouteOnePass ? launch_prompt_scratch(&A, 1, X, b, &Y, y_dtype, stream, ws)
+                                                : launch_prefill_scratch(A, X, b, Y, y_dtype, stream, ws);
+    if (e != hipErrorNotSupported) return e;   // no library scratch of that size to be had: the slices below
   }
   int k = 0;
   while (k < b) {
@@ -74,6 +70,12 @@ hipError_t launch_gemm(const DevMatrix& A, const uint16_t* X, int b, void* Y, in
     k += done;
   }
   return hipSuccess;
+}
+
+BatchRoute batch_route(const DevMatrix& A, int b, const Workspace& ws) {
+  if (prompt_wanted(A, b) && prompt_fit(&A, 1, b, ws) >= 0) return kRouteOnePass;
+  const bool copy = prefill_has_instance(A.g) && prefill_wanted(A, b) && (!ws.from_caller || ws.bytes >= prefill_workspace_bytes(A, b));
+  return copy ? kRouteCopy : kRouteSlices;
 }
 
 // Whether launch_gemm_fused gives several matrices to the one-pass kernel together.
@@ -153,13 +155,12 @@ size_t workspace_bound(const DevMatrix* As, int count, int b, bool with_dense_co
   if (option(SPQR_OPT_FORCE_GENERIC) != 0) return 0;
   size_t worst = 0;
   // a large batch: one matrix at a time, in one pass or through the dense copy (a smaller workspace sends the call to the
-  // slices of 16; one that holds the dense copy and not what the one pass needs, to the copy)
+  // slices of 16, see prompt_line_bytes)
   if (with_dense_copy && prefill_has_instance(As[0].g))
     for (int i = 0; i < count; ++i) {
       if (!prefill_wanted(As[i], b)) continue;
-      const bool one_pass = prompt_wanted(As[i], b);
-      if (one_pass) worst = std::max(worst, prompt_workspace_bytes(&As[i], 1, b));
-      if (!one_pass || prompt_reports_copy(As[i], b)) worst = std::max(worst, prefill_workspace_bytes(As[i], b));
+      if (prompt_wanted(As[i], b)) worst = std::max({worst, prompt_workspace_bytes(&As[i], 1, b), prompt_line_bytes(As[i], b)});
+      else worst = std::max(worst, prefill_workspace_bytes(As[i], b));
     }
   if (with_dense_copy && prompt_set_wanted(As, count, b)) {
     const size_t need = prompt_workspace_bytes(As, count, b);

@@ -45,6 +45,9 @@ hipError_t launch_gemm(const DevMatrix& A, const uint16_t* X, int b, void* Y, in
 hipError_t launch_gemm_fused(const DevMatrix* As, int count, const uint16_t* X, int b, void* const* Ys,
                              int y_dtype, hipStream_t stream, const Workspace& ws);
 size_t workspace_bound(const DevMatrix* As, int count, int b, bool with_dense_copy = true);
+// How a batch is multiplied with that scratch: in slices (of 16 and fewer), by a dense copy of the matrix, in one pass.
+enum BatchRoute { kRouteSlices = 0, kRouteCopy = 1, kRouteOnePass = 2 };
+BatchRoute batch_route(const DevMatrix& A, int b, const Workspace& ws);
 
 // ---- spqr_gemv.hip: the vector kernel ----
 // Largest number of activation vectors (1, 2 or 4, at most `want`) one launch of the tuned kernel takes for this
@@ -106,7 +109,11 @@ bool prompt_wanted(const DevMatrix& A, int b);
 // Matrices that share X, the format and the permutation.
 // most_slots > 0: a plan with no more partial results of a group than that (0: the fastest).
 size_t prompt_workspace_bytes(const DevMatrix* As, int count, int b, int most_slots = 0);
-bool prompt_reports_copy(const DevMatrix& A, int b);
+// With less of a caller's workspace or of the static array than this the call is not the one-pass kernel's.
+size_t prompt_line_bytes(const DevMatrix& A, int b);
+// What `ws` holds: -1 no plan of the call, 0 the fastest (the library's own scratch grows to it), else (the static array) most_slots
+// of one that it holds.
+int prompt_fit(const DevMatrix* As, int count, int b, const Workspace& ws);
 // `scratch`: prompt_workspace_bytes(As, count, b, most_slots) bytes, 256-byte aligned; Ys 16-byte aligned.
 hipError_t launch_prompt(const DevMatrix* As, int count, const uint16_t* X, int b, void* const* Ys, int y_dtype, hipStream_t stream,
                          uint8_t* scratch, int most_slots = 0);

@@ -922,11 +922,10 @@ static hipError_t on_scratch(const Workspace& ws, size_t need, hipStream_t strea
 
 hipError_t launch_prompt_scratch(const DevMatrix* As, int count, const uint16_t* X, int b, void* const* Ys, int y_dtype,
                                  hipStream_t stream, const Workspace& ws) {
-  int most = 0;
-  size_t need = prompt_workspace_bytes(As, count, b);
-  // in the static array with fewer partial results, where the fastest plan's don't fit
-  for (int slots = 3; ws.fixed && need > ws.bytes && slots >= 1; --slots) need = prompt_workspace_bytes(As, count, b, most = slots);
-  return on_scratch(ws, need, stream, [&](uint8_t* p) { return launch_prompt(As, count, X, b, Ys, y_dtype, stream, p, most); });
+  const int most = prompt_fit(As, count, b, ws);
+  if (most < 0) return hipErrorNotSupported;
+  return on_scratch(ws, prompt_workspace_bytes(As, count, b, most), stream,
+                    [&](uint8_t* p) { return launch_prompt(As, count, X, b, Ys, y_dtype, stream, p, most); });
 }
 
 hipError_t launch_prefill_scratch(const DevMatrix& A, const uint16_t* X, int b, void* Y, int y_dtype, hipStream_t stream,

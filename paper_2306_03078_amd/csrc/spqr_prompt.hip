@@ -526,13 +526,6 @@ bool prompt_wanted(const DevMatrix& A, int b) {
          (prompt_pays(A.g) || option(SPQR_OPT_PROMPT_PLAN) >= 1);
 }
 
-// Whether a caller's workspace for such a call holds the dense copy too: calls that the copy took before this kernel was the faster
-// one for them, so that what was reported for them does not shrink.
-bool prompt_reports_copy(const DevMatrix& A, int b) {
-  const double weights = (double)A.g.m * A.g.n;
-  return option(SPQR_OPT_PROMPT_PLAN) < 1 && A.g.tile_rows != 8 && (weights < 24e6 || (b > 192 && A.g.n <= 2048));
-}
-
 // Scratch of one call: the batch as operands, in column order before that if there is a permutation, per matrix the sorted outliers, their ranges,
 // the counts, the partial results.
 static int prompt_blocks16(const PromptPlan& p) { return p.vblocks * kWidths[p.width].vectors / 16; }
@@ -565,6 +558,46 @@ static size_t prompt_offsets(const DevMatrix* As, int count, int b, const Prompt
 
 size_t prompt_workspace_bytes(const DevMatrix* As, int count, int b, int most_slots) {
   return prompt_offsets(As, count, b, plan_prompt(As, count, b, most_slots), nullptr, nullptr);
+}
+
+// Scratch of a given size, a caller's workspace or the static array: with less than this the call takes the slices of 16, which
+// add the outliers in binary32, where this kernel and the dense copy round weight + outlier to binary16.  A call's rounding is not to
+// depend on what a plan of this kernel happens to need, so the line does not move with the plans: it is the room of the dense copy for
+// the layers that are this kernel's only because it is faster than the copy, and for those that it always took the room of the
+// plan it began with, groups of 16 strips of 8 or 16 rows and equal splits of the columns, one workgroup per CU.
+size_t prompt_line_bytes(const DevMatrix& A, int b) {
+  const Geometry& g = A.g;
+  const double weights = (double)g.m * g.n;
+  if (option(SPQR_OPT_PROMPT_PLAN) >= 1) return 0;             // a pinned plan takes layers of any size
+  if (g.tile_rows != 8 && (weights < 24e6 || (b > 192 && g.n <= 2048))) return prefill_workspace_bytes(A, b);
+  const int rows = 16 * lane_rows(g.tile_rows), groups = (g.m + rows - 1) / rows, units = (g.ntc + kUnitTiles - 1) / kUnitTiles;
+  const int kg = g.tile_cols / 8, phases = units * kg;
+  const int64_t values = (int64_t)b * g.m, most = ((int64_t)16 << 20) / values;               // 64 MB of partial results
+  int splits = 1;
+  double best = 1e30;
+  for (int nvb = 1; nvb <= (rows == 256 ? 2 : 4); nvb *= 2) {  // 64 * nvb vectors a workgroup: us of a phase, 5 of its start
+    const double phase_us = rows == 256 ? (nvb == 1 ? 1.8 : 2.3) : (nvb == 1 ? 1.0 : nvb == 2 ? 1.2 : 1.8);
+    const int64_t wgs = (int64_t)groups * ((b + 64 * nvb - 1) / (64 * nvb));
+    for (int s = 1; s <= units && (s == 1 || s <= most); ++s) {
+      const int per = (units + s - 1) / s, even = (units + per - 1) / per;
+      const double cost = (double)((wgs * even + kCUs - 1) / kCUs) * (per * kg * phase_us + 5.0) + even * ((double)b * g.m * 8 / 4e6);
+      if (cost < best - 1e-9) { best = cost; splits = even; }
+    }
+  }
+  size_t total = up256((size_t)splits * values * sizeof(float)) + (A.perm != nullptr ? up256((size_t)b * g.n * 2) : 0);
+  if (A.nnz > 0)                             // the sorted outliers, their ranges, the counts
+    total += up256((size_t)A.nnz * 4) + up256((size_t)groups * (phases + 1) * 4) + up256((size_t)count_slots(A.nnz, groups) * phases * 4);
+  return total;
+}
+
+int prompt_fit(const DevMatrix* As, int count, int b, const Workspace& ws) {
+  if (!ws.from_caller) return 0;
+  for (int i = 0; i < count; ++i)
+    if (ws.bytes < prompt_line_bytes(As[i], b)) return -1;
+  if (prompt_workspace_bytes(As, count, b) <= ws.bytes) return 0;
+  for (int slots = 3; ws.fixed && slots >= 1; --slots)         // fewer partial results
+    if (prompt_workspace_bytes(As, count, b, slots) <= ws.bytes) return slots;
+  return -1;
 }
 
 template <int W, int TR, int TC, int AXIS, int RW, int NVB>

@@ -384,3 +384,26 @@ def test_static_array_takes_a_plan_of_fewer_partial_results(P):
     assert not torch.equal(out, slices)
     P.spqr_set_option(P.SPQR_OPT_BATCH_PATH, P.SPQR_BATCH_PATH_AUTO)
     assert (out - P.spqr_gemm_smallbatch(A, Xd)).norm() <= 1e-5 * out.norm()   # the same weights, sums in another order
+
+
+def test_scratch_without_room_for_the_copy_is_the_slices(P):
+    """A layer that the one-pass kernel took over from the dense copy, which never fitted the static array: without room for the
+    copy its outliers are added in binary32 as they always were, bit for bit the slices, one matrix or several."""
+    import torch
+    fs = [synth.make_matrix(m, 4096, w_bits=3, beta1=16, beta2=16, group_axis=1, outlier_rate=0.005, outlier_structure="uniform", seed=(91, m))
+          for m in (4096, 4112)]
+    As = [P.SpQRMatrix.from_logical(f) for f in fs]
+    b = 48
+    Xd = torch.from_numpy(synth.make_x(4096, b, seed=(92,))).to("cuda:0")
+    need = P.spqr_workspace_bytes(As, b)
+    ws = torch.empty(need, dtype=torch.uint8, device="cuda:0")
+    P.spqr_set_option(P.SPQR_OPT_BATCH_PATH, P.SPQR_BATCH_PATH_MATRIX)
+    slices = [P.spqr_gemm_smallbatch_ws(A, Xd, ws).clone() for A in As]
+    P.spqr_set_option(P.SPQR_OPT_BATCH_PATH, P.SPQR_BATCH_PATH_AUTO)
+    one = P.spqr_gemm_smallbatch_ws(As[0], Xd, ws).clone()
+    assert not torch.equal(one, slices[0])
+    out = torch.zeros_like(one)
+    assert torch.equal(P.spqr_gemm_smallbatch_noalloc(As[0], Xd, out), slices[0])
+    few = ws[:2 * 4096 * 4096]                 # more than a plan of the one-pass kernel needs, less than the copy and its sums
+    assert torch.equal(P.spqr_gemm_smallbatch_ws(As[0], Xd, few), slices[0])
+    assert all(torch.equal(Y, S) for Y, S in zip(P.spqr_gemm_fused_ws(As, Xd, few), slices))

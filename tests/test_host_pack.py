@@ -33,7 +33,7 @@ def test_library_exports_every_declared_symbol():
             "spqr_permute_columns", "spqr_permute_symmetric"} == enc
     names = names | enc
     hooks = _declared(os.path.join(ROOT, "paper_2306_03078_amd", "csrc", "spqr_test_hooks.h"))
-    assert hooks == {"spqr_plan_batch", "spqr_plan_grouped", "spqr_sort_ranges"}
+    assert hooks == {"spqr_plan_batch", "spqr_plan_grouped", "spqr_sort_ranges", "spqr_batch_route"}
     lib = C.CDLL(P.library_path())
     for nm in sorted(names | hooks):
         assert hasattr(lib, nm), nm
@@ -377,12 +377,12 @@ def test_batch_plan_pins():
 
 # ---- scratch of large batches (host arithmetic on descriptors whose pointers are never followed) ----
 
-def _workspace_bytes(m, n, w, b1, b2, axis, rate, b):
+def _workspace_bytes(m, n, w, b1, b2, axis, rate, b, perm=False):
     from paper_2306_03078_amd import binding as B
     lib = B.load_library()
     d = B.spqr_matrix_t(m=m, n=n, w_bits=w, s_bits=3, z_bits=3, beta1=b1, beta2=b2, group_axis=axis, layout_version=1,
                         packed=4096, packed_bytes=P.packed_bytes(m, n, w, 3, 3, b1, b2, axis), row_ptr=4096, col_idx=4096,
-                        out_val=4096, nnz=int(rate * m * n))
+                        out_val=4096, nnz=int(rate * m * n), perm=4096 if perm else None)
     return lib.spqr_workspace_bytes((C.POINTER(B.spqr_matrix_t) * 1)(C.pointer(d)), 1, b)
 
 
@@ -405,6 +405,47 @@ def test_workspace_of_the_one_pass_kernel_holds_no_dense_copy():
 def test_sizes_of_the_one_pass_kernel(m, n, w, b1, b2, b, one_pass):
     """Where the dense copy is faster, the batch takes the copy, and its scratch holds one: 2 bytes per weight."""
     assert (_workspace_bytes(m, n, w, b1, b2, 1, 0.01, b) < 2 * m * n) == one_pass
+
+
+SLICES, COPY, ONE_PASS = 0, 1, 2
+LIBRARY, STATIC = -1, -2
+
+
+def _route(m, n, w, b1, b2, axis, rate, b, scratch, perm=False):
+    from paper_2306_03078_amd import binding as B
+    return B.load_library().spqr_batch_route(m, n, C.c_int64(int(rate * m * n)), int(perm), w, b1, b2, axis, b, C.c_int64(scratch))
+
+
+# `line`: the scratch from which on a call of that size has had 16-bit sums of weight and outlier since it could, the dense copy
+# (a multiple of it: `copy`) or the plan of the one-pass kernel's first form; `static`: what 32 MB are
+@pytest.mark.parametrize("m,n,w,b1,b2,axis,rate,perm,b,line,copy,static", [
+    (4096, 4096, 3, 16, 16, 1, 0.01, False, 48, 39845888, True, SLICES), (4096, 4096, 4, 16, 16, 0, 0.01, True, 256, 69206016, True, SLICES),
+    (4864, 4864, 4, 16, 16, 1, 0.01, False, 128, 67239936, True, SLICES), (2048, 8192, 3, 8, 32, 0, 0.01, False, 48, 36700160, True, SLICES),
+    (17920, 2048, 4, 16, 16, 1, 0.01, True, 256, 221249536, True, SLICES), (2048, 2048, 3, 16, 16, 1, 0.01, False, 48, 11534336, True, ONE_PASS),
+    (5120, 5120, 3, 16, 16, 1, 0.01, False, 256, 27280128, False, ONE_PASS), (17920, 2064, 4, 16, 16, 1, 0.01, False, 256, 19846912, False, ONE_PASS),
+    (8192, 8192, 3, 8, 32, 1, 0.02, False, 64, 13874432, False, ONE_PASS), (2048, 2048, 3, 8, 32, 1, 0.01, True, 64, 2530304, False, ONE_PASS),
+    (6464, 8416, 3, 16, 16, 1, 0.05, True, 96, 35025408, False, SLICES), (4528, 13536, 4, 16, 16, 0, 0.01, False, 128, 34987776, False, SLICES),
+    (5376, 5800, 4, 8, 32, 0, 0.005, False, 256, 33669120, False, SLICES), (17920, 6656, 4, 16, 16, 1, 0.01, False, 256, 59911680, False, SLICES),
+    (16320, 3200, 3, 8, 32, 1, 0.02, False, 200, 17291776, False, ONE_PASS), (22016, 8192, 3, 8, 32, 1, 0.02, True, 192, 34796800, False, SLICES)])
+def test_a_batch_is_rounded_no_earlier_for_a_smaller_plan(m, n, w, b1, b2, axis, rate, perm, b, line, copy, static):
+    """With less scratch than `line` the outliers are added in binary32 (slices), however little a plan of the one-pass kernel
+    needs, and what spqr_workspace_bytes reports is never less than that."""
+    need = _workspace_bytes(m, n, w, b1, b2, axis, rate, b, perm)
+    route = [_route(m, n, w, b1, b2, axis, rate, b, scratch, perm) for scratch in (LIBRARY, need, line - 1, 0, STATIC)]
+    assert route == [ONE_PASS, ONE_PASS, SLICES, SLICES, static] and need >= line
+    if copy:
+        assert _route(m, n, w, b1, b2, axis, rate, b, line, perm) == ONE_PASS
+
+
+def test_a_batch_with_the_reported_scratch_goes_as_with_the_librarys():
+    rng = np.random.default_rng(14)
+    for w, b1, b2, axis, _ in FORMATS:
+        tr, tc = synth.tile_shape(b1, b2, axis)
+        for _ in range(200):
+            m, n = tr * int(rng.integers(1, 24000 // tr)), tc * int(rng.integers(1, 24000 // tc))
+            args = (m, n, w, b1, b2, axis, float(rng.choice([0.0, 0.01, 0.02, 0.3])), int(rng.integers(1, 257)))
+            perm = bool(rng.integers(2))
+            assert _route(*args, _workspace_bytes(*args, perm), perm) == _route(*args, LIBRARY, perm)
 
 
 def test_direct_calls_take_tensors_by_address_and_refuse_what_they_cannot_pass():
