@@ -249,11 +249,11 @@ extern "C" int spqr_dequant_dense(const spqr_matrix_t* A, int what, void* out, v
   return e == hipSuccess ? SPQR_OK : SPQR_ERR_HIP;
 }
 
-extern "C" int spqr_plan_batch(int count, const int32_t* m, const int32_t* n, const int32_t* max_row_nnz, const int64_t* nnz,
-                               int w_bits, int beta1, int beta2, int group_axis, int b, int32_t* plan) {
-  if (!m || !n || !max_row_nnz || !nnz || !plan) return SPQR_ERR_NULL;
-  if (count < 1 || count > SPQR_MAX_FUSED || b < 1 || b > 16) return SPQR_ERR_PARAM;
-  spqr::DevMatrix D[SPQR_MAX_FUSED] = {};
+// Matrices of one width and format for the plans' hooks, pointers null.
+static int plan_matrices(int count, const int32_t* m, const int32_t* n, const int32_t* max_row_nnz, const int64_t* nnz, int w_bits,
+                         int beta1, int beta2, int group_axis, spqr::DevMatrix* D) {
+  if (!m || !n || !max_row_nnz || !nnz) return SPQR_ERR_NULL;
+  if (count < 1 || count > SPQR_MAX_FUSED) return SPQR_ERR_PARAM;
   for (int i = 0; i < count; ++i) {
     if (max_row_nnz[i] < 0 || nnz[i] < 0 || n[i] != n[0]) return SPQR_ERR_PARAM;
     const int rc = spqr::make_geometry(spqr::kBilevel, m[i], n[i], w_bits, 3, 3, beta1, beta2, group_axis, &D[i].g);
@@ -261,8 +261,29 @@ extern "C" int spqr_plan_batch(int count, const int32_t* m, const int32_t* n, co
     D[i].nnz = nnz[i];
     D[i].max_row_nnz = max_row_nnz[i];
   }
-  if (!spqr::mfma_has_instance(D[0].g)) return SPQR_ERR_PARAM;
+  return SPQR_OK;
+}
+
+extern "C" int spqr_plan_batch(int count, const int32_t* m, const int32_t* n, const int32_t* max_row_nnz, const int64_t* nnz,
+                               int w_bits, int beta1, int beta2, int group_axis, int b, int32_t* plan) {
+  spqr::DevMatrix D[SPQR_MAX_FUSED] = {};
+  const int rc = plan_matrices(count, m, n, max_row_nnz, nnz, w_bits, beta1, beta2, group_axis, D);
+  if (rc) return rc;
+  if (!plan) return SPQR_ERR_NULL;
+  if (b < 1 || b > 16 || !spqr::mfma_has_instance(D[0].g)) return SPQR_ERR_PARAM;
   return spqr::plan_batch_hook(D, count, b, &plan[0], &plan[1], &plan[2]);
+}
+
+extern "C" int spqr_plan_prompt(int count, const int32_t* m, const int32_t* n, const int32_t* max_row_nnz, const int64_t* nnz,
+                                int w_bits, int beta1, int beta2, int group_axis, int b, int most_slots, int32_t* plan) {
+  spqr::DevMatrix D[SPQR_MAX_FUSED] = {};
+  const int rc = plan_matrices(count, m, n, max_row_nnz, nnz, w_bits, beta1, beta2, group_axis, D);
+  if (rc) return rc;
+  if (!plan) return SPQR_ERR_NULL;
+  if (b < 1 || b > SPQR_MAX_BATCH || most_slots < 0) return SPQR_ERR_PARAM;
+  for (int i = 0; i < count; ++i)
+    if (!spqr::prompt_has_instance(D[i])) return SPQR_ERR_PARAM;
+  return spqr::plan_prompt_hook(D, count, b, most_slots, plan);
 }
 
 extern "C" int spqr_plan_grouped(int count, const int32_t* m, const int32_t* n, const int32_t* max_row_nnz,

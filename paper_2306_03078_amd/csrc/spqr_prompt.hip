@@ -54,10 +54,8 @@ __device__ __forceinline__ int find_item(const PromptSet& S, int& group) {   // 
 // (spqr_sort.h).
 // ---------------------------------------------------------------------------
 constexpr int kSortThreads = 512, kSortPer = kSortChunk / kSortThreads, kSortMaxPhases = 512, kSortMaxBins = 4 * kSortMaxPhases;
-// Workgroups per group, each takes every 4th chunk.  The kernels are trips to memory one after the other, so the entries of a
-// thread are few (512 threads: 11008 x 4096 twice, 5.8 and 10.2 us; 256: 5.2 and 12; 1024: 6.4 and 13) and the chunks side by side
-// (17920 x 6656 with Zipf rows: 2 workgroups 11.6 and 22.6, 4 8.9 and 14.8; 8 start too many that find no chunk: 10.3 and 14.4).
-constexpr int kSortWgs = 4;
+// The kernels are trips to memory one after the other, so the entries of a thread are few (512 threads: 11008 x 4096 twice, 5.8
+// and 10.2 us; 256: 5.2 and 12; 1024: 6.4 and 13) and the chunks of a group side by side, see sort_workgroups.
 
 // Bin of a column: a unit of 16 tile columns (1 << unit_shift columns) has kg phases of 4 bins.
 __device__ __forceinline__ int bin_of(int col, int unit_shift, int kg) {
@@ -78,24 +76,26 @@ __device__ __forceinline__ void order_x(const uint16_t* __restrict__ X, int batc
   XS[at] = v < batch && col < n ? *reinterpret_cast<const u32x4*>(X + (int64_t)v * n + col) : u32x4{0u, 0u, 0u, 0u};
 }
 
-// Workgroups of groups * kSortWgs and more order the batch, the others count.
+// Workgroups of groups * wgs and more order the batch, the others count, `wgs` to a group: each takes every wgs-th chunk.  (The first
+// chunks of all groups side by side: workgroups go to the XCDs in turn, and with the chunks of a group side by side and 32 of them
+// the only ones that most groups have were all one XCD's, 9.1 us against 5.6 at 4096^2 with Zipf rows.)
 __global__ void __launch_bounds__(kSortThreads)
-count_phases_kernel(PromptSet S, int groups, int unit_shift, int kg, int bins, const uint16_t* __restrict__ X, int batch,
+count_phases_kernel(PromptSet S, int groups, int wgs, int unit_shift, int kg, int bins, const uint16_t* __restrict__ X, int batch,
                     int blocks16, u32x4* __restrict__ XS) {
   __shared__ uint32_t hist[kSortMaxBins];
-  if ((int)blockIdx.x >= groups * kSortWgs) {
-    const int at = ((int)blockIdx.x - groups * kSortWgs) * kSortThreads + (int)threadIdx.x;
+  if ((int)blockIdx.x >= groups * wgs) {
+    const int at = ((int)blockIdx.x - groups * wgs) * kSortThreads + (int)threadIdx.x;
     if (at < bins * blocks16 * 64) order_x(X, batch, S.it[0].A.g.n, S.it[0].A.g.tile_cols, kg, blocks16, at, XS);
     return;
   }
-  int group = blockIdx.x / kSortWgs;
+  int group = blockIdx.x % groups;
   const PromptItem& it = S.it[find_item(S, group)];
   const DevMatrix& A = it.A;
   if (A.nnz == 0) return;                    // workgroup-uniform
   const int tid = threadIdx.x;
   const GroupRange range = group_range(A.row_ptr, group, kGroupRows, A.g.m, (int)A.nnz);
   const int s = range.s, z = range.z;
-  for (int k = blockIdx.x % kSortWgs; s + kSortChunk * k < z; k += kSortWgs) {   // workgroup-uniform
+  for (int k = blockIdx.x / groups; s + kSortChunk * k < z; k += wgs) {          // workgroup-uniform
     for (int u = tid; u < bins; u += kSortThreads) hist[u] = 0;
     __syncthreads();
     uint16_t c[kSortPer];
@@ -128,7 +128,7 @@ sort_phases_kernel(PromptSet S, int unit_shift, int kg, int bins) {
   const int s = range.s, z = range.z, chunks = sort_chunks(range);
   const uint32_t* in = it.counts + count_slot(range, group, 0) * bins;
   int32_t* offs = it.offs + (int64_t)group * (bins + 1);
-  for (int k = blockIdx.y; k < max(chunks, 1); k += kSortWgs) {              // workgroup-uniform
+  for (int k = blockIdx.y; k < max(chunks, 1); k += gridDim.y) {             // workgroup-uniform
     // the chunk's entries and the row pointers are on their way while the places are worked out
     uint16_t c[kSortPer], v[kSortPer];
     if (chunks > 0) {
@@ -556,6 +556,30 @@ static size_t prompt_offsets(const DevMatrix* As, int count, int b, const Prompt
   return total;
 }
 
+// Workgroups per group of the sort: as many as the group with the most outliers may have chunks, by what the descriptors say of the
+// longest row (nothing: any row may be full): a chunk behind another one waits for all of its trips to memory.  In all no more
+// than the chip takes about at once (but 4 a group), for most find no chunk where a few rows hold the outliers.  128 vectors, whole
+// call in us, 4 a group -> this: 512 x 24576 with 8 full rows 74 .. 103 -> 40 .. 45, 1024 x 17920 with Zipf rows 63 .. 70 -> 42 .. 48,
+// 8192 x 22016 with them 120 .. 143 -> 105 .. 117 (counting and sorting 12 + 31 -> 9.4 + 17.4; with 512 in all 10 + 22, with 2048 9.4 +
+// 17.6); 4096^2 and 17920 x 6656 as before.
+constexpr int kMostSortWgs = 1024;
+static int sort_workgroups(const DevMatrix* As, int count, int groups) {
+  int64_t most = 0;
+  for (int i = 0; i < count; ++i) {
+    const int64_t row = As[i].max_row_nnz > 0 ? As[i].max_row_nnz : As[i].g.n;
+    most = std::max(most, std::min(As[i].nnz, row * kGroupRows));
+  }
+  const int64_t chunks = (most + kSortChunk - 1) / kSortChunk;
+  return (int)std::max<int64_t>(1, std::min<int64_t>(chunks, std::max(4, kMostSortWgs / groups)));
+}
+
+int plan_prompt_hook(const DevMatrix* As, int count, int b, int most_slots, int32_t* plan) {
+  const PromptPlan p = plan_prompt(As, count, b, most_slots);
+  plan[0] = kWidths[p.width].vectors; plan[1] = p.run; plan[2] = p.runs; plan[3] = p.slots;
+  plan[4] = sort_workgroups(As, count, p.groups);
+  return p.units;
+}
+
 size_t prompt_workspace_bytes(const DevMatrix* As, int count, int b, int most_slots) {
   return prompt_offsets(As, count, b, plan_prompt(As, count, b, most_slots), nullptr, nullptr);
 }
@@ -654,11 +678,12 @@ hipError_t launch_prompt(const DevMatrix* As, int count, const uint16_t* X, int 
     if (e != hipSuccess) return e;
     Xin = xp;
   }
-  hipLaunchKernelGGL(count_phases_kernel, dim3(p.groups * kSortWgs + (p.bins * blocks16 * 64 + kSortThreads - 1) / kSortThreads), dim3(kSortThreads), 0, stream, S, p.groups,
-                     p.unit_shift, p.kg, p.bins, Xin, b, blocks16, XS);
+  const int wgs = sort_workgroups(As, count, p.groups);
+  hipLaunchKernelGGL(count_phases_kernel, dim3(p.groups * wgs + (p.bins * blocks16 * 64 + kSortThreads - 1) / kSortThreads), dim3(kSortThreads), 0, stream, S, p.groups,
+                     wgs, p.unit_shift, p.kg, p.bins, Xin, b, blocks16, XS);
   if (nnz > 0) {
     const auto sort = p.bins <= kSortThreads ? &sort_phases_kernel<1> : p.bins <= 2 * kSortThreads ? &sort_phases_kernel<2> : &sort_phases_kernel<4>;
-    hipLaunchKernelGGL(sort, dim3(p.groups, kSortWgs), dim3(kSortThreads), 0, stream, S, p.unit_shift, p.kg, p.bins);
+    hipLaunchKernelGGL(sort, dim3(p.groups, wgs), dim3(kSortThreads), 0, stream, S, p.unit_shift, p.kg, p.bins);
   }
   if ((e = hipGetLastError()) != hipSuccess) return e;
   e = hipErrorInvalidValue;

@@ -407,3 +407,24 @@ def test_scratch_without_room_for_the_copy_is_the_slices(P):
     few = ws[:2 * 4096 * 4096]                 # more than a plan of the one-pass kernel needs, less than the copy and its sums
     assert torch.equal(P.spqr_gemm_smallbatch_ws(As[0], Xd, few), slices[0])
     assert all(torch.equal(Y, S) for Y, S in zip(P.spqr_gemm_fused_ws(As, Xd, few), slices))
+
+
+# groups of many chunks of the sort with a workgroup for each, and with one workgroup for all of them (a hint that is too small)
+@pytest.mark.parametrize("w,b1,b2,axis,ntr,ntc,structure,rate", [(3, 16, 16, 1, 9, 131, "zipf", 0.15), (4, 8, 32, 0, 3, 450, "rows8cols4", 0.2)])
+@pytest.mark.parametrize("hint", [0, 1, None])
+def test_sort_with_any_number_of_workgroups(P, w, b1, b2, axis, ntr, ntc, structure, rate, hint):
+    import torch
+    tr, tc = synth.tile_shape(b1, b2, axis)
+    f = synth.make_matrix(ntr * tr, ntc * tc, w_bits=w, beta1=b1, beta2=b2, group_axis=axis, outlier_rate=rate,
+                          outlier_structure=structure, seed=(93, w, axis))
+    A = P.SpQRMatrix.from_logical(f)
+    X = torch.from_numpy(synth.make_x(f.n, 64, seed=(94,))).to("cuda:0")
+    P.spqr_set_option(P.SPQR_OPT_PROMPT_PLAN, 1000)
+    want = P.spqr_gemm_smallbatch(A, X).clone()
+    if hint is None:
+        P.spqr_set_option(P.SPQR_OPT_PROMPT_PLAN, 0)
+        run(P, f, 64, prompt=1000)
+        return
+    A.desc.max_row_nnz = hint
+    assert torch.equal(P.spqr_gemm_smallbatch(A, X), want)
+    P.spqr_set_option(P.SPQR_OPT_PROMPT_PLAN, 0)

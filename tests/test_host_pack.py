@@ -33,7 +33,7 @@ def test_library_exports_every_declared_symbol():
             "spqr_permute_columns", "spqr_permute_symmetric"} == enc
     names = names | enc
     hooks = _declared(os.path.join(ROOT, "paper_2306_03078_amd", "csrc", "spqr_test_hooks.h"))
-    assert hooks == {"spqr_plan_batch", "spqr_plan_grouped", "spqr_sort_ranges", "spqr_batch_route"}
+    assert hooks == {"spqr_plan_batch", "spqr_plan_grouped", "spqr_sort_ranges", "spqr_batch_route", "spqr_plan_prompt"}
     lib = C.CDLL(P.library_path())
     for nm in sorted(names | hooks):
         assert hasattr(lib, nm), nm
@@ -446,6 +446,29 @@ def test_a_batch_with_the_reported_scratch_goes_as_with_the_librarys():
             args = (m, n, w, b1, b2, axis, float(rng.choice([0.0, 0.01, 0.02, 0.3])), int(rng.integers(1, 257)))
             perm = bool(rng.integers(2))
             assert _route(*args, _workspace_bytes(*args, perm), perm) == _route(*args, LIBRARY, perm)
+
+
+def _plan_prompt(ms, n, nnz, hints, w, b1, b2, axis, b, most_slots=0):
+    """units, vectors and units per workgroup, workgroups per block of vectors, partial results, workgroups of the sort"""
+    from paper_2306_03078_amd import binding as B
+    k = len(ms)
+    plan = (C.c_int32 * 5)()
+    rc = B.load_library().spqr_plan_prompt(k, (C.c_int32 * k)(*ms), (C.c_int32 * k)(*[n] * k), (C.c_int32 * k)(*hints), (C.c_int64 * k)(*nnz),
+                                           w, b1, b2, axis, b, most_slots, plan)
+    return (rc, *plan)
+
+
+def test_the_outlier_sort_of_a_few_heavy_rows_has_a_workgroup_for_every_chunk():
+    """A chunk is 4096 outliers.  Four workgroups a group, whatever it held, cost up to 60 of 107 us on layers of few rows."""
+    wgs = lambda ms, n, nnz, hints: _plan_prompt(ms, n, nnz, hints, 3, 16, 16, 1, 128)[5]
+    full, even = 128 * 24576, [256] * 4
+    assert wgs([512], 24576, [300000], [24576]) == -(-300000 // 4096)       # any group may hold all of them
+    assert wgs([512], 24576, [300000], [0]) == -(-300000 // 4096)           # nothing known of the rows
+    assert wgs([512], 24576, [125829], [300]) == -(-128 * 300 // 4096)      # rows of much the same length
+    assert wgs([512], 24576, [0], [0]) == 1
+    assert wgs([17920], 6656, [1192755], [6656]) == 1024 // 140             # no more than the chip takes at once
+    assert wgs([512] * 4, 24576, [100000] * 3 + [full], even[:3] + [24576]) == 1024 // 16
+    assert wgs([65536], 4096, [2684354], [4096]) == 4
 
 
 def test_direct_calls_take_tensors_by_address_and_refuse_what_they_cannot_pass():
