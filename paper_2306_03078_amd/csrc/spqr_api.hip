@@ -275,15 +275,15 @@ extern "C" int spqr_plan_batch(int count, const int32_t* m, const int32_t* n, co
 }
 
 extern "C" int spqr_plan_prompt(int count, const int32_t* m, const int32_t* n, const int32_t* max_row_nnz, const int64_t* nnz,
-                                int w_bits, int beta1, int beta2, int group_axis, int b, int most_slots, int32_t* plan) {
+                                int w_bits, int beta1, int beta2, int group_axis, int b, int most_slots, int32_t* plan, double* us) {
   spqr::DevMatrix D[SPQR_MAX_FUSED] = {};
   const int rc = plan_matrices(count, m, n, max_row_nnz, nnz, w_bits, beta1, beta2, group_axis, D);
   if (rc) return rc;
-  if (!plan) return SPQR_ERR_NULL;
+  if (!plan || !us) return SPQR_ERR_NULL;
   if (b < 1 || b > SPQR_MAX_BATCH || most_slots < 0) return SPQR_ERR_PARAM;
   for (int i = 0; i < count; ++i)
     if (!spqr::prompt_has_instance(D[i])) return SPQR_ERR_PARAM;
-  return spqr::plan_prompt_hook(D, count, b, most_slots, plan);
+  return spqr::plan_prompt_hook(D, count, b, most_slots, plan, us);
 }
 
 extern "C" int spqr_plan_grouped(int count, const int32_t* m, const int32_t* n, const int32_t* max_row_nnz,

@@ -78,15 +78,20 @@ BatchRoute batch_route(const DevMatrix& A, int b, const Workspace& ws) {
   return copy ? kRouteCopy : kRouteSlices;
 }
 
-// Whether launch_gemm_fused gives several matrices to the one-pass kernel together.
+// Whether launch_gemm_fused gives several matrices to the one-pass kernel together: where all of them are its own and that is
+// faster than one after the other by its plans' model.  It hardly ever is not: the partial results of all of them have the room of
+// one's (64 MB), so with very many rows and vectors groups of rows have to stay whole.  (Gate and up 17920 x 6656, 4-bit, 256
+// vectors: 236 to 262 us together, 222 one by one; 22016 x 8192 289 and 361; the model 304 and 280, 398 and 424.)
 static bool prompt_set_wanted(const DevMatrix* As, int count, int b) {
-  bool all = count > 1;
+  if (count < 2) return false;
   int64_t nnz = 0;                           // (counted in 32 bits there)
-  for (int i = 0; i < count && all; ++i) {
-    all = prompt_wanted(As[i], b);
+  double apart = 0.0;
+  for (int i = 0; i < count; ++i) {
+    if (!prompt_wanted(As[i], b)) return false;
     nnz += As[i].nnz;
+    apart += prompt_us(&As[i], 1, b);
   }
-  return all && nnz < 0x7FFF0000ll;
+  return nnz < 0x7FFF0000ll && (option(SPQR_OPT_PROMPT_PLAN) >= 1 || prompt_us(As, count, b) <= apart);
 }
 
 // Whether launch_gemm_fused takes the fused matrix-core launches for a slice of nb vectors.

@@ -108,7 +108,9 @@ bool prompt_has_instance(const DevMatrix& A);
 bool prompt_wanted(const DevMatrix& A, int b);
 // Matrices that share X, the format and the permutation.
 // most_slots > 0: a plan with no more partial results of a group than that (0: the fastest).
-int plan_prompt_hook(const DevMatrix* As, int count, int b, int most_slots, int32_t* plan);
+// What the plan's model says of the whole call, us.
+double prompt_us(const DevMatrix* As, int count, int b);
+int plan_prompt_hook(const DevMatrix* As, int count, int b, int most_slots, int32_t* plan, double* us);
 size_t prompt_workspace_bytes(const DevMatrix* As, int count, int b, int most_slots = 0);
 // With less of a caller's workspace or of the static array than this the call is not the one-pass kernel's.
 size_t prompt_line_bytes(const DevMatrix& A, int b);

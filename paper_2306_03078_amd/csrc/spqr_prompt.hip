@@ -455,10 +455,11 @@ static size_t up256(size_t v) { return (v + 255) & ~(size_t)255; }
 // sums a lane: the compiler spills, 140 us against 95 for 17920 x 6656, 4-bit, 256 vectors.)
 struct PromptWidth { int rw, nvb, vectors; double one_us, two_us; };
 constexpr PromptWidth kWidths[] = {{2, 2, 64, 1.6, 2.2}, {2, 3, 96, 1.7, 2.4}, {1, 2, 128, 2.05, 2.9}, {1, 3, 192, 2.25, 3.5}};
+constexpr double kSortUs = 15;                // the counting and the sorting of the outliers and the launches of a call
 constexpr int kMostRunPhases = 2048;          // their ranges of outliers lie in LDS: 32 bytes each
 constexpr int kWidthCount = sizeof(kWidths) / sizeof(kWidths[0]);
 
-struct PromptPlan { int groups, units, unit_shift, kg, bins, width, vblocks, run, runs, slots; };
+struct PromptPlan { int groups, units, unit_shift, kg, bins, width, vblocks, run, runs, slots; double us; };
 static int prompt_groups(const Geometry& g) { return (g.m + kGroupRows - 1) / kGroupRows; }
 // Partial results of a group: the most runs that a group can be part of.  Groups begin at multiples of gcd(units, run) behind a
 // run's beginning, at run - gcd at the latest.
@@ -480,23 +481,31 @@ static PromptPlan plan_prompt(const DevMatrix* As, int count, int b, int most_sl
   const int pin = option(SPQR_OPT_PROMPT_PLAN), pin_units = pin % 1024;   // (tuning, tests)
   const int widest = kWidths[kWidthCount - 1].vectors;
   const int pin_vectors = 64 * (pin / 1024) < widest ? 64 * (pin / 1024) : widest;
-  p.width = kWidthCount - 1;
-  p.vblocks = (b + widest - 1) / widest;
-  p.run = p.units;                           // whole groups: one partial result
-  double best = 1e30;
+  p.us = 1e30;
   for (int w = 0; w < kWidthCount; ++w) {
     const PromptWidth& c = kWidths[w];
     if (pin_vectors > 0 && c.vectors != pin_vectors && !(c.vectors < pin_vectors && 2 * c.vectors > pin_vectors && b <= c.vectors)) continue;
     const int vblocks = (b + c.vectors - 1) / c.vectors;
     for (int k = 1; k <= 2; ++k) {           // workgroups per CU
-      const int wgs = k * kCUs / vblocks > 0 ? k * kCUs / vblocks : 1, run = std::min((total + wgs - 1) / wgs, most_run), runs = (total + run - 1) / run;
-      if (prompt_slots(p.units, run) > most) continue;
-      const double parts_us = (double)b * kGroupRows * 8 / 4e6 * (runs + p.groups);
-      const int rounds = (runs + wgs - 1) / wgs;
-      const double cost = rounds * (run * p.kg * (k == 1 ? c.one_us : c.two_us) + 3.0 + 0.04 * c.vectors + (k == 1 ? 0.0 : 5.0)) + parts_us;
-      if (cost < best - 1e-9) { best = cost; p.width = w; p.vblocks = vblocks; p.run = run; }
+      const int wgs = k * kCUs / vblocks > 0 ? k * kCUs / vblocks : 1, even = std::min((total + wgs - 1) / wgs, most_run);
+      auto consider = [&](int run) {
+        if (run > most_run || prompt_slots(p.units, run) > most) return false;
+        const int runs = (total + run - 1) / run, rest = runs % wgs;
+        const double one = run * p.kg * c.one_us + 3.0 + 0.04 * c.vectors, all = k == 1 ? one : run * p.kg * c.two_us + 8.0 + 0.04 * c.vectors;
+        const double parts_us = (double)b * kGroupRows * 8 / 4e6 * (runs + p.groups);
+        // full rounds of workgroups, then one that may have the CUs to themselves
+        const double last = rest == 0 ? 0.0 : runs > wgs && rest * vblocks <= kCUs ? one : all;
+        const double cost = runs / wgs * all + last + parts_us;
+        if (cost < p.us - 1e-9) { p.us = cost; p.width = w; p.vblocks = vblocks; p.run = run; }
+        return true;
+      };
+      // Even shares; where those are more partial results of a group than there may be, the next longer runs that are not, and
+      // whole groups, one result each (a run may hold one at least: kSortMaxPhases).
+      if (consider(even)) continue;
+      if (most > 1) consider(std::max<int>(even, (int)((p.units - 1 + most - 2) / (most - 1))));
+      consider(p.units);
+      consider(std::min((even + p.units - 1) / p.units, most_run / p.units) * p.units);
     }
-    if (best > 1e29) { p.width = w; p.vblocks = vblocks; }
   }
   if (pin_units >= 1) p.run = std::min(pin_units, std::min(total, most_run));
   p.runs = (total + p.run - 1) / p.run;
@@ -573,8 +582,11 @@ static int sort_workgroups(const DevMatrix* As, int count, int groups) {
   return (int)std::max<int64_t>(1, std::min<int64_t>(chunks, std::max(4, kMostSortWgs / groups)));
 }
 
-int plan_prompt_hook(const DevMatrix* As, int count, int b, int most_slots, int32_t* plan) {
+double prompt_us(const DevMatrix* As, int count, int b) { return plan_prompt(As, count, b, 0).us + kSortUs; }
+
+int plan_prompt_hook(const DevMatrix* As, int count, int b, int most_slots, int32_t* plan, double* us) {
   const PromptPlan p = plan_prompt(As, count, b, most_slots);
+  *us = p.us;
   plan[0] = kWidths[p.width].vectors; plan[1] = p.run; plan[2] = p.runs; plan[3] = p.slots;
   plan[4] = sort_workgroups(As, count, p.groups);
   return p.units;

@@ -38,9 +38,10 @@ int spqr_plan_grouped(int count, const int32_t* m, const int32_t* n, const int32
 /* Plan of the one-pass kernel for matrices as for spqr_plan_batch and b vectors (1 .. 256), with no more partial results of a
  * row than most_slots (0: the fastest plan's); host arithmetic only.  plan[0..4] = vectors per workgroup, units of 16 tile
  * columns per workgroup, workgroups per block of vectors, partial results of a row at most, workgroups per group of rows
- * of the outlier sort.  Returns the units of the matrix, or an SPQR_ERR_* code (SPQR_ERR_PARAM also for a format without that kernel). */
+ * of the outlier sort; *us = what its model says of it.  Returns the units of the matrix, or an SPQR_ERR_* code (SPQR_ERR_PARAM
+ * also for a format without that kernel). */
 int spqr_plan_prompt(int count, const int32_t* m, const int32_t* n, const int32_t* max_row_nnz, const int64_t* nnz, int w_bits,
-                     int beta1, int beta2, int group_axis, int b, int most_slots, int32_t* plan);
+                     int beta1, int beta2, int group_axis, int b, int most_slots, int32_t* plan, double* us);
 
 /* The way a batch of b vectors (Y 16-byte aligned) goes through a matrix of layout 1 (3-bit statistic codes) with nnz outliers
  * and, if has_perm, a permutation: 0 slices of 16 and fewer, 1 a dense copy, 2 the one-pass kernel, or an SPQR_ERR_* code.

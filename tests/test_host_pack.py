@@ -449,13 +449,54 @@ def test_a_batch_with_the_reported_scratch_goes_as_with_the_librarys():
 
 
 def _plan_prompt(ms, n, nnz, hints, w, b1, b2, axis, b, most_slots=0):
-    """units, vectors and units per workgroup, workgroups per block of vectors, partial results, workgroups of the sort"""
+    """units, vectors and units per workgroup, workgroups per block of vectors, partial results, workgroups of the sort, us"""
     from paper_2306_03078_amd import binding as B
     k = len(ms)
-    plan = (C.c_int32 * 5)()
+    plan, us = (C.c_int32 * 5)(), C.c_double()
     rc = B.load_library().spqr_plan_prompt(k, (C.c_int32 * k)(*ms), (C.c_int32 * k)(*[n] * k), (C.c_int32 * k)(*hints), (C.c_int64 * k)(*nnz),
-                                           w, b1, b2, axis, b, most_slots, plan)
-    return (rc, *plan)
+                                           w, b1, b2, axis, b, most_slots, plan, C.byref(us))
+    return (rc, *plan, us.value)
+
+
+def test_one_pass_plans_keep_the_kernels_invariants():
+    rng = np.random.default_rng(15)
+    for w, b1, b2, axis, _ in FORMATS:
+        tr, tc = synth.tile_shape(b1, b2, axis)
+        for _ in range(300):
+            k = int(rng.integers(1, 9)) if rng.random() < 0.4 else 1
+            n = tc * int(rng.integers(1, 32768 // tc // 2))
+            ms = [tr * int(rng.integers(1, 40000 // tr)) for _ in range(k)]
+            b, most = int(rng.integers(1, 257)), int(rng.integers(0, 4))
+            units, vectors, run, runs, slots, wgs, us = _plan_prompt(ms, n, [0] * k, [0] * k, w, b1, b2, axis, b, most)
+            total = units * sum(-(-m // 128) for m in ms)
+            assert vectors in (64, 96, 128, 192) and runs == -(-total // run) and 1 <= run <= 2048 // (tc // 8)
+            assert slots >= max(((g * units + units - 1) // run - g * units // run + 1) for g in range(min(total // units, 300)))
+            assert slots == 1 or (slots <= (most or slots) and 4 * slots * b * 128 * total // units <= 64 << 20)
+            assert 0 < us < 1e6
+
+
+def test_one_pass_plans_of_few_partial_results_are_as_wide_as_they_should_be():
+    """Whole groups per workgroup are priced like any other plan: 256 vectors are 2 x 128 and not 2 x 192 (128 and 192 vectors a
+    workgroup, runs of a group, timed: two of 22016 x 8192 289 and 324 us, two of 17920 x 6656 236 and 261)."""
+    z8, z16 = int(0.01 * 22016 * 8192), int(0.01 * 17920 * 6656)
+    assert _plan_prompt([22016] * 2, 8192, [z8] * 2, [0, 0], 3, 8, 32, 1, 256)[1:5] == (128, 16, 344, 1)
+    for b, most in ((256, 0), (256, 1), (200, 1)):
+        assert _plan_prompt([17920] * 2, 6656, [z16] * 2, [0, 0], 4, 16, 16, 1, b, most)[1] <= 128
+    assert _plan_prompt([17920] * 2, 6656, [z16] * 2, [0, 0], 4, 16, 16, 1, 128)[1:5] == (128, 15, 486, 3)   # nothing in the way
+
+
+def test_matrices_go_one_by_one_where_that_is_faster():
+    """The scratch of two is that of one where they don't share launches: gate and up 17920 x 6656 with 256 vectors (251 us together,
+    222 one by one), not with 192 (156 and 191), not 22016 x 8192 with 256 (289 and 361)."""
+    def together(m, n, w, b1, b2, b):
+        from paper_2306_03078_amd import binding as B
+        d = B.spqr_matrix_t(m=m, n=n, w_bits=w, s_bits=3, z_bits=3, beta1=b1, beta2=b2, group_axis=1, layout_version=1,
+                            packed=4096, packed_bytes=P.packed_bytes(m, n, w, 3, 3, b1, b2, 1), row_ptr=4096, col_idx=4096,
+                            out_val=4096, nnz=int(0.01 * m * n))
+        two = (C.POINTER(B.spqr_matrix_t) * 2)(C.pointer(d), C.pointer(d))
+        return B.load_library().spqr_workspace_bytes(two, 2, b) != B.load_library().spqr_workspace_bytes(two, 1, b)
+    assert not together(17920, 6656, 4, 16, 16, 256)
+    assert together(17920, 6656, 4, 16, 16, 192) and together(22016, 8192, 3, 8, 32, 256) and together(11008, 4096, 3, 16, 16, 77)
 
 
 def test_the_outlier_sort_of_a_few_heavy_rows_has_a_workgroup_for_every_chunk():
