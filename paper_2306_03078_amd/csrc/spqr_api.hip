@@ -314,15 +314,16 @@ extern "C" int spqr_plan_grouped(int count, const int32_t* m, const int32_t* n, 
   return gp.count;
 }
 
-extern "C" int spqr_batch_route(int m, int n, int64_t nnz, int has_perm, int w_bits, int beta1, int beta2, int group_axis, int b,
-                                int64_t scratch) {
+extern "C" int spqr_batch_route(int m, int n, int64_t nnz, int max_row_nnz, int has_perm, int w_bits, int beta1, int beta2,
+                                int group_axis, int b, int64_t scratch) {
   static const int32_t some = 0;             // an address that is not null, never read
   spqr::DevMatrix D = {};
-  if (nnz < 0 || scratch < SPQR_SCRATCH_STATIC) return SPQR_ERR_PARAM;
+  if (nnz < 0 || max_row_nnz < 0 || scratch < SPQR_SCRATCH_STATIC) return SPQR_ERR_PARAM;
   if (b < 1 || b > SPQR_MAX_BATCH) return SPQR_ERR_BATCH;
   const int rc = spqr::make_geometry(spqr::kBilevel, m, n, w_bits, 3, 3, beta1, beta2, group_axis, &D.g);
   if (rc) return rc;
   D.nnz = nnz;
+  D.max_row_nnz = max_row_nnz;
   D.perm = has_perm ? &some : nullptr;
   spqr::Workspace ws;
   ws.from_caller = scratch != SPQR_SCRATCH_LIBRARY;

@@ -520,19 +520,26 @@ bool prompt_has_instance(const DevMatrix& A) {
 }
 
 // Where the dense copy pays against slices of 16 (prefill_wanted: from 48 vectors on, later on larger layers) and this kernel
-// is faster than the copy: from 4 M weights and 512 columns on, with tiles of 8 columns from 12 M on.  Times in us, the copy ->
-// here, 48 to 256 vectors, 1 % of outliers, uniform: 2048^2 25 .. 32 -> 22 .. 29, 4096^2 35 .. 45 -> 27 .. 40, 11008 x 4096 62 .. 95 ->
-// 38 .. 61, 17920 x 2048 54 .. 81 -> 38 .. 64; 1024^2 21 .. 24 against 22 .. 24; 17920 x 256 23 .. 32 against 27 .. 36 (too few
-// phases to a group).  With Zipf rows, over the same sizes and formats, 2048^2 is 6 % faster, 4096^2 8 % (with tiles of 8 columns
-// 4 % slower from 96 vectors on, and 2048^2 up to 16 % slower: a unit is one phase there), 1024 x 17920 at 256 vectors up to 10 %
-// slower.  From 17 vectors on this kernel would beat the slices, but they add the outliers in binary32 and here weight +
-// outlier is rounded to binary16, so no batch that took the slices moves here.  With a pinned plan (SPQR_OPT_PROMPT_PLAN) the
-// size is no matter.
-static bool prompt_pays(const Geometry& g) { return (double)g.m * g.n >= (g.tile_cols == 8 ? 12e6 : 4e6) && g.n >= 512; }
+// is faster than the copy: from 4 M weights and 512 columns on.  Times in us, the copy -> here, 48 to 256 vectors, 1 % of outliers,
+// uniform and with Zipf rows: 2048^2 25 .. 31 -> 21 .. 27 and 24 .. 31 -> 23 .. 29, 4096^2 35 .. 45 -> 28 .. 43 and 33 .. 44 -> 29 .. 44,
+// 1024 x 17920 58 .. 65 -> 32 .. 47 and 57 .. 63 -> 36 .. 49, 17920 x 1536 44 .. 65 -> 33 .. 52 and 42 .. 62 -> 35 .. 57; 1024^2 21 .. 24
+// against 22 .. 24; 17920 x 256 23 .. 32 against 27 .. 36 (too few phases to a group).  The one size above the line that loses
+// is 2048 x 4096 and its like above 192 vectors with uneven rows, 31 .. 33 against 32 .. 36, where the copy's multiply fills the chip.
+// Tiles of 8 columns: from 18 M on (17920 x 1024, Zipf rows, 34 .. 48 against 33 .. 49; 3072 x 6144 37 .. 48 against 36 .. 47); from 12 M
+// on below 96 vectors or where the rows hold much the same number of outliers (a unit is one phase, and a group with heavy rows makes
+// every one of its phases longer: 4096^2 from 96 vectors on 35 .. 43 against 35 .. 43 uniform, 35 .. 42 against 37 .. 47 with Zipf rows).
+// From 17 vectors on this kernel would beat the slices, but they add the outliers in binary32 and here weight + outlier is rounded to
+// binary16, so no batch that took the slices moves here.  With a pinned plan (SPQR_OPT_PROMPT_PLAN) the size is no matter.
+static bool prompt_pays(const DevMatrix& A, int b) {
+  const double weights = (double)A.g.m * A.g.n, mean = (double)A.nnz / A.g.m;
+  if (A.g.n < 512 || weights < 4e6) return false;
+  const bool even = A.nnz == 0 || (A.max_row_nnz > 0 && A.max_row_nnz <= 64 + 8 * mean);     // by the descriptor's hint
+  return A.g.tile_cols != 8 || weights >= 18e6 || (weights >= 12e6 && (b < 96 || even));
+}
 
 bool prompt_wanted(const DevMatrix& A, int b) {
   return option(SPQR_OPT_BATCH_PATH) == SPQR_BATCH_PATH_AUTO && prompt_has_instance(A) && prefill_wanted(A, b) &&
-         (prompt_pays(A.g) || option(SPQR_OPT_PROMPT_PLAN) >= 1);
+         (prompt_pays(A, b) || option(SPQR_OPT_PROMPT_PLAN) >= 1);
 }
 
 // Scratch of one call: the batch as operands, in column order before that if there is a permutation, per matrix the sorted outliers, their ranges,

@@ -43,12 +43,12 @@ int spqr_plan_grouped(int count, const int32_t* m, const int32_t* n, const int32
 int spqr_plan_prompt(int count, const int32_t* m, const int32_t* n, const int32_t* max_row_nnz, const int64_t* nnz, int w_bits,
                      int beta1, int beta2, int group_axis, int b, int most_slots, int32_t* plan, double* us);
 
-/* The way a batch of b vectors (Y 16-byte aligned) goes through a matrix of layout 1 (3-bit statistic codes) with nnz outliers
- * and, if has_perm, a permutation: 0 slices of 16 and fewer, 1 a dense copy, 2 the one-pass kernel, or an SPQR_ERR_* code.
+/* The way a batch of b vectors (Y 16-byte aligned) goes through a matrix of layout 1 (3-bit statistic codes) with nnz outliers,
+ * the hint max_row_nnz and, if has_perm, a permutation: 0 slices of 16 and fewer, 1 a dense copy, 2 the one-pass kernel, or an SPQR_ERR_* code.
  * Its scratch is a workspace of `scratch` bytes, SPQR_SCRATCH_LIBRARY or SPQR_SCRATCH_STATIC (the static array). */
 #define SPQR_SCRATCH_LIBRARY (-1)
 #define SPQR_SCRATCH_STATIC  (-2)
-int spqr_batch_route(int m, int n, int64_t nnz, int has_perm, int w_bits, int beta1, int beta2, int group_axis, int b, int64_t scratch);
+int spqr_batch_route(int m, int n, int64_t nnz, int max_row_nnz, int has_perm, int w_bits, int beta1, int beta2, int group_axis, int b, int64_t scratch);
 
 /* What the outlier sort of the one-pass product makes of the row pointers (a HOST array of m + 1 entries) of a matrix with
  * nnz outliers in groups of `rows` rows: ranges[3 * g + 0..2] = first entry, end, slot of the group's first chunk of

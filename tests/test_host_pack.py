@@ -411,9 +411,9 @@ SLICES, COPY, ONE_PASS = 0, 1, 2
 LIBRARY, STATIC = -1, -2
 
 
-def _route(m, n, w, b1, b2, axis, rate, b, scratch, perm=False):
+def _route(m, n, w, b1, b2, axis, rate, b, scratch, perm=False, hint=0):
     from paper_2306_03078_amd import binding as B
-    return B.load_library().spqr_batch_route(m, n, C.c_int64(int(rate * m * n)), int(perm), w, b1, b2, axis, b, C.c_int64(scratch))
+    return B.load_library().spqr_batch_route(m, n, C.c_int64(int(rate * m * n)), hint, int(perm), w, b1, b2, axis, b, C.c_int64(scratch))
 
 
 # `line`: the scratch from which on a call of that size has had 16-bit sums of weight and outlier since it could, the dense copy
@@ -435,6 +435,16 @@ def test_a_batch_is_rounded_no_earlier_for_a_smaller_plan(m, n, w, b1, b2, axis,
     assert route == [ONE_PASS, ONE_PASS, SLICES, SLICES, static] and need >= line
     if copy:
         assert _route(m, n, w, b1, b2, axis, rate, b, line, perm) == ONE_PASS
+
+
+@pytest.mark.parametrize("m,n,b,hint,route", [
+    (4096, 4096, 48, 4096, ONE_PASS), (4096, 4096, 95, 0, ONE_PASS), (4096, 4096, 96, 4096, COPY), (4096, 4096, 256, 0, COPY),
+    (4096, 4096, 256, 80, ONE_PASS), (2048, 8192, 192, 8192, COPY), (3584, 3584, 128, 700, COPY), (3584, 3584, 128, 60, ONE_PASS),
+    (17920, 1024, 256, 1024, ONE_PASS), (3072, 6144, 128, 0, ONE_PASS), (3456, 3456, 64, 60, COPY)])
+def test_narrow_tiles_with_heavy_rows_take_the_copy(m, n, b, hint, route):
+    """Tiles of 8 columns between 12 and 18 M weights: the copy is up to 15 % faster there where a few rows hold the outliers (hint:
+    the longest row; 0: not known) and the batch is not small."""
+    assert _route(m, n, 3, 8, 32, 0, 0.01, b, LIBRARY, hint=hint) == route
 
 
 def test_a_batch_with_the_reported_scratch_goes_as_with_the_librarys():
