@@ -397,16 +397,6 @@ def test_workspace_of_the_one_pass_kernel_holds_no_dense_copy():
     assert _workspace_bytes(1024, 1024, 4, 16, 16, 1, 0.01, 64) > 2 * 1024 * 1024
 
 
-@pytest.mark.parametrize("m,n,w,b1,b2,b,one_pass", [
-    (17920, 2048, 4, 16, 16, 256, False), (17920, 2048, 4, 16, 16, 192, True), (17920, 1536, 3, 16, 16, 256, False),
-    (17920, 2064, 4, 16, 16, 256, True), (5120, 5120, 3, 16, 16, 256, True), (4864, 4864, 4, 16, 16, 128, False),
-    (17920, 256, 3, 8, 32, 128, False), (17920, 480, 3, 8, 32, 128, False), (8192, 512, 3, 8, 32, 128, True),
-    (2048, 2048, 3, 8, 32, 64, True), (1024, 1024, 3, 8, 32, 64, False)])
-def test_sizes_of_the_one_pass_kernel(m, n, w, b1, b2, b, one_pass):
-    """Where the dense copy is faster, the batch takes the copy, and its scratch holds one: 2 bytes per weight."""
-    assert (_workspace_bytes(m, n, w, b1, b2, 1, 0.01, b) < 2 * m * n) == one_pass
-
-
 SLICES, COPY, ONE_PASS = 0, 1, 2
 LIBRARY, STATIC = -1, -2
 
@@ -414,6 +404,18 @@ LIBRARY, STATIC = -1, -2
 def _route(m, n, w, b1, b2, axis, rate, b, scratch, perm=False, hint=0):
     from paper_2306_03078_amd import binding as B
     return B.load_library().spqr_batch_route(m, n, C.c_int64(int(rate * m * n)), hint, int(perm), w, b1, b2, axis, b, C.c_int64(scratch))
+
+
+# both sides of 4 M weights, of 512 columns and of 12 M weights with tiles of 8 columns
+@pytest.mark.parametrize("m,n,w,b1,b2,axis,b,route", [
+    (17920, 2048, 4, 16, 16, 1, 256, ONE_PASS), (17920, 2048, 4, 16, 16, 1, 192, ONE_PASS), (17920, 1536, 3, 16, 16, 1, 256, ONE_PASS),
+    (17920, 2064, 4, 16, 16, 1, 256, ONE_PASS), (5120, 5120, 3, 16, 16, 1, 256, ONE_PASS), (4864, 4864, 4, 16, 16, 1, 128, ONE_PASS),
+    (2000, 2000, 3, 16, 16, 0, 48, ONE_PASS), (1984, 2000, 3, 16, 16, 0, 48, COPY), (1984, 2000, 3, 16, 16, 0, 47, SLICES),
+    (8192, 512, 4, 16, 16, 1, 128, ONE_PASS), (8192, 496, 4, 16, 16, 1, 128, COPY), (17920, 256, 3, 8, 32, 1, 128, COPY),
+    (17920, 480, 3, 8, 32, 1, 128, COPY), (8192, 512, 3, 8, 32, 1, 128, ONE_PASS), (2048, 2048, 3, 8, 32, 1, 64, ONE_PASS),
+    (1024, 1024, 3, 8, 32, 1, 64, COPY), (3488, 3440, 3, 8, 32, 0, 64, COPY), (3488, 3448, 3, 8, 32, 0, 64, ONE_PASS)])
+def test_sizes_of_the_one_pass_kernel(m, n, w, b1, b2, axis, b, route):
+    assert _route(m, n, w, b1, b2, axis, 0.01, b, LIBRARY) == route
 
 
 # `line`: the scratch from which on a call of that size has had 16-bit sums of weight and outlier since it could, the dense copy
