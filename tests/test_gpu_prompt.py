@@ -85,9 +85,9 @@ def test_every_width_of_the_one_pass_kernel(P, w, b1, b2, axis, ntr, ntc, struct
     run(P, f, b, prompt=1024 * vectors + units)
 
 
-def test_a_large_layer_takes_four_blocks_of_64_vectors_by_itself(P):
-    """8-row strips and 200 vectors, nothing pinned: 172 groups of strips are one workgroup per CU with 256 vectors each (19
-    us by the plan's model), two rounds of them with 128 (29) and three with 64 (39)."""
+def test_two_blocks_of_vectors_by_itself(P):
+    """8-row strips and 200 vectors, nothing pinned: 172 groups of 2 units, two blocks of 128 vectors, runs of 3 units from one
+    group into the next, the last rows and columns ragged."""
     f = synth.make_matrix(8 * 2751, 32 * 19, w_bits=3, beta1=8, beta2=32, group_axis=1, outlier_rate=0.02,
                           outlier_structure="cols64", seed=(82,))
     run(P, f, 200)
@@ -428,3 +428,33 @@ def test_sort_with_any_number_of_workgroups(P, w, b1, b2, axis, ntr, ntc, struct
     A.desc.max_row_nnz = hint
     assert torch.equal(P.spqr_gemm_smallbatch(A, X), want)
     P.spqr_set_option(P.SPQR_OPT_PROMPT_PLAN, 0)
+
+
+# 77 vectors: runs of 2 of 8 units; 256: of 5, two blocks of vectors
+@pytest.mark.parametrize("b,perm", [(77, True), (256, False)])
+def test_one_pass_of_several_matrices_by_itself(P, b, perm):
+    """Nothing pinned, layers just above the size from which it is this kernel's, rows that differ: against the oracle, other partial
+    sums than the single calls' (so they went together), and the binary16 outputs are the binary32 ones rounded."""
+    import torch
+    fs = [synth.make_matrix(m, 2000, w_bits=3, beta1=16, beta2=16, group_axis=1, outlier_rate=0.01, outlier_structure=st, seed=(95, m))
+          for m, st in ((2064, "zipf"), (2128, "uniform"), (2000, "rows8cols4"))]
+    if perm:
+        for f in fs:
+            f.perm = np.random.default_rng(5).permutation(f.n).astype(np.int32)
+    As = [P.SpQRMatrix.from_logical(f) for f in fs]
+    for A in As[1:]:
+        A.desc.perm = As[0].desc.perm          # descriptors must name the same device permutation
+    X = synth.make_x(2000, b, seed=(96, b))
+    Xd = torch.from_numpy(X).to("cuda:0")
+    ws = torch.empty(P.spqr_workspace_bytes(As, b), dtype=torch.uint8, device="cuda:0")
+    Ys = P.spqr_gemm_fused_ws(As, Xd, ws)
+    halves = P.spqr_gemm_fused_ws(As, Xd, ws, y_dtype=P.SPQR_F16)
+    own = [P.spqr_gemm_smallbatch_ws(A, Xd, ws).clone() for A in As]
+    assert not all(torch.equal(Y, O) for Y, O in zip(Ys, own))
+    for f, Y, H, O in zip(fs, Ys, halves, own):
+        assert torch.equal(H, Y.to(torch.float16))
+        assert (Y - O).norm() <= 1e-5 * O.norm()               # the same weights, sums in another order
+        Xp = X.astype(np.float64) if f.perm is None else X.astype(np.float64)[:, f.perm]
+        terms = np.sqrt(Xp ** 2 @ (orc.reconstruct(f) ** 2).T)
+        err = np.linalg.norm(Y.cpu().numpy() - orc.matvec(f, X), axis=1) / np.linalg.norm(terms, axis=1)
+        assert err.max() <= REL_L2
