@@ -331,7 +331,8 @@ int spqr_gemv_fused(const spqr_matrix_t* const* A, int count, const uint16_t* x_
  * otherwise), A and Y are HOST arrays.  Where the batch takes the matrix-core
  * path of spqr_gemm_smallbatch, all matrices share one launch for the products
  * and one for the sums per slice of 16 vectors, and where every matrix takes the
- * one-pass kernel, that kernel's launches;
+ * one-pass kernel and all of them together are no slower than one by one (by the
+ * plans' model), that kernel's launches;
  * otherwise, and whenever `stream` is being captured into a graph, the call is
  * `count` calls of spqr_gemm_smallbatch (b == 1: one spqr_gemv_fused).  Scratch
  * as for spqr_gemm_smallbatch (library-owned; spqr_gemm_fused_ws takes the
@@ -342,7 +343,11 @@ int spqr_gemm_fused(const spqr_matrix_t* const* A, int count, const uint16_t* X_
                     void* const* Y, int y_dtype, void* stream);
 
 /* spqr_gemm_fused with scratch the caller owns: see spqr_gemm_smallbatch_ws;
- * the workspace holds at least spqr_workspace_bytes(A, count, b) bytes. */
+ * the workspace holds at least spqr_workspace_bytes(A, count, b) bytes.  One thing
+ * differs: where the matrices would share launches, a call on a capturing stream is
+ * `count` calls of spqr_gemm_smallbatch_ws (kernel nodes only all the same), so its
+ * partial sums may meet in another order than those of the same call made eagerly,
+ * and the results differ in their last bits. */
 int spqr_gemm_fused_ws(const spqr_matrix_t* const* A, int count, const uint16_t* X_f16, int b,
                        void* const* Y, int y_dtype, void* workspace, int64_t workspace_bytes,
                        void* stream);

@@ -115,6 +115,8 @@ hipError_t launch_gemm_fused(const DevMatrix* As, int count, const uint16_t* X, 
   // 42 calls (a whole decoder block, six weight copies) once ended in a memory fault inside the fused kernel that
   // added the outliers (gone since: batch_group_fused_kernel adds them), while the same calls passed eagerly and
   // graphs of the per-matrix path replay correctly; the cause was never known, so captured calls take the per-matrix path.
+  // That holds for the one-pass kernel's sets too: it is another kernel, but several matrices in a captured launch set are what
+  // the calls of that graph had and the others had not.  (Results then differ from the eager call's in the order of sums.)
   const bool capturing = mfma_ok && b >= kMfmaMinBatch && stream_is_capturing(stream);
   if (capturing) mfma_ok = false;
   // a large batch: all matrices in the launches of the one-pass kernel where every one of them takes it, else one matrix at a
