@@ -7,6 +7,7 @@ from __future__ import annotations
 
 import ctypes as C
 import os
+from operator import index
 from typing import Optional
 
 import numpy as np
@@ -14,7 +15,7 @@ import numpy as np
 HERE = os.path.dirname(os.path.abspath(__file__))
 _LIB_PATH = os.path.join(HERE, "libspqr.so")
 _lib = None
-_call = None                    # the extension module's call, the entries' addresses for it, torch.float16
+_call = None                    # the extension module's call (or _ctypes_call), the entries for it, torch.float16
 _entry = {}
 _half = None
 
@@ -47,6 +48,11 @@ class spqr_matrix_t(C.Structure):
         ("row_ptr", C.c_void_p), ("col_idx", C.c_void_p), ("out_val", C.c_void_p),
         ("nnz", C.c_int64), ("perm", C.c_void_p),
     ]
+
+
+def _ctypes_call(entry, descriptor, *args):
+    """What the extension module's call does, through ctypes."""
+    return entry(C.byref(descriptor), *[a.data_ptr() if hasattr(a, "data_ptr") else a for a in args])
 
 
 def library_path() -> str:
@@ -104,10 +110,13 @@ def load_library():
     lib.spqr_gemv_grouped.argtypes = [C.POINTER(P), C.c_int, C.POINTER(vp), C.POINTER(vp), C.c_int, vp]
     lib.spqr_gemm_smallbatch_noalloc.restype = C.c_int
     lib.spqr_gemm_smallbatch_noalloc.argtypes = [P, vp, C.c_int, vp, C.c_int, vp]
-    from . import _calls
+    try:
+        from . import _calls
+    except ImportError:          # built without it (no C compiler or no Python.h): the same calls, 3 us slower each
+        _calls = None
     for name in ("spqr_gemv", "spqr_gemm_smallbatch", "spqr_gemm_smallbatch_ws"):
-        _entry[name] = C.cast(getattr(lib, name), C.c_void_p).value
-    _call = _calls.call
+        _entry[name] = C.cast(getattr(lib, name), C.c_void_p).value if _calls else getattr(lib, name)
+    _call = _calls.call if _calls else _ctypes_call
     _half = torch.float16
     _lib = lib
     return lib
@@ -255,7 +264,8 @@ def spqr_gemv(A: SpQRMatrix, x, out=None, y_dtype: int = SPQR_F32, stream=None):
     if out is None:
         import torch
         out = torch.empty(A.m, dtype=_out_dtype(y_dtype), device=x.device)
-    rc = _call(_entry["spqr_gemv"], A.desc, x, out, y_dtype, _stream_ptr(stream))
+    # (as ctypes had it: an output has an address of its own, a dtype is a number)
+    rc = _call(_entry["spqr_gemv"], A.desc, x, out.data_ptr(), index(y_dtype), _stream_ptr(stream))
     if rc != 0:
         _check(rc, "spqr_gemv")
     return out
@@ -270,7 +280,8 @@ def spqr_gemm_smallbatch(A: SpQRMatrix, X, out=None, y_dtype: int = SPQR_F32, st
         out = torch.empty((b, A.m), dtype=_out_dtype(y_dtype), device=X.device)
     if _lib is None:
         load_library()
-    _check(_call(_entry["spqr_gemm_smallbatch"], A.desc, X, b, out, y_dtype, _stream_ptr(stream)), "spqr_gemm_smallbatch")
+    _check(_call(_entry["spqr_gemm_smallbatch"], A.desc, X, b, out.data_ptr(), index(y_dtype), _stream_ptr(stream)),
+           "spqr_gemm_smallbatch")
     return out
 
 
@@ -337,7 +348,8 @@ def spqr_gemm_smallbatch_ws(A: SpQRMatrix, X, workspace, out=None, y_dtype: int 
     wp, wb = _ws_args(workspace)
     if _lib is None:
         load_library()
-    _check(_call(_entry["spqr_gemm_smallbatch_ws"], A.desc, X, b, out, y_dtype, wp, wb, _stream_ptr(stream)), "spqr_gemm_smallbatch_ws")
+    _check(_call(_entry["spqr_gemm_smallbatch_ws"], A.desc, X, b, out.data_ptr(), index(y_dtype), wp, wb, _stream_ptr(stream)),
+           "spqr_gemm_smallbatch_ws")
     return out
 
 

@@ -3,7 +3,9 @@ extension module through which Python calls it (host code only)."""
 from __future__ import annotations
 
 import os
+import shutil
 import subprocess
+import sys
 import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
@@ -36,9 +38,23 @@ def build_library(verbose: bool = False) -> str:
     with ThreadPoolExecutor(max_workers=min(len(jobs), os.cpu_count() or 1, 8)) as pool:
         list(pool.map(lambda c: _run(c, verbose), jobs))
     _run([hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB, *objs], verbose)
-    _run(["gcc", "-O2", "-Wall", "-shared", "-fPIC", "-I" + sysconfig.get_paths()["include"], "-o", CALLS,
-          os.path.join(CSRC, "spqr_calls.c")], verbose)
+    calls = calls_command()
+    if calls is not None:
+        _run(calls, verbose)
+    else:                        # nor one of an earlier build
+        if os.path.exists(CALLS):
+            os.remove(CALLS)
+        print("no C compiler or no Python.h: Python calls the library through ctypes", file=sys.stderr)
     return LIB
+
+
+def calls_command():
+    """The command that builds the extension module, None where there is no C compiler or no Python.h: the binding does without."""
+    include = sysconfig.get_paths()["include"]
+    cc = next(filter(None, map(shutil.which, [os.environ.get("CC", "").split(" ")[0], "gcc", "cc", "clang"])), None)
+    if cc is None or not os.path.exists(os.path.join(include, "Python.h")):
+        return None
+    return [cc, "-O2", "-Wall", "-shared", "-fPIC", "-I" + include, "-o", CALLS, os.path.join(CSRC, "spqr_calls.c")]
 
 
 if __name__ == "__main__":

@@ -544,3 +544,51 @@ def test_direct_calls_take_tensors_by_address_and_refuse_what_they_cannot_pass()
         with pytest.raises(TypeError):
             B._call(*bad)
     assert B._call(B._entry["spqr_gemv"], d, one, one, 0, None) == -3      # refused before any HIP call
+
+
+@pytest.mark.parametrize("extension", [True, False])
+def test_product_calls_refuse_what_they_always_did_with_and_without_the_extension_module(extension, monkeypatch):
+    """A number is no output, None no dtype; a library that was built without the extension module loads and gives the same
+    statuses.  (A descriptor of zeros is refused before any HIP call.)"""
+    import sys
+    from types import SimpleNamespace
+    import torch
+    from paper_2306_03078_amd import binding as B
+    B.load_library()
+    monkeypatch.setattr(B, "_lib", None)
+    monkeypatch.setattr(B, "_call", None)
+    monkeypatch.setattr(B, "_entry", {})
+    if not extension:
+        monkeypatch.setitem(sys.modules, "paper_2306_03078_amd._calls", None)
+        monkeypatch.delattr(sys.modules["paper_2306_03078_amd"], "_calls", raising=False)
+    B.load_library()
+    assert (B._call is B._ctypes_call) != extension
+    stream = SimpleNamespace(cuda_stream=0)
+    A = SimpleNamespace(desc=B.spqr_matrix_t(), m=4, n=8)
+    x, X, y, Y, ws = (torch.zeros(k, dtype=torch.float16) for k in (8, (2, 8), 4, (2, 4), 256))
+    calls = (lambda out, dt: B.spqr_gemv(A, x, out=out, y_dtype=dt, stream=stream),
+             lambda out, dt: B.spqr_gemm_smallbatch(A, X, out=out, y_dtype=dt, stream=stream),
+             lambda out, dt: B.spqr_gemm_smallbatch_ws(A, X, ws, out=out, y_dtype=dt, stream=stream))
+    for call, out in zip(calls, (y, Y, Y)):
+        with pytest.raises(AttributeError):
+            call(out.data_ptr(), B.SPQR_F16)
+        for dtype in (None, 1.0):
+            with pytest.raises((TypeError, C.ArgumentError)):
+                call(out, dtype)
+        with pytest.raises(B.SpQRError) as e:
+            call(out, B.SPQR_F16)
+        assert e.value.status == -3
+
+
+def test_build_does_without_the_extension_module(monkeypatch, tmp_path):
+    """No compiler or no Python.h: no command for it, rather than a build that fails."""
+    import shutil
+    import sysconfig
+    from paper_2306_03078_amd import build
+    assert build.calls_command()[-1].endswith("spqr_calls.c")
+    paths = dict(sysconfig.get_paths())
+    with monkeypatch.context() as m:
+        m.setattr(sysconfig, "get_paths", lambda *a: dict(paths, include=str(tmp_path)))
+        assert build.calls_command() is None
+    monkeypatch.setattr(shutil, "which", lambda name: None)
+    assert build.calls_command() is None
