@@ -51,7 +51,7 @@ def build_library(verbose: bool = False) -> str:
 def calls_command():
     """The command that builds the extension module, None where there is no C compiler or no Python.h: the binding does without."""
     include = sysconfig.get_paths()["include"]
-    cc = next(filter(None, map(shutil.which, [os.environ.get("CC", "").split(" ")[0], "gcc", "cc", "clang"])), None)
+    cc = next(filter(None, map(shutil.which, ["gcc", "cc", "clang"])), None)
     if cc is None or not os.path.exists(os.path.join(include, "Python.h")):
         return None
     return [cc, "-O2", "-Wall", "-shared", "-fPIC", "-I" + include, "-o", CALLS, os.path.join(CSRC, "spqr_calls.c")]

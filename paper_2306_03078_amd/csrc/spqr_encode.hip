@@ -344,8 +344,8 @@ __global__ void __launch_bounds__(64 * kWaves) sweep_kernel(SweepArgs a) {
 //   feedback  lanes = columns, a wavefront takes up to 256 columns of all 16 rows (64 sums a lane, far_feedback)
 // Same operations in the same order on every weight as sweep_kernel, hence the same bits.
 // Bound: binary64 issue of the feedback (m n^2 products and differences) next to the chain (n columns, two true
-// divisions each, one after the other).  4096^2 with blocks of 16, measured part by part: far feedback 3.3 ms (2.1 at the
-// issue rate of its products and differences, 9.5 clocks a pair), chain 1.9 (7.5 us a block), tests 0.9, the rest 0.6.
+// divisions each, one after the other).  4096^2 with blocks of 16, measured part by part: far feedback 3.3 ms (1.74 at the
+// vector unit's rate, 8 clocks a product and its difference; the pairs are issued in 9.5), chain 1.9 (7.5 us a block), tests 0.9, the rest 0.6.
 // ---------------------------------------------------------------------------
 constexpr int kRows16 = 16, kWaves16 = 8, kSuper16 = 128;
 
@@ -719,11 +719,12 @@ int spqr_quantize(const double* W, const double* Hic, int32_t m, int32_t n, int3
   a.w_top = (double)((1 << w_bits) - 1); a.s_top = (double)((1 << s_bits) - 1); a.z_top = (double)((1 << z_bits) - 1);
   a.tau = tau;
   a.out = *out;
-  // 16 rows per workgroup where a tile has no more and every workgroup gets a CU (beta1 = beta2 = 16, 1 % outliers, 4096
-  // columns: 4096 rows 17.7 -> 11.1 ms, 1024 columns and rows 2.38 -> 1.33 ms; beta1 = 32, no outlier test, 4000 x 512 0.76 -> 0.43),
-  // in place on W_final where the caller wants it; 64 rows per workgroup where there are more rows (5120^2 25.7 ms, with 16 a
-  // workgroup 30.9; 8192 x 1024 2.44 against 2.68, 11008 x 4096 18.3 against 32.4; with beta1 = 8 the line would lie higher: 8192 x
-  // 2048 5.8 against 4.3) or taller tiles.
+  // 16 rows per workgroup where a tile has no more and every workgroup gets a CU, in place on W_final where the caller wants it; 64
+  // rows per workgroup where there are more rows or taller tiles.  ms with 64 and with 16 rows a workgroup, beta2 = 16, 1 % outliers,
+  // the time of either a staircase of rounds of 256 workgroups: 4096^2 17.7 and 6.6; 11008 x 4096 18.4 and 19.7 (beta1 = 8: 17.3 and
+  // 20.2, beta1 = 32: 21.1 and 21.8), 9216 x 4096 18.1 and 19.4, 16384 x 2048 6.65 and 10.2.  The line at one round is older than
+  // the 16-row kernel as it is: at two rounds that would be the faster one in most cases (8192 x 4096 18.1 and 13.2, 5120^2 25.9 and 18.0,
+  // 6656^2 40.6 and 26.5; 8192 x 1024 2.45 and 2.28, with beta1 = 8 2.20 and 2.35).
   if (beta2 <= kRows16 && m <= kRows16 * 256) {
     if (out->W_final) a.Wt = out->W_final;
     if (a.Wt != W) hipLaunchKernelGGL(copy_kernel, dim3(2048), dim3(256), 0, st, W, a.Wt, (size_t)m * n);

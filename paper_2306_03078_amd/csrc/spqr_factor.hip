@@ -16,9 +16,9 @@
 //
 // Every tile product runs on the matrix cores (v_mfma_f64_16x16x4_f64), at the vector ALU's rate, but an operand of one
 // 8-byte half of an LDS read per lane feeds two instructions of 64 clocks.  n = d = 4096: Hessian 2.4 -> 1.65 ms (42 of 68 TFLOP/s;
-// staged by rows, squares of tiles per XCD), a block column of the factorisation 47 -> 32 us (the next diagonal block beside the trailing
-// update), the triangular inverse 1.13 -> 0.92 ms, Hessian and factor together 6.75 -> 4.9 ms.  What is left: the chain of 64
-// diagonal blocks of 20 us and panels of 5, bank conflicts and the barrier of every step of k in the products.
+// staged by rows, squares of tiles per XCD), a block column of the factorisation 47 -> 33 us (the next diagonal block beside the trailing
+// update), the triangular inverse 1.13 -> 0.92 ms, Hessian and factor together 6.7 -> 4.7 ms.  What is left: the chain of 64
+// diagonal blocks of 20 us and panels of 5, bank conflicts (half of the LDS clocks of every product) and the barrier of every step of k.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -28,7 +28,9 @@ namespace spqr_fac {
 
 constexpr int NB = 64;                       // block size of the factorisation
 constexpr int KC = 16;                       // depth of one LDS stage of a tile product
-constexpr int LP = KC + 2;                   // padded row of a staged operand: 16 rows of 16 bytes each meet every bank once
+// Padded row of a staged operand.  Conflicts are as many LDS clocks as the rest still (SQ_LDS_BANK_CONFLICT is half of
+// SQ_LDS_IDX_ACTIVE, reads and writes together); the Hessian with 0, 4, 6 and 8 instead of 2: 4.4, 1.79, 1.69 and 2.6 ms against 1.65.
+constexpr int LP = KC + 2;
 
 typedef double f64x2 __attribute__((ext_vector_type(2)));
 typedef double f64x2_8 __attribute__((ext_vector_type(2), aligned(8)));
