@@ -212,9 +212,11 @@ sort_phases_kernel(PromptSet S, int unit_shift, int kg, int bins) {
 // registers and the LDS (65 KB) for a second workgroup, whose wavefronts run where this one's wait at the barrier.  A whole
 // row of units instead of a grid of groups times splits: 17920 x 6656 is 140 groups of 26 units, which no number of splits
 // deals evenly to 256 CUs.
-// Measured (the whole call with the sort, 24 and 16 us, and the sums, 11 and 5; before: groups of 256 rows, one workgroup of one
-// wavefront per SIMD, a matrix at a time): 17920 x 6656, 4-bit, 256 vectors 162 -> 124 us; gate and up 11008 x 4096, 3-bit, 77
-// vectors 101 -> 63; 4096^2 at 128 vectors, which the dense copy took, 38 -> 33.
+// Measured (the whole call with the sort, 20 and 15 us, and the sums, 11 and 5; before: groups of 256 rows, one workgroup of one
+// wavefront per SIMD, a matrix at a time): 17920 x 6656, 4-bit, 256 vectors 162 -> 114 us; gate and up 11008 x 4096, 3-bit, 77
+// vectors 101 -> 59; 4096^2 at 128 vectors, which the dense copy took, 39 -> 34.  Slower than that kernel: 8 x 32 tiles, 4 to 16 M
+// weights and 48 vectors, up to 4 % of 24 us one call behind another (a workgroup's start is 1.5 us longer; 7 % faster alone), and
+// without outliers, where ordering the batch is a launch more (2048^2 10.9 -> 15.4).
 // ---------------------------------------------------------------------------
 template <int W, int TR, int TC, int AXIS, int RW, int NVB>
 __global__ void __launch_bounds__(256, 2)
