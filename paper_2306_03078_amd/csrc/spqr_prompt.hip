@@ -214,9 +214,9 @@ sort_phases_kernel(PromptSet S, int unit_shift, int kg, int bins) {
 // deals evenly to 256 CUs.
 // Measured (the whole call with the sort, 20 and 15 us, and the sums, 11 and 5; before: groups of 256 rows, one workgroup of one
 // wavefront per SIMD, a matrix at a time): 17920 x 6656, 4-bit, 256 vectors 162 -> 114 us; gate and up 11008 x 4096, 3-bit, 77
-// vectors 101 -> 59; 4096^2 at 128 vectors, which the dense copy took, 39 -> 34.  Slower than that kernel: 8 x 32 tiles, 4 to 16 M
-// weights and 48 vectors, up to 4 % of 24 us one call behind another (a workgroup's start is 1.5 us longer; 7 % faster alone), and
-// without outliers, where ordering the batch is a launch more (2048^2 10.9 -> 15.4).
+// vectors 101 -> 59; 4096^2 at 128 vectors, which the dense copy took, 39 -> 34.  Slower than that kernel: 8 x 32 tiles with 4 to 16 M
+// weights, 1 to 2 of some 25 us (a workgroup's start is that much longer; at most 4 % when calls follow one another closely, 7 %
+// faster alone), and layers without outliers, where ordering the batch is a launch more (2048^2 10.9 -> 15.4).
 // ---------------------------------------------------------------------------
 template <int W, int TR, int TC, int AXIS, int RW, int NVB>
 __global__ void __launch_bounds__(256, 2)
@@ -528,15 +528,16 @@ bool prompt_has_instance(const DevMatrix& A) {
 // against 22 .. 24; 17920 x 256 23 .. 32 against 27 .. 36 (too few phases to a group).  The one size above the line that loses
 // is 2048 x 4096 and its like above 192 vectors with uneven rows, 31 .. 33 against 32 .. 36, where the copy's multiply fills the chip.
 // Tiles of 8 columns: from 18 M on (17920 x 1024, Zipf rows, 34 .. 48 against 33 .. 49; 3072 x 6144 37 .. 48 against 36 .. 47); from 12 M
-// on below 96 vectors or where the rows hold much the same number of outliers (a unit is one phase, and a group with heavy rows makes
-// every one of its phases longer: 4096^2 from 96 vectors on 35 .. 43 against 35 .. 43 uniform, 35 .. 42 against 37 .. 47 with Zipf rows).
+// on below 96 vectors, with fewer than 2048 rows (the copy's multiply has few workgroups there: 512 x 24576, Zipf rows, 65 .. 70 -> 37 .. 45)
+// or where the rows hold much the same number of outliers (a unit is one phase, and a group with heavy rows makes every one of its
+// phases longer: 4096^2 from 96 vectors on 35 .. 43 against 35 .. 43 uniform, 35 .. 42 against 37 .. 47 with Zipf rows).
 // From 17 vectors on this kernel would beat the slices, but they add the outliers in binary32 and here weight + outlier is rounded to
 // binary16, so no batch that took the slices moves here.  With a pinned plan (SPQR_OPT_PROMPT_PLAN) the size is no matter.
 static bool prompt_pays(const DevMatrix& A, int b) {
   const double weights = (double)A.g.m * A.g.n, mean = (double)A.nnz / A.g.m;
   if (A.g.n < 512 || weights < 4e6) return false;
   const bool even = A.nnz == 0 || (A.max_row_nnz > 0 && A.max_row_nnz <= 64 + 8 * mean);     // by the descriptor's hint
-  return A.g.tile_cols != 8 || weights >= 18e6 || (weights >= 12e6 && (b < 96 || even));
+  return A.g.tile_cols != 8 || weights >= 18e6 || (weights >= 12e6 && (b < 96 || A.g.m < 2048 || even));
 }
 
 bool prompt_wanted(const DevMatrix& A, int b) {

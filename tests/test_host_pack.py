@@ -442,6 +442,7 @@ def test_a_batch_is_rounded_no_earlier_for_a_smaller_plan(m, n, w, b1, b2, axis,
 @pytest.mark.parametrize("m,n,b,hint,route", [
     (4096, 4096, 48, 4096, ONE_PASS), (4096, 4096, 95, 0, ONE_PASS), (4096, 4096, 96, 4096, COPY), (4096, 4096, 256, 0, COPY),
     (4096, 4096, 256, 80, ONE_PASS), (2048, 8192, 192, 8192, COPY), (3584, 3584, 128, 700, COPY), (3584, 3584, 128, 60, ONE_PASS),
+    (512, 24576, 256, 24576, ONE_PASS), (2016, 8192, 256, 8192, ONE_PASS), (2048, 8192, 256, 8192, COPY),
     (17920, 1024, 256, 1024, ONE_PASS), (3072, 6144, 128, 0, ONE_PASS), (3456, 3456, 64, 60, COPY)])
 def test_narrow_tiles_with_heavy_rows_take_the_copy(m, n, b, hint, route):
     """Tiles of 8 columns between 12 and 18 M weights: the copy is up to 15 % faster there where a few rows hold the outliers (hint:
