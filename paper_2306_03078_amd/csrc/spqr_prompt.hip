@@ -216,7 +216,8 @@ sort_phases_kernel(PromptSet S, int unit_shift, int kg, int bins) {
 // wavefront per SIMD, a matrix at a time): 17920 x 6656, 4-bit, 256 vectors 162 -> 114 us; gate and up 11008 x 4096, 3-bit, 77
 // vectors 101 -> 59; 4096^2 at 128 vectors, which the dense copy took, 39 -> 34.  Slower than that kernel: 8 x 32 tiles with 4 to 16 M
 // weights, 1 to 2 of some 25 us (a workgroup's start is that much longer; at most 4 % when calls follow one another closely, 7 %
-// faster alone), and layers without outliers, where ordering the batch is a launch more (2048^2 10.9 -> 15.4).
+// faster alone), and the same tiles without any outliers, where ordering the batch is a launch more and 256 vectors are two passes
+// instead of one (48 .. 256 vectors, 2048^2 11 .. 13 -> 15 .. 20, 4096^2 13 .. 25 -> 18 .. 36; from 45 M weights on as fast or faster).
 // ---------------------------------------------------------------------------
 template <int W, int TR, int TC, int AXIS, int RW, int NVB>
 __global__ void __launch_bounds__(256, 2)
