@@ -213,7 +213,7 @@ sort_phases_kernel(PromptSet S, int unit_shift, int kg, int bins) {
 // row of units instead of a grid of groups times splits: 17920 x 6656 is 140 groups of 26 units, which no number of splits
 // deals evenly to 256 CUs.
 // Measured (the whole call with the sort, 20 and 15 us, and the sums, 11 and 5; before: groups of 256 rows, one workgroup of one
-// wavefront per SIMD, a matrix at a time): 17920 x 6656, 4-bit, 256 vectors 162 -> 114 us; gate and up 11008 x 4096, 3-bit, 77
+// wavefront per SIMD, a matrix at a time): 17920 x 6656, 4-bit, 256 vectors 162 -> 118 us; gate and up 11008 x 4096, 3-bit, 77
 // vectors 101 -> 59; 4096^2 at 128 vectors, which the dense copy took, 39 -> 34.  Slower than that kernel: 8 x 32 tiles with 4 to 16 M
 // weights, 1 to 2 of some 25 us (a workgroup's start is that much longer; at most 4 % when calls follow one another closely, 7 %
 // faster alone), and the same tiles without any outliers, where ordering the batch is a launch more and 256 vectors are two passes
