@@ -17,6 +17,8 @@
 #include <stdint.h>
 
 #include <cmath>
+#include <type_traits>
+#include <utility>
 
 #include "../../include/spqr_encode.h"
 
@@ -31,29 +33,15 @@ namespace spqr_enc {
 constexpr int kWaves = SPQR_SWEEP_WAVES;     // wavefronts per workgroup of the sweep
 constexpr int kRows = 64;                    // rows per workgroup: one per lane
 
-// binary64 -> binary16, round to nearest even, in one rounding (integer arithmetic on the bit pattern).
+// binary64 -> binary16, round to nearest even, in one rounding: by way of binary32 rounded to odd (its 24 bits are two more than the
+// 11 of binary16 need, so the second rounding sees what the first one dropped).  A NaN becomes the one quiet NaN.
 __device__ __forceinline__ uint16_t f64_to_f16_bits(double x) {
-  const uint64_t b = __builtin_bit_cast(uint64_t, x);
-  const uint16_t sign = (uint16_t)((b >> 48) & 0x8000u);
-  const int e = (int)((b >> 52) & 0x7FF);
-  const uint64_t mant = b & 0xFFFFFFFFFFFFFull;
-  if (e == 0x7FF) return sign | (mant ? 0x7E00u : 0x7C00u);
-  const int E = e - 1023;
-  if (E > 15) return sign | 0x7C00u;
-  if (E >= -14) {
-    uint32_t h = (uint32_t)((E + 15) << 10) | (uint32_t)(mant >> 42);
-    const uint64_t rem = mant & ((1ull << 42) - 1), half = 1ull << 41;
-    if (rem > half || (rem == half && (h & 1u))) ++h;          // a carry runs into the exponent, up to infinity
-    return sign | (uint16_t)h;
-  }
-  if (e == 0) return sign;                                     // binary64 subnormals are far below 2^-25
-  int shift = 42 + (-14 - E);
-  if (shift > 63) return sign;
-  const uint64_t full = mant | (1ull << 52);
-  uint32_t h = (uint32_t)(full >> shift);
-  const uint64_t rem = full & ((1ull << shift) - 1), half = 1ull << (shift - 1);
-  if (rem > half || (rem == half && (h & 1u))) ++h;
-  return sign | (uint16_t)h;
+  float f = (float)x;
+  const double back = (double)f;
+  uint32_t b = __builtin_bit_cast(uint32_t, f);
+  if (back != x) b = (b - (fabs(back) > fabs(x) ? 1u : 0u)) | 1u;
+  const uint16_t h = __builtin_bit_cast(uint16_t, (_Float16)__builtin_bit_cast(float, b));
+  return x == x ? h : (uint16_t)((b >> 16 & 0x8000u) | 0x7E00u);
 }
 
 __device__ __forceinline__ double f16_bits_to_f64(uint16_t h) {
@@ -81,16 +69,9 @@ __device__ __forceinline__ double shfl_xor_f64(double v, int mask) {
   return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
 }
 
-// One first-level statistic through the second level (Alg. 1 fit_statistics, lines 4-10): the beta2 lanes of a tile
-// fit a quantiser to their values, round its two parameters to binary16, and every lane gets its code and the
-// de-quantised statistic.
-__device__ __forceinline__ void second_level(double v, int beta2, double levels, double* hat, uint8_t* code,
-                                             uint16_t* s2_bits, uint16_t* z2_bits) {
-  double lo = v, hi = v;
-  for (int off = 1; off < beta2; off <<= 1) {
-    lo = fmin(lo, shfl_xor_f64(lo, off));
-    hi = fmax(hi, shfl_xor_f64(hi, off));
-  }
+// A quantiser for the tile's values in [lo, hi], its two parameters rounded to binary16: the code of v and v as the decoder has it.
+__device__ __forceinline__ void second_level_of_range(double v, double lo, double hi, double levels, double* hat, uint8_t* code,
+                                                      uint16_t* s2_bits, uint16_t* z2_bits) {
   double s2, z2;
   fit_from_range(lo, hi, levels, &s2, &z2);
   uint16_t sb = f64_to_f16_bits(s2);
@@ -104,6 +85,18 @@ __device__ __forceinline__ void second_level(double v, int beta2, double levels,
   *s2_bits = sb; *z2_bits = zb;
 }
 
+// One first-level statistic through the second level (Alg. 1 fit_statistics, lines 4-10): the beta2 lanes of a tile
+// fit a quantiser to their values, round its two parameters to binary16, and every lane gets its code and the
+// de-quantised statistic.
+__device__ __forceinline__ void second_level(double v, int beta2, double levels, double* hat, uint8_t* code,
+                                             uint16_t* s2_bits, uint16_t* z2_bits) {
+  double lo = v, hi = v;
+  for (int off = 1; off < beta2; off <<= 1) {
+    lo = fmin(lo, shfl_xor_f64(lo, off));
+    hi = fmax(hi, shfl_xor_f64(hi, off));
+  }
+  second_level_of_range(v, lo, hi, levels, hat, code, s2_bits, z2_bits);
+}
 struct SweepArgs {
   const double* U;       // H^ic [n][n]
   double* Wt;            // working copy, column-major: Wt[j * m + i]
@@ -336,259 +329,11 @@ __global__ void __launch_bounds__(64 * kWaves) sweep_kernel(SweepArgs a) {
   }
 }
 
-// ---------------------------------------------------------------------------
-// The sweep for layers of up to 4096 rows (and beta2 <= 16): a workgroup of 8 wavefronts owns 16 rows, so 4096 rows have
-// a workgroup per CU where 64 rows each would leave three of four idle.  The working copy is row-major.
-//   chain     the first wavefront alone, a lane per row (its four groups of 16 lanes do the same), 16 of the block's columns
-//             in registers: the steps of a column depend on one another
-//   feedback  lanes = columns, a wavefront takes up to 256 columns of all 16 rows (64 sums a lane, far_feedback)
-// Same operations in the same order on every weight as sweep_kernel, hence the same bits.
-// Bound: binary64 issue of the feedback (m n^2 products and differences) next to the chain (n columns, two true
-// divisions each, one after the other).  4096^2 with blocks of 16, measured part by part: far feedback 3.3 ms (1.74 at the
-// vector unit's rate, 8 clocks a product and its difference; the pairs are issued in 9.5), chain 1.9 (7.5 us a block), tests 0.9, the rest 0.6.
-// ---------------------------------------------------------------------------
-constexpr int kRows16 = 16, kWaves16 = 8, kSuper16 = 128;
+}  // namespace spqr_enc
 
-// Line 16 for the columns k0 + 64 c + lane, c < C, of the workgroup's rows: W[:, k] -= E[:, j] * H^ic[sb + j, k] for all sbw columns
-// j of the super-block, in order.  A lane holds 16 rows of C columns: the errors are LDS broadcasts (eight reads of 16 bytes
-// per column j whatever C is: with one column a lane they are what the pass waits for, two are even with the arithmetic),
-// H^ic comes straight from memory, four j ahead.  4096^2: 7.8 of the sweep's 11.0 ms with one column a lane, 4.3 of 7.5 with four,
-// 3.3 of 6.9 with super-blocks of 128 columns (half the trips of W to memory and back) and even shares.
-template <int C>
-__device__ __forceinline__ void far_feedback(double* __restrict__ W, const double* __restrict__ U, int n, int row0, int rows, int lane,
-                                             int sb, int sbw, int k0, const double (*esb)[kRows16]) {
-  typedef double f64x2 __attribute__((ext_vector_type(2)));
-  constexpr int PF = 4;                                  // a super-block has a multiple of 4 columns
-  uint32_t off[C];
-#pragma unroll
-  for (int c = 0; c < C; ++c) off[c] = (uint32_t)min(k0 + 64 * c + lane, n - 1) * 8u;
-  auto at = [&](const double* row, int c) { return *reinterpret_cast<const double*>(reinterpret_cast<const char*>(row) + off[c]); };
-  double cur[C][kRows16], u[PF][C], un[PF][C];
-  const double* uj = U + (size_t)sb * n;
-#pragma unroll
-  for (int q = 0; q < PF; ++q)
-#pragma unroll
-    for (int c = 0; c < C; ++c) u[q][c] = at(uj + (size_t)q * n, c);
-#pragma unroll
-  for (int r = 0; r < kRows16; ++r)
-#pragma unroll
-    for (int c = 0; c < C; ++c) cur[c][r] = at(W + (size_t)(row0 + min(r, rows - 1)) * n, c);
-  // pairs of errors, AHEAD of them on their way (the last ones read behind the errors, into what follows them in LDS)
-  constexpr int AHEAD = 1, PAIRS = kRows16 / 2;
-  const f64x2* pe = reinterpret_cast<const f64x2*>(&esb[0][0]);
-  f64x2 e[AHEAD + 1];
-#pragma unroll
-  for (int t = 0; t < AHEAD; ++t) e[t] = pe[t];
-#pragma unroll 1
-  for (int j = 0; j < sbw; j += PF) {
-    if (j + PF < sbw) uj += (size_t)PF * n;              // behind the last four: the same ones again, unused
-#pragma unroll
-    for (int q = 0; q < PF; ++q)
-#pragma unroll
-      for (int c = 0; c < C; ++c) un[q][c] = at(uj + (size_t)q * n, c);
-#pragma unroll
-    for (int q = 0; q < PF; ++q) {
-#pragma unroll
-      for (int h = 0; h < PAIRS; ++h) {
-        const int t = q * PAIRS + h;
-        e[(t + AHEAD) % (AHEAD + 1)] = pe[t + AHEAD];
-#pragma unroll
-        for (int c = 0; c < C; ++c) {
-          cur[c][2 * h] = cur[c][2 * h] - e[t % (AHEAD + 1)].x * u[q][c];
-          cur[c][2 * h + 1] = cur[c][2 * h + 1] - e[t % (AHEAD + 1)].y * u[q][c];
-        }
-        __builtin_amdgcn_sched_barrier(0);
-      }
-    }
-    pe += PF * PAIRS;
-#pragma unroll
-    for (int q = 0; q < PF; ++q)
-#pragma unroll
-      for (int c = 0; c < C; ++c) u[q][c] = un[q][c];
-  }
-#pragma unroll
-  for (int c = 0; c < C; ++c) {
-    if (k0 + 64 * c + lane < n) {
-#pragma unroll
-      for (int r = 0; r < kRows16; ++r)
-        if (r < rows) *reinterpret_cast<double*>(reinterpret_cast<char*>(W + (size_t)(row0 + r) * n) + off[c]) = cur[c][r];
-    }
-  }
-}
+#include "spqr_sweep16.h"
 
-// A super-block's columns of the workgroup's rows and its corner of H^ic stay in LDS from its first block to its last, so that a
-// block waits for no memory (three trips of it a block before: 4096^2 7.45 -> 6.65 ms with all that is said above, 256 x 4064
-// 10.0 -> 6.2 against one column a lane).  The corner: for each block of B1 rows the columns from its own diagonal on, block after block.
-template <int B1> struct Sweep16Lds {
-  double esb[kSuper16][kRows16];                         // errors E of the current super-block's columns
-  double wsb[kSuper16][kRows16 + 1];                     // its weights (the 1: banks)
-  double corner[(kSuper16 / B1 + 1) * kSuper16 * B1 / 2];
-  double err[B1 + 1][kRows16];                           // summed error of the group, whole and without each column
-};
-template <int B1> constexpr int corner_at(int g) { return B1 * (g * kSuper16 - B1 * (g * (g - 1) / 2)); }   // block g's rows of kSuper16 - g B1
-static_assert(corner_at<16>(kSuper16 / 16) == (kSuper16 / 16 + 1) * kSuper16 * 16 / 2, "all of the blocks");
-
-template <int B1>
-__global__ void __launch_bounds__(64 * kWaves16, 2) sweep16_kernel(SweepArgs a) {
-  extern __shared__ __align__(16) uint8_t lds[];
-  Sweep16Lds<B1>& S = *reinterpret_cast<Sweep16Lds<B1>*>(lds);
-  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int m = a.m, n = a.n, row0 = blockIdx.x * kRows16, rows = min(kRows16, m - row0);   // a tile is inside or outside
-  const int ng = n / B1;
-  const double* __restrict__ U = a.U;
-  double* __restrict__ W = a.Wt;                         // row-major here
-
-  for (int sb = 0; sb < n; sb += kSuper16) {
-    const int sbw = min(kSuper16, n - sb);
-#pragma unroll 4
-    for (int j = wave; j < sbw; j += kWaves16) {
-      const int g = j / B1;
-      double* to = S.corner + corner_at<B1>(g) + (j % B1) * (kSuper16 - g * B1) - g * B1;
-#pragma unroll
-      for (int k = 0; k < kSuper16; k += 64)
-        if (k + lane >= g * B1 && k + lane < sbw) to[k + lane] = U[(size_t)(sb + j) * n + sb + k + lane];
-    }
-#pragma unroll
-    for (int r = tid / kSuper16; r < kRows16; r += 64 * kWaves16 / kSuper16)           // rows behind the last one shadow it
-      if (tid % kSuper16 < sbw) S.wsb[tid % kSuper16][r] = W[(size_t)(row0 + min(r, rows - 1)) * n + sb + tid % kSuper16];
-    __syncthreads();
-    for (int i = sb; i < sb + sbw; i += B1) {
-      const int g = i / B1, ib = i - sb, width = kSuper16 - ib;
-      const double* ublk = S.corner + corner_at<B1>(ib / B1);              // rows i .., columns i ..
-
-      // ---- outliers(): a thread per leave-one-out test (line 8), and one for the whole group ----
-      if (a.tau < INFINITY) {
-        for (int idx = tid; idx < (B1 + 1) * kRows16; idx += 64 * kWaves16) {
-          const int r = idx & 15, x = (idx >> 4) - 1;    // without column x (-1: all columns)
-          double lo = INFINITY, hi = -INFINITY;
-#pragma unroll 4
-          for (int c = 0; c < B1; ++c) {
-            const double v = S.wsb[ib + c][r];
-            if (c != x) { lo = fmin(lo, v); hi = fmax(hi, v); }
-          }
-          double s, z;
-          fit_from_range(lo, hi, a.w_top, &s, &z);
-          double t = 0.0;
-#pragma unroll 4
-          for (int c = 0; c < B1; ++c) {
-            const double v = S.wsb[ib + c][r];
-            const double e = (v - s * (quantize(v, s, z, a.w_top) - z)) / ublk[c * width + c];
-            t = c != x ? t + e * e : t;
-          }
-          S.err[x + 1][r] = t;
-        }
-        __syncthreads();
-      }
-
-      // ---- fit_statistics() (line 9) and lines 10-15 ----
-      if (wave == 0) {
-        const int r = lane & 15, row = row0 + r;
-        uint32_t om = 0;
-        if (a.tau < INFINITY) {                          // (the four groups of lanes share the columns)
-          for (int c = lane >> 4; c < B1; c += 4) om |= (S.err[0][r] - S.err[c + 1][r]) > a.tau ? 1u << c : 0u;
-          om |= __shfl_xor(om, 16, 64);
-          om |= __shfl_xor(om, 32, 64);
-        }
-        double s_hat, z_hat;
-        uint8_t sq, zq;
-        uint16_t ssb, zsb, szb, zzb;
-        {
-          double lo = INFINITY, hi = -INFINITY;
-#pragma unroll
-          for (int c = 0; c < B1; ++c) {
-            const double v = S.wsb[ib + c][r];
-            if (!((om >> c) & 1u)) { lo = fmin(lo, v); hi = fmax(hi, v); }
-          }
-          if (lo > hi) { lo = 0.0; hi = 0.0; }           // nothing left
-          double s1, z1;
-          fit_from_range(lo, hi, a.w_top, &s1, &z1);
-          second_level(s1, a.beta2, a.s_top, &s_hat, &sq, &ssb, &zsb);
-          second_level(z1, a.beta2, a.z_top, &z_hat, &zq, &szb, &zzb);
-        }
-        if (lane < rows) {
-          a.out.s_q[(size_t)row * ng + g] = sq;
-          a.out.z_q[(size_t)row * ng + g] = zq;
-          if ((row % a.beta2) == 0) {
-            const size_t t = (size_t)(row / a.beta2) * ng + g;
-            a.out.s_s[t] = ssb; a.out.z_s[t] = zsb; a.out.s_z[t] = szb; a.out.z_z[t] = zzb;
-          }
-        }
-        // HB columns in registers at a time: 32 of them spill (540 registers).  The second half first takes the errors of the
-        // first, in the order of the columns, which is the order line 14 gives it.
-        constexpr int HB = B1 < 16 ? B1 : 16;
-#pragma unroll 1
-        for (int h0 = 0; h0 < B1; h0 += HB) {
-          double w[HB];
-#pragma unroll
-          for (int c = 0; c < HB; ++c) w[c] = S.wsb[ib + h0 + c][r];
-          for (int j = 0; j < h0; ++j) {
-            const double ej = S.esb[ib + j][r];
-#pragma unroll
-            for (int k = 0; k < HB; ++k) w[k] = w[k] - ej * ublk[j * width + h0 + k];
-          }
-          uint32_t qs[HB / 4], ms[HB / 4], vs[HB / 2];
-#pragma unroll
-          for (int k = 0; k < HB / 4; ++k) qs[k] = ms[k] = 0;
-#pragma unroll
-          for (int k = 0; k < HB / 2; ++k) vs[k] = 0;
-#pragma unroll
-          for (int c = 0; c < HB; ++c) {
-            const bool is_out = (om >> (h0 + c)) & 1u;
-            const double v = w[c];
-            const double q = quantize(v, s_hat, z_hat, a.w_top);
-            const double wq = s_hat * (q - z_hat);
-            const double ec = (v - wq) / ublk[(h0 + c) * width + h0 + c] * (is_out ? 0.0 : 1.0);
-            if (lane < kRows16) S.esb[ib + h0 + c][r] = ec;
-#pragma unroll
-            for (int k = c; k < HB; ++k) w[k] = w[k] - ec * ublk[(h0 + c) * width + h0 + k];    // line 14, inside the block
-            qs[c / 4] |= (uint32_t)(uint8_t)q << (8 * (c % 4));
-            ms[c / 4] |= (is_out ? 1u : 0u) << (8 * (c % 4));
-            vs[c / 2] |= (uint32_t)(is_out ? f64_to_f16_bits(w[c] - wq) : (uint16_t)0) << (16 * (c % 2));
-          }
-          if (lane < rows) {
-            const size_t at = (size_t)row * n + i + h0;
-#pragma unroll
-            for (int k = 0; k < HB / 4; ++k) {
-              reinterpret_cast<uint32_t*>(a.out.Q + at)[k] = qs[k];
-              reinterpret_cast<uint32_t*>(a.out.outlier_mask + at)[k] = ms[k];
-            }
-#pragma unroll
-            for (int k = 0; k < HB / 2; ++k) reinterpret_cast<uint32_t*>(a.out.outlier_val + at)[k] = vs[k];
-#pragma unroll
-            for (int c = 0; c < HB; ++c) W[at + c] = w[c];
-          }
-        }
-      }
-      __syncthreads();
-      // ---- line 16 for the rest of the super-block: a thread per weight ----
-      for (int k = ib + B1 + (tid >> 4); k < sbw; k += 64 * kWaves16 / 16) {
-        const int r = tid & 15;
-        double c = S.wsb[k][r];
-#pragma unroll
-        for (int j = 0; j < B1; ++j) c = c - S.esb[ib + j][r] * ublk[j * width + k - ib];
-        S.wsb[k][r] = c;
-      }
-      __syncthreads();       // the next block's columns are complete
-    }
-    // ---- line 16 for everything right of the super-block: all of its errors in one pass.  Its columns in runs of 64, as many
-    // for each wavefront as for the others or one more (the first four, one on each SIMD, before the others), up to four of them at
-    // a time ----
-    const int chunks = (n - (sb + sbw) + 63) / 64, each = chunks / kWaves16, more = chunks % kWaves16;
-    int at = sb + sbw + 64 * (wave * each + min(wave, more));
-    for (int left = each + (wave < more ? 1 : 0); left > 0;) {             // wave-uniform
-      const int cols = left == 5 ? 3 : min(left, 4);
-      switch (cols) {
-        case 1: far_feedback<1>(W, U, n, row0, rows, lane, sb, sbw, at, S.esb); break;
-        case 2: far_feedback<2>(W, U, n, row0, rows, lane, sb, sbw, at, S.esb); break;
-        case 3: far_feedback<3>(W, U, n, row0, rows, lane, sb, sbw, at, S.esb); break;
-        default: far_feedback<4>(W, U, n, row0, rows, lane, sb, sbw, at, S.esb); break;
-      }
-      at += 64 * cols;
-      left -= cols;
-    }
-    __syncthreads();
-  }
-}
+namespace spqr_enc {
 
 __global__ void __launch_bounds__(256) copy_kernel(const double* __restrict__ src, double* __restrict__ dst, size_t count) {
   for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < count; i += (size_t)gridDim.x * 256) dst[i] = src[i];
@@ -719,13 +464,11 @@ int spqr_quantize(const double* W, const double* Hic, int32_t m, int32_t n, int3
   a.w_top = (double)((1 << w_bits) - 1); a.s_top = (double)((1 << s_bits) - 1); a.z_top = (double)((1 << z_bits) - 1);
   a.tau = tau;
   a.out = *out;
-  // 16 rows per workgroup where a tile has no more and every workgroup gets a CU, in place on W_final where the caller wants it; 64
-  // rows per workgroup where there are more rows or taller tiles.  ms with 64 and with 16 rows a workgroup, beta2 = 16, 1 % outliers,
-  // the time of either a staircase of rounds of 256 workgroups: 4096^2 17.7 and 6.6; 11008 x 4096 18.4 and 19.7 (beta1 = 8: 17.3 and
-  // 20.2, beta1 = 32: 21.1 and 21.8), 9216 x 4096 18.1 and 19.4, 16384 x 2048 6.65 and 10.2.  The line at one round is older than
-  // the 16-row kernel as it is: at two rounds that would be the faster one in most cases (8192 x 4096 18.1 and 13.2, 5120^2 25.9 and 18.0,
-  // 6656^2 40.6 and 26.5; 8192 x 1024 2.45 and 2.28, with beta1 = 8 2.20 and 2.35).
-  if (beta2 <= kRows16 && m <= kRows16 * 256) {
+  // 16 rows per workgroup where a tile has no more, in place on W_final where the caller wants it; 64 rows, which the tiles of 32 and 64
+  // rows need, take four to five times as long for four times the rows.  ms with 64 and with 16 rows a workgroup,
+  // beta2 = 16, 1 % outliers (the time of either is a staircase of rounds of 256 workgroups): 4096^2 17.7 and 3.6, 5120^2 25.4 and 10.2, 8192 x 4096 17.8 and
+  // 7.3, 11008 x 4096 18.0 and 10.8, 16384 x 2048 6.8 and 4.9, 8192 x 1024 (beta1 = 8) 2.1 and 1.07.
+  if (beta2 <= kRows16) {
     if (out->W_final) a.Wt = out->W_final;
     if (a.Wt != W) hipLaunchKernelGGL(copy_kernel, dim3(2048), dim3(256), 0, st, W, a.Wt, (size_t)m * n);
     hipError_t e = hipSuccess;

@@ -223,3 +223,40 @@ def test_hessian_and_factor_at_the_edges_of_tiles_and_squares(n, d):
     A = H + lam * torch.eye(n, dtype=torch.float64, device="cuda")
     cond = float(torch.linalg.norm(A, 2) / lam)
     assert float((U.T @ U @ A - torch.eye(n, dtype=torch.float64, device="cuda")).abs().max()) <= 4 * n * cond * 2.0 ** -53
+
+
+# the 16-row kernel: divisions outside the range of the prepared divisors (weights above 2^300 and below 2^-300, a diagonal below
+# 2^-100 or negative, errors that are exactly 0), more rows than 256 workgroups hold, ragged workgroups and super-blocks
+@pytest.mark.parametrize("kind,b1,b2,m,n,tau", [
+    ("huge", 16, 16, 48, 288, 20.0), ("huge", 8, 8, 24, 136, 20.0), ("huge", 32, 16, 32, 416, 20.0), ("huge", 4, 2, 18, 132, 20.0),
+    ("tiny", 16, 16, 32, 160, float("inf")), ("tiny", 32, 4, 20, 160, 0.1), ("diagonal", 16, 16, 32, 400, 2e71), ("diagonal", 32, 8, 24, 288, 2e71),
+    ("negative", 16, 16, 32, 288, 20.0), ("zeros", 16, 16, 64, 272, 1e-3), ("zeros", 8, 4, 36, 264, 1e-3), ("plain", 16, 16, 4112, 144, 20.0),
+    ("plain", 4, 8, 4104, 132, 20.0)])
+def test_sweep_outside_the_prepared_divisors_bit_exact(E, kind, b1, b2, m, n, tau):
+    rng = np.random.default_rng(m + n + b1)
+    W = rng.normal(0, 0.05, (m, n))
+    W[rng.random((m, n)) < 0.02] *= 6.0
+    U = np.triu(rng.normal(0, 0.3 / np.sqrt(n), (n, n)), 1) + np.eye(n)
+    U *= 0.01 * (0.5 + rng.random((n, 1)))
+    some = rng.random((m, n)) < 0.01
+    if kind == "huge":
+        some[:, np.arange(n) % 4 != 1] = False        # apart: with two in a group of 4 neither is an outlier, and the 16-bit scale is infinite
+        W[some] = rng.normal(0, 1, some.sum()) * 2.0 ** 310
+    elif kind == "tiny":
+        W *= 2.0 ** -4
+        W[some] *= 2.0 ** -1000
+        W[::3, :b1] = 2.0 ** -320                     # a group that is all but 0
+    elif kind == "diagonal":
+        U[n // 3:n // 3 + 40] *= 1e-35
+    elif kind == "negative":
+        U[::3] *= -1.0
+    elif kind == "zeros":
+        W = np.round(W * 16) / 16                     # few values: codes that meet their weight exactly
+        W[:, 16:32] = 0.0
+        U = 0.01 * np.eye(n)
+    with np.errstate(all="ignore"):
+        ref = enc.spqr_quantize(W, U, 3, b1, b2, tau)
+    got = E.spqr_quantize(dev(W), dev(U), 3, b1, b2, tau)
+    if kind == "huge":                                # the largest magnitudes round to infinity as stored outlier values
+        assert np.isinf(np.asarray(ref.val, dtype=np.float64)).any()
+    _compare_exact(got, ref)
