@@ -226,12 +226,13 @@ def test_hessian_and_factor_at_the_edges_of_tiles_and_squares(n, d):
 
 
 # the 16-row kernel: divisions outside the range of the prepared divisors (weights above 2^300 and below 2^-300, a diagonal below
-# 2^-100 or negative, errors that are exactly 0), more rows than 256 workgroups hold, ragged workgroups and super-blocks
+# 2^-100 or negative, errors that are exactly 0), more rows than 256 workgroups hold, ragged workgroups and super-blocks; the last: the
+# line from where few narrow columns go to 64 rows a workgroup
 @pytest.mark.parametrize("kind,b1,b2,m,n,tau", [
     ("huge", 16, 16, 48, 288, 20.0), ("huge", 8, 8, 24, 136, 20.0), ("huge", 32, 16, 32, 416, 20.0), ("huge", 4, 2, 18, 132, 20.0),
     ("tiny", 16, 16, 32, 160, float("inf")), ("tiny", 32, 4, 20, 160, 0.1), ("diagonal", 16, 16, 32, 400, 2e71), ("diagonal", 32, 8, 24, 288, 2e71),
     ("negative", 16, 16, 32, 288, 20.0), ("zeros", 16, 16, 64, 272, 1e-3), ("zeros", 8, 4, 36, 264, 1e-3), ("plain", 16, 16, 4112, 144, 20.0),
-    ("plain", 4, 8, 4104, 132, 20.0)])
+    ("plain", 4, 8, 4104, 132, 20.0), ("plain", 8, 8, 12296, 72, 20.0)])
 def test_sweep_outside_the_prepared_divisors_bit_exact(E, kind, b1, b2, m, n, tau):
     rng = np.random.default_rng(m + n + b1)
     W = rng.normal(0, 0.05, (m, n))
