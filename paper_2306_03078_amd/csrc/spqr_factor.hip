@@ -17,10 +17,13 @@
 // Every tile product runs on the matrix cores (v_mfma_f64_16x16x4_f64), at the vector ALU's rate, but an operand of one
 // 8-byte half of an LDS read per lane feeds two instructions of 64 clocks.  n = d = 4096: Hessian 2.4 -> 1.65 ms (42 of 68 TFLOP/s;
 // staged by rows, squares of tiles per XCD), a block column of the factorisation 47 -> 33 us (the next diagonal block beside the trailing
-// update), the triangular inverse 1.13 -> 0.92 ms, Hessian and factor together 6.7 -> 4.7 ms.  What is left: the chain of 64
-// diagonal blocks of 20 us and panels of 5, bank conflicts (half of the LDS clocks of every product) and the barrier of every step of k.
+// update), the triangular inverse 1.13 -> 0.92 ms, Hessian and factor together 6.7 -> 4.4 ms.  What is left: the chain of 64
+// diagonal blocks of 13 us and panels of 5, bank conflicts (half of the LDS clocks of every product) and the barrier of every step of k.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+
+#include <type_traits>
+#include <utility>
 
 #include "../../include/spqr_encode.h"
 
@@ -106,6 +109,20 @@ __device__ __forceinline__ void each_element(const Tile<WM, WN>& acc, F f) {
 #pragma unroll
       for (int r = 0; r < 4; ++r) f(r0 + 16 * a + 4 * r, c0 + 16 * b, acc.d[a][b][r]);
 }
+// The tile with f(row, column) as this thread's elements.
+template <int WM, int WN, class F>
+__device__ __forceinline__ Tile<WM, WN> load_tile(F f) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int r0 = 16 * WM * (wave & 1) + (lane >> 4), c0 = 16 * WN * (wave >> 1) + (lane & 15);
+  Tile<WM, WN> t;
+#pragma unroll
+  for (int a = 0; a < WM; ++a)
+#pragma unroll
+    for (int b = 0; b < WN; ++b)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) t.d[a][b][r] = f(r0 + 16 * a + 4 * r, c0 + 16 * b);
+  return t;
+}
 __device__ __forceinline__ f64x2 pair_at(const double* p) { return *reinterpret_cast<const f64x2_8*>(p); }   // two in a row, 8-byte aligned
 
 // Number of a cell of an upper triangle (row by row, `side` cells in the first) -> row and column.
@@ -156,14 +173,6 @@ __global__ void __launch_bounds__(256) init_reversed_kernel(const double* __rest
   L[idx] = v;
 }
 
-// A lane's double as every lane sees it (v_readlane: the source lane is uniform).
-__device__ __forceinline__ double readlane_f64(double v, int src) {
-  const uint64_t b = __builtin_bit_cast(uint64_t, v);
-  const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)b, src);
-  const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(b >> 32), src);
-  return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
-}
-
 // 1 / sqrt(x) and sqrt(x) by Newton steps on the hardware's estimate, to about a unit in the last place (x <= 0: NaN).
 __device__ __forceinline__ double rsqrt_f64(double x, double* root) {
   double y = __builtin_amdgcn_rsq(x);
@@ -177,19 +186,36 @@ __device__ __forceinline__ double rsqrt_f64(double x, double* root) {
   return y;
 }
 
-// Diagonal block kb: Cholesky factor in place, its inverse to Dinv[kb].  Four panels of 16 columns: a panel's 16 steps
-// depend on each other, so one wavefront takes them (a lane per row, the row in registers, column j handed to the other
-// rows by v_readlane); the columns right of the panel are updated by all four on the matrix cores.  The inverse by
-// doubling: the four diagonal blocks of 16 at once, a wavefront each, then 16 -> 32 -> 64 as products of blocks.  (One
-// wavefront for all 64 columns and the inverse took 51 us: 2016 updates and as many LDS reads in one chain, and a
-// division and a square root per step.)
-struct Diagonal {                            // block, inverse, a product between, 1 / diagonal
+// d += (s of lane LANE of the row of 16) * m, as one instruction: v_fmac_f64 takes that operand across lanes by itself.  The compiler does
+// not look into the text for the two wait states between a write of `s` and its reading across lanes: bcast_ready() stands between.
+template <int LANE>
+__device__ __forceinline__ void fma_bcast(double& d, double s, double m) {
+  asm("v_fmac_f64_dpp %0, %1, %2 row_newbcast:%3 row_mask:0xf bank_mask:0xf" : "+v"(d) : "v"(s), "v"(m), "n"(LANE));
+}
+__device__ __forceinline__ void bcast_ready(double& s) { asm("s_nop 1" : "+v"(s)); }
+template <int LANE>
+__device__ __forceinline__ double bcast(double s) {
+  double d;
+  asm("v_mov_b64_dpp %0, %1 row_newbcast:%2 row_mask:0xf bank_mask:0xf" : "=v"(d) : "v"(s), "n"(LANE));
+  return d;
+}
+template <int... I, class F> __device__ __forceinline__ void unrolled(std::integer_sequence<int, I...>, F f) { (f(std::integral_constant<int, I>{}), ...); }
+
+// Diagonal block kb: Cholesky factor in place, its inverse to Dinv[kb].  Four panels of 16 columns.  A panel's own 16 x 16 block is the
+// chain: one wavefront factorises and inverts it in registers, a lane per row of the factor and per column of the inverse (the four
+// groups of 16 lanes do the same), 2 (15 - j) updates a step of one instruction each, which take the step's column of the factor across
+// lanes themselves.  The rows below take the product with the inverse and the columns right of the panel their update from all
+// four wavefronts on the matrix cores; the inverse of the whole by doubling, 16 -> 32 -> 64, as products of blocks.
+// A lane per row of the whole panel, the column by two v_readlane a lane and the inverses of the 16 x 16 blocks afterwards, row by row
+// out of LDS, took 5 us more: the launch of a block column with few tiles left 22.5 -> 17.5 us, Hessian and factor of 4096 inputs 4.77 ->
+// 4.51 ms.
+struct Diagonal {                            // block, inverse, a product between
   static constexpr int DP = NB + 2;
-  double D[NB][DP], X[NB][DP], T[32][34], rd[NB];
+  double D[NB][DP], X[NB][DP], T[32][34];
 };
 // `S.D` holds the block; every thread of the workgroup.
 __device__ __forceinline__ void potrf_diag(Diagonal& S, double* __restrict__ L, int np, int kb, double* __restrict__ Dinv) {
-  double (&D)[NB][Diagonal::DP] = S.D, (&X)[NB][Diagonal::DP] = S.X, (&T)[32][34] = S.T, (&rd)[NB] = S.rd;
+  double (&D)[NB][Diagonal::DP] = S.D, (&X)[NB][Diagonal::DP] = S.X, (&T)[32][34] = S.T;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, i16 = lane & 15, g4 = lane >> 4;
   double* blk = L + (size_t)kb * NB * np + (size_t)kb * NB;
   for (int idx = tid; idx < NB * NB; idx += 256) X[idx >> 6][idx & 63] = 0.0;
@@ -197,21 +223,38 @@ __device__ __forceinline__ void potrf_diag(Diagonal& S, double* __restrict__ L, 
   for (int p = 0; p < 4; ++p) {              // panel of columns c0 .. c0 + 15
     const int c0 = 16 * p;
     if (wave == 0) {
-      double r[16];
+      double r[16], v[16];                   // row i16 of the block (right of the diagonal: nothing), column i16 of the inverse
 #pragma unroll
-      for (int k = 0; k < 16; ++k) r[k] = D[lane][c0 + k];
-#pragma unroll
-      for (int j = 0; j < 16; ++j) {
+      for (int k = 0; k < 16; ++k) { r[k] = D[c0 + i16][c0 + k]; v[k] = k == i16 ? 1.0 : 0.0; }
+      unrolled(std::make_integer_sequence<int, 16>{}, [&](auto column) __attribute__((always_inline)) {
+        constexpr int j = decltype(column)::value;
         double root;
-        const double y = rsqrt_f64(readlane_f64(r[j], c0 + j), &root);
-        const double l = r[j] * y;           // L[lane][c0 + j] for lane > c0 + j
-        r[j] = lane == c0 + j ? root : l;
-        if (lane == 0) rd[c0 + j] = y;
+        bcast_ready(r[j]);
+        const double y = rsqrt_f64(bcast<j>(r[j]), &root);
+        double l = i16 == j ? root : r[j] * y;
+        r[j] = l;
+        v[j] *= y;
+        const double nl = -l, nv = -v[j];
+        bcast_ready(l);
+        unrolled(std::make_integer_sequence<int, 15 - j>{}, [&](auto at) __attribute__((always_inline)) {
+          constexpr int k = j + 1 + decltype(at)::value;
+          fma_bcast<k>(r[k], l, nl);         // meaningful for k <= i16
+          fma_bcast<k>(v[k], l, nv);
+        });
+      });
+      if (g4 == 0) {
 #pragma unroll
-        for (int k = j + 1; k < 16; ++k) r[k] = fma(-l, readlane_f64(l, c0 + k), r[k]);   // meaningful for c0 + k <= lane
+        for (int k = 0; k < 16; ++k) { D[c0 + i16][c0 + k] = k <= i16 ? r[k] : 0.0; X[c0 + k][c0 + i16] = v[k]; }
       }
+    }
+    __syncthreads();
+    if (p == 3) break;
+    if (wave > p) {                          // wave-uniform: the rows of block `wave` times the inverse, transposed
+      f64x4 d = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-      for (int k = 0; k < 16; ++k) D[lane][c0 + k] = c0 + k <= lane ? r[k] : 0.0;
+      for (int q = 0; q < 16; q += 4) d = mfma4(D[16 * wave + i16][c0 + q + g4], X[c0 + i16][c0 + q + g4], d);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) D[16 * wave + g4 + 4 * r][c0 + i16] = d[r];
     }
     __syncthreads();
     // blocks (bi, bj), p < bj <= bi: minus L[bi][p] L[bj][p]^T, dealt to the wavefronts in turn
@@ -229,24 +272,6 @@ __device__ __forceinline__ void potrf_diag(Diagonal& S, double* __restrict__ L, 
   }
   for (int idx = tid; idx < NB * NB; idx += 256)
     blk[(size_t)(idx >> 6) * np + (idx & 63)] = (idx & 63) <= (idx >> 6) ? D[idx >> 6][idx & 63] : 0.0;
-  // inverse of diagonal block `wave`, column i16 per lane (the four lane groups do the same)
-  {
-    const int o = 16 * wave;
-    double v[16];
-#pragma unroll
-    for (int i = 0; i < 16; ++i) {
-      double s0 = 0.0, s1 = 0.0;
-#pragma unroll
-      for (int k = 0; k + 1 < i; k += 2) { s0 = fma(D[o + i][o + k], v[k], s0); s1 = fma(D[o + i][o + k + 1], v[k + 1], s1); }
-      if (i & 1) s0 = fma(D[o + i][o + i - 1], v[i - 1], s0);
-      v[i] = i < i16 ? 0.0 : (i == i16 ? rd[o + i] : -(s0 + s1) * rd[o + i]);
-    }
-    if (g4 == 0) {
-#pragma unroll
-      for (int i = 0; i < 16; ++i) X[o + i][o + i16] = v[i];
-    }
-  }
-  __syncthreads();
   // [[A, 0], [C, B]]^-1 = [[A^-1, 0], [-B^-1 C A^-1, B^-1]], first for the pairs of blocks of 16, then of 32
 #pragma unroll
   for (int h = 16; h <= 32; h *= 2) {
@@ -311,13 +336,19 @@ __global__ void __launch_bounds__(256) update_kernel(double* __restrict__ L, int
   Tile<2, 2> acc = {};
   auto fa = [&](int r, int k) { return pair_at(pi + (size_t)r * np + k); };
   auto fb = [&](int c, int k) { return pair_at(pj + (size_t)c * np + k); };
-  tile_product<false>(acc, 0, NB, fa, fb, S.stage);
+  // the tile itself, on its way while the product is formed (64 deep, that is short: 4096 inputs 4.51 -> 4.42 ms)
   double* blk = L + (size_t)ib * NB * np + (size_t)jb * NB;
+  const Tile<2, 2> before = load_tile<2, 2>([&](int r, int c) { return blk[(size_t)r * np + c]; });
+  tile_product<false>(acc, 0, NB, fa, fb, S.stage);
+#pragma unroll
+  for (int a = 0; a < 2; ++a)
+#pragma unroll
+    for (int b = 0; b < 2; ++b) acc.d[a][b] = before.d[a][b] - acc.d[a][b];
   if (blockIdx.x > 0) {                      // workgroup-uniform
-    each_element(acc, [&](int r, int c, double v) { blk[(size_t)r * np + c] -= v; });
+    each_element(acc, [&](int r, int c, double v) { blk[(size_t)r * np + c] = v; });
     return;
   }
-  each_element(acc, [&](int r, int c, double v) { S.diagonal.D[r][c] = blk[(size_t)r * np + c] - v; });   // (the product is over: a barrier ends it)
+  each_element(acc, [&](int r, int c, double v) { S.diagonal.D[r][c] = v; });   // (the product is over: a barrier ends it)
   __syncthreads();
   potrf_diag(S.diagonal, L, np, kb + 1, Dinv);
 }
