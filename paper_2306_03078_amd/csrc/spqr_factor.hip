@@ -49,31 +49,59 @@ __device__ __forceinline__ f64x4 mfma4(double a, double b, f64x4 d) { return __b
 template <int WM, int WN> struct Tile { f64x4 d[WM][WN]; };
 template <int WM, int WN> struct Stage { double a[2][32 * WM][LP], b[2][32 * WN][LP]; };
 
-// get_a / get_b (row, k): the values at k and k + 1; b_by_k: consecutive threads fetch consecutive rows of B, else consecutive k.
+// get_a / get_b (q, k0): the values at k and k + 1 of the q-th row that the thread stages of the stage that begins at k0; row and k - k0:
+// staged_row and staged_k, with B_BY_K column_row and column_k for B (consecutive threads fetch consecutive rows of it, not consecutive k).
+__device__ __forceinline__ int staged_row(int q) { return ((int)threadIdx.x + 256 * q) / (KC / 2); }
+__device__ __forceinline__ int staged_k() { return 2 * ((int)threadIdx.x % (KC / 2)); }
+template <int WN> __device__ __forceinline__ int column_row() { return (int)threadIdx.x % (32 * WN); }
+template <int WN> __device__ __forceinline__ int column_k(int q) { return 2 * (((int)threadIdx.x + 256 * q) / (32 * WN)); }
+
+template <class Get> __device__ __forceinline__ f64x2 settle(const Get&, f64x2 p, int) { return p; }
+
+// Rows of d values as operands, zeros behind them: the pair that ends a row is read one step early where it has to be and put right
+// when it goes to LDS.  SHORT: d = 1, whose pairs reach behind the matrix.
+template <bool SHORT> struct PaddedRows {
+  const double* p[2];
+  int d;
+  __device__ __forceinline__ PaddedRows(const double* X, int first, int n, int d_) : d(d_) {        // (rows behind the last: the last)
+#pragma unroll
+    for (int q = 0; q < 2; ++q) p[q] = X + (size_t)min(first + staged_row(q), n - 1) * d;
+  }
+  __device__ __forceinline__ f64x2 operator()(int q, int k0) const {
+    if constexpr (SHORT) return f64x2{*p[q], 0.0};
+    return *reinterpret_cast<const f64x2_8*>(p[q] + min(k0 + staged_k(), d - 2));
+  }
+};
+template <bool SHORT> __device__ __forceinline__ f64x2 settle(const PaddedRows<SHORT>& rows, f64x2 p, int k0) {
+  const int k = k0 + staged_k();
+  if constexpr (SHORT) return f64x2{k == 0 ? p.x : 0.0, 0.0};
+  return f64x2{k < rows.d - 1 ? p.x : k == rows.d - 1 ? p.y : 0.0, k < rows.d - 1 ? p.y : 0.0};
+}
+
 template <bool B_BY_K, int WM, int WN, class GetA, class GetB>
 __device__ __forceinline__ void tile_product(Tile<WM, WN>& acc, int kb, int ke, GetA get_a, GetB get_b, Stage<WM, WN>& S) {
   constexpr int NA = WM, NW = WN;            // pairs a thread stages: 32 W rows of KC / 2 pairs over 256 threads
+  static_assert(256 % (32 * WN) == 0, "column_row is the same for every q");
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6, i16 = lane & 15, g4 = lane >> 4;
   const int r0 = 16 * WM * (wave & 1) + i16, c0 = 16 * WN * (wave >> 1) + i16;
   f64x2 pa[NA], pb[NW];
-  auto b_row = [&](int idx) { return B_BY_K ? idx % (32 * WN) : idx / (KC / 2); };
-  auto b_k = [&](int idx) { return 2 * (B_BY_K ? idx / (32 * WN) : idx % (KC / 2)); };
   auto fetch = [&](int k0) {
 #pragma unroll
-    for (int q = 0; q < NA; ++q) pa[q] = get_a((t + 256 * q) / (KC / 2), k0 + 2 * (t % (KC / 2)));
+    for (int q = 0; q < NA; ++q) pa[q] = get_a(q, k0);
 #pragma unroll
-    for (int q = 0; q < NW; ++q) pb[q] = get_b(b_row(t + 256 * q), k0 + b_k(t + 256 * q));
+    for (int q = 0; q < NW; ++q) pb[q] = get_b(q, k0);
   };
-  auto stash = [&](int buf) {
+  auto stash = [&](int buf, int k0) {        // (settled here: done where they are fetched, the products would wait for them)
 #pragma unroll
-    for (int q = 0; q < NA; ++q) *reinterpret_cast<f64x2*>(&S.a[buf][(t + 256 * q) / (KC / 2)][2 * (t % (KC / 2))]) = pa[q];
+    for (int q = 0; q < NA; ++q) *reinterpret_cast<f64x2*>(&S.a[buf][staged_row(q)][staged_k()]) = settle(get_a, pa[q], k0);
 #pragma unroll
-    for (int q = 0; q < NW; ++q) *reinterpret_cast<f64x2*>(&S.b[buf][b_row(t + 256 * q)][b_k(t + 256 * q)]) = pb[q];
+    for (int q = 0; q < NW; ++q)
+      *reinterpret_cast<f64x2*>(&S.b[buf][B_BY_K ? column_row<WN>() : staged_row(q)][B_BY_K ? column_k<WN>(q) : staged_k()]) = settle(get_b, pb[q], k0);
   };
   if (kb >= ke) return;                      // workgroup-uniform
   __syncthreads();                           // a product before this one may still be read
   fetch(kb);
-  stash(0);
+  stash(0, kb);
   __syncthreads();
   int buf = 0;
   for (int k0 = kb; k0 < ke; k0 += KC, buf ^= 1) {
@@ -92,7 +120,7 @@ __device__ __forceinline__ void tile_product(Tile<WM, WN>& acc, int kb, int ke, 
 #pragma unroll
           for (int n = 0; n < WN; ++n) acc.d[m][n] = mfma4(a[m][e], b[n][e], acc.d[m][n]);
     }
-    if (k0 + KC < ke) stash(buf ^ 1);
+    if (k0 + KC < ke) stash(buf ^ 1, k0 + KC);
     __syncthreads();
   }
 }
@@ -125,6 +153,16 @@ __device__ __forceinline__ Tile<WM, WN> load_tile(F f) {
 }
 __device__ __forceinline__ f64x2 pair_at(const double* p) { return *reinterpret_cast<const f64x2_8*>(p); }   // two in a row, 8-byte aligned
 
+// Rows of a matrix as an operand: row(q) is where the thread's q-th row begins.
+template <int N> struct RowPairs {
+  const double* p[N];
+  template <class F> __device__ __forceinline__ RowPairs(F row) {
+#pragma unroll
+    for (int q = 0; q < N; ++q) p[q] = row(staged_row(q)) + staged_k();
+  }
+  __device__ __forceinline__ f64x2 operator()(int q, int k0) const { return pair_at(p[q] + k0); }
+};
+
 // Number of a cell of an upper triangle (row by row, `side` cells in the first) -> row and column.
 __device__ __forceinline__ void upper_cell(int at, int side, int* row, int* col) {
   int r = 0;
@@ -136,6 +174,7 @@ __device__ __forceinline__ void upper_cell(int at, int side, int* row, int* col)
 // H = 2 X X^T, tiles on and above the diagonal, mirrored.  Squares of SQ x SQ tiles, a run of them for each of the 8 XCDs
 // (workgroups go to the XCDs in turn): the tiles that run side by side on an XCD share rows of X in its L2.
 constexpr int SQ = 2;
+template <bool SHORT>
 __global__ void __launch_bounds__(256) hessian_kernel(const double* __restrict__ X, int n, int d, double* __restrict__ H, int squares, int run) {
   __shared__ Stage<2, 2> S;
   const int xcd = blockIdx.x % 8, at = blockIdx.x / 8, square = xcd * run + at / (SQ * SQ), side = (n + SQ * NB - 1) / (SQ * NB);
@@ -145,12 +184,7 @@ __global__ void __launch_bounds__(256) hessian_kernel(const double* __restrict__
   const int i0 = (sr * SQ + at % (SQ * SQ) / SQ) * NB, j0 = (sc * SQ + at % SQ) * NB;
   if (j0 < i0 || j0 >= n) return;            // below the diagonal or behind the matrix
   Tile<2, 2> acc = {};
-  auto get = [&](int row, int k) {           // (rows behind the last: the last, their sums are not written)
-    const double* x = X + (size_t)min(row, n - 1) * d + k;
-    if (k + 1 < d) return pair_at(x);
-    return f64x2{k < d ? *x : 0.0, 0.0};
-  };
-  tile_product<false>(acc, 0, d, [&](int i, int k) { return get(i0 + i, k); }, [&](int j, int k) { return get(j0 + j, k); }, S);
+  tile_product<false>(acc, 0, d, PaddedRows<SHORT>(X, i0, n, d), PaddedRows<SHORT>(X, j0, n, d), S);
   each_element(acc, [&](int r, int c, double v) {
     const int i = i0 + r, j = j0 + c;
     if (i <= j && j < n) {
@@ -314,8 +348,7 @@ __global__ void __launch_bounds__(256) trsm_panel_kernel(double* __restrict__ L,
   double* blk = L + (size_t)ib * NB * np + (size_t)kb * NB;
   const double* inv = Dinv + (size_t)kb * NB * NB;
   Tile<2, 2> acc = {};
-  auto fa = [&](int r, int k) { return pair_at(blk + (size_t)r * np + k); };
-  auto fb = [&](int c, int k) { return pair_at(inv + c * NB + k); };
+  const RowPairs<2> fa([&](int r) { return blk + (size_t)r * np; }), fb([&](int c) { return inv + c * NB; });
   tile_product<false>(acc, 0, NB, fa, fb, S);           // every read of the block is done when it returns
   each_element(acc, [&](int r, int c, double v) { blk[(size_t)r * np + c] = v; });
 }
@@ -334,8 +367,7 @@ __global__ void __launch_bounds__(256) update_kernel(double* __restrict__ L, int
   const double* pi = L + (size_t)ib * NB * np + (size_t)kb * NB;
   const double* pj = L + (size_t)jb * NB * np + (size_t)kb * NB;
   Tile<2, 2> acc = {};
-  auto fa = [&](int r, int k) { return pair_at(pi + (size_t)r * np + k); };
-  auto fb = [&](int c, int k) { return pair_at(pj + (size_t)c * np + k); };
+  const RowPairs<2> fa([&](int r) { return pi + (size_t)r * np; }), fb([&](int c) { return pj + (size_t)c * np; });
   // the tile itself, on its way while the product is formed (64 deep, that is short: 4096 inputs 4.51 -> 4.42 ms)
   double* blk = L + (size_t)ib * NB * np + (size_t)jb * NB;
   const Tile<2, 2> before = load_tile<2, 2>([&](int r, int c) { return blk[(size_t)r * np + c]; });
@@ -362,24 +394,34 @@ __device__ __forceinline__ double inverse_at(const double* __restrict__ L, const
   return rb > cb ? L[(size_t)r * np + c] : 0.0;
 }
 
-// Elements (r, c) and (r, c + 1), c even.
-__device__ __forceinline__ f64x2 inverse_pair(const double* __restrict__ L, const double* __restrict__ Dinv, int np, int r, int c) {
-  const int rb = r >> 6, cb = c >> 6;
-  if (rb == cb) return pair_at(Dinv + (size_t)rb * NB * NB + (r & 63) * NB + (c & 63));
-  return rb > cb ? pair_at(L + (size_t)r * np + c) : f64x2{0.0, 0.0};
+// Where the inverse of the diagonal block that holds row r, or the row itself, has its values: the block's rows are NB apart.
+struct InversePart { const double* base; size_t pitch; };
+__device__ __forceinline__ InversePart inverse_part(const double* __restrict__ L, const double* __restrict__ Dinv, int np, int r, int c) {
+  if (r >> 6 == c >> 6) return {Dinv + (size_t)(r >> 6) * NB * NB + (r & 63) * NB + (c & 63), (size_t)NB};
+  return {L + (size_t)r * np + c, (size_t)np};
 }
+
+// The tiles of one pair of a level, `tiles` a side (a power of two), in such an order that the workgroups that share a CU, every 256th,
+// have much the same to do in all: the depth falls along the columns in step 1 and grows along the rows in step 2, and every other
+// 256 tiles go through them the other way (n = 4096, the last level: 319 and 235 us -> TRTRI).
+__device__ __forceinline__ bool other_way(int tiles) { return tiles <= 256 && ((blockIdx.x + tiles * blockIdx.y) / 256 & 1); }
 
 // Level with diagonal blocks of `b` rows: pair p joins A = [2pb, 2pb + b) and B = [2pb + b, min(2pb + 2b, np)).
 // Step 1: T = C . A^-1 into `T` (at C's place);  C = L[B rows, A columns].
 __global__ void __launch_bounds__(256) trtri_step1_kernel(const double* __restrict__ L, const double* __restrict__ Dinv,
                                                          int np, int b, double* __restrict__ T) {
   __shared__ Stage<2, 2> S;
-  const int a0 = 2 * b * blockIdx.z, b0 = a0 + b;
-  const int i0 = b0 + blockIdx.y * NB, j0 = blockIdx.x * NB;        // tile: rows i0.. (in B), columns a0 + j0.. (in A)
+  const int a0 = 2 * b * blockIdx.z, b0 = a0 + b, tiles = gridDim.x;
+  const int x = other_way(tiles) ? tiles - 1 - (int)blockIdx.x : (int)blockIdx.x;
+  const int i0 = b0 + blockIdx.y * NB, j0 = x * NB;                  // tile: rows i0.. (in B), columns a0 + j0.. (in A)
   if (i0 >= np) return;                                              // B is shorter than b, or missing
   Tile<2, 2> acc = {};
-  auto fa = [&](int i, int k) { return pair_at(L + (size_t)(i0 + i) * np + a0 + k); };
-  auto fb = [&](int j, int k) { return f64x2{inverse_at(L, Dinv, np, a0 + k, a0 + j0 + j), inverse_at(L, Dinv, np, a0 + k + 1, a0 + j0 + j)}; };
+  const RowPairs<2> fa([&](int r) { return L + (size_t)(i0 + r) * np + a0; });
+  auto fb = [&](int q, int k0) {             // (a stage of k lies in one block of rows)
+    const InversePart p = inverse_part(L, Dinv, np, a0 + k0, a0 + j0);
+    const double* v = p.base + (size_t)column_k<2>(q) * p.pitch + column_row<2>();
+    return f64x2{v[0], v[p.pitch]};
+  };
   tile_product<true>(acc, j0, b, fa, fb, S);                    // A^-1 is lower triangular: rows k >= j0 only
   each_element(acc, [&](int r, int c, double v) { T[(size_t)(i0 + r) * np + a0 + j0 + c] = v; });
 }
@@ -388,14 +430,21 @@ __global__ void __launch_bounds__(256) trtri_step1_kernel(const double* __restri
 __global__ void __launch_bounds__(256) trtri_step2_kernel(double* __restrict__ L, const double* __restrict__ Dinv, int np,
                                                          int b, const double* __restrict__ T) {
   __shared__ Stage<2, 2> S;
-  const int a0 = 2 * b * blockIdx.z, b0 = a0 + b;
-  const int i0 = blockIdx.y * NB, j0 = blockIdx.x * NB;              // tile: rows b0 + i0.., columns a0 + j0..
+  const int a0 = 2 * b * blockIdx.z, b0 = a0 + b, tiles = gridDim.x;
+  const int rows = max(256 / tiles, 1), y = other_way(tiles) ? (int)blockIdx.y + rows - 1 - 2 * ((int)blockIdx.y % rows) : (int)blockIdx.y;
+  const int i0 = y * NB, j0 = blockIdx.x * NB;                       // tile: rows b0 + i0.., columns a0 + j0..
   if (b0 + i0 >= np) return;
   Tile<2, 2> acc = {};
   // B^-1 (lower triangular, rows / columns relative to b0): its blocks left of the diagonal were written by the
   // lower levels, which are complete; this level writes blocks of C only
-  auto fa = [&](int i, int k) { return inverse_pair(L, Dinv, np, b0 + i0 + i, b0 + k); };
-  auto fb = [&](int j, int k) { return f64x2{T[(size_t)(b0 + k) * np + a0 + j0 + j], T[(size_t)(b0 + k + 1) * np + a0 + j0 + j]}; };
+  auto fa = [&](int q, int k0) {
+    const InversePart p = inverse_part(L, Dinv, np, b0 + i0, b0 + k0);
+    return pair_at(p.base + (size_t)staged_row(q) * p.pitch + staged_k());
+  };
+  auto fb = [&](int q, int k0) {
+    const double* v = T + (size_t)(b0 + k0 + column_k<2>(q)) * np + a0 + j0 + column_row<2>();
+    return f64x2{v[0], v[np]};
+  };
   tile_product<true>(acc, 0, i0 + NB, fa, fb, S);
   each_element(acc, [&](int r, int c, double v) { L[(size_t)(b0 + i0 + r) * np + a0 + j0 + c] = -v; });
 }
@@ -419,7 +468,7 @@ int spqr_hessian(const double* X, int32_t n, int32_t d, double* H, void* stream)
   if (reinterpret_cast<uintptr_t>(X) % 8 != 0 || reinterpret_cast<uintptr_t>(H) % 8 != 0) return SPQR_ERR_ALIGN;
   hipStream_t st = static_cast<hipStream_t>(stream);
   const int side = (n + SQ * NB - 1) / (SQ * NB), squares = side * (side + 1) / 2, run = (squares + 7) / 8;
-  hipLaunchKernelGGL(hessian_kernel, dim3(8 * run * SQ * SQ), dim3(256), 0, st, X, n, d, H, squares, run);
+  hipLaunchKernelGGL(d > 1 ? &hessian_kernel<false> : &hessian_kernel<true>, dim3(8 * run * SQ * SQ), dim3(256), 0, st, X, n, d, H, squares, run);
   return hipGetLastError() == hipSuccess ? SPQR_OK : SPQR_ERR_HIP;
 }
 
