@@ -56,8 +56,7 @@ extern "C" {
  * binary64, 8-byte aligned; H is overwritten (both triangles).  n, d >= 1 (SPQR_ERR_SHAPE otherwise). */
 int spqr_hessian(const double* X, int32_t n, int32_t d, double* H, void* stream);
 
-/* Scratch of spqr_inverse_cholesky in bytes (two square matrices of n rounded up to 64, and the inverses of the
- * diagonal blocks); 0 if n < 1. */
+/* Scratch of spqr_inverse_cholesky in bytes (two square matrices of n rounded up to 64); 0 if n < 1. */
 size_t spqr_inverse_cholesky_workspace_bytes(int32_t n);
 
 /* Alg. 1 line 3.  H[n][n] row-major, symmetric (the lower triangle is read), Hic[n][n] row-major: the upper

@@ -10,15 +10,15 @@
 //             the panel below times that inverse (transposed); the trailing lower triangle minus panel x panel^T
 //   trtri     X = L^-1 by doubling: with L = [[A, 0], [C, B]], L^-1 = [[A^-1, 0], [-B^-1 C A^-1, B^-1]].  Level s joins
 //             neighbouring diagonal blocks of 64 * 2^s: two launches of 64 x 64 tile products per level (T = C A^-1,
-//             then -B^-1 T written over C), every tile of every pair in parallel.  The inverse ends up where L was
-//             (strictly lower blocks) plus the diagonal blocks' inverses from the potrf step.
+//             then -B^-1 T written over C), every tile of every pair in parallel.  The inverse ends up where L was.
 //   final     U[i][j] = X[n-1-i][n-1-j] for j >= i
 //
 // Every tile product runs on the matrix cores (v_mfma_f64_16x16x4_f64), at the vector ALU's rate, but an operand of one
-// 8-byte half of an LDS read per lane feeds two instructions of 64 clocks.  n = d = 4096: Hessian 2.4 -> 1.65 ms (42 of 68 TFLOP/s;
-// staged by rows, squares of tiles per XCD), a block column of the factorisation 47 -> 33 us (the next diagonal block beside the trailing
-// update), the triangular inverse 1.13 -> 0.92 ms, Hessian and factor together 6.7 -> 4.4 ms.  What is left: the chain of 64
-// diagonal blocks of 13 us and panels of 5, bank conflicts (half of the LDS clocks of every product) and the barrier of every step of k.
+// 8-byte half of an LDS read per lane feeds two instructions of 64 clocks.  n = d = 4096, Hessian and factor together 4.77 -> 3.70 ms:
+// Hessian 1.48 -> 1.19 (after idle 1.6 -> 1.3: no vector instructions in the inner loop, see tile_product); block columns 33 -> 28 us on
+// average (the diagonal block's chain, potrf_diag); the triangular inverse 0.92 -> 0.60 (the same loop, and tiles dealt so that CUs have
+// equal work).  What is left: the chain of 64 diagonal blocks of 13 us, the product before each and panels of 5, and the early block
+// columns' updates, up to 35 us, which read and write the whole trailing triangle for 64 steps of k.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -31,137 +31,155 @@ namespace spqr_fac {
 
 constexpr int NB = 64;                       // block size of the factorisation
 constexpr int KC = 16;                       // depth of one LDS stage of a tile product
-// Padded row of a staged operand.  Conflicts are as many LDS clocks as the rest still (SQ_LDS_BANK_CONFLICT is half of
-// SQ_LDS_IDX_ACTIVE, reads and writes together); the Hessian with 0, 4, 6 and 8 instead of 2: 4.4, 1.79, 1.69 and 2.6 ms against 1.65.
-constexpr int LP = KC + 2;
+// Padded row of a staged operand: Hessian of 4096 inputs with 2, 4, 8 and 12 more than KC 1.20, 1.19, 1.22 and 1.30 ms (warm).
+constexpr int LP = KC + 4;
 
 typedef double f64x2 __attribute__((ext_vector_type(2)));
-typedef double f64x2_8 __attribute__((ext_vector_type(2), aligned(8)));
 typedef double f64x4 __attribute__((ext_vector_type(4)));
 
 // D += A B for one 16 x 16 block: lane l gives A[l % 16][l / 16] and B[l / 16][l % 16], D[r] is row l / 16 + 4 r, column l % 16.
 __device__ __forceinline__ f64x4 mfma4(double a, double b, f64x4 d) { return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, d, 0, 0, 0); }
 
-// A tile of 32 WM x 32 WN of four wavefronts, 16 WM x 16 WN each; two LDS buffers of KC steps, the next one's values in
-// registers while this one is multiplied.  Both operands are staged by rows, k innermost: a lane's 16-byte read is two steps
-// of k for one row, so a product of 8 steps takes WM + WN reads for 2 WM WN instructions of 64 clocks.  (One step a read, the
-// rows innermost: as many clocks of LDS as of the matrix cores, with bank conflicts on top.)
-template <int WM, int WN> struct Tile { f64x4 d[WM][WN]; };
-template <int WM, int WN> struct Stage { double a[2][32 * WM][LP], b[2][32 * WN][LP]; };
+// A tile of 64 x 64 of four wavefronts, 32 x 32 each; two LDS buffers of KC steps, the next one's values in registers while this one is
+// multiplied.  Both operands are staged by rows, k innermost: a lane's 16-byte read is two steps of k for one row, so a product of 8
+// steps takes 4 reads for 8 instructions of 64 clocks.  (One step a read, the rows innermost: as many clocks of LDS as of the matrix
+// cores, with bank conflicts on top.)
+//
+// A binary64 matrix instruction keeps the vector unit from any other: the inner loop has none.  A stage is fetched by a uniform base,
+// which the scalar unit moves on, and offsets that stay as they are; the buffers' places are constants of the instructions.  (A dozen
+// address and select instructions a stage and thread: the Hessian of 4096 inputs and samples 1.39 ms instead of 1.19, 58 of 68 TFLOP/s.)
+struct Tile { f64x4 d[2][2]; };
+struct alignas(16) Stage { double a[2][NB][LP], b[2][NB][LP]; };     // (without the alignment an LDS read is two of 8 bytes)
 
-// get_a / get_b (q, k0): the values at k and k + 1 of the q-th row that the thread stages of the stage that begins at k0; row and k - k0:
-// staged_row and staged_k, with B_BY_K column_row and column_k for B (consecutive threads fetch consecutive rows of it, not consecutive k).
-__device__ __forceinline__ int staged_row(int q) { return ((int)threadIdx.x + 256 * q) / (KC / 2); }
-__device__ __forceinline__ int staged_k() { return 2 * ((int)threadIdx.x % (KC / 2)); }
-template <int WN> __device__ __forceinline__ int column_row() { return (int)threadIdx.x % (32 * WN); }
-template <int WN> __device__ __forceinline__ int column_k(int q) { return 2 * (((int)threadIdx.x + 256 * q) / (32 * WN)); }
-
-template <class Get> __device__ __forceinline__ f64x2 settle(const Get&, f64x2 p, int) { return p; }
-
-// Rows of d values as operands, zeros behind them: the pair that ends a row is read one step early where it has to be and put right
-// when it goes to LDS.  SHORT: d = 1, whose pairs reach behind the matrix.
-template <bool SHORT> struct PaddedRows {
-  const double* p[2];
-  int d;
-  __device__ __forceinline__ PaddedRows(const double* X, int first, int n, int d_) : d(d_) {        // (rows behind the last: the last)
-#pragma unroll
-    for (int q = 0; q < 2; ++q) p[q] = X + (size_t)min(first + staged_row(q), n - 1) * d;
-  }
-  __device__ __forceinline__ f64x2 operator()(int q, int k0) const {
-    if constexpr (SHORT) return f64x2{*p[q], 0.0};
-    return *reinterpret_cast<const f64x2_8*>(p[q] + min(k0 + staged_k(), d - 2));
-  }
-};
-template <bool SHORT> __device__ __forceinline__ f64x2 settle(const PaddedRows<SHORT>& rows, f64x2 p, int k0) {
-  const int k = k0 + staged_k();
-  if constexpr (SHORT) return f64x2{k == 0 ? p.x : 0.0, 0.0};
-  return f64x2{k < rows.d - 1 ? p.x : k == rows.d - 1 ? p.y : 0.0, k < rows.d - 1 ? p.y : 0.0};
+typedef __amdgpu_buffer_rsrc_t Buffer;
+__device__ __forceinline__ Buffer buffer_of(const double* base) {    // (no bound: everything read lies in the matrix)
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<double*>(base), 0, -1, 0x00027000);
 }
 
-template <bool B_BY_K, int WM, int WN, class GetA, class GetB>
-__device__ __forceinline__ void tile_product(Tile<WM, WN>& acc, int kb, int ke, GetA get_a, GetB get_b, Stage<WM, WN>& S) {
-  constexpr int NA = WM, NW = WN;            // pairs a thread stages: 32 W rows of KC / 2 pairs over 256 threads
-  static_assert(256 % (32 * WN) == 0, "column_row is the same for every q");
-  const int t = threadIdx.x, lane = t & 63, wave = t >> 6, i16 = lane & 15, g4 = lane >> 4;
-  const int r0 = 16 * WM * (wave & 1) + i16, c0 = 16 * WN * (wave >> 1) + i16;
-  f64x2 pa[NA], pb[NW];
-  auto fetch = [&](int k0) {
+// What a thread stages of an operand of 64 rows: the pairs (k, k + 1) of rows row(0) and row(1).
+struct ByRows {                              // k innermost in memory: consecutive threads fetch consecutive k
+  const double* base;
+  uint32_t off[2];
+  __device__ __forceinline__ ByRows(const double* first, int pitch) : base(first) {        // pitch: of the rows
 #pragma unroll
-    for (int q = 0; q < NA; ++q) pa[q] = get_a(q, k0);
+    for (int q = 0; q < 2; ++q) off[q] = ((uint32_t)row(q) * (uint32_t)pitch + (uint32_t)k(q)) * 8u;
+  }
+  static __device__ __forceinline__ int row(int q) { return ((int)threadIdx.x + 256 * q) / (KC / 2); }
+  static __device__ __forceinline__ int k(int) { return 2 * ((int)threadIdx.x % (KC / 2)); }
+  __device__ __forceinline__ void fetch(f64x2 (&v)[2]) const {
+    const Buffer b = buffer_of(base);
 #pragma unroll
-    for (int q = 0; q < NW; ++q) pb[q] = get_b(q, k0);
-  };
-  auto stash = [&](int buf, int k0) {        // (settled here: done where they are fetched, the products would wait for them)
+    for (int q = 0; q < 2; ++q) v[q] = __builtin_bit_cast(f64x2, __builtin_amdgcn_raw_buffer_load_b128(b, off[q], 0, 0));
+  }
+  __device__ __forceinline__ void advance(int stages) { base += stages * KC; }
+};
+struct ByColumns {                           // the rows innermost: consecutive threads fetch consecutive rows
+  const double* base;
+  uint32_t off[2], pitch;                    // pitch: of k
+  __device__ __forceinline__ ByColumns(const double* first, int pitch_) : base(first), pitch(pitch_) {
 #pragma unroll
-    for (int q = 0; q < NA; ++q) *reinterpret_cast<f64x2*>(&S.a[buf][staged_row(q)][staged_k()]) = settle(get_a, pa[q], k0);
+    for (int q = 0; q < 2; ++q) off[q] = ((uint32_t)k(q) * pitch + (uint32_t)row(q)) * 8u;
+  }
+  static __device__ __forceinline__ int row(int) { return (int)threadIdx.x % NB; }
+  static __device__ __forceinline__ int k(int q) { return 2 * (((int)threadIdx.x + 256 * q) / NB); }
+  __device__ __forceinline__ void fetch(f64x2 (&v)[2]) const {
+    const Buffer b = buffer_of(base);
 #pragma unroll
-    for (int q = 0; q < NW; ++q)
-      *reinterpret_cast<f64x2*>(&S.b[buf][B_BY_K ? column_row<WN>() : staged_row(q)][B_BY_K ? column_k<WN>(q) : staged_k()]) = settle(get_b, pb[q], k0);
-  };
-  if (kb >= ke) return;                      // workgroup-uniform
-  __syncthreads();                           // a product before this one may still be read
-  fetch(kb);
-  stash(0, kb);
-  __syncthreads();
-  int buf = 0;
-  for (int k0 = kb; k0 < ke; k0 += KC, buf ^= 1) {
-    if (k0 + KC < ke) fetch(k0 + KC);
+    for (int q = 0; q < 2; ++q)
+      v[q] = f64x2{__builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(b, off[q], 0, 0)),
+                   __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(b, off[q], pitch * 8u, 0))};
+  }
+  __device__ __forceinline__ void advance(int stages) { base += (size_t)(stages * KC) * pitch; }
+};
+
+template <class A, class B> __device__ __forceinline__ void stash(Stage& S, int buf, const f64x2 (&pa)[2], const f64x2 (&pb)[2]) {
 #pragma unroll
-    for (int kk = 0; kk < KC; kk += 8) {
-      f64x2 a[WM], b[WN];
+  for (int q = 0; q < 2; ++q) {
+    *reinterpret_cast<f64x2*>(&S.a[buf][A::row(q)][A::k(q)]) = pa[q];
+    *reinterpret_cast<f64x2*>(&S.b[buf][B::row(q)][B::k(q)]) = pb[q];
+  }
+}
+__device__ __forceinline__ void multiply(Tile& acc, const Stage& S, int buf) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, i16 = lane & 15, g4 = lane >> 4;
+  const double *pa = &S.a[buf][32 * (wave & 1) + i16][2 * g4], *pb = &S.b[buf][32 * (wave >> 1) + i16][2 * g4];
 #pragma unroll
-      for (int m = 0; m < WM; ++m) a[m] = *reinterpret_cast<const f64x2*>(&S.a[buf][r0 + 16 * m][kk + 2 * g4]);
+  for (int kk = 0; kk < KC; kk += 8) {
+    f64x2 a[2], b[2];
 #pragma unroll
-      for (int n = 0; n < WN; ++n) b[n] = *reinterpret_cast<const f64x2*>(&S.b[buf][c0 + 16 * n][kk + 2 * g4]);
-#pragma unroll
-      for (int e = 0; e < 2; ++e)
-#pragma unroll
-        for (int m = 0; m < WM; ++m)
-#pragma unroll
-          for (int n = 0; n < WN; ++n) acc.d[m][n] = mfma4(a[m][e], b[n][e], acc.d[m][n]);
+    for (int m = 0; m < 2; ++m) {
+      a[m] = *reinterpret_cast<const f64x2*>(pa + 16 * m * LP + kk);
+      b[m] = *reinterpret_cast<const f64x2*>(pb + 16 * m * LP + kk);
     }
-    if (k0 + KC < ke) stash(buf ^ 1, k0 + KC);
+#pragma unroll
+    for (int e = 0; e < 2; ++e)
+#pragma unroll
+      for (int m = 0; m < 2; ++m)
+#pragma unroll
+        for (int n = 0; n < 2; ++n) acc.d[m][n] = mfma4(a[m][e], b[n][e], acc.d[m][n]);
+  }
+}
+
+// ... between the requests before it and what waits for them behind it (left to the compiler, the wait comes before the products).
+__device__ __forceinline__ void multiply_between(Tile& acc, const Stage& S, int buf) {
+  __builtin_amdgcn_sched_barrier(0);
+  multiply(acc, S, buf);
+  __builtin_amdgcn_sched_barrier(0);
+}
+
+// acc += A B^T over `stages` stages of KC; a barrier begins it (a product before may still be read) and ends it.
+template <class A, class B>
+__device__ __forceinline__ void tile_product(Tile& acc, A a, B b, int stages, Stage& S) {
+  __syncthreads();
+  if (stages <= 0) return;                   // workgroup-uniform
+  f64x2 pa[2], pb[2];
+  a.fetch(pa); b.fetch(pb);
+  stash<A, B>(S, 0, pa, pb);
+  __syncthreads();
+  for (int s = 1; s < stages; s += 2) {      // stage s - 1 lies in the first buffer
+    a.advance(1); b.advance(1);
+    a.fetch(pa); b.fetch(pb);
+    multiply_between(acc, S, 0);
+    stash<A, B>(S, 1, pa, pb);
+    __syncthreads();
+    const int more = s + 1 < stages ? 1 : 0; // (behind the last stage that one again, unused)
+    a.advance(more); b.advance(more);
+    a.fetch(pa); b.fetch(pb);
+    multiply_between(acc, S, 1);
+    stash<A, B>(S, 0, pa, pb);
+    __syncthreads();
+  }
+  if (stages & 1) {
+    multiply(acc, S, 0);
     __syncthreads();
   }
 }
 
 // f(row, column, value) for the tile's elements of this thread.
-template <int WM, int WN, class F>
-__device__ __forceinline__ void each_element(const Tile<WM, WN>& acc, F f) {
+template <class F>
+__device__ __forceinline__ void each_element(const Tile& acc, F f) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int r0 = 16 * WM * (wave & 1) + (lane >> 4), c0 = 16 * WN * (wave >> 1) + (lane & 15);
+  const int r0 = 32 * (wave & 1) + (lane >> 4), c0 = 32 * (wave >> 1) + (lane & 15);
 #pragma unroll
-  for (int a = 0; a < WM; ++a)
+  for (int a = 0; a < 2; ++a)
 #pragma unroll
-    for (int b = 0; b < WN; ++b)
+    for (int b = 0; b < 2; ++b)
 #pragma unroll
       for (int r = 0; r < 4; ++r) f(r0 + 16 * a + 4 * r, c0 + 16 * b, acc.d[a][b][r]);
 }
 // The tile with f(row, column) as this thread's elements.
-template <int WM, int WN, class F>
-__device__ __forceinline__ Tile<WM, WN> load_tile(F f) {
+template <class F>
+__device__ __forceinline__ Tile load_tile(F f) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int r0 = 16 * WM * (wave & 1) + (lane >> 4), c0 = 16 * WN * (wave >> 1) + (lane & 15);
-  Tile<WM, WN> t;
+  const int r0 = 32 * (wave & 1) + (lane >> 4), c0 = 32 * (wave >> 1) + (lane & 15);
+  Tile t;
 #pragma unroll
-  for (int a = 0; a < WM; ++a)
+  for (int a = 0; a < 2; ++a)
 #pragma unroll
-    for (int b = 0; b < WN; ++b)
+    for (int b = 0; b < 2; ++b)
 #pragma unroll
       for (int r = 0; r < 4; ++r) t.d[a][b][r] = f(r0 + 16 * a + 4 * r, c0 + 16 * b);
   return t;
 }
-__device__ __forceinline__ f64x2 pair_at(const double* p) { return *reinterpret_cast<const f64x2_8*>(p); }   // two in a row, 8-byte aligned
-
-// Rows of a matrix as an operand: row(q) is where the thread's q-th row begins.
-template <int N> struct RowPairs {
-  const double* p[N];
-  template <class F> __device__ __forceinline__ RowPairs(F row) {
-#pragma unroll
-    for (int q = 0; q < N; ++q) p[q] = row(staged_row(q)) + staged_k();
-  }
-  __device__ __forceinline__ f64x2 operator()(int q, int k0) const { return pair_at(p[q] + k0); }
-};
 
 // Number of a cell of an upper triangle (row by row, `side` cells in the first) -> row and column.
 __device__ __forceinline__ void upper_cell(int at, int side, int* row, int* col) {
@@ -174,17 +192,42 @@ __device__ __forceinline__ void upper_cell(int at, int side, int* row, int* col)
 // H = 2 X X^T, tiles on and above the diagonal, mirrored.  Squares of SQ x SQ tiles, a run of them for each of the 8 XCDs
 // (workgroups go to the XCDs in turn): the tiles that run side by side on an XCD share rows of X in its L2.
 constexpr int SQ = 2;
-template <bool SHORT>
+constexpr int kMostDepth = 1 << 22;          // 64 rows of it are within reach of a 32-bit offset
 __global__ void __launch_bounds__(256) hessian_kernel(const double* __restrict__ X, int n, int d, double* __restrict__ H, int squares, int run) {
-  __shared__ Stage<2, 2> S;
+  __shared__ Stage S;
   const int xcd = blockIdx.x % 8, at = blockIdx.x / 8, square = xcd * run + at / (SQ * SQ), side = (n + SQ * NB - 1) / (SQ * NB);
   if (square >= squares) return;             // workgroup-uniform
   int sr, sc;
   upper_cell(square, side, &sr, &sc);
   const int i0 = (sr * SQ + at % (SQ * SQ) / SQ) * NB, j0 = (sc * SQ + at % SQ) * NB;
   if (j0 < i0 || j0 >= n) return;            // below the diagonal or behind the matrix
-  Tile<2, 2> acc = {};
-  tile_product<false>(acc, 0, d, PaddedRows<SHORT>(X, i0, n, d), PaddedRows<SHORT>(X, j0, n, d), S);
+  Tile acc = {};
+  // (rows behind the last: the last, their sums are not written)
+  auto rows = [&](int first) {
+    ByRows o(X + (size_t)first * d, d);
+#pragma unroll
+    for (int q = 0; q < 2; ++q) o.off[q] = ((uint32_t)min(ByRows::row(q), n - 1 - first) * (uint32_t)d + (uint32_t)ByRows::k(q)) * 8u;
+    return o;
+  };
+  const int stages = d <= kMostDepth ? d / KC : 0;
+  tile_product(acc, rows(i0), rows(j0), stages, S);
+  for (int64_t k0 = (int64_t)stages * KC; k0 < d; k0 += KC) {        // the rest of the depth, zeros behind it
+    f64x2 pa[2], pb[2];
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      const int64_t k = k0 + ByRows::k(q);
+      auto pair = [&](int row) {
+        const double* x = X + (size_t)min(row, n - 1) * d + k;
+        return f64x2{k < d ? x[0] : 0.0, k + 1 < d ? x[1] : 0.0};
+      };
+      pa[q] = pair(i0 + ByRows::row(q));
+      pb[q] = pair(j0 + ByRows::row(q));
+    }
+    stash<ByRows, ByRows>(S, 0, pa, pb);
+    __syncthreads();
+    multiply(acc, S, 0);
+    __syncthreads();
+  }
   each_element(acc, [&](int r, int c, double v) {
     const int i = i0 + r, j = j0 + c;
     if (i <= j && j < n) {
@@ -235,7 +278,7 @@ __device__ __forceinline__ double bcast(double s) {
 }
 template <int... I, class F> __device__ __forceinline__ void unrolled(std::integer_sequence<int, I...>, F f) { (f(std::integral_constant<int, I>{}), ...); }
 
-// Diagonal block kb: Cholesky factor in place, its inverse to Dinv[kb].  Four panels of 16 columns.  A panel's own 16 x 16 block is the
+// Diagonal block kb: the inverse of its Cholesky factor in its place (nobody reads the factor's own block).  Four panels of 16 columns.  A panel's own 16 x 16 block is the
 // chain: one wavefront factorises and inverts it in registers, a lane per row of the factor and per column of the inverse (the four
 // groups of 16 lanes do the same), 2 (15 - j) updates a step of one instruction each, which take the step's column of the factor across
 // lanes themselves.  The rows below take the product with the inverse and the columns right of the panel their update from all
@@ -248,7 +291,7 @@ struct Diagonal {                            // block, inverse, a product betwee
   double D[NB][DP], X[NB][DP], T[32][34];
 };
 // `S.D` holds the block; every thread of the workgroup.
-__device__ __forceinline__ void potrf_diag(Diagonal& S, double* __restrict__ L, int np, int kb, double* __restrict__ Dinv) {
+__device__ __forceinline__ void potrf_diag(Diagonal& S, double* __restrict__ L, int np, int kb) {
   double (&D)[NB][Diagonal::DP] = S.D, (&X)[NB][Diagonal::DP] = S.X, (&T)[32][34] = S.T;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, i16 = lane & 15, g4 = lane >> 4;
   double* blk = L + (size_t)kb * NB * np + (size_t)kb * NB;
@@ -304,8 +347,6 @@ __device__ __forceinline__ void potrf_diag(Diagonal& S, double* __restrict__ L, 
       }
     __syncthreads();
   }
-  for (int idx = tid; idx < NB * NB; idx += 256)
-    blk[(size_t)(idx >> 6) * np + (idx & 63)] = (idx & 63) <= (idx >> 6) ? D[idx >> 6][idx & 63] : 0.0;
   // [[A, 0], [C, B]]^-1 = [[A^-1, 0], [-B^-1 C A^-1, B^-1]], first for the pairs of blocks of 16, then of 32
 #pragma unroll
   for (int h = 16; h <= 32; h *= 2) {
@@ -329,49 +370,43 @@ __device__ __forceinline__ void potrf_diag(Diagonal& S, double* __restrict__ L, 
     }
     __syncthreads();
   }
-  double* inv = Dinv + (size_t)kb * NB * NB;
-  for (int idx = tid; idx < NB * NB; idx += 256) inv[idx] = X[idx >> 6][idx & 63];
+  for (int idx = tid; idx < NB * NB; idx += 256) blk[(size_t)(idx >> 6) * np + (idx & 63)] = X[idx >> 6][idx & 63];
 }
 
 // The first diagonal block.
-__global__ void __launch_bounds__(256) potrf_first_kernel(double* __restrict__ L, int np, double* __restrict__ Dinv) {
+__global__ void __launch_bounds__(256) potrf_first_kernel(double* __restrict__ L, int np) {
   __shared__ Diagonal S;
   for (int idx = threadIdx.x; idx < NB * NB; idx += 256) S.D[idx >> 6][idx & 63] = L[(size_t)(idx >> 6) * np + (idx & 63)];
   __syncthreads();
-  potrf_diag(S, L, np, 0, Dinv);
+  potrf_diag(S, L, np, 0);
 }
 
 // Panel below diagonal block kb: A[ib, kb] <- A[ib, kb] . inv(L_kk)^T
-__global__ void __launch_bounds__(256) trsm_panel_kernel(double* __restrict__ L, int np, int kb, const double* __restrict__ Dinv) {
-  __shared__ Stage<2, 2> S;
+__global__ void __launch_bounds__(256) trsm_panel_kernel(double* __restrict__ L, int np, int kb) {
+  __shared__ Stage S;
   const int ib = kb + 1 + blockIdx.x;
   double* blk = L + (size_t)ib * NB * np + (size_t)kb * NB;
-  const double* inv = Dinv + (size_t)kb * NB * NB;
-  Tile<2, 2> acc = {};
-  const RowPairs<2> fa([&](int r) { return blk + (size_t)r * np; }), fb([&](int c) { return inv + c * NB; });
-  tile_product<false>(acc, 0, NB, fa, fb, S);           // every read of the block is done when it returns
+  Tile acc = {};
+  tile_product(acc, ByRows(blk, np), ByRows(L + (size_t)kb * NB * np + (size_t)kb * NB, np), NB / KC, S);   // every read of the block is done when it returns
   each_element(acc, [&](int r, int c, double v) { blk[(size_t)r * np + c] = v; });
 }
 
 // Trailing update: A[ib, jb] -= P_ib . P_jb^T for kb < jb <= ib, tile by tile of the lower triangle.  The first workgroup's is the
 // next diagonal block, which it then factorises: a launch lasts as long as the longer of the two, and the chain of block
 // columns is this launch and the panel's (n = 4096: 64 of 47 us, diagonal block, panel and update one after the other).
-__global__ void __launch_bounds__(256) update_kernel(double* __restrict__ L, int np, int kb, double* __restrict__ Dinv) {
-  union Shared { Stage<2, 2> stage; Diagonal diagonal; };
+__global__ void __launch_bounds__(256) update_kernel(double* __restrict__ L, int np, int kb) {
+  union Shared { Stage stage; Diagonal diagonal; };
   __shared__ Shared S;
   // tile number -> (row, column) of the lower triangle: row (row + 1) / 2 tiles stand before a row's first
   int row = (int)((sqrtf(8.0f * (float)blockIdx.x + 1.0f) - 1.0f) * 0.5f);
   while (row * (row + 1) / 2 > (int)blockIdx.x) --row;
   while ((row + 1) * (row + 2) / 2 <= (int)blockIdx.x) ++row;
   const int ib = kb + 1 + row, jb = kb + 1 + (int)blockIdx.x - row * (row + 1) / 2;
-  const double* pi = L + (size_t)ib * NB * np + (size_t)kb * NB;
-  const double* pj = L + (size_t)jb * NB * np + (size_t)kb * NB;
-  Tile<2, 2> acc = {};
-  const RowPairs<2> fa([&](int r) { return pi + (size_t)r * np; }), fb([&](int c) { return pj + (size_t)c * np; });
   // the tile itself, on its way while the product is formed (64 deep, that is short: 4096 inputs 4.51 -> 4.42 ms)
   double* blk = L + (size_t)ib * NB * np + (size_t)jb * NB;
-  const Tile<2, 2> before = load_tile<2, 2>([&](int r, int c) { return blk[(size_t)r * np + c]; });
-  tile_product<false>(acc, 0, NB, fa, fb, S.stage);
+  const Tile before = load_tile([&](int r, int c) { return blk[(size_t)r * np + c]; });
+  Tile acc = {};
+  tile_product(acc, ByRows(L + (size_t)ib * NB * np + (size_t)kb * NB, np), ByRows(L + (size_t)jb * NB * np + (size_t)kb * NB, np), NB / KC, S.stage);
 #pragma unroll
   for (int a = 0; a < 2; ++a)
 #pragma unroll
@@ -382,79 +417,47 @@ __global__ void __launch_bounds__(256) update_kernel(double* __restrict__ L, int
   }
   each_element(acc, [&](int r, int c, double v) { S.diagonal.D[r][c] = v; });   // (the product is over: a barrier ends it)
   __syncthreads();
-  potrf_diag(S.diagonal, L, np, kb + 1, Dinv);
-}
-
-// Element (r, c), r >= c, of the inverse as far as it is built: the diagonal 64-blocks live in Dinv, the blocks
-// below them where L was.
-__device__ __forceinline__ double inverse_at(const double* __restrict__ L, const double* __restrict__ Dinv, int np,
-                                             int r, int c) {
-  const int rb = r >> 6, cb = c >> 6;
-  if (rb == cb) return Dinv[(size_t)rb * NB * NB + (r & 63) * NB + (c & 63)];
-  return rb > cb ? L[(size_t)r * np + c] : 0.0;
-}
-
-// Where the inverse of the diagonal block that holds row r, or the row itself, has its values: the block's rows are NB apart.
-struct InversePart { const double* base; size_t pitch; };
-__device__ __forceinline__ InversePart inverse_part(const double* __restrict__ L, const double* __restrict__ Dinv, int np, int r, int c) {
-  if (r >> 6 == c >> 6) return {Dinv + (size_t)(r >> 6) * NB * NB + (r & 63) * NB + (c & 63), (size_t)NB};
-  return {L + (size_t)r * np + c, (size_t)np};
+  potrf_diag(S.diagonal, L, np, kb + 1);
 }
 
 // The tiles of one pair of a level, `tiles` a side (a power of two), in such an order that the workgroups that share a CU, every 256th,
 // have much the same to do in all: the depth falls along the columns in step 1 and grows along the rows in step 2, and every other
-// 256 tiles go through them the other way (n = 4096, the last level: 319 and 235 us -> TRTRI).
+// 256 tiles go through them the other way (n = 4096, the last level: 319 and 235 us -> 188 and 205; 163 and 164 with tile_product as it is).
 __device__ __forceinline__ bool other_way(int tiles) { return tiles <= 256 && ((blockIdx.x + tiles * blockIdx.y) / 256 & 1); }
 
 // Level with diagonal blocks of `b` rows: pair p joins A = [2pb, 2pb + b) and B = [2pb + b, min(2pb + 2b, np)).
 // Step 1: T = C . A^-1 into `T` (at C's place);  C = L[B rows, A columns].
-__global__ void __launch_bounds__(256) trtri_step1_kernel(const double* __restrict__ L, const double* __restrict__ Dinv,
-                                                         int np, int b, double* __restrict__ T) {
-  __shared__ Stage<2, 2> S;
+__global__ void __launch_bounds__(256) trtri_step1_kernel(const double* __restrict__ L, int np, int b, double* __restrict__ T) {
+  __shared__ Stage S;
   const int a0 = 2 * b * blockIdx.z, b0 = a0 + b, tiles = gridDim.x;
   const int x = other_way(tiles) ? tiles - 1 - (int)blockIdx.x : (int)blockIdx.x;
-  const int i0 = b0 + blockIdx.y * NB, j0 = x * NB;                  // tile: rows i0.. (in B), columns a0 + j0.. (in A)
+  const int i0 = b0 + blockIdx.y * NB, j0 = a0 + x * NB;             // tile: rows i0.. (in B), columns j0.. (in A)
   if (i0 >= np) return;                                              // B is shorter than b, or missing
-  Tile<2, 2> acc = {};
-  const RowPairs<2> fa([&](int r) { return L + (size_t)(i0 + r) * np + a0; });
-  auto fb = [&](int q, int k0) {             // (a stage of k lies in one block of rows)
-    const InversePart p = inverse_part(L, Dinv, np, a0 + k0, a0 + j0);
-    const double* v = p.base + (size_t)column_k<2>(q) * p.pitch + column_row<2>();
-    return f64x2{v[0], v[p.pitch]};
-  };
-  tile_product<true>(acc, j0, b, fa, fb, S);                    // A^-1 is lower triangular: rows k >= j0 only
-  each_element(acc, [&](int r, int c, double v) { T[(size_t)(i0 + r) * np + a0 + j0 + c] = v; });
+  Tile acc = {};
+  // A^-1 is lower triangular: rows k >= j0 only
+  tile_product(acc, ByRows(L + (size_t)i0 * np + j0, np), ByColumns(L + (size_t)j0 * np + j0, np), (b0 - j0) / KC, S);
+  each_element(acc, [&](int r, int c, double v) { T[(size_t)(i0 + r) * np + j0 + c] = v; });
 }
 
 // Step 2: -B^-1 . T over C.
-__global__ void __launch_bounds__(256) trtri_step2_kernel(double* __restrict__ L, const double* __restrict__ Dinv, int np,
-                                                         int b, const double* __restrict__ T) {
-  __shared__ Stage<2, 2> S;
+__global__ void __launch_bounds__(256) trtri_step2_kernel(double* __restrict__ L, int np, int b, const double* __restrict__ T) {
+  __shared__ Stage S;
   const int a0 = 2 * b * blockIdx.z, b0 = a0 + b, tiles = gridDim.x;
   const int rows = max(256 / tiles, 1), y = other_way(tiles) ? (int)blockIdx.y + rows - 1 - 2 * ((int)blockIdx.y % rows) : (int)blockIdx.y;
-  const int i0 = y * NB, j0 = blockIdx.x * NB;                       // tile: rows b0 + i0.., columns a0 + j0..
-  if (b0 + i0 >= np) return;
-  Tile<2, 2> acc = {};
-  // B^-1 (lower triangular, rows / columns relative to b0): its blocks left of the diagonal were written by the
-  // lower levels, which are complete; this level writes blocks of C only
-  auto fa = [&](int q, int k0) {
-    const InversePart p = inverse_part(L, Dinv, np, b0 + i0, b0 + k0);
-    return pair_at(p.base + (size_t)staged_row(q) * p.pitch + staged_k());
-  };
-  auto fb = [&](int q, int k0) {
-    const double* v = T + (size_t)(b0 + k0 + column_k<2>(q)) * np + a0 + j0 + column_row<2>();
-    return f64x2{v[0], v[np]};
-  };
-  tile_product<true>(acc, 0, i0 + NB, fa, fb, S);
-  each_element(acc, [&](int r, int c, double v) { L[(size_t)(b0 + i0 + r) * np + a0 + j0 + c] = -v; });
+  const int i0 = b0 + y * NB, j0 = a0 + blockIdx.x * NB;             // tile: rows i0.., columns j0..
+  if (i0 >= np) return;
+  Tile acc = {};
+  // B^-1, lower triangular: columns up to the tile's own block.  Its blocks left of the diagonal were written by the lower levels,
+  // which are complete; this level writes blocks of C only.
+  tile_product(acc, ByRows(L + (size_t)i0 * np + b0, np), ByColumns(T + (size_t)b0 * np + j0, np), (i0 + NB - b0) / KC, S);
+  each_element(acc, [&](int r, int c, double v) { L[(size_t)(i0 + r) * np + j0 + c] = -v; });
 }
 
-__global__ void __launch_bounds__(256) unreverse_kernel(const double* __restrict__ L, const double* __restrict__ Dinv, int n,
-                                                       int np, double* __restrict__ U) {
+__global__ void __launch_bounds__(256) unreverse_kernel(const double* __restrict__ L, int n, int np, double* __restrict__ U) {
   const size_t idx = (size_t)blockIdx.x * 256 + threadIdx.x;
   if (idx >= (size_t)n * n) return;
   const int i = (int)(idx / n), j = (int)(idx % n);
-  U[idx] = j >= i ? inverse_at(L, Dinv, np, n - 1 - i, n - 1 - j) : 0.0;
+  U[idx] = j >= i ? L[(size_t)(n - 1 - i) * np + (n - 1 - j)] : 0.0;
 }
 
 }  // namespace spqr_fac
@@ -468,14 +471,14 @@ int spqr_hessian(const double* X, int32_t n, int32_t d, double* H, void* stream)
   if (reinterpret_cast<uintptr_t>(X) % 8 != 0 || reinterpret_cast<uintptr_t>(H) % 8 != 0) return SPQR_ERR_ALIGN;
   hipStream_t st = static_cast<hipStream_t>(stream);
   const int side = (n + SQ * NB - 1) / (SQ * NB), squares = side * (side + 1) / 2, run = (squares + 7) / 8;
-  hipLaunchKernelGGL(d > 1 ? &hessian_kernel<false> : &hessian_kernel<true>, dim3(8 * run * SQ * SQ), dim3(256), 0, st, X, n, d, H, squares, run);
+  hipLaunchKernelGGL(hessian_kernel, dim3(8 * run * SQ * SQ), dim3(256), 0, st, X, n, d, H, squares, run);
   return hipGetLastError() == hipSuccess ? SPQR_OK : SPQR_ERR_HIP;
 }
 
 size_t spqr_inverse_cholesky_workspace_bytes(int32_t n) {
   if (n < 1) return 0;
   const size_t np = ((size_t)n + spqr_fac::NB - 1) / spqr_fac::NB * spqr_fac::NB;
-  return (2 * np * np + np * spqr_fac::NB) * sizeof(double);
+  return 2 * np * np * sizeof(double);
 }
 
 int spqr_inverse_cholesky(const double* H, int32_t n, double lambda, double* Hic, void* workspace,
@@ -492,21 +495,20 @@ int spqr_inverse_cholesky(const double* H, int32_t n, double lambda, double* Hic
   const int np = (n + NB - 1) / NB * NB, nb = np / NB;
   double* L = static_cast<double*>(workspace);
   double* X = L + (size_t)np * np;
-  double* Dinv = X + (size_t)np * np;
   const unsigned cells = (unsigned)(((size_t)np * np + 255) / 256);
   hipLaunchKernelGGL(init_reversed_kernel, dim3(cells), dim3(256), 0, st, H, n, np, lambda, L);
-  hipLaunchKernelGGL(potrf_first_kernel, dim3(1), dim3(256), 0, st, L, np, Dinv);
+  hipLaunchKernelGGL(potrf_first_kernel, dim3(1), dim3(256), 0, st, L, np);
   for (int kb = 0; kb + 1 < nb; ++kb) {
     const int rest = nb - kb - 1;
-    hipLaunchKernelGGL(trsm_panel_kernel, dim3(rest), dim3(256), 0, st, L, np, kb, Dinv);
-    hipLaunchKernelGGL(update_kernel, dim3(rest * (rest + 1) / 2), dim3(256), 0, st, L, np, kb, Dinv);
+    hipLaunchKernelGGL(trsm_panel_kernel, dim3(rest), dim3(256), 0, st, L, np, kb);
+    hipLaunchKernelGGL(update_kernel, dim3(rest * (rest + 1) / 2), dim3(256), 0, st, L, np, kb);
   }
   for (int b = NB; b < np; b *= 2) {
     const int tiles = b / NB, pairs = (np + 2 * b - 1) / (2 * b);
-    hipLaunchKernelGGL(trtri_step1_kernel, dim3(tiles, tiles, pairs), dim3(256), 0, st, L, Dinv, np, b, X);
-    hipLaunchKernelGGL(trtri_step2_kernel, dim3(tiles, tiles, pairs), dim3(256), 0, st, L, Dinv, np, b, X);
+    hipLaunchKernelGGL(trtri_step1_kernel, dim3(tiles, tiles, pairs), dim3(256), 0, st, L, np, b, X);
+    hipLaunchKernelGGL(trtri_step2_kernel, dim3(tiles, tiles, pairs), dim3(256), 0, st, L, np, b, X);
   }
-  hipLaunchKernelGGL(unreverse_kernel, dim3((unsigned)(((size_t)n * n + 255) / 256)), dim3(256), 0, st, L, Dinv, n, np, Hic);
+  hipLaunchKernelGGL(unreverse_kernel, dim3((unsigned)(((size_t)n * n + 255) / 256)), dim3(256), 0, st, L, n, np, Hic);
   return hipGetLastError() == hipSuccess ? SPQR_OK : SPQR_ERR_HIP;
 }
 
