@@ -1,6 +1,7 @@
 // Batches of 4 to 16 vectors on the matrix cores: one kernel for the dense part and the outliers, one that adds the
 // partial results; launchers, launch plan and scratch of that path.
 #include <hip/hip_runtime.h>
+#include <algorithm>
 #include <cstdint>
 #include <cstdlib>
 #include <mutex>
@@ -418,23 +419,29 @@ __device__ __forceinline__ void batch_group_body(const DevMatrix& A, const uint1
   }
 }
 
+// The units of a split: `per`, `more` more for the first `lead` of them.
+struct Shares {
+  int per, lead, more;
+  __host__ __device__ int first(int y) const { return y * per + (y < lead ? y : lead) * more; }
+};
+
 // APART: z == 0 is the dense part, the other z share the sets of 64 rows of the outliers, whose sums are partial results of
 // their own (gridDim.y of them, behind the dense ones).
 template <int W, int TR, int TC, int AXIS, bool APART>
 __device__ __forceinline__ void batch_group_share(const DevMatrix& A, const uint16_t* __restrict__ X, int batch,
-                                                  float* __restrict__ P, int group, int units_per_split, uint8_t* smem) {
-  const int units = (A.g.ntc + kUnitTiles - 1) / kUnitTiles, u_lo = blockIdx.y * units_per_split;   // never empty (host)
+                                                  float* __restrict__ P, int group, Shares shares, uint8_t* smem) {
+  const int units = (A.g.ntc + kUnitTiles - 1) / kUnitTiles, y = blockIdx.y, u_lo = shares.first(y);   // never empty (host)
   const int z = APART ? blockIdx.z : 0, sets = APART ? BatchShape<TR, TC>::ROWS / 64 / (gridDim.z - 1) : 0;
-  const int split = blockIdx.y + (z > 0 ? gridDim.y : 0);
+  const int split = y + (z > 0 ? gridDim.y : 0);
   batch_group_body<W, TR, TC, AXIS, APART>(A, X, batch, P + (int64_t)split * batch * A.g.m, group, u_lo,
-                                           min(units, u_lo + units_per_split), z > 0 ? (z - 1) * sets : 0, z * sets, smem);
+                                           min(units, shares.first(y + 1)), z > 0 ? (z - 1) * sets : 0, z * sets, smem);
 }
 
 template <int W, int TR, int TC, int AXIS, bool APART>
 __global__ void __launch_bounds__(256, 2)
-batch_group_kernel(DevMatrix A, const uint16_t* __restrict__ X, int batch, float* __restrict__ P, int units_per_split) {
+batch_group_kernel(DevMatrix A, const uint16_t* __restrict__ X, int batch, float* __restrict__ P, Shares shares) {
   extern __shared__ __align__(16) uint8_t smem[];
-  batch_group_share<W, TR, TC, AXIS, APART>(A, X, batch, P, blockIdx.x, units_per_split, smem);
+  batch_group_share<W, TR, TC, AXIS, APART>(A, X, batch, P, blockIdx.x, shares, smem);
 }
 
 // Several matrices that share the batch X and the format (q/k/v, gate/up of a decoder block) in one grid: blockIdx.x
@@ -452,14 +459,14 @@ struct BatchFused {
 
 template <int W, int TR, int TC, int AXIS, bool APART>
 __global__ void __launch_bounds__(256, 2)
-batch_group_fused_kernel(BatchFused F, const uint16_t* __restrict__ X, int batch, int units_per_split) {
+batch_group_fused_kernel(BatchFused F, const uint16_t* __restrict__ X, int batch, Shares shares) {
   extern __shared__ __align__(16) uint8_t smem[];
   int bx = blockIdx.x, i = 0;
   for (; i < F.count - 1; ++i) {             // workgroup-uniform
     if (bx < F.it[i].groups) break;
     bx -= F.it[i].groups;
   }
-  batch_group_share<W, TR, TC, AXIS, APART>(F.it[i].A, X, batch, F.it[i].P, bx, units_per_split, smem);
+  batch_group_share<W, TR, TC, AXIS, APART>(F.it[i].A, X, batch, F.it[i].P, bx, shares, smem);
 }
 
 // Y[v][row] = sum over the splits of P, in their order, rounded once to the output type.  One workgroup per group of
@@ -751,6 +758,25 @@ static BatchPlan plan_batch(const DevMatrix* As, int count, int b) {
   return best;
 }
 
+// The units of a plan's splits.  Where every CU gets two workgroups that do both parts, the first takes the dense part first and the
+// second the outliers (batch_group_body), and the second of a CU lives longer: us of a workgroup by its units, of 17920 x 6656 and
+// three of 6656^2, Zipf rows, 4 and 16 vectors: 9.4 + 4.2 u and 12.2 + 5.2 u.  So the splits whose workgroups come first get more.
+// Three of 6656^2, 4 vectors, units 5 5 5 5 5 1 -> 5 5 5 4 4 3: 46.5 -> 43.1 us; 17920 x 6656, 16 vectors, 4 4 4 4 4 4 2 -> 5 5 5 3 3 3 2:
+// 42.3 -> 40.8, the best of 35 ways to share them out each.
+static Shares batch_shares(const BatchPlan& p, const DevMatrix* As, int count) {
+  const Geometry& g = As[0].g;
+  const int units = batch_units(g), chunk = 1536 / (kUnitTiles * g.tile_cols), wgs = p.groups * p.splits, lead = kCUs / p.groups;
+  const Shares even = {p.per, 0, 0};
+  int64_t nnz = 0;
+  for (int i = 0; i < count; ++i) nnz += As[i].nnz;
+  if (nnz == 0 || p.shares > 0 || wgs <= kCUs || wgs > 2 * kCUs || lead < 1 || lead >= p.splits || option(SPQR_OPT_BATCH_STEPS) >= 1) return even;
+  Shares s = {(int)(((float)units - 0.67f * (float)lead) / (1.24f * (float)lead + (float)(p.splits - lead)) + 0.5f), lead, 0};
+  if (s.per < 1) return even;
+  s.more = std::max(0, (units - p.splits * s.per + lead - 1) / lead);
+  const bool covered = s.first(p.splits) >= units && s.first(p.splits - 1) < units;        // all of them, no split empty
+  return covered && s.per + s.more <= std::max(chunk, p.per) ? s : even;                   // (one piece of XT more would cost more)
+}
+
 int plan_batch_hook(const DevMatrix* As, int count, int b, int* per, int* splits, int* shares) {
   const BatchPlan p = plan_batch(As, count, b);
   *per = p.per; *splits = p.splits; *shares = p.shares;
@@ -806,7 +832,7 @@ static hipError_t launch_mfma_t(const DevMatrix& A, const uint16_t* X, int b, vo
     Xin = xp;
   }
   if (e == hipSuccess) {
-    hipLaunchKernelGGL(kernel, dim3(p.groups, p.splits, 1 + p.shares), dim3(256), SH::LDS, stream, A, Xin, b, P, p.per);
+    hipLaunchKernelGGL(kernel, dim3(p.groups, p.splits, 1 + p.shares), dim3(256), SH::LDS, stream, A, Xin, b, P, batch_shares(p, &A, 1));
     e = hipGetLastError();
   }
   if (e == hipSuccess) e = launch_sum_groups(g, P, p.parts, b, Y, y_dtype, stream);
@@ -873,7 +899,7 @@ static hipError_t launch_mfma_fused_t(const DevMatrix* As, int count, const uint
     Xin = xp;
   }
   if (e == hipSuccess) {
-    hipLaunchKernelGGL(kernel, dim3(p.groups, p.splits, 1 + p.shares), dim3(256), SH::LDS, stream, F, Xin, b, p.per);
+    hipLaunchKernelGGL(kernel, dim3(p.groups, p.splits, 1 + p.shares), dim3(256), SH::LDS, stream, F, Xin, b, batch_shares(p, As, count));
     e = hipGetLastError();
   }
   if (e == hipSuccess) {

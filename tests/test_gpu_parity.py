@@ -777,3 +777,28 @@ def test_matrix_core_batch_path_without_outliers_and_sparse_only(P, monkeypatch)
     Yg = P.spqr_gemm_smallbatch(B, dev(Xg)).cpu().numpy()
     refg = orc.matvec_sparse_only(g, Xg)
     assert max(rel_l2(Yg[k], refg[k]) for k in range(8)) <= REL_L2
+
+
+# more for the splits that come first: 3 3 3 1 1 1 units (even: 2 each) with a ragged last group of rows, 4 2 2 (3 3 2)
+@pytest.mark.parametrize("w,b1,b2,axis,m,n,b,per", [(3, 8, 32, 1, 8312, 6144, 16, 2), (4, 16, 16, 1, 33008, 2048, 4, 3)])
+def test_matrix_core_splits_of_unequal_width(P, w, b1, b2, axis, m, n, b, per):
+    """Against the same kernel with every split as wide as the next: the same weights and products, so the results differ by the
+    order of binary32 sums alone, a few roundings of 2^-24 of the largest partial sum each; and one vector against the batch-1 kernel
+    (u_j or the weights rounded to binary16: 2.1e-4 each)."""
+    f = synth.make_matrix(m, n, w_bits=w, beta1=b1, beta2=b2, group_axis=axis, outlier_rate=0.02, outlier_structure="cols64", seed=(91, m))
+    A = P.SpQRMatrix.from_logical(f)
+    X = dev(synth.make_x(n, b, seed=(92, m)))
+    P.spqr_set_option(P.SPQR_OPT_BATCH_PATH, P.SPQR_BATCH_PATH_MATRIX)
+    got = P.spqr_gemm_smallbatch(A, X).cpu().numpy().astype(np.float64)
+    again = P.spqr_gemm_smallbatch(A, X).cpu().numpy()
+    P.spqr_set_option(P.SPQR_OPT_BATCH_STEPS, per)
+    P.spqr_set_option(P.SPQR_OPT_BATCH_SHARES, 1)
+    even = P.spqr_gemm_smallbatch(A, X).cpu().numpy().astype(np.float64)
+    P.spqr_set_option(P.SPQR_OPT_BATCH_STEPS, 0)
+    P.spqr_set_option(P.SPQR_OPT_BATCH_SHARES, 0)
+    assert np.array_equal(got, again.astype(np.float64))
+    scale = np.abs(even).max()
+    assert np.abs(got - even).max() <= 2.0 ** -24 * 64 * scale
+    assert np.abs(got - even).max() > 0              # another order of sums: the two do take different splits
+    one = P.spqr_gemv(A, X[0].contiguous()).cpu().numpy()
+    assert rel_l2(got[0], one) <= 6e-4
