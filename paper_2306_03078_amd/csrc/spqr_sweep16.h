@@ -540,6 +540,8 @@ __device__ __forceinline__ void block_feedback(Sweep16Lds<B1>& S, int ib, int sb
     }
   }
 }
+// Wavefronts 1 to 3 for many columns, 2 and 3 have nothing else to do then; 1 alone for few.
+__device__ __forceinline__ int feedback_threads(int columns) { return columns > 48 ? 64 * 3 : 64; }
 // Its codes, outliers and their values, by one wavefront.
 template <int B1>
 __device__ __forceinline__ void block_results(const Sweep16Lds<B1>& S, const SweepArgs& a, int ib, int sb, int par, int lane, int row0, int rows) {
@@ -675,7 +677,7 @@ __global__ void __launch_bounds__(64 * kWaves16, 2) sweep16_kernel(SweepArgs a) 
           meet(&S.met, &target, lane);
           if (wave == 0) block_chain<B1>(S, a, fresh_s(b * B1), sb / B1 + b, b & 1, p, fresh_v(lane), row0, rows, S.esb[p]);
           else if (b > 0) {
-            block_feedback<B1>(S, fresh_s(b * B1) - B1, sbw, fresh_v(lane), 64 * 3, S.esb[p]);
+            block_feedback<B1>(S, fresh_s(b * B1) - B1, sbw, fresh_v(lane), feedback_threads(sbw - (b + 1) * B1), S.esb[p]);
             block_results<B1>(S, a, fresh_s(b * B1) - B1, sb, (b & 1) ^ 1, fresh_v(lane), row0, rows);
           }
           meet(&S.met, &target, lane);
@@ -700,8 +702,7 @@ __global__ void __launch_bounds__(64 * kWaves16, 2) sweep16_kernel(SweepArgs a) 
           meet(&S.met, &target, lane);
           CornerRows<B1 / 2> c = {};
           if (near && b >= 2) fetch_corner(c, U, n, next, (b - 2) * B1 + half, 2, lane);
-          if (b > 0) block_feedback<B1>(S, fresh_s(b * B1) - B1, sbw, fresh_v(tid) - 64, 64 * 3, S.esb[p]);
-          if (near && b >= 2) put_corner<B1>(S, c, (b - 2) * B1 + half, 2, lane);
+          if (b > 0 && feedback_threads(sbw - (b + 1) * B1) > 64) block_feedback<B1>(S, fresh_s(b * B1) - B1, sbw, fresh_v(tid) - 64, 64 * 3, S.esb[p]);
           if (near) {                                    // (128 columns: at least four blocks)
             const int start = blocks / 4;
             if (b == start) {                            // the far wavefronts have been over these columns
@@ -712,6 +713,7 @@ __global__ void __launch_bounds__(64 * kWaves16, 2) sweep16_kernel(SweepArgs a) 
               for (int r = 0; r < kRows16; ++r) N.cur[r] = buffer_f64(w_rows, noff, min(r, rows - 1) * n * 8);
             }
             if (b >= start) near_steps(N, U, n, sb, noff, min(b * B1, kSuper16 * (b + 1 - start) / (blocks - start)) & -Near::PF, S.esb[p]);
+            if (b >= 2) put_corner<B1>(S, c, (b - 2) * B1 + half, 2, lane);
           }
           meet(&S.met, &target, lane);
         }
