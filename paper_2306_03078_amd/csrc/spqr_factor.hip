@@ -14,10 +14,10 @@
 //   final     U[i][j] = X[n-1-i][n-1-j] for j >= i
 //
 // Every tile product runs on the matrix cores (v_mfma_f64_16x16x4_f64), at the vector ALU's rate, but an operand of one
-// 8-byte half of an LDS read per lane feeds two instructions of 64 clocks.  n = d = 4096, Hessian and factor together 4.77 -> 3.70 ms:
-// Hessian 1.48 -> 1.19 (after idle 1.6 -> 1.3: no vector instructions in the inner loop, see tile_product); block columns 33 -> 28 us on
+// 8-byte half of an LDS read per lane feeds two instructions of 64 clocks.  n = d = 4096, Hessian and factor together 4.77 -> 3.43 ms:
+// Hessian 1.48 -> 1.19 (after idle 1.6 -> 1.3: no vector instructions in the inner loop, see tile_product); block columns 33 -> 24 us on
 // average (the diagonal block's chain, potrf_diag); the triangular inverse 0.92 -> 0.60 (the same loop, and tiles dealt so that CUs have
-// equal work).  What is left: the chain of 64 diagonal blocks of 13 us, the product before each and panels of 5, and the early block
+// equal work).  What is left: the chain of 64 diagonal blocks of 9 us, the product before each and panels of 5, and the early block
 // columns' updates, up to 35 us, which read and write the whole trailing triangle for 64 steps of k.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -250,127 +250,150 @@ __global__ void __launch_bounds__(256) init_reversed_kernel(const double* __rest
   L[idx] = v;
 }
 
-// 1 / sqrt(x) and sqrt(x) by Newton steps on the hardware's estimate, to about a unit in the last place (x <= 0: NaN).
-__device__ __forceinline__ double rsqrt_f64(double x, double* root) {
-  double y = __builtin_amdgcn_rsq(x);
-#pragma unroll
-  for (int k = 0; k < 2; ++k) {
-    const double e = fma(-x * y, y, 1.0);    // 1 - x y^2
-    y = fma(0.5 * y, e, y);
-  }
-  const double r = x * y;
-  *root = fma(fma(-r, r, x), 0.5 * y, r);
-  return y;
+// 1 / sqrt(x) to about a unit in the last place (x <= 0: NaN).  The hardware's estimate is good to 2^-24 or better; with
+// e = 1 - x y^2 the true value is y (1 - e)^-1/2 = y (1 + e / 2 + 3 e^2 / 8 + ...), and what follows is below 2^-69.
+__device__ __forceinline__ double rsqrt_f64(double x) {
+  const double y = __builtin_amdgcn_rsq(x);
+  const double e = fma(-x * y, y, 1.0);
+  return fma(y * e, fma(e, 0.375, 0.5), y);
 }
 
-// d += (s of lane LANE of the row of 16) * m, as one instruction: v_fmac_f64 takes that operand across lanes by itself.  The compiler does
+// d -= (s of lane LANE of the row of 16) * m, as one instruction: v_fmac_f64 takes that operand across lanes by itself.  The compiler does
 // not look into the text for the two wait states between a write of `s` and its reading across lanes: bcast_ready() stands between.
 template <int LANE>
-__device__ __forceinline__ void fma_bcast(double& d, double s, double m) {
-  asm("v_fmac_f64_dpp %0, %1, %2 row_newbcast:%3 row_mask:0xf bank_mask:0xf" : "+v"(d) : "v"(s), "v"(m), "n"(LANE));
+__device__ __forceinline__ void fnma_bcast(double& d, double s, double m) {
+  asm volatile("v_fmac_f64_dpp %0, -%1, %2 row_newbcast:%3 row_mask:0xf bank_mask:0xf" : "+v"(d) : "v"(s), "v"(m), "n"(LANE));
 }
-__device__ __forceinline__ void bcast_ready(double& s) { asm("s_nop 1" : "+v"(s)); }
+__device__ __forceinline__ void bcast_ready(double& s) { asm volatile("s_nop 1" : "+v"(s)); }
 template <int LANE>
 __device__ __forceinline__ double bcast(double s) {
   double d;
-  asm("v_mov_b64_dpp %0, %1 row_newbcast:%2 row_mask:0xf bank_mask:0xf" : "=v"(d) : "v"(s), "n"(LANE));
+  asm volatile("v_mov_b64_dpp %0, %1 row_newbcast:%2 row_mask:0xf bank_mask:0xf" : "=v"(d) : "v"(s), "n"(LANE));
   return d;
 }
 template <int... I, class F> __device__ __forceinline__ void unrolled(std::integer_sequence<int, I...>, F f) { (f(std::integral_constant<int, I>{}), ...); }
 
-// Diagonal block kb: the inverse of its Cholesky factor in its place (nobody reads the factor's own block).  Four panels of 16 columns.  A panel's own 16 x 16 block is the
-// chain: one wavefront factorises and inverts it in registers, a lane per row of the factor and per column of the inverse (the four
-// groups of 16 lanes do the same), 2 (15 - j) updates a step of one instruction each, which take the step's column of the factor across
-// lanes themselves.  The rows below take the product with the inverse and the columns right of the panel their update from all
-// four wavefronts on the matrix cores; the inverse of the whole by doubling, 16 -> 32 -> 64, as products of blocks.
-// A lane per row of the whole panel, the column by two v_readlane a lane and the inverses of the 16 x 16 blocks afterwards, row by row
-// out of LDS, took 5 us more: the launch of a block column with few tiles left 22.5 -> 17.5 us, Hessian and factor of 4096 inputs 4.77 ->
-// 4.51 ms.
-struct Diagonal {                            // block, inverse, a product between
+// Diagonal block kb: the inverse of its Cholesky factor in its place (nobody reads the factor's own block).  Four panels of 16 columns.
+// A panel's own 16 x 16 block is the chain: wavefront 0 factorises and inverts it in registers, a lane per row of the factor and per
+// column of the inverse (the four groups of 16 lanes do the same), 2 (15 - j) updates a step of one instruction each, which take the
+// step's column of the factor across lanes themselves.  The next step's root hangs on the first of them; the others stand between
+// the operations of that root, in the clocks these wait for one another.
+//
+// Everything else is products of blocks of 16 on the matrix cores, and all of it that the next chain does not need is done beside it by
+// the other wavefronts: the blocks right of the next panel, and of row p of the inverse, X[p][j] = -X[p][p] W[j], the sums
+// W[j] = L[p][j] X[j][j] + ... + L[p][p - 1] X[p - 1][j], which wavefront j + 1 keeps in registers: an accumulator's layout is that
+// of a right operand.
+//
+// n = 4096, the launch of a block column with few tiles left: a lane per row of the whole panel, the column by two v_readlane a lane
+// and the inverses afterwards row by row out of LDS 22.5 us; updates across lanes and the inverse joined by doubling at the end 17.0;
+// as it is 12.0 (the diagonal entry itself, which nobody reads, no longer formed, a root by one step of third order instead of
+// two of second, the updates in its gaps, 4 of 8 products and barriers after the last chain gone).
+struct Diagonal {                            // block, inverse of its factor
   static constexpr int DP = NB + 2;
-  double D[NB][DP], X[NB][DP], T[32][34];
+  double D[NB][DP], X[NB][DP];
 };
+// The chain: r is row i of the block (what stands right of the diagonal means nothing), v column i of the identity, then of the inverse.
+__device__ __forceinline__ void potrf_chain(double (&r)[16], double (&v)[16]) {
+  bcast_ready(r[0]);
+  double y = rsqrt_f64(bcast<0>(r[0]));
+  unrolled(std::make_integer_sequence<int, 16>{}, [&](auto column) __attribute__((always_inline)) {
+    constexpr int j = decltype(column)::value, updates = 2 * (15 - j), gap = (updates - 1 + 5) / 6;
+    v[j] *= y;
+    if constexpr (j < 15) {
+      double l = r[j] * y;
+      bcast_ready(l);
+      // update 2 i of row or column j + 1 + i of r, 2 i + 1 of v
+      const auto update = [&](auto from, auto count) __attribute__((always_inline)) {
+        unrolled(std::make_integer_sequence<int, decltype(count)::value>{}, [&](auto at) __attribute__((always_inline)) {
+          constexpr int u = decltype(from)::value + decltype(at)::value, k = j + 1 + u / 2;
+          if constexpr (u < updates && u % 2 == 0) fnma_bcast<k>(r[k], l, l);
+          if constexpr (u < updates && u % 2 == 1) fnma_bcast<k>(v[k], l, v[j]);
+        });
+        __builtin_amdgcn_sched_barrier(0);
+      };
+#define SPQR_STEP(n, ...) __VA_ARGS__; update(std::integral_constant<int, 1 + (n)*gap>{}, std::integral_constant<int, gap>{})
+      update(std::integral_constant<int, 0>{}, std::integral_constant<int, 1>{});
+      bcast_ready(r[j + 1]);
+      SPQR_STEP(0, const double x = bcast<j + 1>(r[j + 1]));
+      SPQR_STEP(1, const double y0 = __builtin_amdgcn_rsq(x));      // rsqrt_f64(x)
+      SPQR_STEP(2, const double xy = x * y0);
+      SPQR_STEP(3, const double e = fma(-xy, y0, 1.0));
+      SPQR_STEP(4, const double h = fma(e, 0.375, 0.5); const double ye = y0 * e);
+      SPQR_STEP(5, y = fma(ye, h, y0));
+#undef SPQR_STEP
+    }
+  });
+}
 // `S.D` holds the block; every thread of the workgroup.
 __device__ __forceinline__ void potrf_diag(Diagonal& S, double* __restrict__ L, int np, int kb) {
-  double (&D)[NB][Diagonal::DP] = S.D, (&X)[NB][Diagonal::DP] = S.X, (&T)[32][34] = S.T;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, i16 = lane & 15, g4 = lane >> 4;
+  double (&D)[NB][Diagonal::DP] = S.D, (&X)[NB][Diagonal::DP] = S.X;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), i16 = lane & 15, g4 = lane >> 4;
   double* blk = L + (size_t)kb * NB * np + (size_t)kb * NB;
-  for (int idx = tid; idx < NB * NB; idx += 256) X[idx >> 6][idx & 63] = 0.0;
-  __syncthreads();
-  for (int p = 0; p < 4; ++p) {              // panel of columns c0 .. c0 + 15
+  const auto put = [&](int bi, int bj, auto value) __attribute__((always_inline)) {    // block (bi, bj) of the result, in an accumulator's layout
+#pragma unroll
+    for (int r = 0; r < 4; ++r) blk[(size_t)(16 * bi + g4 + 4 * r) * np + 16 * bj + i16] = value(r);
+  };
+  const auto trailing = [&](int p, int bi, int bj) __attribute__((always_inline)) {     // block (bi, bj) minus L[bi][p] L[bj][p]^T
+    f64x4 d = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int q = 0; q < 16; q += 4) d = mfma4(D[16 * bi + i16][16 * p + q + g4], D[16 * bj + i16][16 * p + q + g4], d);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) D[16 * bi + g4 + 4 * r][16 * bj + i16] -= d[r];
+  };
+  f64x4 W = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+  for (int p = 0; p < 4; ++p) {              // panel of columns 16 p ..
     const int c0 = 16 * p;
     if (wave == 0) {
-      double r[16], v[16];                   // row i16 of the block (right of the diagonal: nothing), column i16 of the inverse
+      if (p > 0) trailing(p - 1, p, p);
+      double r[16], v[16];
 #pragma unroll
       for (int k = 0; k < 16; ++k) { r[k] = D[c0 + i16][c0 + k]; v[k] = k == i16 ? 1.0 : 0.0; }
-      unrolled(std::make_integer_sequence<int, 16>{}, [&](auto column) __attribute__((always_inline)) {
-        constexpr int j = decltype(column)::value;
-        double root;
-        bcast_ready(r[j]);
-        const double y = rsqrt_f64(bcast<j>(r[j]), &root);
-        double l = i16 == j ? root : r[j] * y;
-        r[j] = l;
-        v[j] *= y;
-        const double nl = -l, nv = -v[j];
-        bcast_ready(l);
-        unrolled(std::make_integer_sequence<int, 15 - j>{}, [&](auto at) __attribute__((always_inline)) {
-          constexpr int k = j + 1 + decltype(at)::value;
-          fma_bcast<k>(r[k], l, nl);         // meaningful for k <= i16
-          fma_bcast<k>(v[k], l, nv);
-        });
-      });
+      potrf_chain(r, v);
       if (g4 == 0) {
 #pragma unroll
-        for (int k = 0; k < 16; ++k) { D[c0 + i16][c0 + k] = k <= i16 ? r[k] : 0.0; X[c0 + k][c0 + i16] = v[k]; }
+        for (int k = 0; k < 16; ++k) X[c0 + k][c0 + i16] = v[k];
+      }
+    } else {                                 // beside the chain
+      if (p > 0) {
+        int turn = 0;
+        for (int bi = p + 1; bi < 4; ++bi)
+          for (int bj = p; bj <= bi; ++bj)
+            if (turn++ % 3 == wave - 1) trailing(p - 1, bi, bj);
+        if (wave <= p) {
+          const int j = wave - 1;
+          W = f64x4{0.0, 0.0, 0.0, 0.0};
+          for (int k = j; k < p; ++k)
+#pragma unroll
+            for (int q = 0; q < 16; q += 4) W = mfma4(D[c0 + i16][16 * k + q + g4], X[16 * k + q + g4][16 * j + i16], W);
+        }
+        if (wave == 3) put(p - 1, p - 1, [&](int r) { return X[c0 - 16 + g4 + 4 * r][c0 - 16 + i16]; });
+      } else {                               // above the diagonal
+        put(0, wave, [](int) { return 0.0; });
+        put(wave == 3 ? 2 : 1, wave == 1 ? 2 : 3, [](int) { return 0.0; });
       }
     }
     __syncthreads();
-    if (p == 3) break;
-    if (wave > p) {                          // wave-uniform: the rows of block `wave` times the inverse, transposed
+    if (wave > p) {                          // the rows of block `wave` times the inverse, transposed
       f64x4 d = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
       for (int q = 0; q < 16; q += 4) d = mfma4(D[16 * wave + i16][c0 + q + g4], X[c0 + i16][c0 + q + g4], d);
 #pragma unroll
       for (int r = 0; r < 4; ++r) D[16 * wave + g4 + 4 * r][c0 + i16] = d[r];
-    }
-    __syncthreads();
-    // blocks (bi, bj), p < bj <= bi: minus L[bi][p] L[bj][p]^T, dealt to the wavefronts in turn
-    int pair = 0;
-    for (int bi = p + 1; bi < 4; ++bi)
-      for (int bj = p + 1; bj <= bi; ++bj) {
-        if ((pair++ & 3) != wave) continue;  // wave-uniform
-        f64x4 d = {0.0, 0.0, 0.0, 0.0};
+    } else if (wave > 0) {                   // block (p, wave - 1) of the inverse
+      f64x4 d = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-        for (int q = 0; q < 16; q += 4) d = mfma4(D[16 * bi + i16][c0 + q + g4], D[16 * bj + i16][c0 + q + g4], d);
+      for (int q = 0; q < 16; q += 4) d = mfma4(X[c0 + i16][c0 + q + g4], W[q / 4], d);
+      if (p < 3) {
 #pragma unroll
-        for (int r = 0; r < 4; ++r) D[16 * bi + g4 + 4 * r][16 * bj + i16] -= d[r];
+        for (int r = 0; r < 4; ++r) X[c0 + g4 + 4 * r][16 * (wave - 1) + i16] = -d[r];
       }
-    __syncthreads();
-  }
-  // [[A, 0], [C, B]]^-1 = [[A^-1, 0], [-B^-1 C A^-1, B^-1]], first for the pairs of blocks of 16, then of 32
-#pragma unroll
-  for (int h = 16; h <= 32; h *= 2) {
-    const int per = h / 16;                  // blocks of 16 per side of C
-    const int pairs = 32 / h;                // joins of this level; per * per blocks each, one per wavefront
-    const int join = wave / (per * per), b = wave % (per * per), bi = 16 * (b / per), bj = 16 * (b % per);
-    const int a0 = 2 * h * join, b0 = a0 + h;
-    const bool mine = join < pairs;          // wave-uniform
-    f64x4 d = {0.0, 0.0, 0.0, 0.0};
-    if (mine) {
-      for (int q = 0; q < h; q += 4) d = mfma4(D[b0 + bi + i16][a0 + q + g4], X[a0 + q + g4][a0 + bj + i16], d);   // C A^-1
-#pragma unroll
-      for (int r = 0; r < 4; ++r) T[(h == 16 ? 16 * join : bi) + g4 + 4 * r][bj + i16] = d[r];
+      put(p, wave - 1, [&](int r) { return -d[r]; });
+    } else if (p == 3) {
+      put(3, 3, [&](int r) { return X[48 + g4 + 4 * r][48 + i16]; });
     }
-    __syncthreads();
-    if (mine) {
-      d = f64x4{0.0, 0.0, 0.0, 0.0};
-      for (int q = 0; q < h; q += 4) d = mfma4(X[b0 + bi + i16][b0 + q + g4], T[(h == 16 ? 16 * join : 0) + q + g4][bj + i16], d);
-#pragma unroll
-      for (int r = 0; r < 4; ++r) X[b0 + bi + g4 + 4 * r][a0 + bj + i16] = -d[r];
-    }
-    __syncthreads();
+    if (p < 3) __syncthreads();
   }
-  for (int idx = tid; idx < NB * NB; idx += 256) blk[(size_t)(idx >> 6) * np + (idx & 63)] = X[idx >> 6][idx & 63];
 }
 
 // The first diagonal block.
