@@ -14,11 +14,11 @@
 //   final     U[i][j] = X[n-1-i][n-1-j] for j >= i
 //
 // Every tile product runs on the matrix cores (v_mfma_f64_16x16x4_f64), at the vector ALU's rate, but an operand of one
-// 8-byte half of an LDS read per lane feeds two instructions of 64 clocks.  n = d = 4096, Hessian and factor together 4.77 -> 3.43 ms:
-// Hessian 1.48 -> 1.19 (after idle 1.6 -> 1.3: no vector instructions in the inner loop, see tile_product); block columns 33 -> 24 us on
+// 8-byte half of an LDS read per lane feeds two instructions of 64 clocks.  n = d = 4096, Hessian and factor together 4.77 -> 3.33 ms:
+// Hessian 1.48 -> 1.19 (after idle 1.6 -> 1.3: no vector instructions in the inner loop, see tile_product); block columns 33 -> 22 us on
 // average (the diagonal block's chain, potrf_diag); the triangular inverse 0.92 -> 0.60 (the same loop, and tiles dealt so that CUs have
-// equal work).  What is left: the chain of 64 diagonal blocks of 9 us, the product before each and panels of 5, and the early block
-// columns' updates, up to 35 us, which read and write the whole trailing triangle for 64 steps of k.
+// equal work).  What is left: the chain of 64 diagonal blocks of 9 us, the product before each and panels of 5, and the chain's
+// neighbours in the early block columns (update_kernel).
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -288,9 +288,9 @@ template <int... I, class F> __device__ __forceinline__ void unrolled(std::integ
 // and the inverses afterwards row by row out of LDS 22.5 us; updates across lanes and the inverse joined by doubling at the end 17.0;
 // as it is 12.0 (the diagonal entry itself, which nobody reads, no longer formed, a root by one step of third order instead of
 // two of second, the updates in its gaps, 4 of 8 products and barriers after the last chain gone).
-struct Diagonal {                            // block, inverse of its factor
+struct Diagonal {
   static constexpr int DP = NB + 2;
-  double D[NB][DP], X[NB][DP];
+  double D[NB][DP];                          // the block; block (i, j) of the inverse in the place of block (j, i), which nobody reads by then
 };
 // The chain: r is row i of the block (what stands right of the diagonal means nothing), v column i of the identity, then of the inverse.
 __device__ __forceinline__ void potrf_chain(double (&r)[16], double (&v)[16]) {
@@ -326,7 +326,7 @@ __device__ __forceinline__ void potrf_chain(double (&r)[16], double (&v)[16]) {
 }
 // `S.D` holds the block; every thread of the workgroup.
 __device__ __forceinline__ void potrf_diag(Diagonal& S, double* __restrict__ L, int np, int kb) {
-  double (&D)[NB][Diagonal::DP] = S.D, (&X)[NB][Diagonal::DP] = S.X;
+  double (&D)[NB][Diagonal::DP] = S.D;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), i16 = lane & 15, g4 = lane >> 4;
   double* blk = L + (size_t)kb * NB * np + (size_t)kb * NB;
   const auto put = [&](int bi, int bj, auto value) __attribute__((always_inline)) {    // block (bi, bj) of the result, in an accumulator's layout
@@ -352,7 +352,7 @@ __device__ __forceinline__ void potrf_diag(Diagonal& S, double* __restrict__ L, 
       potrf_chain(r, v);
       if (g4 == 0) {
 #pragma unroll
-        for (int k = 0; k < 16; ++k) X[c0 + k][c0 + i16] = v[k];
+        for (int k = 0; k < 16; ++k) D[c0 + k][c0 + i16] = v[k];
       }
     } else {                                 // beside the chain
       if (p > 0) {
@@ -365,9 +365,9 @@ __device__ __forceinline__ void potrf_diag(Diagonal& S, double* __restrict__ L, 
           W = f64x4{0.0, 0.0, 0.0, 0.0};
           for (int k = j; k < p; ++k)
 #pragma unroll
-            for (int q = 0; q < 16; q += 4) W = mfma4(D[c0 + i16][16 * k + q + g4], X[16 * k + q + g4][16 * j + i16], W);
+            for (int q = 0; q < 16; q += 4) W = mfma4(D[c0 + i16][16 * k + q + g4], D[16 * j + q + g4][16 * k + i16], W);
         }
-        if (wave == 3) put(p - 1, p - 1, [&](int r) { return X[c0 - 16 + g4 + 4 * r][c0 - 16 + i16]; });
+        if (wave == 3) put(p - 1, p - 1, [&](int r) { return D[c0 - 16 + g4 + 4 * r][c0 - 16 + i16]; });
       } else {                               // above the diagonal
         put(0, wave, [](int) { return 0.0; });
         put(wave == 3 ? 2 : 1, wave == 1 ? 2 : 3, [](int) { return 0.0; });
@@ -377,20 +377,20 @@ __device__ __forceinline__ void potrf_diag(Diagonal& S, double* __restrict__ L, 
     if (wave > p) {                          // the rows of block `wave` times the inverse, transposed
       f64x4 d = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-      for (int q = 0; q < 16; q += 4) d = mfma4(D[16 * wave + i16][c0 + q + g4], X[c0 + i16][c0 + q + g4], d);
+      for (int q = 0; q < 16; q += 4) d = mfma4(D[16 * wave + i16][c0 + q + g4], D[c0 + i16][c0 + q + g4], d);
 #pragma unroll
       for (int r = 0; r < 4; ++r) D[16 * wave + g4 + 4 * r][c0 + i16] = d[r];
     } else if (wave > 0) {                   // block (p, wave - 1) of the inverse
       f64x4 d = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-      for (int q = 0; q < 16; q += 4) d = mfma4(X[c0 + i16][c0 + q + g4], W[q / 4], d);
+      for (int q = 0; q < 16; q += 4) d = mfma4(D[c0 + i16][c0 + q + g4], W[q / 4], d);
       if (p < 3) {
 #pragma unroll
-        for (int r = 0; r < 4; ++r) X[c0 + g4 + 4 * r][16 * (wave - 1) + i16] = -d[r];
+        for (int r = 0; r < 4; ++r) D[16 * (wave - 1) + g4 + 4 * r][c0 + i16] = -d[r];
       }
       put(p, wave - 1, [&](int r) { return -d[r]; });
     } else if (p == 3) {
-      put(3, 3, [&](int r) { return X[48 + g4 + 4 * r][48 + i16]; });
+      put(3, 3, [&](int r) { return D[48 + g4 + 4 * r][48 + i16]; });
     }
     if (p < 3) __syncthreads();
   }
@@ -417,25 +417,48 @@ __global__ void __launch_bounds__(256) trsm_panel_kernel(double* __restrict__ L,
 // Trailing update: A[ib, jb] -= P_ib . P_jb^T for kb < jb <= ib, tile by tile of the lower triangle.  The first workgroup's is the
 // next diagonal block, which it then factorises: a launch lasts as long as the longer of the two, and the chain of block
 // columns is this launch and the panel's (n = 4096: 64 of 47 us, diagonal block, panel and update one after the other).
+//
+// A tile is 64 KiB of traffic however many panels it takes, and the workgroups beside the chain on its CU hold it up (12 us alone, 18 with
+// one, 28 with three: a binary64 matrix instruction keeps the vector unit for 64 clocks).  So a column of tiles takes its panels kLag
+// at a time, a launch before it becomes the panel itself and every kLag-th before that, and a launch has a kLag-th of the columns.
+// What stands before the chain stays 64 deep: the diagonal block that comes after the next takes what it lacks a launch early, by the
+// last workgroup.  The 63 launches of n = 4096 (warm): 1, 2, 3 and 4 panels at a time 1183, 1130, 1052 and 1146 us
+// (one, two workgroups more of which fit a CU beside the chain than with the inverse in an array of its own: 1214).
+constexpr int kLag = 3;
+// Tiles of the columns before column c of those of a launch; `rest` block rows are left.
+__host__ __device__ constexpr int tiles_before(int c, int rest) { return c * rest - kLag * (c * (c - 1) / 2); }
+static int update_tiles(int rest) { return tiles_before((rest + kLag - 1) / kLag, rest) + (rest > 1 ? 1 : 0); }
 __global__ void __launch_bounds__(256) update_kernel(double* __restrict__ L, int np, int kb) {
   union Shared { Stage stage; Diagonal diagonal; };
   __shared__ Shared S;
-  // tile number -> (row, column) of the lower triangle: row (row + 1) / 2 tiles stand before a row's first
-  int row = (int)((sqrtf(8.0f * (float)blockIdx.x + 1.0f) - 1.0f) * 0.5f);
-  while (row * (row + 1) / 2 > (int)blockIdx.x) --row;
-  while ((row + 1) * (row + 2) / 2 <= (int)blockIdx.x) ++row;
-  const int ib = kb + 1 + row, jb = kb + 1 + (int)blockIdx.x - row * (row + 1) / 2;
+  const int at = blockIdx.x, rest = np / NB - kb - 1;
+  int ib = kb + 1, jb = kb + 1, from = kb;   // row and column; first panel
+  if (at > 0 && at == (int)gridDim.x - 1) {
+    ib = jb = kb + 2;
+    from = max(kb - kLag + 2, 0);
+  } else if (at > 0) {                       // tile number -> column and row of it
+    const float h = (float)rest + 0.5f * kLag;
+    int c = max((int)((h - sqrtf(fmaxf(h * h - 2.0f * kLag * (float)at, 0.0f))) * (1.0f / kLag)), 0);
+    while (tiles_before(c, rest) > at) --c;
+    while (tiles_before(c + 1, rest) <= at) ++c;
+    jb = kb + 1 + kLag * __builtin_amdgcn_readfirstlane(c);
+    ib = __builtin_amdgcn_readfirstlane(jb + at - tiles_before(c, rest));
+    from = max(kb - kLag + 1, 0);
+  }
   // the tile itself, on its way while the product is formed (64 deep, that is short: 4096 inputs 4.51 -> 4.42 ms)
   double* blk = L + (size_t)ib * NB * np + (size_t)jb * NB;
   const Tile before = load_tile([&](int r, int c) { return blk[(size_t)r * np + c]; });
   Tile acc = {};
-  tile_product(acc, ByRows(L + (size_t)ib * NB * np + (size_t)kb * NB, np), ByRows(L + (size_t)jb * NB * np + (size_t)kb * NB, np), NB / KC, S.stage);
+  tile_product(acc, ByRows(L + (size_t)ib * NB * np + (size_t)from * NB, np), ByRows(L + (size_t)jb * NB * np + (size_t)from * NB, np),
+               (kb + 1 - from) * (NB / KC), S.stage);
 #pragma unroll
   for (int a = 0; a < 2; ++a)
 #pragma unroll
     for (int b = 0; b < 2; ++b) acc.d[a][b] = before.d[a][b] - acc.d[a][b];
-  if (blockIdx.x > 0) {                      // workgroup-uniform
-    each_element(acc, [&](int r, int c, double v) { blk[(size_t)r * np + c] = v; });
+  if (at > 0) {                              // workgroup-uniform
+    int pitch = np;
+    asm volatile("" : "+s"(pitch));          // the places anew: kept, they would cost the fourth workgroup of a CU
+    each_element(acc, [&](int r, int c, double v) { blk[(size_t)r * pitch + c] = v; });
     return;
   }
   each_element(acc, [&](int r, int c, double v) { S.diagonal.D[r][c] = v; });   // (the product is over: a barrier ends it)
@@ -524,7 +547,7 @@ int spqr_inverse_cholesky(const double* H, int32_t n, double lambda, double* Hic
   for (int kb = 0; kb + 1 < nb; ++kb) {
     const int rest = nb - kb - 1;
     hipLaunchKernelGGL(trsm_panel_kernel, dim3(rest), dim3(256), 0, st, L, np, kb);
-    hipLaunchKernelGGL(update_kernel, dim3(rest * (rest + 1) / 2), dim3(256), 0, st, L, np, kb);
+    hipLaunchKernelGGL(update_kernel, dim3(update_tiles(rest)), dim3(256), 0, st, L, np, kb);
   }
   for (int b = NB; b < np; b *= 2) {
     const int tiles = b / NB, pairs = (np + 2 * b - 1) / (2 * b);

@@ -225,6 +225,24 @@ def test_hessian_and_factor_at_the_edges_of_tiles_and_squares(n, d):
     assert float((U.T @ U @ A - torch.eye(n, dtype=torch.float64, device="cuda")).abs().max()) <= 4 * n * cond * 2.0 ** -53
 
 
+# 3, 4, 5 and 6 block columns (a column takes three panels at a time, fewer at the left edge; the block behind the next takes its own
+# early, or is not there), and a second pair of 16 blocks a side whose lower half is short (its tiles are dealt the other way round)
+@pytest.mark.parametrize("n", [130, 193, 320, 321, 3150])
+def test_inverse_cholesky_panels_at_a_time(n):
+    import torch
+    import paper_2306_03078_amd.encode_binding as E
+    g = torch.Generator(device="cuda")
+    g.manual_seed(n)
+    X = torch.randn((n, n // 2), generator=g, dtype=torch.float64, device="cuda")
+    H = 2 * X @ X.T
+    lam = float(H.diagonal().mean()) * 0.1
+    U = E.spqr_inverse_cholesky(H, lam)
+    assert bool((U.tril(-1) == 0).all()) and bool((U.diagonal() > 0).all())
+    A = H + lam * torch.eye(n, dtype=torch.float64, device="cuda")
+    cond = float(torch.linalg.norm(A) / lam)
+    assert float((U.T @ U @ A - torch.eye(n, dtype=torch.float64, device="cuda")).abs().max()) <= 4 * n * cond * 2.0 ** -53
+
+
 # the 16-row kernel: divisions outside the range of the prepared divisors (weights above 2^300 and below 2^-300, a diagonal below
 # 2^-100 or negative, errors that are exactly 0), more rows than 256 workgroups hold, ragged workgroups and super-blocks; the last: the
 # line from where few narrow columns go to 64 rows a workgroup
