@@ -14,9 +14,9 @@
 //   final     U[i][j] = X[n-1-i][n-1-j] for j >= i
 //
 // Every tile product runs on the matrix cores (v_mfma_f64_16x16x4_f64), at the vector ALU's rate, but an operand of one
-// 8-byte half of an LDS read per lane feeds two instructions of 64 clocks.  n = d = 4096, Hessian and factor together 4.77 -> 3.33 ms:
+// 8-byte half of an LDS read per lane feeds two instructions of 64 clocks.  n = d = 4096, Hessian and factor together 4.77 -> 3.28 ms:
 // Hessian 1.48 -> 1.19 (after idle 1.6 -> 1.3: no vector instructions in the inner loop, see tile_product); block columns 33 -> 22 us on
-// average (the diagonal block's chain, potrf_diag); the triangular inverse 0.92 -> 0.60 (the same loop, and tiles dealt so that CUs have
+// average (the diagonal block's chain, potrf_diag); the triangular inverse 0.92 -> 0.55 (the same loop, and tiles dealt so that CUs have
 // equal work).  What is left: the chain of 64 diagonal blocks of 9 us, the product before each and panels of 5, and the chain's
 // neighbours in the early block columns (update_kernel).
 #include <hip/hip_runtime.h>
@@ -468,8 +468,9 @@ __global__ void __launch_bounds__(256) update_kernel(double* __restrict__ L, int
 
 // The tiles of one pair of a level, `tiles` a side (a power of two), in such an order that the workgroups that share a CU, every 256th,
 // have much the same to do in all: the depth falls along the columns in step 1 and grows along the rows in step 2, and every other
-// 256 tiles go through them the other way (n = 4096, the last level: 319 and 235 us -> 188 and 205; 163 and 164 with tile_product as it is).
-__device__ __forceinline__ bool other_way(int tiles) { return tiles <= 256 && ((blockIdx.x + tiles * blockIdx.y) / 256 & 1); }
+// 256 tiles go through them the other way (n = 4096, the last level: 319 and 235 us -> 188 and 205; 163 and 164 with
+// tile_product as it is; the level before, two pairs of 256 tiles: 81 -> 51, counted through the pairs).
+__device__ __forceinline__ bool other_way(int tiles) { return tiles <= 256 && ((blockIdx.x + tiles * (blockIdx.y + tiles * blockIdx.z)) / 256 & 1); }
 
 // Level with diagonal blocks of `b` rows: pair p joins A = [2pb, 2pb + b) and B = [2pb + b, min(2pb + 2b, np)).
 // Step 1: T = C . A^-1 into `T` (at C's place);  C = L[B rows, A columns].
@@ -489,7 +490,7 @@ __global__ void __launch_bounds__(256) trtri_step1_kernel(const double* __restri
 __global__ void __launch_bounds__(256) trtri_step2_kernel(double* __restrict__ L, int np, int b, const double* __restrict__ T) {
   __shared__ Stage S;
   const int a0 = 2 * b * blockIdx.z, b0 = a0 + b, tiles = gridDim.x;
-  const int rows = max(256 / tiles, 1), y = other_way(tiles) ? (int)blockIdx.y + rows - 1 - 2 * ((int)blockIdx.y % rows) : (int)blockIdx.y;
+  const int rows = min(max(256 / tiles, 1), tiles), y = other_way(tiles) ? (int)blockIdx.y + rows - 1 - 2 * ((int)blockIdx.y % rows) : (int)blockIdx.y;
   const int i0 = b0 + y * NB, j0 = a0 + blockIdx.x * NB;             // tile: rows i0.., columns j0..
   if (i0 >= np) return;
   Tile acc = {};
