@@ -472,12 +472,12 @@ def run_encoder(torch, dev, with_cpu):
            "hessian_ms": round(t_h, 3), "hessian_TFLOPs": round(2.0 * n * n * d / t_h / 1e9, 2),
            "inverse_cholesky_ms": round(t_c, 3), "quantize_ms": round(t_q, 3),
            "weights_per_s": round(m * n / (t_q * 1e-3), 1), "outlier_rate": round(nnz / (m * n), 5),
-           "roofline": {"bound": "alu", "kernel": "sweep_kernel<16>", "unit": "Tops/s",
+           "roofline": {"bound": "alu", "kernel": "sweep16_kernel<16>", "unit": "Tops/s",
                         "achieved": round(ops / (t_q * 1e-3) / 1e12, 3), "peak": 39.3,
                         "frac": round(ops / (t_q * 1e-3) / 1e12 / 39.3, 4),
                         "note": "binary64 products and differences of the error feedback, never fused (m n^2 of them); "
                                 "peak = half the 78.6 TFLOP/s binary64 vector rate, which counts a fused multiply-add "
-                                f"as two; the launch has m / 64 = {m // 64} workgroups for 256 compute units"}}
+                                f"as two; the launch has m / 16 = {m // 16} workgroups for 256 compute units"}}
     if with_cpu:
         from oracle import spqr_encoder as enc
         rows = 64

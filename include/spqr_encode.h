@@ -104,7 +104,7 @@ typedef struct spqr_quantized_t {
   double* W_final;
 } spqr_quantized_t;
 
-/* Scratch of spqr_quantize in bytes: a column-major binary64 working copy of W. */
+/* Scratch of spqr_quantize in bytes: a binary64 working copy of W. */
 size_t spqr_quantize_workspace_bytes(int32_t m, int32_t n);
 
 /* Alg. 1 lines 4-20 (H^ic given).  W[m][n] row-major binary64 (read only), Hic[n][n] from

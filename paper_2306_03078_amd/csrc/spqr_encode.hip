@@ -466,7 +466,7 @@ int spqr_quantize(const double* W, const double* Hic, int32_t m, int32_t n, int3
   a.out = *out;
   // 16 rows per workgroup where a tile has no more, in place on W_final where the caller wants it; 64 rows, which the tiles of 32 and 64
   // rows need, take four to five times as long for four times the rows.  ms with 64 and with 16 rows a workgroup,
-  // beta2 = 16, 1 % outliers (the time of either is a staircase of rounds of 256 workgroups): 4096^2 17.7 and 3.6, 5120^2 25.4 and
+  // beta2 = 16, 1 % outliers (the time of either is a staircase of rounds of 256 workgroups): 4096^2 17.7 and 3.5, 5120^2 25.4 and
   // 10.2, 8192 x 4096 17.8 and 7.3, 11008 x 4096 18.0 and 10.8, 16384 x 2048 6.8 and 4.9, 32768 x 1024 5.4 and 4.0.  Only where blocks are
   // narrow and there are few columns behind them, so that a block's tests and chain are all there is, are four rounds of 16 rows (three
   // with beta1 = 4) no faster than one of 64: beta1 = 8, 16384 rows: 256 columns 0.49 and 0.54, 512 0.99 and 1.04, 1024 2.44 and 2.02;

@@ -34,8 +34,8 @@ namespace spqr {
 // kLongRow entries in the piece are shared out among the wavefronts, 64 lanes each.  One writer per sum, fixed orders
 // everywhere: results are deterministic.  Where the launch leaves CUs over, they are a workgroup's own (APART, plan_batch).
 //
-// What bounds it (17920 x 6656, 4-bit, Zipf outliers, 16 vectors, weights streamed, 41.5 us with the sums; 43.5 before the weights
-// were rounded in pairs): vector issue for a half of it (5.5 instructions per weight with the outliers) beside the stream of the
+// What bounds it (17920 x 6656, 4-bit, Zipf outliers, 16 vectors, weights streamed, 39 us with the sums; 43.5 before the weights
+// were rounded in pairs, 41.2 before the first workgroups of the CUs had more units, batch_shares): vector issue for a half of it (5.5 instructions per weight with the outliers) beside the stream of the
 // weights (14 us at the rate of a copy); the rest is the start (row bounds, XT) and the memory latency that two workgroups per CU
 // leave.  Without outliers 30 us.  Before (weights transposed through LDS quarter tile by quarter tile, outliers in a
 // kernel of their own that gathered from L2): 55 us; 8192 x 22016, 3-bit, 75 -> 63 us; 22016 x 8192 77 -> 66 us; three of

@@ -11,8 +11,8 @@
 //           applied to everything right of the next one, in tasks out of a queue.
 // Same operations in the same order on every weight as sweep_kernel, hence the same bits.
 //
-// 4096^2, blocks of 16, 1.3 % outliers: 3.65 ms (6.65 with the far columns after the chain instead of beside it, true divisions
-// everywhere and B1 + 1 fits a test).  Clocks of a workgroup, of 7.4 M: the front has 4.6 (a block of 16 columns: tests 4400, chain
+// 4096^2, blocks of 16, 1.3 % outliers: 3.5 ms (6.6 with the far columns after the chain instead of beside it, true divisions
+// everywhere and B1 + 1 fits a test).  Clocks of a workgroup, of 7.4 M when they were taken (3.65 ms): the front has 4.6 (a block of 16 columns: tests 4400, chain
 // with the second level 7300, the meetings and what wavefronts 2 and 3 are late 4300), the far columns alone after it 2.2, the end of
 // a super-block 0.4.  Bound: binary64 issue.  The products and differences of the feedback are 3.6 M clocks of a SIMD at 3.7 ns a pair
 // (two wavefronts, 256 CUs), the tests 0.9, chain or near columns 1.1: three quarters of the time; what is left is the chain
