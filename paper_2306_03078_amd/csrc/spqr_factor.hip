@@ -17,8 +17,8 @@
 // 8-byte half of an LDS read per lane feeds two instructions of 64 clocks.  n = d = 4096, Hessian and factor together 4.77 -> 3.28 ms:
 // Hessian 1.48 -> 1.19 (after idle 1.6 -> 1.3: no vector instructions in the inner loop, see tile_product); block columns 33 -> 22 us on
 // average (the diagonal block's chain, potrf_diag); the triangular inverse 0.92 -> 0.55 (the same loop, and tiles dealt so that CUs have
-// equal work).  What is left: the chain of 64 diagonal blocks of 9 us, the product before each and panels of 5, and the chain's
-// neighbours in the early block columns (update_kernel).
+// equal work).  What is left: a block column's two launches, of 12 us (the 64 dependent steps 4 of them, the product before them 3, the blocks
+// between the panels 3) and of 5 (start, end and one product), and in the early ones the tiles beside them, up to 30 (update_kernel).
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
