@@ -5,7 +5,7 @@
 // so A^-1 = R^-T R^-1 and U = R^-1 = J L^-1 J: one Cholesky factorisation and one triangular inverse, both in the
 // reversed index space, no product of two triangular matrices and no second factorisation.
 //
-//   init      L <- lower triangle of J A J, padded with an identity to a multiple of 64
+//   init      L <- lower triangle of J A J, padded with an identity to a multiple of 64 (nothing right of the diagonal blocks)
 //   per block column k (64 wide): potrf of the diagonal block and its inverse (one workgroup, in LDS);
 //             the panel below times that inverse (transposed); the trailing lower triangle minus panel x panel^T
 //   trtri     X = L^-1 by doubling: with L = [[A, 0], [C, B]], L^-1 = [[A^-1, 0], [-B^-1 C A^-1, B^-1]].  Level s joins
@@ -14,7 +14,7 @@
 //   final     U[i][j] = X[n-1-i][n-1-j] for j >= i
 //
 // Every tile product runs on the matrix cores (v_mfma_f64_16x16x4_f64), at the vector ALU's rate, but an operand of one
-// 8-byte half of an LDS read per lane feeds two instructions of 64 clocks.  n = d = 4096, Hessian and factor together 4.77 -> 3.28 ms:
+// 8-byte half of an LDS read per lane feeds two instructions of 64 clocks.  n = d = 4096, Hessian and factor together 4.77 -> 3.26 ms:
 // Hessian 1.48 -> 1.19 (after idle 1.6 -> 1.3: no vector instructions in the inner loop, see tile_product); block columns 33 -> 22 us on
 // average (the diagonal block's chain, potrf_diag); the triangular inverse 0.92 -> 0.55 (the same loop, and tiles dealt so that CUs have
 // equal work).  What is left: a block column's two launches, of 12 us (the 64 dependent steps 4 of them, the product before them 3, the blocks
@@ -237,17 +237,19 @@ __global__ void __launch_bounds__(256) hessian_kernel(const double* __restrict__
   });
 }
 
+// A row a workgroup up to the end of its diagonal block: nobody reads the blocks right of that (n = 4096: 46 us for every
+// element of the square, 27 as it is).
 __global__ void __launch_bounds__(256) init_reversed_kernel(const double* __restrict__ H, int n, int np, double lambda,
                                                            double* __restrict__ L) {
-  const size_t idx = (size_t)blockIdx.x * 256 + threadIdx.x;
-  if (idx >= (size_t)np * np) return;
-  const int a = (int)(idx / np), b = (int)(idx % np);
-  double v = 0.0;
-  if (b <= a) {
-    if (a < n) v = H[(size_t)(n - 1 - a) * n + (n - 1 - b)] + (a == b ? lambda : 0.0);   // lower triangle of J A J
-    else v = a == b ? 1.0 : 0.0;
+  const int a = blockIdx.x, end = (a | (NB - 1)) + 1;
+  for (int b = threadIdx.x; b < end; b += 256) {
+    double v = 0.0;
+    if (b <= a) {
+      if (a < n) v = H[(size_t)(n - 1 - a) * n + (n - 1 - b)] + (a == b ? lambda : 0.0);   // lower triangle of J A J
+      else v = a == b ? 1.0 : 0.0;
+    }
+    L[(size_t)a * np + b] = v;
   }
-  L[idx] = v;
 }
 
 // 1 / sqrt(x) to about a unit in the last place (x <= 0: NaN).  The hardware's estimate is good to 2^-24 or better; with
@@ -542,8 +544,7 @@ int spqr_inverse_cholesky(const double* H, int32_t n, double lambda, double* Hic
   const int np = (n + NB - 1) / NB * NB, nb = np / NB;
   double* L = static_cast<double*>(workspace);
   double* X = L + (size_t)np * np;
-  const unsigned cells = (unsigned)(((size_t)np * np + 255) / 256);
-  hipLaunchKernelGGL(init_reversed_kernel, dim3(cells), dim3(256), 0, st, H, n, np, lambda, L);
+  hipLaunchKernelGGL(init_reversed_kernel, dim3(np), dim3(256), 0, st, H, n, np, lambda, L);
   hipLaunchKernelGGL(potrf_first_kernel, dim3(1), dim3(256), 0, st, L, np);
   for (int kb = 0; kb + 1 < nb; ++kb) {
     const int rest = nb - kb - 1;

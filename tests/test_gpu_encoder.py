@@ -226,7 +226,8 @@ def test_hessian_and_factor_at_the_edges_of_tiles_and_squares(n, d):
 
 
 # 3, 4, 5 and 6 block columns (a column takes three panels at a time, fewer at the left edge; the block behind the next takes its own
-# early, or is not there), and a second pair of 16 blocks a side whose lower half is short (its tiles are dealt the other way round)
+# early, or is not there), and a second pair of 16 blocks a side whose lower half is short (its tiles are dealt the other way round);
+# and the blocks of the scratch that are never written are never read: all NaN before, the same factor
 @pytest.mark.parametrize("n", [130, 193, 320, 321, 3150])
 def test_inverse_cholesky_panels_at_a_time(n):
     import torch
@@ -238,6 +239,8 @@ def test_inverse_cholesky_panels_at_a_time(n):
     lam = float(H.diagonal().mean()) * 0.1
     U = E.spqr_inverse_cholesky(H, lam)
     assert bool((U.tril(-1) == 0).all()) and bool((U.diagonal() > 0).all())
+    scratch = torch.full((int(E._lib().spqr_inverse_cholesky_workspace_bytes(n)),), 255, dtype=torch.uint8, device="cuda")
+    assert torch.equal(E.spqr_inverse_cholesky(H, lam, workspace=scratch), U)
     A = H + lam * torch.eye(n, dtype=torch.float64, device="cuda")
     cond = float(torch.linalg.norm(A) / lam)
     assert float((U.T @ U @ A - torch.eye(n, dtype=torch.float64, device="cuda")).abs().max()) <= 4 * n * cond * 2.0 ** -53
