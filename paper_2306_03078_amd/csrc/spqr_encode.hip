@@ -99,7 +99,8 @@ __device__ __forceinline__ void second_level(double v, int beta2, double levels,
 }
 struct SweepArgs {
   const double* U;       // H^ic [n][n]
-  double* Wt;            // working copy, column-major: Wt[j * m + i]
+  double* Wt;            // working copy, column-major: Wt[j * m + i] (row-major in sweep16_kernel)
+  const double* W;       // as given, row-major
   int m, n, beta2;
   double w_top, s_top, z_top;   // 2^bits - 1
   double tau;
@@ -335,10 +336,6 @@ __global__ void __launch_bounds__(64 * kWaves) sweep_kernel(SweepArgs a) {
 
 namespace spqr_enc {
 
-__global__ void __launch_bounds__(256) copy_kernel(const double* __restrict__ src, double* __restrict__ dst, size_t count) {
-  for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < count; i += (size_t)gridDim.x * 256) dst[i] = src[i];
-}
-
 // W[m][n] row-major <-> Wt[n][m] column-major, through a 32 x 32 LDS tile.
 __global__ void __launch_bounds__(256) transpose_kernel(const double* __restrict__ src, double* __restrict__ dst,
                                                        int rows, int cols) {   // src[rows][cols] -> dst[cols][rows]
@@ -459,7 +456,7 @@ int spqr_quantize(const double* W, const double* Hic, int32_t m, int32_t n, int3
     return SPQR_ERR_ALIGN;
   hipStream_t st = static_cast<hipStream_t>(stream);
   SweepArgs a;
-  a.U = Hic; a.Wt = static_cast<double*>(workspace);
+  a.U = Hic; a.Wt = static_cast<double*>(workspace); a.W = W;
   a.m = m; a.n = n; a.beta2 = beta2;
   a.w_top = (double)((1 << w_bits) - 1); a.s_top = (double)((1 << s_bits) - 1); a.z_top = (double)((1 << z_bits) - 1);
   a.tau = tau;
@@ -475,7 +472,6 @@ int spqr_quantize(const double* W, const double* Hic, int32_t m, int32_t n, int3
   const bool narrow = beta1 <= 8 && n <= 4096 / beta1 && rounds16 > (beta1 == 4 ? 2 : 3) * rounds64;
   if (beta2 <= kRows16 && !narrow) {
     if (out->W_final) a.Wt = out->W_final;
-    if (a.Wt != W) hipLaunchKernelGGL(copy_kernel, dim3(2048), dim3(256), 0, st, W, a.Wt, (size_t)m * n);
     hipError_t e = hipSuccess;
     switch (beta1) {
       case 4: e = launch_sweep16<4>(m, st, a); break;

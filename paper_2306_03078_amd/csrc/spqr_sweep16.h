@@ -144,13 +144,13 @@ __device__ __forceinline__ void meet(uint32_t* met, uint32_t* target, int lane) 
 }
 
 // ---------------------------------------------------------------------------
-// Far: line 16 for C runs of 64 columns from k0 on, ROWS of the workgroup's rows from r0 on: W[:, k] -= E[:, j] * H^ic[ub + j, k] for
+// Far: line 16 for C runs of 64 columns from k0 on, ROWS of the workgroup's rows from r0 on: W[:, k] = src[:, k] - E[:, j] * H^ic[ub + j, k] for
 // the kSuper16 columns j of a super-block, in order.  A lane holds ROWS rows of C columns; the errors are LDS broadcasts (for 16
 // rows eight reads of 16 bytes per column j whatever C is: with one column a lane they are what the pass waits for, two are even with
 // the arithmetic), three reads ahead; H^ic comes straight from memory, four j ahead.
 // ---------------------------------------------------------------------------
 template <int C, int ROWS>
-__device__ __forceinline__ void far_feedback(double* __restrict__ W, const double* __restrict__ U, int m, int n, int row0, int rows, int lane,
+__device__ __forceinline__ void far_feedback(const double* src, double* W, const double* __restrict__ U, int m, int n, int row0, int rows, int lane,
                                              int ub, int k0, int r0, const double (*esb)[kRows16]) {
   constexpr int PF = 4;                                  // (kSuper16 is a multiple of 2 PF)
   const int off = (k0 + lane) * 8, pitch = n * 8;        // columns behind the last one: the next row's, or zeros behind the matrix
@@ -166,7 +166,7 @@ __device__ __forceinline__ void far_feedback(double* __restrict__ W, const doubl
   };
   fetch(0, 0);
   const size_t w_first = (size_t)row0 * n;
-  const auto w_rows = buffer_of(W + w_first, w_end - w_first);
+  const auto w_rows = buffer_of(src + w_first, w_end - w_first);
 #pragma unroll
   for (int r = 0; r < ROWS; ++r)
 #pragma unroll
@@ -209,13 +209,13 @@ __device__ __forceinline__ void far_feedback(double* __restrict__ W, const doubl
 }
 
 template <int ROWS>
-__device__ __forceinline__ void far_task(int runs, double* __restrict__ W, const double* __restrict__ U, int m, int n, int row0, int rows, int lane,
-                                         int ub, int k0, int r0, const double (*esb)[kRows16]) {
+__device__ __forceinline__ void far_task(int runs, const double* src, double* W, const double* __restrict__ U, int m, int n, int row0, int rows,
+                                         int lane, int ub, int k0, int r0, const double (*esb)[kRows16]) {
   switch (runs) {
-    case 1: far_feedback<1, ROWS>(W, U, m, n, row0, rows, lane, ub, k0, r0, esb); break;
-    case 2: far_feedback<2, ROWS>(W, U, m, n, row0, rows, lane, ub, k0, r0, esb); break;
-    case 3: far_feedback<3, ROWS>(W, U, m, n, row0, rows, lane, ub, k0, r0, esb); break;
-    default: far_feedback<4, ROWS>(W, U, m, n, row0, rows, lane, ub, k0, r0, esb); break;
+    case 1: far_feedback<1, ROWS>(src, W, U, m, n, row0, rows, lane, ub, k0, r0, esb); break;
+    case 2: far_feedback<2, ROWS>(src, W, U, m, n, row0, rows, lane, ub, k0, r0, esb); break;
+    case 3: far_feedback<3, ROWS>(src, W, U, m, n, row0, rows, lane, ub, k0, r0, esb); break;
+    default: far_feedback<4, ROWS>(src, W, U, m, n, row0, rows, lane, ub, k0, r0, esb); break;
   }
 }
 
@@ -628,7 +628,7 @@ __device__ __forceinline__ void put_corner(Sweep16Lds<B1>& S, const CornerRows<R
 
 // The super-block's weights as the sweep leaves them, 8 rows for each of two wavefronts.
 template <int B1>
-__device__ __forceinline__ void store_final(const Sweep16Lds<B1>& S, double* __restrict__ W, int n, int sb, int sbw, int wave, int row0, int rows, int lane) {
+__device__ __forceinline__ void store_final(const Sweep16Lds<B1>& S, double* W, int n, int sb, int sbw, int wave, int row0, int rows, int lane) {
   for (int r = 8 * wave; r < min(8 * wave + 8, rows); ++r)
     for (int k = lane; k < sbw; k += 64) W[(size_t)(row0 + r) * n + sb + k] = S.wsb[k][r];
 }
@@ -640,7 +640,9 @@ __global__ void __launch_bounds__(64 * kWaves16, 2) sweep16_kernel(SweepArgs a) 
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int n = a.n, row0 = blockIdx.x * kRows16, rows = min(kRows16, a.m - row0);   // a tile is inside or outside
   const double* __restrict__ U = a.U;
-  double* __restrict__ W = a.Wt;                         // row-major here
+  // Row-major here, written as the super-blocks and their far columns are through; what no far pass has been over yet is read where
+  // the caller left it (a copy of 4096^2 before the sweep took 41 us, of 11008 x 4096 118).
+  double* W = a.Wt;
   const Divisor levels = divisor_of(a.w_top);
   uint32_t target = 0;
 
@@ -649,7 +651,7 @@ __global__ void __launch_bounds__(64 * kWaves16, 2) sweep16_kernel(SweepArgs a) 
   if (tid == 0) S.met = S.ready = 0;
   for (int r = 2 * wave; r < 2 * wave + 2; ++r)
 #pragma unroll
-    for (int k = lane; k < kSuper16; k += 64) S.wsb[k][r] = W[(size_t)(row0 + min(r, rows - 1)) * n + min(k, n - 1)];
+    for (int k = lane; k < kSuper16; k += 64) S.wsb[k][r] = a.W[(size_t)(row0 + min(r, rows - 1)) * n + min(k, n - 1)];
   {
     bool ok = true;
     if (tid < kSuper16) {
@@ -708,7 +710,7 @@ __global__ void __launch_bounds__(64 * kWaves16, 2) sweep16_kernel(SweepArgs a) 
             if (b == start) {                            // the far wavefronts have been over these columns
               if (sb > 0) wait_for(&S.ready, 4 * (uint32_t)(sb / kSuper16));
               const size_t first = (size_t)row0 * n;
-              const Buffer w_rows = buffer_of(W + first, (size_t)a.m * n - first);
+              const Buffer w_rows = buffer_of((sb > 0 ? W : a.W) + first, (size_t)a.m * n - first);
 #pragma unroll
               for (int r = 0; r < kRows16; ++r) N.cur[r] = buffer_f64(w_rows, noff, min(r, rows - 1) * n * 8);
             }
@@ -735,7 +737,7 @@ __global__ void __launch_bounds__(64 * kWaves16, 2) sweep16_kernel(SweepArgs a) 
       __builtin_amdgcn_s_setprio(0);
     } else if (sb > 0 && next < n) {
       // the errors of the super-block before, first to the columns the near wavefronts wait for, 4 rows each
-      far_feedback<2, 4>(W, U, a.m, n, row0, rows, lane, sb - kSuper16, next, 4 * (wave - kFront16), S.esb[p ^ 1]);
+      far_feedback<2, 4>(sb == kSuper16 ? a.W : W, W, U, a.m, n, row0, rows, lane, sb - kSuper16, next, 4 * (wave - kFront16), S.esb[p ^ 1]);
       __builtin_amdgcn_s_waitcnt(0x0F70);                // vmcnt(0): the stores are done
       __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
       if (lane == 0) __hip_atomic_fetch_add(&S.ready, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
@@ -745,6 +747,7 @@ __global__ void __launch_bounds__(64 * kWaves16, 2) sweep16_kernel(SweepArgs a) 
     const int from = next + kSuper16, runs = sb > 0 && from < n ? (n - from + 63) / 64 : 0;
     const int fine = min(runs, 6), medium = min(runs - fine, 8), wide = runs - fine - medium;
     const int wides = (wide + 3) / 4, mediums = (medium + 3) / 4 * 2, tasks = wides + mediums + (fine + 1) / 2 * 2;
+    const double* src = sb == kSuper16 ? a.W : W;
     while (runs > 0) {
       uint32_t got = 0;
       if (lane == 0) got = __hip_atomic_fetch_add(&S.task[p], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
@@ -752,12 +755,12 @@ __global__ void __launch_bounds__(64 * kWaves16, 2) sweep16_kernel(SweepArgs a) 
       if (task >= tasks) break;                          // wave-uniform; the count only grows
       const int n = fresh_s(a.n), row0 = fresh_s(blockIdx.x * kRows16), rows = fresh_s(min(kRows16, a.m - row0)), lane = fresh_v(tid & 63);
       if (task < wides) {
-        far_task<16>(min(4, wide - 4 * task), W, U, a.m, n, row0, rows, lane, sb - kSuper16, from + 256 * task, 0, S.esb[p ^ 1]);
+        far_task<16>(min(4, wide - 4 * task), src, W, U, a.m, n, row0, rows, lane, sb - kSuper16, from + 256 * task, 0, S.esb[p ^ 1]);
       } else {
         const bool last = task >= wides + mediums;
         const int t = last ? task - wides - mediums : task - wides, first = last ? wide + medium + t / 2 * 2 : wide + t / 2 * 4;
-        far_task<8>(last ? min(2, runs - first) : min(4, wide + medium - first), W, U, a.m, n, row0, rows, lane, sb - kSuper16, from + 64 * first,
-                    8 * (t & 1), S.esb[p ^ 1]);
+        far_task<8>(last ? min(2, runs - first) : min(4, wide + medium - first), src, W, U, a.m, n, row0, rows, lane, sb - kSuper16,
+                    from + 64 * first, 8 * (t & 1), S.esb[p ^ 1]);
       }
     }
     __syncthreads();
