@@ -54,7 +54,8 @@ __device__ __forceinline__ bool scale_of_range(double lo, double hi, const Divis
 __device__ __forceinline__ int fresh_s(int v) { asm volatile("" : "+s"(v)); return v; }
 __device__ __forceinline__ int fresh_v(int v) { asm volatile("" : "+v"(v)); return v; }
 
-// Doubles by a uniform base and row and a lane's offset in bytes (no addresses in vector registers); reads behind the end give zeros.
+// Doubles by a uniform base and row and a lane's offset in bytes (no addresses in vector registers).  The row's offset is not part of a
+// buffer's bounds check: rows and columns that may lie behind the last ones are held back by the callers.
 typedef __amdgpu_buffer_rsrc_t Buffer;
 __device__ __forceinline__ Buffer buffer_of(const double* base, size_t count) {
   const size_t bytes = count * sizeof(double);
@@ -150,12 +151,12 @@ __device__ __forceinline__ void meet(uint32_t* met, uint32_t* target, int lane) 
 // the arithmetic), three reads ahead; H^ic comes straight from memory, four j ahead.
 // ---------------------------------------------------------------------------
 template <int C, int ROWS>
-__device__ __forceinline__ void far_feedback(const double* src, double* W, const double* __restrict__ U, int m, int n, int row0, int rows, int lane,
+__device__ __forceinline__ void far_feedback(const double* src, double* W, const double* __restrict__ U, int n, int row0, int rows, int lane,
                                              int ub, int k0, int r0, const double (*esb)[kRows16]) {
   constexpr int PF = 4;                                  // (kSuper16 is a multiple of 2 PF)
-  const int off = (k0 + lane) * 8, pitch = n * 8;        // columns behind the last one: the next row's, or zeros behind the matrix
+  const int off = (k0 + lane) * 8, pitch = n * 8;        // columns behind the last one: the next row's of H^ic (there is one), the last one's of W
   double cur[C][ROWS], u[2][PF][C];
-  const size_t u_end = (size_t)n * n, w_end = (size_t)m * n;
+  const size_t u_end = (size_t)n * n;
   auto fetch = [&](int buf, int j) {                     // rows ub + j .. + PF - 1 of H^ic
     const size_t first = (size_t)(ub + j) * n;
     const auto rows_j = buffer_of(U + first, u_end - first);
@@ -166,11 +167,11 @@ __device__ __forceinline__ void far_feedback(const double* src, double* W, const
   };
   fetch(0, 0);
   const size_t w_first = (size_t)row0 * n;
-  const auto w_rows = buffer_of(src + w_first, w_end - w_first);
+  const auto w_rows = buffer_of(src + w_first, (size_t)rows * n);
 #pragma unroll
   for (int r = 0; r < ROWS; ++r)
 #pragma unroll
-    for (int c = 0; c < C; ++c) cur[c][r] = buffer_f64(w_rows, off + 512 * c, min(r0 + r, rows - 1) * pitch);
+    for (int c = 0; c < C; ++c) cur[c][r] = buffer_f64(w_rows, min(off + 512 * c, pitch - 8), min(r0 + r, rows - 1) * pitch);
   constexpr int AHEAD = 3, PAIRS = ROWS / 2;             // the last ones read behind the errors, into what follows them in LDS
   const double* pe = &esb[0][r0];
   auto pair = [&](int t) { return *reinterpret_cast<const f64x2*>(pe + t / PAIRS * kRows16 + t % PAIRS * 2); };
@@ -197,7 +198,7 @@ __device__ __forceinline__ void far_feedback(const double* src, double* W, const
     }
   }
   rows = fresh_s(rows);
-  const auto w_out = buffer_of(W + w_first, (size_t)(rows - 1) * n + n);
+  const auto w_out = buffer_of(W + w_first, (size_t)rows * n);
 #pragma unroll
   for (int c = 0; c < C; ++c) {
     if (k0 + 64 * c + lane < n) {
@@ -209,13 +210,13 @@ __device__ __forceinline__ void far_feedback(const double* src, double* W, const
 }
 
 template <int ROWS>
-__device__ __forceinline__ void far_task(int runs, const double* src, double* W, const double* __restrict__ U, int m, int n, int row0, int rows,
+__device__ __forceinline__ void far_task(int runs, const double* src, double* W, const double* __restrict__ U, int n, int row0, int rows,
                                          int lane, int ub, int k0, int r0, const double (*esb)[kRows16]) {
   switch (runs) {
-    case 1: far_feedback<1, ROWS>(src, W, U, m, n, row0, rows, lane, ub, k0, r0, esb); break;
-    case 2: far_feedback<2, ROWS>(src, W, U, m, n, row0, rows, lane, ub, k0, r0, esb); break;
-    case 3: far_feedback<3, ROWS>(src, W, U, m, n, row0, rows, lane, ub, k0, r0, esb); break;
-    default: far_feedback<4, ROWS>(src, W, U, m, n, row0, rows, lane, ub, k0, r0, esb); break;
+    case 1: far_feedback<1, ROWS>(src, W, U, n, row0, rows, lane, ub, k0, r0, esb); break;
+    case 2: far_feedback<2, ROWS>(src, W, U, n, row0, rows, lane, ub, k0, r0, esb); break;
+    case 3: far_feedback<3, ROWS>(src, W, U, n, row0, rows, lane, ub, k0, r0, esb); break;
+    default: far_feedback<4, ROWS>(src, W, U, n, row0, rows, lane, ub, k0, r0, esb); break;
   }
 }
 
@@ -603,16 +604,27 @@ __device__ __forceinline__ void near_steps(Near& N, const double* __restrict__ U
   }
 }
 
-// ROWS rows j0, j0 + step, .. of the corner of H^ic at column `at`, on their way into LDS.
+// The next super-block's columns of the weights, as the passes before left them.
+__device__ __forceinline__ void near_weights(Near& N, const double* src, int n, int row0, int rows, int off) {
+  const Buffer b = buffer_of(src + (size_t)row0 * n, (size_t)rows * n);
+  off = min(off, (n - 1) * 8);
+#pragma unroll
+  for (int r = 0; r < kRows16; ++r) N.cur[r] = buffer_f64(b, off, min(r, rows - 1) * n * 8);
+}
+
+// ROWS rows j0, j0 + step, .. of the corner of H^ic at column `at`, on their way into LDS (behind the last row and column: the last
+// ones, never used).
 template <int ROWS> struct CornerRows { double v[ROWS][2]; };
 template <int ROWS>
 __device__ __forceinline__ void fetch_corner(CornerRows<ROWS>& c, const double* __restrict__ U, int n, int at, int j0, int step, int lane) {
-  const size_t first = (size_t)(at + j0) * n;            // (rows and columns behind the last ones: what is there, or zeros; never used)
-  const Buffer b = buffer_of(U + first, (size_t)n * n > first ? (size_t)n * n - first : 0);
+  const int left = n - 1 - at, first = at + min(j0, left);
+  const Buffer b = buffer_of(U + (size_t)first * n, (size_t)(n - first) * n);
+  const int col = at + min(lane, left), col64 = at + min(64 + lane, left);
 #pragma unroll
   for (int t = 0; t < ROWS; ++t) {
-    c.v[t][0] = buffer_f64(b, (at + lane) * 8, step * t * n * 8);
-    c.v[t][1] = buffer_f64(b, (at + lane) * 8 + 512, step * t * n * 8);
+    const int row_off = (min(at + j0 + step * t, n - 1) - first) * n * 8;
+    c.v[t][0] = buffer_f64(b, col * 8, row_off);
+    c.v[t][1] = buffer_f64(b, col64 * 8, row_off);
   }
 }
 template <int B1, int ROWS>
@@ -703,16 +715,13 @@ __global__ void __launch_bounds__(64 * kWaves16, 2) sweep16_kernel(SweepArgs a) 
           block_tests<B1>(S, a, levels, fresh_s(b * B1), b & 1, p, wave, fresh_v(lane), S.esb[p]);
           meet(&S.met, &target, lane);
           CornerRows<B1 / 2> c = {};
-          if (near && b >= 2) fetch_corner(c, U, n, next, (b - 2) * B1 + half, 2, lane);
+          if (near && b >= 2) fetch_corner(c, U, n, next, (b - 2) * B1 + half, 2, fresh_v(lane));
           if (b > 0 && feedback_threads(sbw - (b + 1) * B1) > 64) block_feedback<B1>(S, fresh_s(b * B1) - B1, sbw, fresh_v(tid) - 64, 64 * 3, S.esb[p]);
           if (near) {                                    // (128 columns: at least four blocks)
             const int start = blocks / 4;
             if (b == start) {                            // the far wavefronts have been over these columns
               if (sb > 0) wait_for(&S.ready, 4 * (uint32_t)(sb / kSuper16));
-              const size_t first = (size_t)row0 * n;
-              const Buffer w_rows = buffer_of((sb > 0 ? W : a.W) + first, (size_t)a.m * n - first);
-#pragma unroll
-              for (int r = 0; r < kRows16; ++r) N.cur[r] = buffer_f64(w_rows, noff, min(r, rows - 1) * n * 8);
+              near_weights(N, sb > 0 ? W : a.W, n, row0, rows, fresh_v(noff));
             }
             if (b >= start) near_steps(N, U, n, sb, noff, min(b * B1, kSuper16 * (b + 1 - start) / (blocks - start)) & -Near::PF, S.esb[p]);
             if (b >= 2) put_corner<B1>(S, c, (b - 2) * B1 + half, 2, lane);
@@ -727,7 +736,7 @@ __global__ void __launch_bounds__(64 * kWaves16, 2) sweep16_kernel(SweepArgs a) 
 #pragma unroll 1
           for (int j = kSuper16 - 2 * B1 + half; j < kSuper16; j += B1 < 8 ? 2 * B1 : 16) {
             CornerRows<B1 < 8 ? B1 : 8> c;
-            fetch_corner(c, U, n, next, j, 2, lane);
+            fetch_corner(c, U, n, next, j, 2, fresh_v(lane));
             put_corner<B1>(S, c, j, 2, lane);
           }
           S.diag[ncol] = f64x2{diag.hi, diag.lo};
@@ -737,7 +746,7 @@ __global__ void __launch_bounds__(64 * kWaves16, 2) sweep16_kernel(SweepArgs a) 
       __builtin_amdgcn_s_setprio(0);
     } else if (sb > 0 && next < n) {
       // the errors of the super-block before, first to the columns the near wavefronts wait for, 4 rows each
-      far_feedback<2, 4>(sb == kSuper16 ? a.W : W, W, U, a.m, n, row0, rows, lane, sb - kSuper16, next, 4 * (wave - kFront16), S.esb[p ^ 1]);
+      far_feedback<2, 4>(sb == kSuper16 ? a.W : W, W, U, n, row0, rows, lane, sb - kSuper16, next, 4 * (wave - kFront16), S.esb[p ^ 1]);
       __builtin_amdgcn_s_waitcnt(0x0F70);                // vmcnt(0): the stores are done
       __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
       if (lane == 0) __hip_atomic_fetch_add(&S.ready, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
@@ -755,11 +764,11 @@ __global__ void __launch_bounds__(64 * kWaves16, 2) sweep16_kernel(SweepArgs a) 
       if (task >= tasks) break;                          // wave-uniform; the count only grows
       const int n = fresh_s(a.n), row0 = fresh_s(blockIdx.x * kRows16), rows = fresh_s(min(kRows16, a.m - row0)), lane = fresh_v(tid & 63);
       if (task < wides) {
-        far_task<16>(min(4, wide - 4 * task), src, W, U, a.m, n, row0, rows, lane, sb - kSuper16, from + 256 * task, 0, S.esb[p ^ 1]);
+        far_task<16>(min(4, wide - 4 * task), src, W, U, n, row0, rows, lane, sb - kSuper16, from + 256 * task, 0, S.esb[p ^ 1]);
       } else {
         const bool last = task >= wides + mediums;
         const int t = last ? task - wides - mediums : task - wides, first = last ? wide + medium + t / 2 * 2 : wide + t / 2 * 4;
-        far_task<8>(last ? min(2, runs - first) : min(4, wide + medium - first), src, W, U, a.m, n, row0, rows, lane, sb - kSuper16,
+        far_task<8>(last ? min(2, runs - first) : min(4, wide + medium - first), src, W, U, n, row0, rows, lane, sb - kSuper16,
                     from + 64 * first, 8 * (t & 1), S.esb[p ^ 1]);
       }
     }
