@@ -35,6 +35,7 @@ constexpr int KC = 16;                       // depth of one LDS stage of a tile
 constexpr int LP = KC + 4;
 
 typedef double f64x2 __attribute__((ext_vector_type(2)));
+typedef double f64x2_8 __attribute__((ext_vector_type(2), aligned(8)));
 typedef double f64x4 __attribute__((ext_vector_type(4)));
 
 // D += A B for one 16 x 16 block: lane l gives A[l % 16][l / 16] and B[l / 16][l % 16], D[r] is row l / 16 + 4 r, column l % 16.
@@ -72,6 +73,21 @@ struct ByRows {                              // k innermost in memory: consecuti
     for (int q = 0; q < 2; ++q) v[q] = __builtin_bit_cast(f64x2, __builtin_amdgcn_raw_buffer_load_b128(b, off[q], 0, 0));
   }
   __device__ __forceinline__ void advance(int stages) { base += stages * KC; }
+};
+struct ByFarRows : ByRows {                  // ... of rows that a 32-bit offset does not reach: a pointer each (two additions a stage and row more)
+  const f64x2_8* at[2];
+  __device__ __forceinline__ ByFarRows(const double* first, int pitch, int last) : ByRows(first, 0) {      // rows behind `last`: the last
+#pragma unroll
+    for (int q = 0; q < 2; ++q) at[q] = reinterpret_cast<const f64x2_8*>(first + (size_t)min(row(q), last) * pitch + k(q));
+  }
+  __device__ __forceinline__ void fetch(f64x2 (&v)[2]) const {
+#pragma unroll
+    for (int q = 0; q < 2; ++q) v[q] = *at[q];
+  }
+  __device__ __forceinline__ void advance(int stages) {
+#pragma unroll
+    for (int q = 0; q < 2; ++q) at[q] += stages * (KC / 2);
+  }
 };
 struct ByColumns {                           // the rows innermost: consecutive threads fetch consecutive rows
   const double* base;
@@ -192,7 +208,10 @@ __device__ __forceinline__ void upper_cell(int at, int side, int* row, int* col)
 // H = 2 X X^T, tiles on and above the diagonal, mirrored.  Squares of SQ x SQ tiles, a run of them for each of the 8 XCDs
 // (workgroups go to the XCDs in turn): the tiles that run side by side on an XCD share rows of X in its L2.
 constexpr int SQ = 2;
-constexpr int kMostDepth = 1 << 22;          // 64 rows of it are within reach of a 32-bit offset
+// 64 rows of it are within reach of a 32-bit offset.  Deeper, n = 128, d = 2^22 + 16: 259 ms with pointers checked element by element, 355
+// stage after stage without overlap, 194 as it is (197 with offsets, d = 2^22); n = 1024: 268, 401, 212.
+constexpr int kMostDepth = 1 << 22;
+template <bool FAR>
 __global__ void __launch_bounds__(256) hessian_kernel(const double* __restrict__ X, int n, int d, double* __restrict__ H, int squares, int run) {
   __shared__ Stage S;
   const int xcd = blockIdx.x % 8, at = blockIdx.x / 8, square = xcd * run + at / (SQ * SQ), side = (n + SQ * NB - 1) / (SQ * NB);
@@ -204,12 +223,16 @@ __global__ void __launch_bounds__(256) hessian_kernel(const double* __restrict__
   Tile acc = {};
   // (rows behind the last: the last, their sums are not written)
   auto rows = [&](int first) {
-    ByRows o(X + (size_t)first * d, d);
+    const double* x = X + (size_t)first * d;
+    if constexpr (FAR) return ByFarRows(x, d, n - 1 - first);
+    else {
+      ByRows o(x, d);
 #pragma unroll
-    for (int q = 0; q < 2; ++q) o.off[q] = ((uint32_t)min(ByRows::row(q), n - 1 - first) * (uint32_t)d + (uint32_t)ByRows::k(q)) * 8u;
-    return o;
+      for (int q = 0; q < 2; ++q) o.off[q] = ((uint32_t)min(ByRows::row(q), n - 1 - first) * (uint32_t)d + (uint32_t)ByRows::k(q)) * 8u;
+      return o;
+    }
   };
-  const int stages = d <= kMostDepth ? d / KC : 0;
+  const int stages = d / KC;
   tile_product(acc, rows(i0), rows(j0), stages, S);
   for (int64_t k0 = (int64_t)stages * KC; k0 < d; k0 += KC) {        // the rest of the depth, zeros behind it
     f64x2 pa[2], pb[2];
@@ -520,7 +543,7 @@ int spqr_hessian(const double* X, int32_t n, int32_t d, double* H, void* stream)
   if (reinterpret_cast<uintptr_t>(X) % 8 != 0 || reinterpret_cast<uintptr_t>(H) % 8 != 0) return SPQR_ERR_ALIGN;
   hipStream_t st = static_cast<hipStream_t>(stream);
   const int side = (n + SQ * NB - 1) / (SQ * NB), squares = side * (side + 1) / 2, run = (squares + 7) / 8;
-  hipLaunchKernelGGL(hessian_kernel, dim3(8 * run * SQ * SQ), dim3(256), 0, st, X, n, d, H, squares, run);
+  hipLaunchKernelGGL(d <= kMostDepth ? hessian_kernel<false> : hessian_kernel<true>, dim3(8 * run * SQ * SQ), dim3(256), 0, st, X, n, d, H, squares, run);
   return hipGetLastError() == hipSuccess ? SPQR_OK : SPQR_ERR_HIP;
 }
 

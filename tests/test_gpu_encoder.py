@@ -204,7 +204,7 @@ def test_sweep_far_columns_bit_exact(E, b1, m, n):
 
 
 # one tile, ragged ones, a square of tiles and one more, several squares per XCD; odd depths (a rest of a stage), one beyond 32-bit offsets
-@pytest.mark.parametrize("n,d", [(1, 1), (63, 5), (65, 129), (128, 64), (130, 33), (449, 1000), (1157, 17), (2, (1 << 22) + 17)])
+@pytest.mark.parametrize("n,d", [(1, 1), (63, 5), (65, 129), (128, 64), (130, 33), (449, 1000), (1157, 17), (2, (1 << 22) + 17), (130, (1 << 22) + 17)])
 def test_hessian_and_factor_at_the_edges_of_tiles_and_squares(n, d):
     """Sums of d products against torch's: d roundings of 2^-53 of the sum of the magnitudes each way.  H is symmetric to the
     bit.  U: the residual of U^T U (H + lambda I) is n roundings of the condition number at most."""
