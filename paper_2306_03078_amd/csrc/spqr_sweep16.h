@@ -365,6 +365,9 @@ __device__ __forceinline__ void block_tests(Sweep16Lds<B1>& S, const SweepArgs& 
 // got its update at once), and the LDS reads of the next column's row of H^ic.  (As the compiler orders it, every column first takes
 // the updates of all columns before it, one after the other, and then waits for its reads: 11200 clocks a block of 16 columns
 // with the second level, 7300 so.)
+//
+// An error of exactly 0, of a row of zeros or of weights that their codes meet, stays on this path, its sign set by hand: 4096^2 with a
+// row of zeros in every workgroup 3.5 ms, as without, 5.1 when zeros were taken again with true divisions.
 template <int B1>
 __device__ __forceinline__ bool block_columns(Sweep16Lds<B1>& S, double w_top, int ib, int h0, int par, int lane, double s_hat, double z_hat,
                                               double (*esb)[kRows16]) {
@@ -374,8 +377,11 @@ __device__ __forceinline__ bool block_columns(Sweep16Lds<B1>& S, double w_top, i
   const f64x2* diag = S.diag + ib + h0;
   const int kept = (int)~(S.om[par][r] >> h0);
   const Divisor ds = divisor_of(s_hat);
-  uint32_t worst = divisor_in_range(s_hat) ? 0u : ~0u;   // of |x|, as the distance of its high word above 2^-300
-  constexpr uint32_t kLow = (1023u - 300u) << 20, kSpan = 599u << 20;      // to 2^299: then v is below 2^300 too (s_hat (q - z_hat) is small)
+  // of |x|: its high word, the lowest bit set where the low word is not 0, less 1: a zero is -1, the largest unsigned and the least signed
+  uint32_t lowest = divisor_in_range(s_hat) ? ~0u : 0u;
+  int highest = -1;
+  const uint32_t one = (uint32_t)fresh_s(1);             // (min with a constant 1 becomes a comparison, a wait and a selection)
+  constexpr uint32_t kLow = (1023u - 300u) << 20, kHigh = (1023u + 299u) << 20;      // 2^299: then v is below 2^300 too (s_hat (q - z_hat) is small)
   double w[HB];
 #pragma unroll
   for (int c = 0; c < HB; ++c) w[c] = S.wsb[ib + h0 + c][r];
@@ -438,13 +444,18 @@ __device__ __forceinline__ bool block_columns(Sweep16Lds<B1>& S, double w_top, i
     SPQR_STEP(const double x = v - d);
     SPQR_STEP(t = x * lo);
     SPQR_STEP(t = __builtin_fma(x, hi, t));
-    const uint32_t high = (uint32_t)(__builtin_bit_cast(uint64_t, x) >> 32) & 0x7FFFFFFFu;
-    const uint32_t one = (uint32_t)__builtin_amdgcn_sbfe(kept, c, 1) & 0x3FF00000u;
+    const uint32_t high = (uint32_t)(__builtin_bit_cast(uint64_t, x) >> 32), low = (uint32_t)__builtin_bit_cast(uint64_t, x);
+    const uint32_t size = ((high & 0x7FFFFFFFu) | min(low, one)) - 1u;
+    const uint32_t sign = (high ^ (uint32_t)(__builtin_bit_cast(uint64_t, hi) >> 32)) & 0x80000000u;    // (divide() may lose a zero's)
+    const uint32_t keep = (uint32_t)__builtin_amdgcn_sbfe(kept, c, 1);
     SPQR_STEP(d = __builtin_fma(-t, at(c, c), x));
     SPQR_STEP(t = __builtin_fma(d, hi, t));
-    worst = max(worst, high - kLow);
+    lowest = min(lowest, size);
+    highest = max(highest, (int)size);
     qs[c / 4] |= (uint32_t)q << (8 * (c % 4));
-    SPQR_STEP(const double ec = t * __builtin_bit_cast(double, (uint64_t)one << 32));
+    const uint64_t tb = __builtin_bit_cast(uint64_t, t);
+    const uint32_t ec_low = (uint32_t)tb & keep, ec_high = ((uint32_t)(tb >> 32) & keep & 0x7FFFFFFFu) | sign;
+    SPQR_STEP(const double ec = __builtin_bit_cast(double, (uint64_t)ec_high << 32 | ec_low));
     esb[ib + h0 + c][r] = ec;                            // (the same from all four groups)
 #pragma unroll
     for (int rest = 0; rest < 2 * owed; ++rest) fill();
@@ -453,7 +464,7 @@ __device__ __forceinline__ bool block_columns(Sweep16Lds<B1>& S, double w_top, i
     before = ec;
 #undef SPQR_STEP
   });
-  if (__any(worst > kSpan)) return false;
+  if (__any(lowest < kLow || highest > (int)kHigh)) return false;
   if (lane < kRows16) {
 #pragma unroll
     for (int k = 0; k < HB / 4; ++k) S.q[par][r][h0 / 4 + k] = qs[k];

@@ -20,7 +20,8 @@
 struct Dim { int x; };
 static Dim threadIdx, blockIdx;
 static int min(int a, int b) { return a < b ? a : b; }
-static uint32_t max(uint32_t a, uint32_t b) { return a > b ? a : b; }
+static uint32_t min(uint32_t a, uint32_t b) { return a < b ? a : b; }
+static int max(int a, int b) { return a > b ? a : b; }
 
 struct Range { const char* at; size_t bytes; };
 static Range U_range, W_range;                 // never read: addresses only

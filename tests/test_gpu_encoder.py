@@ -282,3 +282,34 @@ def test_sweep_outside_the_prepared_divisors_bit_exact(E, kind, b1, b2, m, n, ta
     if kind == "huge":                                # the largest magnitudes round to infinity as stored outlier values
         assert np.isinf(np.asarray(ref.val, dtype=np.float64)).any()
     _compare_exact(got, ref)
+
+
+# exact zeros of either sign: rows and columns of them, weights on the grid of their codes, with H^ic that leaves them alone and that does not
+@pytest.mark.parametrize("kind,b1,b2,m,n,tau", [
+    ("rows", 16, 16, 48, 400, 1.0), ("rows", 32, 16, 32, 288, 1.0), ("rows", 8, 2, 18, 136, float("inf")), ("dead", 16, 16, 32, 272, 1.0),
+    ("dead", 4, 4, 20, 260, 1.0), ("grid", 16, 8, 40, 272, 1e-3), ("grid", 32, 16, 32, 160, 1e-3), ("grid", 8, 16, 16, 136, 1e-3),
+    ("subnormal", 16, 16, 32, 272, 1.0), ("subnormal", 8, 4, 20, 264, 1.0)])
+def test_sweep_of_exact_zeros_bit_exact(E, kind, b1, b2, m, n, tau):
+    rng = np.random.default_rng(m + n + b1 + b2)
+    W = rng.normal(0, 0.05, (m, n))
+    W[rng.random((m, n)) < 0.02] *= 6.0
+    U = np.triu(rng.normal(0, 0.3 / np.sqrt(n), (n, n)), 1) + np.eye(n)
+    U *= 0.01 * (0.5 + rng.random((n, 1)))
+    if kind == "rows":
+        W[::3] = 0.0
+    elif kind == "dead":
+        U[:, ::3] = np.diag(U.diagonal())[:, ::3]
+        W[:, ::3] *= 0.0                              # zeros of both signs
+        U[5] *= -1.0
+    elif kind == "grid":
+        W = np.round(W * 16) / 16
+        U = np.diag(0.01 * np.where(rng.random(n) < 0.5, -1.0, 1.0))
+    else:
+        W[::3] *= 2.0 ** -1040
+        W[1::3, ::5] = 0.0
+    with np.errstate(all="ignore"):
+        ref = enc.spqr_quantize(W, U, 3, b1, b2, tau)
+    got = E.spqr_quantize(dev(W), dev(U), 3, b1, b2, tau)
+    for a in (got, ref):                              # the least of zeros of both signs: which of them a minimum returns is not said
+        a.z_z = np.where(np.asarray(a.z_z).view(np.uint16) == 0x8000, np.uint16(0), np.asarray(a.z_z).view(np.uint16))
+    _compare_exact(got, ref)
