@@ -21,6 +21,7 @@
 #include <utility>
 
 #include "../../include/spqr_encode.h"
+#include "spqr_test_hooks.h"
 
 namespace spqr_enc {
 
@@ -426,6 +427,24 @@ hipError_t launch_sweep16(int m, hipStream_t st, const SweepArgs& a) {
   return hipGetLastError();
 }
 
+// 16 rows per workgroup where a tile has no more; 64 rows, which the tiles of 32 and 64 rows need, take four to five times as long for
+// four times the rows.  ms with 64 and with 16 rows a workgroup, beta1 = beta2 = 16, 1 % outliers (the time of either is a staircase of
+// rounds of 256 workgroups): 4096^2 17.7 and 3.5, 5120^2 25.4 and 10.2, 8192 x 4096 17.8 and 7.3, 11008 x 4096 18.0 and 10.8,
+// 16384 x 2048 6.8 and 4.9, 32768 x 1024 5.4 and 4.0.
+// Only where there are few columns behind a block, and its tests are little beside its chain (narrow blocks) or there are none, is a
+// round of 64 rows as short as `half_rounds` / 2 of 16.  us with 64 and 16 rows, so many rounds of either: beta1 = 4: 12288 x 256 (1, 3)
+// 457 and 581, 16384 x 1024 (1, 4) 2650 and 3210, 20480 x 1024 (2, 5) 4992 and 3755; beta1 = 8, 16384 x 512 (1, 4) 950 and 1048; no tests: beta1 = 4, 8192 x 64 (1, 2)
+// 88 and 102, 8192 x 128 162 and 169; beta1 = 8, 20480 x 64 (2, 5) 157 and 171, 12288 x 256 (1, 3) 297 and 308; beta1 = 16, 16384 x 256 (1, 4)
+// 314 and 378, 16384 x 512 680 and 748, 12288 x 512 16 rows 15 % faster, 16384 x 1024 13 %; beta1 = 32, 16384 x 256 382 and 490, 12288 x 128 even.
+static int sweep_rows(int m, int n, int beta1, int beta2, bool tests) {
+  const int rounds16 = (m + 256 * kRows16 - 1) / (256 * kRows16), rounds64 = (m + 256 * kRows - 1) / (256 * kRows);
+  int half_rounds = 0;                       // (0: 16 rows however many)
+  if (beta1 == 4) half_rounds = n > 1024 ? 0 : (n > 768 ? 6 : (tests || n > 64 ? 4 : 3));
+  else if (beta1 == 8) half_rounds = n > 512 ? 0 : (tests || n > 256 ? 6 : (n > 64 ? 5 : 4));
+  else if (!tests) half_rounds = n > 512 ? 0 : (n > (beta1 == 16 ? 64 : 128) ? 6 : 5);
+  return beta2 > kRows16 || (half_rounds > 0 && 2 * rounds16 > half_rounds * rounds64) ? kRows : kRows16;
+}
+
 }  // namespace spqr_enc
 
 extern "C" {
@@ -461,16 +480,7 @@ int spqr_quantize(const double* W, const double* Hic, int32_t m, int32_t n, int3
   a.w_top = (double)((1 << w_bits) - 1); a.s_top = (double)((1 << s_bits) - 1); a.z_top = (double)((1 << z_bits) - 1);
   a.tau = tau;
   a.out = *out;
-  // 16 rows per workgroup where a tile has no more, in place on W_final where the caller wants it; 64 rows, which the tiles of 32 and 64
-  // rows need, take four to five times as long for four times the rows.  ms with 64 and with 16 rows a workgroup,
-  // beta2 = 16, 1 % outliers (the time of either is a staircase of rounds of 256 workgroups): 4096^2 17.7 and 3.5, 5120^2 25.4 and
-  // 10.2, 8192 x 4096 17.8 and 7.3, 11008 x 4096 18.0 and 10.8, 16384 x 2048 6.8 and 4.9, 32768 x 1024 5.4 and 4.0.  Only where blocks are
-  // narrow and there are few columns behind them, so that a block's tests and chain are all there is, are four rounds of 16 rows (three
-  // with beta1 = 4) no faster than one of 64: beta1 = 8, 16384 rows: 256 columns 0.49 and 0.54, 512 0.99 and 1.04, 1024 2.44 and 2.02;
-  // beta1 = 4: 12288 x 256 0.49 and 0.60, 16384 x 1024 2.76 and 3.04.
-  const int rounds16 = (m + 256 * kRows16 - 1) / (256 * kRows16), rounds64 = (m + 256 * kRows - 1) / (256 * kRows);
-  const bool narrow = beta1 <= 8 && n <= 4096 / beta1 && rounds16 > (beta1 == 4 ? 2 : 3) * rounds64;
-  if (beta2 <= kRows16 && !narrow) {
+  if (sweep_rows(m, n, beta1, beta2, tau < INFINITY) == kRows16) {         // in place on W_final where the caller wants it
     if (out->W_final) a.Wt = out->W_final;
     hipError_t e = hipSuccess;
     switch (beta1) {
@@ -501,6 +511,8 @@ int spqr_quantize(const double* W, const double* Hic, int32_t m, int32_t n, int3
   hipLaunchKernelGGL(prefix_kernel, dim3(1), dim3(1024), 0, st, out->row_ptr, m);
   return hipGetLastError() == hipSuccess ? SPQR_OK : SPQR_ERR_HIP;
 }
+
+int spqr_sweep_rows(int m, int n, int beta1, int beta2, int tests) { return spqr_enc::sweep_rows(m, n, beta1, beta2, tests != 0); }
 
 int spqr_gather_outliers(const uint8_t* outlier_mask, const uint16_t* outlier_val, const int32_t* row_ptr,
                          int32_t m, int32_t n, uint16_t* col_idx, uint16_t* val, void* stream) {

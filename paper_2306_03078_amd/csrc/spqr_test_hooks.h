@@ -55,6 +55,10 @@ int spqr_batch_route(int m, int n, int64_t nnz, int max_row_nnz, int has_perm, i
  * 4096 entries (the others follow).  Returns the number of slots the scratch holds, or an SPQR_ERR_* code. */
 int64_t spqr_sort_ranges(const int32_t* row_ptr, int m, int64_t nnz, int rows, int32_t* ranges);
 
+/* Rows per workgroup, 16 or 64, of spqr_quantize's sweep of an m x n layer in blocks of beta1 columns and tiles of beta2 rows, with
+ * outlier tests (tau finite) or without. */
+int spqr_sweep_rows(int m, int n, int beta1, int beta2, int tests);
+
 #ifdef __cplusplus
 }
 #endif

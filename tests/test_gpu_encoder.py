@@ -313,3 +313,17 @@ def test_sweep_of_exact_zeros_bit_exact(E, kind, b1, b2, m, n, tau):
     for a in (got, ref):                              # the least of zeros of both signs: which of them a minimum returns is not said
         a.z_z = np.where(np.asarray(a.z_z).view(np.uint16) == 0x8000, np.uint16(0), np.asarray(a.z_z).view(np.uint16))
     _compare_exact(got, ref)
+
+
+# tall layers on either side of the line from where 64 rows a workgroup are faster, ragged last workgroups
+@pytest.mark.parametrize("b1,b2,m,n,tau,rows", [
+    (4, 16, 4112, 64, float("inf"), 64), (4, 8, 4112, 68, float("inf"), 16), (8, 4, 8196, 64, float("inf"), 64), (16, 16, 8208, 64, float("inf"), 64),
+    (16, 8, 12296, 80, float("inf"), 64), (32, 16, 8208, 96, float("inf"), 64), (32, 8, 12272, 160, float("inf"), 16), (4, 4, 8196, 68, 20.0, 64)])
+def test_sweep_of_tall_layers_bit_exact(E, b1, b2, m, n, tau, rows):
+    assert E._lib().spqr_sweep_rows(m, n, b1, b2, int(tau < float("inf"))) == rows
+    rng = np.random.default_rng(m + n)
+    W = rng.normal(0, 0.05, (m, n))
+    W[rng.random((m, n)) < 0.02] *= 6.0
+    U = np.triu(rng.normal(0, 0.3 / np.sqrt(n), (n, n)), 1) + np.eye(n)
+    U *= 0.01 * (0.5 + rng.random((n, 1)))
+    _compare_exact(E.spqr_quantize(dev(W), dev(U), 3, b1, b2, tau), enc.spqr_quantize(W, U, 3, b1, b2, tau))

@@ -33,7 +33,7 @@ def test_library_exports_every_declared_symbol():
             "spqr_permute_columns", "spqr_permute_symmetric"} == enc
     names = names | enc
     hooks = _declared(os.path.join(ROOT, "paper_2306_03078_amd", "csrc", "spqr_test_hooks.h"))
-    assert hooks == {"spqr_plan_batch", "spqr_plan_grouped", "spqr_sort_ranges", "spqr_batch_route", "spqr_plan_prompt"}
+    assert hooks == {"spqr_plan_batch", "spqr_plan_grouped", "spqr_sort_ranges", "spqr_batch_route", "spqr_plan_prompt", "spqr_sweep_rows"}
     lib = C.CDLL(P.library_path())
     for nm in sorted(names | hooks):
         assert hasattr(lib, nm), nm
