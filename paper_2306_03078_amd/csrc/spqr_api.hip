@@ -271,7 +271,7 @@ extern "C" int spqr_plan_batch(int count, const int32_t* m, const int32_t* n, co
   if (rc) return rc;
   if (!plan) return SPQR_ERR_NULL;
   if (b < 1 || b > 16 || !spqr::mfma_has_instance(D[0].g)) return SPQR_ERR_PARAM;
-  return spqr::plan_batch_hook(D, count, b, &plan[0], &plan[1], &plan[2]);
+  return spqr::plan_batch_hook(D, count, b, plan);
 }
 
 extern "C" int spqr_plan_prompt(int count, const int32_t* m, const int32_t* n, const int32_t* max_row_nnz, const int64_t* nnz,

@@ -83,7 +83,7 @@ size_t mfma_workspace_bound(const DevMatrix* As, int count, int b, bool fused);
 hipError_t static_workspace(Workspace* ws);
 // The launch plan of a slice of b vectors (host arithmetic only): units of 16 tile columns per split, splits, workgroups
 // that share a split's outliers.  Returns the units of the matrix.
-int plan_batch_hook(const DevMatrix* As, int count, int b, int* per, int* splits, int* shares);
+int plan_batch_hook(const DevMatrix* As, int count, int b, int* plan);
 
 // Prompt-sized batches (spqr_prompt.hip) and large batches through a dense binary16 copy of the matrix
 // (spqr_prefill.hip) on the library's scratch or the caller's workspace.  hipErrorNotSupported: no scratch of that size to

@@ -760,26 +760,40 @@ static BatchPlan plan_batch(const DevMatrix* As, int count, int b) {
 
 // The units of a plan's splits.  Where every CU gets two workgroups that do both parts, the first takes the dense part first and the
 // second the outliers (batch_group_body), and the second of a CU lives longer: us of a workgroup by its units, of 17920 x 6656 and
-// three of 6656^2, Zipf rows, 4 and 16 vectors: 9.4 + 4.2 u and 12.2 + 5.2 u.  So the splits whose workgroups come first get more.
-// Three of 6656^2, 4 vectors, units 5 5 5 5 5 1 -> 5 5 5 4 4 3: 46.5 -> 43.1 us; 17920 x 6656, 16 vectors, 4 4 4 4 4 4 2 -> 5 5 5 3 3 3 2:
-// 42.3 -> 40.8, the best of 35 ways to share them out each.
+// three of 6656^2, 16 x 16 tiles, Zipf rows, 4 and 16 vectors: 9.4 + 4.2 u and 12.2 + 5.2 u; a unit of 32 x 8 tiles is half as wide.  So the
+// splits whose workgroups come first get more where that shortens the longest life by 2 us (less is not seen: 3 3 3 3 3 -> 5 5 2 2 1
+// cost up to 9 %, 2 of 8 x 32 tiles -> 3 and 1 3 to 8 %; those have no more than 3 units a piece of XT and stay even).
+// Three of 6656^2, 4 vectors, units 5 5 5 5 5 1 -> 5 5 5 4 4 3: 44.3 -> 41.1 us; 17920 x 6656, 16 vectors, 4 4 4 4 4 4 2 -> 5 5 5 3 3 3 2:
+// 41.2 -> 39.3.  262 layers and sets of layers against even splits: 7.5 % faster to 2 % slower, on average 2.4, 2.1 and 2.4 % faster (16 x 16
+// along the columns and the rows, 32 x 8) where the widths differ.
 static Shares batch_shares(const BatchPlan& p, const DevMatrix* As, int count) {
   const Geometry& g = As[0].g;
   const int units = batch_units(g), chunk = 1536 / (kUnitTiles * g.tile_cols), wgs = p.groups * p.splits, lead = kCUs / p.groups;
-  const Shares even = {p.per, 0, 0};
+  Shares best = {p.per, 0, 0};
   int64_t nnz = 0;
   for (int i = 0; i < count; ++i) nnz += As[i].nnz;
-  if (nnz == 0 || p.shares > 0 || wgs <= kCUs || wgs > 2 * kCUs || lead < 1 || lead >= p.splits || option(SPQR_OPT_BATCH_STEPS) >= 1) return even;
-  Shares s = {(int)(((float)units - 0.67f * (float)lead) / (1.24f * (float)lead + (float)(p.splits - lead)) + 0.5f), lead, 0};
-  if (s.per < 1) return even;
-  s.more = std::max(0, (units - p.splits * s.per + lead - 1) / lead);
-  const bool covered = s.first(p.splits) >= units && s.first(p.splits - 1) < units;        // all of them, no split empty
-  return covered && s.per + s.more <= std::max(chunk, p.per) ? s : even;                   // (one piece of XT more would cost more)
+  if (nnz == 0 || p.shares > 0 || wgs <= kCUs || wgs > 2 * kCUs || lead < 1 || lead >= p.splits || g.tile_cols == 32 || option(SPQR_OPT_BATCH_STEPS) >= 1)
+    return best;
+  const float wide = (float)g.tile_cols / 16.f;
+  auto longest = [&](const Shares& s) {      // of a first one and of the widest that comes second
+    return std::max(9.4f + 4.2f * wide * (float)(s.per + s.more), 12.2f + 5.2f * wide * (float)std::min(s.per, units - s.first(lead)));
+  };
+  float least = longest(best) - 2.f;
+  for (int per = p.per; per >= 1; --per) {
+    const Shares s = {per, lead, std::max(0, (units - p.splits * per + lead - 1) / lead)};
+    const bool covered = s.first(p.splits) >= units && s.first(p.splits - 1) < units;      // all of them, no split empty
+    if (!covered || per + s.more > std::max(chunk, p.per) || longest(s) >= least) continue;   // (one piece of XT more would cost more)
+    best = s;
+    least = longest(s);
+  }
+  return best;
 }
 
-int plan_batch_hook(const DevMatrix* As, int count, int b, int* per, int* splits, int* shares) {
+int plan_batch_hook(const DevMatrix* As, int count, int b, int* plan) {
   const BatchPlan p = plan_batch(As, count, b);
-  *per = p.per; *splits = p.splits; *shares = p.shares;
+  const Shares s = batch_shares(p, As, count);
+  plan[0] = p.per; plan[1] = p.splits; plan[2] = p.shares;
+  plan[3] = s.per; plan[4] = s.lead; plan[5] = s.more;
   return batch_units(As[0].g);
 }
 

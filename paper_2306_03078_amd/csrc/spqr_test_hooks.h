@@ -13,8 +13,9 @@ extern "C" {
 
 /* Launch plan of a slice of b <= 16 vectors on the matrix-core path of spqr_gemm_smallbatch (count = 1) or of
  * spqr_gemm_fused for matrices m[i] x n[0] of one format (layout 1, 3-bit statistic codes) with nnz[i] outliers and the
- * hint max_row_nnz[i]; host arithmetic only, no device is touched.  plan[0..2] = units of 16 tile columns per split,
- * splits, workgroups that share a split's outliers beside its dense one (0: none).  Returns the units of the matrix, or
+ * hint max_row_nnz[i]; host arithmetic only, no device is touched.  plan[0..2] = units of 16 tile columns per split as the plan
+ * prices them, splits, workgroups that share a split's outliers beside its dense one (0: none); plan[3..5] = the widths the launch
+ * gives them: units of a split, how many of the first have more, how many units more.  Returns the units of the matrix, or
  * an SPQR_ERR_* code (SPQR_ERR_PARAM also for a format without that path). */
 int spqr_plan_batch(int count, const int32_t* m, const int32_t* n, const int32_t* max_row_nnz, const int64_t* nnz, int w_bits,
                     int beta1, int beta2, int group_axis, int b, int32_t* plan);

@@ -779,26 +779,31 @@ def test_matrix_core_batch_path_without_outliers_and_sparse_only(P, monkeypatch)
     assert max(rel_l2(Yg[k], refg[k]) for k in range(8)) <= REL_L2
 
 
-# more for the splits that come first: 3 3 3 1 1 1 units (even: 2 each) with a ragged last group of rows, 4 2 2 (3 3 2)
-@pytest.mark.parametrize("w,b1,b2,axis,m,n,b,per", [(3, 8, 32, 1, 8312, 6144, 16, 2), (4, 16, 16, 1, 33008, 2048, 4, 3)])
-def test_matrix_core_splits_of_unequal_width(P, w, b1, b2, axis, m, n, b, per):
+# more for the splits that come first, of one matrix and of several in one launch, ragged last groups of rows: 5 3 3 units (even: 4 4 3),
+# 6 6 5 5 5 (6 6 6 6 3), 5 5 5 4 4 3 (5 5 5 5 5 1), 8 6 6 (7 7 6)
+@pytest.mark.parametrize("w,b1,b2,axis,ms,n,b,structure", [
+    (4, 16, 16, 0, [32816], 2576, 16, "cols64"), (4, 8, 32, 0, [24864], 3336, 16, "cols64"), (4, 16, 16, 1, [6656, 6640, 6624], 6656, 4, "zipf"),
+    (3, 8, 32, 0, [16448, 16512], 2456, 4, "cols64")])
+def test_matrix_core_splits_of_unequal_width(P, w, b1, b2, axis, ms, n, b, structure):
     """Against the same kernel with every split as wide as the next: the same weights and products, so the results differ by the
     order of binary32 sums alone, a few roundings of 2^-24 of the largest partial sum each; and one vector against the batch-1 kernel
     (u_j or the weights rounded to binary16: 2.1e-4 each)."""
-    f = synth.make_matrix(m, n, w_bits=w, beta1=b1, beta2=b2, group_axis=axis, outlier_rate=0.02, outlier_structure="cols64", seed=(91, m))
-    A = P.SpQRMatrix.from_logical(f)
-    X = dev(synth.make_x(n, b, seed=(92, m)))
+    from test_host_pack import _plan_batch
+    fs = [synth.make_matrix(m, n, w_bits=w, beta1=b1, beta2=b2, group_axis=axis, outlier_rate=0.02, outlier_structure=structure, seed=(91, m)) for m in ms]
+    As = [P.SpQRMatrix.from_logical(f) for f in fs]
+    _, per, splits, shares, _, lead, more = _plan_batch(ms, n, [int(A.val.numel()) for A in As], [int(A.max_row_nnz) for A in As], w, b1, b2, axis, b, True)
+    assert shares == 0 and 0 < lead < splits and more > 0
+    X = dev(synth.make_x(n, b, seed=(92, ms[0])))
+    product = lambda: [y.cpu().numpy().astype(np.float64) for y in ([P.spqr_gemm_smallbatch(As[0], X)] if len(As) == 1 else P.spqr_gemm_fused(As, X))]
     P.spqr_set_option(P.SPQR_OPT_BATCH_PATH, P.SPQR_BATCH_PATH_MATRIX)
-    got = P.spqr_gemm_smallbatch(A, X).cpu().numpy().astype(np.float64)
-    again = P.spqr_gemm_smallbatch(A, X).cpu().numpy()
+    got, again = product(), product()
     P.spqr_set_option(P.SPQR_OPT_BATCH_STEPS, per)
     P.spqr_set_option(P.SPQR_OPT_BATCH_SHARES, 1)
-    even = P.spqr_gemm_smallbatch(A, X).cpu().numpy().astype(np.float64)
+    even = product()
     P.spqr_set_option(P.SPQR_OPT_BATCH_STEPS, 0)
     P.spqr_set_option(P.SPQR_OPT_BATCH_SHARES, 0)
-    assert np.array_equal(got, again.astype(np.float64))
-    scale = np.abs(even).max()
-    assert np.abs(got - even).max() <= 2.0 ** -24 * 64 * scale
-    assert np.abs(got - even).max() > 0              # another order of sums: the two do take different splits
-    one = P.spqr_gemv(A, X[0].contiguous()).cpu().numpy()
-    assert rel_l2(got[0], one) <= 6e-4
+    for A, y, y2, e in zip(As, got, again, even):
+        assert np.array_equal(y, y2)
+        assert np.abs(y - e).max() <= 2.0 ** -24 * 64 * np.abs(e).max()
+        assert np.abs(y - e).max() > 0           # another order of sums: the two do take different splits
+        assert rel_l2(y[0], P.spqr_gemv(A, X[0].contiguous()).cpu().numpy()) <= 6e-4
