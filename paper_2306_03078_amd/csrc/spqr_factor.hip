@@ -284,16 +284,19 @@ __device__ __forceinline__ double rsqrt_f64(double x) {
 }
 
 // d -= (s of lane LANE of the row of 16) * m, as one instruction: v_fmac_f64 takes that operand across lanes by itself.  The compiler does
-// not look into the text for the two wait states between a write of `s` and its reading across lanes: bcast_ready() stands between.
-template <int LANE>
+// not look into the text for the two wait states between a write of `s` and its reading across lanes: the first reading after a write
+// (FRESH) waits in its own text; that no later one follows a copy of `s` is looked after by a test, which reads the assembly.
+template <int LANE, bool FRESH>
 __device__ __forceinline__ void fnma_bcast(double& d, double s, double m) {
-  asm volatile("v_fmac_f64_dpp %0, -%1, %2 row_newbcast:%3 row_mask:0xf bank_mask:0xf" : "+v"(d) : "v"(s), "v"(m), "n"(LANE));
+  if constexpr (FRESH)
+    asm volatile("s_nop 1\n\tv_fmac_f64_dpp %0, -%1, %2 row_newbcast:%3 row_mask:0xf bank_mask:0xf" : "+v"(d) : "v"(s), "v"(m), "n"(LANE));
+  else
+    asm volatile("v_fmac_f64_dpp %0, -%1, %2 row_newbcast:%3 row_mask:0xf bank_mask:0xf" : "+v"(d) : "v"(s), "v"(m), "n"(LANE));
 }
-__device__ __forceinline__ void bcast_ready(double& s) { asm volatile("s_nop 1" : "+v"(s)); }
 template <int LANE>
-__device__ __forceinline__ double bcast(double s) {
+__device__ __forceinline__ double bcast(double s) {                  // always the first
   double d;
-  asm volatile("v_mov_b64_dpp %0, %1 row_newbcast:%2 row_mask:0xf bank_mask:0xf" : "=v"(d) : "v"(s), "n"(LANE));
+  asm volatile("s_nop 1\n\tv_mov_b64_dpp %0, %1 row_newbcast:%2 row_mask:0xf bank_mask:0xf" : "=v"(d) : "v"(s), "n"(LANE));
   return d;
 }
 template <int... I, class F> __device__ __forceinline__ void unrolled(std::integer_sequence<int, I...>, F f) { (f(std::integral_constant<int, I>{}), ...); }
@@ -319,26 +322,23 @@ struct Diagonal {
 };
 // The chain: r is row i of the block (what stands right of the diagonal means nothing), v column i of the identity, then of the inverse.
 __device__ __forceinline__ void potrf_chain(double (&r)[16], double (&v)[16]) {
-  bcast_ready(r[0]);
   double y = rsqrt_f64(bcast<0>(r[0]));
   unrolled(std::make_integer_sequence<int, 16>{}, [&](auto column) __attribute__((always_inline)) {
     constexpr int j = decltype(column)::value, updates = 2 * (15 - j), gap = (updates - 1 + 5) / 6;
     v[j] *= y;
     if constexpr (j < 15) {
-      double l = r[j] * y;
-      bcast_ready(l);
+      const double l = r[j] * y;
       // update 2 i of row or column j + 1 + i of r, 2 i + 1 of v
       const auto update = [&](auto from, auto count) __attribute__((always_inline)) {
         unrolled(std::make_integer_sequence<int, decltype(count)::value>{}, [&](auto at) __attribute__((always_inline)) {
           constexpr int u = decltype(from)::value + decltype(at)::value, k = j + 1 + u / 2;
-          if constexpr (u < updates && u % 2 == 0) fnma_bcast<k>(r[k], l, l);
-          if constexpr (u < updates && u % 2 == 1) fnma_bcast<k>(v[k], l, v[j]);
+          if constexpr (u < updates && u % 2 == 0) fnma_bcast<k, u == 0>(r[k], l, l);
+          if constexpr (u < updates && u % 2 == 1) fnma_bcast<k, false>(v[k], l, v[j]);
         });
         __builtin_amdgcn_sched_barrier(0);
       };
 #define SPQR_STEP(n, ...) __VA_ARGS__; update(std::integral_constant<int, 1 + (n)*gap>{}, std::integral_constant<int, gap>{})
       update(std::integral_constant<int, 0>{}, std::integral_constant<int, 1>{});
-      bcast_ready(r[j + 1]);
       SPQR_STEP(0, const double x = bcast<j + 1>(r[j + 1]));
       SPQR_STEP(1, const double y0 = __builtin_amdgcn_rsq(x));      // rsqrt_f64(x)
       SPQR_STEP(2, const double xy = x * y0);
