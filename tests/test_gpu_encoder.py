@@ -327,3 +327,17 @@ def test_sweep_of_tall_layers_bit_exact(E, b1, b2, m, n, tau, rows):
     U = np.triu(rng.normal(0, 0.3 / np.sqrt(n), (n, n)), 1) + np.eye(n)
     U *= 0.01 * (0.5 + rng.random((n, 1)))
     _compare_exact(E.spqr_quantize(dev(W), dev(U), 3, b1, b2, tau), enc.spqr_quantize(W, U, 3, b1, b2, tau))
+
+
+# 64 rows a workgroup with outlier tests, every width of block: tiles of 32 and 64 rows, a last workgroup that is not full, several super-blocks
+@pytest.mark.parametrize("b1,b2,m,n", [(4, 32, 96, 132), (4, 64, 64, 68), (8, 32, 160, 136), (16, 32, 96, 208), (32, 32, 96, 160), (32, 64, 192, 96)])
+def test_sweep_with_64_rows_bit_exact(E, b1, b2, m, n):
+    assert E._lib().spqr_sweep_rows(m, n, b1, b2, 1) == 64
+    rng = np.random.default_rng(m + n + b2)
+    W = rng.normal(0, 0.05, (m, n))
+    W[rng.random((m, n)) < 0.02] *= 6.0
+    U = np.triu(rng.normal(0, 0.3 / np.sqrt(n), (n, n)), 1) + np.eye(n)
+    U *= 0.01 * (0.5 + rng.random((n, 1)))
+    ref = enc.spqr_quantize(W, U, 3, b1, b2, 20.0)
+    assert 0 < ref.row_ptr[-1] < m * n
+    _compare_exact(E.spqr_quantize(dev(W), dev(U), 3, b1, b2, 20.0), ref)

@@ -109,19 +109,20 @@ def test_permutation_wider_than_the_room_of_the_products(P):
 
 
 def test_sweep_is_the_same_on_both_row_splits(P):
-    """Rows are independent outside their tile: the first rows of a layer too tall for 16 rows per workgroup come out bit
+    """Rows are independent outside their tile: the first rows of a layer so tall that it takes 64 rows per workgroup come out bit
     for bit as when they are a layer of their own, which takes 16 rows per workgroup."""
     import torch
     import paper_2306_03078_amd.encode_binding as E
-    for b1, b2, n in ((16, 16, 160), (8, 2, 72), (32, 8, 128), (4, 16, 68)):
-        m = 4096 + 16
+    for b1, b2, n, m, tau in ((16, 16, 160, 12304, float("inf")), (8, 2, 72, 12304, 5.0), (32, 8, 128, 8208, float("inf")), (4, 16, 68, 8208, 5.0)):
+        rows_of = lambda rows: E._lib().spqr_sweep_rows(rows, n, b1, b2, int(tau < float("inf")))
+        assert rows_of(m) == 64 and rows_of(4096) == rows_of(48) == 16
         W, _ = synth.make_quantizer_problem(7, m, n, 8)
         rng = np.random.default_rng(8)
         U = np.triu(rng.normal(size=(n, n)) * 0.02, 1) + np.diag(0.01 + 0.01 * rng.random(n))
         Wd, Ud = torch.from_numpy(W).to("cuda:0"), torch.from_numpy(U).to("cuda:0")
-        tall = E.spqr_quantize_device(Wd, Ud, 3, b1, b2, 5.0)
+        tall = E.spqr_quantize_device(Wd, Ud, 3, b1, b2, tau)
         for rows in (4096, 48):
-            own = E.spqr_quantize_device(Wd[:rows].contiguous(), Ud, 3, b1, b2, 5.0)
+            own = E.spqr_quantize_device(Wd[:rows].contiguous(), Ud, 3, b1, b2, tau)
             for k in ("Q", "s_q", "z_q", "outlier_mask"):
                 assert torch.equal(own[k], tall[k][:rows]), k
             for k in ("s_s", "z_s", "s_z", "z_z"):
@@ -130,7 +131,7 @@ def test_sweep_is_the_same_on_both_row_splits(P):
             assert torch.equal(own["W_final"].view(torch.int64), tall["W_final"][:rows].view(torch.int64))
             assert torch.equal(own["row_ptr"], tall["row_ptr"][:rows + 1])
         # without W_final the workspace is the working copy
-        none = E.spqr_quantize_device(Wd[:48].contiguous(), Ud, 3, b1, b2, 5.0, want_final=False)
+        none = E.spqr_quantize_device(Wd[:48].contiguous(), Ud, 3, b1, b2, tau, want_final=False)
         assert torch.equal(none["Q"], tall["Q"][:48])
 
 
