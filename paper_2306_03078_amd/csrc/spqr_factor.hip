@@ -481,9 +481,7 @@ __global__ void __launch_bounds__(256) update_kernel(double* __restrict__ L, int
 #pragma unroll
     for (int b = 0; b < 2; ++b) acc.d[a][b] = before.d[a][b] - acc.d[a][b];
   if (at > 0) {                              // workgroup-uniform
-    int pitch = np;
-    asm volatile("" : "+s"(pitch));          // the places anew: kept, they would cost the fourth workgroup of a CU
-    each_element(acc, [&](int r, int c, double v) { blk[(size_t)r * pitch + c] = v; });
+    each_element(acc, [&](int r, int c, double v) { blk[(size_t)r * np + c] = v; });
     return;
   }
   each_element(acc, [&](int r, int c, double v) { S.diagonal.D[r][c] = v; });   // (the product is over: a barrier ends it)
