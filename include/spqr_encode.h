@@ -16,11 +16,12 @@
  *   spqr_gather_outliers   line 19:  the outlier set as CSR arrays, by row, then by column
  *   spqr_act_order, spqr_permute_columns, spqr_permute_symmetric: the activation-order heuristic around it (App. B)
  *
- * Arithmetic: binary64 throughout.  spqr_quantize performs exactly one correctly rounded binary64 operation per
- * step of the algorithm, elementwise, sums and updates in column order, never fused: given the same W, H^ic and
- * parameters its integer outputs (codes, statistic codes, outlier set) and the stored 16-bit values are a pure
- * function of the inputs, reproducible bit for bit.  spqr_hessian and spqr_inverse_cholesky are ordinary
- * floating-point linear algebra (blocked, fused multiply-adds): accurate to rounding, not order-exact.
+ * Arithmetic: binary64 throughout.  spqr_quantize rounds every step of the algorithm (sum, difference, product,
+ * quotient) once, correctly, to binary64, elementwise, sums and updates in column order, no product fused with the sum
+ * behind it: given the same W, H^ic and parameters its integer outputs (codes, statistic codes, outlier set) and the
+ * stored 16-bit values are a pure function of the inputs, reproducible bit for bit.  spqr_hessian and
+ * spqr_inverse_cholesky are ordinary floating-point linear algebra (blocked, fused multiply-adds): accurate to
+ * rounding, not order-exact.
  *
  * Conventions where Alg. 1 is silent or garbled:
  *   - quantize(v, s, z) = min(max(floor(v / s + z + 0.5), 0), 2^bits - 1);
@@ -59,7 +60,7 @@ int spqr_hessian(const double* X, int32_t n, int32_t d, double* H, void* stream)
 /* Scratch of spqr_inverse_cholesky in bytes (two square matrices of n rounded up to 64); 0 if n < 1. */
 size_t spqr_inverse_cholesky_workspace_bytes(int32_t n);
 
-/* Alg. 1 line 3.  H[n][n] row-major, symmetric (the lower triangle is read), Hic[n][n] row-major: the upper
+/* Alg. 1 line 3.  H[n][n] row-major, symmetric (the upper triangle is read), Hic[n][n] row-major: the upper
  * triangular factor with positive diagonal, zeros below it.  H and Hic may not overlap.  workspace: 256-byte
  * aligned, at least spqr_inverse_cholesky_workspace_bytes(n) bytes (SPQR_ERR_WORKSPACE if smaller).  H + lambda I
  * must be positive definite: otherwise Hic holds NaNs (nothing is reported: no synchronisation). */

@@ -2,16 +2,18 @@
 // fit_statistics(), fit_quantizer(), quantize(), dequantize()) and the gathering of the outlier set.
 //
 // Every floating-point step is ONE rounded binary64 operation, in the order the algorithm states, so the integer
-// results do not depend on how the work is spread over the machine: no fused multiply-add (contraction is off
-// for this file), true divisions, sums from left to right.
+// results do not depend on how the work is spread over the machine: no product is fused with a sum (contraction is off
+// for this file), sums go from left to right, quotients are correctly rounded (by the division instructions, or by four fused
+// operations with a prepared divisor, which round the same way).
 //
-// Rows are independent except for the second level of the statistics, which joins beta2 consecutive rows of a
-// column block: a lane owns a row, a workgroup 64 consecutive rows, and the lanes of a tile exchange the
-// minima / maxima of their statistics with cross-lane shuffles.  The workgroup's wavefronts all hold the same 64
-// rows: each computes the block's statistics, codes and errors for itself (identical inputs, identical results:
-// nothing has to be exchanged), they share out the leave-one-out tests of the block's columns and the columns
-// right of the block that receive the error feedback (line 16, the O(m n^2) part).  The working copy of W is
-// column-major, so a wavefront's access to a column is one contiguous run.
+// Rows are independent except for the second level of the statistics, which joins beta2 consecutive rows of a column block.  Two
+// kernels, which sweep_rows() chooses between:
+//   sweep16_kernel (spqr_sweep16.h)  16 rows a workgroup, for tiles of up to 16 rows, which is nearly every layer; row-major
+//   sweep_kernel   64 rows a workgroup, for tiles of 32 and 64 rows and for tall layers of few columns.  A lane owns a row, and the
+//                  lanes of a tile exchange the minima / maxima of their statistics with cross-lane shuffles.  The wavefronts all
+//                  hold the same 64 rows: they share out the leave-one-out tests of a block's columns and the columns right of the
+//                  block that receive the error feedback (line 16, the O(m n^2) part); the first takes the block's own columns.
+//                  The working copy of W is column-major, so a wavefront's access to a column is one contiguous run.
 #pragma clang fp contract(off)
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -25,17 +27,11 @@
 
 namespace spqr_enc {
 
-#ifndef SPQR_SWEEP_WAVES
-#define SPQR_SWEEP_WAVES 16
-#endif
-#ifndef SPQR_SWEEP_PREFETCH
-#define SPQR_SWEEP_PREFETCH 0       // a chunk ahead in registers: pays with 8 wavefronts per workgroup, not with 16 (4 per SIMD hide the loads)
-#endif
-constexpr int kWaves = SPQR_SWEEP_WAVES;     // wavefronts per workgroup of the sweep
+constexpr int kWaves = 16;                   // wavefronts per workgroup of the sweep
 constexpr int kRows = 64;                    // rows per workgroup: one per lane
 
-// binary64 -> binary16, round to nearest even, in one rounding: by way of binary32 rounded to odd (its 24 bits are two more than the
-// 11 of binary16 need, so the second rounding sees what the first one dropped).  A NaN becomes the one quiet NaN.
+// binary64 -> binary16, round to nearest even, in one rounding: by way of binary32 rounded to odd (two bits more than the 11 of
+// binary16 would do, it has 13: the second rounding sees what the first one dropped).  A NaN becomes the one quiet NaN.
 __device__ __forceinline__ uint16_t f64_to_f16_bits(double x) {
   float f = (float)x;
   const double back = (double)f;
@@ -124,9 +120,9 @@ template <int B1> struct SweepLds {
 
 // Line 14 / line 16 for the columns [k_begin, k_end): W[:, k] -= E[:, j] * H^ic[urow0 + j, k] for j = 0 .. rows - 1, in
 // that order, one product and one difference at a time.  esrc[j][lane] is E of column urow0 + j.  Chunks of CB
-// columns are dealt to the wavefronts; a chunk's columns of W and its rows x CB piece of H^ic are requested one
-// chunk ahead; the piece passes through a corner of LDS that belongs to the wavefront, from where every lane reads
-// the same numbers (broadcast reads).  (k_end - k_begin) is a multiple of CB.
+// columns are dealt to the wavefronts; a chunk's columns of W and its rows x CB piece of H^ic are requested when the one before is
+// stored (four wavefronts a SIMD hide the wait: a chunk ahead in registers is no faster); the piece passes through a corner of LDS
+// that belongs to the wavefront, from where every lane reads the same numbers (broadcast reads).  (k_end - k_begin) is a multiple of CB.
 template <int CB>
 __device__ __forceinline__ void feedback(double* __restrict__ Wt, const double* __restrict__ U, int m, int n, int rrow,
                                          bool live, int lane, int wave, int urow0, int rows, int k_begin, int k_end,
@@ -136,7 +132,7 @@ __device__ __forceinline__ void feedback(double* __restrict__ Wt, const double* 
   const int cells = rows * CB;
   int k0 = k_begin + CB * wave;
   if (k0 >= k_end) return;                               // wave-uniform
-  double cur[CB], nxt[CB], ucur[PER], unxt[PER];
+  double cur[CB], ucur[PER];
 #pragma unroll
   for (int q = 0; q < CB; ++q) cur[q] = *reinterpret_cast<const double*>(reinterpret_cast<const char*>(Wt + (size_t)(k0 + q) * m) + roff);
 #pragma unroll
@@ -146,15 +142,6 @@ __device__ __forceinline__ void feedback(double* __restrict__ Wt, const double* 
   }
   for (; k0 < k_end; k0 += CB * kWaves) {                // wave-uniform
     const int k1 = k0 + CB * kWaves < k_end ? k0 + CB * kWaves : k0;   // behind the last chunk: the same one again, unused
-    if (SPQR_SWEEP_PREFETCH) {
-#pragma unroll
-    for (int q = 0; q < CB; ++q) nxt[q] = *reinterpret_cast<const double*>(reinterpret_cast<const char*>(Wt + (size_t)(k1 + q) * m) + roff);
-#pragma unroll
-    for (int p = 0; p < PER; ++p) {
-      const int idx = min(lane + 64 * p, cells - 1);
-      unxt[p] = U[(size_t)(urow0 + idx / CB) * n + k1 + idx % CB];
-    }
-    }
 #pragma unroll
     for (int p = 0; p < PER; ++p) {
       const int idx = lane + 64 * p;
@@ -177,12 +164,7 @@ __device__ __forceinline__ void feedback(double* __restrict__ Wt, const double* 
 #pragma unroll
       for (int q = 0; q < CB; ++q) *reinterpret_cast<double*>(reinterpret_cast<char*>(Wt + (size_t)(k0 + q) * m) + roff) = cur[q];
     }
-    if (SPQR_SWEEP_PREFETCH) {
-#pragma unroll
-      for (int q = 0; q < CB; ++q) cur[q] = nxt[q];
-#pragma unroll
-      for (int p = 0; p < PER; ++p) ucur[p] = unxt[p];
-    } else if (k1 != k0) {
+    if (k1 != k0) {
 #pragma unroll
       for (int q = 0; q < CB; ++q) cur[q] = *reinterpret_cast<const double*>(reinterpret_cast<const char*>(Wt + (size_t)(k1 + q) * m) + roff);
 #pragma unroll
