@@ -763,7 +763,7 @@ static BatchPlan plan_batch(const DevMatrix* As, int count, int b) {
 // three of 6656^2, 16 x 16 tiles, Zipf rows, 4 and 16 vectors: 9.4 + 4.2 u and 12.2 + 5.2 u; a unit of 32 x 8 tiles is half as wide.  So the
 // splits whose workgroups come first get more where that shortens the longest life by 2 us (less is not seen: 3 3 3 3 3 -> 5 5 2 2 1
 // cost up to 9 %, 2 of 8 x 32 tiles -> 3 and 1 3 to 8 %; those have no more than 3 units a piece of XT and stay even).
-// Three of 6656^2, 4 vectors, units 5 5 5 5 5 1 -> 5 5 5 4 4 3: 44.3 -> 41.1 us; 17920 x 6656, 16 vectors, 4 4 4 4 4 4 2 -> 5 5 5 3 3 3 2:
+// Three of 6656^2, 4 vectors, units 5 5 5 5 5 1 -> 5 5 5 4 4 3: 44.5 -> 41.2 us; 17920 x 6656, 16 vectors, 4 4 4 4 4 4 2 -> 5 5 5 3 3 3 2:
 // 41.2 -> 39.3.  262 layers and sets of layers against even splits: 7.5 % faster to 2 % slower, on average 2.4, 2.1 and 2.4 % faster (16 x 16
 // along the columns and the rows, 32 x 8) where the widths differ.
 static Shares batch_shares(const BatchPlan& p, const DevMatrix* As, int count) {

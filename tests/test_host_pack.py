@@ -382,7 +382,7 @@ def test_widths_of_the_layers_that_lost_time():
     assert widths([8384] * 3, 3616, 0.02, 3616, 3, 16, 16, 0, 4) == [3] * 5                          # 5 5 2 2 1: 44.8 -> 48.9 us
     assert widths([12768] * 2, 5024, 0.01, 5024, 3, 16, 16, 0, 4) == [4] * 5                         # 6 6 3 3 2: 39.7 -> 41.8
     assert widths([8768] * 3, 1728, 0.02, 1728, 3, 8, 32, 1, 15) == [2, 2]                           # 3 1: 33.6 -> 36.4
-    assert widths([6656] * 3, 6656, 0.01, 6656, 4, 16, 16, 1, 4) == [5, 5, 5, 4, 4, 3]               # 5 5 5 5 5 1: 44.3 -> 41.1
+    assert widths([6656] * 3, 6656, 0.01, 6656, 4, 16, 16, 1, 4) == [5, 5, 5, 4, 4, 3]               # 5 5 5 5 5 1: 44.5 -> 41.2
     assert widths([13248] * 3, 2464, 0.02, 2464, 3, 16, 16, 0, 6) == [4, 3, 3]                       # 4 4 2: 43.6 -> 38.5
 
 
