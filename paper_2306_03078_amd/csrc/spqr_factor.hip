@@ -449,6 +449,8 @@ __global__ void __launch_bounds__(256) trsm_panel_kernel(double* __restrict__ L,
 // What stands before the chain stays 64 deep: the diagonal block that comes after the next takes what it lacks a launch early, by the
 // last workgroup.  The 63 launches of n = 4096 (warm): 1, 2, 3 and 4 panels at a time 1183, 1130, 1052 and 1146 us
 // (one, two workgroups more of which fit a CU beside the chain than with the inverse in an array of its own: 1214).
+// The whole factor, ms with 2, 3 and 4 at a time: 1024 inputs 0.398, 0.395 and 0.414, 4096 1.99, 1.96 and 2.01, 8192 9.39, 9.11 and 9.02, 11008 21.7,
+// 20.9 and 20.4.
 constexpr int kLag = 3;
 // Tiles of the columns before column c of those of a launch; `rest` block rows are left.
 __host__ __device__ constexpr int tiles_before(int c, int rest) { return c * rest - kLag * (c * (c - 1) / 2); }
@@ -492,7 +494,8 @@ __global__ void __launch_bounds__(256) update_kernel(double* __restrict__ L, int
 // The tiles of one pair of a level, `tiles` a side (a power of two), in such an order that the workgroups that share a CU, every 256th,
 // have much the same to do in all: the depth falls along the columns in step 1 and grows along the rows in step 2, and every other
 // 256 tiles go through them the other way (n = 4096, the last level: 319 and 235 us -> 188 and 205; 163 and 164 with
-// tile_product as it is; the level before, two pairs of 256 tiles: 81 -> 51, counted through the pairs).
+// tile_product as it is; the level before, two pairs of 256 tiles: 81 -> 51, counted through the pairs).  The whole factor without and
+// with it: 2048 inputs the same, 3072 1.37 and 1.29 ms, 8192 9.87 and 9.11, 11008 22.0 and 20.9.
 __device__ __forceinline__ bool other_way(int tiles) { return tiles <= 256 && ((blockIdx.x + tiles * (blockIdx.y + tiles * blockIdx.z)) / 256 & 1); }
 
 // Level with diagonal blocks of `b` rows: pair p joins A = [2pb, 2pb + b) and B = [2pb + b, min(2pb + 2b, np)).
